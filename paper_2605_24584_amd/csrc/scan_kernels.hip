@@ -865,20 +865,23 @@ k_scan_reduce_wide(const ScanArgs A)
 // Phased kernel, PhaseIn::split_blocks: the doubled rows [x cos psi | x sin psi] of the blocks whose rows the downsweeps
 // will read (mode 1: blocks that hold result rows, x injected; mode 2: blocks with more than a few injected rows, x the
 // weights of the result rows), one wavefront per eight rows of a block, row by row; the same products as k_phase_split.
+// Blocks with at most kFewRows result rows are not among them in mode 1: k_scan_down_fewres modulates x itself.  Where the
+// list of the heavy downsweep holds every block in question the kernel walks the list instead of all blocks' flags.
 __global__ void __launch_bounds__(kStreamWaves * 64)
-k_phase_split_blocks(const ScanArgs A)
+k_phase_split_blocks(const ScanArgs A, int from_list)
 {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t part = (int64_t)blockIdx.x * kStreamWaves + wave;       // eight rows of a block per wavefront
-    const int64_t blk = part >> 3;
-    if (blk >= A.blocks) return;
+    const int64_t slot = part >> 3;
     if (part == 0 && lane == 0 && A.pin.whole != nullptr) *A.pin.whole = 0u;       // x2 holds the rows of some blocks only
+    if (from_list ? slot >= (int64_t)A.counters[1] : slot >= A.blocks) return;
+    const int64_t blk = from_list ? (int64_t)lane_u(A.list_both[slot], 0) : slot;
     const int flags = (int)A.blk_flags[blk];
     const int mode = A.pin.split_blocks;
     uint32_t lo, hi;          // ids of the rows of x
     if (mode == 1) {
-        if (!(flags & kFlagRes) || !(flags & kFlagInj)) return;
+        if (!(flags & kFlagRes) || !(flags & kFlagInj) || (flags & (kFlagFewInj | kFlagFewRes)) == kFlagFewRes) return;
         lo = A.inj_lo; hi = A.inj_hi;
     } else {
         if (!(flags & kFlagRes) || !(flags & kFlagInj) || (flags & kFlagFewInj)) return;
@@ -1567,7 +1570,11 @@ k_scan_down_sparse(const ScanArgs A)
 // ---------------------------------------------------------------------------
 constexpr int kFewWaves = 4;
 
-template <bool STRICT>
+// HALVES = 2 (phased kernel, PhaseIn): as in k_scan_reduce_wide a lane owns four columns of both halves and the block's rows of
+// x are read once and modulated on the way in, so that no doubled copy of them has to be written first (the pass that wrote it
+// took 72 us for the 1000 blocks of the projection layer with phases, n = 2^20, k = 1024, batch 256, and this kernel 25 us after it;
+// reading x here takes 20 us, and the pass, left with the blocks that hold more result rows, 5 us).  One slab, no row reduction (only forward problems inject x).
+template <bool STRICT, int HALVES>
 __global__ void __launch_bounds__(kFewWaves * 64)
 k_scan_down_fewres(const ScanArgs A)
 {
@@ -1580,14 +1587,17 @@ k_scan_down_fewres(const ScanArgs A)
     const int flags = (int)A.blk_flags[blk];
     if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes | kFlagFewRes)) return;
     const uint32_t poison = plan_poison(A.counters);
-    const int64_t col0 = ((int64_t)blockIdx.y * 64 + lane) * VEC;
-    const bool col_ok = col0 < A.batch;
-    const float* const base = A.inj + (col_ok ? col0 : 0);
+    const int64_t half = HALVES == 2 ? A.pin.half : 0;
+    const int64_t col0 = ((int64_t)(HALVES == 2 ? 0 : blockIdx.y) * 64 + lane) * VEC;
+    const bool col_ok = col0 < (HALVES == 2 ? half : A.batch);
+    const int64_t ld_in = HALVES == 2 ? A.pin.ldx : A.ld_inj;
+    const float* const base = (HALVES == 2 ? A.pin.x : A.inj) + (col_ok ? col0 : 0);
 
     WideMeta M;
     M.fetch(A, blk, lane);
-    float Fc[VEC], Ec[VEC], Rc[VEC], Gc[VEC];
-    load_block_carries<VEC, STRICT>(A, blk, col0, col_ok, Fc, Ec, Rc, Gc);
+    float Fc[HALVES][VEC], Ec[HALVES][VEC], Rc[HALVES][VEC], Gc[HALVES][VEC];
+#pragma unroll
+    for (int h = 0; h < HALVES; ++h) load_block_carries<VEC, STRICT>(A, blk, col0 + h * half, col_ok, Fc[h], Ec[h], Rc[h], Gc[h]);
     const uint32_t idv = M.live ? M.id : 0xFFFFFFFFu;
     const bool inj = idv >= A.inj_lo && idv < A.inj_hi;
     const uint64_t inj_mask = __ballot(inj);
@@ -1595,6 +1605,9 @@ k_scan_down_fewres(const ScanArgs A)
     const uint64_t hf_mask = __ballot(M.live && M.dl >= 0.0f), hb_mask = __ballot(M.live && M.dr >= 0.0f);
     // decay of the carries to row `lane`
     const float df = expf(-(M.p - M.p_before)), db = expf(-(M.p_after - M.p));
+    // phased: lane l holds the cosine and sine of the phase of row l
+    float cph = 1.0f, sph = 0.0f;
+    if (HALVES == 2 && inj) sincosf(A.pin.psi[idv - A.inj_lo], &sph, &cph);
 
     int rrow[NR]; bool have[NR];
     float wP[NR], wZ[NR];           // lane l: weight of injected row l for result row q
@@ -1607,11 +1620,13 @@ k_scan_down_fewres(const ScanArgs A)
         wP[q] = (have[q] && inj) ? expf(-fabsf(M.p - pr)) : 0.0f;
         wZ[q] = M.p > pr ? wP[q] : (M.p < pr ? -wP[q] : 0.0f);
     }
-    float aP[NR][VEC], aZ[NR][VEC];
+    float aP[HALVES][NR][VEC], aZ[HALVES][NR][VEC];
 #pragma unroll
-    for (int q = 0; q < NR; ++q)
+    for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { aP[q][e] = 0.0f; aZ[q][e] = 0.0f; }
+        for (int q = 0; q < NR; ++q)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { aP[h][q][e] = 0.0f; aZ[h][q][e] = 0.0f; }
 
     {
         v4f buf[2][CH];
@@ -1621,7 +1636,7 @@ k_scan_down_fewres(const ScanArgs A)
                 const int row = c0 + i;
                 const uint32_t id = lane_u(idv, row);
                 const int64_t r = ((inj_mask >> row) & 1ull) ? (int64_t)(id - A.inj_lo) : 0;
-                dst[i] = *reinterpret_cast<const v4f*>(base + r * A.ld_inj);
+                dst[i] = *reinterpret_cast<const v4f*>(base + r * ld_in);
             }
         };
         auto fold = [&](int c0, const v4f* src) {
@@ -1629,18 +1644,27 @@ k_scan_down_fewres(const ScanArgs A)
             for (int i = 0; i < CH; ++i) {
                 const int row = c0 + i;
                 const uint32_t keep = ((inj_mask >> row) & 1ull) ? 0xFFFFFFFFu : 0u;
-                float x[VEC];
+                float x[HALVES][VEC];
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) x[e] = __uint_as_float(__float_as_uint(src[i][e]) & keep);
+                for (int e = 0; e < VEC; ++e) x[0][e] = __uint_as_float(__float_as_uint(src[i][e]) & keep);
+                if (HALVES == 2) {
+                    const float cr = lane_f(cph, row), sr = lane_f(sph, row);
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) { const float v = x[0][e]; x[0][e] = v * cr; x[HALVES - 1][e] = v * sr; }
+                }
 #pragma unroll
                 for (int q = 0; q < NR; ++q) {
                     const float a = lane_f(wP[q], row);
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e) aP[q][e] += a * x[e];
+                    for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) aP[h][q][e] += a * x[h][e];
                     if (STRICT) {
                         const float z = lane_f(wZ[q], row);
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e) aZ[q][e] += z * x[e];
+                        for (int h = 0; h < HALVES; ++h)
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) aZ[h][q][e] += z * x[h][e];
                     }
                 }
             }
@@ -1653,7 +1677,7 @@ k_scan_down_fewres(const ScanArgs A)
         }
     }
 
-    const bool want_red = STRICT && A.out_red != nullptr;
+    const bool want_red = STRICT && HALVES == 1 && A.out_red != nullptr;
     const int64_t res_rows = (int64_t)A.res_hi - (int64_t)A.res_lo;
 #pragma unroll
     for (int q = 0; q < NR; ++q) {
@@ -1663,24 +1687,27 @@ k_scan_down_fewres(const ScanArgs A)
         const bool seen_f = (hf_mask & ((2ull << r) - 1ull)) != 0;   // a run head at or before row r inside the block
         const bool seen_b = (hb_mask >> r) != 0;                     // ... at or after it, seen from the right
         const int64_t rr = (int64_t)lane_u(idv, r) - (int64_t)A.res_lo;
-        float P[VEC], Z[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const float Fj = kf * Fc[e], Rj = kb * Rc[e];
-            P[e] = taint(aP[q][e] + Fj + Rj, poison);
-            Z[e] = taint(aZ[q][e] + ((seen_b ? Rj : Gc[e]) - (seen_f ? Fj : Ec[e])), poison);
-        }
-        if (col_ok) {
-            if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0, Z);
-        }
-        if (want_red) {
-            float wrow[VEC];
-            load_vec_or_zero<VEC>(wrow, A.w, rr * A.ld_w + col0, col_ok);
-            float acc = 0.0f;
+        for (int h = 0; h < HALVES; ++h) {
+            float P[VEC], Z[VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) acc += wrow[e] * Z[e];
-            emit_row_sum(A, acc, 64, lane, true, rr, res_rows);
+            for (int e = 0; e < VEC; ++e) {
+                const float Fj = kf * Fc[h][e], Rj = kb * Rc[h][e];
+                P[e] = taint(aP[h][q][e] + Fj + Rj, poison);
+                Z[e] = taint(aZ[h][q][e] + ((seen_b ? Rj : Gc[h][e]) - (seen_f ? Fj : Ec[h][e])), poison);
+            }
+            if (col_ok) {
+                if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0 + h * half, P);
+                if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0 + h * half, Z);
+            }
+            if (want_red) {
+                float wrow[VEC];
+                load_vec_or_zero<VEC>(wrow, A.w, rr * A.ld_w + col0, col_ok);
+                float acc = 0.0f;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc += wrow[e] * Z[e];
+                emit_row_sum(A, acc, 64, lane, true, rr, res_rows);
+            }
         }
     }
 }
@@ -2028,8 +2055,9 @@ k_phase_merge_blocks(const ScanArgs A)
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t part = (int64_t)blockIdx.x * kStreamWaves + wave;       // eight rows of a block per wavefront
-    const int64_t blk = part >> 3;
-    if (blk >= A.blocks) return;
+    const int64_t slot = part >> 3;
+    if (A.down_from_list ? slot >= (int64_t)A.counters[1] : slot >= A.blocks) return;
+    const int64_t blk = A.down_from_list ? (int64_t)lane_u(A.list_both[slot], 0) : slot;
     const int flags = (int)A.blk_flags[blk];
     if (!(flags & kFlagRes) || !(flags & kFlagInj) || (flags & kFlagFewInj)) return;
     const int64_t j = blk * 64 + lane;
@@ -2672,13 +2700,19 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
         const std::string fx = "phase_split_blocks." + tag;
-        LAPLEX_TIMED(fx.c_str(), st, hipLaunchKernelGGL(k_phase_split_blocks, dim3((unsigned)((8 * g.blocks + kStreamWaves - 1) / kStreamWaves)),
-                                                        dim3(kStreamWaves * 64), 0, st, A));
+        // the list holds the blocks with injected and result rows, except those with few injected rows (mode 1 needs them too)
+        const int from_list = A.down_from_list && (A.pin.split_blocks == 2 || !A.few_inj_ok);
+        const int64_t visited = from_list ? dcap : g.blocks;
+        LAPLEX_TIMED(fx.c_str(), st, hipLaunchKernelGGL(k_phase_split_blocks, dim3((unsigned)((8 * visited + kStreamWaves - 1) / kStreamWaves)),
+                                                        dim3(kStreamWaves * 64), 0, st, A, from_list));
     }
     if (VEC == 4 && A.few_res_ok) {
         const std::string ff = "scan_down_fewres." + tag;
         const dim3 fgrid((dgrid.x + kFewWaves - 1) / kFewWaves, dgrid.y);
-        LAPLEX_TIMED(ff.c_str(), st, hipLaunchKernelGGL((k_scan_down_fewres<STRICT>), fgrid, dim3(kFewWaves * 64), 0, st, A));
+        if (A.pin.half && A.pin.virtual_inj)
+            LAPLEX_TIMED(ff.c_str(), st, hipLaunchKernelGGL((k_scan_down_fewres<STRICT, 2>), dim3(fgrid.x), dim3(kFewWaves * 64), 0, st, A));
+        else
+            LAPLEX_TIMED(ff.c_str(), st, hipLaunchKernelGGL((k_scan_down_fewres<STRICT, 1>), fgrid, dim3(kFewWaves * 64), 0, st, A));
     }
     {
         const bool red = STRICT && A.out_red != nullptr;
@@ -2696,12 +2730,14 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     }
     if (VEC == 4 && g.sub_shift) {
         const dim3 sgrid((unsigned)((g.blocks + kStreamWaves - 1) / kStreamWaves), (unsigned)g.slabs);
-        if (A.ph.half) {     // phased backward: one wavefront merges both halves of its block's rows; the other blocks' rows after it
+        if (A.ph.half) {     // phased backward: one wavefront merges both halves of its block's rows; the other blocks' rows before it
+            // (the merge first: the streaming downsweep clears the list's length)
             const dim3 pgrid(sgrid.x);
-            LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse_wide_phased<STRICT>), pgrid, dim3(kStreamWaves * 64), 0, st, A));
             const std::string fm = "phase_merge_blocks." + tag;
-            LAPLEX_TIMED(fm.c_str(), st, hipLaunchKernelGGL(k_phase_merge_blocks, dim3((unsigned)((8 * g.blocks + kStreamWaves - 1) / kStreamWaves)),
+            const int64_t visited = A.down_from_list ? dcap : g.blocks;
+            LAPLEX_TIMED(fm.c_str(), st, hipLaunchKernelGGL(k_phase_merge_blocks, dim3((unsigned)((8 * visited + kStreamWaves - 1) / kStreamWaves)),
                                                             dim3(kStreamWaves * 64), 0, st, A));
+            LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse_wide_phased<STRICT>), pgrid, dim3(kStreamWaves * 64), 0, st, A));
         } else {
             LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse_wide<STRICT>), sgrid, dim3(kStreamWaves * 64), 0, st, A));
         }
