@@ -198,6 +198,9 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
     if (both_sorted) {
         LAPLEX_HIP(launch_merge(a, k, b, n, tau, keys0, P.ids, st));
         LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
+    } else if (L.N <= kRunSortMax) {
+        LAPLEX_HIP(launch_run_sort(a, k, b, n, tau, reinterpret_cast<uint32_t*>(pair0), reinterpret_cast<uint32_t*>(pair1), P.ids, P.dh, P.pk, P.pk8, counters,
+                                   1, 0, 0, 0, st));
     } else {
         LAPLEX_HIP(launch_onesweep_sort(a, k, b, n, tau, pair0, pair1, P.ids, P.pk, small,
                                         reinterpret_cast<unsigned long long*>(ws + L.off_status), st));

@@ -15,13 +15,19 @@ constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 constexpr int kSortPasses = 4;
 constexpr int kSortThreads = 512;                       // 8 wavefronts
-// Keys per thread of a sort pass, hence per tile (512 x 4, 8 or 16).  A short sort is bound by the latency of one
-// tile (its ranking, the hop from tile to tile), not by throughput: it gets smaller tiles, so more of them run side by side.
-inline int sort_keys_per_thread(int64_t N) { return N <= (int64_t(1) << 18) ? 4 : N <= (int64_t(5) << 18) ? 8 : 16; }
-inline int64_t sort_tile(int64_t N) { return (int64_t)kSortThreads * sort_keys_per_thread(N); }
-// keys per workgroup of the histogram kernel (up to its grid limit): fewer for a short sort, whose histogram is bound by
-// the latency of one workgroup; more for a long one, where every workgroup adds its 1024 counts to the global ones
-inline int64_t sort_hist_tile(int64_t N) { return (int64_t)kSortThreads * (N <= (int64_t(1) << 18) ? 4 : 16); }
+// Keys per thread of a sort pass, hence per tile (512 x 8 or 16).  A short sort is bound by the latency of one tile (its
+// ranking, the hop from tile to tile), not by throughput: it gets smaller tiles, so more of them run side by side.
+inline int sort_keys_per_thread(int64_t N) { return N <= (int64_t(5) << 18) ? 8 : 16; }
+inline int64_t sort_tiles_of(int64_t N)
+{
+    const int64_t tile = (int64_t)kSortThreads * sort_keys_per_thread(N);
+    return (N + tile - 1) / tile;
+}
+constexpr int64_t kSortHistTile = 8192;                 // keys per workgroup of the histogram kernel, up to its grid limit
+// Up to this many merged positions the anchors are sorted in two launches by runs and buckets (run_sort_kernels.hip).
+constexpr int64_t kRunSortMax = int64_t(1) << 19;
+constexpr int kRunSampleBits = 6;                       // samples per run: 2^6
+constexpr int kRunSortMaxRuns = 128;                    // tiles of 1024, 2048 and 4096 positions
 // Small state of one sort, u32 words: [0, 1024) histogram of the four digits; then the per-pass tile
 // tickets, the error flag and the histogram's done counter in one cache line, and the mask of the passes that run in a line of its own.
 constexpr int kSortTicketWord = 1024;
@@ -195,7 +201,7 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
 
     // sort view
     size_t s = o;
-    L.sort_tiles = (N + sort_tile(N) - 1) / sort_tile(N);
+    L.sort_tiles = sort_tiles_of(N);
     L.status_words = L.sort_tiles * kRadix;
     L.off_pair0 = s;  s = align_up(s + 2 * sizeof(uint32_t) * (size_t)N);
     L.off_pair1 = s;  s = align_up(s + 2 * sizeof(uint32_t) * (size_t)N);
@@ -278,6 +284,13 @@ void profile_after(const char* family, hipStream_t st);
 hipError_t launch_onesweep_sort(const float* a, int64_t k, const float* b, int64_t n, float tau,
                                 uint2* pair0, uint2* pair1, uint32_t* ids, float* pk,
                                 uint32_t* small, unsigned long long* status, hipStream_t st);
+
+// Stable sort of up to kRunSortMax anchors (run_sort_kernels.hip): writes the whole plan, decays and cleared list counters
+// included.  runs: 2 N words and 64 beyond them that may be read, samples: 2^kRunSampleBits words per run, 16-byte aligned, scratch.  For
+// `operators` problems of the same sizes at once, their anchors op_a / op_b elements and everything else op_ws bytes apart.
+hipError_t launch_run_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, uint32_t* runs, uint32_t* samples,
+                           uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters,
+                           int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st);
 
 // Both inputs ascending: merged keys/ids in one pass (ties: a first).
 hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, float tau,

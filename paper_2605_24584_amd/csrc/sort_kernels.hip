@@ -2,6 +2,7 @@
 // App. B "Combined complexity").  Hand-written for gfx950:
 // 64-wide wavefronts, ballot-based stable ranking, LDS-staged scatter.
 //
+//   (up to kRunSortMax merged positions: run_sort_kernels.hip)
 //   radix sort  one-sweep LSD sort, up to 4 passes of 8 bits (a pass whose digit is the same
 //               for every key is skipped): one histogram kernel (key
 //               build fused: a ++ b -> order-preserving u32 keys, ids = positions),
@@ -657,7 +658,7 @@ hipError_t launch_onesweep_sort(const float* a, int64_t k, const float* b, int64
                                 uint32_t* small, unsigned long long* status, hipStream_t st)
 {
     const int64_t N = k + n;
-    const int64_t tiles = (N + sort_tile(N) - 1) / sort_tile(N);
+    const int64_t tiles = sort_tiles_of(N);
     const int64_t words = tiles * kRadix;
     unsigned long long* region[2] = {status, status + words};
     LAPLEX_TIMED("sort_hist", st, hipLaunchKernelGGL(k_sort_reset, dim3(1), dim3(1024), 0, st, small));
@@ -667,7 +668,7 @@ hipError_t launch_onesweep_sort(const float* a, int64_t k, const float* b, int64
         LAPLEX_TIMED("sort_hist", st, hipLaunchKernelGGL(k_sort_hist<true>, dim3((unsigned)hgrid), dim3(kHistBankedThreads), 0, st,
                                                          a, k, b, n, tau, small, region[0], words));
     } else {
-        int64_t hgrid = (N + sort_hist_tile(N) - 1) / sort_hist_tile(N);
+        int64_t hgrid = (N + kSortHistTile - 1) / kSortHistTile;
         if (hgrid > 2048) hgrid = 2048;
         LAPLEX_TIMED("sort_hist", st, hipLaunchKernelGGL(k_sort_hist<false>, dim3((unsigned)hgrid), dim3(kSortThreads), 0, st,
                                                          a, k, b, n, tau, small, region[0], words));
@@ -683,11 +684,8 @@ hipError_t launch_onesweep_sort(const float* a, int64_t k, const float* b, int64
     };
     if (N <= (int64_t(1) << 30)) {
         uint32_t* r = reinterpret_cast<uint32_t*>(status);
-        switch (sort_keys_per_thread(N)) {
-            case 4:  passes(k_onesweep_pass<uint32_t, 4>, r, r + words); break;
-            case 8:  passes(k_onesweep_pass<uint32_t, 8>, r, r + words); break;
-            default: passes(k_onesweep_pass<uint32_t, 16>, r, r + words); break;
-        }
+        if (sort_keys_per_thread(N) == 8) passes(k_onesweep_pass<uint32_t, 8>, r, r + words);
+        else passes(k_onesweep_pass<uint32_t, 16>, r, r + words);
     } else {
         passes(k_onesweep_pass<unsigned long long, 16>, region[0], region[1]);
     }

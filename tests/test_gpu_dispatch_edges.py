@@ -35,3 +35,58 @@ def test_weighted_gram_tile_edges(oracle, k, n, gap):
     got = m.cpu().numpy()
     assert np.all(np.isfinite(got)) and np.array_equal(got, got.T)
     assert float((np.abs(got - ref) / (1e-12 * tol + 1e-300)).max()) <= 1.0
+
+
+RUN_SORT_SIZES = [8193, 9217, (1 << 17) - 1, 1 << 17, (1 << 17) + 1, 1 << 18, (1 << 18) + 1, 1 << 19, (1 << 19) + 1]
+
+
+def sorted_ids(keys_a, keys_b):
+    """np's stable order of a ++ b, and the plan that the library builds for it (ids, and y of the product with ones)."""
+    k, n = keys_a.size, keys_b.size
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, 1), dtype=torch.uint8, device="cuda")
+    y = torch.empty(k, 1, device="cuda")
+    B.laplex_apply(dev(keys_a), dev(keys_b), torch.ones(n, 1, device="cuda"), y, ws, 0)
+    perm = torch.empty(k + n, dtype=torch.int32, device="cuda")
+    B.laplex_get_perm(ws, k + n, perm)
+    torch.cuda.synchronize()
+    return perm.cpu().numpy(), y.cpu().numpy()
+
+
+@pytest.mark.parametrize("kind", ["uniform", "few_values", "equal", "ascending", "repeating", "between_samples"])
+@pytest.mark.parametrize("N", RUN_SORT_SIZES)
+def test_run_sort_order_and_decays(oracle, N, kind):
+    """The two-launch sort at the ends of its configurations (tiles of 1024, 2048, 4096 keys).  `between_samples` puts, in
+    every run, all keys between two of the run's samples into one narrow window: a stretch beyond the capacity of a workgroup."""
+    r = np.random.default_rng(N)
+    tile = 1024 if N <= 1 << 17 else 2048 if N <= 1 << 18 else 4096
+    step = tile // 64
+    if kind == "uniform":
+        v = r.uniform(0, N / 64, N)
+    elif kind == "few_values":
+        v = r.integers(0, 37, N) * 0.25
+    elif kind == "equal":
+        v = np.zeros(N)
+    elif kind == "ascending":
+        v = np.arange(N) / 64.0
+    elif kind == "repeating":
+        v = (np.arange(N) % tile) * 0.5
+    else:
+        v = np.empty(N)
+        for run in range((N + tile - 1) // tile):
+            q = np.arange(tile)
+            w = q / 8.0
+            first = (run * 11) % step + 5 * step
+            inside = (q > first) & (q < first + step)
+            w[q <= first] = q[q <= first] * 0.01
+            w[inside] = 50.0 + r.uniform(0, 1, step - 1)
+            w[q >= first + step] += 60.0
+            part = r.permutation(w)[: min(tile, N - run * tile)]
+            v[run * tile: run * tile + part.size] = part
+    v = v.astype(np.float32)
+    k = N // 3
+    ids, y = sorted_ids(v[:k], v[k:])
+    assert np.array_equal(ids, np.argsort(v, kind="stable"))
+    pick = r.integers(0, k, 200)                                  # decays: a few outputs against the definition
+    a, b = v[:k][pick].astype(np.float64), v[k:].astype(np.float64)
+    ref = np.exp(-np.abs(a[:, None] - b[None, :])).sum(axis=1)
+    assert float((np.abs(y[pick, 0] - ref) / (1e-5 * ref + 1e-7)).max()) <= 1.0
