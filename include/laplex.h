@@ -246,11 +246,11 @@ int laplex_phased_apply_backward(const float* a, const float* phi, int64_t k,
  *   y[i*ldy + t] = sum_q w[q] * sum_j exp(-|a[q*k + i] - b[q*n + j]|) * x[j*ldx + t]
  *
  * a[r][k], b[r][n] contiguous, w[r] in DEVICE memory (the mixing weights are
- * trained like the anchors), r <= LAPLEX_MIX_MAX_OPERATORS.  Computed as r plain
- * applies whose products are combined in a fixed order.  The workspace
+ * trained like the anchors), r <= LAPLEX_MIX_MAX_OPERATORS.  The operators are
+ * summed in a fixed order.  The workspace
  * (laplex_mix_workspace_bytes) holds r plain workspaces back to back (operator q's
  * plan sits at q * (their common size); the flags act on every operator alike),
- * then the r products and the scratch of the backward call.
+ * then what the operators share and the scratch of the backward call.
  * laplex_mix_apply_backward: gradients of sum(gy * y): gx[n][batch], ga[r][k],
  * gb[r][n] (tie rule as above), gw[r] = <gy, L_q x>; any may be NULL.  With
  * LAPLEX_SAVE_SCANS the forward call (same flag, same workspace) has left what the
@@ -258,8 +258,8 @@ int laplex_phased_apply_backward(const float* a, const float* phi, int64_t k,
  * NULL if only gx is wanted.  r == 0 gives y = 0.
  * Streams: everything is ordered after the work already in `stream`, and work put
  * into `stream` afterwards is ordered after everything these calls do.  In between,
- * operators with more than 8192 merged positions and small matrices may run on up to
- * four streams that the library creates once per device (default priority) and keeps;
+ * operators with more than 2^17 merged positions (2^19 for narrow batches) and small
+ * matrices may run on up to four streams that the library creates once per device (default priority) and keeps;
  * while `stream` is being captured into a graph they stay on it.  The results do not
  * depend on which of the two happens.  Calls on different host threads take turns
  * while they enqueue.

@@ -335,6 +335,10 @@ int check_wgram_sizes(int64_t k, int64_t n)
 struct MixLayout {
     size_t inner = 0, off_parts = 0, off_gyq = 0, off_gxq = 0, off_gxp = 0, off_partial = 0, total = 0;
     int lanes = 1;      // operators in flight at a time on the large path (each on a stream of its own)
+    bool common = false;      // all operators in common launches (mix_kernels.hip); in place of the regions above:
+    size_t off_srow = 0, off_sp = 0, off_cuts = 0, off_recs = 0, off_sums = 0, off_fr = 0, off_p = 0, off_z = 0, off_scan = 0,
+           off_dot_long = 0, off_dot_short = 0, off_dot_total = 0;
+    Layout ops;               // scan scratch of one operator
 };
 
 // Beyond the small path an operator is a chain of two dozen launches; while the matrices are small each of them fills a
@@ -342,6 +346,16 @@ struct MixLayout {
 // kMixLanes of them run side by side, each on a stream of the library's own, with its own copy of the per-operator scratch.
 constexpr int kMixLanes = 4;
 constexpr int64_t kMixLanesMaxElements = int64_t(1) << 24;      // (k + n) * batch up to which that pays
+
+// Common launches: what the two-launch sort takes (beyond it 16 operators fill the device one by one), and one chunk of tiles in
+// the scan of the merged sequence: 2^17 positions at 29 columns and more, 2^19 below.
+bool mix_common(int64_t k, int64_t n, int64_t batch)
+{
+    const int64_t N = k + n;
+    if (N <= kSmallMax || N > kRunSortMax || k < 1 || n < 1 || batch < 1) return false;
+    if (batch > 65535 * (int64_t)kOpsLanes) return false;      // slabs are a grid dimension
+    return make_ops_layout(N, batch).max_chunks == 1;
+}
 
 int mix_lanes(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
@@ -355,6 +369,26 @@ MixLayout mix_layout(int64_t r, int64_t k, int64_t n, int64_t batch)
     M.lanes = mix_lanes(r, k, n, batch);
     M.inner = align_up(make_layout(k + n, k, batch).total);
     size_t o = M.inner * (size_t)r;
+    M.common = mix_common(k, n, batch);
+    if (M.common) {
+        const size_t ops = (size_t)r, m = (size_t)(k < n ? k : n), l = (size_t)(k < n ? n : k), width = (size_t)mix_width(batch);
+        const size_t slabs = ((size_t)batch + width - 1) / width, rows = sizeof(float) * ops * m * (size_t)batch;
+        M.ops = make_ops_layout(k + n, batch);
+        M.off_srow = o; o = align_up(o + sizeof(uint32_t) * ops * m);
+        M.off_sp = o;   o = align_up(o + sizeof(float) * ops * m);
+        M.off_cuts = o; o = align_up(o + sizeof(uint2) * ops * l);
+        M.off_recs = o; o = align_up(o + sizeof(uint4) * ops * l);
+        M.off_sums = o; o = align_up(o + sizeof(float) * ops * slabs * 2 * (size_t)mix_max_tiles((int64_t)m, batch) * width);
+        M.off_fr = o;   o = align_up(o + sizeof(float) * ops * slabs * m * 2 * width);
+        M.off_p = o;    o = align_up(o + rows);
+        M.off_z = o;    o = align_up(o + rows);
+        M.off_scan = o; o = align_up(o + M.ops.total * ops);
+        M.off_dot_long = o;  o = align_up(o + sizeof(float) * slabs * ops * l);
+        M.off_dot_short = o; o = align_up(o + sizeof(float) * slabs * ops * m);
+        M.off_dot_total = o; o = align_up(o + sizeof(float) * slabs * ops * m);
+        M.total = o;
+        return M;
+    }
     M.off_parts = o;   o = align_up(o + sizeof(float) * (size_t)r * (size_t)k * (size_t)batch);
     // small problems run all operators in one launch and need these per operator; the large path per lane
     const size_t per_op = (k + n <= kSmallMax) ? (size_t)r : (size_t)M.lanes;
@@ -365,6 +399,123 @@ MixLayout mix_layout(int64_t r, int64_t k, int64_t n, int64_t batch)
     M.off_partial = o; o = align_up(o + sizeof(float) * dots);
     M.total = o;
     return M;
+}
+
+// One call on the common launches: the plans, and the two directions of a product.
+struct MixCommon {
+    MixPath A;
+    MixLayout M;
+    char* base;
+    Layout L;
+    const float* a; const float* b; int64_t n; hipStream_t st;
+    MixGather sum;      // w and the regions; a call fills in what it wants
+    float* dot_long; float* dot_short; float* dot_total; float* p; float* z;
+
+    MixCommon(const MixLayout& M_, const float* a_, const float* b_, const float* w, int64_t r, int64_t k, int64_t n_, int64_t batch,
+              char* base_, hipStream_t st_)
+        : A{}, M(M_), base(base_), L(make_layout(k + n_, k, batch)), a(a_), b(b_), n(n_), st(st_), sum{}
+    {
+        const Plan P = plan_of(L, base);
+        A.ids = P.ids; A.pk = P.pk; A.counters = reinterpret_cast<const uint32_t*>(base + L.off_counters); A.op_ws = (int64_t)M.inner;
+        A.k = k; A.N = (int)(k + n); A.short_b = n <= k; A.operators = (int)r;
+        A.m = (int)(A.short_b ? n : k); A.l = (int)(A.short_b ? k : n);
+        A.long_anchor = A.short_b ? a : b;
+        A.srow = reinterpret_cast<uint32_t*>(base + M.off_srow); A.sp = reinterpret_cast<float*>(base + M.off_sp);
+        A.cuts = reinterpret_cast<uint2*>(base + M.off_cuts); A.recs = reinterpret_cast<uint4*>(base + M.off_recs);
+        A.sums = reinterpret_cast<float*>(base + M.off_sums); A.fr = reinterpret_cast<float*>(base + M.off_fr);
+        A.batch = batch; A.width = mix_width(batch); A.slabs = (int)((batch + A.width - 1) / A.width);
+        sum.w = w;
+        dot_long = reinterpret_cast<float*>(base + M.off_dot_long); dot_short = reinterpret_cast<float*>(base + M.off_dot_short);
+        dot_total = reinterpret_cast<float*>(base + M.off_dot_total);
+        p = reinterpret_cast<float*>(base + M.off_p); z = reinterpret_cast<float*>(base + M.off_z);
+    }
+    // (anchors that arrive sorted are sorted again: two launches for all operators, where the merge would take two for each)
+    int plan(uint32_t flags)
+    {
+        if (flags & LAPLEX_REUSE_PLAN) return LAPLEX_OK;
+        const Plan P = plan_of(L, base);
+        LAPLEX_HIP(launch_run_sort(a, A.k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
+                                   P.ids, P.dh, P.pk, P.pk8, reinterpret_cast<uint32_t*>(base + L.off_counters),
+                                   A.operators, A.k, n, (int64_t)M.inner, st));
+        LAPLEX_HIP(launch_mix_index(A, st));
+        return LAPLEX_OK;
+    }
+    // the rows v of the short side scanned, per operator
+    int scan_short(const float* v, int64_t ldv) { LAPLEX_HIP(launch_mix_scan(A, v, ldv, st)); return LAPLEX_OK; }
+    // the products (p) and strict sums (z) of the rows v of the long side at the short rows, per operator
+    int scan_long(const float* v, int64_t ldv, bool want_p, bool want_z)
+    {
+        const Plan P = plan_of(L, base);
+        ScanProblem q{};
+        q.ids = P.ids; q.dh = P.dh; q.pk = P.pk; q.N = A.N; q.batch = A.batch;
+        const uint32_t k32 = (uint32_t)A.k, N32 = (uint32_t)A.N;
+        q.inj = v; q.ld_inj = ldv;
+        q.inj_lo = A.short_b ? 0 : k32; q.inj_hi = A.short_b ? k32 : N32;
+        q.res_lo = A.short_b ? k32 : 0; q.res_hi = A.short_b ? N32 : k32;
+        q.out_p = want_p ? p : nullptr; q.out_z = want_z ? z : nullptr;
+        q.tag = "mix";
+        LAPLEX_HIP(launch_scan_ops(q, M.ops, base + M.off_scan, reinterpret_cast<uint32_t*>(base + L.off_counters), A.operators, (int64_t)M.inner, st));
+        return LAPLEX_OK;
+    }
+    // sums over the operators and the rows' dots with u, at the long rows (from the scanned short side) ...
+    int at_long(const float* u, int64_t ldu, float* out, int64_t ldo, float* grad)
+    {
+        MixGather S = sum;
+        S.u = grad ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo; S.dot1 = grad ? dot_long : nullptr;
+        LAPLEX_HIP(launch_mix_gather(A, S, false, st));
+        if (grad) LAPLEX_HIP(launch_mix_finish(A, dot_long, sum.w, A.l, grad, st));
+        return LAPLEX_OK;
+    }
+    // ... and at the short rows (from p and z); gw[q] = sum of the rows' dots with p
+    int at_short(const float* u, int64_t ldu, float* out, int64_t ldo, float* grad, float* gw)
+    {
+        MixGather S = sum;
+        S.u = grad || gw ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo;
+        S.p = out || gw ? p : nullptr; S.z = grad ? z : nullptr;
+        S.dot1 = grad ? dot_short : nullptr; S.dot2 = gw ? dot_total : nullptr;
+        LAPLEX_HIP(launch_mix_gather(A, S, true, st));
+        if (grad) LAPLEX_HIP(launch_mix_finish(A, dot_short, sum.w, A.m, grad, st));
+        if (gw) LAPLEX_HIP(launch_mix_total(A, dot_total, gw, st));
+        return LAPLEX_OK;
+    }
+};
+
+int mix_common_forward(MixCommon& C, const float* x, int64_t ldx, float* y, int64_t ldy, uint32_t flags)
+{
+    LAPLEX_CHECK(C.plan(flags));
+    if (C.A.short_b) {
+        LAPLEX_CHECK(C.scan_short(x, ldx));
+        return C.at_long(nullptr, 0, y, ldy, nullptr);
+    }
+    LAPLEX_CHECK(C.scan_long(x, ldx, true, (flags & LAPLEX_SAVE_SCANS) != 0));
+    return C.at_short(nullptr, 0, y, ldy, nullptr, nullptr);
+}
+
+int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* gy, int64_t ldgy,
+                        float* gx, int64_t ldgx, float* ga, float* gb, float* gw, uint32_t flags)
+{
+    const bool saved = (flags & LAPLEX_SAVE_SCANS) != 0;      // the forward left the scanned short side (or p and z) of x
+    LAPLEX_CHECK(C.plan(flags));
+    if (C.A.short_b) {
+        if (ga) {
+            if (!saved) LAPLEX_CHECK(C.scan_short(x, ldx));
+            LAPLEX_CHECK(C.at_long(gy, ldgy, nullptr, 0, ga));
+        }
+        if (gx || gb || gw) {      // <gy, L_q x> = <L_q^T gy, x>: the weights' gradients come from the short rows
+            LAPLEX_CHECK(C.scan_long(gy, ldgy, gx || gw, gb != nullptr));
+            LAPLEX_CHECK(C.at_short(x, ldx, gx, ldgx, gb, gw));
+        }
+        return LAPLEX_OK;
+    }
+    if (ga || gw) {
+        if (!saved) LAPLEX_CHECK(C.scan_long(x, ldx, true, true));
+        LAPLEX_CHECK(C.at_short(gy, ldgy, nullptr, 0, ga, gw));
+    }
+    if (gx || gb) {
+        LAPLEX_CHECK(C.scan_short(gy, ldgy));
+        LAPLEX_CHECK(C.at_long(x, ldx, gx, ldgx, gb));
+    }
+    return LAPLEX_OK;
 }
 
 constexpr int kMaxDevices = 64;
@@ -1112,6 +1263,10 @@ int laplex_mix_apply(const float* a, const float* b, const float* w, int64_t r, 
     if (misaligned(ws, 256)) return LAPLEX_ERR_ALIGN;
     if (ws_bytes < M.total) return LAPLEX_ERR_WORKSPACE;
     char* base = static_cast<char*>(ws);
+    if (M.common) {
+        MixCommon C(M, a, b, w, r, k, n, batch, base, st);
+        return mix_common_forward(C, x, ldx, y, ldy, flags);
+    }
     float* parts = reinterpret_cast<float*>(base + M.off_parts);
     if (k + n <= kSmallMax) {      // every operator in the same two launches
         const Layout L = make_layout(k + n, k, batch);
@@ -1172,6 +1327,10 @@ int laplex_mix_apply_backward(const float* a, const float* b, const float* w, in
     if (misaligned(ws, 256)) return LAPLEX_ERR_ALIGN;
     if (ws_bytes < M.total) return LAPLEX_ERR_WORKSPACE;
     char* base = static_cast<char*>(ws);
+    if (M.common) {
+        MixCommon C(M, a, b, w, r, k, n, batch, base, st);
+        return mix_common_backward(C, x, ldx, gy, ldgy, gx, ldgx, ga, gb, gw, flags);
+    }
     float* parts = reinterpret_cast<float*>(base + M.off_parts);
     float* gyq = reinterpret_cast<float*>(base + M.off_gyq);
     float* gxq = reinterpret_cast<float*>(base + M.off_gxq);

@@ -1,0 +1,554 @@
+// LAPLEX^(r), y = sum_q w_q L(a_q, b_q) x, with all operators in the same launches (Sec. 7, "Learned anchor geometry in neural
+// heads"), for operators whose merged sequence the two-launch sort takes and the narrow scan geometry covers in one chunk.
+//
+// One side of an operator is shorter (a head over a vocabulary: few inputs, many outputs).  Nothing per operator is ever as
+// large as the long side times the batch:
+//   short -> long   the rows of the short side are scanned in sorted order into, per row s, the inclusive decayed sums
+//                   F_s (rows at or before s) and R_s (rows at or after s); a row of the long side at anchor p is then
+//                   exp(-(p - p_lo)) F_lo + exp(-(p_hi - p)) R_hi of its two neighbours (Thm "Dual reduction", App. B.3), and
+//                   one kernel adds that up over the operators, in registers (k_mix_scan_reduce, k_mix_scan_down, k_mix_gather)
+//   long -> short   a scan of the merged sequence whose results are rows of the short side (launch_scan_ops), then the same
+//                   kernel in its other form adds the operators up
+// Anchor gradients are row products of the caller's matrices with the strict sums, formed where the sums are in registers.
+//
+// The batch is cut into slabs of up to 32 columns, workgroup % slabs = slab: with eight slabs a slab's rows F, R of the
+// operator at hand (2 x 128 bytes x 4096 short rows = 1 MB) stay in the L2 of one chiplet while its workgroups walk through
+// the operators together.
+//
+// Measured (MI355X, forward + backward): 16 operators of 32000 x 4096, batch 256: 2.97 ms one operator after the other on four
+// streams (320 launches, 4 GB of per-operator products and strict sums of the long side written and read) -> 0.76 ms in 14
+// launches.  Of the 13 TB/s that k_mix_gather reads there (80 us for 2 x 16 rows of 1 KB per output) most comes from the L2.
+#include "laplex_internal.h"
+
+namespace laplex {
+
+namespace {
+
+constexpr int kMixThreads = 256;
+constexpr int kMixWaves = kMixThreads / 64;
+constexpr int kMixItems = 8;                             // rows per row-lane of the scan kernels
+constexpr int kMixTileMax = kMixWaves * 64 * kMixItems;  // rows of a workgroup with one lane across the batch
+constexpr int kIndexThreads = 512;
+constexpr int kIndexTile = kIndexThreads * 4;
+
+template <typename T>
+__device__ __forceinline__ T* shift_bytes(T* p, int64_t bytes)
+{
+    return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + (uintptr_t)bytes);
+}
+
+// dst[0 .. VEC) <- ok ? src : 0 (not read if !ok)
+template <int VEC>
+__device__ __forceinline__ void load_cols(float* dst, const float* src, bool ok)
+{
+    if (VEC == 4) {
+        const float4 t = ok ? *reinterpret_cast<const float4*>(src) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        dst[0] = t.x; dst[1] = t.y; dst[2] = t.z; dst[3] = t.w;
+    } else {
+        dst[0] = ok ? src[0] : 0.0f;
+    }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_cols(float* dst, const float* src)
+{
+    if (VEC == 4) *reinterpret_cast<float4*>(dst) = make_float4(src[0], src[1], src[2], src[3]);
+    else dst[0] = src[0];
+}
+
+// ---------------------------------------------------------------------------
+// From the merged order of an operator: its short side as a list in sorted order (row, anchor), and for every row of the long
+// side how many short anchors lie strictly below it and how many at or below it.  A workgroup takes 2048 merged positions and
+// counts the short ones before them itself (a few dozen KB of ids from the L2, instead of a launch that would count per tile).
+// ---------------------------------------------------------------------------
+__global__ void __launch_bounds__(kIndexThreads)
+k_mix_index(const MixPath A)
+{
+    __shared__ int before[kIndexThreads / 64], total[kIndexThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t op = blockIdx.y;
+    const uint32_t* ids = shift_bytes(A.ids, op * A.op_ws);
+    const float* pk = shift_bytes(A.pk, op * A.op_ws);
+    const uint32_t k = (uint32_t)A.k;
+    const bool short_b = A.short_b != 0;
+    auto is_short = [&](uint32_t id) { return (id >= k) == short_b; };
+    const int base = blockIdx.x * kIndexTile;
+
+    int count = 0;                                        // (base is a multiple of 2048 and the ids start on 256 bytes)
+    for (int j = tid * 4; j < base; j += kIndexTile) {
+        const uint4 v = *reinterpret_cast<const uint4*>(ids + j);
+        count += (is_short(v.x) ? 1 : 0) + (is_short(v.y) ? 1 : 0) + (is_short(v.z) ? 1 : 0) + (is_short(v.w) ? 1 : 0);
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) count += __shfl_xor(count, m);
+
+    const int j0 = base + tid * 4;
+    uint32_t id[4];
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        id[i] = j0 + i < A.N ? ids[j0 + i] : 0xFFFFFFFFu;
+        mine += j0 + i < A.N && is_short(id[i]) ? 1 : 0;
+    }
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) { const int o = __shfl_up(incl, d); if (lane >= d) incl += o; }
+    if (lane == 63) total[wave] = incl;
+    if (lane == 0) before[wave] = count;
+    __syncthreads();
+    int s = incl - mine;
+#pragma unroll
+    for (int w = 0; w < kIndexThreads / 64; ++w) s += before[w] + (w < wave ? total[w] : 0);
+
+    uint32_t* srow = A.srow + op * A.m;
+    float* sp = A.sp + op * A.m;
+    uint2* cuts = A.cuts + op * A.l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = j0 + i;
+        if (j >= A.N) break;
+        const float p = pk[j + 1];
+        if (is_short(id[i])) {
+            srow[s] = short_b ? id[i] - k : id[i];
+            sp[s] = p;
+            ++s;
+            continue;
+        }
+        int lo = s, hi = s;
+        if (pk[j] == p || pk[j + 2] == p) {               // equal keys: outputs first, then inputs (the stable order)
+            int a0 = 0, a1 = j;                           // first position of the run
+            while (a0 < a1) { const int mid = (a0 + a1) >> 1; if (pk[mid + 1] < p) a0 = mid + 1; else a1 = mid; }
+            int b0 = j + 1, b1 = A.N;                     // one past its last
+            while (b0 < b1) { const int mid = (b0 + b1) >> 1; if (pk[mid + 1] <= p) b0 = mid + 1; else b1 = mid; }
+            int f0 = a0, f1 = b0;                         // its first input
+            while (f0 < f1) { const int mid = (f0 + f1) >> 1; if (ids[mid] < k) f0 = mid + 1; else f1 = mid; }
+            if (short_b) hi = s + (b0 - f0);
+            else lo = s - (f0 - a0);
+            lo = lo < 0 ? 0 : lo;                         // (not-a-number anchors order without comparing)
+            hi = hi > A.m ? A.m : hi;
+        }
+        cuts[short_b ? id[i] : id[i] - k] = make_uint2((uint32_t)lo, (uint32_t)hi);
+    }
+}
+
+// Row j of the sorted short list, clamped to it.
+__device__ __forceinline__ int clamp_row(int j, int m) { return j < 0 ? 0 : (j < m ? j : m - 1); }
+
+// ---------------------------------------------------------------------------
+// Scan of the short side, first launch: per tile and slab the sum of its rows decayed to the tile's last row and to its first
+// one, as weighted sums (a row's two weights are one exponential of an anchor difference each, taken once per workgroup).
+// Workgroups behind the tiles turn the cuts of the long side into records (rows below and above, their two weights).
+// ---------------------------------------------------------------------------
+template <int VEC>
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
+{
+    __shared__ float wf[kMixTileMax], wb[kMixTileMax];
+    __shared__ float part[2][kMixWaves][32];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t op = blockIdx.y;
+    const float* sp = A.sp + op * A.m;
+    const int m = A.m;
+    const int tile_blocks = A.tiles * A.slabs;
+    if ((int)blockIdx.x >= tile_blocks) {
+        const int i = ((int)blockIdx.x - tile_blocks) * kMixThreads + tid;
+        if (i >= A.l) return;
+        const uint2 cut = A.cuts[op * A.l + i];
+        const float p = A.long_anchor[op * A.l + i];
+        const int lo = (int)cut.x;
+        const float el = lo > 0 ? expf(-(p - sp[lo - 1])) : 0.0f;
+        const float er = lo < m ? expf(-(sp[lo] - p)) : 0.0f;
+        A.recs[op * A.l + i] = make_uint4(cut.x, cut.y, __float_as_uint(el), __float_as_uint(er));
+        return;
+    }
+    const int slab = (int)blockIdx.x % A.slabs, tile = (int)blockIdx.x / A.slabs;
+    const int bv = A.width / VEC, rv = 64 / bv;
+    const int c = lane & (bv - 1), rl = wave * rv + lane / bv;
+    const int rows = kMixWaves * rv * kMixItems;
+    const int base = tile * rows, last = clamp_row(base + rows - 1, m);
+    const int64_t col = (int64_t)slab * A.width + c * VEC;
+    const bool col_ok = col < A.batch;
+    const uint32_t* srow = A.srow + op * m;
+    float val[kMixItems][VEC];
+#pragma unroll
+    for (int i = 0; i < kMixItems; ++i) {
+        const int j = base + rl * kMixItems + i;
+        load_cols<VEC>(val[i], v + (int64_t)srow[clamp_row(j, m)] * ldv + col, col_ok && j < m);
+    }
+    const float p_first = sp[base], p_last = sp[last];
+    for (int q = tid; q < rows; q += kMixThreads) {
+        const float p = sp[clamp_row(base + q, m)];
+        wf[q] = expf(-(p_last - p));
+        wb[q] = expf(-(p - p_first));
+    }
+    __syncthreads();
+    float f[VEC], b[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) f[e] = b[e] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMixItems; ++i) {
+        const float x = wf[rl * kMixItems + i], y = wb[rl * kMixItems + i];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { f[e] += x * val[i][e]; b[e] += y * val[i][e]; }
+    }
+    for (int d = bv; d < 64; d <<= 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { f[e] += __shfl_xor(f[e], d); b[e] += __shfl_xor(b[e], d); }
+    }
+    if (lane < bv) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { part[0][wave][c * VEC + e] = f[e]; part[1][wave][c * VEC + e] = b[e]; }
+    }
+    __syncthreads();
+    if (tid < 2 * A.width) {
+        const int dir = tid / A.width, w = tid % A.width;
+        float s = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kMixWaves; ++u) s += part[dir][u][w];
+        A.sums[(((op * A.slabs + slab) * 2 + dir) * A.tiles + tile) * A.width + w] = s;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Second launch: a tile adds up the other tiles' sums itself, each brought to the tile by one exponential of an anchor
+// difference (a tile beyond the reach of an fp32 decay is not read), scans its row-lanes, and walks its rows in both directions.
+// fr[op][slab][row] = (F_row | R_row), 2 x width floats.
+// ---------------------------------------------------------------------------
+template <int VEC>
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
+{
+    __shared__ float dec[kMixTileMax + 1];                // dec[q]: decay between rows base + q - 1 and base + q
+    __shared__ float part[4][kMixWaves][32];              // wavefront totals and carries, forward and backward
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t op = blockIdx.y;
+    const int m = A.m;
+    const float* sp = A.sp + op * m;
+    const int slab = (int)blockIdx.x % A.slabs, tile = (int)blockIdx.x / A.slabs;
+    const int bv = A.width / VEC, rv = 64 / bv;
+    const int c = lane & (bv - 1), r = lane / bv, rl = wave * rv + r;
+    const int rows = kMixWaves * rv * kMixItems;
+    const int base = tile * rows;
+    const int64_t col = (int64_t)slab * A.width + c * VEC;
+    const bool col_ok = col < A.batch;
+    const uint32_t* srow = A.srow + op * m;
+    const int j0 = base + rl * kMixItems;
+    float val[kMixItems][VEC];
+#pragma unroll
+    for (int i = 0; i < kMixItems; ++i) {
+        const int j = j0 + i;
+        load_cols<VEC>(val[i], v + (int64_t)srow[clamp_row(j, m)] * ldv + col, col_ok && j < m);
+    }
+    auto pos = [&](int j) { return sp[clamp_row(j, m)]; };
+    for (int q = tid; q <= rows; q += kMixThreads) dec[q] = expf(-(pos(base + q) - pos(base + q - 1)));
+
+    // the tiles before and after, spread over the row-lanes
+    float Fc[VEC], Rc[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) Fc[e] = Rc[e] = 0.0f;
+    {
+        const float p_before = pos(base - 1), p_after = pos(base + rows);
+        const float* sf = A.sums + ((op * A.slabs + slab) * 2) * (int64_t)A.tiles * A.width + c * VEC;
+        const float* sb = sf + (int64_t)A.tiles * A.width;
+        for (int u = rl; u < A.tiles; u += kMixWaves * rv) {
+            if (u == tile) continue;
+            const float w = u < tile ? expf(-(p_before - pos((u + 1) * rows - 1))) : expf(-(pos(u * rows) - p_after));
+            if (w == 0.0f) continue;
+            float t[VEC];
+            load_cols<VEC>(t, (u < tile ? sf : sb) + (int64_t)u * A.width, true);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { if (u < tile) Fc[e] += w * t[e]; else Rc[e] += w * t[e]; }
+        }
+        for (int d = bv; d < 64; d <<= 1) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { Fc[e] += __shfl_xor(Fc[e], d); Rc[e] += __shfl_xor(Rc[e], d); }
+        }
+        if (r == 0) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { part[2][wave][c * VEC + e] = Fc[e]; part[3][wave][c * VEC + e] = Rc[e]; }
+        }
+    }
+    __syncthreads();
+    // own rows from zero, then an inclusive scan over the wavefront's row-lanes with decays from the anchors
+    float S[VEC], U[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) S[e] = U[e] = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kMixItems; ++i) {
+        const float d = dec[rl * kMixItems + i];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) S[e] = d * S[e] + val[i][e];
+    }
+#pragma unroll
+    for (int i = kMixItems - 1; i >= 0; --i) {
+        const float d = dec[rl * kMixItems + i + 1];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) U[e] = d * U[e] + val[i][e];
+    }
+    for (int d = 1; d < rv; d <<= 1) {
+        const float Df = expf(-(pos(j0 + kMixItems - 1) - pos(j0 - d * kMixItems + kMixItems - 1)));
+        const float Db = expf(-(pos(j0 + d * kMixItems) - pos(j0)));
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float So = __shfl_up(S[e], (unsigned)(d * bv)), Uo = __shfl_down(U[e], (unsigned)(d * bv));
+            if (r >= d) S[e] += Df * So;
+            if (r + d < rv) U[e] += Db * Uo;
+        }
+    }
+    if (r == rv - 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part[0][wave][c * VEC + e] = S[e];
+    }
+    if (r == 0) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part[1][wave][c * VEC + e] = U[e];
+    }
+    __syncthreads();
+    // state at the row before this row-lane (after it): what precedes the wavefront, then the row-lanes before this one
+    float F[VEC], R[VEC];
+    {
+        const int w0 = base + wave * rv * kMixItems, w1 = w0 + rv * kMixItems;      // this wavefront's rows
+        const float pw = pos(w0 - 1), pe = pos(w1);
+        float Fw[VEC], Rw[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) Fw[e] = Rw[e] = 0.0f;
+        const float cf = expf(-(pw - pos(base - 1))), cb = expf(-(pos(base + rows) - pe));
+#pragma unroll
+        for (int u = 0; u < kMixWaves; ++u) {
+            const float gf = u < wave ? expf(-(pw - pos(base + (u + 1) * rv * kMixItems - 1))) : 0.0f;
+            const float gb = u > wave ? expf(-(pos(base + u * rv * kMixItems) - pe)) : 0.0f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                Fw[e] += gf * part[0][u][c * VEC + e] + cf * part[2][u][c * VEC + e];
+                Rw[e] += gb * part[1][u][c * VEC + e] + cb * part[3][u][c * VEC + e];
+            }
+        }
+        const float df = expf(-(pos(j0 - 1) - pw)), db = expf(-(pe - pos(j0 + kMixItems)));
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float Sb = __shfl_up(S[e], (unsigned)bv), Ua = __shfl_down(U[e], (unsigned)bv);
+            F[e] = df * Fw[e] + (r > 0 ? Sb : 0.0f);
+            R[e] = db * Rw[e] + (r < rv - 1 ? Ua : 0.0f);
+        }
+    }
+    const uint32_t poison = *(shift_bytes(A.counters, op * A.op_ws) + kPlanStatusWord) ? 0x7FC00000u : 0u;
+    float* out = A.fr + ((op * A.slabs + slab) * (int64_t)m) * (2 * A.width) + c * VEC;
+#pragma unroll
+    for (int i = 0; i < kMixItems; ++i) {
+        const float d = dec[rl * kMixItems + i];
+        float t[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + val[i][e]; t[e] = __uint_as_float(__float_as_uint(F[e]) | poison); }
+        if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width), t);
+    }
+#pragma unroll
+    for (int i = kMixItems - 1; i >= 0; --i) {
+        const float d = dec[rl * kMixItems + i + 1];
+        float t[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { R[e] = d * R[e] + val[i][e]; t[e] = __uint_as_float(__float_as_uint(R[e]) | poison); }
+        if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width) + A.width, t);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The operators added up, and the anchor gradients' row products.  T target rows and VEC columns a lane.
+//   ROWS = false   targets: the long side, from the scanned short side:
+//                  out_i = sum_q w_q (el F_lo + er R_lo'),   dot1[q][i] = sum_t u_it (strict R - strict F)
+//   ROWS = true    targets: the short side, whose products P_q and strict sums Z_q (either may be null) lie in memory:
+//                  out_j = sum_q w_q P_q[j],   dot1[q][j] = sum_t u_jt Z_q[j][t],   dot2[q][j] = sum_t u_jt P_q[j][t]
+// Dots are left per slab (dot[slab][q][row]); k_mix_finish adds the slabs.
+// ---------------------------------------------------------------------------
+template <int VEC, int T, bool ROWS>
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_gather(const MixPath A, const MixGather S)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int slab = (int)blockIdx.x % A.slabs, chunk = (int)blockIdx.x / A.slabs;
+    const int width = A.width, bv = width / VEC, rv = 64 / bv;
+    const int c = lane & (bv - 1);
+    const int count = ROWS ? A.m : A.l, m = A.m;
+    const int64_t col = (int64_t)slab * width + c * VEC;
+    const bool col_ok = col < A.batch;
+    int row[T];
+    bool live[T];
+    float acc[T][VEC], u[T][VEC];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        row[t] = ((chunk * kMixWaves + wave) * T + t) * rv + lane / bv;
+        live[t] = row[t] < count;
+        row[t] = live[t] ? row[t] : count - 1;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[t][e] = u[t][e] = 0.0f;
+        if (S.u) load_cols<VEC>(u[t], S.u + (int64_t)row[t] * S.ldu + col, col_ok);
+    }
+    const bool first = !ROWS || S.p != nullptr, second = ROWS && S.z != nullptr;
+    uint4 rec[T];
+    if (!ROWS) {
+#pragma unroll
+        for (int t = 0; t < T; ++t) rec[t] = A.recs[row[t]];
+    }
+    for (int q = 0; q < A.operators; ++q) {
+        const float wq = S.w[q];
+        float f[T][VEC], g[T][VEC];
+        uint4 now[T];
+        if (!ROWS) {
+            const float* fr = A.fr + ((int64_t)q * A.slabs + slab) * m * (2 * width) + c * VEC;
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                now[t] = rec[t];
+                const int lo = (int)now[t].x;
+                load_cols<VEC>(f[t], fr + (int64_t)(lo - 1) * (2 * width), lo > 0);
+                load_cols<VEC>(g[t], fr + (int64_t)lo * (2 * width) + width, lo < m);
+            }
+            if (q + 1 < A.operators) {
+#pragma unroll
+                for (int t = 0; t < T; ++t) rec[t] = A.recs[(int64_t)(q + 1) * A.l + row[t]];
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const int64_t at = ((int64_t)q * m + row[t]) * A.batch + col;
+                load_cols<VEC>(f[t], S.p + at, first && col_ok);
+                load_cols<VEC>(g[t], S.z + at, second && col_ok);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const float el = ROWS ? 1.0f : __uint_as_float(now[t].z), er = ROWS ? 0.0f : __uint_as_float(now[t].w);
+            float d1 = 0.0f, d2 = 0.0f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (ROWS) {
+                    acc[t][e] += wq * f[t][e];
+                    d1 += u[t][e] * g[t][e];
+                    d2 += u[t][e] * f[t][e];
+                } else {
+                    acc[t][e] += wq * (el * f[t][e] + er * g[t][e]);
+                }
+            }
+            if (!ROWS && S.dot1) {
+                float es = er;
+                if (now[t].x != now[t].y) {               // short anchors equal to this one: the strict sum starts behind them
+                    const int hi = (int)now[t].y;
+                    const bool any = hi < m;
+                    es = any ? expf(-(A.sp[(int64_t)q * m + (any ? hi : 0)] - A.long_anchor[(int64_t)q * A.l + row[t]])) : 0.0f;
+                    load_cols<VEC>(g[t], A.fr + (((int64_t)q * A.slabs + slab) * m + hi) * (2 * width) + width + c * VEC, any);
+                }
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) d1 += u[t][e] * (es * g[t][e] - el * f[t][e]);
+            }
+            if (S.dot1) {
+                for (int d = 1; d < bv; d <<= 1) d1 += __shfl_xor(d1, d);
+                if (c == 0 && live[t]) S.dot1[((int64_t)slab * A.operators + q) * count + row[t]] = d1;
+            }
+            if (ROWS && S.dot2) {
+                for (int d = 1; d < bv; d <<= 1) d2 += __shfl_xor(d2, d);
+                if (c == 0 && live[t]) S.dot2[((int64_t)slab * A.operators + q) * count + row[t]] = d2;
+            }
+        }
+    }
+    if (S.out && col_ok) {
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if (live[t]) store_cols<VEC>(S.out + (int64_t)row[t] * S.ldo + col, acc[t]);
+    }
+}
+
+// out[q][i] = w_q sum_slab dot[slab][q][i]
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_finish(const float* __restrict__ dot, const float* __restrict__ w, int slabs, int operators, int count, float* __restrict__ out)
+{
+    const int64_t q = blockIdx.y;
+    const int i = blockIdx.x * kMixThreads + threadIdx.x;
+    if (i >= count) return;
+    float s = 0.0f;
+    for (int b = 0; b < slabs; ++b) s += dot[((int64_t)b * operators + q) * count + i];
+    out[q * count + i] = w[q] * s;
+}
+
+// out[q] = sum over slabs and rows of dot[slab][q][row]; one workgroup per operator, fixed order
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_total(const float* __restrict__ dot, int slabs, int operators, int count, float* __restrict__ out)
+{
+    __shared__ float red[kMixThreads];
+    const int64_t q = blockIdx.x;
+    float s = 0.0f;
+    for (int i = threadIdx.x; i < count; i += kMixThreads)
+        for (int b = 0; b < slabs; ++b) s += dot[((int64_t)b * operators + q) * count + i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int d = kMixThreads / 2; d >= 1; d >>= 1) {
+        if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) out[q] = red[0];
+}
+
+bool aligned_rows(const float* p, int64_t ld) { return !p || ((reinterpret_cast<uintptr_t>(p) & 15u) == 0 && ld % 4 == 0); }
+
+int scan_rows(const MixPath& A, int vec) { return kMixWaves * (64 / (A.width / vec)) * kMixItems; }
+
+template <int VEC, bool ROWS>
+void go_gather(const MixPath& A, const MixGather& S, hipStream_t st)
+{
+    const int64_t count = ROWS ? A.m : A.l, per = (int64_t)kMixWaves * (64 / (A.width / VEC));
+    const char* family = ROWS ? "mix_rows" : "mix_gather";
+    // four rows a lane once that still leaves every compute unit four workgroups, else one
+    if ((count + 4 * per - 1) / (4 * per) * A.slabs >= 1024) {
+        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_mix_gather<VEC, 4, ROWS>), dim3((unsigned)((count + 4 * per - 1) / (4 * per) * A.slabs)),
+                                                    dim3(kMixThreads), 0, st, A, S));
+    } else {
+        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_mix_gather<VEC, 1, ROWS>), dim3((unsigned)((count + per - 1) / per * A.slabs)),
+                                                    dim3(kMixThreads), 0, st, A, S));
+    }
+}
+
+}  // namespace
+
+hipError_t launch_mix_index(const MixPath& A, hipStream_t st)
+{
+    LAPLEX_TIMED("mix_index", st, hipLaunchKernelGGL(k_mix_index, dim3((unsigned)((A.N + kIndexTile - 1) / kIndexTile), (unsigned)A.operators),
+                                                     dim3(kIndexThreads), 0, st, A));
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_scan(const MixPath& A0, const float* v, int64_t ldv, hipStream_t st)
+{
+    MixPath A = A0;
+    const bool v4 = A.batch % 4 == 0 && aligned_rows(v, ldv);
+    const int rows = scan_rows(A, v4 ? 4 : 1);
+    A.tiles = (A.m + rows - 1) / rows;
+    const unsigned records = (unsigned)((A.l + kMixThreads - 1) / kMixThreads), work = (unsigned)(A.tiles * A.slabs);
+    auto go = [&](auto reduce, auto down) {
+        LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL(reduce, dim3(work + records, (unsigned)A.operators), dim3(kMixThreads), 0, st, A, v, ldv));
+        LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL(down, dim3(work, (unsigned)A.operators), dim3(kMixThreads), 0, st, A, v, ldv));
+    };
+    if (v4) go(k_mix_scan_reduce<4>, k_mix_scan_down<4>);
+    else go(k_mix_scan_reduce<1>, k_mix_scan_down<1>);
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_gather(const MixPath& A, const MixGather& S, bool rows, hipStream_t st)
+{
+    const bool v4 = A.batch % 4 == 0 && aligned_rows(S.u, S.ldu) && aligned_rows(S.out, S.ldo);
+    if (v4) { if (rows) go_gather<4, true>(A, S, st); else go_gather<4, false>(A, S, st); }
+    else    { if (rows) go_gather<1, true>(A, S, st); else go_gather<1, false>(A, S, st); }
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_finish(const MixPath& A, const float* dot, const float* w, int64_t count, float* out, hipStream_t st)
+{
+    LAPLEX_TIMED("mix_finish", st, hipLaunchKernelGGL(k_mix_finish, dim3((unsigned)((count + kMixThreads - 1) / kMixThreads), (unsigned)A.operators),
+                                                      dim3(kMixThreads), 0, st, dot, w, A.slabs, A.operators, (int)count, out));
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_total(const MixPath& A, const float* dot, float* out, hipStream_t st)
+{
+    LAPLEX_TIMED("mix_finish", st, hipLaunchKernelGGL(k_mix_total, dim3((unsigned)A.operators), dim3(kMixThreads), 0, st,
+                                                      dot, A.slabs, A.operators, A.m, out));
+    return hipGetLastError();
+}
+
+}  // namespace laplex

@@ -90,3 +90,45 @@ def test_run_sort_order_and_decays(oracle, N, kind):
     a, b = v[:k][pick].astype(np.float64), v[k:].astype(np.float64)
     ref = np.exp(-np.abs(a[:, None] - b[None, :])).sum(axis=1)
     assert float((np.abs(y[pick, 0] - ref) / (1e-5 * ref + 1e-7)).max()) <= 1.0
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
+@pytest.mark.parametrize("r,k,n,batch,pad", [
+    (2, 8192, 1, 4, 0), (2, 1, 8192, 5, 0), (3, 8000, 255, 32, 0), (2, 257, 8100, 36, 4), (2, 8191, 2049, 1, 0),
+    (3, 4097, 4096, 3, 2), (2, 4096, 4097, 33, 1), (2, 6000, 3000, 100, 0), (1, 30000, 600, 8, 0), (2, 700, 20000, 64, 0),
+])
+def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
+    """Sums of operators beyond 8192 merged positions: either side the shorter one, one and several tiles of the short side (256
+    rows with 4-column lanes, 64 to 2048 with single columns), odd batches, rows that allow no 16-byte access (pad), sorted
+    anchors; bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(k + 3 * n + batch)
+    ab = [anchors(kind, q, k, n) for _ in range(r)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, g = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32)
+    padded = lambda rows: torch.full((rows, batch + pad), float("nan"), device="cuda")[:, :batch]
+    dx, dg, y, gx = padded(n), padded(k), padded(k), padded(n)
+    dx.copy_(dev(x)); dg.copy_(dev(g))
+    new = lambda *s: torch.full(s, float("nan"), device="cuda")
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    for step in range(2):
+        da, db, dw = dev(a), dev(b), dev(w)
+        ga, gb, gw = new(r, k), new(r, n), new(r)
+        flags = 0 if step == 0 else B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED
+        B.laplex_mix_apply(da, db, dw, dx, y, ws, flags | B.LAPLEX_SAVE_SCANS)
+        B.laplex_mix_apply_backward(da, db, dw, dx, dg, gx, ga, gb, gw, ws, flags | B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+        ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+        want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
+        assert_close("y", y.cpu().numpy(), ref, tol)
+        for name, got, rv, tv in zip(("gx", "ga", "gb", "gw"), (gx, ga, gb, gw), want, tols):
+            assert_close(name, got.cpu().numpy(), rv, tv)
+        for pick in ((0,), (1,), (2,), (3,), (1, 3)):             # the gradients one by one, the backward standing alone
+            outs = [padded(n) if i == 0 else new(*s) for i, s in enumerate(((n,), (r, k), (r, n), (r,)))]
+            outs = [v if i in pick else None for i, v in enumerate(outs)]
+            B.laplex_mix_apply_backward(da, db, dw, None if pick == (0,) else dx, dg, *outs, ws, flags)
+            torch.cuda.synchronize()
+            for i in pick:
+                assert_close(str(i), outs[i].cpu().numpy(), want[i], tols[i])
+        a, b = np.sort(a, axis=1), np.sort(b, axis=1)             # second round: both sides ascending
