@@ -336,9 +336,8 @@ struct MixLayout {
     size_t inner = 0, off_parts = 0, off_gyq = 0, off_gxq = 0, off_gxp = 0, off_partial = 0, total = 0;
     int lanes = 1;      // operators in flight at a time on the large path (each on a stream of its own)
     bool common = false;      // all operators in common launches (mix_kernels.hip); in place of the regions above:
-    size_t off_srow = 0, off_sp = 0, off_cuts = 0, off_recs = 0, off_sums = 0, off_fr = 0, off_p = 0, off_z = 0, off_scan = 0,
-           off_dot_long = 0, off_dot_short = 0, off_dot_total = 0;
-    Layout ops;               // scan scratch of one operator
+    size_t off_srow = 0, off_sp = 0, off_tied = 0, off_bound = 0, off_slots = 0, off_recs = 0, off_sorted = 0, off_tasks = 0, off_folds = 0, off_equal = 0,
+           off_sums = 0, off_fr = 0, off_p = 0, off_z = 0, off_dot_long = 0, off_dot_short = 0, off_dot_total = 0;
 };
 
 // Beyond the small path an operator is a chain of two dozen launches; while the matrices are small each of them fills a
@@ -347,15 +346,23 @@ struct MixLayout {
 constexpr int kMixLanes = 4;
 constexpr int64_t kMixLanesMaxElements = int64_t(1) << 24;      // (k + n) * batch up to which that pays
 
-// Common launches: what the two-launch sort takes (beyond it 16 operators fill the device one by one), and one chunk of tiles in
-// the scan of the merged sequence: 2^17 positions at 29 columns and more, 2^19 below.
-bool mix_common(int64_t k, int64_t n, int64_t batch)
+// Common launches: what the two-launch sort takes (beyond it one operator fills the device), and a short side whose tiles (64 to
+// 2048 rows) are few enough that each adds up the others itself: at 2^15 rows that is at most three times the tile's own bytes.
+// Small operators stay with k_small, which needs two launches fewer, until its one workgroup per 16 columns is what a call waits
+// for (us, k_small / common, forward; forward + backward): 2 x (1000 x 2048), batch 64: 31 / 42; 85 / 70; 2 x (4000 x 4000), batch
+// 64: 56 / 48; 148 / 90; 16 x (1000 x 2048), batch 64: 71 / 69; 189 / 127; batch 256: 312 / 145 forward + backward.
+constexpr int64_t kMixShortMax = int64_t(1) << 15;
+constexpr int64_t kMixCommonMin = 2048, kMixCommonElements = int64_t(1) << 20;
+bool mix_common(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
     const int64_t N = k + n;
-    if (N <= kSmallMax || N > kRunSortMax || k < 1 || n < 1 || batch < 1) return false;
-    if (batch > 65535 * (int64_t)kOpsLanes) return false;      // slabs are a grid dimension
-    return make_ops_layout(N, batch).max_chunks == 1;
+    if (N > kRunSortMax || k < 1 || n < 1 || batch < 1 || (k < n ? k : n) > kMixShortMax) return false;
+    return N > kSmallMax || (N >= kMixCommonMin && r * N >= (kMixCommonElements + batch - 1) / batch);
 }
+
+// Counting ranks costs r N^2 comparisons, two launches of the run sort about 23 us whatever the operators: 16 x 3048 positions 33
+// us / 23 us, 16 x 8000 100 / 25, 2 x 8000 18 / 24, one operator of 8192 12 / 22.
+bool mix_ranked(int64_t r, int64_t N) { return N <= kSmallMax && r * N * N <= 140000000; }
 
 int mix_lanes(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
@@ -369,20 +376,25 @@ MixLayout mix_layout(int64_t r, int64_t k, int64_t n, int64_t batch)
     M.lanes = mix_lanes(r, k, n, batch);
     M.inner = align_up(make_layout(k + n, k, batch).total);
     size_t o = M.inner * (size_t)r;
-    M.common = mix_common(k, n, batch);
+    M.common = mix_common(r, k, n, batch);
     if (M.common) {
         const size_t ops = (size_t)r, m = (size_t)(k < n ? k : n), l = (size_t)(k < n ? n : k), width = (size_t)mix_width(batch);
         const size_t slabs = ((size_t)batch + width - 1) / width, rows = sizeof(float) * ops * m * (size_t)batch;
-        M.ops = make_ops_layout(k + n, batch);
-        M.off_srow = o; o = align_up(o + sizeof(uint32_t) * ops * m);
-        M.off_sp = o;   o = align_up(o + sizeof(float) * ops * m);
-        M.off_cuts = o; o = align_up(o + sizeof(uint2) * ops * l);
-        M.off_recs = o; o = align_up(o + sizeof(uint4) * ops * l);
-        M.off_sums = o; o = align_up(o + sizeof(float) * ops * slabs * 2 * (size_t)mix_max_tiles((int64_t)m, batch) * width);
-        M.off_fr = o;   o = align_up(o + sizeof(float) * ops * slabs * m * 2 * width);
-        M.off_p = o;    o = align_up(o + rows);
-        M.off_z = o;    o = align_up(o + rows);
-        M.off_scan = o; o = align_up(o + M.ops.total * ops);
+        const size_t tasks = (size_t)mix_task_count((int64_t)m, (int64_t)l);
+        M.off_srow = o;   o = align_up(o + sizeof(uint32_t) * ops * m);
+        M.off_sp = o;     o = align_up(o + sizeof(float) * ops * m);
+        M.off_tied = o;   o = align_up(o + sizeof(uint32_t) * ops * m);
+        M.off_bound = o;  o = align_up(o + sizeof(uint32_t) * ops * (m + 2));
+        M.off_slots = o;  o = align_up(o + sizeof(uint2) * ops * (m + 1));
+        M.off_recs = o;   o = align_up(o + sizeof(uint4) * ops * l);
+        M.off_sorted = o; o = align_up(o + sizeof(uint4) * ops * l);
+        M.off_tasks = o;  o = align_up(o + sizeof(uint2) * ops * tasks);
+        M.off_folds = o;  o = align_up(o + sizeof(float) * ops * slabs * tasks * 2 * width);
+        M.off_equal = o;  o = align_up(o + sizeof(float) * ops * slabs * tasks * width);
+        M.off_sums = o;   o = align_up(o + sizeof(float) * ops * slabs * 2 * (size_t)mix_max_tiles((int64_t)m, batch) * width);
+        M.off_fr = o;     o = align_up(o + sizeof(float) * ops * slabs * m * 2 * width);
+        M.off_p = o;      o = align_up(o + rows);
+        M.off_z = o;      if (k < n) o = align_up(o + rows);      // (strict sums at the outputs wait there for the backward)
         M.off_dot_long = o;  o = align_up(o + sizeof(float) * slabs * ops * l);
         M.off_dot_short = o; o = align_up(o + sizeof(float) * slabs * ops * m);
         M.off_dot_total = o; o = align_up(o + sizeof(float) * slabs * ops * m);
@@ -416,12 +428,15 @@ struct MixCommon {
         : A{}, M(M_), base(base_), L(make_layout(k + n_, k, batch)), a(a_), b(b_), n(n_), st(st_), sum{}
     {
         const Plan P = plan_of(L, base);
-        A.ids = P.ids; A.pk = P.pk; A.counters = reinterpret_cast<const uint32_t*>(base + L.off_counters); A.op_ws = (int64_t)M.inner;
+        A.ids = P.ids; A.pk = P.pk; A.status = plan_status_word(L, base); A.op_ws = (int64_t)M.inner;
         A.k = k; A.N = (int)(k + n); A.short_b = n <= k; A.operators = (int)r;
         A.m = (int)(A.short_b ? n : k); A.l = (int)(A.short_b ? k : n);
         A.long_anchor = A.short_b ? a : b;
         A.srow = reinterpret_cast<uint32_t*>(base + M.off_srow); A.sp = reinterpret_cast<float*>(base + M.off_sp);
-        A.cuts = reinterpret_cast<uint2*>(base + M.off_cuts); A.recs = reinterpret_cast<uint4*>(base + M.off_recs);
+        A.tied = reinterpret_cast<uint32_t*>(base + M.off_tied); A.bound = reinterpret_cast<uint32_t*>(base + M.off_bound);
+        A.recs = reinterpret_cast<uint4*>(base + M.off_recs); A.sorted = reinterpret_cast<uint4*>(base + M.off_sorted);
+        A.slots = reinterpret_cast<uint2*>(base + M.off_slots); A.tasks = reinterpret_cast<uint2*>(base + M.off_tasks); A.task_count = (int)mix_task_count(A.m, A.l);
+        A.folds = reinterpret_cast<float*>(base + M.off_folds); A.equal = reinterpret_cast<float*>(base + M.off_equal);
         A.sums = reinterpret_cast<float*>(base + M.off_sums); A.fr = reinterpret_cast<float*>(base + M.off_fr);
         A.batch = batch; A.width = mix_width(batch); A.slabs = (int)((batch + A.width - 1) / A.width);
         sum.w = w;
@@ -434,47 +449,45 @@ struct MixCommon {
     {
         if (flags & LAPLEX_REUSE_PLAN) return LAPLEX_OK;
         const Plan P = plan_of(L, base);
-        LAPLEX_HIP(launch_run_sort(a, A.k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
+        if (mix_ranked(A.operators, A.N)) {
+            SmallArgs S = small_args(a, A.k, b, n, 1.0f, P, L, flags);      // no scan problem: the sort alone
+            S.op_a = A.k; S.op_b = n; S.op_ws = (int64_t)M.inner;
+            LAPLEX_HIP(launch_small(S, A.operators, st));
+        } else LAPLEX_HIP(launch_run_sort(a, A.k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
                                    P.ids, P.dh, P.pk, P.pk8, reinterpret_cast<uint32_t*>(base + L.off_counters),
                                    A.operators, A.k, n, (int64_t)M.inner, st));
-        LAPLEX_HIP(launch_mix_index(A, st));
+        LAPLEX_HIP(launch_mix_plan(A, st));
         return LAPLEX_OK;
     }
     // the rows v of the short side scanned, per operator
     int scan_short(const float* v, int64_t ldv) { LAPLEX_HIP(launch_mix_scan(A, v, ldv, st)); return LAPLEX_OK; }
-    // the products (p) and strict sums (z) of the rows v of the long side at the short rows, per operator
-    int scan_long(const float* v, int64_t ldv, bool want_p, bool want_z)
-    {
-        const Plan P = plan_of(L, base);
-        ScanProblem q{};
-        q.ids = P.ids; q.dh = P.dh; q.pk = P.pk; q.N = A.N; q.batch = A.batch;
-        const uint32_t k32 = (uint32_t)A.k, N32 = (uint32_t)A.N;
-        q.inj = v; q.ld_inj = ldv;
-        q.inj_lo = A.short_b ? 0 : k32; q.inj_hi = A.short_b ? k32 : N32;
-        q.res_lo = A.short_b ? k32 : 0; q.res_hi = A.short_b ? N32 : k32;
-        q.out_p = want_p ? p : nullptr; q.out_z = want_z ? z : nullptr;
-        q.tag = "mix";
-        LAPLEX_HIP(launch_scan_ops(q, M.ops, base + M.off_scan, reinterpret_cast<uint32_t*>(base + L.off_counters), A.operators, (int64_t)M.inner, st));
-        return LAPLEX_OK;
-    }
+    // the products and strict sums of the rows v of the long side at the short rows, per operator, left as S says
+    int scan_long(const float* v, int64_t ldv, const MixFolded& S) { LAPLEX_HIP(launch_mix_fold(A, v, ldv, S, st)); return LAPLEX_OK; }
+    // where the rows' dots of an anchor gradient go: a single slab's are the gradient
+    float* dots(float* grad, float* partial) const { return !grad ? nullptr : A.slabs == 1 ? grad : partial; }
     // sums over the operators and the rows' dots with u, at the long rows (from the scanned short side) ...
     int at_long(const float* u, int64_t ldu, float* out, int64_t ldo, float* grad)
     {
         MixGather S = sum;
-        S.u = grad ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo; S.dot1 = grad ? dot_long : nullptr;
+        S.u = grad ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo; S.dot1 = dots(grad, dot_long);
         LAPLEX_HIP(launch_mix_gather(A, S, false, st));
-        if (grad) LAPLEX_HIP(launch_mix_finish(A, dot_long, sum.w, A.l, grad, st));
+        if (grad && A.slabs > 1) LAPLEX_HIP(launch_mix_finish(A, dot_long, sum.w, A.l, grad, st));
         return LAPLEX_OK;
     }
-    // ... and at the short rows (from p and z); gw[q] = sum of the rows' dots with p
+    // ... and at the short rows (from p and z)
     int at_short(const float* u, int64_t ldu, float* out, int64_t ldo, float* grad, float* gw)
     {
         MixGather S = sum;
         S.u = grad || gw ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo;
         S.p = out || gw ? p : nullptr; S.z = grad ? z : nullptr;
-        S.dot1 = grad ? dot_short : nullptr; S.dot2 = gw ? dot_total : nullptr;
+        S.dot1 = dots(grad, dot_short); S.dot2 = gw ? dot_total : nullptr;
         LAPLEX_HIP(launch_mix_gather(A, S, true, st));
-        if (grad) LAPLEX_HIP(launch_mix_finish(A, dot_short, sum.w, A.m, grad, st));
+        return short_dots(grad, gw);
+    }
+    // the short rows' dots: with the strict sums the anchor gradients, with the products, added up, the weights' gradients
+    int short_dots(float* grad, float* gw)
+    {
+        if (grad && A.slabs > 1) LAPLEX_HIP(launch_mix_finish(A, dot_short, sum.w, A.m, grad, st));
         if (gw) LAPLEX_HIP(launch_mix_total(A, dot_total, gw, st));
         return LAPLEX_OK;
     }
@@ -487,7 +500,9 @@ int mix_common_forward(MixCommon& C, const float* x, int64_t ldx, float* y, int6
         LAPLEX_CHECK(C.scan_short(x, ldx));
         return C.at_long(nullptr, 0, y, ldy, nullptr);
     }
-    LAPLEX_CHECK(C.scan_long(x, ldx, true, (flags & LAPLEX_SAVE_SCANS) != 0));
+    MixFolded S{};
+    S.p = C.p; S.z = (flags & LAPLEX_SAVE_SCANS) ? C.z : nullptr;
+    LAPLEX_CHECK(C.scan_long(x, ldx, S));
     return C.at_short(nullptr, 0, y, ldy, nullptr, nullptr);
 }
 
@@ -502,19 +517,38 @@ int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* 
             LAPLEX_CHECK(C.at_long(gy, ldgy, nullptr, 0, ga));
         }
         if (gx || gb || gw) {      // <gy, L_q x> = <L_q^T gy, x>: the weights' gradients come from the short rows
-            LAPLEX_CHECK(C.scan_long(gy, ldgy, gx || gw, gb != nullptr));
-            LAPLEX_CHECK(C.at_short(x, ldx, gx, ldgx, gb, gw));
+            MixFolded S{};
+            S.p = gx ? C.p : nullptr;
+            S.u = gb || gw ? x : nullptr; S.ldu = ldx;
+            S.w = C.sum.w;
+            S.dot_z = C.dots(gb, C.dot_short); S.dot_p = gw ? C.dot_total : nullptr;
+            LAPLEX_CHECK(C.scan_long(gy, ldgy, S));
+            if (gx) LAPLEX_CHECK(C.at_short(nullptr, 0, gx, ldgx, nullptr, nullptr));
+            LAPLEX_CHECK(C.short_dots(gb, gw));
         }
         return LAPLEX_OK;
     }
     if (ga || gw) {
-        if (!saved) LAPLEX_CHECK(C.scan_long(x, ldx, true, true));
+        MixFolded S{};
+        S.p = C.p; S.z = C.z;
+        if (!saved) LAPLEX_CHECK(C.scan_long(x, ldx, S));
         LAPLEX_CHECK(C.at_short(gy, ldgy, nullptr, 0, ga, gw));
     }
     if (gx || gb) {
         LAPLEX_CHECK(C.scan_short(gy, ldgy));
         LAPLEX_CHECK(C.at_long(x, ldx, gx, ldgx, gb));
     }
+    return LAPLEX_OK;
+}
+
+// The plans of many small operators where sorting them beats ranking them: the flags then say that they are there.
+int mix_small_sorted(const MixLayout& M, const Layout& L, const Plan& P, char* base, const float* a, const float* b, int64_t r, int64_t k, int64_t n,
+                     uint32_t& flags, hipStream_t st)
+{
+    if ((flags & LAPLEX_REUSE_PLAN) || mix_ranked(r, k + n)) return LAPLEX_OK;
+    LAPLEX_HIP(launch_run_sort(a, k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
+                               P.ids, P.dh, P.pk, P.pk8, reinterpret_cast<uint32_t*>(base + L.off_counters), r, k, n, (int64_t)M.inner, st));
+    flags |= LAPLEX_REUSE_PLAN;
     return LAPLEX_OK;
 }
 
@@ -1271,6 +1305,7 @@ int laplex_mix_apply(const float* a, const float* b, const float* w, int64_t r, 
     if (k + n <= kSmallMax) {      // every operator in the same two launches
         const Layout L = make_layout(k + n, k, batch);
         const Plan P = plan_of(L, base);
+        LAPLEX_CHECK(mix_small_sorted(M, L, P, base, a, b, r, k, n, flags, st));
         SmallArgs S = small_args(a, k, b, n, 1.0f, P, L, flags);
         S.op_a = k; S.op_b = n; S.op_ws = (int64_t)M.inner;
         S.nprob = 1;
@@ -1341,6 +1376,7 @@ int laplex_mix_apply_backward(const float* a, const float* b, const float* w, in
         const Plan P = plan_of(L, base);
         const int64_t op_f = (int64_t)(M.inner / sizeof(float));
         float* zg = reinterpret_cast<float*>(base + L.off_small);
+        LAPLEX_CHECK(mix_small_sorted(M, L, P, base, a, b, r, k, n, flags, st));
         bool have_plan = (flags & LAPLEX_REUSE_PLAN) != 0;
         bool have_z = saved;
         if (gw && !saved) {        // the weights' gradients need the operators' own products (and leave the strict scans)

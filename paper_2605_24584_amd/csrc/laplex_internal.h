@@ -109,13 +109,13 @@ struct ScanGeom {
 
 inline int pow2_at_least(int64_t v) { int p = 1; while (p < v) p <<= 1; return p; }
 
-inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec, int max_lanes = 64)
+inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec)
 {
     ScanGeom g;
     g.vec = vec;
     g.items = vec == 4 ? kItemsVec4 : kItemsVec1;
     const int64_t groups = (batch + vec - 1) / vec;          // column groups of `vec`
-    g.bv = groups >= max_lanes ? max_lanes : pow2_at_least(groups < 1 ? 1 : groups);
+    g.bv = groups >= 64 ? 64 : pow2_at_least(groups < 1 ? 1 : groups);
     g.rv = 64 / g.bv;
     g.slabs = (int)((groups + g.bv - 1) / g.bv);
     if (g.slabs < 1) g.slabs = 1;
@@ -256,29 +256,6 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     }
     L.off_small = align_up(L.total);
     if (N <= kSmallMax) L.total = align_up(L.off_small + sizeof(float) * (size_t)N * (size_t)batch);
-    return L;
-}
-
-// Many operators of the same sizes in the same launches (blockIdx.z): rows are cut into slabs of kOpsLanes lanes, so a block is
-// 256 rows whatever the batch (with 64 lanes across the batch 16 operators of 36096 merged positions would be 64-row blocks with
-// lists and summaries of their own).  Scratch of one operator's scan, offsets from the start of that scratch.
-constexpr int kOpsLanes = 8;
-inline Layout make_ops_layout(int64_t N, int64_t batch)
-{
-    Layout L;
-    L.N = N; L.batch = batch; L.bpad = (batch + 3) / 4 * 4;
-    const ScanGeom g1 = scan_geom(N, batch, 1, kOpsLanes), g4 = scan_geom(N, batch, 4, kOpsLanes);
-    L.max_tiles = g1.tiles > g4.tiles ? g1.tiles : g4.tiles;
-    L.max_chunks = g1.chunks > g4.chunks ? g1.chunks : g4.chunks;
-    const size_t per = sizeof(float) * 2 * (size_t)L.max_tiles * (size_t)L.bpad;
-    size_t c = 0;
-    L.off_agg_scalar = c; c = align_up(c + sizeof(float) * 4 * 2 * (size_t)L.max_tiles);
-    L.off_agg_s = c;      c = align_up(c + per);
-    L.off_agg_q = c;      c = align_up(c + per);
-    L.off_car_f = c;      c = align_up(c + per);
-    L.off_car_e = c;      c = align_up(c + per);
-    L.off_blk_flags = c;  c = align_up(c + sizeof(uint32_t) * (size_t)L.max_tiles);
-    L.total = c;
     return L;
 }
 
@@ -433,11 +410,6 @@ struct ScanProblem {
     const PhaseIn* phase_in = nullptr;     // the same geometry (see PhaseIn)
 };
 hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
-// The same problem for `operators` plans at once: the plans op_ws bytes apart (p.ids, p.dh, p.pk and `counters` are the first
-// one's), out_p / out_z rows * batch elements apart, one injected matrix for all.  L = make_ops_layout (one chunk), scratch
-// L.total bytes per operator.  Without row reductions, stages and phases.
-hipError_t launch_scan_ops(const ScanProblem& p, const Layout& L, char* scratch, uint32_t* counters, int64_t operators, int64_t op_ws,
-                           hipStream_t st);
 
 // Phase modulation of the phased kernel (phase_kernels.hip): split a (rows, batch) matrix into its
 // cosine and sine halves, dst (rows, 2*batch) contiguous; merge two halves back and, if wanted, form
@@ -500,19 +472,34 @@ hipError_t launch_dot_ops(const float* u, int64_t ldu, const float* v, int64_t r
                           float* partial, float* out, hipStream_t st);
 
 // Sums of operators in common launches (mix_kernels.hip).  `short`: the side with fewer rows (m of them; the inputs if
-// short_b), `long`: the other one (l rows).
+// short_b), `long`: the other one (l rows).  Interval c of an operator: the long rows above short anchor c - 1 and not above c.
+constexpr int kMixWidth = 32;            // columns of a slab, at most
+constexpr int kMixTaskRows = 32;         // long rows that one row-lane folds
 struct MixPath {
-    const uint32_t* ids; const float* pk; const uint32_t* counters; int64_t op_ws;      // plan of operator 0; bytes to the next
+    const uint32_t* ids; const float* pk; const uint32_t* status; int64_t op_ws;      // plan of operator 0 (status: may be null); bytes to the next
     int64_t k; int N, m, l, short_b, operators;
     const float* long_anchor;      // [operators][l], the caller's
-    // part of the plan: the short side in sorted order; per long row how many short anchors are below it / below or equal
-    uint32_t* srow; float* sp;     // [operators][m]
-    uint2* cuts;                   // [operators][l]
-    // written by launch_mix_scan: records of the long rows (cuts and weights), tile sums, the scanned short side
-    uint4* recs;                   // [operators][l]
-    float* sums;                   // [operators][slabs][2][tiles][width]
-    float* fr;                     // [operators][slabs][m][2][width]
-    int64_t batch; int width, slabs, tiles;      // slabs of `width` columns (power of two <= 32); tiles: set by launch_mix_scan
+    // part of the plan, per operator:
+    uint32_t* srow; float* sp;     // [m]      the short side in sorted order: row, anchor
+    uint32_t* tied;                // [m]      0, or 1 + the first of the short rows with this anchor if long rows have it too
+    uint32_t* bound;               // [m + 2]  first long row, in sorted order, of every interval
+    uint4* recs;                   // [l]      by row: short anchors below, below or equal; decays from / to the neighbours
+    uint4* sorted;                 // [l]      in sorted order: row, the two decays, equal to a short anchor
+    uint2* slots;                  // [m + 1]  of every interval: its first task, its rows
+    uint2* tasks;                  // [task_count] stretches of at most kMixTaskRows sorted long rows of one interval: first, count
+    // written by launch_mix_fold, [operators][slabs][task_count][2 | 1][width]: per task its rows decayed to the short anchors above
+    // (without rows equal to it) and below; the rows equal to it (where there are any)
+    float* folds; float* equal; int task_count;
+    float* sums;                   // [operators][slabs][2][tiles][width] tile sums
+    float* fr;                     // [operators][slabs][m][2][width]     the scanned short side
+    int64_t batch; int width, slabs, tiles;      // slabs of `width` columns (power of two <= 32); tiles: set by the launchers
+};
+// What the scan of folded long rows leaves at the short rows: products and strict sums ([operators][m][batch], row order), and
+// their dots with the rows of u ([slabs][operators][m]); any may be null.
+struct MixFolded {
+    float* p; float* z;
+    const float* u; int64_t ldu; float* dot_z; float* dot_p;
+    const float* w;                               // [operators] mixing weights (a single slab's dot_z is scaled by them)
 };
 struct MixGather {
     const float* w;                               // [operators] mixing weights
@@ -521,11 +508,13 @@ struct MixGather {
     float* dot1; float* dot2;                     // [slabs][operators][rows], or null
     const float* p; const float* z;               // rows = true: [operators][m][batch], either may be null
 };
-constexpr int kMixWidth = 32;
 inline int mix_width(int64_t batch) { return batch >= kMixWidth ? kMixWidth : pow2_at_least(batch < 1 ? 1 : batch); }
 inline int64_t mix_max_tiles(int64_t m, int64_t batch) { const int64_t rows = 32 * (64 / mix_width(batch)); return (m + rows - 1) / rows; }
-hipError_t launch_mix_index(const MixPath& A, hipStream_t st);
+// The tasks of interval c start at c + bound[c] / kMixTaskRows: room for ceil(rows / kMixTaskRows) of them without a count.
+inline int64_t mix_task_count(int64_t m, int64_t l) { return m + 2 + l / kMixTaskRows; }
+hipError_t launch_mix_plan(const MixPath& A, hipStream_t st);
 hipError_t launch_mix_scan(const MixPath& A, const float* v, int64_t ldv, hipStream_t st);
+hipError_t launch_mix_fold(const MixPath& A, const float* v, int64_t ldv, const MixFolded& S, hipStream_t st);
 hipError_t launch_mix_gather(const MixPath& A, const MixGather& S, bool rows, hipStream_t st);
 hipError_t launch_mix_finish(const MixPath& A, const float* dot, const float* w, int64_t count, float* out, hipStream_t st);
 hipError_t launch_mix_total(const MixPath& A, const float* dot, float* out, hipStream_t st);

@@ -1,5 +1,5 @@
 // LAPLEX^(r), y = sum_q w_q L(a_q, b_q) x, with all operators in the same launches (Sec. 7, "Learned anchor geometry in neural
-// heads"), for operators whose merged sequence the two-launch sort takes and the narrow scan geometry covers in one chunk.
+// heads"), for operators whose merged sequence the two-launch sort takes.
 //
 // One side of an operator is shorter (a head over a vocabulary: few inputs, many outputs).  Nothing per operator is ever as
 // large as the long side times the batch:
@@ -7,7 +7,8 @@
 //                   F_s (rows at or before s) and R_s (rows at or after s); a row of the long side at anchor p is then
 //                   exp(-(p - p_lo)) F_lo + exp(-(p_hi - p)) R_hi of its two neighbours (Thm "Dual reduction", App. B.3), and
 //                   one kernel adds that up over the operators, in registers (k_mix_scan_reduce, k_mix_scan_down, k_mix_gather)
-//   long -> short   a scan of the merged sequence whose results are rows of the short side (launch_scan_ops), then the same
+//   long -> short   the other way round: the long rows between two short anchors are folded into two sums, decayed to the one
+//                   above and to the one below (k_mix_fold), these are scanned like rows of the short side, and the same
 //                   kernel in its other form adds the operators up
 // Anchor gradients are row products of the caller's matrices with the strict sums, formed where the sums are in registers.
 //
@@ -16,8 +17,10 @@
 // the operators together.
 //
 // Measured (MI355X, forward + backward): 16 operators of 32000 x 4096, batch 256: 2.97 ms one operator after the other on four
-// streams (320 launches, 4 GB of per-operator products and strict sums of the long side written and read) -> 0.76 ms in 14
-// launches.  Of the 13 TB/s that k_mix_gather reads there (80 us for 2 x 16 rows of 1 KB per output) most comes from the L2.
+// streams (320 launches, 4 GB of per-operator products and strict sums of the long side written and read) -> 0.55 ms in 15
+// launches; 16 of 1000 x 2048: 0.31 ms (k_small) -> 0.145.  Of the former 0.18 ms are k_mix_gather, which reads 2 x 16 rows per
+// output at 10 to 13 TB/s, most of it from the L2, 0.09 k_mix_fold (5.6 TB/s of the long rows), 0.11 the scans of what it
+// leaves, 0.09 the sort and the plan.
 #include "laplex_internal.h"
 
 namespace laplex {
@@ -56,10 +59,21 @@ __device__ __forceinline__ void store_cols(float* dst, const float* src)
     else dst[0] = src[0];
 }
 
+// Row j of the sorted short list, clamped to it.
+__device__ __forceinline__ int clamp_row(int j, int m) { return j < 0 ? 0 : (j < m ? j : m - 1); }
+
+// The sort's order of the anchors, not-a-numbers included: what is counted and searched by it is consistent whatever they hold.
+__device__ __forceinline__ uint32_t order_of(float f)
+{
+    const uint32_t u = __float_as_uint(f);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+
 // ---------------------------------------------------------------------------
-// From the merged order of an operator: its short side as a list in sorted order (row, anchor), and for every row of the long
-// side how many short anchors lie strictly below it and how many at or below it.  A workgroup takes 2048 merged positions and
-// counts the short ones before them itself (a few dozen KB of ids from the L2, instead of a launch that would count per tile).
+// From the merged order of an operator: its short side as a list in sorted order, the intervals' bounds, and for every row of the
+// long side how many short anchors lie strictly below it, how many at or below it, and its place among the long rows.  A
+// workgroup takes 2048 merged positions and counts the short ones before them itself (a few dozen KB of ids from the L2, instead
+// of a launch that would count per tile).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(kIndexThreads)
 k_mix_index(const MixPath A)
@@ -75,9 +89,15 @@ k_mix_index(const MixPath A)
     const int base = blockIdx.x * kIndexTile;
 
     int count = 0;                                        // (base is a multiple of 2048 and the ids start on 256 bytes)
-    for (int j = tid * 4; j < base; j += kIndexTile) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ids + j);
-        count += (is_short(v.x) ? 1 : 0) + (is_short(v.y) ? 1 : 0) + (is_short(v.z) ? 1 : 0) + (is_short(v.w) ? 1 : 0);
+    for (int j1 = tid * 4; j1 < base; j1 += 8 * kIndexTile) {
+        uint4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const uint4*>(ids + (j1 + q * kIndexTile < base ? j1 + q * kIndexTile : 0));
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int here = (is_short(v[q].x) ? 1 : 0) + (is_short(v[q].y) ? 1 : 0) + (is_short(v[q].z) ? 1 : 0) + (is_short(v[q].w) ? 1 : 0);
+            count += j1 + q * kIndexTile < base ? here : 0;
+        }
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) count += __shfl_xor(count, m);
@@ -102,78 +122,237 @@ k_mix_index(const MixPath A)
 
     uint32_t* srow = A.srow + op * A.m;
     float* sp = A.sp + op * A.m;
-    uint2* cuts = A.cuts + op * A.l;
+    uint32_t* tied = A.tied + op * A.m;
+    uint32_t* bound = A.bound + op * (A.m + 2);
+    uint4* recs = A.recs + op * A.l;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int j = j0 + i;
         if (j >= A.N) break;
         const float p = pk[j + 1];
+        const uint32_t key = order_of(p);
+        // Equal keys, in the stable order: outputs first, then inputs.  [a0, b0): the run; f0: its first input.
+        int a0 = j, b0 = j + 1, f0 = 0;
+        const bool run = order_of(pk[j]) == key || order_of(pk[j + 2]) == key;
+        if (run) {
+            a0 = 0;
+            for (int hi = j; a0 < hi;) { const int mid = (a0 + hi) >> 1; if (order_of(pk[mid + 1]) < key) a0 = mid + 1; else hi = mid; }
+            for (int hi = A.N; b0 < hi;) { const int mid = (b0 + hi) >> 1; if (order_of(pk[mid + 1]) <= key) b0 = mid + 1; else hi = mid; }
+            f0 = a0;
+            for (int hi = b0; f0 < hi;) { const int mid = (f0 + hi) >> 1; if (ids[mid] < k) f0 = mid + 1; else hi = mid; }
+        }
         if (is_short(id[i])) {
+            int not_above = j - s, first = 0;             // long rows at or below this anchor; 1 + first short row of the run
+            if (run) {
+                const int head = short_b ? s - (j - f0) : s - (j - a0);
+                if (!short_b) not_above = b0 - head - (f0 - a0);
+                first = (short_b ? f0 - a0 : b0 - f0) > 0 ? 1 + head : 0;
+            }
             srow[s] = short_b ? id[i] - k : id[i];
             sp[s] = p;
+            tied[s] = (uint32_t)first;
+            bound[s + 1] = (uint32_t)not_above;
             ++s;
-            continue;
+        } else {
+            int lo = s, hi = s;
+            if (run) {
+                if (short_b) hi = s + (b0 - f0);
+                else lo = s - (f0 - a0);
+            }
+            recs[short_b ? id[i] : id[i] - k] = make_uint4((uint32_t)lo, (uint32_t)hi, (uint32_t)(j - s), 0u);
         }
-        int lo = s, hi = s;
-        if (pk[j] == p || pk[j + 2] == p) {               // equal keys: outputs first, then inputs (the stable order)
-            int a0 = 0, a1 = j;                           // first position of the run
-            while (a0 < a1) { const int mid = (a0 + a1) >> 1; if (pk[mid + 1] < p) a0 = mid + 1; else a1 = mid; }
-            int b0 = j + 1, b1 = A.N;                     // one past its last
-            while (b0 < b1) { const int mid = (b0 + b1) >> 1; if (pk[mid + 1] <= p) b0 = mid + 1; else b1 = mid; }
-            int f0 = a0, f1 = b0;                         // its first input
-            while (f0 < f1) { const int mid = (f0 + f1) >> 1; if (ids[mid] < k) f0 = mid + 1; else f1 = mid; }
-            if (short_b) hi = s + (b0 - f0);
-            else lo = s - (f0 - a0);
-            lo = lo < 0 ? 0 : lo;                         // (not-a-number anchors order without comparing)
-            hi = hi > A.m ? A.m : hi;
+    }
+    if (blockIdx.x == 0 && tid == 0) { bound[0] = 0u; bound[A.m + 1] = (uint32_t)A.l; }
+}
+
+// Second launch of the plan: the long rows' decays to their short neighbours (rows in the caller's order for the gather, in sorted
+// order for the fold), and the fold's tasks.
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_records(const MixPath A)
+{
+    const int64_t op = blockIdx.y;
+    const int m = A.m, i = blockIdx.x * kMixThreads + threadIdx.x;
+    const float* sp = A.sp + op * m;
+    if (i < A.l) {
+        const uint4 r = A.recs[op * A.l + i];
+        const int lo = (int)r.x;
+        const float p = A.long_anchor[op * A.l + i];
+        const float el = lo > 0 ? expf(-(p - sp[lo - 1])) : 0.0f;
+        const float er = lo < m ? expf(-(sp[lo] - p)) : 0.0f;
+        A.recs[op * A.l + i] = make_uint4(r.x, r.y, __float_as_uint(el), __float_as_uint(er));
+        const bool equal = r.x != r.y;
+        A.sorted[op * A.l + r.z] = make_uint4((uint32_t)i, __float_as_uint(el), equal ? 0u : __float_as_uint(er), equal ? 1u : 0u);
+    }
+    if (i <= m) {
+        const uint32_t* bound = A.bound + op * (m + 2);
+        const int first = (int)bound[i], end = (int)bound[i + 1];
+        const int t0 = i + first / kMixTaskRows, t1 = i + 1 + end / kMixTaskRows;
+        uint2* tasks = A.tasks + op * A.task_count;
+        A.slots[op * (m + 1) + i] = make_uint2((uint32_t)t0, (uint32_t)(end - first));
+        for (int t = t0; t < t1; ++t) {
+            const int at = first + (t - t0) * kMixTaskRows;
+            const int n = at < end ? (end - at < kMixTaskRows ? end - at : kMixTaskRows) : 0;
+            tasks[t] = make_uint2((uint32_t)at, (uint32_t)n);
         }
-        cuts[short_b ? id[i] : id[i] - k] = make_uint2((uint32_t)lo, (uint32_t)hi);
+        if (i == m) for (int t = t1; t < A.task_count; ++t) tasks[t] = make_uint2(0u, 0u);
     }
 }
 
-// Row j of the sorted short list, clamped to it.
-__device__ __forceinline__ int clamp_row(int j, int m) { return j < 0 ? 0 : (j < m ? j : m - 1); }
+// ---------------------------------------------------------------------------
+// Fold: a row-lane takes one task, a few consecutive long rows of an interval in sorted order, and adds them up with the two
+// decays of their records.  Every row is read once per operator; what leaves is two rows per interval.  With 64 lanes across the
+// batch (UNI) a task is a wavefront's: its records are scalars, and no row-lane waits for a longer neighbour (16 operators of
+// 32000 x 4096, batch 256: 140 us with eight tasks of 32 columns a wavefront, busy with the longest of the eight).
+// ---------------------------------------------------------------------------
+template <int VEC, bool UNI>
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_fold(const MixPath A, const float* __restrict__ v, int64_t ldv, int lanes, int spans)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t op = blockIdx.y;
+    const int span = (int)blockIdx.x % spans, chunk = (int)blockIdx.x / spans;
+    const int c = UNI ? lane : lane & (lanes - 1);
+    const int t = UNI ? chunk * kMixWaves + wave : (chunk * kMixWaves + wave) * (64 / lanes) + lane / lanes;
+    if (t >= A.task_count) return;
+    const int64_t col = ((int64_t)span * lanes + c) * VEC;
+    const bool col_ok = col < A.batch;
+    const uint2 task = A.tasks[op * A.task_count + t];
+    const int n = (int)task.y;
+    if (n == 0) return;                                   // (nobody reads the sums of an empty task)
+    const uint4* recs = A.sorted + op * A.l + task.x;
+    float up[VEC], down[VEC], eq[VEC];
+    uint32_t any = 0u;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) up[e] = down[e] = eq[e] = 0.0f;
+    constexpr int AHEAD = 8;
+    for (int i0 = 0; i0 < n; i0 += AHEAD) {
+        uint4 rec[AHEAD];
+        float x[AHEAD][VEC];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) rec[i] = recs[i0 + i < n ? i0 + i : n - 1];
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) load_cols<VEC>(x[i], v + (int64_t)rec[i].x * ldv + col, col_ok && i0 + i < n);
+#pragma unroll
+        for (int i = 0; i < AHEAD; ++i) {
+            if (UNI && i0 + i >= n) break;
+            const float el = __uint_as_float(rec[i].y), er = __uint_as_float(rec[i].z);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { down[e] += el * x[i][e]; up[e] += er * x[i][e]; }
+            if (rec[i].w != 0u) {                         // equal to the short anchor above: kept apart (er is 0)
+                any = 1u;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) eq[e] += x[i][e];
+            }
+        }
+    }
+    if (col >= (int64_t)A.slabs * A.width) return;        // (columns that fill up the last slab are written, as zeros)
+    const int64_t slot = (op * A.slabs + (int64_t)(col / A.width)) * A.task_count + t;
+    const int in = (int)(col % A.width);
+    store_cols<VEC>(A.folds + slot * (2 * A.width) + in, up);
+    store_cols<VEC>(A.folds + slot * (2 * A.width) + A.width + in, down);
+    if (any) store_cols<VEC>(A.equal + slot * A.width + in, eq);
+}
+
+// Sum over the tasks of an interval (slot: its first task, its rows) of the vectors at base + task * stride.
+template <int VEC>
+__device__ __forceinline__ void load_interval(float* dst, uint2 slot, const float* base, int stride)
+{
+    const int n = (int)slot.y;
+    const float* at = base + (int64_t)slot.x * stride;
+    load_cols<VEC>(dst, at, n > 0);
+    for (int q = kMixTaskRows; q < n; q += kMixTaskRows) {
+        float t[VEC];
+        at += stride;
+        load_cols<VEC>(t, at, true);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) dst[e] += t[e];
+    }
+}
+
+// What the scans add at the kMixItems rows from j0 on of the short side: forward and backward the row itself; or (FOLDED) forward
+// the folded rows of the interval below it, backward those of the interval above it.
+template <int VEC, bool FOLDED>
+__device__ __forceinline__ void load_rows(const MixPath& A, int64_t op, int slab, int c, int j0, const float* __restrict__ v, int64_t ldv,
+                                          float (*f)[VEC], float (*b)[VEC])
+{
+    if constexpr (!FOLDED) {
+        const int64_t col = (int64_t)slab * A.width + c * VEC;
+        const uint32_t* srow = A.srow + op * A.m;
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) {
+            const int j = j0 + i;
+            load_cols<VEC>(f[i], v + (int64_t)srow[j < A.m ? j : A.m - 1] * ldv + col, col < A.batch && j < A.m);
+        }
+    } else {
+        const float* folds = A.folds + (op * A.slabs + slab) * (int64_t)A.task_count * (2 * A.width) + c * VEC;
+        const uint2* slots = A.slots + op * (A.m + 1);
+        uint2 slot[kMixItems + 1];
+#pragma unroll
+        for (int i = 0; i <= kMixItems; ++i) {
+            slot[i] = slots[j0 + i <= A.m ? j0 + i : A.m];
+            if (j0 + i > A.m) slot[i].y = 0u;
+        }
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) load_interval<VEC>(f[i], j0 + i < A.m ? slot[i] : make_uint2(0u, 0u), folds, 2 * A.width);
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) load_interval<VEC>(b[i], slot[i + 1], folds + A.width, 2 * A.width);
+    }
+}
+// The long rows equal to short anchor j, to be added to the forward value (they are in the interval of the first such anchor).
+template <int VEC>
+__device__ __forceinline__ void load_equal(const MixPath& A, int64_t op, int slab, int c, int j, float* t)
+{
+    const uint32_t* bound = A.bound + op * (A.m + 2);
+    const float* equal = A.equal + (op * A.slabs + slab) * (int64_t)A.task_count * A.width + c * VEC;
+    // (equal rows come last in their interval, and a task without any has not written its vector)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) t[e] = 0.0f;
+    const uint2* tasks = A.tasks + op * A.task_count;
+    const int first = (int)bound[j], end = (int)bound[j + 1];
+    const int t0 = j + first / kMixTaskRows, parts = (end - first + kMixTaskRows - 1) / kMixTaskRows;
+    for (int q = parts - 1; q >= 0; --q) {
+        const uint2 task = tasks[t0 + q];
+        if (task.y == 0u || A.sorted[op * A.l + task.x + task.y - 1].w == 0u) break;
+        float u[VEC];
+        load_cols<VEC>(u, equal + (int64_t)(t0 + q) * A.width, true);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) t[e] += u[e];
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Scan of the short side, first launch: per tile and slab the sum of its rows decayed to the tile's last row and to its first
 // one, as weighted sums (a row's two weights are one exponential of an anchor difference each, taken once per workgroup).
-// Workgroups behind the tiles turn the cuts of the long side into records (rows below and above, their two weights).
 // ---------------------------------------------------------------------------
-template <int VEC>
+template <int VEC, bool FOLDED>
 __global__ void __launch_bounds__(kMixThreads)
 k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
 {
     __shared__ float wf[kMixTileMax], wb[kMixTileMax];
-    __shared__ float part[2][kMixWaves][32];
+    __shared__ float part[2][kMixWaves][kMixWidth];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t op = blockIdx.y;
     const float* sp = A.sp + op * A.m;
     const int m = A.m;
-    const int tile_blocks = A.tiles * A.slabs;
-    if ((int)blockIdx.x >= tile_blocks) {
-        const int i = ((int)blockIdx.x - tile_blocks) * kMixThreads + tid;
-        if (i >= A.l) return;
-        const uint2 cut = A.cuts[op * A.l + i];
-        const float p = A.long_anchor[op * A.l + i];
-        const int lo = (int)cut.x;
-        const float el = lo > 0 ? expf(-(p - sp[lo - 1])) : 0.0f;
-        const float er = lo < m ? expf(-(sp[lo] - p)) : 0.0f;
-        A.recs[op * A.l + i] = make_uint4(cut.x, cut.y, __float_as_uint(el), __float_as_uint(er));
-        return;
-    }
     const int slab = (int)blockIdx.x % A.slabs, tile = (int)blockIdx.x / A.slabs;
     const int bv = A.width / VEC, rv = 64 / bv;
     const int c = lane & (bv - 1), rl = wave * rv + lane / bv;
     const int rows = kMixWaves * rv * kMixItems;
     const int base = tile * rows, last = clamp_row(base + rows - 1, m);
-    const int64_t col = (int64_t)slab * A.width + c * VEC;
-    const bool col_ok = col < A.batch;
-    const uint32_t* srow = A.srow + op * m;
-    float val[kMixItems][VEC];
+    float vf[kMixItems][VEC], vb[FOLDED ? kMixItems : 1][VEC];
+    load_rows<VEC, FOLDED>(A, op, slab, c, base + rl * kMixItems, v, ldv, vf, vb);
+    if (FOLDED) {
 #pragma unroll
-    for (int i = 0; i < kMixItems; ++i) {
-        const int j = base + rl * kMixItems + i;
-        load_cols<VEC>(val[i], v + (int64_t)srow[clamp_row(j, m)] * ldv + col, col_ok && j < m);
+        for (int i = 0; i < kMixItems; ++i) {
+            const int j = base + rl * kMixItems + i;
+            if (j < m && A.tied[op * m + j] == (uint32_t)j + 1u) {
+                float t[VEC];
+                load_equal<VEC>(A, op, slab, c, j, t);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) vf[i][e] += t[e];
+            }
+        }
     }
     const float p_first = sp[base], p_last = sp[last];
     for (int q = tid; q < rows; q += kMixThreads) {
@@ -189,7 +368,7 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
     for (int i = 0; i < kMixItems; ++i) {
         const float x = wf[rl * kMixItems + i], y = wb[rl * kMixItems + i];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { f[e] += x * val[i][e]; b[e] += y * val[i][e]; }
+        for (int e = 0; e < VEC; ++e) { f[e] += x * vf[i][e]; b[e] += y * (FOLDED ? vb[FOLDED ? i : 0][e] : vf[i][e]); }
     }
     for (int d = bv; d < 64; d <<= 1) {
 #pragma unroll
@@ -212,11 +391,13 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
 // ---------------------------------------------------------------------------
 // Second launch: a tile adds up the other tiles' sums itself, each brought to the tile by one exponential of an anchor
 // difference (a tile beyond the reach of an fp32 decay is not read), scans its row-lanes, and walks its rows in both directions.
-// fr[op][slab][row] = (F_row | R_row), 2 x width floats.
+// Rows of the short side: fr[op][slab][row] = (F_row | R_row), 2 x width floats.  FOLDED: F_j holds the long rows not above short
+// anchor j, R_j those above it; products F + R and strict sums R - (F without the rows equal to the anchor) leave row by row, or
+// as dots with the rows of u.
 // ---------------------------------------------------------------------------
-template <int VEC>
+template <int VEC, bool FOLDED>
 __global__ void __launch_bounds__(kMixThreads)
-k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
+k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const MixFolded O)
 {
     __shared__ float dec[kMixTileMax + 1];                // dec[q]: decay between rows base + q - 1 and base + q
     __shared__ float part[4][kMixWaves][32];              // wavefront totals and carries, forward and backward
@@ -229,15 +410,26 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
     const int c = lane & (bv - 1), r = lane / bv, rl = wave * rv + r;
     const int rows = kMixWaves * rv * kMixItems;
     const int base = tile * rows;
-    const int64_t col = (int64_t)slab * A.width + c * VEC;
-    const bool col_ok = col < A.batch;
-    const uint32_t* srow = A.srow + op * m;
     const int j0 = base + rl * kMixItems;
-    float val[kMixItems][VEC];
+    float vf[kMixItems][VEC], vr[FOLDED ? kMixItems : 1][VEC];
+    load_rows<VEC, FOLDED>(A, op, slab, c, j0, v, ldv, vf, vr);
+    // rows of the long side equal to a short anchor: 1 + the first short row with it, or 0
+    uint32_t tie[FOLDED ? kMixItems : 1];
+    if (FOLDED) {
 #pragma unroll
-    for (int i = 0; i < kMixItems; ++i) {
-        const int j = j0 + i;
-        load_cols<VEC>(val[i], v + (int64_t)srow[clamp_row(j, m)] * ldv + col, col_ok && j < m);
+        for (int i = 0; i < kMixItems; ++i) tie[FOLDED ? i : 0] = j0 + i < m ? A.tied[op * m + j0 + i] : 0u;
+    }
+    auto is_first = [&](int i) { return FOLDED && tie[FOLDED ? i : 0] == (uint32_t)(j0 + i) + 1u; };
+    if (FOLDED) {
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) {
+            if (is_first(i)) {
+                float t[VEC];
+                load_equal<VEC>(A, op, slab, c, j0 + i, t);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) vf[i][e] += t[e];
+            }
+        }
     }
     auto pos = [&](int j) { return sp[clamp_row(j, m)]; };
     for (int q = tid; q <= rows; q += kMixThreads) dec[q] = expf(-(pos(base + q) - pos(base + q - 1)));
@@ -277,13 +469,13 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
     for (int i = 0; i < kMixItems; ++i) {
         const float d = dec[rl * kMixItems + i];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) S[e] = d * S[e] + val[i][e];
+        for (int e = 0; e < VEC; ++e) S[e] = d * S[e] + vf[i][e];
     }
 #pragma unroll
     for (int i = kMixItems - 1; i >= 0; --i) {
         const float d = dec[rl * kMixItems + i + 1];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) U[e] = d * U[e] + val[i][e];
+        for (int e = 0; e < VEC; ++e) U[e] = d * U[e] + (FOLDED ? vr[FOLDED ? i : 0][e] : vf[i][e]);
     }
     for (int d = 1; d < rv; d <<= 1) {
         const float Df = expf(-(pos(j0 + kMixItems - 1) - pos(j0 - d * kMixItems + kMixItems - 1)));
@@ -331,23 +523,61 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
             R[e] = db * Rw[e] + (r < rv - 1 ? Ua : 0.0f);
         }
     }
-    const uint32_t poison = *(shift_bytes(A.counters, op * A.op_ws) + kPlanStatusWord) ? 0x7FC00000u : 0u;
-    float* out = A.fr + ((op * A.slabs + slab) * (int64_t)m) * (2 * A.width) + c * VEC;
+    const uint32_t poison = A.status && *shift_bytes(A.status, op * A.op_ws) ? 0x7FC00000u : 0u;
+    auto mark = [&](float x) { return __uint_as_float(__float_as_uint(x) | poison); };
+    if constexpr (!FOLDED) {
+        float* out = A.fr + ((op * A.slabs + slab) * (int64_t)m) * (2 * A.width) + c * VEC;
 #pragma unroll
-    for (int i = 0; i < kMixItems; ++i) {
-        const float d = dec[rl * kMixItems + i];
-        float t[VEC];
+        for (int i = 0; i < kMixItems; ++i) {
+            const float d = dec[rl * kMixItems + i];
+            float t[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + val[i][e]; t[e] = __uint_as_float(__float_as_uint(F[e]) | poison); }
-        if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width), t);
-    }
+            for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + vf[i][e]; t[e] = mark(F[e]); }
+            if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width), t);
+        }
 #pragma unroll
-    for (int i = kMixItems - 1; i >= 0; --i) {
-        const float d = dec[rl * kMixItems + i + 1];
-        float t[VEC];
+        for (int i = kMixItems - 1; i >= 0; --i) {
+            const float d = dec[rl * kMixItems + i + 1];
+            float t[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { R[e] = d * R[e] + val[i][e]; t[e] = __uint_as_float(__float_as_uint(R[e]) | poison); }
-        if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width) + A.width, t);
+            for (int e = 0; e < VEC; ++e) { R[e] = d * R[e] + vf[i][e]; t[e] = mark(R[e]); }
+            if (j0 + i < m) store_cols<VEC>(out + (int64_t)(j0 + i) * (2 * A.width) + A.width, t);
+        }
+    } else {
+        const int64_t col = (int64_t)slab * A.width + c * VEC;
+        const bool col_ok = col < A.batch;
+        // backward first: R of every row takes the place of what was added there
+#pragma unroll
+        for (int i = kMixItems - 1; i >= 0; --i) {
+            const float d = dec[rl * kMixItems + i + 1];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { R[e] = d * R[e] + vr[i][e]; vr[i][e] = R[e]; }
+        }
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) {
+            const int j = j0 + i;
+            const float d = dec[rl * kMixItems + i];
+            float P[VEC], Z[VEC], t[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + vf[i][e]; P[e] = mark(F[e] + vr[i][e]); t[e] = 0.0f; }
+            if (tie[i] != 0u) load_equal<VEC>(A, op, slab, c, (int)tie[i] - 1, t);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) Z[e] = mark(vr[i][e] - (F[e] - t[e]));
+            if (j >= m) continue;
+            const int64_t row = A.srow[op * m + j], at = (op * m + row) * A.batch + col;
+            if (O.p && col_ok) store_cols<VEC>(O.p + at, P);
+            if (O.z && col_ok) store_cols<VEC>(O.z + at, Z);
+            if (O.u) {                                   // uniform
+                float u[VEC], dz = 0.0f, dp = 0.0f;
+                load_cols<VEC>(u, O.u + row * O.ldu + col, col_ok);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) { dz += u[e] * Z[e]; dp += u[e] * P[e]; }
+                for (int q = 1; q < bv; q <<= 1) { dz += __shfl_xor(dz, q); dp += __shfl_xor(dp, q); }
+                const int64_t slot = ((int64_t)slab * A.operators + op) * m + row;
+                if (c == 0 && O.dot_z) O.dot_z[slot] = A.slabs == 1 ? O.w[op] * dz : dz;
+                if (c == 0 && O.dot_p) O.dot_p[slot] = dp;
+            }
+        }
     }
 }
 
@@ -357,7 +587,7 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv)
 //                  out_i = sum_q w_q (el F_lo + er R_lo'),   dot1[q][i] = sum_t u_it (strict R - strict F)
 //   ROWS = true    targets: the short side, whose products P_q and strict sums Z_q (either may be null) lie in memory:
 //                  out_j = sum_q w_q P_q[j],   dot1[q][j] = sum_t u_jt Z_q[j][t],   dot2[q][j] = sum_t u_jt P_q[j][t]
-// Dots are left per slab (dot[slab][q][row]); k_mix_finish adds the slabs.
+// Dots are left per slab (dot[slab][q][row]) for k_mix_finish to add; a single slab writes w_q dot1, the gradient, itself.
 // ---------------------------------------------------------------------------
 template <int VEC, int T, bool ROWS>
 __global__ void __launch_bounds__(kMixThreads)
@@ -440,7 +670,7 @@ k_mix_gather(const MixPath A, const MixGather S)
             }
             if (S.dot1) {
                 for (int d = 1; d < bv; d <<= 1) d1 += __shfl_xor(d1, d);
-                if (c == 0 && live[t]) S.dot1[((int64_t)slab * A.operators + q) * count + row[t]] = d1;
+                if (c == 0 && live[t]) S.dot1[((int64_t)slab * A.operators + q) * count + row[t]] = A.slabs == 1 ? wq * d1 : d1;
             }
             if (ROWS && S.dot2) {
                 for (int d = 1; d < bv; d <<= 1) d2 += __shfl_xor(d2, d);
@@ -468,17 +698,22 @@ k_mix_finish(const float* __restrict__ dot, const float* __restrict__ w, int sla
 }
 
 // out[q] = sum over slabs and rows of dot[slab][q][row]; one workgroup per operator, fixed order
-__global__ void __launch_bounds__(kMixThreads)
+constexpr int kTotalThreads = 1024;
+
+__global__ void __launch_bounds__(kTotalThreads)
 k_mix_total(const float* __restrict__ dot, int slabs, int operators, int count, float* __restrict__ out)
 {
-    __shared__ float red[kMixThreads];
+    __shared__ float red[kTotalThreads];
     const int64_t q = blockIdx.x;
     float s = 0.0f;
-    for (int i = threadIdx.x; i < count; i += kMixThreads)
-        for (int b = 0; b < slabs; ++b) s += dot[((int64_t)b * operators + q) * count + i];
+    for (int b = 0; b < slabs; ++b) {
+        const float* at = dot + ((int64_t)b * operators + q) * count;
+#pragma unroll 4
+        for (int i = threadIdx.x; i < count; i += kTotalThreads) s += at[i];
+    }
     red[threadIdx.x] = s;
     __syncthreads();
-    for (int d = kMixThreads / 2; d >= 1; d >>= 1) {
+    for (int d = kTotalThreads / 2; d >= 1; d >>= 1) {
         if ((int)threadIdx.x < d) red[threadIdx.x] += red[threadIdx.x + d];
         __syncthreads();
     }
@@ -486,8 +721,6 @@ k_mix_total(const float* __restrict__ dot, int slabs, int operators, int count, 
 }
 
 bool aligned_rows(const float* p, int64_t ld) { return !p || ((reinterpret_cast<uintptr_t>(p) & 15u) == 0 && ld % 4 == 0); }
-
-int scan_rows(const MixPath& A, int vec) { return kMixWaves * (64 / (A.width / vec)) * kMixItems; }
 
 template <int VEC, bool ROWS>
 void go_gather(const MixPath& A, const MixGather& S, hipStream_t st)
@@ -506,26 +739,55 @@ void go_gather(const MixPath& A, const MixGather& S, hipStream_t st)
 
 }  // namespace
 
-hipError_t launch_mix_index(const MixPath& A, hipStream_t st)
+hipError_t launch_mix_plan(const MixPath& A, hipStream_t st)
 {
-    LAPLEX_TIMED("mix_index", st, hipLaunchKernelGGL(k_mix_index, dim3((unsigned)((A.N + kIndexTile - 1) / kIndexTile), (unsigned)A.operators),
-                                                     dim3(kIndexThreads), 0, st, A));
+    LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_index, dim3((unsigned)((A.N + kIndexTile - 1) / kIndexTile), (unsigned)A.operators),
+                                                    dim3(kIndexThreads), 0, st, A));
+    const int64_t items = A.l > A.m + 1 ? A.l : A.m + 1;
+    LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_records, dim3((unsigned)((items + kMixThreads - 1) / kMixThreads), (unsigned)A.operators),
+                                                    dim3(kMixThreads), 0, st, A));
     return hipGetLastError();
 }
 
-hipError_t launch_mix_scan(const MixPath& A0, const float* v, int64_t ldv, hipStream_t st)
+namespace {
+
+template <int VEC, bool FOLDED>
+void go_scan(MixPath A, const float* v, int64_t ldv, const MixFolded& S, hipStream_t st)
 {
-    MixPath A = A0;
-    const bool v4 = A.batch % 4 == 0 && aligned_rows(v, ldv);
-    const int rows = scan_rows(A, v4 ? 4 : 1);
+    const int rows = kMixWaves * (64 / (A.width / VEC)) * kMixItems;
     A.tiles = (A.m + rows - 1) / rows;
-    const unsigned records = (unsigned)((A.l + kMixThreads - 1) / kMixThreads), work = (unsigned)(A.tiles * A.slabs);
-    auto go = [&](auto reduce, auto down) {
-        LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL(reduce, dim3(work + records, (unsigned)A.operators), dim3(kMixThreads), 0, st, A, v, ldv));
-        LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL(down, dim3(work, (unsigned)A.operators), dim3(kMixThreads), 0, st, A, v, ldv));
-    };
-    if (v4) go(k_mix_scan_reduce<4>, k_mix_scan_down<4>);
-    else go(k_mix_scan_reduce<1>, k_mix_scan_down<1>);
+    const dim3 grid((unsigned)(A.tiles * A.slabs), (unsigned)A.operators), block(kMixThreads);
+    if (A.tiles > 1)      // (a single tile has no others to add up)
+        LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL((k_mix_scan_reduce<VEC, FOLDED>), grid, block, 0, st, A, v, ldv));
+    LAPLEX_TIMED("mix_scan", st, hipLaunchKernelGGL((k_mix_scan_down<VEC, FOLDED>), grid, block, 0, st, A, v, ldv, S));
+}
+
+template <int VEC>
+void go_fold(const MixPath& A, const float* v, int64_t ldv, hipStream_t st)
+{
+    const int64_t groups = (A.batch + VEC - 1) / VEC;
+    const int lanes = groups >= 64 ? 64 : pow2_at_least(groups), spans = (int)((groups + lanes - 1) / lanes);
+    const int per = kMixWaves * (64 / lanes);
+    const dim3 grid((unsigned)((A.task_count + per - 1) / per * spans), (unsigned)A.operators), block(kMixThreads);
+    if (lanes == 64) LAPLEX_TIMED("mix_fold", st, hipLaunchKernelGGL((k_mix_fold<VEC, true>), grid, block, 0, st, A, v, ldv, lanes, spans));
+    else LAPLEX_TIMED("mix_fold", st, hipLaunchKernelGGL((k_mix_fold<VEC, false>), grid, block, 0, st, A, v, ldv, lanes, spans));
+}
+
+}  // namespace
+
+hipError_t launch_mix_scan(const MixPath& A, const float* v, int64_t ldv, hipStream_t st)
+{
+    if (A.batch % 4 == 0 && aligned_rows(v, ldv)) go_scan<4, false>(A, v, ldv, MixFolded{}, st);
+    else go_scan<1, false>(A, v, ldv, MixFolded{}, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_fold(const MixPath& A, const float* v, int64_t ldv, const MixFolded& S, hipStream_t st)
+{
+    if (A.batch % 4 == 0 && aligned_rows(v, ldv)) go_fold<4>(A, v, ldv, st);
+    else go_fold<1>(A, v, ldv, st);
+    if (A.batch % 4 == 0 && aligned_rows(S.u, S.ldu)) go_scan<4, true>(A, nullptr, 0, S, st);
+    else go_scan<1, true>(A, nullptr, 0, S, st);
     return hipGetLastError();
 }
 
@@ -546,7 +808,7 @@ hipError_t launch_mix_finish(const MixPath& A, const float* dot, const float* w,
 
 hipError_t launch_mix_total(const MixPath& A, const float* dot, float* out, hipStream_t st)
 {
-    LAPLEX_TIMED("mix_finish", st, hipLaunchKernelGGL(k_mix_total, dim3((unsigned)A.operators), dim3(kMixThreads), 0, st,
+    LAPLEX_TIMED("mix_finish", st, hipLaunchKernelGGL(k_mix_total, dim3((unsigned)A.operators), dim3(kTotalThreads), 0, st,
                                                       dot, A.slabs, A.operators, A.m, out));
     return hipGetLastError();
 }

@@ -35,7 +35,6 @@
 #include "permute_tile.h"
 
 #include <string>
-#include <type_traits>
 
 
 namespace laplex {
@@ -86,28 +85,7 @@ struct ScanArgs {
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
-    int64_t op_ws, op_scratch, op_p, op_z;   // launches over several operators: bytes between plans and between scan scratches, elements between results
 };
-
-// The arguments of operator q of a launch over several (all strides are zero in a launch over one).
-__device__ __forceinline__ ScanArgs of_operator(ScanArgs A, unsigned q)
-{
-    auto move = [](auto* p, int64_t bytes) { return reinterpret_cast<decltype(p)>(reinterpret_cast<uintptr_t>(p) + (uintptr_t)bytes); };
-    const int64_t w = (int64_t)q * A.op_ws, s = (int64_t)q * A.op_scratch;
-    A.ids = move(A.ids, w); A.dh = move(A.dh, w); A.pk = move(A.pk, w); A.counters = move(A.counters, w);
-    A.l1.scalar = move(A.l1.scalar, s); A.l1.s = move(A.l1.s, s); A.l1.q = move(A.l1.q, s);
-    A.l1.car_f = move(A.l1.car_f, s); A.l1.car_e = move(A.l1.car_e, s); A.blk_flags = move(A.blk_flags, s);
-    A.out_p = A.out_p ? A.out_p + q * A.op_p : nullptr;
-    A.out_z = A.out_z ? A.out_z + q * A.op_z : nullptr;
-    return A;
-}
-// (A kernel for one operator reads the launch's arguments where they are: moving them cost the Gram form's downsweep 2 %.)
-template <bool OPS>
-__device__ __forceinline__ std::conditional_t<OPS, ScanArgs, const ScanArgs&> args_of(const ScanArgs& A, unsigned q)
-{
-    if constexpr (OPS) return of_operator(A, q);
-    else return A;
-}
 
 constexpr int kFlagInj = 1, kFlagRes = 2;
 
@@ -936,11 +914,10 @@ k_phase_split_blocks(const ScanArgs A, int from_list)
 // ---------------------------------------------------------------------------
 constexpr int kLoneWaves = 4;
 
-template <int VEC, bool STRICT, bool OPS = false>
+template <int VEC, bool STRICT>
 __global__ void __launch_bounds__(kLoneWaves * 64)
-k_scan_reduce_wave(const ScanArgs A0)
+k_scan_reduce_wave(const ScanArgs A)
 {
-    const ScanArgs& A = args_of<OPS>(A0, blockIdx.z);
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -1102,16 +1079,15 @@ k_spine_top(const Level L, int64_t bpad)
 // ---------------------------------------------------------------------------
 // spine, level 2 -> 1: push the chunk carries down to the tiles of each chunk
 // ---------------------------------------------------------------------------
-template <int VEC, bool STRICT, bool OPS = false>
+template <int VEC, bool STRICT>
 __global__ void __launch_bounds__(kScanThreads)
-k_spine_down(const ScanArgs A0)
+k_spine_down(const ScanArgs A)
 {
-    const ScanArgs& A = args_of<OPS>(A0, blockIdx.z >> 1);
     __shared__ WaveSegs<VEC> W;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int bv = A.bv, rv = A.rv;
     const int c = lane & (bv - 1), r = lane >> A.bv_log2;
-    const int dir = OPS ? blockIdx.z & 1 : blockIdx.z;
+    const int dir = blockIdx.z;
     const int64_t chunk = blockIdx.x;
 
     // The list of the blocks the heavy downsweep must visit, when the reduce saw every tile itself (with a
@@ -1295,11 +1271,10 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 // WAVES: wavefronts of the workgroup (sizes the LDS buffer); RED: the row reduction is wanted (out_red);
 // ZS: the reduction takes in the saved strict scans (A.zs) -- without them the kernel fits in 128 registers
 // at scalar lanes, and a compute unit holds two workgroups of eight wavefronts instead of one.
-template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS = RED, bool OPS = false>
+template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS = RED>
 __global__ void __launch_bounds__(WAVES * 64)
-k_scan_down(const ScanArgs A0)
+k_scan_down(const ScanArgs A)
 {
-    const ScanArgs& A = args_of<OPS>(A0, blockIdx.z);
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     // One LDS buffer, used twice: first for the exchange of wavefront summaries, then (strict scans only)
     // for the per-row strict forward values, which would otherwise cost ITEMS * VEC registers per lane.
@@ -1312,7 +1287,7 @@ k_scan_down(const ScanArgs A0)
     if (A.down_from_list && blockIdx.x >= A.counters[1]) return;
     const int64_t tile = A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
     const int flags = (int)A.blk_flags[tile];
-    if (!OPS && (flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) return;
+    if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) return;
     const uint32_t poison = plan_poison(A.counters);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -2784,7 +2759,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     if (p.out_red) v4 = v4 && aligned16(p.w) && p.ld_w % 4 == 0 && (!p.zs || aligned16(p.zs));
     const ScanGeom g = scan_geom(p.N, p.batch, v4 ? 4 : 1);
 
-    ScanArgs A{};
+    ScanArgs A;
     A.ids = p.ids; A.dh = p.dh; A.pk = p.pk; A.pk8 = p.pk8; A.N = p.N;
     A.inj = p.inj; A.ld_inj = p.ld_inj; A.inj_lo = p.inj_lo; A.inj_hi = p.inj_hi;
     A.res_lo = p.res_lo; A.res_hi = p.res_hi;
@@ -2853,53 +2828,6 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         LAPLEX_TIMED("sum_slabs", st, hipLaunchKernelGGL(k_sum_slabs, dim3((unsigned)gsz), dim3(256), 0, st,
                                                          (const float*)A.red_partial, rows, g.slabs, p.out_red));
     }
-    return hipGetLastError();
-}
-
-namespace {
-
-template <int VEC, bool STRICT>
-void launch_ops(const ScanArgs& A, const ScanGeom& g, const std::string& tag, int64_t operators, hipStream_t st)
-{
-    const unsigned z = (unsigned)operators;
-    const std::string fr = "scan_reduce." + tag, fs = "scan_spine." + tag, fd = "scan_down." + tag;
-    LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wave<VEC, STRICT, true>),
-                                                    dim3((unsigned)((g.tiles + kLoneWaves - 1) / kLoneWaves), (unsigned)g.slabs, z), dim3(kLoneWaves * 64), 0, st, A));
-    LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT, true>), dim3(1, (unsigned)g.slabs, 2 * z), dim3(kScanThreads), 0, st, A));
-    constexpr int WAVES = VEC == 4 ? kBlockWavesNarrow : kScanWaves;
-    LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down<VEC, STRICT, WAVES, false, false, true>),
-                                                    dim3((unsigned)g.blocks, (unsigned)g.slabs, z), dim3(WAVES * 64), 0, st, A));
-}
-
-}  // namespace
-
-hipError_t launch_scan_ops(const ScanProblem& p, const Layout& L, char* scratch, uint32_t* counters, int64_t operators, int64_t op_ws,
-                           hipStream_t st)
-{
-    bool v4 = p.batch % 4 == 0 && aligned16(p.inj) && p.ld_inj % 4 == 0;
-    v4 = v4 && (!p.out_p || aligned16(p.out_p)) && (!p.out_z || aligned16(p.out_z));
-    const ScanGeom g = scan_geom(p.N, p.batch, v4 ? 4 : 1, kOpsLanes);
-    if (g.chunks > 1 || g.sub_shift) return hipErrorInvalidValue;
-    const int64_t res_rows = (int64_t)p.res_hi - (int64_t)p.res_lo;
-    ScanArgs A{};
-    A.ids = p.ids; A.dh = p.dh; A.pk = p.pk; A.N = p.N;
-    A.inj = p.inj; A.ld_inj = p.ld_inj; A.inj_lo = p.inj_lo; A.inj_hi = p.inj_hi; A.res_lo = p.res_lo; A.res_hi = p.res_hi;
-    A.out_p = p.out_p; A.ld_p = p.batch; A.out_z = p.out_z; A.ld_z = p.batch; A.ld_red = 1;
-    A.batch = p.batch; A.bpad = L.bpad;
-    A.bv = g.bv; A.bv_log2 = ilog2(g.bv); A.rv = g.rv; A.tile_rows = g.tile_rows; A.slabs = g.slabs;
-    A.chunk_tiles = g.chunk_tiles; A.spine_items = g.spine_items; A.waves = g.waves;
-    A.spine_rows = g.tile_rows; A.blocks = g.blocks;
-    A.blk_flags = reinterpret_cast<uint32_t*>(scratch + L.off_blk_flags);
-    A.l1 = Level{reinterpret_cast<float4*>(scratch + L.off_agg_scalar), reinterpret_cast<float*>(scratch + L.off_agg_s),
-                 reinterpret_cast<float*>(scratch + L.off_agg_q), reinterpret_cast<float*>(scratch + L.off_car_f),
-                 reinterpret_cast<float*>(scratch + L.off_car_e), g.tiles};
-    A.l2.count = g.chunks;
-    A.counters = counters;
-    A.op_ws = op_ws; A.op_scratch = (int64_t)L.total; A.op_p = A.op_z = res_rows * p.batch;
-    const std::string tag = p.tag ? p.tag : "scan";
-    const bool strict = p.out_z != nullptr;
-    if (v4) { if (strict) launch_ops<4, true>(A, g, tag, operators, st); else launch_ops<4, false>(A, g, tag, operators, st); }
-    else    { if (strict) launch_ops<1, true>(A, g, tag, operators, st); else launch_ops<1, false>(A, g, tag, operators, st); }
     return hipGetLastError();
 }
 

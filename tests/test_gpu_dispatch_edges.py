@@ -92,13 +92,39 @@ def test_run_sort_order_and_decays(oracle, N, kind):
     assert float((np.abs(y[pick, 0] - ref) / (1e-5 * ref + 1e-7)).max()) <= 1.0
 
 
+def test_mix_common_launches_non_finite_anchors(oracle):
+    """Values are unspecified, but the calls end, and the workspace serves a clean problem afterwards."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(77)
+    r, batch = 2, 8
+    for k, n in ((7000, 3000), (3000, 7000)):
+        x, g = dev(q.normal(size=(n, batch)).astype(np.float32)), dev(q.normal(size=(k, batch)).astype(np.float32))
+        ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+        w = np.array([0.5, -2.0], dtype=np.float32)
+        for bad in (True, False):
+            ab = [anchors("ties", q, k, n) for _ in range(r)]
+            a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+            if bad:
+                a[0, ::50] = np.nan; a[1, ::7] = -np.nan; a[:, 3] = np.inf; a[:, 4] = -np.inf
+                b[0, ::33] = -np.nan; b[1, ::11] = np.nan; b[:, 5] = np.inf; b[:, 6] = -np.inf
+            out = [torch.zeros(*v, device="cuda") for v in ((k, batch), (n, batch), (r, k), (r, n), (r,))]
+            B.laplex_mix_apply(dev(a), dev(b), dev(w), x, out[0], ws, B.LAPLEX_SAVE_SCANS)
+            B.laplex_mix_apply_backward(dev(a), dev(b), dev(w), x, g, *out[1:], ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+            torch.cuda.synchronize()
+        ref, tol = oracle.mix_apply(a, b, w, x.cpu().numpy(), brute=False)
+        assert_close("y", out[0].cpu().numpy(), ref, tol)
+
+
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
 @pytest.mark.parametrize("r,k,n,batch,pad", [
     (2, 8192, 1, 4, 0), (2, 1, 8192, 5, 0), (3, 8000, 255, 32, 0), (2, 257, 8100, 36, 4), (2, 8191, 2049, 1, 0),
     (3, 4097, 4096, 3, 2), (2, 4096, 4097, 33, 1), (2, 6000, 3000, 100, 0), (1, 30000, 600, 8, 0), (2, 700, 20000, 64, 0),
+    (2, 9000, 31, 16, 0), (1, 33, 9001, 2, 0),                    # hundreds of long rows between two short ones: several tasks each
+    (16, 40, 2008, 32, 0), (16, 40, 2007, 32, 0), (2, 2000, 48, 256, 0), (1, 1, 2047, 512, 0),     # the first sizes on common launches
+    (3, 6831, 1, 1, 0), (3, 1, 6832, 1, 0), (16, 1500, 1500, 1, 0),             # the last operators ranked by counting, the first sorted
 ])
 def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
-    """Sums of operators beyond 8192 merged positions: either side the shorter one, one and several tiles of the short side (256
+    """Sums of operators in common launches: either side the shorter one, one and several tiles of the short side (256
     rows with 4-column lanes, 64 to 2048 with single columns), odd batches, rows that allow no 16-byte access (pad), sorted
     anchors; bars of test_gpu_parity."""
     from test_gpu_parity import anchors, assert_close
