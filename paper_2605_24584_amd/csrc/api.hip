@@ -225,7 +225,7 @@ SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float
     S.a = a; S.b = b; S.k = k; S.n = n; S.tau = tau;
     S.ids = P.ids; S.dh = P.dh; S.pk = P.pk;
     S.reuse_plan = (flags & LAPLEX_REUSE_PLAN) ? 1 : 0;
-    S.batch = L.batch; S.cols = small_cols(L.batch);
+    S.batch = L.batch;
     return S;
 }
 
@@ -348,16 +348,17 @@ constexpr int64_t kMixLanesMaxElements = int64_t(1) << 24;      // (k + n) * bat
 
 // Common launches: what the two-launch sort takes (beyond it one operator fills the device), and a short side whose tiles (64 to
 // 2048 rows) are few enough that each adds up the others itself: at 2^15 rows that is at most three times the tile's own bytes.
-// Small operators stay with k_small, which needs two launches fewer, until its one workgroup per 16 columns is what a call waits
-// for (us, k_small / common, forward; forward + backward): 2 x (1000 x 2048), batch 64: 31 / 42; 85 / 70; 2 x (4000 x 4000), batch
-// 64: 56 / 48; 148 / 90; 16 x (1000 x 2048), batch 64: 71 / 69; 189 / 127; batch 256: 312 / 145 forward + backward.
+// Small operators stay with k_small, two to four launches fewer, until the rows that its chunks read again, about r N^2 batch / 512,
+// are what a call waits for (us, k_small / common, forward; forward + backward): 2 x (2048 x 1000), batch 64 (1.2e9): 24 / 34; 58 / 72;
+// 16 x (1000 x 2048), batch 64 (9.5e9): 58 / 69; 149 / 128; 2 x (4000 x 4000), batch 64 (8.2e9): 61 / 49; 134 / 91; 16 x (4000 x 4000),
+// batch 64 (6.6e10): 198 / 77; 477 / 150.
 constexpr int64_t kMixShortMax = int64_t(1) << 15;
-constexpr int64_t kMixCommonMin = 2048, kMixCommonElements = int64_t(1) << 20;
+constexpr double kMixCommonWork = 8e9;
 bool mix_common(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
     const int64_t N = k + n;
     if (N > kRunSortMax || k < 1 || n < 1 || batch < 1 || (k < n ? k : n) > kMixShortMax) return false;
-    return N > kSmallMax || (N >= kMixCommonMin && r * N >= (kMixCommonElements + batch - 1) / batch);
+    return N > kSmallMax || (double)r * (double)(N * N) * (double)batch >= kMixCommonWork;
 }
 
 // Counting ranks costs r N^2 comparisons, two launches of the run sort about 23 us whatever the operators: 16 x 3048 positions 33

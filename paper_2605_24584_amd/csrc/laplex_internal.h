@@ -445,12 +445,10 @@ struct SmallArgs {
     uint32_t* ids; float* dh; float* pk;       // the plan in the workspace: written (slab 0), or read if reuse_plan
     int64_t op_a, op_b, op_ws;
     int reuse_plan;                            // the workspace holds the plan: no sort
-    int write_dh;                              // set by the launcher: the decays are stored beside the plan
-    int64_t batch; int cols;                   // cols: power of two <= 16
+    int64_t batch; int cols;                   // cols: set by the launcher, power of two <= 16
     int nprob; SmallProblem prob[2];
 };
 hipError_t launch_small(const SmallArgs& A, int64_t operators, hipStream_t st);
-inline int small_cols(int64_t batch) { int c = 1; while (c < batch && c < 16) c <<= 1; return c; }
 
 // LAPLEX^(r) helpers (phase_kernels.hip).  parts: r contiguous (rows, batch) matrices; w, scale: device memory.
 //   combine: y = sum_q w[q] parts[q];  scale: dst (contiguous) = scale[0] * src;  accumulate: dst (+)= src (contiguous);

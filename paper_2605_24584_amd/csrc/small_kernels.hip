@@ -1,17 +1,11 @@
 // Small problems in two launches.  When the merged sequence a ++ b has at most kSmallMax positions the
 // whole path of one call (Sec. 3: sort, then the prefix recurrence and its mirror image) is one launch
-// that sorts (k_small_rank: ranks by counting, over the whole device) and one that holds the plan of an
-// operator in LDS and runs the decays, the decayed scans in both directions and the scatter (k_small),
+// that sorts (k_small_rank: ranks by counting, over the whole device) and one that runs the decayed scans in both directions
+// and scatters the results (k_small),
 // where the large path needs some thirty launches of a few microseconds each.  (App. "GPU runtime": below
 // n = 2^17 the paper's curves are flat at the cost of the launches.)  Several operators (the r anchor
 // pairs of a sum of operators) and several slabs of batch columns are separate workgroups of a launch.
 //
-// Layout of the work: a workgroup of 16 wavefronts handles C <= 16 batch columns; lane l of a wavefront
-// works on column l % C and is row-lane l / C of the wavefront's 64 / C (adjacent lanes read adjacent
-// columns of one row), so a column has RL = 1024 / C row-lanes, each walking 8 consecutive rows per
-// sweep of RS = 8 * RL rows.  Inside a row-lane decays are multiplied up (at most 8 factors); every
-// longer decay is exp of an anchor difference; row-lanes are combined by wavefront shuffles, wavefronts
-// and sweeps through LDS.
 // The numbers carried are those of the large path: F (inclusive decayed sum) and E (the sum over
 // strictly smaller keys), summarised per segment as (D, S, H, Q):
 //     F_out = D F_in + S,    E_out = H ? D F_in + Q : E_in.
@@ -35,146 +29,6 @@ __device__ __forceinline__ uint32_t small_float_to_key(float f)
 __device__ __forceinline__ float small_key_to_float(uint32_t key)
 {
     return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xFFFFFFFFu));
-}
-
-struct SmallShared {
-    uint32_t* id;      // [N]      sorted ids
-    float* p;          // [N + 2]  sorted anchors between -inf and +inf
-    float* dh;         // [N + 1]  decay into row j from row j - 1; negative: same key
-};
-
-// One direction of one scan problem.  DIR = 0: ascending keys; DIR = 1: descending (the mirror image).
-// q counts rows in processing order.  The first direction parks its results at the result rows
-// (out_p <- F, out_z <- -E); the second adds its own and finishes them:  out_p = F + R - v,  out_z = G - E.
-template <int DIR, bool STRICT>
-__device__ __forceinline__ void small_pass(const SmallProblem& P, const SmallShared& sh, int N, int64_t batch,
-                                           int C, int64_t col0, float* wtot /* [4][256] */)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int RPW = 64 / C;                     // row-lanes per wavefront
-    const int c = lane % C, rls = lane / C;     // adjacent lanes hold adjacent columns of a row: a load touches RPW rows
-    const int RL = kSmallWaves * RPW;
-    const int RS = RL * kSmallItems;
-    const int64_t col = col0 + c;
-    const bool col_ok = col < batch;
-    const int sweeps = (N + RS - 1) / RS;
-    auto pos = [&](int q) -> float { return DIR ? -sh.p[N - q] : sh.p[q + 1]; };      // q in -1 .. N
-    float Fc = 0.0f, Ec = 0.0f;                 // state at the end of the previous sweep
-    for (int s = 0; s < sweeps; ++s) {
-        const int q0 = s * RS + (wave * RPW + rls) * kSmallItems;
-        float v[kSmallItems], F0[kSmallItems], E0[kSmallItems], cf[kSmallItems];
-        uint32_t idr[kSmallItems];
-        int seen = 0;
-        {
-            float F = 0.0f, E = 0.0f, prod = 1.0f;
-            int sn = 0;
-#pragma unroll
-            for (int i = 0; i < kSmallItems; ++i) {
-                const int q = q0 + i;
-                const bool live = q < N;
-                const int row = live ? (DIR ? N - 1 - q : q) : 0;
-                const uint32_t id = live ? sh.id[row] : 0xFFFFFFFFu;
-                const float d = live ? (DIR ? sh.dh[row + 1] : sh.dh[row]) : -1.0f;     // past the end: transparent
-                const bool h = d >= 0.0f;
-                float val = 0.0f;
-                if (live && col_ok && id >= P.inj_lo && id < P.inj_hi) val = P.inj[(int64_t)(id - P.inj_lo) * P.ld_inj + col];
-                E = h ? d * F : E;
-                F = (h ? E : F) + val;
-                prod *= h ? d : 1.0f;
-                sn |= h ? 1 : 0;
-                v[i] = val; F0[i] = F; E0[i] = E; cf[i] = prod; idr[i] = id;
-                seen |= sn << i;
-            }
-        }
-        // Everything beyond a row-lane is combined with decays taken from the anchors, never with products
-        // of decays (a product of m equal factors carries m times the factor's rounding error, and on a
-        // regular grid the factors ARE equal).  endq(r): the last row of row-lane r of this sweep.
-        auto endq = [&](int r) -> int { const int q = s * RS + (r + 1) * kSmallItems - 1; return q < N ? q : N - 1; };
-        const int rl = wave * RPW + rls;
-        // inclusive scan over the row-lanes of the wavefront (lanes C apart hold the same column): (S, Q, H) of
-        // the row-lanes rl - 2^j + 1 .. rl; the decay across them is exp(-(anchor at their end - anchor before them))
-        float S = F0[kSmallItems - 1], Q = E0[kSmallItems - 1];
-        int H = (seen >> (kSmallItems - 1)) & 1;
-        for (int d = 1; d < RPW; d <<= 1) {
-            const float So = __shfl_up(S, d * C), Qo = __shfl_up(Q, d * C);
-            const int Ho = __shfl_up(H, d * C);
-            if (rls >= d) {
-                const float Dl = expf(-(pos(endq(rl)) - pos(endq(rl - d))));
-                Q = H ? Dl * So + Q : Qo;
-                S = Dl * So + S;
-                H |= Ho;
-            }
-        }
-        if (rls == RPW - 1) {
-            const int slot = wave * 16 + c;
-            wtot[1 * 256 + slot] = S; wtot[2 * 256 + slot] = Q; wtot[3 * 256 + slot] = __int_as_float(H);
-        }
-        // the row-lanes before this one in the wavefront
-        float Sb = __shfl_up(S, C), Qb = __shfl_up(Q, C);
-        int Hb = __shfl_up(H, C);
-        if (rls == 0) { Sb = 0.0f; Qb = 0.0f; Hb = 0; }
-        // Decays from the end of wavefront u (lane u), and from the end of the previous sweep (lane 16), to the
-        // row before this wavefront's first (gw) and to the end of this sweep (ge); the same for every column.
-        float gw = 0.0f, ge = 0.0f;
-        {
-            const int q_before_wave = s * RS + wave * RPW * kSmallItems - 1;      // >= -1
-            const float target_w = pos(q_before_wave < N ? q_before_wave : N - 1);
-            const float target_e = pos(endq(RL - 1));
-            if (lane <= kSmallWaves) {
-                const float from = lane < kSmallWaves ? pos(endq((lane + 1) * RPW - 1)) : pos(s * RS - 1);
-                // (the first wavefront of the first sweep has nothing before it: both anchors are the -inf sentinel)
-                gw = (lane < wave || lane == kSmallWaves) && q_before_wave >= 0 ? expf(-(target_w - from)) : 0.0f;
-                ge = expf(-(target_e - from));
-            }
-        }
-        __syncthreads();
-        // state entering this wavefront (Fin, Ein) and state at the end of the sweep (Fc, Ec): sums over the
-        // wavefronts' summaries, each decayed to the target directly
-        auto lane_value = [](float x, int l) -> float { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
-        float Fin = lane_value(gw, kSmallWaves) * Fc, Ein = Ec;
-        float Fe = lane_value(ge, kSmallWaves) * Fc, Ee = Ec;
-#pragma unroll
-        for (int u = 0; u < kSmallWaves; ++u) {
-            const int slot = u * 16 + c;
-            const float tS = wtot[1 * 256 + slot], tQ = wtot[2 * 256 + slot];
-            const int tH = __float_as_int(wtot[3 * 256 + slot]);
-            const float gwu = lane_value(gw, u), geu = lane_value(ge, u);
-            if (u < wave) {
-                if (tH) Ein = Fin + tQ;       // a run head inside u: everything before u, decayed, plus u's own strict sum
-                Fin += gwu * tS;
-            }
-            if (tH) Ee = Fe + tQ;
-            Fe += geu * tS;
-        }
-        Fc = Fe; Ec = Ee;
-        __syncthreads();                                            // wtot is rewritten by the next sweep
-        // ... and through the row-lanes before this one
-        {
-            const int qw = s * RS + wave * RPW * kSmallItems - 1;
-            const float Dwl = rls == 0 ? 1.0f : expf(-(pos(q0 - 1 < N ? q0 - 1 : N - 1) - pos(qw < N ? qw : N - 1)));
-            const float f = Dwl * Fin;
-            Ein = Hb ? f + Qb : Ein;
-            Fin = f + Sb;
-        }
-        // the rows
-#pragma unroll
-        for (int i = 0; i < kSmallItems; ++i) {
-            const uint32_t id = idr[i];
-            if (!(id >= P.res_lo && id < P.res_hi) || !col_ok) continue;
-            const float f = cf[i] * Fin;
-            const float Fi = f + F0[i];
-            const float Ei = ((seen >> i) & 1) ? f + E0[i] : Ein;
-            const int64_t rr = (int64_t)(id - P.res_lo);
-            if (P.out_p) {
-                float* o = P.out_p + rr * P.ld_p + col;
-                *o = DIR == 0 ? Fi : *o + Fi - v[i];
-            }
-            if (STRICT && P.out_z) {
-                float* o = P.out_z + rr * batch + col;
-                *o = DIR == 0 ? -Ei : *o + Ei;
-            }
-        }
-    }
 }
 
 // The sort of a small problem, spread over the whole device: the stable rank of an anchor is the number
@@ -236,52 +90,219 @@ k_small_rank(SmallArgs A, int queries)
     if (blockIdx.x == 0 && tid == 0) { g_pk[0] = __uint_as_float(0xFF800000u); g_pk[N + 1] = __uint_as_float(0x7F800000u); }
 }
 
-__global__ void __launch_bounds__(kSmallThreads)
-k_small(SmallArgs A)
-{
-    __shared__ unsigned long long comp[kSmallMax + 1];      // ids (first half), sorted keys / anchors (second half)
-    __shared__ float sdh[kSmallMax + 1];
-    __shared__ float wtot[4 * 256];                          // per sweep: (D, S, Q, H) of wavefront w, column c at [w * 16 + c]
-    const int tid = threadIdx.x;
-    const int64_t op = blockIdx.y;
-    const int64_t N = A.k + A.n;
-    const uint32_t* g_ids = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(A.ids) + op * A.op_ws);
-    float* g_dh = reinterpret_cast<float*>(reinterpret_cast<char*>(A.dh) + op * A.op_ws);
-    const float* g_pk = reinterpret_cast<const float*>(reinterpret_cast<const char*>(A.pk) + op * A.op_ws);
-    uint32_t* sid = reinterpret_cast<uint32_t*>(comp);
-    float* sp = reinterpret_cast<float*>(comp) + kSmallMax;         // N + 2 floats, the last two in comp[kSmallMax]
+// ---------------------------------------------------------------------------
+// One scan problem.  A workgroup owns a chunk of consecutive rows of the merged sequence and C batch columns, and needs nothing
+// from other workgroups: the state before its chunk is a weighted sum of all rows before it, sum_j exp(-(p_before - p_j)) v_j
+// (the recurrence of Sec. 3 unrolled), the state after it likewise.  Each workgroup forms those two sums itself -- reading every
+// injected row once more per chunk costs less than one workgroup walking all of them, because a small problem leaves the device
+// idle --, then scans its own rows in both directions.  Lane l works on column l % C (adjacent lanes read adjacent columns of a
+// row); a row-lane holds ITEMS consecutive rows.  Only those are chained by products of decays; everything else is combined with
+// decays taken from the anchors.
+// Measured (MI355X, us, this kernel / one workgroup per up to 16 columns that walked all rows; plan reused): n = k = 4096, batch 1:
+// 11.8 / 21.2, batch 64: 18 / 30, batch 256: 44 / 53; 1024: 9.8 / 13.3, batch 256: 10.5 / 18.6; 16 operators of 100 x 768, batch 64:
+// 17 / 20.  Bound by one chain: ids and anchors, injected rows, the reduction over the workgroup, the scan, the stores.
+// Strict channel: rows with the key at which a sum is taken are kept apart (weight -1 stands for "equal": the strict sum leaves
+// them out, the inclusive sum is strict + equal).
+// ---------------------------------------------------------------------------
+constexpr int kChunkThreads = 512;
+constexpr int kChunkWaves = kChunkThreads / 64;
 
-    // the plan: sorted ids and anchors from the workspace (written by k_small_rank or by an earlier call);
-    // the decays between neighbours are formed here (Sec. 3 "Symmetric case": exp(a_i - a_{i+1}))
-    for (int64_t j = tid; j < N; j += kSmallThreads) sid[j] = g_ids[j];
-    for (int64_t j = tid; j < N + 2; j += kSmallThreads) sp[j] = g_pk[j];
-    __syncthreads();
-    for (int64_t j = tid; j <= N; j += kSmallThreads) {
-        float d = 0.0f;
-        if (j > 0 && j < N) d = sp[j + 1] == sp[j] ? -1.0f : expf(-(sp[j + 1] - sp[j]));
-        sdh[j] = d;
-        if (blockIdx.x == 0 && A.write_dh) g_dh[j] = d;
+template <int ITEMS, bool STRICT>
+__global__ void __launch_bounds__(kChunkThreads)
+k_small(const SmallArgs A, int slabs)
+{
+    extern __shared__ float lds[];                            // [N] weights, [N] rows of the injected matrix
+    __shared__ float red[4][kChunkWaves][16];                 // sums outside the chunk; then the wavefronts' summaries
+    __shared__ float wave_s[2][3][kChunkWaves][16];
+    __shared__ float wave_p[2][kChunkWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int N = (int)(A.k + A.n), C = A.cols, RPW = 64 / C, RL = kChunkThreads / C;
+    const int64_t op = blockIdx.y / A.nprob;
+    const SmallProblem P = A.prob[blockIdx.y % A.nprob];
+    const uint32_t* ids = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(A.ids) + op * A.op_ws);
+    const float* pk = reinterpret_cast<const float*>(reinterpret_cast<const char*>(A.pk) + op * A.op_ws);
+    const float* inj = P.inj + op * P.op_inj;
+    const int slab = (int)blockIdx.x % slabs, chunk = (int)blockIdx.x / slabs;
+    const int rows = RL * ITEMS, row0 = chunk * rows, row1 = row0 + rows < N ? row0 + rows : N;
+    const int c = lane % C, r = lane / C, rl = wave * RPW + r;
+    const int64_t col = (int64_t)slab * C + c;
+    const bool col_ok = col < A.batch;
+    float* const wt = lds;
+    uint32_t* const src = reinterpret_cast<uint32_t*>(lds + N);
+    auto pos = [&](int j) { return pk[1 + (j < 0 ? 0 : (j < N ? j : N - 1))]; };
+    const float pf = pos(row0 - 1), pb = pos(row1);          // (clamped: at the ends of the sequence there is nothing to carry)
+
+    // own rows
+    const int q0 = row0 + rl * ITEMS;
+    uint32_t id[ITEMS];
+    float p[ITEMS], v[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int q = q0 + i;
+        id[i] = q < N ? ids[q] : 0xFFFFFFFFu;
+        p[i] = pos(q);
+        v[i] = q < N && col_ok && id[i] >= P.inj_lo && id[i] < P.inj_hi ? inj[(int64_t)(id[i] - P.inj_lo) * P.ld_inj + col] : 0.0f;
+    }
+    const float p_left = pos(q0 - 1), p_right = pos(q0 + ITEMS);
+
+    // the other rows' weights, once per workgroup
+    for (int j = tid; j < N; j += kChunkThreads) {
+        const uint32_t e = ids[j];
+        const float pj = pk[j + 1];
+        const bool in = e >= P.inj_lo && e < P.inj_hi && !(j >= row0 && j < row1);
+        const float at = j < row0 ? pf : pb;
+        const float w = pj == at ? -1.0f : expf(j < row0 ? pj - pf : pb - pj);
+        wt[j] = in ? w : 0.0f;
+        src[j] = e - P.inj_lo;
     }
     __syncthreads();
-
-    SmallShared sh;
-    sh.id = sid; sh.p = sp; sh.dh = sdh;
-    const int64_t col0 = (int64_t)blockIdx.x * A.cols;
-    for (int i = 0; i < A.nprob; ++i) {
-        SmallProblem P = A.prob[i];
-        if (P.inj) P.inj += op * P.op_inj;
-        if (P.out_p) P.out_p += op * P.op_p;
-        if (P.out_z) P.out_z += op * P.op_z;
-        if (P.out_z) {
-            small_pass<0, true>(P, sh, (int)N, A.batch, A.cols, col0, wtot);
-            __syncthreads();          // a row's two directions are walked by different threads: what the first parked must be visible
-            small_pass<1, true>(P, sh, (int)N, A.batch, A.cols, col0, wtot);
-        } else {
-            small_pass<0, false>(P, sh, (int)N, A.batch, A.cols, col0, wtot);
-            __syncthreads();
-            small_pass<1, false>(P, sh, (int)N, A.batch, A.cols, col0, wtot);
+    float sum[2], same[2];                                    // strictly beyond the key at the chunk's edge, and at it
+    sum[0] = sum[1] = same[0] = same[1] = 0.0f;
+    constexpr int AHEAD = 8;
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+        const int lo = dir == 0 ? rl : row1 + rl, hi = dir == 0 ? row0 : N;
+        for (int j0 = lo; j0 < hi; j0 += AHEAD * RL) {
+            float w[AHEAD], x[AHEAD];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                const int j = j0 + i * RL;
+                w[i] = j < hi ? wt[j] : 0.0f;
+                x[i] = w[i] != 0.0f && col_ok ? inj[(int64_t)src[j] * P.ld_inj + col] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                if (STRICT) {
+                    sum[dir] += w[i] > 0.0f ? w[i] * x[i] : 0.0f;
+                    same[dir] += w[i] < 0.0f ? x[i] : 0.0f;
+                } else {
+                    sum[dir] += fabsf(w[i]) * x[i];
+                }
+            }
         }
-        __syncthreads();
+    }
+#pragma unroll
+    for (int dir = 0; dir < 2; ++dir) {
+        for (int m = C; m < 64; m <<= 1) {
+            sum[dir] += __shfl_xor(sum[dir], m);
+            if (STRICT) same[dir] += __shfl_xor(same[dir], m);
+        }
+        if (r == 0) { red[2 * dir][wave][c] = sum[dir]; if (STRICT) red[2 * dir + 1][wave][c] = same[dir]; }
+    }
+
+    // the row-lane's rows from zero, in both directions (cf, cb: decays from the row-lane's edges, at most ITEMS factors)
+    float F0[ITEMS], E0[ITEMS], cf[ITEMS], R0[ITEMS], G0[ITEMS], cb[ITEMS];
+    int seen_f = 0, seen_b = 0;                               // bit i: the key has changed between the edge and row i
+    {
+        float F = 0.0f, E = 0.0f, prod = 1.0f;
+        int sn = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const float before = i == 0 ? p_left : p[i > 0 ? i - 1 : 0];
+            const bool first = q0 + i == 0, h = first || p[i] != before;      // (rows past the end repeat the last anchor)
+            const float d = first ? 0.0f : expf(-(p[i] - before));
+            E = h ? d * F : E;
+            F = (h ? E : F) + v[i];
+            prod *= d;
+            sn |= h ? 1 : 0;
+            F0[i] = F; E0[i] = E; cf[i] = prod; seen_f |= sn << i;
+        }
+        F = E = 0.0f; prod = 1.0f; sn = 0;
+#pragma unroll
+        for (int i = ITEMS - 1; i >= 0; --i) {
+            const float after = i == ITEMS - 1 ? p_right : p[i < ITEMS - 1 ? i + 1 : 0];
+            const bool h = p[i] != after;
+            const float d = expf(-(after - p[i]));
+            E = h ? d * F : E;
+            F = (h ? E : F) + v[i];
+            prod *= d;
+            sn |= h ? 1 : 0;
+            R0[i] = F; G0[i] = E; cb[i] = prod; seen_b |= sn << i;
+        }
+    }
+    // inclusive scans over the wavefront's row-lanes, decays from the anchors at their ends
+    const float pe = p[ITEMS - 1], ps = p[0];
+    float S = F0[ITEMS - 1], Q = E0[ITEMS - 1], U = R0[0], V = G0[0];
+    int H = (seen_f >> (ITEMS - 1)) & 1, J = seen_b & 1;
+    for (int d = 1; d < RPW; d <<= 1) {
+        const float So = __shfl_up(S, d * C), Qo = __shfl_up(Q, d * C), peo = __shfl_up(pe, d * C);
+        const float Uo = __shfl_down(U, d * C), Vo = __shfl_down(V, d * C), pso = __shfl_down(ps, d * C);
+        const int Ho = __shfl_up(H, d * C), Jo = __shfl_down(J, d * C);
+        if (r >= d) {
+            const float D = expf(-(pe - peo));
+            Q = H ? D * So + Q : Qo;
+            S = D * So + S;
+            H |= Ho;
+        }
+        if (r + d < RPW) {
+            const float D = expf(-(pso - ps));
+            V = J ? D * Uo + V : Vo;
+            U = D * Uo + U;
+            J |= Jo;
+        }
+    }
+    if (r == RPW - 1) {
+        wave_s[0][0][wave][c] = S; wave_s[0][1][wave][c] = Q; wave_s[0][2][wave][c] = __int_as_float(H);
+        if (c == 0) wave_p[0][wave] = pe;
+    }
+    if (r == 0) {
+        wave_s[1][0][wave][c] = U; wave_s[1][1][wave][c] = V; wave_s[1][2][wave][c] = __int_as_float(J);
+        if (c == 0) wave_p[1][wave] = ps;
+    }
+    // the row-lanes before (after) this one in the wavefront
+    float Sb = __shfl_up(S, C), Qb = __shfl_up(Q, C), Ua = __shfl_down(U, C), Va = __shfl_down(V, C);
+    int Hb = __shfl_up(H, C), Ja = __shfl_down(J, C);
+    if (r == 0) { Sb = Qb = 0.0f; Hb = 0; }
+    if (r == RPW - 1) { Ua = Va = 0.0f; Ja = 0; }
+    __syncthreads();
+    // state entering the wavefront: the chunk's, and the wavefronts in between, each decayed to the wavefront's edge directly
+    const float pw = wave == 0 ? pf : wave_p[0][wave - 1], pv = wave == kChunkWaves - 1 ? pb : wave_p[1][wave + 1];
+    float ef = 0.0f, eb = 0.0f;                               // factors of wavefront `lane`; lane kChunkWaves: of the chunk's edge
+    if (lane <= kChunkWaves) {
+        const float from_f = lane < kChunkWaves ? wave_p[0][lane] : pf, from_b = lane < kChunkWaves ? wave_p[1][lane] : pb;
+        if (lane < wave || lane == kChunkWaves) ef = expf(-(pw - from_f));
+        if (lane > wave) eb = expf(-(from_b - pv));
+    }
+    auto lane_value = [](float x, int l) -> float { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l)); };
+    float Fin = 0.0f, Ein = 0.0f, Rin = 0.0f, Gin = 0.0f;
+#pragma unroll
+    for (int u = 0; u < kChunkWaves; ++u) {
+        Ein += red[0][u][c]; Gin += red[2][u][c];
+        if (STRICT) { Fin += red[1][u][c]; Rin += red[3][u][c]; }
+    }
+    Fin = lane_value(ef, kChunkWaves) * (Ein + Fin);
+    Rin = lane_value(eb, kChunkWaves) * (Gin + Rin);
+#pragma unroll
+    for (int u = 0; u < kChunkWaves; ++u) {
+        if (u < wave) {
+            if (STRICT && __float_as_int(wave_s[0][2][u][c])) Ein = Fin + wave_s[0][1][u][c];
+            Fin += lane_value(ef, u) * wave_s[0][0][u][c];
+        }
+    }
+#pragma unroll
+    for (int u = kChunkWaves - 1; u >= 0; --u) {
+        if (u > wave) {
+            if (STRICT && __float_as_int(wave_s[1][2][u][c])) Gin = Rin + wave_s[1][1][u][c];
+            Rin += lane_value(eb, u) * wave_s[1][0][u][c];
+        }
+    }
+    // ... and the row-lane
+    {
+        const float f = (r == 0 ? 1.0f : expf(-(p_left - pw))) * Fin, b = (r == RPW - 1 ? 1.0f : expf(-(pv - p_right))) * Rin;
+        Ein = Hb ? f + Qb : Ein;
+        Fin = f + Sb;
+        Gin = Ja ? b + Va : Gin;
+        Rin = b + Ua;
+    }
+    float* const out_p = P.out_p ? P.out_p + op * P.op_p : nullptr;
+    float* const out_z = P.out_z ? P.out_z + op * P.op_z : nullptr;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        if (id[i] < P.res_lo || id[i] >= P.res_hi || !col_ok) continue;
+        const int64_t rr = (int64_t)(id[i] - P.res_lo);
+        const float f = cf[i] * Fin, b = cb[i] * Rin;
+        if (out_p) out_p[rr * P.ld_p + col] = f + F0[i] + (b + R0[i]) - v[i];
+        if (STRICT && out_z) out_z[rr * A.batch + col] = (((seen_b >> i) & 1) ? b + G0[i] : Gin) - (((seen_f >> i) & 1) ? f + E0[i] : Ein);
     }
 }
 
@@ -290,24 +311,37 @@ k_small(SmallArgs A)
 hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
 {
     SmallArgs A = A0;
-    // Columns per workgroup: as few as still give the device a workgroup per compute unit (fewer
-    // columns = more row-lanes per column = fewer sweeps, and with the device idle otherwise more workgroups beat
-    // wider rows: measured on five shapes), at most 16.
-    int cols = 16;
-    while (cols > 1 && ((A.batch + cols - 1) / cols) * operators < 256) cols >>= 1;
-    while (cols > 1 && cols / 2 >= A.batch) cols >>= 1;
-    A.cols = cols;
-    const int64_t slabs = (A.batch + A.cols - 1) / A.cols;
     const int64_t N = A.k + A.n;
-    A.write_dh = A.reuse_plan ? 0 : 1;
     if (!A.reuse_plan) {
         int queries = 32;          // per workgroup (more per workgroup measured slower until the grid gets very large)
         while (queries < kRankQueriesMax && ((N + queries - 1) / queries) * operators > 8192) queries <<= 1;
         LAPLEX_TIMED("small_sort", st, hipLaunchKernelGGL(k_small_rank, dim3((unsigned)((N + queries - 1) / queries), (unsigned)operators),
                                                           dim3(kSmallThreads), 0, st, A, queries));
     }
-    if (A.nprob > 0)
-        LAPLEX_TIMED("small", st, hipLaunchKernelGGL(k_small, dim3((unsigned)slabs, (unsigned)operators), dim3(kSmallThreads), 0, st, A));
+    if (A.nprob > 0) {
+        // Columns and rows per lane: as few as still leave a compute unit no more than one workgroup (short chains, nothing
+        // chained twice), since every chunk reads the rows of all others; then wider.  Measured (us, forward + backward; the four
+        // forms): n = k = 4096, batch 8: 43 / 44 / 56 / 72, batch 32: 60 / 51 / 56 / 104, batch 64: 94 / 67 / 61 / 104, batch 256:
+        // 332 / 191 / 123 / 128; 16 operators of 500 x 500, batch 64: 102 / 82 / 68 / 70, batch 256: 231 / 150 / 118 / 105.
+        const int forms[4][2] = {{1, 1}, {1, 2}, {4, 4}, {16, 8}};
+        int cols = 1, items = 1;
+        int64_t slabs = 0, chunks = 0;
+        for (const auto& f : forms) {
+            cols = 1; items = f[1];
+            while (cols < A.batch && cols < f[0]) cols <<= 1;
+            const int64_t rows = (int64_t)kChunkThreads / cols * items;
+            slabs = (A.batch + cols - 1) / cols; chunks = (N + rows - 1) / rows;
+            if (slabs * chunks * operators <= 256) break;      // (whatever the problems of the launch: the form shows in the last bits)
+        }
+        A.cols = cols;
+        const dim3 grid((unsigned)(chunks * slabs), (unsigned)(operators * A.nprob));
+        const size_t lds = 2 * sizeof(float) * (size_t)N;
+        bool strict = false;
+        for (int i = 0; i < A.nprob; ++i) strict = strict || A.prob[i].out_z != nullptr;
+        auto go = [&](auto kernel) { LAPLEX_TIMED("small", st, hipLaunchKernelGGL(kernel, grid, dim3(kChunkThreads), lds, st, A, (int)slabs)); };
+        if (strict) { if (items == 1) go(k_small<1, true>); else if (items == 2) go(k_small<2, true>); else if (items == 4) go(k_small<4, true>); else go(k_small<8, true>); }
+        else        { if (items == 1) go(k_small<1, false>); else if (items == 2) go(k_small<2, false>); else if (items == 4) go(k_small<4, false>); else go(k_small<8, false>); }
+    }
     return hipGetLastError();
 }
 

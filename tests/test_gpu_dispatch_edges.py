@@ -92,6 +92,31 @@ def test_run_sort_order_and_decays(oracle, N, kind):
     assert float((np.abs(y[pick, 0] - ref) / (1e-5 * ref + 1e-7)).max()) <= 1.0
 
 
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
+@pytest.mark.parametrize("k,n,batch", [
+    (1, 510, 1), (1, 511, 1), (256, 257, 2), (700, 323, 1), (701, 324, 3), (3000, 5192, 1), (1, 8191, 2),      # chunks of 512 rows
+    (4096, 4096, 17), (4000, 4191, 30),                                          # chunks of 1024
+    (513, 1024, 64), (4096, 4096, 50), (2047, 2, 100),                           # chunks of 512, four columns a workgroup
+    (300, 212, 1000), (4096, 4096, 100), (128, 129, 2100),                       # chunks of 256, sixteen columns
+])
+def test_small_problem_chunks(oracle, kind, k, n, batch):
+    """One-launch scans of small problems at the edges of their chunks, in each of the launch's four forms, forward and both
+    backward forms (the strict scans saved, and recomputed beside the other problem); bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward
+    r = np.random.default_rng(k + 5 * n + batch)
+    a, b = anchors(kind, r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    y, ws = gpu_apply(a, b, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    saved = gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws)
+    alone = gpu_backward(a, b, x, g)
+    for name, u, v, rv, tv in zip(("gx", "ga", "gb"), saved, alone, want, tols):
+        assert_close(name, u, rv, tv)
+        assert_close(name, v, rv, tv)
+
+
 def test_mix_common_launches_non_finite_anchors(oracle):
     """Values are unspecified, but the calls end, and the workspace serves a clean problem afterwards."""
     from test_gpu_parity import anchors, assert_close
@@ -120,7 +145,7 @@ def test_mix_common_launches_non_finite_anchors(oracle):
     (2, 8192, 1, 4, 0), (2, 1, 8192, 5, 0), (3, 8000, 255, 32, 0), (2, 257, 8100, 36, 4), (2, 8191, 2049, 1, 0),
     (3, 4097, 4096, 3, 2), (2, 4096, 4097, 33, 1), (2, 6000, 3000, 100, 0), (1, 30000, 600, 8, 0), (2, 700, 20000, 64, 0),
     (2, 9000, 31, 16, 0), (1, 33, 9001, 2, 0),                    # hundreds of long rows between two short ones: several tasks each
-    (16, 40, 2008, 32, 0), (16, 40, 2007, 32, 0), (2, 2000, 48, 256, 0), (1, 1, 2047, 512, 0),     # the first sizes on common launches
+    (2, 7000, 906, 64, 0), (2, 7000, 905, 64, 0), (16, 500, 898, 256, 0),       # from 8e9 / (r batch) = N^2 on: common launches
     (3, 6831, 1, 1, 0), (3, 1, 6832, 1, 0), (16, 1500, 1500, 1, 0),             # the last operators ranked by counting, the first sorted
 ])
 def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
