@@ -1076,6 +1076,134 @@ k_spine_top(const Level L, int64_t bpad)
     }
 }
 
+// The list of the blocks the heavy downsweep must visit, when the reduce saw every tile itself (with a
+// metadata pass the list is already there): one workgroup per chunk compacts its blocks' flags, slots from
+// a counter in LDS, and takes its stretch of the list with ONE atomic on the shared counter (instead of one
+// per listed block from inside the reduce, each waited for by a wavefront on its way to the tile's barrier).
+__device__ __forceinline__ void list_blocks(const ScanArgs& A, int64_t chunk)
+{
+    if (!A.down_from_list || A.reduce_from_list) return;
+    __shared__ uint32_t l_count, l_base;
+    constexpr int kMaxPer = 8;                               // a chunk has at most 4096 blocks
+    const int tid = threadIdx.x;
+    if (tid == 0) l_count = 0u;
+    __syncthreads();
+    const int64_t b0 = (chunk * A.chunk_tiles) << A.sub_shift;
+    const int64_t nb = (int64_t)A.chunk_tiles << A.sub_shift;
+    uint32_t slot[kMaxPer];
+#pragma unroll
+    for (int q = 0; q < kMaxPer; ++q) {
+        const int64_t o = (int64_t)q * kScanThreads + tid, b = b0 + o;
+        const bool listed = o < nb && b < A.blocks && listed_block((int)A.blk_flags[b]);
+        slot[q] = listed ? atomicAdd(&l_count, 1u) : 0xFFFFFFFFu;
+    }
+    __syncthreads();
+    if (tid == 0) l_base = l_count ? atomicAdd(&A.counters[1], l_count) : 0u;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kMaxPer; ++q)
+        if (slot[q] != 0xFFFFFFFFu) A.list_both[l_base + slot[q]] = (uint32_t)(b0 + (int64_t)q * kScanThreads + tid);
+}
+
+// ---------------------------------------------------------------------------
+// spine in one launch, for few tiles: a tile's carry is the sum of the other tiles' summaries, each brought to the tile's edge by
+// one exponential of an anchor difference; tiles beyond the reach of an fp32 decay (104 units) are not read.  Strict channel: a
+// tile that ends at the edge's key contributes its own strict sum if it holds the start of that run, else nothing; the tiles
+// before it contribute whole.
+// WAVES wavefronts share a tile (all of the workgroup where a summary is a wavefront wide), so that row-lanes are many.
+// ---------------------------------------------------------------------------
+template <int VEC, bool STRICT, int WAVES>
+__global__ void __launch_bounds__(kScanThreads)
+k_spine_direct(const ScanArgs A, int list_groups)
+{
+    if ((int)blockIdx.x < list_groups) {                     // uniform
+        if (blockIdx.y == 0 && blockIdx.z == 0) list_blocks(A, blockIdx.x);
+        return;
+    }
+    constexpr int kAhead = 4;
+    __shared__ float red[2][WAVES > 1 ? WAVES : 1][WAVES > 1 ? 64 * VEC : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int bv = A.bv, rv = A.rv;
+    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
+    const int dir = blockIdx.z;
+    const int64_t count = A.l1.count, SR = A.spine_rows;
+    const int64_t group = (int64_t)blockIdx.x - list_groups;
+    const int64_t t = WAVES > 1 ? group : group * kScanWaves + wave;
+    if (t >= count) return;                                  // (uniform over the wavefronts that share a tile)
+    const int rl = WAVES > 1 ? wave * rv + r : r;
+    const int step = WAVES * rv;
+    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
+    const bool col_ok = col0 < A.batch;
+    // anchor at the tile's edge; anchor of tile v's last row towards it, and of the row behind tile v (sentinels beyond the ends)
+    auto end_of = [&](int64_t v) { const int64_t e = (v + 1) * SR; return e < A.N ? e : A.N; };
+    auto near_anchor = [&](int64_t v) { return dir == 0 ? A.pk[end_of(v)] : A.pk[v * SR + 1]; };
+    auto far_anchor = [&](int64_t v) { return dir == 0 ? A.pk[v * SR] : A.pk[end_of(v) + 1]; };
+    const float at = dir == 0 ? A.pk[t * SR] : A.pk[end_of(t) + 1];
+    const int64_t others = dir == 0 ? t : count - 1 - t;     // tiles on that side, counted from the tile outwards
+    float F[VEC], E[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) F[e] = E[e] = 0.0f;
+    for (int64_t o0 = rl; o0 < others; o0 += (int64_t)kAhead * step) {
+        float near_[kAhead], w[kAhead], S[kAhead][VEC], Q[kAhead][VEC];
+        float4 sc[kAhead];
+        int64_t v[kAhead];
+        float any = 0.0f;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const int64_t o = o0 + (int64_t)i * step;
+            const bool live = o < others;
+            v[i] = live ? (dir == 0 ? t - 1 - o : t + 1 + o) : t;
+            near_[i] = near_anchor(v[i]);
+            sc[i] = A.l1.scalar[(int64_t)dir * count + v[i]];
+            w[i] = live ? expf(-fabsf(at - near_[i])) : 0.0f;
+            any += w[i];
+        }
+        if (any == 0.0f) break;                              // (farther tiles are out of reach as well)
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            // a tile with nothing injected has no vectors: they are zero, and may never have been written
+            const bool in = w[i] != 0.0f && ((int)sc[i].w & kFlagInj) != 0 && col_ok;
+            const int64_t at_v = ((int64_t)dir * count + v[i]) * A.bpad + col0;
+            load_vec_or_zero<VEC>(S[i], A.l1.s, at_v, in);
+            if (STRICT) load_vec_or_zero<VEC>(Q[i], A.l1.q, at_v, in);
+        }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            const bool edge = near_[i] == at;
+            const bool starts = STRICT && edge && w[i] != 0.0f && far_anchor(v[i]) != at;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                const float x = w[i] * S[i][e];
+                F[e] += x;
+                if (STRICT) E[e] += edge ? (starts ? Q[i][e] : 0.0f) : x;
+            }
+        }
+    }
+    for (int m = bv; m < 64; m <<= 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { F[e] += __shfl_xor(F[e], m); if (STRICT) E[e] += __shfl_xor(E[e], m); }
+    }
+    if (WAVES > 1) {
+        if (r == 0) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { red[0][WAVES > 1 ? wave : 0][WAVES > 1 ? c * VEC + e : 0] = F[e]; if (STRICT) red[1][WAVES > 1 ? wave : 0][WAVES > 1 ? c * VEC + e : 0] = E[e]; }
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            F[e] = E[e] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < WAVES; ++u) { F[e] += red[0][WAVES > 1 ? u : 0][WAVES > 1 ? c * VEC + e : 0]; if (STRICT) E[e] += red[1][WAVES > 1 ? u : 0][WAVES > 1 ? c * VEC + e : 0]; }
+        }
+    }
+    if (r == 0 && col_ok) {
+        const int64_t o = ((int64_t)dir * count + t) * A.bpad + col0;
+        store_vec<VEC>(A.l1.car_f + o, F);
+        if (STRICT) store_vec<VEC>(A.l1.car_e + o, E);
+    }
+}
+
 // ---------------------------------------------------------------------------
 // spine, level 2 -> 1: push the chunk carries down to the tiles of each chunk
 // ---------------------------------------------------------------------------
@@ -1090,31 +1218,7 @@ k_spine_down(const ScanArgs A)
     const int dir = blockIdx.z;
     const int64_t chunk = blockIdx.x;
 
-    // The list of the blocks the heavy downsweep must visit, when the reduce saw every tile itself (with a
-    // metadata pass the list is already there): one workgroup per chunk compacts its blocks' flags, slots from
-    // a counter in LDS, and takes its stretch of the list with ONE atomic on the shared counter (instead of one
-    // per listed block from inside the reduce, each waited for by a wavefront on its way to the tile's barrier).
-    if (A.down_from_list && !A.reduce_from_list && dir == 0 && blockIdx.y == 0) {
-        __shared__ uint32_t l_count, l_base;
-        constexpr int kMaxPer = 8;                               // a chunk has at most 4096 blocks
-        if (tid == 0) l_count = 0u;
-        __syncthreads();
-        const int64_t b0 = (chunk * A.chunk_tiles) << A.sub_shift;
-        const int64_t nb = (int64_t)A.chunk_tiles << A.sub_shift;
-        uint32_t slot[kMaxPer];
-#pragma unroll
-        for (int q = 0; q < kMaxPer; ++q) {
-            const int64_t o = (int64_t)q * kScanThreads + tid, b = b0 + o;
-            const bool listed = o < nb && b < A.blocks && listed_block((int)A.blk_flags[b]);
-            slot[q] = listed ? atomicAdd(&l_count, 1u) : 0xFFFFFFFFu;
-        }
-        __syncthreads();
-        if (tid == 0) l_base = l_count ? atomicAdd(&A.counters[1], l_count) : 0u;
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kMaxPer; ++q)
-            if (slot[q] != 0xFFFFFFFFu) A.list_both[l_base + slot[q]] = (uint32_t)(b0 + (int64_t)q * kScanThreads + tid);
-    }
+    if (dir == 0 && blockIdx.y == 0) list_blocks(A, chunk);
     const int64_t q0 = chunk * A.chunk_tiles + (int64_t)(wave * rv + r) * A.spine_items;
     const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
     const bool col_ok = col0 < A.batch;
@@ -2643,6 +2747,32 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// One launch where every tile can read every other tile's summary, three (or one workgroup per direction, for a single chunk) otherwise.
+// tiles^2 * batch summaries are read if all anchors are within reach of each other, a few tiles each if they are spread.  Measured
+// (us, forward + backward, before / after; anchors spread, all within reach): n = k = 2^16, batch 8 (128 tiles): 102 / 92, 109 / 98;
+// 20000, batch 32 (157 tiles): 105 / 90, 106 / 102; 2^18, batch 8 (512 tiles, 2^21): 161 / 150, 167 / 163; beyond the line n = k = 2^20,
+// batch 8 (2^25): 424 / 404, 424 / 449.
+constexpr double kSpineDirectWork = double(1 << 24);
+template <int VEC, bool STRICT>
+void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
+{
+    const dim3 block(kScanThreads), cgrid((unsigned)g.chunks, (unsigned)g.slabs, 2);
+    if ((double)g.tiles * (double)g.tiles * (double)A.bpad <= kSpineDirectWork) {
+        const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
+        if (g.rv >= 8)
+            LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_direct<VEC, STRICT, 1>), dim3((unsigned)(lists + (g.tiles + kScanWaves - 1) / kScanWaves), (unsigned)g.slabs, 2),
+                                                        block, 0, st, A, lists));
+        else
+            LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_direct<VEC, STRICT, kScanWaves>), dim3((unsigned)(lists + g.tiles), (unsigned)g.slabs, 2), block, 0, st, A, lists));
+        return;
+    }
+    if (g.chunks > 1) {     // one chunk: nothing to carry between chunks, the tiles' carries come from k_spine_down alone
+        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_reduce<VEC, STRICT>), cgrid, block, 0, st, A));
+        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_top<STRICT>), dim3((unsigned)A.batch, 2), dim3(kSpineThreads), 0, st, A.l2, A.bpad));
+    }
+    LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
+}
+
 template <int VEC, bool STRICT>
 void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bool two, hipStream_t st)
 {
@@ -2662,17 +2792,11 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         const std::string fm = "scan_meta." + tag;
         LAPLEX_TIMED(fm.c_str(), st, hipLaunchKernelGGL(k_scan_meta, dim3((unsigned)((g.tiles + 3) / 4)), dim3(256), 0, st, A));
     }
-    const dim3 cgrid((unsigned)g.chunks, (unsigned)g.slabs, 2);
-    const dim3 tgrid((unsigned)A.batch, 2);
     const std::string fr = "scan_reduce." + tag, fs = "scan_spine." + tag, fd = "scan_down." + tag,
                       fp = "scan_down_sparse." + tag;
     if (VEC == 1 && A.inj_sorted && A.out_sorted) {     // batch 1, everything in sorted order: the ids are not looked at
         LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_seq_reduce<STRICT>), dim3((unsigned)g.tiles), block, 0, st, A));
-        if (g.chunks > 1) {
-            LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_reduce<VEC, STRICT>), cgrid, block, 0, st, A));
-            LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_top<STRICT>), tgrid, dim3(kSpineThreads), 0, st, A.l2, A.bpad));
-        }
-        LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
+        launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
         const dim3 tiles((unsigned)g.tiles), dblock(kSeqDownThreads);
         const bool red = STRICT && A.wstage != nullptr;
         if (!STRICT) LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_seq_down<false, false, 1>), tiles, dblock, 0, st, A));
@@ -2693,11 +2817,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     } else {
         LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT>), rgrid, bblock, 0, st, A));
     }
-    if (g.chunks > 1) {     // one chunk: nothing to carry between chunks, the tiles' carries come from k_spine_down alone
-        LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_reduce<VEC, STRICT>), cgrid, block, 0, st, A));
-        LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_top<STRICT>), tgrid, dim3(kSpineThreads), 0, st, A.l2, A.bpad));
-    }
-    LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
+    launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
         const std::string fx = "phase_split_blocks." + tag;
         // the list holds the blocks with injected and result rows, except those with few injected rows (mode 1 needs them too)
