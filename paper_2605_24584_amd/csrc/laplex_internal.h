@@ -62,6 +62,7 @@ constexpr int kItemsVec4 = 8;    // rows per row-lane when a lane holds 4 column
 constexpr int kStageMaxBatch = 8;
 constexpr int kSpineItems = 8;    // tile summaries per row-lane in the chunked spine kernels, at most (ScanGeom::spine_items)
 constexpr int kSpineThreads = 1024;
+constexpr int kSpineSuperTiles = 32;   // tiles summed up together by the spine that adds summaries directly, when it has two levels
 
 // ----------------------------------------------------------------------------
 // Batch 1, many rows: values move between the caller's order and the sorted order as records through
@@ -229,6 +230,8 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     L.off_blk_e = c;     c = align_up(c + per_blk);
     L.off_stage = c; c = align_up(c + stage_bytes);
     L.max_chunks = g1.chunks > g4.chunks ? g1.chunks : g4.chunks;
+    const int64_t supers = (L.max_tiles + kSpineSuperTiles - 1) / kSpineSuperTiles;
+    if (supers > L.max_chunks) L.max_chunks = supers;
     const size_t per2 = sizeof(float) * 2 * (size_t)L.max_chunks * (size_t)L.bpad;
     L.off_agg2_scalar = c; c = align_up(c + sizeof(float) * 4 * 2 * (size_t)L.max_chunks);
     L.off_agg2_s = c;      c = align_up(c + per2);

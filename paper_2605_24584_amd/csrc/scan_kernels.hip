@@ -1106,66 +1106,48 @@ __device__ __forceinline__ void list_blocks(const ScanArgs& A, int64_t chunk)
 }
 
 // ---------------------------------------------------------------------------
-// spine in one launch, for few tiles: a tile's carry is the sum of the other tiles' summaries, each brought to the tile's edge by
+// spine by direct sums, for few tiles: a tile's carry is the sum of the other tiles' summaries, each brought to the tile's edge by
 // one exponential of an anchor difference; tiles beyond the reach of an fp32 decay (104 units) are not read.  Strict channel: a
 // tile that ends at the edge's key contributes its own strict sum if it holds the start of that run, else nothing; the tiles
-// before it contribute whole.
+// before it contribute whole.  With two levels, k_spine_super first sums up groups of kSuperTiles tiles the same way, and a tile
+// reads the others of its group and the other groups.
 // WAVES wavefronts share a tile (all of the workgroup where a summary is a wavefront wide), so that row-lanes are many.
 // ---------------------------------------------------------------------------
-template <int VEC, bool STRICT, int WAVES>
-__global__ void __launch_bounds__(kScanThreads)
-k_spine_direct(const ScanArgs A, int list_groups)
+constexpr int kSuperTiles = kSpineSuperTiles;
+
+// F, E += the sums of `others` entries of level L (SR rows each), counted from entry v0 away from the edge whose anchor is `at`;
+// this row-lane takes every `step`-th of them from `rl` on.  FLAGGED: an entry with nothing injected may not have been written.
+template <int VEC, bool STRICT, bool FLAGGED>
+__device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, int64_t SR, int dir, float at, int64_t v0, int64_t others,
+                                            int rl, int step, int64_t col0, bool col_ok, float* F, float* E)
 {
-    if ((int)blockIdx.x < list_groups) {                     // uniform
-        if (blockIdx.y == 0 && blockIdx.z == 0) list_blocks(A, blockIdx.x);
-        return;
-    }
     constexpr int kAhead = 4;
-    __shared__ float red[2][WAVES > 1 ? WAVES : 1][WAVES > 1 ? 64 * VEC : 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bv = A.bv, rv = A.rv;
-    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
-    const int dir = blockIdx.z;
-    const int64_t count = A.l1.count, SR = A.spine_rows;
-    const int64_t group = (int64_t)blockIdx.x - list_groups;
-    const int64_t t = WAVES > 1 ? group : group * kScanWaves + wave;
-    if (t >= count) return;                                  // (uniform over the wavefronts that share a tile)
-    const int rl = WAVES > 1 ? wave * rv + r : r;
-    const int step = WAVES * rv;
-    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
-    const bool col_ok = col0 < A.batch;
-    // anchor at the tile's edge; anchor of tile v's last row towards it, and of the row behind tile v (sentinels beyond the ends)
+    // the entry's end towards the edge, and the row behind it (sentinels beyond the ends of the sequence)
     auto end_of = [&](int64_t v) { const int64_t e = (v + 1) * SR; return e < A.N ? e : A.N; };
     auto near_anchor = [&](int64_t v) { return dir == 0 ? A.pk[end_of(v)] : A.pk[v * SR + 1]; };
     auto far_anchor = [&](int64_t v) { return dir == 0 ? A.pk[v * SR] : A.pk[end_of(v) + 1]; };
-    const float at = dir == 0 ? A.pk[t * SR] : A.pk[end_of(t) + 1];
-    const int64_t others = dir == 0 ? t : count - 1 - t;     // tiles on that side, counted from the tile outwards
-    float F[VEC], E[VEC];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) F[e] = E[e] = 0.0f;
     for (int64_t o0 = rl; o0 < others; o0 += (int64_t)kAhead * step) {
         float near_[kAhead], w[kAhead], S[kAhead][VEC], Q[kAhead][VEC];
-        float4 sc[kAhead];
+        int flags[kAhead];
         int64_t v[kAhead];
         float any = 0.0f;
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
             const int64_t o = o0 + (int64_t)i * step;
             const bool live = o < others;
-            v[i] = live ? (dir == 0 ? t - 1 - o : t + 1 + o) : t;
+            v[i] = live ? (dir == 0 ? v0 - o : v0 + o) : v0;
             near_[i] = near_anchor(v[i]);
-            sc[i] = A.l1.scalar[(int64_t)dir * count + v[i]];
+            flags[i] = FLAGGED ? (int)L.scalar[(int64_t)dir * L.count + v[i]].w : kFlagInj;
             w[i] = live ? expf(-fabsf(at - near_[i])) : 0.0f;
             any += w[i];
         }
-        if (any == 0.0f) break;                              // (farther tiles are out of reach as well)
+        if (any == 0.0f) break;                              // (farther entries are out of reach as well)
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
-            // a tile with nothing injected has no vectors: they are zero, and may never have been written
-            const bool in = w[i] != 0.0f && ((int)sc[i].w & kFlagInj) != 0 && col_ok;
-            const int64_t at_v = ((int64_t)dir * count + v[i]) * A.bpad + col0;
-            load_vec_or_zero<VEC>(S[i], A.l1.s, at_v, in);
-            if (STRICT) load_vec_or_zero<VEC>(Q[i], A.l1.q, at_v, in);
+            const bool in = w[i] != 0.0f && (flags[i] & kFlagInj) != 0 && col_ok;
+            const int64_t at_v = ((int64_t)dir * L.count + v[i]) * A.bpad + col0;
+            load_vec_or_zero<VEC>(S[i], L.s, at_v, in);
+            if (STRICT) load_vec_or_zero<VEC>(Q[i], L.q, at_v, in);
         }
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
@@ -1179,24 +1161,88 @@ k_spine_direct(const ScanArgs A, int list_groups)
             }
         }
     }
+}
+
+// The row-lanes' sums added up, over the wavefront and over WAVES wavefronts; false: another wavefront holds the result.
+template <int VEC, bool STRICT, int WAVES>
+__device__ __forceinline__ bool add_row_lanes(float* F, float* E, int bv, int wave, int r, int c)
+{
     for (int m = bv; m < 64; m <<= 1) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) { F[e] += __shfl_xor(F[e], m); if (STRICT) E[e] += __shfl_xor(E[e], m); }
     }
-    if (WAVES > 1) {
+    if constexpr (WAVES > 1) {
+        __shared__ float red[2][WAVES][64 * VEC];
         if (r == 0) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { red[0][WAVES > 1 ? wave : 0][WAVES > 1 ? c * VEC + e : 0] = F[e]; if (STRICT) red[1][WAVES > 1 ? wave : 0][WAVES > 1 ? c * VEC + e : 0] = E[e]; }
+            for (int e = 0; e < VEC; ++e) { red[0][wave][c * VEC + e] = F[e]; if (STRICT) red[1][wave][c * VEC + e] = E[e]; }
         }
         __syncthreads();
-        if (wave > 0) return;
+        if (wave > 0) return false;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             F[e] = E[e] = 0.0f;
 #pragma unroll
-            for (int u = 0; u < WAVES; ++u) { F[e] += red[0][WAVES > 1 ? u : 0][WAVES > 1 ? c * VEC + e : 0]; if (STRICT) E[e] += red[1][WAVES > 1 ? u : 0][WAVES > 1 ? c * VEC + e : 0]; }
+            for (int u = 0; u < WAVES; ++u) { F[e] += red[0][u][c * VEC + e]; if (STRICT) E[e] += red[1][u][c * VEC + e]; }
         }
     }
+    return true;
+}
+
+template <int VEC, bool STRICT, int WAVES>
+__global__ void __launch_bounds__(kScanThreads)
+k_spine_super(const ScanArgs A, const Level super)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int bv = A.bv, rv = A.rv, c = lane & (bv - 1), r = lane >> A.bv_log2, dir = blockIdx.z;
+    const int64_t g = WAVES > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kScanWaves + wave;
+    if (g >= super.count) return;
+    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
+    const bool col_ok = col0 < A.batch;
+    const int64_t count = A.l1.count, t0 = g * kSuperTiles, t1 = t0 + kSuperTiles < count ? t0 + kSuperTiles : count;
+    const int64_t end = t1 * A.spine_rows < A.N ? t1 * A.spine_rows : A.N;
+    float F[VEC], E[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) F[e] = E[e] = 0.0f;
+    add_entries<VEC, STRICT, true>(A, A.l1, A.spine_rows, dir, dir == 0 ? A.pk[end] : A.pk[t0 * A.spine_rows + 1], dir == 0 ? t1 - 1 : t0, t1 - t0,
+                                   WAVES > 1 ? wave * rv + r : r, WAVES * rv, col0, col_ok, F, E);
+    if (!add_row_lanes<VEC, STRICT, WAVES>(F, E, bv, wave, r, c)) return;
+    if (r == 0 && col_ok) {
+        const int64_t o = ((int64_t)dir * super.count + g) * A.bpad + col0;
+        store_vec<VEC>(super.s + o, F);
+        if (STRICT) store_vec<VEC>(super.q + o, E);
+    }
+}
+
+template <int VEC, bool STRICT, int WAVES, bool TWO>
+__global__ void __launch_bounds__(kScanThreads)
+k_spine_direct(const ScanArgs A, const Level super, int list_groups)
+{
+    if ((int)blockIdx.x < list_groups) {                     // uniform
+        if (blockIdx.y == 0 && blockIdx.z == 0) list_blocks(A, blockIdx.x);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int bv = A.bv, rv = A.rv, c = lane & (bv - 1), r = lane >> A.bv_log2, dir = blockIdx.z;
+    const int64_t count = A.l1.count, SR = A.spine_rows;
+    const int64_t group = (int64_t)blockIdx.x - list_groups;
+    const int64_t t = WAVES > 1 ? group : group * kScanWaves + wave;
+    if (t >= count) return;                                  // (uniform over the wavefronts that share a tile)
+    const int rl = WAVES > 1 ? wave * rv + r : r, step = WAVES * rv;
+    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
+    const bool col_ok = col0 < A.batch;
+    const int64_t end = (t + 1) * SR < A.N ? (t + 1) * SR : A.N;
+    const float at = dir == 0 ? A.pk[t * SR] : A.pk[end + 1];
+    float F[VEC], E[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) F[e] = E[e] = 0.0f;
+    const int64_t g = t / kSuperTiles, t0 = TWO ? g * kSuperTiles : 0;
+    const int64_t t1 = TWO && t0 + kSuperTiles < count ? t0 + kSuperTiles : count;
+    add_entries<VEC, STRICT, true>(A, A.l1, SR, dir, at, dir == 0 ? t - 1 : t + 1, dir == 0 ? t - t0 : t1 - 1 - t, rl, step, col0, col_ok, F, E);
+    if (TWO)
+        add_entries<VEC, STRICT, false>(A, super, SR * kSuperTiles, dir, at, dir == 0 ? g - 1 : g + 1, dir == 0 ? g : super.count - 1 - g,
+                                        rl, step, col0, col_ok, F, E);
+    if (!add_row_lanes<VEC, STRICT, WAVES>(F, E, bv, wave, r, c)) return;
     if (r == 0 && col_ok) {
         const int64_t o = ((int64_t)dir * count + t) * A.bpad + col0;
         store_vec<VEC>(A.l1.car_f + o, F);
@@ -2751,19 +2797,27 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // tiles^2 * batch summaries are read if all anchors are within reach of each other, a few tiles each if they are spread.  Measured
 // (us, forward + backward, before / after; anchors spread, all within reach): n = k = 2^16, batch 8 (128 tiles): 102 / 92, 109 / 98;
 // 20000, batch 32 (157 tiles): 105 / 90, 106 / 102; 2^18, batch 8 (512 tiles, 2^21): 161 / 150, 167 / 163; beyond the line n = k = 2^20,
-// batch 8 (2^25): 424 / 404, 424 / 449.
-constexpr double kSpineDirectWork = double(1 << 24);
+// batch 8 (2^25): 424 / 404, 424 / 449.  There two levels read tiles * (32 + tiles / 32) * batch summaries at worst: 424 / 412, 424 / 414
+// (1.6e6); 1024 x 2^18, batch 256 (6.3e6): 300 / 287, 307 / 296; n = k = 2^17, batch 64 (1.3e7): 231 / 243, 237 / 258.
+constexpr double kSpineDirectWork = double(1 << 24), kSpineSuperWork = double(1 << 23);
 template <int VEC, bool STRICT>
 void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
 {
     const dim3 block(kScanThreads), cgrid((unsigned)g.chunks, (unsigned)g.slabs, 2);
-    if ((double)g.tiles * (double)g.tiles * (double)A.bpad <= kSpineDirectWork) {
+    Level super = A.l2;
+    super.count = (g.tiles + kSuperTiles - 1) / kSuperTiles;
+    const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= kSpineDirectWork;
+    // (with single columns and fewer than eight row-lanes a workgroup reads 256 bytes per entry: 217 us with three launches, 220 with two)
+    const bool two = !one && (VEC == 4 || g.rv >= 8) && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= kSpineSuperWork;
+    if (one || two) {
         const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
-        if (g.rv >= 8)
-            LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_direct<VEC, STRICT, 1>), dim3((unsigned)(lists + (g.tiles + kScanWaves - 1) / kScanWaves), (unsigned)g.slabs, 2),
-                                                        block, 0, st, A, lists));
-        else
-            LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_direct<VEC, STRICT, kScanWaves>), dim3((unsigned)(lists + g.tiles), (unsigned)g.slabs, 2), block, 0, st, A, lists));
+        auto groups = [&](int64_t n) { return (unsigned)(g.rv >= 8 ? (n + kScanWaves - 1) / kScanWaves : n); };
+        const dim3 sgrid(groups(super.count), (unsigned)g.slabs, 2), dgrid((unsigned)lists + groups(g.tiles), (unsigned)g.slabs, 2);
+        auto go = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, dgrid, block, 0, st, A, super, lists)); };
+        auto sums = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, sgrid, block, 0, st, A, super)); };
+        if (two) { if (g.rv >= 8) sums(k_spine_super<VEC, STRICT, 1>); else sums(k_spine_super<VEC, STRICT, kScanWaves>); }
+        if (g.rv >= 8) { if (two) go(k_spine_direct<VEC, STRICT, 1, true>); else go(k_spine_direct<VEC, STRICT, 1, false>); }
+        else           { if (two) go(k_spine_direct<VEC, STRICT, kScanWaves, true>); else go(k_spine_direct<VEC, STRICT, kScanWaves, false>); }
         return;
     }
     if (g.chunks > 1) {     // one chunk: nothing to carry between chunks, the tiles' carries come from k_spine_down alone

@@ -183,3 +183,27 @@ def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
             for i in pick:
                 assert_close(str(i), outs[i].cpu().numpy(), want[i], tols[i])
         a, b = np.sort(a, axis=1), np.sort(b, axis=1)             # second round: both sides ascending
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
+@pytest.mark.parametrize("k,n,batch", [
+    (4000, 4200, 1), (9000, 7385, 1),                             # one and two tiles of 8192 rows, and a row more
+    (65000, 66072, 8), (65000, 66073, 8),                         # 128 tiles of 1024 rows, and one more
+    (32768, 32769, 32), (20, 60000, 8),                           # few outputs: the list of heavy blocks beside the sums
+    (1000, 40000, 33), (700, 30000, 256),                         # a summary is a wavefront wide: a workgroup per tile
+    (900000, 600000, 8), (30, 140000, 256),                       # two levels: groups of 32 tiles, the last one shorter
+])
+def test_direct_spine(oracle, kind, k, n, batch):
+    """The spine that adds the other tiles' summaries directly, at one tile, at the ends of its groups, with runs of equal keys that
+    reach over tiles (all_equal: over all of them); bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward
+    r = np.random.default_rng(k + 7 * n + batch)
+    a, b = anchors(kind, r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    y, ws = gpu_apply(a, b, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    grads = gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws)
+    for name, u, rv, tv in zip(("gx", "ga", "gb"), grads, want, tols):
+        assert_close(name, u, rv, tv)
