@@ -78,6 +78,7 @@ struct ScanArgs {
     // list_inj is written by the metadata pass; list_both by the metadata pass if it runs, else by the reduce
     int reduce_from_list, down_from_list;
     int few_inj_ok, few_res_ok;   // the block flags kFlagFewInj / kFlagFewRes may be set
+    int every_block;              // the downsweep takes the blocks without injected rows too: no streaming downsweep follows
     int pair_out;                 // batch 1: out_p and the row's second output (out_z, else out_red) are the halves of an 8-byte slot
     int inj_sorted;               // batch 1: `stage` already holds the injected rows in sorted order: nothing is gathered
     int out_sorted;               // batch 1: outputs are indexed by the sorted row, not by the id (a later pass takes them home)
@@ -1416,6 +1417,99 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 }
 
 // ---------------------------------------------------------------------------
+// downsweep_sparse: tiles with result rows and nothing injected.  With no
+// injection inside the tile every row is a closed form of the two carries:
+//   F_j = cf_j F_in,           cf_j = product of the decays from the tile start to j
+//   E_j = F_j if a run head lies at or before j inside the tile, else E_in
+// and symmetrically from the right.  The decays come from the anchors directly, so
+// the kernel has no scan, no LDS and no barrier; the batch columns are streamed.
+// ---------------------------------------------------------------------------
+template <int VEC, bool STRICT>
+__device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
+{
+    constexpr int ITEMS = TileRows<VEC>::ITEMS;
+    const uint32_t poison = plan_poison(A.counters);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int bv = A.bv, rv = A.rv;
+    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
+    const int64_t row0 = tile * A.tile_rows + (int64_t)(wave * rv + r) * ITEMS;
+    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
+    const bool col_ok = col0 < A.batch;
+
+    // everything in the tile before / after this row-lane: one exponential of an anchor difference each,
+    // so no scan over the row-lanes and no LDS are needed (asked for first: the loads go out early)
+    const int64_t tile_base = tile * A.tile_rows, after = row0 + ITEMS, tile_end = tile_base + A.tile_rows;
+    const float Df = span_decay_f(A, tile_base, row0 - tile_base), Db = span_decay_b(A, after, tile_end - after);
+    const int Hf = span_head_f(A, tile_base, row0 - tile_base) ? 1 : 0, Hb = span_head_b(A, after, tile_end - after) ? 1 : 0;
+
+    TileRows<VEC> T;
+    load_meta<VEC>(A, row0, T);
+    const bool want_red = STRICT && A.out_red != nullptr;
+    float wv[ITEMS][VEC];
+    load_weights<VEC>(A, T, row0, col0, col_ok, want_red, wv);
+    float Fin[VEC], Ein[VEC], Rin[VEC], Gin[VEC];
+    load_block_carries<VEC, STRICT>(A, tile, col0, col_ok, Fin, Ein, Rin, Gin);
+
+    // per-row cumulative decays inside this row-lane, from the left and from the right (at most ITEMS factors)
+    float cf[ITEMS], cb[ITEMS];
+    int hf = 0, hb = 0;               // bit i: a run head at or before (after) row i inside the row-lane
+    {
+        float p = 1.0f; int seen = 0;
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) {
+            const bool h = head_f<VEC>(T, i);
+            p *= h ? T.dh[i] : 1.0f; seen |= h ? 1 : 0;
+            cf[i] = p; hf |= seen << i;
+        }
+        p = 1.0f; seen = 0;
+#pragma unroll
+        for (int i = ITEMS - 1; i >= 0; --i) {
+            const bool h = head_b<VEC>(T, i);
+            p *= h ? T.dh[i + 1] : 1.0f; seen |= h ? 1 : 0;
+            cb[i] = p; hb |= seen << i;
+        }
+    }
+    const int64_t res_rows = (int64_t)A.res_hi - (int64_t)A.res_lo;
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool is_res = T.id[i] >= A.res_lo && T.id[i] < A.res_hi;
+        const int64_t rr = A.out_sorted ? row0 + i : (int64_t)T.id[i] - (int64_t)A.res_lo;
+        const float kf = Df * cf[i], kb = Db * cb[i];
+        const bool seen_f = Hf | ((hf >> i) & 1), seen_b = Hb | ((hb >> i) & 1);
+        float P[VEC], Z[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            const float Fj = kf * Fin[e], Rj = kb * Rin[e];
+            P[e] = taint(Fj + Rj, poison);
+            Z[e] = taint((seen_b ? Rj : Gin[e]) - (seen_f ? Fj : Ein[e]), poison);
+        }
+        if (is_res && col_ok) {
+            if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
+            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0, Z);
+        }
+        if (want_red) {
+            float acc = 0.0f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc += wv[i][e] * Z[e];      // wv is 0 off the result rows
+            emit_row_sum(A, acc, bv, c, is_res, rr, res_rows);
+        }
+    }
+}
+
+template <int VEC, bool STRICT>
+__global__ void __launch_bounds__(kScanThreads)
+k_scan_down_sparse(const ScanArgs A)
+{
+    // the last kernel of a scan: nothing reads the list lengths any more, and the next scan wants them at zero
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.counters[threadIdx.x] = 0u;
+    const int flags = (int)A.blk_flags[blockIdx.x];
+    // result rows and nothing injected (blocks with a few injected rows exist in the wide geometry only, which has a kernel of its own)
+    if (!(flags & kFlagRes) || (flags & kFlagInj)) return;
+    sparse_block<VEC, STRICT>(A, blockIdx.x);
+}
+
+// ---------------------------------------------------------------------------
 // downsweep: tiles that hold both injected and result rows
 // ---------------------------------------------------------------------------
 // WAVES: wavefronts of the workgroup (sizes the LDS buffer); RED: the row reduction is wanted (out_red);
@@ -1437,7 +1531,10 @@ k_scan_down(const ScanArgs A)
     if (A.down_from_list && blockIdx.x >= A.counters[1]) return;
     const int64_t tile = A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
     const int flags = (int)A.blk_flags[tile];
-    if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) return;
+    if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) {
+        if (A.every_block && (flags & kFlagRes)) sparse_block<VEC, STRICT>(A, tile);      // nothing injected
+        return;
+    }
     const uint32_t poison = plan_poison(A.counters);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1617,94 +1714,6 @@ k_scan_down(const ScanArgs A)
             float acc = ZS ? vz[ZS ? i : 0] : 0.0f;
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc += wrow[e] * Z[e];     // wrow is 0 off the result rows
-            emit_row_sum(A, acc, bv, c, is_res, rr, res_rows);
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// downsweep_sparse: tiles with result rows and nothing injected.  With no
-// injection inside the tile every row is a closed form of the two carries:
-//   F_j = cf_j F_in,           cf_j = product of the decays from the tile start to j
-//   E_j = F_j if a run head lies at or before j inside the tile, else E_in
-// and symmetrically from the right.  The decays come from the anchors directly, so
-// the kernel has no scan, no LDS and no barrier; the batch columns are streamed.
-// ---------------------------------------------------------------------------
-template <int VEC, bool STRICT>
-__global__ void __launch_bounds__(kScanThreads)
-k_scan_down_sparse(const ScanArgs A)
-{
-    constexpr int ITEMS = TileRows<VEC>::ITEMS;
-    // the last kernel of a scan: nothing reads the list lengths any more, and the next scan wants them at zero
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.counters[threadIdx.x] = 0u;
-    const int64_t tile = blockIdx.x;                // the block this workgroup owns
-    const int flags = (int)A.blk_flags[tile];
-    // result rows and nothing injected (blocks with a few injected rows exist in the wide geometry only, which has a kernel of its own)
-    if (!(flags & kFlagRes) || (flags & kFlagInj)) return;
-    const uint32_t poison = plan_poison(A.counters);
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int bv = A.bv, rv = A.rv;
-    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
-    const int64_t row0 = tile * A.tile_rows + (int64_t)(wave * rv + r) * ITEMS;
-    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
-    const bool col_ok = col0 < A.batch;
-
-    // everything in the tile before / after this row-lane: one exponential of an anchor difference each,
-    // so no scan over the row-lanes and no LDS are needed (asked for first: the loads go out early)
-    const int64_t tile_base = tile * A.tile_rows, after = row0 + ITEMS, tile_end = tile_base + A.tile_rows;
-    const float Df = span_decay_f(A, tile_base, row0 - tile_base), Db = span_decay_b(A, after, tile_end - after);
-    const int Hf = span_head_f(A, tile_base, row0 - tile_base) ? 1 : 0, Hb = span_head_b(A, after, tile_end - after) ? 1 : 0;
-
-    TileRows<VEC> T;
-    load_meta<VEC>(A, row0, T);
-    const bool want_red = STRICT && A.out_red != nullptr;
-    float wv[ITEMS][VEC];
-    load_weights<VEC>(A, T, row0, col0, col_ok, want_red, wv);
-    float Fin[VEC], Ein[VEC], Rin[VEC], Gin[VEC];
-    load_block_carries<VEC, STRICT>(A, tile, col0, col_ok, Fin, Ein, Rin, Gin);
-
-    // per-row cumulative decays inside this row-lane, from the left and from the right (at most ITEMS factors)
-    float cf[ITEMS], cb[ITEMS];
-    int hf = 0, hb = 0;               // bit i: a run head at or before (after) row i inside the row-lane
-    {
-        float p = 1.0f; int seen = 0;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            const bool h = head_f<VEC>(T, i);
-            p *= h ? T.dh[i] : 1.0f; seen |= h ? 1 : 0;
-            cf[i] = p; hf |= seen << i;
-        }
-        p = 1.0f; seen = 0;
-#pragma unroll
-        for (int i = ITEMS - 1; i >= 0; --i) {
-            const bool h = head_b<VEC>(T, i);
-            p *= h ? T.dh[i + 1] : 1.0f; seen |= h ? 1 : 0;
-            cb[i] = p; hb |= seen << i;
-        }
-    }
-    const int64_t res_rows = (int64_t)A.res_hi - (int64_t)A.res_lo;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        const bool is_res = T.id[i] >= A.res_lo && T.id[i] < A.res_hi;
-        const int64_t rr = A.out_sorted ? row0 + i : (int64_t)T.id[i] - (int64_t)A.res_lo;
-        const float kf = Df * cf[i], kb = Db * cb[i];
-        const bool seen_f = Hf | ((hf >> i) & 1), seen_b = Hb | ((hb >> i) & 1);
-        float P[VEC], Z[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const float Fj = kf * Fin[e], Rj = kb * Rin[e];
-            P[e] = taint(Fj + Rj, poison);
-            Z[e] = taint((seen_b ? Rj : Gin[e]) - (seen_f ? Fj : Ein[e]), poison);
-        }
-        if (is_res && col_ok) {
-            if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0, Z);
-        }
-        if (want_red) {
-            float acc = 0.0f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) acc += wv[i][e] * Z[e];      // wv is 0 off the result rows
             emit_row_sum(A, acc, bv, c, is_res, rr, res_rows);
         }
     }
@@ -2902,6 +2911,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
             else go(k_scan_down<VEC, STRICT, kBlockWavesNarrow, false, false>);
         }
     }
+    if (A.every_block) return;
     if (VEC == 4 && g.sub_shift) {
         const dim3 sgrid((unsigned)((g.blocks + kStreamWaves - 1) / kStreamWaves), (unsigned)g.slabs);
         if (A.ph.half) {     // phased backward: one wavefront merges both halves of its block's rows; the other blocks' rows before it
@@ -2983,6 +2993,11 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         A.reduce_from_list = inj_rows * 4 <= g.tiles;
         A.down_from_list = both * 4 <= g.blocks;
         if (p.inj_sorted && p.out_sorted) A.reduce_from_list = A.down_from_list = 0;   // every block is visited
+        // One downsweep for all blocks when every block is visited: each of its workgroups looks at its block and takes the scan or
+        // the closed form, in place of a launch for either, which cost 4 to 15 us where it found few blocks (us, forward + backward,
+        // two launches / one: n = k = 2^16, batch 8: 92 / 88; 2999 x 100003, batch 33: 210 / 195; inputs and outputs apart, 2^20 each,
+        // batch 8: 309 / 303).  (No lists: their lengths stay at zero.)
+        A.every_block = !A.reduce_from_list && !A.down_from_list && !g.sub_shift;
         // blocks with a handful of injected (result) rows skip the scan inside the block: wide geometry,
         // injected and result rows from different matrices, and few such rows overall
         const bool disjoint = p.inj_hi <= p.res_lo || p.res_hi <= p.inj_lo;
