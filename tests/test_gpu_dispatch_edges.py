@@ -207,3 +207,40 @@ def test_direct_spine(oracle, kind, k, n, batch):
     grads = gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws)
     for name, u, rv, tv in zip(("gx", "ga", "gb"), grads, want, tols):
         assert_close(name, u, rv, tv)
+
+
+@pytest.mark.parametrize("r,k,n,batch", [(5, 40, 530000, 2), (2, 33000, 32769, 4), (2, 32768, 33000, 4)])
+def test_mix_operator_by_operator(oracle, r, k, n, batch):
+    """Sums of operators beyond the common launches (more than 2^19 merged positions, or 2^15 of either kind; the last case is the first
+    within): operators on the library's streams, five of them in two rounds; bars of test_gpu_parity.  A captured call keeps to its
+    stream and gives the same bits on every replay."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(r + k + n)
+    ab = [anchors("ties", q, k, n) for _ in range(r)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, g = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32)
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    out = [torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (r, k), (r, n), (r,))]
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+
+    def run():
+        B.laplex_mix_apply(da, db, dw, dx, out[0], ws, B.LAPLEX_SAVE_SCANS)
+        B.laplex_mix_apply_backward(da, db, dw, dx, dg, *out[1:], ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+
+    run()
+    torch.cuda.synchronize()
+    eager = [v.clone() for v in out]
+    ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+    want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
+    for name, got, rv, tv in zip(("y", "gx", "ga", "gb", "gw"), eager, (ref,) + tuple(want), (tol,) + tuple(tols)):
+        assert_close(name, got.cpu().numpy(), rv, tv)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        for v in out:
+            v.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(u, v) for u, v in zip(out, eager))
