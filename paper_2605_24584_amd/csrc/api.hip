@@ -392,7 +392,7 @@ MixLayout mix_layout(int64_t r, int64_t k, int64_t n, int64_t batch)
         M.off_tasks = o;  o = align_up(o + sizeof(uint2) * ops * tasks);
         M.off_folds = o;  o = align_up(o + sizeof(float) * ops * slabs * tasks * 2 * width);
         M.off_equal = o;  o = align_up(o + sizeof(float) * ops * slabs * tasks * width);
-        M.off_sums = o;   o = align_up(o + sizeof(float) * ops * slabs * 2 * (size_t)mix_max_tiles((int64_t)m, batch) * width);
+        M.off_sums = o;   o = align_up(o + sizeof(float) * ops * slabs * kMixSums * (size_t)mix_max_tiles((int64_t)m, batch) * width);
         M.off_fr = o;     o = align_up(o + sizeof(float) * ops * slabs * m * 2 * width);
         M.off_p = o;      o = align_up(o + rows);
         M.off_z = o;      if (k < n) o = align_up(o + rows);      // (strict sums at the outputs wait there for the backward)

@@ -476,6 +476,7 @@ hipError_t launch_dot_ops(const float* u, int64_t ldu, const float* v, int64_t r
 // short_b), `long`: the other one (l rows).  Interval c of an operator: the long rows above short anchor c - 1 and not above c.
 constexpr int kMixWidth = 32;            // columns of a slab, at most
 constexpr int kMixTaskRows = 32;         // long rows that one row-lane folds
+constexpr int kMixSums = 3;              // sums per tile of the short side: forward, backward, forward strictly below the last anchor
 struct MixPath {
     const uint32_t* ids; const float* pk; const uint32_t* status; int64_t op_ws;      // plan of operator 0 (status: may be null); bytes to the next
     int64_t k; int N, m, l, short_b, operators;
@@ -491,7 +492,7 @@ struct MixPath {
     // written by launch_mix_fold, [operators][slabs][task_count][2 | 1][width]: per task its rows decayed to the short anchors above
     // (without rows equal to it) and below; the rows equal to it (where there are any)
     float* folds; float* equal; int task_count;
-    float* sums;                   // [operators][slabs][2][tiles][width] tile sums
+    float* sums;                   // [operators][slabs][kMixSums][tiles][width] tile sums
     float* fr;                     // [operators][slabs][m][2][width]     the scanned short side
     int64_t batch; int width, slabs, tiles;      // slabs of `width` columns (power of two <= 32); tiles: set by the launchers
 };

@@ -329,8 +329,9 @@ template <int VEC, bool FOLDED>
 __global__ void __launch_bounds__(kMixThreads)
 k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
 {
+    constexpr int SUMS = FOLDED ? kMixSums : 2;
     __shared__ float wf[kMixTileMax], wb[kMixTileMax];
-    __shared__ float part[2][kMixWaves][kMixWidth];
+    __shared__ float part[SUMS][kMixWaves][kMixWidth];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t op = blockIdx.y;
     const float* sp = A.sp + op * A.m;
@@ -342,7 +343,11 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
     const int base = tile * rows, last = clamp_row(base + rows - 1, m);
     float vf[kMixItems][VEC], vb[FOLDED ? kMixItems : 1][VEC];
     load_rows<VEC, FOLDED>(A, op, slab, c, base + rl * kMixItems, v, ldv, vf, vb);
+    float eq[VEC];                                        // rows equal to the tile's last anchor: not part of its strict sum
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) eq[e] = 0.0f;
     if (FOLDED) {
+        const uint32_t last_run = A.tied[op * m + last];
 #pragma unroll
         for (int i = 0; i < kMixItems; ++i) {
             const int j = base + rl * kMixItems + i;
@@ -350,7 +355,7 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
                 float t[VEC];
                 load_equal<VEC>(A, op, slab, c, j, t);
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) vf[i][e] += t[e];
+                for (int e = 0; e < VEC; ++e) { if (last_run == (uint32_t)j + 1u) eq[e] = t[e]; else vf[i][e] += t[e]; }
             }
         }
     }
@@ -372,19 +377,33 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
     }
     for (int d = bv; d < 64; d <<= 1) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { f[e] += __shfl_xor(f[e], d); b[e] += __shfl_xor(b[e], d); }
+        for (int e = 0; e < VEC; ++e) {
+            f[e] += __shfl_xor(f[e], d); b[e] += __shfl_xor(b[e], d);
+            if (FOLDED) eq[e] += __shfl_xor(eq[e], d);
+        }
     }
     if (lane < bv) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { part[0][wave][c * VEC + e] = f[e]; part[1][wave][c * VEC + e] = b[e]; }
+        for (int e = 0; e < VEC; ++e) {
+            part[0][wave][c * VEC + e] = f[e]; part[1][wave][c * VEC + e] = b[e];
+            if (FOLDED) part[SUMS - 1][wave][c * VEC + e] = eq[e];
+        }
     }
     __syncthreads();
     if (tid < 2 * A.width) {
         const int dir = tid / A.width, w = tid % A.width;
+        float* at = A.sums + (((op * A.slabs + slab) * kMixSums + dir) * A.tiles + tile) * A.width + w;
         float s = 0.0f;
 #pragma unroll
         for (int u = 0; u < kMixWaves; ++u) s += part[dir][u][w];
-        A.sums[(((op * A.slabs + slab) * 2 + dir) * A.tiles + tile) * A.width + w] = s;
+        if (FOLDED && dir == 0) {                         // without, then with the rows equal to the last anchor (of weight 1)
+            at[(int64_t)2 * A.tiles * A.width] = s;
+            float t = 0.0f;
+#pragma unroll
+            for (int u = 0; u < kMixWaves; ++u) t += part[SUMS - 1][u][w];
+            s += t;
+        }
+        *at = s;
     }
 }
 
@@ -392,15 +411,19 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
 // Second launch: a tile adds up the other tiles' sums itself, each brought to the tile by one exponential of an anchor
 // difference (a tile beyond the reach of an fp32 decay is not read), scans its row-lanes, and walks its rows in both directions.
 // Rows of the short side: fr[op][slab][row] = (F_row | R_row), 2 x width floats.  FOLDED: F_j holds the long rows not above short
-// anchor j, R_j those above it; products F + R and strict sums R - (F without the rows equal to the anchor) leave row by row, or
-// as dots with the rows of u.
+// anchor j, R_j those above it, E_j those strictly below; products F + R and strict sums R - E leave row by row, or as dots with
+// the rows of u.  E is never F with the equal rows taken out again, which would keep no digit of a strict sum that is 2^-24 of
+// them: it is the forward sum at the first row of a run of equal short anchors before they are added, and stays over the run.  A
+// row-lane that starts inside a run takes it from the row-lane with the run's first row or, where the run reaches back over the
+// tile's edge, from the tile sums, with the strict one for the tile with that row (the tiles in between hold rows of the run alone).
 // ---------------------------------------------------------------------------
 template <int VEC, bool FOLDED>
 __global__ void __launch_bounds__(kMixThreads)
 k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const MixFolded O)
 {
     __shared__ float dec[kMixTileMax + 1];                // dec[q]: decay between rows base + q - 1 and base + q
-    __shared__ float part[4][kMixWaves][32];              // wavefront totals and carries, forward and backward
+    __shared__ float part[FOLDED ? 5 : 4][kMixWaves][32]; // wavefront totals and carries, forward and backward; strict carries
+    __shared__ __align__(16) float run_e[FOLDED ? kMixThreads * VEC : 1];      // per row-lane: E of the run at its last row
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t op = blockIdx.y;
     const int m = A.m;
@@ -420,27 +443,19 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
         for (int i = 0; i < kMixItems; ++i) tie[FOLDED ? i : 0] = j0 + i < m ? A.tied[op * m + j0 + i] : 0u;
     }
     auto is_first = [&](int i) { return FOLDED && tie[FOLDED ? i : 0] == (uint32_t)(j0 + i) + 1u; };
-    if (FOLDED) {
-#pragma unroll
-        for (int i = 0; i < kMixItems; ++i) {
-            if (is_first(i)) {
-                float t[VEC];
-                load_equal<VEC>(A, op, slab, c, j0 + i, t);
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) vf[i][e] += t[e];
-            }
-        }
-    }
     auto pos = [&](int j) { return sp[clamp_row(j, m)]; };
     for (int q = tid; q <= rows; q += kMixThreads) dec[q] = expf(-(pos(base + q) - pos(base + q - 1)));
 
     // the tiles before and after, spread over the row-lanes
-    float Fc[VEC], Rc[VEC];
+    float Fc[VEC], Rc[VEC], Ec[VEC];
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) Fc[e] = Rc[e] = 0.0f;
+    for (int e = 0; e < VEC; ++e) Fc[e] = Rc[e] = Ec[e] = 0.0f;
+    // the tile that holds the first row of the run that this tile starts inside of, or -1
+    const uint32_t open_run = FOLDED ? A.tied[op * m + base] : 0u;
+    const int run_tile = open_run != 0u && (int)open_run - 1 < base ? ((int)open_run - 1) / rows : -1;
     {
         const float p_before = pos(base - 1), p_after = pos(base + rows);
-        const float* sf = A.sums + ((op * A.slabs + slab) * 2) * (int64_t)A.tiles * A.width + c * VEC;
+        const float* sf = A.sums + ((op * A.slabs + slab) * kMixSums) * (int64_t)A.tiles * A.width + c * VEC;
         const float* sb = sf + (int64_t)A.tiles * A.width;
         for (int u = rl; u < A.tiles; u += kMixWaves * rv) {
             if (u == tile) continue;
@@ -450,14 +465,25 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
             load_cols<VEC>(t, (u < tile ? sf : sb) + (int64_t)u * A.width, true);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) { if (u < tile) Fc[e] += w * t[e]; else Rc[e] += w * t[e]; }
+            if (FOLDED && u <= run_tile) {
+                if (u == run_tile) load_cols<VEC>(t, sb + ((int64_t)A.tiles + u) * A.width, true);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) Ec[e] += w * t[e];
+            }
         }
         for (int d = bv; d < 64; d <<= 1) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { Fc[e] += __shfl_xor(Fc[e], d); Rc[e] += __shfl_xor(Rc[e], d); }
+            for (int e = 0; e < VEC; ++e) {
+                Fc[e] += __shfl_xor(Fc[e], d); Rc[e] += __shfl_xor(Rc[e], d);
+                if (FOLDED) Ec[e] += __shfl_xor(Ec[e], d);
+            }
         }
         if (r == 0) {
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { part[2][wave][c * VEC + e] = Fc[e]; part[3][wave][c * VEC + e] = Rc[e]; }
+            for (int e = 0; e < VEC; ++e) {
+                part[2][wave][c * VEC + e] = Fc[e]; part[3][wave][c * VEC + e] = Rc[e];
+                if (FOLDED) part[FOLDED ? 4 : 0][wave][c * VEC + e] = Ec[e];
+            }
         }
     }
     __syncthreads();
@@ -470,6 +496,12 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
         const float d = dec[rl * kMixItems + i];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) S[e] = d * S[e] + vf[i][e];
+        if (is_first(i)) {
+            float t[VEC];
+            load_equal<VEC>(A, op, slab, c, j0 + i, t);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) S[e] += t[e];
+        }
     }
 #pragma unroll
     for (int i = kMixItems - 1; i >= 0; --i) {
@@ -553,16 +585,53 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
 #pragma unroll
             for (int e = 0; e < VEC; ++e) { R[e] = d * R[e] + vr[i][e]; vr[i][e] = R[e]; }
         }
+        // forward: the row's product takes the place of its F, its strict sum that of its R; E is unknown at the rows of a run that
+        // the row-lane starts inside of
+        float run[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) run[e] = 0.0f;
+        auto unknown = [&](int i) { return tie[i] != 0u && (int)tie[i] - 1 < j0; };
+#pragma unroll
+        for (int i = 0; i < kMixItems; ++i) {
+            const float d = dec[rl * kMixItems + i];
+            float t[VEC], E[VEC];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + vf[i][e]; E[e] = F[e]; t[e] = 0.0f; }
+            if (is_first(i)) load_equal<VEC>(A, op, slab, c, j0 + i, t);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (is_first(i)) run[e] = E[e];
+                if (tie[i] != 0u) E[e] = run[e];          // (unknown: nothing taken off yet)
+                F[e] += t[e];
+                vf[i][e] = F[e] + vr[i][e];
+                vr[i][e] -= unknown(i) ? 0.0f : E[e];
+            }
+        }
+        store_cols<VEC>(run_e + rl * A.width + c * VEC, run);
+        __syncthreads();
+        if (unknown(0)) {
+            const int at = (int)tie[0] - 1 - base;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) run[e] = 0.0f;
+            if (at >= 0) {
+                load_cols<VEC>(run, run_e + (at / kMixItems) * A.width + c * VEC, true);
+            } else {
+#pragma unroll
+                for (int u = 0; u < kMixWaves; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) run[e] += part[4][u][c * VEC + e];
+            }
+#pragma unroll
+            for (int i = 0; i < kMixItems; ++i)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) vr[i][e] -= unknown(i) ? run[e] : 0.0f;
+        }
 #pragma unroll
         for (int i = 0; i < kMixItems; ++i) {
             const int j = j0 + i;
-            const float d = dec[rl * kMixItems + i];
-            float P[VEC], Z[VEC], t[VEC];
+            float P[VEC], Z[VEC];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { F[e] = d * F[e] + vf[i][e]; P[e] = mark(F[e] + vr[i][e]); t[e] = 0.0f; }
-            if (tie[i] != 0u) load_equal<VEC>(A, op, slab, c, (int)tie[i] - 1, t);
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) Z[e] = mark(vr[i][e] - (F[e] - t[e]));
+            for (int e = 0; e < VEC; ++e) { P[e] = mark(vf[i][e]); Z[e] = mark(vr[i][e]); }
             if (j >= m) continue;
             const int64_t row = A.srow[op * m + j], at = (op * m + row) * A.batch + col;
             if (O.p && col_ok) store_cols<VEC>(O.p + at, P);

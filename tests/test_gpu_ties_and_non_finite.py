@@ -1,0 +1,76 @@
+"""Values at equal anchors and of non-finite rows.  Tied pairs contribute exactly nothing to anchor gradients, however large their
+rows are; so the bars here scale with the strict sums alone (the usual denominators include the tied terms, which hide what is
+lost beside them)."""
+import numpy as np
+import pytest
+
+from paper_2605_24584_amd import binding as B
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import dev  # noqa: E402
+
+
+def runs_of_ties(count, spacing, lengths):
+    """`count` ascending anchors `spacing` apart, in runs of equal ones of the given lengths, over and over."""
+    v, q = [], 0
+    while len(v) < count:
+        v += [q * spacing] * lengths[q % len(lengths)]
+        q += 1
+    return np.array(v[:count], dtype=np.float32)
+
+
+def mix_step(a, b, w, x, g, flags, ws=None):
+    """y, gx, ga, gb, gw of one forward + backward pair (flags: LAPLEX_SAVE_SCANS or 0)."""
+    r, k, n, batch = a.shape[0], a.shape[1], b.shape[1], x.shape[1]
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda") if ws is None else ws
+    out = [torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (r, k), (r, n), (r,))]
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    B.laplex_mix_apply(da, db, dw, dx, out[0], ws, flags)
+    B.laplex_mix_apply_backward(da, db, dw, dx, dg, *out[1:], ws, flags | B.LAPLEX_REUSE_PLAN)
+    torch.cuda.synchronize()
+    return [v.cpu().numpy().astype(np.float64) for v in out]
+
+
+def strict_gradients(oracle, a, b, w, x, g):
+    """ga, gb and their denominators over the strictly separated pairs, one operator after the other (fp64)."""
+    res = [[], [], [], []]
+    for q in range(a.shape[0]):
+        for at, (src, val, query, mult) in enumerate(((b[q], x, a[q], g), (a[q], g, b[q], x))):
+            _, ls, rs = oracle._dual(src, val, query, want=(False, True, True))
+            _, la, ra = oracle._dual(src, val, query, use_abs=True, want=(False, True, True))
+            m = float(w[q]) * mult.astype(np.float64)
+            res[at].append(np.sum(m * (rs - ls), axis=1))
+            res[2 + at].append(np.sum(np.abs(m) * (la + ra), axis=1))
+    return [np.stack(v) for v in res]
+
+
+@pytest.mark.parametrize("spacing", [2.0, 12.0, 16.0])
+@pytest.mark.parametrize("k,n,batch", [(2600, 7000, 1), (7000, 2600, 4), (2600, 7000, 33), (7000, 2600, 33), (2600, 7000, 64),
+                                       (7000, 2600, 64), (5000, 5000, 8)])
+def test_mix_strict_sums_beside_large_ties(oracle, k, n, batch, spacing):
+    """Sums of operators in common launches: runs of up to 300 equal short anchors (tiles of 64 to 2048 rows), each tied with a
+    couple of hundred long rows of size 1e6.  A strict sum is exp(-spacing) of its tied neighbours at most; formed as a difference
+    it would keep 24 bits of those, an error of 2^-24 exp(spacing): 1e-2 at 12, where the bar is 1e-5 (fp32 decays and sums over a
+    few hundred rows: below 2e-6)."""
+    q = np.random.default_rng(k + batch)
+    r = 2
+    short, long_ = min(k, n), max(k, n)
+    s = runs_of_ties(short, spacing, (1, 3, 300, 2))
+    sides = []
+    for _ in range(r):
+        l = s[q.integers(0, short, long_)]
+        sides.append((q.permutation(s), l) if k <= n else (l, q.permutation(s)))
+    if k == n:
+        sides = [(v, u) for u, v in sides]
+    a, b = np.stack([u for u, _ in sides]), np.stack([v for _, v in sides])
+    w = np.array([0.75, -1.5], dtype=np.float32)
+    x = (1e6 * q.normal(size=(n, batch))).astype(np.float32)
+    g = (1e6 * q.normal(size=(k, batch))).astype(np.float32)
+    ga, gb, ta, tb = strict_gradients(oracle, a, b, w, x, g)
+    for flags in (B.LAPLEX_SAVE_SCANS, 0):
+        _, _, got_a, got_b, _ = mix_step(a, b, w, x, g, flags)
+        for name, got, ref, tol in (("ga", got_a, ga, ta), ("gb", got_b, gb, tb)):
+            worst = float((np.abs(got - ref) / (1e-5 * tol + 1e-30)).max())
+            assert worst <= 1.0, f"{name}: {worst:.3g} times the bar"
