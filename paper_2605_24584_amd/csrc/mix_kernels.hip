@@ -238,11 +238,14 @@ k_mix_fold(const MixPath A, const float* __restrict__ v, int64_t ldv, int lanes,
             if (UNI && i0 + i >= n) break;
             const float el = __uint_as_float(rec[i].y), er = __uint_as_float(rec[i].z);
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) { down[e] += el * x[i][e]; up[e] += er * x[i][e]; }
-            if (rec[i].w != 0u) {                         // equal to the short anchor above: kept apart (er is 0)
+            for (int e = 0; e < VEC; ++e) down[e] += el * x[i][e];
+            if (rec[i].w != 0u) {                         // equal to the short anchor above: kept apart (no 0 * x: x may be infinite)
                 any = 1u;
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) eq[e] += x[i][e];
+            } else {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) up[e] += er * x[i][e];
             }
         }
     }
@@ -543,8 +546,9 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
             const float gb = u > wave ? expf(-(pos(base + u * rv * kMixItems) - pe)) : 0.0f;
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-                Fw[e] += gf * part[0][u][c * VEC + e] + cf * part[2][u][c * VEC + e];
-                Rw[e] += gb * part[1][u][c * VEC + e] + cb * part[3][u][c * VEC + e];
+                // (the sums on the other side are left out, not multiplied by zero: they may be infinite)
+                Fw[e] += (u < wave ? gf * part[0][u][c * VEC + e] : 0.0f) + cf * part[2][u][c * VEC + e];
+                Rw[e] += (u > wave ? gb * part[1][u][c * VEC + e] : 0.0f) + cb * part[3][u][c * VEC + e];
             }
         }
         const float df = expf(-(pos(j0 - 1) - pw)), db = expf(-(pe - pos(j0 + kMixItems)));

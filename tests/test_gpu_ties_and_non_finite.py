@@ -74,3 +74,28 @@ def test_mix_strict_sums_beside_large_ties(oracle, k, n, batch, spacing):
         for name, got, ref, tol in (("ga", got_a, ga, ta), ("gb", got_b, gb, tb)):
             worst = float((np.abs(got - ref) / (1e-5 * tol + 1e-30)).max())
             assert worst <= 1.0, f"{name}: {worst:.3g} times the bar"
+
+
+@pytest.mark.parametrize("k,n,batch", [(3000, 7000, 4), (7000, 3000, 4), (3000, 7000, 33), (7000, 3000, 1), (2500, 6000, 64)])
+def test_mix_infinite_row_at_a_tie(oracle, k, n, batch):
+    """One infinite value in a long row that equals short anchors, everything within reach of it: the product at the tied anchors,
+    and on either side, is infinite, and the tied anchors' gradients, which it does not enter, are finite and right."""
+    q = np.random.default_rng(k + n + batch)
+    a, b = (np.round(q.uniform(0, 40, s) * 4).astype(np.float32) / 4 for s in (k, n))
+    w = np.array([2.0], dtype=np.float32)
+    x, g = (q.normal(size=(s, batch)).astype(np.float32) for s in (n, k))
+    col = batch // 2
+    ga, gb, ta, tb = strict_gradients(oracle, a[None], b[None], w, x, g)
+    if k <= n:
+        x[n // 3, col] = np.inf
+        tied, at, name = a == b[n // 3], 3, "ga"
+    else:
+        g[k // 3, col] = np.inf
+        tied, at, name = b == a[k // 3], 3, "gb"
+    assert 0 < tied.sum() < tied.size
+    y, gx, got_a, got_b, _ = mix_step(a[None], b[None], w, x, g, B.LAPLEX_SAVE_SCANS)
+    product = y if k <= n else gx
+    assert np.all(np.isposinf(product[:, col])) and np.all(np.isfinite(np.delete(product, col, axis=1)))
+    got, ref, tol = (got_a[0], ga[0], ta[0]) if k <= n else (got_b[0], gb[0], tb[0])
+    assert float((np.abs(got - ref) / (1e-5 * tol + 1e-30))[tied].max()) <= 1.0, name
+    assert not np.any(np.isfinite(got[~tied]))
