@@ -101,6 +101,7 @@ k_small_rank(SmallArgs A, int queries)
 // Measured (MI355X, us, this kernel / one workgroup per up to 16 columns that walked all rows; plan reused): n = k = 4096, batch 1:
 // 11.8 / 21.2, batch 64: 18 / 30, batch 256: 44 / 53; 1024: 9.8 / 13.3, batch 256: 10.5 / 18.6; 16 operators of 100 x 768, batch 64:
 // 17 / 20.  Bound by one chain: ids and anchors, injected rows, the reduction over the workgroup, the scan, the stores.
+// Rows beyond the reach of an fp32 decay are read like the others: 0 * NaN and 0 * inf are NaN, as in the dense product.
 // Strict channel: rows with the key at which a sum is taken are kept apart (weight -1 stands for "equal": the strict sum leaves
 // them out, the inclusive sum is strict + equal).
 // ---------------------------------------------------------------------------
@@ -111,7 +112,7 @@ template <int ITEMS, bool STRICT>
 __global__ void __launch_bounds__(kChunkThreads)
 k_small(const SmallArgs A, int slabs)
 {
-    extern __shared__ float lds[];                            // [N] weights, [N] rows of the injected matrix
+    extern __shared__ __align__(8) uint2 others[];            // [N] weight and row of the injected matrix (none: not an injected row)
     __shared__ float red[4][kChunkWaves][16];                 // sums outside the chunk; then the wavefronts' summaries
     __shared__ float wave_s[2][3][kChunkWaves][16];
     __shared__ float wave_p[2][kChunkWaves];
@@ -127,8 +128,7 @@ k_small(const SmallArgs A, int slabs)
     const int c = lane % C, r = lane / C, rl = wave * RPW + r;
     const int64_t col = (int64_t)slab * C + c;
     const bool col_ok = col < A.batch;
-    float* const wt = lds;
-    uint32_t* const src = reinterpret_cast<uint32_t*>(lds + N);
+    constexpr uint32_t none = 0xFFFFFFFFu;
     auto pos = [&](int j) { return pk[1 + (j < 0 ? 0 : (j < N ? j : N - 1))]; };
     const float pf = pos(row0 - 1), pb = pos(row1);          // (clamped: at the ends of the sequence there is nothing to carry)
 
@@ -152,8 +152,7 @@ k_small(const SmallArgs A, int slabs)
         const bool in = e >= P.inj_lo && e < P.inj_hi && !(j >= row0 && j < row1);
         const float at = j < row0 ? pf : pb;
         const float w = pj == at ? -1.0f : expf(j < row0 ? pj - pf : pb - pj);
-        wt[j] = in ? w : 0.0f;
-        src[j] = e - P.inj_lo;
+        others[j] = make_uint2(in ? __float_as_uint(w) : 0u, in ? e - P.inj_lo : none);
     }
     __syncthreads();
     float sum[2], same[2];                                    // strictly beyond the key at the chunk's edge, and at it
@@ -167,13 +166,14 @@ k_small(const SmallArgs A, int slabs)
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) {
                 const int j = j0 + i * RL;
-                w[i] = j < hi ? wt[j] : 0.0f;
-                x[i] = w[i] != 0.0f && col_ok ? inj[(int64_t)src[j] * P.ld_inj + col] : 0.0f;
+                const uint2 o = j < hi ? others[j] : make_uint2(0u, none);
+                w[i] = __uint_as_float(o.x);
+                x[i] = o.y != none && col_ok ? inj[(int64_t)o.y * P.ld_inj + col] : 0.0f;
             }
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) {
                 if (STRICT) {
-                    sum[dir] += w[i] > 0.0f ? w[i] * x[i] : 0.0f;
+                    sum[dir] += w[i] >= 0.0f ? w[i] * x[i] : 0.0f;
                     same[dir] += w[i] < 0.0f ? x[i] : 0.0f;
                 } else {
                     sum[dir] += fabsf(w[i]) * x[i];
@@ -335,7 +335,7 @@ hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
         }
         A.cols = cols;
         const dim3 grid((unsigned)(chunks * slabs), (unsigned)(operators * A.nprob));
-        const size_t lds = 2 * sizeof(float) * (size_t)N;
+        const size_t lds = sizeof(uint2) * (size_t)N;
         bool strict = false;
         for (int i = 0; i < A.nprob; ++i) strict = strict || A.prob[i].out_z != nullptr;
         auto go = [&](auto kernel) { LAPLEX_TIMED("small", st, hipLaunchKernelGGL(kernel, grid, dim3(kChunkThreads), lds, st, A, (int)slabs)); };

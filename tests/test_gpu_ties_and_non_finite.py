@@ -99,3 +99,39 @@ def test_mix_infinite_row_at_a_tie(oracle, k, n, batch):
     got, ref, tol = (got_a[0], ga[0], ta[0]) if k <= n else (got_b[0], gb[0], tb[0])
     assert float((np.abs(got - ref) / (1e-5 * tol + 1e-30))[tied].max()) <= 1.0, name
     assert not np.any(np.isfinite(got[~tied]))
+
+
+def assert_all_non_finite(name, v, cols=slice(None)):
+    v = v.cpu().numpy() if hasattr(v, "cpu") else v
+    bad = np.isfinite(v if v.ndim == 1 else v[:, cols])
+    assert not bad.any(), f"{name}: {int(bad.sum())} of {bad.size} values finite"
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("k,n,batch", [
+    (700, 300, 1), (4000, 4100, 2), (513, 1024, 64), (4000, 4000, 100), (300, 212, 1000),        # small problems, each form
+    (30, 8000, 1100), (2000, 2000, 2100),
+])
+def test_non_finite_rows_reach_every_row(k, n, batch, bad):
+    """As in the dense product (0 * NaN and 0 * inf are NaN), one non-finite value of x or gy shows in every row of its column and in
+    every anchor gradient, also where all decays between underflow: anchors spread over 3000 decay lengths."""
+    q = np.random.default_rng(k + batch)
+    a, b = (q.uniform(0, 3000, s).astype(np.float32) for s in (k, n))
+    x, g = (q.normal(size=(s, batch)).astype(np.float32) for s in (n, k))
+    col = batch // 2
+    new = lambda *s: torch.zeros(*s, device="cuda")
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    da, db = dev(a), dev(b)
+    for side in ("x", "gy"):
+        dx, dg = dev(x), dev(g)
+        (dx if side == "x" else dg)[q.integers(0, n if side == "x" else k), col] = bad
+        y, gx, ga, gb = new(k, batch), new(n, batch), new(k), new(n)
+        B.laplex_apply(da, db, dx, y, ws, B.LAPLEX_SAVE_SCANS)
+        B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+        if side == "x":
+            assert_all_non_finite("y", y, col); assert_all_non_finite("ga", ga)
+        else:
+            assert_all_non_finite("gx", gx, col); assert_all_non_finite("gb", gb)
+        finite = (y if side == "gy" else gx)
+        assert bool(torch.isfinite(finite).all())
