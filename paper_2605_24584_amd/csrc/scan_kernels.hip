@@ -1108,9 +1108,9 @@ __device__ __forceinline__ void list_blocks(const ScanArgs& A, int64_t chunk)
 
 // ---------------------------------------------------------------------------
 // spine by direct sums, for few tiles: a tile's carry is the sum of the other tiles' summaries, each brought to the tile's edge by
-// one exponential of an anchor difference; tiles beyond the reach of an fp32 decay (104 units) are not read.  Strict channel: a
-// tile that ends at the edge's key contributes its own strict sum if it holds the start of that run, else nothing; the tiles
-// before it contribute whole.  With two levels, k_spine_super first sums up groups of kSuperTiles tiles the same way, and a tile
+// one exponential of an anchor difference.  Tiles beyond the reach of an fp32 decay (104 units) are read too: 0 * NaN and 0 * inf
+// are NaN, as in the dense product.  Strict channel: a tile that ends at the edge's key contributes its own strict sum if it holds
+// the start of that run, else nothing; the tiles before it contribute whole.  With two levels, k_spine_super first sums up groups of kSuperTiles tiles the same way, and a tile
 // reads the others of its group and the other groups.
 // WAVES wavefronts share a tile (all of the workgroup where a summary is a wavefront wide), so that row-lanes are many.
 // ---------------------------------------------------------------------------
@@ -1131,7 +1131,6 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
         float near_[kAhead], w[kAhead], S[kAhead][VEC], Q[kAhead][VEC];
         int flags[kAhead];
         int64_t v[kAhead];
-        float any = 0.0f;
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
             const int64_t o = o0 + (int64_t)i * step;
@@ -1140,12 +1139,10 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
             near_[i] = near_anchor(v[i]);
             flags[i] = FLAGGED ? (int)L.scalar[(int64_t)dir * L.count + v[i]].w : kFlagInj;
             w[i] = live ? expf(-fabsf(at - near_[i])) : 0.0f;
-            any += w[i];
         }
-        if (any == 0.0f) break;                              // (farther entries are out of reach as well)
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
-            const bool in = w[i] != 0.0f && (flags[i] & kFlagInj) != 0 && col_ok;
+            const bool in = o0 + (int64_t)i * step < others && (flags[i] & kFlagInj) != 0 && col_ok;
             const int64_t at_v = ((int64_t)dir * L.count + v[i]) * A.bpad + col0;
             load_vec_or_zero<VEC>(S[i], L.s, at_v, in);
             if (STRICT) load_vec_or_zero<VEC>(Q[i], L.q, at_v, in);
