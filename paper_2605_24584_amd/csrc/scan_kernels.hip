@@ -441,10 +441,14 @@ __device__ __forceinline__ Seg<VEC, STRICT> load_level_seg(const Level& L, int d
 
 template <int VEC, bool STRICT>
 __device__ __forceinline__ void store_level_seg(const Level& L, int dir, int64_t idx, int64_t bpad, int64_t col0,
-                                                bool col_ok, bool scalar_writer, const Seg<VEC, STRICT>& s, float flags)
+                                                bool col_ok, bool scalar_writer, const Seg<VEC, STRICT>& s, float flags, uint32_t* counters)
 {
     if (scalar_writer) L.scalar[(int64_t)dir * L.count + idx] = make_float4(s.D, s.C, (float)s.H, flags);
     if (col_ok) {
+        bool finite = true;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) finite = finite && fabsf(s.S[e]) < __uint_as_float(0x7F800000u);
+        if (!finite) counters[kNonFiniteWord] = 1u;      // (any lane's store; cleared by the scan's last kernel)
         const int64_t o = ((int64_t)dir * L.count + idx) * bpad + col0;
         store_vec<VEC>(L.s + o, s.S);
         if (STRICT) store_vec<VEC>(L.q + o, s.Q);
@@ -637,8 +641,8 @@ k_scan_reduce(const ScanArgs A)
         const bool sw = c == 0 && blockIdx.y == 0;
         // (the vectors of a tile with nothing injected are zero and never fetched: not written either)
         const bool vec_ok = col_ok && (tile_flags & kFlagInj);
-        store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, tf, (float)tile_flags);
-        store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, tb, (float)tile_flags);
+        store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, tf, (float)tile_flags, A.counters);
+        store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, tb, (float)tile_flags, A.counters);
     }
 }
 
@@ -847,7 +851,7 @@ k_scan_reduce_wide(const ScanArgs A)
             for (int e = 0; e < VEC; ++e) { tf.S[e] = F[e]; if (STRICT) tf.Q[e] = E[e]; }
             tf.D = tf.C = span_decay_f(A, tile_base, A.spine_rows);     // from the anchors
             if (STRICT) tf.H = Ht;
-            store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, colh, col_ok && (tflags & kFlagInj), sw && h == 0, tf, (float)tflags);
+            store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, colh, col_ok && (tflags & kFlagInj), sw && h == 0, tf, (float)tflags, A.counters);
         }
         if (wave == 0) {
             int Ht = 0;
@@ -858,7 +862,7 @@ k_scan_reduce_wide(const ScanArgs A)
             for (int e = 0; e < VEC; ++e) { tb.S[e] = R[e]; if (STRICT) tb.Q[e] = G[e]; }
             tb.D = tb.C = span_decay_b(A, tile_base, A.spine_rows);
             if (STRICT) tb.H = Ht;
-            store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, colh, col_ok && (tflags & kFlagInj), sw && h == 0, tb, (float)tflags);
+            store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, colh, col_ok && (tflags & kFlagInj), sw && h == 0, tb, (float)tflags, A.counters);
         }
     }
 }
@@ -975,11 +979,11 @@ k_scan_reduce_wave(const ScanArgs A)
     const bool vec_ok = col_ok && (tile_flags & kFlagInj);   // zero vectors are never fetched: not written either
     if (r == rv - 1) {
         f.D = f.C = tile_df;
-        store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, f, (float)tile_flags);
+        store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, f, (float)tile_flags, A.counters);
     }
     if (r == 0) {
         b.D = b.C = tile_db;
-        store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, b, (float)tile_flags);
+        store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, b, (float)tile_flags, A.counters);
     }
 }
 
@@ -1026,7 +1030,7 @@ k_spine_reduce(const ScanArgs A)
             const int64_t t_hi = A.l1.count - 1 - chunk * A.chunk_tiles;          // first tile in scan order
             t.D = span_decay_b(A, (t_hi + 1 - tiles_here) * A.spine_rows, tiles_here * A.spine_rows);
         }
-        store_level_seg<VEC, STRICT>(A.l2, dir, chunk, A.bpad, col0, col_ok, c == 0 && blockIdx.y == 0, t, 0.0f);
+        store_level_seg<VEC, STRICT>(A.l2, dir, chunk, A.bpad, col0, col_ok, c == 0 && blockIdx.y == 0, t, 0.0f, A.counters);
     }
 }
 
@@ -1108,9 +1112,10 @@ __device__ __forceinline__ void list_blocks(const ScanArgs& A, int64_t chunk)
 
 // ---------------------------------------------------------------------------
 // spine by direct sums, for few tiles: a tile's carry is the sum of the other tiles' summaries, each brought to the tile's edge by
-// one exponential of an anchor difference.  Tiles beyond the reach of an fp32 decay (104 units) are read too: 0 * NaN and 0 * inf
-// are NaN, as in the dense product.  Strict channel: a tile that ends at the edge's key contributes its own strict sum if it holds
-// the start of that run, else nothing; the tiles before it contribute whole.  With two levels, k_spine_super first sums up groups of kSuperTiles tiles the same way, and a tile
+// one exponential of an anchor difference.  Tiles beyond the reach of an fp32 decay (104 units) are not read as long as every
+// summary is finite (the reduces mark the scan otherwise): 0 * NaN and 0 * inf are NaN, as in the dense product.  Strict channel: a
+// tile that ends at the edge's key contributes its own strict sum if it holds the start of that run, else nothing; the tiles before
+// it contribute whole.  With two levels, k_spine_super first sums up groups of kSuperTiles tiles the same way, and a tile
 // reads the others of its group and the other groups.
 // WAVES wavefronts share a tile (all of the workgroup where a summary is a wavefront wide), so that row-lanes are many.
 // ---------------------------------------------------------------------------
@@ -1123,6 +1128,7 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
                                             int rl, int step, int64_t col0, bool col_ok, float* F, float* E)
 {
     constexpr int kAhead = 4;
+    const bool read_all = A.counters[kNonFiniteWord] != 0u;
     // the entry's end towards the edge, and the row behind it (sentinels beyond the ends of the sequence)
     auto end_of = [&](int64_t v) { const int64_t e = (v + 1) * SR; return e < A.N ? e : A.N; };
     auto near_anchor = [&](int64_t v) { return dir == 0 ? A.pk[end_of(v)] : A.pk[v * SR + 1]; };
@@ -1131,6 +1137,7 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
         float near_[kAhead], w[kAhead], S[kAhead][VEC], Q[kAhead][VEC];
         int flags[kAhead];
         int64_t v[kAhead];
+        float any = 0.0f;
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
             const int64_t o = o0 + (int64_t)i * step;
@@ -1139,10 +1146,12 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
             near_[i] = near_anchor(v[i]);
             flags[i] = FLAGGED ? (int)L.scalar[(int64_t)dir * L.count + v[i]].w : kFlagInj;
             w[i] = live ? expf(-fabsf(at - near_[i])) : 0.0f;
+            any += w[i];
         }
+        if (any == 0.0f && !read_all) break;                 // (farther entries are out of reach as well)
 #pragma unroll
         for (int i = 0; i < kAhead; ++i) {
-            const bool in = o0 + (int64_t)i * step < others && (flags[i] & kFlagInj) != 0 && col_ok;
+            const bool in = (w[i] != 0.0f || (read_all && o0 + (int64_t)i * step < others)) && (flags[i] & kFlagInj) != 0 && col_ok;
             const int64_t at_v = ((int64_t)dir * L.count + v[i]) * A.bpad + col0;
             load_vec_or_zero<VEC>(S[i], L.s, at_v, in);
             if (STRICT) load_vec_or_zero<VEC>(Q[i], L.q, at_v, in);
@@ -1532,7 +1541,7 @@ __global__ void __launch_bounds__(kScanThreads)
 k_scan_down_sparse(const ScanArgs A)
 {
     // the last kernel of a scan: nothing reads the list lengths any more, and the next scan wants them at zero
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.counters[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kScanCounters) A.counters[threadIdx.x] = 0u;
     const int flags = (int)A.blk_flags[blockIdx.x];
     // result rows and nothing injected (blocks with a few injected rows exist in the wide geometry only, which has a kernel of its own)
     if (!(flags & kFlagRes) || (flags & kFlagInj)) return;
@@ -1558,6 +1567,7 @@ k_scan_down(const ScanArgs A)
     WaveSegs<VEC>& W = *reinterpret_cast<WaveSegs<VEC>*>(smem);
     float* const ef = reinterpret_cast<float*>(smem) + (size_t)threadIdx.x * VEC;   // row i at ef[i * ef_stride]
     constexpr size_t ef_stride = (size_t)WAVES * 64 * VEC;
+    if (A.every_block && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
     if (A.down_from_list && blockIdx.x >= A.counters[1]) return;
     const int64_t tile = A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
     const int flags = (int)A.blk_flags[tile];
@@ -1922,7 +1932,7 @@ k_scan_down_sparse_wide(const ScanArgs A)
 {
     constexpr int VEC = 4, ROWS = 64, CH = 8, NS = kFewRows;
     // the last kernel of a scan: nothing reads the list lengths any more, and the next scan wants them at zero
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) A.counters[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kScanCounters) A.counters[threadIdx.x] = 0u;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t blk = (int64_t)blockIdx.x * kStreamWaves + wave;
@@ -2100,7 +2110,7 @@ k_scan_down_sparse_wide_phased(const ScanArgs A)
 {
     constexpr int VEC = 4, ROWS = 64, CH = 8, NS = kFewRows;
     // the last kernel of a scan that looks at the list lengths: the next scan wants them at zero
-    if (blockIdx.x == 0 && threadIdx.x < 2) A.counters[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < kScanCounters) A.counters[threadIdx.x] = 0u;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int64_t blk = (int64_t)blockIdx.x * kStreamWaves + wave;
@@ -2584,8 +2594,8 @@ k_seq_reduce(const ScanArgs A)
         tf.D = tf.C = span_decay_f(A, tile_base, A.tile_rows);
         tb.D = tb.C = span_decay_b(A, tile_base, A.tile_rows);
         const float flags = (float)(kFlagInj | kFlagRes);
-        store_level_seg<1, STRICT>(A.l1, 0, tile, A.bpad, 0, true, true, tf, flags);
-        store_level_seg<1, STRICT>(A.l1, 1, tile, A.bpad, 0, true, true, tb, flags);
+        store_level_seg<1, STRICT>(A.l1, 0, tile, A.bpad, 0, true, true, tf, flags, A.counters);
+        store_level_seg<1, STRICT>(A.l1, 1, tile, A.bpad, 0, true, true, tb, flags, A.counters);
     }
 }
 
@@ -2606,6 +2616,7 @@ k_seq_down(const ScanArgs A)
     float* const ef = reinterpret_cast<float*>(smem) + threadIdx.x;        // row i at ef[i * THREADS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t tile = blockIdx.x;
+    if (tile == 0 && tid == 0) A.counters[kNonFiniteWord] = 0u;      // the last kernel of the scan
     const uint32_t poison = plan_poison(A.counters);
     const int64_t tile_base = tile * (int64_t)(THREADS * ITEMS);
     const int64_t wave_row0 = tile_base + (int64_t)wave * 64 * ITEMS;
