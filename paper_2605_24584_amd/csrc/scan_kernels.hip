@@ -2849,22 +2849,33 @@ int ilog2(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// One launch where every tile can read every other tile's summary, three (or one workgroup per direction, for a single chunk) otherwise.
-// tiles^2 * batch summaries are read if all anchors are within reach of each other, a few tiles each if they are spread.  Measured
-// (us, forward + backward, before / after; anchors spread, all within reach): n = k = 2^16, batch 8 (128 tiles): 102 / 92, 109 / 98;
-// 20000, batch 32 (157 tiles): 105 / 90, 106 / 102; 2^18, batch 8 (512 tiles, 2^21): 161 / 150, 167 / 163; beyond the line n = k = 2^20,
-// batch 8 (2^25): 424 / 404, 424 / 449.  There two levels read tiles * (32 + tiles / 32) * batch summaries at worst: 424 / 412, 424 / 414
-// (1.6e6); 1024 x 2^18, batch 256 (6.3e6): 300 / 287, 307 / 296; n = k = 2^17, batch 64 (1.3e7): 231 / 243, 237 / 258.
-constexpr double kSpineDirectWork = double(1 << 24), kSpineSuperWork = double(1 << 23);
+// One launch where every tile can read every other tile's summary, two with sums of groups of tiles in between, three (or one
+// workgroup per direction, for a single chunk) otherwise.  With one level tiles^2 * batch values are read where all anchors are within
+// reach of each other, a few tiles each where they are spread; with two, tiles * (32 + tiles / 32) * batch at worst.  A line lies where
+// reading all of them costs as much as the other launches, which depends on how many of a tile's lanes read side by side (us, one
+// product on a kept plan, all within reach: three launches / one level / two; the same spread for one level and two):
+//   eight row-lanes or more, a wavefront per tile   2^18, batch 8 (2.1e6): 40 / 36 / 37; 100000, batch 16 (2.4e6): 31 / 30 / 28 (25 / 29);
+//     50000, batch 20 (3.1e6): 32 / 35 / 29 (24 / 29); 400000, batch 8 (4.9e6): 56 / 55 / 53 (48 / 52); 70000, batch 32 (9.6e6):
+//     41 / 40 / 29 (25 / 29); 200000, batch 16 (9.8e6): 39 / 43 / 36 (32 / 36); 700000, batch 8 (1.5e7): 81 / 84 / 76 (73 / 76)
+//   fewer, a workgroup per tile, 4 columns a lane   30000, batch 256 (3.5e6): 52 / 43 / 45 (41 / 45); 60000, batch 256 (1.4e7): 70 / 67 / 65
+//   single columns, several row-lanes (two levels read 256 bytes per entry there and gain nothing)
+//     60000, batch 17 (4.4e6): 51 / 46; 80000, batch 17 (7.8e6): 59 / 58; 70000, batch 31 (1.1e7): 60 / 55
+//   single columns, one row-lane                    20000, batch 33 (3.5e6): 44 / 43; 12000, batch 130 (4.6e6): 51 / 51; 20000, batch 65
+//     (6.6e6): 50 / 60; 30000, batch 33 (7.9e6): 45 / 51
+// Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
+// 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243.
+constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnsWork = 12e6, kSpineColumnWork = 5e6;
+constexpr double kSpineSuperWork = double(1 << 23);
 template <int VEC, bool STRICT>
 void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
 {
     const dim3 block(kScanThreads), cgrid((unsigned)g.chunks, (unsigned)g.slabs, 2);
     Level super = A.l2;
     super.count = (g.tiles + kSuperTiles - 1) / kSuperTiles;
-    const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= kSpineDirectWork;
-    // (with single columns and fewer than eight row-lanes a workgroup reads 256 bytes per entry: 217 us with three launches, 220 with two)
-    const bool two = !one && (VEC == 4 || g.rv >= 8) && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= kSpineSuperWork;
+    const bool groups_gain = VEC == 4 || g.rv >= 8;
+    const double line = g.rv >= 8 ? kSpineWaveWork : VEC == 4 ? kSpineGroupWork : g.rv > 1 ? kSpineColumnsWork : kSpineColumnWork;
+    const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= line;
+    const bool two = !one && groups_gain && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= kSpineSuperWork;
     if (one || two) {
         const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
         auto groups = [&](int64_t n) { return (unsigned)(g.rv >= 8 ? (n + kScanWaves - 1) / kScanWaves : n); };
