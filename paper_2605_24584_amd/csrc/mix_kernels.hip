@@ -412,7 +412,7 @@ k_mix_scan_reduce(const MixPath A, const float* __restrict__ v, int64_t ldv)
 
 // ---------------------------------------------------------------------------
 // Second launch: a tile adds up the other tiles' sums itself, each brought to the tile by one exponential of an anchor
-// difference (a tile beyond the reach of an fp32 decay is not read), scans its row-lanes, and walks its rows in both directions.
+// difference, scans its row-lanes, and walks its rows in both directions.
 // Rows of the short side: fr[op][slab][row] = (F_row | R_row), 2 x width floats.  FOLDED: F_j holds the long rows not above short
 // anchor j, R_j those above it, E_j those strictly below; products F + R and strict sums R - E leave row by row, or as dots with
 // the rows of u.  E is never F with the equal rows taken out again, which would keep no digit of a strict sum that is 2^-24 of
@@ -463,8 +463,7 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
         for (int u = rl; u < A.tiles; u += kMixWaves * rv) {
             if (u == tile) continue;
             const float w = u < tile ? expf(-(p_before - pos((u + 1) * rows - 1))) : expf(-(pos(u * rows) - p_after));
-            if (w == 0.0f) continue;
-            float t[VEC];
+            float t[VEC];                                 // (read whatever the decay: 0 * NaN and 0 * inf are NaN, as in the dense product)
             load_cols<VEC>(t, (u < tile ? sf : sb) + (int64_t)u * A.width, true);
 #pragma unroll
             for (int e = 0; e < VEC; ++e) { if (u < tile) Fc[e] += w * t[e]; else Rc[e] += w * t[e]; }

@@ -137,3 +137,27 @@ def test_non_finite_rows_reach_every_row(k, n, batch, bad):
             assert_all_non_finite("gx", gx, col); assert_all_non_finite("gb", gb)
         finite = (y if side == "gy" else gx)
         assert bool(torch.isfinite(finite).all())
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("r,k,n,batch", [(2, 3000, 7000, 1), (2, 7000, 3000, 33), (3, 5000, 5000, 64), (2, 300, 400, 8), (4, 33000, 33000, 2)])
+def test_mix_non_finite_rows_reach_every_row(r, k, n, batch, bad):
+    """The same for sums of operators, on each of their routes."""
+    q = np.random.default_rng(k + batch)
+    a, b = (q.uniform(0, 3000, (r, s)).astype(np.float32) for s in (k, n))
+    w = np.ones(r, dtype=np.float32)
+    x, g = (q.normal(size=(s, batch)).astype(np.float32) for s in (n, k))
+    col = batch // 2
+    for side in ("x", "gy"):
+        bx, bg = x.copy(), g.copy()
+        (bx if side == "x" else bg)[q.integers(0, n if side == "x" else k), col] = bad
+        y, gx, ga, gb, gw = mix_step(a, b, w, bx, bg, B.LAPLEX_SAVE_SCANS)
+        assert_all_non_finite("gw", gw)
+        if side == "x":
+            assert_all_non_finite("y", y, col)
+            for v in ga:
+                assert_all_non_finite("ga", v)
+        else:
+            assert_all_non_finite("gx", gx, col)
+            for v in gb:
+                assert_all_non_finite("gb", v)
