@@ -184,6 +184,12 @@ int scan_and_send_home(ScanProblem& p, const Layout& L, char* ws, bool want_firs
     return LAPLEX_OK;
 }
 
+// Small problems: ranks by counting and one launch for the scans (small_kernels.hip).  Its chunks read each other's rows; where that
+// is too much, with wide batches, the tiled scans take over, on a plan that is ranked all the same.
+bool use_small(const Layout& L) { return L.N <= kSmallMax && !small_reads_too_much(L.N, L.batch); }
+
+SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float tau, const Plan& P, const Layout& L, uint32_t flags);
+
 // Sort (or merge) the anchors and compute the neighbour decays, unless the plan is reused.
 int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, const Layout& L, char* ws,
                uint32_t flags, bool both_sorted, hipStream_t st)
@@ -195,7 +201,10 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
     uint32_t* keys0 = reinterpret_cast<uint32_t*>(pair0);      // the merge leaves its sorted keys here
     uint32_t* small = reinterpret_cast<uint32_t*>(ws + L.off_sort_small);
     uint32_t* counters = reinterpret_cast<uint32_t*>(ws + L.off_counters);
-    if (both_sorted) {
+    if (L.N <= kSmallMax) {      // (the promises of sorted anchors are not needed here)
+        LAPLEX_HIP(launch_small(small_args(a, k, b, n, tau, P, L, flags), 1, st));      // no scan problem: the sort alone
+        LAPLEX_HIP(launch_decay(nullptr, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
+    } else if (both_sorted) {
         LAPLEX_HIP(launch_merge(a, k, b, n, tau, keys0, P.ids, st));
         LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
     } else if (L.N <= kRunSortMax) {
@@ -653,7 +662,7 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
         if (flags & LAPLEX_SAVE_SCANS) LAPLEX_HIP(launch_fill(P.z, k, batch, batch, 0.0f, st));
         return LAPLEX_OK;
     }
-    if (L.N <= kSmallMax) {        // sort, decays, both scans and the scatter in one launch
+    if (use_small(L)) {            // a sort and one launch for both scans
         SmallArgs S = small_args(a, k, b, n, tau, P, L, flags);
         S.nprob = 1;
         SmallProblem& q = S.prob[0];
@@ -719,7 +728,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     }
     char* w = static_cast<char*>(ws);
     const Plan P = plan_of(L, w);
-    if (L.N <= kSmallMax) {        // one launch for the sort and both scan problems, then the two row reductions
+    if (use_small(L)) {            // a sort, one launch for both scan problems, then the two row reductions
         SmallArgs S = small_args(a, k, b, n, tau, P, L, flags);
         float* zg = reinterpret_cast<float*>(w + L.off_small);
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {     // strict scans of x at the outputs, not kept by the forward
@@ -821,7 +830,7 @@ static int gram_impl(const float* a, int64_t n, const float* x, int64_t ldx, int
     char* w = static_cast<char*>(ws);
     const Plan P = plan_of(L, w);
     hipStream_t st = stream;
-    if (L.N <= kSmallMax) {        // the two-launch path for small problems
+    if (use_small(L)) {            // the two-launch path for small problems
         SmallArgs S = small_args(a, n, nullptr, 0, tau, P, L, flags);
         S.nprob = 1;
         SmallProblem& q = S.prob[0];
@@ -882,7 +891,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
     LAPLEX_CHECK(check_ws(ws, ws_bytes, L));
     char* w = static_cast<char*>(ws);
     const Plan P = plan_of(L, w);
-    if (L.N <= kSmallMax) {        // the two-launch path for small problems, then one row reduction
+    if (use_small(L)) {            // the two-launch path for small problems, then one row reduction
         SmallArgs S = small_args(a, n, nullptr, 0, tau, P, L, flags);
         float* zg = reinterpret_cast<float*>(w + L.off_small);
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {

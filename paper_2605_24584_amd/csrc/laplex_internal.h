@@ -304,8 +304,9 @@ hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, fl
 
 // dh[j] = decay from sorted key j-1 to j (>= 0), or -1 if the two keys are equal;
 // dh[0] = dh[N] = 0 (nothing beyond either end).  pk[j+1] = sorted anchor j, pk[0] = -inf, pk[N+1] = +inf.
-// After the radix sort (ghist = its small words) the anchors are in pk[1 .. N] already and the kernel adds the sentinels;
-// ghist == nullptr: the merge path, which leaves sorted keys in `keys`.  The last kernel of every plan build: it also
+// keys == nullptr: the anchors are in pk[1 .. N] already (after the radix sort, ghist = its small words, or a sort that never waits,
+// ghist = nullptr) and the kernel adds the sentinels; otherwise the merge path, which leaves sorted keys in `keys`.  The last kernel
+// of these plan builds: it also
 // clears the scans' list counters (64 words).
 hipError_t launch_decay(const uint32_t* keys, const uint32_t* ghist, float* dh, float* pk, float2* pk8, uint32_t* counters,
                         int64_t N, hipStream_t st);
@@ -455,6 +456,8 @@ struct SmallArgs {
     int nprob; SmallProblem prob[2];
 };
 hipError_t launch_small(const SmallArgs& A, int64_t operators, hipStream_t st);
+// Whether the chunks of launch_small's scans read so much of each other's rows that the tiled scans are faster (see its definition).
+bool small_reads_too_much(int64_t N, int64_t batch);
 
 // LAPLEX^(r) helpers (phase_kernels.hip).  parts: r contiguous (rows, batch) matrices; w, scale: device memory.
 //   combine: y = sum_q w[q] parts[q];  scale: dst (contiguous) = scale[0] * src;  accumulate: dst (+)= src (contiguous);

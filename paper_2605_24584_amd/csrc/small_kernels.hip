@@ -146,7 +146,7 @@ k_small(const SmallArgs A, int slabs)
     const float p_left = pos(q0 - 1), p_right = pos(q0 + ITEMS);
 
     // the other rows' weights, once per workgroup
-    for (int j = tid; j < N; j += kChunkThreads) {
+    for (int j = row0 > 0 || row1 < N ? tid : N; j < N; j += kChunkThreads) {
         const uint32_t e = ids[j];
         const float pj = pk[j + 1];
         const bool in = e >= P.inj_lo && e < P.inj_hi && !(j >= row0 && j < row1);
@@ -308,6 +308,18 @@ k_small(const SmallArgs A, int slabs)
 
 }  // namespace
 
+// Measured at the line (us, forward + backward; forward: chunks / tiled scans / one workgroup per 16 columns that walks all rows):
+// n = k = 4096, batch 128 (3.4e7 values): 68 / 68 / 130; 33 / 33 / 50, batch 160: 98 / 88 / 129, batch 1024 (2.7e8): 407 / 130 / 327;
+// 181 / 43 / 119; 4000 x 2000, batch 192 (2.8e7): 88 / 85 / 112, batch 384 (5.5e7): 138 / 96 / 210; 2000 x 2000, batch 512 (3.3e7):
+// 78 / 91 / 141, batch 768 (4.9e7): 114 / 99 / 210; 500 x 500, batch 8192 (3.3e7): 192 / 175 / 227.
+constexpr double kSmallReads = 3.5e7;
+bool small_reads_too_much(int64_t N, int64_t batch)
+{
+    const int64_t rows = kChunkThreads / 16 * 8;               // a chunk of the widest form below
+    const int64_t chunks = (N + rows - 1) / rows;
+    return chunks > 1 && (double)chunks * (double)N * (double)batch > kSmallReads;
+}
+
 hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
 {
     SmallArgs A = A0;
@@ -320,10 +332,12 @@ hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
     }
     if (A.nprob > 0) {
         // Columns and rows per lane: as few as still leave a compute unit no more than one workgroup (short chains, nothing
-        // chained twice), since every chunk reads the rows of all others; then wider.  Measured (us, forward + backward; the four
-        // forms): n = k = 4096, batch 8: 43 / 44 / 56 / 72, batch 32: 60 / 51 / 56 / 104, batch 64: 94 / 67 / 61 / 104, batch 256:
-        // 332 / 191 / 123 / 128; 16 operators of 500 x 500, batch 64: 102 / 82 / 68 / 70, batch 256: 231 / 150 / 118 / 105.
-        const int forms[4][2] = {{1, 1}, {1, 2}, {4, 4}, {16, 8}};
+        // chained twice), since every chunk reads the rows of all others; then wider.  With four chunks or more four columns with four
+        // rows are worth two workgroups a compute unit (100 x 5000, batch 128, forward: 27 us, sixteen with eight 34; 4000 x 2000, batch
+        // 128, forward + backward: 58 / 75), not more (100 x 5000, batch 256: 44 / 37; two chunks, 512 x 512, batch 1024: 51 / 46).  Measured (us, forward + backward; the four forms): n = k =
+        // 4096, batch 8: 43 / 44 / 56 / 72, batch 32: 60 / 51 / 56 / 104, batch 64: 94 / 67 / 61 / 104; 16 operators of 500 x 500, batch
+        // 64: 102 / 82 / 68 / 70, batch 256: 231 / 150 / 118 / 105.
+        const int forms[4][2] = {{1, 1}, {1, 2}, {4, 4}, {16, 8}};      // columns, rows
         int cols = 1, items = 1;
         int64_t slabs = 0, chunks = 0;
         for (const auto& f : forms) {
@@ -331,7 +345,7 @@ hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
             while (cols < A.batch && cols < f[0]) cols <<= 1;
             const int64_t rows = (int64_t)kChunkThreads / cols * items;
             slabs = (A.batch + cols - 1) / cols; chunks = (N + rows - 1) / rows;
-            if (slabs * chunks * operators <= 256) break;      // (whatever the problems of the launch: the form shows in the last bits)
+            if (slabs * chunks * operators <= (f[0] == 4 && chunks >= 4 ? 512 : 256)) break;      // (whatever the problems of the launch: the form shows in the last bits)
         }
         A.cols = cols;
         const dim3 grid((unsigned)(chunks * slabs), (unsigned)(operators * A.nprob));

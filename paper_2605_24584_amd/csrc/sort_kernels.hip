@@ -705,7 +705,7 @@ hipError_t launch_decay(const uint32_t* keys, const uint32_t* ghist, float* dh, 
                         int64_t N, hipStream_t st)
 {
     const dim3 grid(grid_for((N + 5) / 4, 256)), block(256);
-    if (ghist != nullptr) LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<true>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N));
+    if (keys == nullptr) LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<true>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N));
     else LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<false>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N));
     return hipGetLastError();
 }

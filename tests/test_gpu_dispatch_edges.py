@@ -117,6 +117,44 @@ def test_small_problem_chunks(oracle, kind, k, n, batch):
         assert_close(name, v, rv, tv)
 
 
+@pytest.mark.parametrize("k,n,batch", [
+    (4096, 4096, 133), (4096, 4096, 134), (8191, 1, 136), (1, 8191, 139), (7, 7000, 300),         # 3.5e7 values read by the chunks of 256 rows
+    (2000, 2096, 520), (2000, 2096, 560), (300, 213, 22800), (300, 213, 40000), (3, 253, 140000),  # (the last: one chunk, always small)
+])
+def test_small_problems_with_wide_batches(oracle, k, n, batch):
+    """Either side of the line from which problems of at most 8192 positions take the tiled scans: the permutation, both directions
+    with and without a kept plan, a false promise of sorted anchors (small problems make no use of it); bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward, gpu_perm, gpu_plan_status
+    r = np.random.default_rng(k + 3 * n + batch)
+    a, b = anchors("ties", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    y, ws = gpu_apply(a, b, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    assert np.array_equal(gpu_perm(ws, k + n), oracle.merged_permutation(a, b)) and gpu_plan_status(ws, k + n) == 0
+    saved = gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws)
+    alone = gpu_backward(a, b, x, g, flags=B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED)
+    for name, u, v, rv, tv in zip(("gx", "ga", "gb"), saved, alone, want, tols):
+        assert_close(name, u, rv, tv)
+        assert_close(name, v, rv, tv)
+
+
+@pytest.mark.parametrize("n,batch", [(8192, 133), (8192, 134), (4001, 700)])
+def test_small_gram_with_wide_batches(oracle, n, batch):
+    from test_gpu_parity import anchors, assert_close, gpu_gram, gpu_gram_backward
+    r = np.random.default_rng(n + batch)
+    a, _ = anchors("ties", r, n, 1)
+    x, g = (r.normal(size=(n, batch)).astype(np.float32) for _ in range(2))
+    ref, tol = oracle.gram_scan(a, x)
+    y, ws = gpu_gram(a, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    want, tols = oracle.gram_backward_scan(a, x, g)
+    for got in (gpu_gram_backward(a, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws), gpu_gram_backward(a, x, g, flags=B.LAPLEX_A_SORTED)):
+        for name, u, rv, tv in zip(("gx", "ga"), got, want, tols):
+            assert_close(name, u, rv, tv)
+
+
 def test_mix_common_launches_non_finite_anchors(oracle):
     """Values are unspecified, but the calls end, and the workspace serves a clean problem afterwards."""
     from test_gpu_parity import anchors, assert_close
