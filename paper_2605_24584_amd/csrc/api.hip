@@ -345,7 +345,7 @@ struct MixLayout {
     size_t inner = 0, off_parts = 0, off_gyq = 0, off_gxq = 0, off_gxp = 0, off_partial = 0, total = 0;
     int lanes = 1;      // operators in flight at a time on the large path (each on a stream of its own)
     bool common = false;      // all operators in common launches (mix_kernels.hip); in place of the regions above:
-    size_t off_srow = 0, off_sp = 0, off_tied = 0, off_bound = 0, off_slots = 0, off_recs = 0, off_sorted = 0, off_tasks = 0, off_folds = 0, off_equal = 0,
+    size_t off_srow = 0, off_sp = 0, off_tied = 0, off_equals = 0, off_bound = 0, off_slots = 0, off_recs = 0, off_sorted = 0, off_tasks = 0, off_folds = 0, off_equal = 0,
            off_sums = 0, off_fr = 0, off_p = 0, off_z = 0, off_dot_long = 0, off_dot_short = 0, off_dot_total = 0;
 };
 
@@ -394,6 +394,7 @@ MixLayout mix_layout(int64_t r, int64_t k, int64_t n, int64_t batch)
         M.off_srow = o;   o = align_up(o + sizeof(uint32_t) * ops * m);
         M.off_sp = o;     o = align_up(o + sizeof(float) * ops * m);
         M.off_tied = o;   o = align_up(o + sizeof(uint32_t) * ops * m);
+        M.off_equals = o; o = align_up(o + sizeof(uint32_t) * ops * m);
         M.off_bound = o;  o = align_up(o + sizeof(uint32_t) * ops * (m + 2));
         M.off_slots = o;  o = align_up(o + sizeof(uint2) * ops * (m + 1));
         M.off_recs = o;   o = align_up(o + sizeof(uint4) * ops * l);
@@ -443,7 +444,7 @@ struct MixCommon {
         A.m = (int)(A.short_b ? n : k); A.l = (int)(A.short_b ? k : n);
         A.long_anchor = A.short_b ? a : b;
         A.srow = reinterpret_cast<uint32_t*>(base + M.off_srow); A.sp = reinterpret_cast<float*>(base + M.off_sp);
-        A.tied = reinterpret_cast<uint32_t*>(base + M.off_tied); A.bound = reinterpret_cast<uint32_t*>(base + M.off_bound);
+        A.tied = reinterpret_cast<uint32_t*>(base + M.off_tied); A.equals = reinterpret_cast<uint32_t*>(base + M.off_equals); A.bound = reinterpret_cast<uint32_t*>(base + M.off_bound);
         A.recs = reinterpret_cast<uint4*>(base + M.off_recs); A.sorted = reinterpret_cast<uint4*>(base + M.off_sorted);
         A.slots = reinterpret_cast<uint2*>(base + M.off_slots); A.tasks = reinterpret_cast<uint2*>(base + M.off_tasks); A.task_count = (int)mix_task_count(A.m, A.l);
         A.folds = reinterpret_cast<float*>(base + M.off_folds); A.equal = reinterpret_cast<float*>(base + M.off_equal);

@@ -490,6 +490,7 @@ struct MixPath {
     // part of the plan, per operator:
     uint32_t* srow; float* sp;     // [m]      the short side in sorted order: row, anchor
     uint32_t* tied;                // [m]      0, or 1 + the first of the short rows with this anchor if long rows have it too
+    uint32_t* equals;              // [m]      long rows with this anchor
     uint32_t* bound;               // [m + 2]  first long row, in sorted order, of every interval
     uint4* recs;                   // [l]      by row: short anchors below, below or equal; decays from / to the neighbours
     uint4* sorted;                 // [l]      in sorted order: row, the two decays, equal to a short anchor

@@ -123,6 +123,7 @@ k_mix_index(const MixPath A)
     uint32_t* srow = A.srow + op * A.m;
     float* sp = A.sp + op * A.m;
     uint32_t* tied = A.tied + op * A.m;
+    uint32_t* equals = A.equals + op * A.m;
     uint32_t* bound = A.bound + op * (A.m + 2);
     uint4* recs = A.recs + op * A.l;
 #pragma unroll
@@ -142,15 +143,17 @@ k_mix_index(const MixPath A)
             for (int hi = b0; f0 < hi;) { const int mid = (f0 + hi) >> 1; if (ids[mid] < k) f0 = mid + 1; else hi = mid; }
         }
         if (is_short(id[i])) {
-            int not_above = j - s, first = 0;             // long rows at or below this anchor; 1 + first short row of the run
+            int not_above = j - s, first = 0, equal = 0;  // long rows at or below this anchor; 1 + first short row of the run; long rows in it
             if (run) {
                 const int head = short_b ? s - (j - f0) : s - (j - a0);
                 if (!short_b) not_above = b0 - head - (f0 - a0);
-                first = (short_b ? f0 - a0 : b0 - f0) > 0 ? 1 + head : 0;
+                equal = short_b ? f0 - a0 : b0 - f0;
+                first = equal > 0 ? 1 + head : 0;
             }
             srow[s] = short_b ? id[i] - k : id[i];
             sp[s] = p;
             tied[s] = (uint32_t)first;
+            equals[s] = (uint32_t)equal;
             bound[s + 1] = (uint32_t)not_above;
             ++s;
         } else {
@@ -173,6 +176,10 @@ k_mix_records(const MixPath A)
     const int64_t op = blockIdx.y;
     const int m = A.m, i = blockIdx.x * kMixThreads + threadIdx.x;
     const float* sp = A.sp + op * m;
+    const uint32_t* bound = A.bound + op * (m + 2);
+    uint2* tasks = A.tasks + op * A.task_count;
+    // the tasks of interval c, which holds the sorted rows first .. end, start at this one
+    auto first_task = [&](int c, int first) { return c + first / kMixTaskRows; };
     if (i < A.l) {
         const uint4 r = A.recs[op * A.l + i];
         const int lo = (int)r.x;
@@ -182,19 +189,16 @@ k_mix_records(const MixPath A)
         A.recs[op * A.l + i] = make_uint4(r.x, r.y, __float_as_uint(el), __float_as_uint(er));
         const bool equal = r.x != r.y;
         A.sorted[op * A.l + r.z] = make_uint4((uint32_t)i, __float_as_uint(el), equal ? 0u : __float_as_uint(er), equal ? 1u : 0u);
+        const int first = (int)bound[lo], end = (int)bound[lo + 1], at = (int)r.z;      // every 32nd row of an interval writes a task
+        if ((at - first) % kMixTaskRows == 0)
+            tasks[first_task(lo, first) + (at - first) / kMixTaskRows] = make_uint2((uint32_t)at, (uint32_t)(end - at < kMixTaskRows ? end - at : kMixTaskRows));
     }
     if (i <= m) {
-        const uint32_t* bound = A.bound + op * (m + 2);
-        const int first = (int)bound[i], end = (int)bound[i + 1];
-        const int t0 = i + first / kMixTaskRows, t1 = i + 1 + end / kMixTaskRows;
-        uint2* tasks = A.tasks + op * A.task_count;
+        const int first = (int)bound[i], end = (int)bound[i + 1], t0 = first_task(i, first);
         A.slots[op * (m + 1) + i] = make_uint2((uint32_t)t0, (uint32_t)(end - first));
-        for (int t = t0; t < t1; ++t) {
-            const int at = first + (t - t0) * kMixTaskRows;
-            const int n = at < end ? (end - at < kMixTaskRows ? end - at : kMixTaskRows) : 0;
-            tasks[t] = make_uint2((uint32_t)at, (uint32_t)n);
-        }
-        if (i == m) for (int t = t1; t < A.task_count; ++t) tasks[t] = make_uint2(0u, 0u);
+        // the room behind them, at most one task, and behind the last interval's
+        const int t1 = i < m ? first_task(i + 1, end) : A.task_count;
+        for (int t = t0 + (end - first + kMixTaskRows - 1) / kMixTaskRows; t < t1; ++t) tasks[t] = make_uint2(0u, 0u);
     }
 }
 
@@ -257,19 +261,105 @@ k_mix_fold(const MixPath A, const float* __restrict__ v, int64_t ldv, int lanes,
     if (any) store_cols<VEC>(A.equal + slot * A.width + in, eq);
 }
 
-// Sum over the tasks of an interval (slot: its first task, its rows) of the vectors at base + task * stride.
-template <int VEC>
-__device__ __forceinline__ void load_interval(float* dst, uint2 slot, const float* base, int stride)
+// ---------------------------------------------------------------------------
+// Join: the sums of an interval's tasks, added up in the place of its first task's, so that the scans read one of them.  Most
+// intervals have a single task: a workgroup looks through some of them, shares its row-lanes among those that have more, and sets all
+// of them to work on one with very many (few short rows between many long ones, or all of them between two).  With the scans adding up
+// the tasks themselves, interval after interval, 100 x 100000, batch 8, a product on a kept plan took 289 us, now 36.
+// ---------------------------------------------------------------------------
+constexpr int kJoinIntervals = 256, kJoinAlone = 32;
+
+template <int VEC, int THREADS>
+__global__ void __launch_bounds__(THREADS)
+k_mix_join(const MixPath A, int per)
 {
-    const int n = (int)slot.y;
-    const float* at = base + (int64_t)slot.x * stride;
-    load_cols<VEC>(dst, at, n > 0);
-    for (int q = kMixTaskRows; q < n; q += kMixTaskRows) {
-        float t[VEC];
-        at += stride;
-        load_cols<VEC>(t, at, true);
+    static_assert(THREADS >= kJoinIntervals, "an interval per thread");
+    __shared__ int list[kJoinIntervals], count;
+    __shared__ __align__(16) float part[THREADS * VEC];
+    const int tid = threadIdx.x;
+    const int64_t op = blockIdx.y;
+    const int slab = (int)blockIdx.x % A.slabs, i0 = (int)blockIdx.x / A.slabs * per;
+    const uint2* slots = A.slots + op * (A.m + 1);
+    if (tid == 0) count = 0;
+    __syncthreads();
+    if (tid < per && i0 + tid <= A.m && slots[i0 + tid].y > (uint32_t)kMixTaskRows) list[atomicAdd(&count, 1)] = i0 + tid;
+    __syncthreads();
+    const int found = count;
+    if (found == 0) return;                               // uniform
+    // columns: those of the folds (2 * width), then those of the equal rows (width)
+    const int row = 3 * A.width, lanes = row / VEC, side = THREADS / lanes;
+    const int c = tid % lanes * VEC, rl = tid / lanes;    // (rl >= side: lanes that make no whole row)
+    const bool folds = c < 2 * A.width;
+    const int stride = folds ? 2 * A.width : A.width;
+    float* const at = folds ? A.folds + (op * A.slabs + slab) * (int64_t)A.task_count * (2 * A.width) + c
+                            : A.equal + (op * A.slabs + slab) * (int64_t)A.task_count * A.width + (c - 2 * A.width);
+    const int group = found < side ? side / found : 1;    // row-lanes of an interval
+    struct Range { int first, end; bool many; };
+    auto range = [&](int q) {
+        const int i = list[q];
+        const uint2 slot = slots[i];
+        Range r;
+        r.first = (int)slot.x;
+        r.end = r.first + ((int)slot.y + kMixTaskRows - 1) / kMixTaskRows;
+        r.many = r.end - r.first > kJoinAlone * group;
+        if (!folds) {                                     // (they come last in the interval; tasks without any have not written theirs)
+            const bool tied = i < A.m && A.tied[op * A.m + i] == (uint32_t)i + 1u;
+            r.first = tied ? r.first + (int)(slot.y - A.equals[op * A.m + i]) / kMixTaskRows : r.end;
+        }
+        return r;
+    };
+    auto add_up = [&](float* s, int first, int end, int step) {
+        constexpr int AHEAD = 4;
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) dst[e] += t[e];
+        for (int e = 0; e < VEC; ++e) s[e] = 0.0f;
+        for (int t = first; t < end; t += AHEAD * step) {
+            float v[AHEAD][VEC];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) load_cols<VEC>(v[i], at + (int64_t)(t + i * step) * stride, t + i * step < end);
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) s[e] += v[i][e];
+        }
+    };
+    // the row-lanes at first .. first + lanes hold parts of a sum: the first of them adds them up
+    auto finish = [&](const Range& r, int first, int lanes_of_it) {
+        float s[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) s[e] = 0.0f;
+        for (int u = first; u < first + lanes_of_it; ++u) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) s[e] += part[u * row + c + e];
+        }
+        store_cols<VEC>(at + (int64_t)r.first * stride, s);
+    };
+    for (int q0 = 0; q0 < found; q0 += side / group) {
+        const int q = q0 + rl / group;
+        const bool mine = rl < side / group * group && q < found;
+        const Range r = range(mine ? q : 0);
+        const bool work = mine && !r.many && r.end - r.first > 1;
+        float s[VEC];
+        if (work) add_up(s, r.first + rl % group, r.end, group);
+        if (group == 1) {                                 // uniform
+            if (work) store_cols<VEC>(at + (int64_t)r.first * stride, s);
+            continue;
+        }
+        if (work) store_cols<VEC>(part + rl * row + c, s);
+        __syncthreads();
+        if (work && rl % group == 0) finish(r, rl, group);
+        __syncthreads();
+    }
+    for (int q = 0; q < found; ++q) {
+        const Range r = range(q);
+        if (!r.many) continue;                            // uniform
+        if (rl < side) {
+            float s[VEC];
+            add_up(s, r.first + rl, r.end, side);
+            store_cols<VEC>(part + rl * row + c, s);
+        }
+        __syncthreads();
+        if (rl == 0 && r.first < r.end) finish(r, 0, side);
+        __syncthreads();
     }
 }
 
@@ -297,31 +387,18 @@ __device__ __forceinline__ void load_rows(const MixPath& A, int64_t op, int slab
             if (j0 + i > A.m) slot[i].y = 0u;
         }
 #pragma unroll
-        for (int i = 0; i < kMixItems; ++i) load_interval<VEC>(f[i], j0 + i < A.m ? slot[i] : make_uint2(0u, 0u), folds, 2 * A.width);
+        for (int i = 0; i < kMixItems; ++i) load_cols<VEC>(f[i], folds + (int64_t)slot[i].x * (2 * A.width), j0 + i < A.m && slot[i].y > 0u);
 #pragma unroll
-        for (int i = 0; i < kMixItems; ++i) load_interval<VEC>(b[i], slot[i + 1], folds + A.width, 2 * A.width);
+        for (int i = 0; i < kMixItems; ++i) load_cols<VEC>(b[i], folds + (int64_t)slot[i + 1].x * (2 * A.width) + A.width, slot[i + 1].y > 0u);
     }
 }
 // The long rows equal to short anchor j, to be added to the forward value (they are in the interval of the first such anchor).
 template <int VEC>
 __device__ __forceinline__ void load_equal(const MixPath& A, int64_t op, int slab, int c, int j, float* t)
 {
-    const uint32_t* bound = A.bound + op * (A.m + 2);
     const float* equal = A.equal + (op * A.slabs + slab) * (int64_t)A.task_count * A.width + c * VEC;
-    // (equal rows come last in their interval, and a task without any has not written its vector)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) t[e] = 0.0f;
-    const uint2* tasks = A.tasks + op * A.task_count;
-    const int first = (int)bound[j], end = (int)bound[j + 1];
-    const int t0 = j + first / kMixTaskRows, parts = (end - first + kMixTaskRows - 1) / kMixTaskRows;
-    for (int q = parts - 1; q >= 0; --q) {
-        const uint2 task = tasks[t0 + q];
-        if (task.y == 0u || A.sorted[op * A.l + task.x + task.y - 1].w == 0u) break;
-        float u[VEC];
-        load_cols<VEC>(u, equal + (int64_t)(t0 + q) * A.width, true);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) t[e] += u[e];
-    }
+    const uint2 slot = A.slots[op * (A.m + 1) + j];
+    load_cols<VEC>(t, equal + (int64_t)(slot.x + (slot.y - A.equals[op * A.m + j]) / kMixTaskRows) * A.width, true);
 }
 
 // ---------------------------------------------------------------------------
@@ -845,6 +922,17 @@ void go_fold(const MixPath& A, const float* v, int64_t ldv, hipStream_t st)
     else LAPLEX_TIMED("mix_fold", st, hipLaunchKernelGGL((k_mix_fold<VEC, false>), grid, block, 0, st, A, v, ldv, lanes, spans));
 }
 
+// A few intervals and many threads for a workgroup where most intervals have several tasks, many and few where most have one.
+template <int VEC>
+void go_join(const MixPath& A, hipStream_t st)
+{
+    const bool several = A.l / kMixTaskRows * 2 > A.m;
+    const int per = several ? 16 : kJoinIntervals;
+    const dim3 grid((unsigned)((A.m + 1 + per - 1) / per * A.slabs), (unsigned)A.operators);
+    if (several) LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, 1024>), grid, dim3(1024), 0, st, A, per));
+    else LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, kJoinIntervals>), grid, dim3(kJoinIntervals), 0, st, A, per));
+}
+
 }  // namespace
 
 hipError_t launch_mix_scan(const MixPath& A, const float* v, int64_t ldv, hipStream_t st)
@@ -858,6 +946,10 @@ hipError_t launch_mix_fold(const MixPath& A, const float* v, int64_t ldv, const 
 {
     if (A.batch % 4 == 0 && aligned_rows(v, ldv)) go_fold<4>(A, v, ldv, st);
     else go_fold<1>(A, v, ldv, st);
+    if (A.l > kMixTaskRows) {      // (else no interval has two tasks)
+        if (A.batch % 4 == 0) go_join<4>(A, st);
+        else go_join<1>(A, st);
+    }
     if (A.batch % 4 == 0 && aligned_rows(S.u, S.ldu)) go_scan<4, true>(A, nullptr, 0, S, st);
     else go_scan<1, true>(A, nullptr, 0, S, st);
     return hipGetLastError();

@@ -282,3 +282,32 @@ def test_mix_operator_by_operator(oracle, r, k, n, batch):
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(u, v) for u, v in zip(out, eager))
+
+
+@pytest.mark.parametrize("k,n,batch", [(40, 120000, 8), (120000, 40, 5), (300, 70000, 64), (70000, 300, 33), (5, 100000, 1), (3, 9000, 256)])
+@pytest.mark.parametrize("kind", ["apart", "uniform", "ties", "two_values"])
+def test_mix_many_long_rows_between_two_short_ones(oracle, kind, k, n, batch):
+    """Sums of operators whose long side has hundreds or thousands of rows between two short anchors, or all of them beyond the last
+    one (apart), or equal to two of them: intervals of up to 3750 tasks; bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(k + 3 * n + batch)
+    r = 2
+    if kind == "apart":
+        ab = [(q.uniform(0, 1, k).astype(np.float32), q.uniform(2, 9, n).astype(np.float32)) for _ in range(r)]
+    elif kind == "two_values":
+        ab = [(q.integers(0, 4, k).astype(np.float32), q.integers(1, 3, n).astype(np.float32)) for _ in range(r)]
+    else:
+        ab = [anchors(kind, q, k, n) for _ in range(r)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, g = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32)
+    out = [torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (r, k), (r, n), (r,))]
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    B.laplex_mix_apply(da, db, dw, dx, out[0], ws, B.LAPLEX_SAVE_SCANS)
+    B.laplex_mix_apply_backward(da, db, dw, dx, dg, *out[1:], ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    torch.cuda.synchronize()
+    ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+    want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
+    for name, got, rv, tv in zip(("y", "gx", "ga", "gb", "gw"), out, (ref,) + tuple(want), (tol,) + tuple(tols)):
+        assert_close(name, got.cpu().numpy(), rv, tv)
