@@ -365,9 +365,15 @@ constexpr int64_t kMixShortMax = int64_t(1) << 15;
 constexpr double kMixCommonWork = 8e9;
 bool mix_common(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
-    const int64_t N = k + n;
-    if (N > kRunSortMax || k < 1 || n < 1 || batch < 1 || (k < n ? k : n) > kMixShortMax) return false;
-    return N > kSmallMax || (double)r * (double)(N * N) * (double)batch >= kMixCommonWork;
+    const int64_t N = k + n, m = k < n ? k : n, l = k < n ? n : k;
+    if (N > kRunSortMax || k < 1 || n < 1 || batch < 1 || m > kMixShortMax) return false;
+    if (N <= kSmallMax) return (double)r * (double)(N * N) * (double)batch >= kMixCommonWork;
+    // From long inputs to short outputs a single operator is as well off with its own launches unless the matrices are large and the
+    // sides not too different (us, a product on a kept plan, own / common: 1 x (32000 x 100000), batch 8: 30 / 37, batch 64: 56 / 45; 1000 x
+    // 500000, batch 256: 120 / 152), and so are two or three that are bound by reading x (2 x (1000 x 500000), batch 256: 238 / 261).
+    if (k <= n && r == 1) return l <= 16 * m && N * batch >= int64_t(1) << 23;
+    if (k <= n && r < 4) return l <= 256 * m || N * batch <= int64_t(1) << 26;
+    return true;
 }
 
 // Counting ranks costs r N^2 comparisons, two launches of the run sort about 23 us whatever the operators: 16 x 3048 positions 33
