@@ -452,6 +452,7 @@ struct MixCommon {
         A.srow = reinterpret_cast<uint32_t*>(base + M.off_srow); A.sp = reinterpret_cast<float*>(base + M.off_sp);
         A.tied = reinterpret_cast<uint32_t*>(base + M.off_tied); A.equals = reinterpret_cast<uint32_t*>(base + M.off_equals); A.bound = reinterpret_cast<uint32_t*>(base + M.off_bound);
         A.recs = reinterpret_cast<uint4*>(base + M.off_recs); A.sorted = reinterpret_cast<uint4*>(base + M.off_sorted);
+        A.counts = reinterpret_cast<uint32_t*>(base + M.off_sorted);      // (the sorted records are written after they are read)
         A.slots = reinterpret_cast<uint2*>(base + M.off_slots); A.tasks = reinterpret_cast<uint2*>(base + M.off_tasks); A.task_count = (int)mix_task_count(A.m, A.l);
         A.folds = reinterpret_cast<float*>(base + M.off_folds); A.equal = reinterpret_cast<float*>(base + M.off_equal);
         A.sums = reinterpret_cast<float*>(base + M.off_sums); A.fr = reinterpret_cast<float*>(base + M.off_fr);

@@ -487,6 +487,7 @@ struct MixPath {
     const uint32_t* ids; const float* pk; const uint32_t* status; int64_t op_ws;      // plan of operator 0 (status: may be null); bytes to the next
     int64_t k; int N, m, l, short_b, operators;
     const float* long_anchor;      // [operators][l], the caller's
+    uint32_t* counts; int counted;      // [operators][tiles] short positions of the plan's tiles, scratch where `sorted` will lie; counted: set by launch_mix_plan
     // part of the plan, per operator:
     uint32_t* srow; float* sp;     // [m]      the short side in sorted order: row, anchor
     uint32_t* tied;                // [m]      0, or 1 + the first of the short rows with this anchor if long rows have it too

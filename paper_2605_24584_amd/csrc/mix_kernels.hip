@@ -72,9 +72,34 @@ __device__ __forceinline__ uint32_t order_of(float f)
 // ---------------------------------------------------------------------------
 // From the merged order of an operator: its short side as a list in sorted order, the intervals' bounds, and for every row of the
 // long side how many short anchors lie strictly below it, how many at or below it, and its place among the long rows.  A
-// workgroup takes 2048 merged positions and counts the short ones before them itself (a few dozen KB of ids from the L2, instead
-// of a launch that would count per tile).
+// workgroup takes 2048 merged positions and has to know the short ones before them: up to kIndexRecount such tiles it counts them
+// itself (a few dozen KB of ids from the L2), beyond that a launch before it leaves every tile's count (the plan after the sort, us,
+// without / with it: 16 x 36096 positions 47 / 52, 2 x 501000 105 / 88).
 // ---------------------------------------------------------------------------
+constexpr int kIndexRecount = 32;
+
+__global__ void __launch_bounds__(kIndexThreads)
+k_mix_count(const MixPath A)
+{
+    __shared__ int total[kIndexThreads / 64];
+    const int64_t op = blockIdx.y;
+    const uint32_t* ids = shift_bytes(A.ids, op * A.op_ws);
+    int count = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int j = blockIdx.x * kIndexTile + i * kIndexThreads + threadIdx.x;
+        if (j < A.N && (ids[j] >= (uint32_t)A.k) == (A.short_b != 0)) ++count;
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) count += __shfl_xor(count, m);
+    if ((threadIdx.x & 63) == 0) total[threadIdx.x >> 6] = count;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kIndexThreads / 64; ++w) count += total[w];
+        A.counts[op * gridDim.x + blockIdx.x] = (uint32_t)count;
+    }
+}
+
 __global__ void __launch_bounds__(kIndexThreads)
 k_mix_index(const MixPath A)
 {
@@ -88,15 +113,19 @@ k_mix_index(const MixPath A)
     auto is_short = [&](uint32_t id) { return (id >= k) == short_b; };
     const int base = blockIdx.x * kIndexTile;
 
-    int count = 0;                                        // (base is a multiple of 2048 and the ids start on 256 bytes)
-    for (int j1 = tid * 4; j1 < base; j1 += 8 * kIndexTile) {
-        uint4 v[8];
+    int count = 0;
+    if (A.counted) {
+        for (int q = tid; q < (int)blockIdx.x; q += kIndexThreads) count += (int)A.counts[op * gridDim.x + q];
+    } else {                                              // (base is a multiple of 2048 and the ids start on 256 bytes)
+        for (int j1 = tid * 4; j1 < base; j1 += 8 * kIndexTile) {
+            uint4 v[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const uint4*>(ids + (j1 + q * kIndexTile < base ? j1 + q * kIndexTile : 0));
+            for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const uint4*>(ids + (j1 + q * kIndexTile < base ? j1 + q * kIndexTile : 0));
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int here = (is_short(v[q].x) ? 1 : 0) + (is_short(v[q].y) ? 1 : 0) + (is_short(v[q].z) ? 1 : 0) + (is_short(v[q].w) ? 1 : 0);
-            count += j1 + q * kIndexTile < base ? here : 0;
+            for (int q = 0; q < 8; ++q) {
+                const int here = (is_short(v[q].x) ? 1 : 0) + (is_short(v[q].y) ? 1 : 0) + (is_short(v[q].z) ? 1 : 0) + (is_short(v[q].w) ? 1 : 0);
+                count += j1 + q * kIndexTile < base ? here : 0;
+            }
         }
     }
 #pragma unroll
@@ -888,10 +917,14 @@ void go_gather(const MixPath& A, const MixGather& S, hipStream_t st)
 
 }  // namespace
 
-hipError_t launch_mix_plan(const MixPath& A, hipStream_t st)
+hipError_t launch_mix_plan(const MixPath& path, hipStream_t st)
 {
-    LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_index, dim3((unsigned)((A.N + kIndexTile - 1) / kIndexTile), (unsigned)A.operators),
-                                                    dim3(kIndexThreads), 0, st, A));
+    MixPath A = path;
+    const int tiles = (A.N + kIndexTile - 1) / kIndexTile;
+    const dim3 grid((unsigned)tiles, (unsigned)A.operators);
+    A.counted = tiles > kIndexRecount;
+    if (A.counted) LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_count, grid, dim3(kIndexThreads), 0, st, A));
+    LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_index, grid, dim3(kIndexThreads), 0, st, A));
     const int64_t items = A.l > A.m + 1 ? A.l : A.m + 1;
     LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_records, dim3((unsigned)((items + kMixThreads - 1) / kMixThreads), (unsigned)A.operators),
                                                     dim3(kMixThreads), 0, st, A));
