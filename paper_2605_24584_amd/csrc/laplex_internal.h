@@ -165,7 +165,7 @@ struct Layout {
     size_t off_red = 0;          // f32[slabs][N]               per-slab partial row reductions
     size_t off_lists = 0;        // u32[tiles] tile list, u32[blocks] block list (sparse problems)
     size_t off_blk_flags = 0;    // u32[blocks]                 what each block holds (injected rows, result rows)
-    size_t off_blk_f = 0;        // f32[2][blocks][bpad]        carry F into a block from the start of its tile (wide geometry)
+    size_t off_blk_f = 0;        // f32[2][blocks][bpad]        carry F into a block from the start of its tile (wide geometry; else, two per 32 blocks: the spine's groups)
     size_t off_blk_e = 0;        // f32[2][blocks][bpad]        the same, strict
     size_t off_stage = 0;        // f32[N][batch], narrow batches only: this problem's injected rows in sorted order
     // second level of the spine: the same five arrays over chunks of tiles
@@ -233,8 +233,6 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     L.off_blk_e = c;     c = align_up(c + per_blk);
     L.off_stage = c; c = align_up(c + stage_bytes);
     L.max_chunks = g1.chunks > g4.chunks ? g1.chunks : g4.chunks;
-    const int64_t supers = (L.max_tiles + kSpineSuperTiles - 1) / kSpineSuperTiles;
-    if (supers > L.max_chunks) L.max_chunks = supers;
     const size_t per2 = sizeof(float) * 2 * (size_t)L.max_chunks * (size_t)L.bpad;
     L.off_agg2_scalar = c; c = align_up(c + sizeof(float) * 4 * 2 * (size_t)L.max_chunks);
     L.off_agg2_s = c;      c = align_up(c + per2);

@@ -2870,8 +2870,12 @@ template <int VEC, bool STRICT>
 void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
 {
     const dim3 block(kScanThreads), cgrid((unsigned)g.chunks, (unsigned)g.slabs, 2);
+    // The sums of groups lie where the chunks' do in the wide geometry (a chunk is a group there), elsewhere in the room of the blocks'
+    // states, which only the wide geometry uses: no workspace of their own.
+    static_assert(kScanWaves * (kSpineItems / 2) == kSuperTiles, "a chunk of the wide geometry is a group");
     Level super = A.l2;
     super.count = (g.tiles + kSuperTiles - 1) / kSuperTiles;
+    if (!g.sub_shift) { super.s = A.blk_f; super.q = A.blk_e; }
     const bool groups_gain = VEC == 4 || g.rv >= 8;
     const double line = g.rv >= 8 ? kSpineWaveWork : VEC == 4 ? kSpineGroupWork : g.rv > 1 ? kSpineColumnsWork : kSpineColumnWork;
     const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= line;

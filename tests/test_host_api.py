@@ -64,6 +64,15 @@ def apply_args(k=8, n=8, batch=4, a=FAKE, b=FAKE, x=FAKE, ldx=None, y=FAKE, ldy=
             ws, wsb, flags, None)
 
 
+@pytest.mark.parametrize("k,n,batch,limit", [
+    (16806, 259330, 100, 33369600), (37411, 154591, 100, 33496320), (2352, 271954, 128, 33496320), (63103, 22593, 100, 33511680),
+    (58418, 46952, 100, 33539072), (41944, 60462, 128, 33539840), (56544, 56500, 100, 33530368), (41198, 64360, 128, 33523456),
+])
+def test_sizes_that_just_fit_the_static_workspace(L, k, n, batch, limit):
+    """Problems within 200 KB of what laplex_apply_static takes: the spine's groups of tiles need no room of their own."""
+    assert B.laplex_workspace_bytes(k, n, batch) <= limit <= B.LAPLEX_STATIC_WORKSPACE_BYTES
+
+
 def test_apply_rejects_bad_arguments_before_touching_the_gpu(L):
     f = L.laplex_apply
     assert f(*apply_args(a=None)) == B.LAPLEX_ERR_NULL
