@@ -511,8 +511,16 @@ struct MixCommon {
     }
 };
 
+// The scanned rows of x, with the inputs as the short side, are what LAPLEX_SAVE_SCANS keeps: a call without it scans on the room of
+// the folds, which are written only afterwards.
+void mix_spare_saved(MixCommon& C, uint32_t flags)
+{
+    if (C.A.short_b && !(flags & LAPLEX_SAVE_SCANS)) C.A.fr = C.A.folds;
+}
+
 int mix_common_forward(MixCommon& C, const float* x, int64_t ldx, float* y, int64_t ldy, uint32_t flags)
 {
+    mix_spare_saved(C, flags);
     LAPLEX_CHECK(C.plan(flags));
     if (C.A.short_b) {
         LAPLEX_CHECK(C.scan_short(x, ldx));
@@ -528,6 +536,7 @@ int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* 
                         float* gx, int64_t ldgx, float* ga, float* gb, float* gw, uint32_t flags)
 {
     const bool saved = (flags & LAPLEX_SAVE_SCANS) != 0;      // the forward left the scanned short side (or p and z) of x
+    mix_spare_saved(C, flags);
     LAPLEX_CHECK(C.plan(flags));
     if (C.A.short_b) {
         if (ga) {

@@ -311,3 +311,27 @@ def test_mix_many_long_rows_between_two_short_ones(oracle, kind, k, n, batch):
     want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
     for name, got, rv, tv in zip(("y", "gx", "ga", "gb", "gw"), out, (ref,) + tuple(want), (tol,) + tuple(tols)):
         assert_close(name, got.cpu().numpy(), rv, tv)
+
+
+@pytest.mark.parametrize("r,k,n,batch", [(2, 9000, 700, 8), (2, 700, 9000, 8), (2, 300, 400, 8), (2, 33000, 33000, 2)])
+def test_mix_saved_scans_survive_a_call_that_does_not_save(oracle, r, k, n, batch):
+    """forward(x, saving), forward(another x, not saving), backward(x, saved): gx, ga and gb are those of x.  (gw is formed from the
+    operators' products, which every forward call writes.)"""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(k + n)
+    ab = [anchors("uniform", q, k, n) for _ in range(r)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, other = (q.normal(size=(n, batch)).astype(np.float32) for _ in range(2))
+    g = q.normal(size=(k, batch)).astype(np.float32)
+    out = [torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (r, k), (r, n))]
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    B.laplex_mix_apply(da, db, dw, dx, out[0], ws, B.LAPLEX_SAVE_SCANS)
+    B.laplex_mix_apply(da, db, dw, dev(other), out[0], ws, B.LAPLEX_REUSE_PLAN)
+    B.laplex_mix_apply_backward(da, db, dw, dx, dg, *out[1:], None, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    torch.cuda.synchronize()
+    ref, tol = oracle.mix_apply(a, b, w, other, brute=False)
+    want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
+    for name, got, rv, tv in zip(("y", "gx", "ga", "gb"), out, (ref,) + tuple(want[:3]), (tol,) + tuple(tols[:3])):
+        assert_close(name, got.cpu().numpy(), rv, tv)
