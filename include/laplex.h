@@ -250,7 +250,10 @@ int laplex_phased_apply_backward(const float* a, const float* phi, int64_t k,
  * summed in a fixed order.  The workspace
  * (laplex_mix_workspace_bytes) holds r plain workspaces back to back (operator q's
  * plan sits at q * (their common size); the flags act on every operator alike),
- * then what the operators share and the scratch of the backward call.
+ * then what the operators share and the scratch of the backward call.  With
+ * LAPLEX_REUSE_PLAN the plans may come from an earlier sum, of as many operators or
+ * more, or from calls on the single operators there (same k, n, batch); what a sum
+ * adds to them is then completed by the call.
  * laplex_mix_apply_backward: gradients of sum(gy * y): gx[n][batch], ga[r][k],
  * gb[r][n] (tie rule as above), gw[r] = <gy, L_q x>; any may be NULL.  With
  * LAPLEX_SAVE_SCANS the forward call (same flag, same workspace) has left what the

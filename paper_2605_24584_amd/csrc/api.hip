@@ -112,7 +112,7 @@ int check_ws(const void* ws, size_t ws_bytes, const Layout& L)
     } while (0)
 
 struct Plan {
-    uint32_t* ids; float* dh; float* pk; float* z;
+    uint32_t* ids; float* dh; float* pk; uint32_t* counters; float* z;
     float2* pk8;    // every eighth sorted anchor with its successor (batch 1 with the sorted-order routes, else null)
     float* xs;      // saved region: the forward's injected rows in sorted order (narrow batches, else null)
     float* stage;   // scratch: the current problem's injected rows in sorted order (narrow batches, else null)
@@ -122,7 +122,7 @@ Plan plan_of(const Layout& L, char* ws)
 {
     const bool narrow = L.batch <= kStageMaxBatch;
     return Plan{reinterpret_cast<uint32_t*>(ws + L.off_ids), reinterpret_cast<float*>(ws + L.off_dh),
-                reinterpret_cast<float*>(ws + L.off_pk), reinterpret_cast<float*>(ws + L.off_z),
+                reinterpret_cast<float*>(ws + L.off_pk), reinterpret_cast<uint32_t*>(ws + L.off_counters), reinterpret_cast<float*>(ws + L.off_z),
                 L.permute ? reinterpret_cast<float2*>(ws + L.off_pk8) : nullptr,
                 narrow ? reinterpret_cast<float*>(ws + L.off_xs) : nullptr,
                 narrow ? reinterpret_cast<float*>(ws + L.off_stage) : nullptr};
@@ -232,7 +232,7 @@ SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float
 {
     SmallArgs S{};
     S.a = a; S.b = b; S.k = k; S.n = n; S.tau = tau;
-    S.ids = P.ids; S.dh = P.dh; S.pk = P.pk;
+    S.ids = P.ids; S.pk = P.pk; S.counters = P.counters;
     S.reuse_plan = (flags & LAPLEX_REUSE_PLAN) ? 1 : 0;
     S.batch = L.batch;
     return S;
@@ -445,7 +445,7 @@ struct MixCommon {
         : A{}, M(M_), base(base_), L(make_layout(k + n_, k, batch)), a(a_), b(b_), n(n_), st(st_), sum{}
     {
         const Plan P = plan_of(L, base);
-        A.ids = P.ids; A.pk = P.pk; A.status = plan_status_word(L, base); A.op_ws = (int64_t)M.inner;
+        A.ids = P.ids; A.pk = P.pk; A.counters = P.counters; A.status = plan_status_word(L, base); A.op_ws = (int64_t)M.inner;
         A.k = k; A.N = (int)(k + n); A.short_b = n <= k; A.operators = (int)r;
         A.m = (int)(A.short_b ? n : k); A.l = (int)(A.short_b ? k : n);
         A.long_anchor = A.short_b ? a : b;
@@ -465,7 +465,10 @@ struct MixCommon {
     // (anchors that arrive sorted are sorted again: two launches for all operators, where the merge would take two for each)
     int plan(uint32_t flags)
     {
-        if (flags & LAPLEX_REUSE_PLAN) return LAPLEX_OK;
+        if (flags & LAPLEX_REUSE_PLAN) {      // (the operators' own plans may have been built by other calls)
+            LAPLEX_HIP(launch_mix_replan(A, st));
+            return LAPLEX_OK;
+        }
         const Plan P = plan_of(L, base);
         if (mix_ranked(A.operators, A.N)) {
             SmallArgs S = small_args(a, A.k, b, n, 1.0f, P, L, flags);      // no scan problem: the sort alone

@@ -38,6 +38,7 @@ constexpr int kSortSmallWords = 1088;
 // In the plan's 64 counter words: the lengths of the scans' two lists and whether a tile's sum of the scan at hand is not finite.
 constexpr int kScanCounters = 3;
 constexpr int kNonFiniteWord = 2;
+constexpr int kPlanIndexWord = 33;                      // nonzero: what the common launches of a sum of operators add to the plan is there (kMixIndexed + operators)
 constexpr int kPlanStatusWord = 32;                     // in the plan's 64 counter words: the sort's error flag, kept with the plan
 constexpr int kMergeThreads = 256;
 constexpr int kMergePerThread = 8;
@@ -145,7 +146,7 @@ struct Layout {
     int64_t N = 0, zrows = 0, batch = 0, bpad = 0;
     // plan
     size_t off_ids = 0;      // u32[N]    sorted ids
-    size_t off_dh = 0;       // f32[N+1]  decay to the previous sorted key, < 0: same key
+    size_t off_dh = 0;       // f32[N+1]  decay to the previous sorted key, < 0: same key (not there for small problems: k_small takes its own)
     size_t off_pk = 0;       // f32[N+2]  sorted anchors, shifted by one, between -inf and +inf sentinels
     size_t off_counters = 0; // u32[64]   the first kScanCounters: of the scans, zero between calls (the plan build clears them,
                              //           every scan clears them again in its last kernel); word kPlanStatusWord: 1 if the sort gave up a wait
@@ -447,7 +448,7 @@ struct SmallProblem {
 };
 struct SmallArgs {
     const float* a; const float* b; int64_t k, n; float tau;
-    uint32_t* ids; float* dh; float* pk;       // the plan in the workspace: written (slab 0), or read if reuse_plan
+    uint32_t* ids; float* pk; uint32_t* counters;      // the plan in the workspace (no decays): written, or read if reuse_plan
     int64_t op_a, op_b, op_ws;
     int reuse_plan;                            // the workspace holds the plan: no sort
     int64_t batch; int cols;                   // cols: set by the launcher, power of two <= 16
@@ -482,7 +483,7 @@ constexpr int kMixWidth = 32;            // columns of a slab, at most
 constexpr int kMixTaskRows = 32;         // long rows that one row-lane folds
 constexpr int kMixSums = 3;              // sums per tile of the short side: forward, backward, forward strictly below the last anchor
 struct MixPath {
-    const uint32_t* ids; const float* pk; const uint32_t* status; int64_t op_ws;      // plan of operator 0 (status: may be null); bytes to the next
+    const uint32_t* ids; const float* pk; uint32_t* counters; const uint32_t* status; int64_t op_ws;      // plan of operator 0 (status: may be null); bytes to the next
     int64_t k; int N, m, l, short_b, operators;
     const float* long_anchor;      // [operators][l], the caller's
     uint32_t* counts; int counted;      // [operators][tiles] short positions of the plan's tiles, scratch where `sorted` will lie; counted: set by launch_mix_plan
@@ -520,7 +521,12 @@ inline int mix_width(int64_t batch) { return batch >= kMixWidth ? kMixWidth : po
 inline int64_t mix_max_tiles(int64_t m, int64_t batch) { const int64_t rows = 32 * (64 / mix_width(batch)); return (m + rows - 1) / rows; }
 // The tasks of interval c start at c + bound[c] / kMixTaskRows: room for ceil(rows / kMixTaskRows) of them without a count.
 inline int64_t mix_task_count(int64_t m, int64_t l) { return m + 2 + l / kMixTaskRows; }
+// launch_mix_plan: the part of the plan above, after the sort.  launch_mix_replan: the same, in a single workgroup per operator, for
+// operators whose plan word does not say that it is there for this number of operators (plans that were built one by one, or as part
+// of another sum); it returns at once for the others.
+constexpr uint32_t kMixIndexed = 0x10000u;
 hipError_t launch_mix_plan(const MixPath& A, hipStream_t st);
+hipError_t launch_mix_replan(const MixPath& A, hipStream_t st);
 hipError_t launch_mix_scan(const MixPath& A, const float* v, int64_t ldv, hipStream_t st);
 hipError_t launch_mix_fold(const MixPath& A, const float* v, int64_t ldv, const MixFolded& S, hipStream_t st);
 hipError_t launch_mix_gather(const MixPath& A, const MixGather& S, bool rows, hipStream_t st);

@@ -100,34 +100,18 @@ k_mix_count(const MixPath A)
     }
 }
 
-__global__ void __launch_bounds__(kIndexThreads)
-k_mix_index(const MixPath A)
+// One tile, by a workgroup of kIndexThreads; `before`: the threads' parts of the number of short positions before it.  Returns those in it.
+__device__ __forceinline__ int index_tile(const MixPath& A, int64_t op, int tile, int before_part)
 {
     __shared__ int before[kIndexThreads / 64], total[kIndexThreads / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t op = blockIdx.y;
     const uint32_t* ids = shift_bytes(A.ids, op * A.op_ws);
     const float* pk = shift_bytes(A.pk, op * A.op_ws);
     const uint32_t k = (uint32_t)A.k;
     const bool short_b = A.short_b != 0;
     auto is_short = [&](uint32_t id) { return (id >= k) == short_b; };
-    const int base = blockIdx.x * kIndexTile;
-
-    int count = 0;
-    if (A.counted) {
-        for (int q = tid; q < (int)blockIdx.x; q += kIndexThreads) count += (int)A.counts[op * gridDim.x + q];
-    } else {                                              // (base is a multiple of 2048 and the ids start on 256 bytes)
-        for (int j1 = tid * 4; j1 < base; j1 += 8 * kIndexTile) {
-            uint4 v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const uint4*>(ids + (j1 + q * kIndexTile < base ? j1 + q * kIndexTile : 0));
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int here = (is_short(v[q].x) ? 1 : 0) + (is_short(v[q].y) ? 1 : 0) + (is_short(v[q].z) ? 1 : 0) + (is_short(v[q].w) ? 1 : 0);
-                count += j1 + q * kIndexTile < base ? here : 0;
-            }
-        }
-    }
+    const int base = tile * kIndexTile;
+    int count = before_part;
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) count += __shfl_xor(count, m);
 
@@ -194,16 +178,45 @@ k_mix_index(const MixPath A)
             recs[short_b ? id[i] : id[i] - k] = make_uint4((uint32_t)lo, (uint32_t)hi, (uint32_t)(j - s), 0u);
         }
     }
-    if (blockIdx.x == 0 && tid == 0) { bound[0] = 0u; bound[A.m + 1] = (uint32_t)A.l; }
+    if (tile == 0 && tid == 0) { bound[0] = 0u; bound[A.m + 1] = (uint32_t)A.l; }
+    int here = 0;
+#pragma unroll
+    for (int w = 0; w < kIndexThreads / 64; ++w) here += total[w];
+    return here;
 }
+
+__global__ void __launch_bounds__(kIndexThreads)
+k_mix_index(const MixPath A)
+{
+    const int tid = threadIdx.x;
+    const int64_t op = blockIdx.y;
+    const uint32_t* ids = shift_bytes(A.ids, op * A.op_ws);
+    auto is_short = [&](uint32_t id) { return (id >= (uint32_t)A.k) == (A.short_b != 0); };
+    const int base = blockIdx.x * kIndexTile;
+    int count = 0;
+    if (A.counted) {
+        for (int q = tid; q < (int)blockIdx.x; q += kIndexThreads) count += (int)A.counts[op * gridDim.x + q];
+    } else {                                              // (base is a multiple of 2048 and the ids start on 256 bytes)
+        for (int j1 = tid * 4; j1 < base; j1 += 8 * kIndexTile) {
+            uint4 v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = *reinterpret_cast<const uint4*>(ids + (j1 + q * kIndexTile < base ? j1 + q * kIndexTile : 0));
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int here = (is_short(v[q].x) ? 1 : 0) + (is_short(v[q].y) ? 1 : 0) + (is_short(v[q].z) ? 1 : 0) + (is_short(v[q].w) ? 1 : 0);
+                count += j1 + q * kIndexTile < base ? here : 0;
+            }
+        }
+    }
+    index_tile(A, op, blockIdx.x, count);
+}
+
 
 // Second launch of the plan: the long rows' decays to their short neighbours (rows in the caller's order for the gather, in sorted
 // order for the fold), and the fold's tasks.
-__global__ void __launch_bounds__(kMixThreads)
-k_mix_records(const MixPath A)
+__device__ __forceinline__ void make_record(const MixPath& A, int64_t op, int i)
 {
-    const int64_t op = blockIdx.y;
-    const int m = A.m, i = blockIdx.x * kMixThreads + threadIdx.x;
+    const int m = A.m;
     const float* sp = A.sp + op * m;
     const uint32_t* bound = A.bound + op * (m + 2);
     uint2* tasks = A.tasks + op * A.task_count;
@@ -229,6 +242,33 @@ k_mix_records(const MixPath A)
         const int t1 = i < m ? first_task(i + 1, end) : A.task_count;
         for (int t = t0 + (end - first + kMixTaskRows - 1) / kMixTaskRows; t < t1; ++t) tasks[t] = make_uint2(0u, 0u);
     }
+}
+
+__device__ __forceinline__ uint32_t* index_word(const MixPath& A, int64_t op) { return shift_bytes(A.counters, op * A.op_ws) + kPlanIndexWord; }
+
+__global__ void __launch_bounds__(kMixThreads)
+k_mix_records(const MixPath A)
+{
+    make_record(A, blockIdx.y, blockIdx.x * kMixThreads + threadIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *index_word(A, blockIdx.y) = kMixIndexed + (uint32_t)A.operators;
+}
+
+// All of it for one operator, by one workgroup, if it is not there: a kept plan of this sum costs the look at the word (16 x (9000 x
+// 1000), batch 8, a product on a kept plan: 21 us without, 22 with), one that was built by other calls a walk over its tiles.
+__global__ void __launch_bounds__(kIndexThreads)
+k_mix_replan(const MixPath A)
+{
+    const int64_t op = blockIdx.x;
+    if (*index_word(A, op) == kMixIndexed + (uint32_t)A.operators) return;      // uniform
+    int before = 0;
+    for (int tile = 0; tile * kIndexTile < A.N; ++tile) {
+        before += index_tile(A, op, tile, threadIdx.x == 0 ? before : 0);
+        __syncthreads();
+    }
+    const int items = A.l > A.m + 1 ? A.l : A.m + 1;
+    for (int i = threadIdx.x; i < items; i += kIndexThreads) make_record(A, op, i);
+    __syncthreads();
+    if (threadIdx.x == 0) *index_word(A, op) = kMixIndexed + (uint32_t)A.operators;
 }
 
 // ---------------------------------------------------------------------------
@@ -928,6 +968,12 @@ hipError_t launch_mix_plan(const MixPath& path, hipStream_t st)
     const int64_t items = A.l > A.m + 1 ? A.l : A.m + 1;
     LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_records, dim3((unsigned)((items + kMixThreads - 1) / kMixThreads), (unsigned)A.operators),
                                                     dim3(kMixThreads), 0, st, A));
+    return hipGetLastError();
+}
+
+hipError_t launch_mix_replan(const MixPath& A, hipStream_t st)
+{
+    LAPLEX_TIMED("mix_plan", st, hipLaunchKernelGGL(k_mix_replan, dim3((unsigned)A.operators), dim3(kIndexThreads), 0, st, A));
     return hipGetLastError();
 }
 

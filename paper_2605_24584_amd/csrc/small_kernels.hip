@@ -87,7 +87,11 @@ k_small_rank(SmallArgs A, int queries)
         g_ids[rank] = (uint32_t)me;
         g_pk[rank + 1] = small_key_to_float((uint32_t)(me >> 32));
     }
-    if (blockIdx.x == 0 && tid == 0) { g_pk[0] = __uint_as_float(0xFF800000u); g_pk[N + 1] = __uint_as_float(0x7F800000u); }
+    if (blockIdx.x == 0 && tid == 0) {
+        g_pk[0] = __uint_as_float(0xFF800000u);
+        g_pk[N + 1] = __uint_as_float(0x7F800000u);
+        reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(A.counters) + op * A.op_ws)[kPlanIndexWord] = 0u;      // a new plan
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -335,3 +335,38 @@ def test_mix_saved_scans_survive_a_call_that_does_not_save(oracle, r, k, n, batc
     want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
     for name, got, rv, tv in zip(("y", "gx", "ga", "gb"), out, (ref,) + tuple(want[:3]), (tol,) + tuple(tols[:3])):
         assert_close(name, got.cpu().numpy(), rv, tv)
+
+
+@pytest.mark.parametrize("r,k,n,batch", [(3, 9000, 700, 8), (3, 700, 9000, 5), (4, 4000, 4000, 64), (3, 60000, 9000, 4), (2, 300, 400, 8)])
+def test_mix_on_plans_that_other_calls_built(oracle, r, k, n, batch):
+    """LAPLEX_REUSE_PLAN for a sum of operators whose plans, at their places in the workspace, come from calls on the single operators;
+    then with one of them built anew on other anchors, and for a sum of fewer operators on the same workspace."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(k + n)
+    ab = [anchors("ties", q, k, n) for _ in range(r + 1)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, g = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32)
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    one = (B.laplex_workspace_bytes(k, n, batch) + 255) // 256 * 256
+    y = torch.empty(k, batch, device="cuda")
+
+    def check(count):
+        out = [torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (count, k), (count, n), (count,))]
+        B.laplex_mix_apply(da[:count], db[:count], dw[:count], dx, out[0], ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        B.laplex_mix_apply_backward(da[:count], db[:count], dw[:count], dx, dg, *out[1:], ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+        ha, hb = da[:count].cpu().numpy(), db[:count].cpu().numpy()
+        ref, tol = oracle.mix_apply(ha, hb, w[:count], x, brute=False)
+        want, tols = oracle.mix_backward(ha, hb, w[:count], x, g, brute=False)
+        for name, got, rv, tv in zip(("y", "gx", "ga", "gb", "gw"), out, (ref,) + tuple(want), (tol,) + tuple(tols)):
+            assert_close(name, got.cpu().numpy(), rv, tv)
+
+    for p in range(r):
+        B.laplex_apply(da[p], db[p], dx, y, ws[p * one:], 0)
+    check(r)
+    da[1].copy_(da[r]); db[1].copy_(db[r])
+    B.laplex_apply(da[1], db[1], dx, y, ws[one:], 0)
+    check(r)
+    check(r - 1)
