@@ -13,12 +13,14 @@
 // are compared as (key, run, position in the run), and runs are stretches of positions in ascending order.
 // A bound is a sample, so a stretch holds the average number of pairs up to what lies between samples: for R runs a
 // boundary scatters by about STEP * sqrt(R / 12) pairs, and the configurations below leave more than three times the scatter of
-// a stretch to the capacity of a workgroup.  In the worst case it holds (samples per stretch + R) * STEP pairs; a stretch
-// beyond the capacity is placed by counting.
+// a stretch to the capacity of a workgroup.  In the worst case it holds (samples per stretch + R) * STEP pairs, 2.7 times the
+// capacity; a stretch beyond the capacity is sorted in parts, whose pairs are then searched in each other.
 //
-// Measured (MI355X, us, this sort / radix sort and decay pass; keys uniform): 9000 positions 22 / 33, 36096: 24 / 40,
-// 2^17: 27 / 47, 2^18: 35 / 55, 2^19: 53 / 65; at 2^20 positions, with 257 runs, 107 / 83: hence kRunSortMax = 2^19.  Of the
-// second kernel's 18 us at 2^17 positions the sort in LDS is 5.6, the selection 5.3, cutting and gathering 4.7.
+// Measured (MI355X, us, this sort / radix sort and decay pass; keys uniform): 9000 positions 22 / 35, 2^15: 23 / 41, 2^17: 28 / 48,
+// 2^18: 36 / 57, 2^19: 57 / 71; at 2^20 positions, with 257 runs, 107 / 83: hence kRunSortMax = 2^19.  Of the second kernel's 18 us at
+// 2^17 positions the sort in LDS is 5.6, the selection 5.3, cutting and gathering 4.7.  Keys that arrive ascending: 39 / 49 at 2^17,
+// 62 / 69 at 2^19; all equal, where the radix sort skips every pass: 31 / 28 and 56 / 40; all stretches' keys between two samples of
+// every run (the most that a stretch can hold): 56 / 49 and 148 / 73.
 #include "laplex_internal.h"
 #include "block_sort.h"
 
@@ -44,10 +46,10 @@ struct RunArgs {
     int64_t op_a, op_b, op_ws;                            // strides from one operator to the next (elements; bytes of workspace)
 };
 
-// Position of a run's first sample; the others follow STEP pairs apart.  Staggered from run to run: with the same place in every
-// run the stretches at the ends of the sequence would hold up to STEP / 4 pairs a run more than the average (12693 instead of
-// 2865 at the most for 320 runs of random keys with an average of 1792), and so would others on inputs that repeat themselves.
-// The samples of a last run that is shorter repeat its largest key.
+// Position of a run's first sample; the others follow STEP pairs apart.  Staggered from run to run: with the same place in every run
+// the stretches at the ends of the sequence, and on inputs that repeat themselves any stretch, would hold what lies between two samples
+// of all runs at once (R * STEP / 2 pairs more or less than the average).  The samples of a last run that is shorter repeat its largest
+// key.
 __device__ __forceinline__ int first_sample(int run, int step) { return (run * 11) & (step - 1); }
 
 template <typename T>
@@ -409,23 +411,56 @@ k_bucket_sort(const RunArgs A)
             if (e0 + i < cnt) write(base + e0 + i, key[i], before, id[i]);
             before = key[i];
         }
-    } else {                                        // by counting: CAP keys at a time beside every pair of the stretch
-        for (int e0 = 0; e0 < cnt; e0 += THREADS) {
-            const int e = e0 + tid;
-            const int at = place(e < cnt ? e : 0);
-            const uint32_t me = run_keys[at];
-            int rank = 0;
+    } else {
+        // Beyond the capacity: CAP pairs at a time are sorted in LDS, and every pair of the stretch is searched in each such part (in its
+        // own with its place in the stretch as the second key; equal keys of earlier parts come before it).  At most three parts.
+        constexpr int MINE = 3 * ITEMS;
+        uint32_t* const sk = buf;
+        uint32_t* const sv = buf + CAP + 2;
+        for (int e0 = 0; e0 < cnt; e0 += MINE * THREADS) {
+            uint32_t me[MINE];
+            int rank[MINE];
+#pragma unroll
+            for (int i = 0; i < MINE; ++i) {
+                const int e = e0 + i * THREADS + tid;
+                me[i] = e < cnt ? run_keys[place(e)] : 0u;
+                rank[i] = 0;
+            }
             for (int c0 = 0; c0 < cnt; c0 += CAP) {
+                const int len = cnt - c0 < CAP ? cnt - c0 : CAP;
+                uint32_t key[ITEMS], val[ITEMS];
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) {
+                    const int q = tid * ITEMS + i;
+                    key[i] = q < len ? run_keys[place(c0 + q)] : 0xFFFFFFFFu;
+                    val[i] = (uint32_t)q;
+                }
                 __syncthreads();
-                for (int q = tid; q < CAP && c0 + q < cnt; q += THREADS) buf[q] = run_keys[place(c0 + q)];
+                block_sort<THREADS, ITEMS>(key, val, sk, sv);
                 __syncthreads();
-                const int stop = cnt - c0 < CAP ? cnt - c0 : CAP;
-                for (int q = 0; q < stop; ++q) {
-                    const uint32_t v = buf[q];
-                    rank += (v < me || (v == me && c0 + q < e)) ? 1 : 0;
+#pragma unroll
+                for (int i = 0; i < ITEMS; ++i) { sk[tid * ITEMS + i] = key[i]; sv[tid * ITEMS + i] = val[i]; }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < MINE; ++i) {
+                    const int e = e0 + i * THREADS + tid;
+                    if (e >= cnt) continue;
+                    const uint32_t own = e < c0 ? 0u : e - c0 < CAP ? (uint32_t)(e - c0) : 0xFFFFFFFFu;      // equal keys below this place count
+                    int lo = 0, hi = len;
+                    while (lo < hi) {
+                        const int mid = (lo + hi) >> 1;
+                        const uint32_t v = sk[mid];
+                        if (v < me[i] || (v == me[i] && sv[mid] < own)) lo = mid + 1; else hi = mid;
+                    }
+                    rank[i] += lo;
                 }
             }
-            if (e < cnt) { ids[base + rank] = run_ids[at]; pk[base + rank + 1] = run_key_to_float(me); }
+#pragma unroll
+            for (int i = 0; i < MINE; ++i) {
+                const int e = e0 + i * THREADS + tid;
+                if (e < cnt) { ids[base + rank[i]] = run_ids[place(e)]; pk[base + rank[i] + 1] = run_key_to_float(me[i]); }
+            }
+            __syncthreads();
         }
         __threadfence_block();
         __syncthreads();
