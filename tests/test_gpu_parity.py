@@ -127,10 +127,11 @@ SHAPES = [(1, 1, 1), (5, 1, 2), (1, 6, 1), (37, 53, 3), (100, 9000, 1), (9000, 1
 # ------------------------------------------------------------------ the sort
 
 @pytest.mark.parametrize("kind", KINDS)
-# the last four: one size for each tile size of the sort passes (2048, 4096 and 8192 pairs), with ragged last tiles, and one
-# beyond 2^22 merged positions, where the histogram keeps its counters once per LDS bank
+# up to 8192 merged positions ranks by counting, up to 2^19 runs and buckets (their edges: test_gpu_dispatch_edges), then radix passes:
+# tiles of 4096 pairs up to 5 * 2^18 positions, of 8192 beyond, and beyond 2^22 - 1 a histogram that keeps its counters once per LDS bank
 @pytest.mark.parametrize("k,n", [(1, 1), (3, 0), (0, 5), (100, 157), (9000, 8000), (20000, 70001),
-                                 (130000, 132001), (300001, 400122), (1500000, 1000003), (2300001, 2100003)])
+                                 (130000, 132001), (300001, 400122), (1500000, 1000003), (2300001, 2100003),
+                                 (655360, 655360), (655361, 655360), (2097152, 2097151), (2097152, 2097152)])
 def test_permutation_bit_exact(oracle, kind, k, n):
     if k == 0 or n == 0:
         pytest.skip("apply with an empty side builds no plan")
@@ -143,9 +144,10 @@ def test_permutation_bit_exact(oracle, kind, k, n):
 
 
 @pytest.mark.parametrize("off_a,off_b", [(1, 0), (2, 3), (3, 1), (0, 2)])
-@pytest.mark.parametrize("k,n", [(1, 2), (2, 1), (3, 7), (4100, 4100), (9001, 20003), (2100001, 2100002)])
+@pytest.mark.parametrize("k,n", [(1, 2), (2, 1), (3, 7), (4100, 4100), (9001, 20003), (2100001, 2100002), (300001, 400122), (700003, 900002)])
 def test_anchor_arrays_off_a_16_byte_boundary(oracle, off_a, off_b, k, n):
-    """The histogram reads the anchors 16 bytes at a time between a scalar head and a scalar tail."""
+    """The radix sort's two histograms (the last two sizes, and the one before them) read the anchors 16 bytes at a time between a
+    scalar head and a scalar tail; the other sorts read them one by one."""
     r = np.random.default_rng(k * 5 + n + off_a * 16 + off_b)
     a, b = anchors("ties", r, k, n)
     x = r.normal(size=(n, 1)).astype(np.float32)
@@ -560,21 +562,23 @@ def test_hip_graph_replays_mix_on_the_large_path():
 
 # ------------------------------------------------------------------ non-finite anchors
 
+# the run sort, and the radix sort with each of its tiles and histograms
+@pytest.mark.parametrize("k,n", [(700, 9000), (300000, 400000), (700000, 900000), (2200000, 2100000)])
 @pytest.mark.parametrize("sorted_flags", [0, B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED])
-def test_non_finite_anchors_do_not_fault(oracle, sorted_flags):
+def test_non_finite_anchors_do_not_fault(oracle, sorted_flags, k, n):
     """NaN and infinite anchors are unsupported: values are unspecified, but the calls must run
     to completion without touching memory out of bounds, and the library must work afterwards."""
     r = np.random.default_rng(31)
-    k, n, batch = 700, 9000, 4
+    batch = 4
     a, b = anchors("uniform", r, k, n)
     a[::50] = np.nan; a[7] = np.inf; a[9] = -np.inf
     b[::333] = np.nan; b[5] = np.inf; b[11] = -np.inf
     x = r.normal(size=(n, batch)).astype(np.float32); g = r.normal(size=(k, batch)).astype(np.float32)
     y, ws = gpu_apply(a, b, x, flags=sorted_flags | B.LAPLEX_SAVE_SCANS)
     gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws)
-    gpu_gram(a, np.ascontiguousarray(x[:k]))
+    gpu_gram(a, np.ascontiguousarray(np.resize(x, (k, batch))))
     perm = gpu_perm(ws, k + n)
-    if sorted_flags == 0:                      # the radix sort still yields a permutation of all ids
+    if sorted_flags == 0:                      # the sort still yields a permutation of all ids
         assert np.array_equal(np.sort(perm), np.arange(k + n, dtype=np.uint32))
     # and a clean problem right after is still exact
     a2, b2 = anchors("uniform", r, k, n)
