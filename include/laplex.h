@@ -35,20 +35,25 @@
  *
  * Workspace.  laplex_workspace_bytes(k, n, batch, ...) gives the size for the
  * apply form; the Gram form of n anchors uses (k = 0, n, batch).  Its front
- * holds the PLAN of the anchors: the sorted order (ids) and the decay between
- * sorted neighbours.  The plan depends on the anchors only, so it stays valid
- * across batches and across the forward / backward pair until the anchors
- * change or the caller overwrites it (Sec. 3 "Complexity": the sorted order is
+ * holds the PLAN of the anchors: the sorted order (ids), the sorted anchors and,
+ * but for small problems, the decay between sorted neighbours.  The plan depends
+ * on the anchors only, so it stays valid across batches and across the forward /
+ * backward pair until the anchors change or the caller overwrites it (Sec. 3 "Complexity": the sorted order is
  * reused across batches).  After the plan comes the saved-scan region written
  * under LAPLEX_SAVE_SCANS, then scratch whose contents are undefined between
  * calls.
  *
  * Small problems.  With k + n <= 8192 the apply and Gram calls (and the calls
- * built on them) run in two launches: a sort by counting ranks over the whole
- * device and one kernel that holds the plan in LDS for the scans.  Arguments,
- * flags, workspace and results are the same (the sorted-input promises are then
- * not needed and not used); values differ from the large path's in rounding
- * only.
+ * built on them) sort by counting ranks over the whole device, and, unless the
+ * batch is so wide that the large path's scans are faster, run both scans in one
+ * launch whose workgroups take chunks of the merged sequence and form the state
+ * at a chunk's edges themselves.  Arguments, flags, workspace and results are the
+ * same (the sorted-input promises are then not needed and not used); values differ
+ * from the large path's in rounding only.
+ *
+ * Non-finite values of x or gy are carried as in the dense product: 0 * NaN and
+ * 0 * inf are NaN, so a NaN shows in every row of its column, however far away, and
+ * in the gradient of every anchor that is not tied with its own.
  */
 #ifndef LAPLEX_H
 #define LAPLEX_H
@@ -334,7 +339,7 @@ int laplex_get_perm(const void* ws, size_t ws_bytes, int64_t count, uint32_t* pe
  * gradients of the phased and mixed calls): the kernels that store results read
  * the plan's status word and set every exponent and a mantissa bit of what they
  * store.  Repeating the call without LAPLEX_REUSE_PLAN rebuilds the plan.
- * Plans of at most 8192 positions and merged plans (both inputs promised
+ * Plans of at most 2^19 positions and merged plans (both inputs promised
  * sorted) never wait and are always valid.
  *
  * laplex_get_plan_status writes the status word of the plan in `ws` (count =

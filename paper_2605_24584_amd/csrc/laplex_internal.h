@@ -43,7 +43,7 @@ constexpr int kPlanStatusWord = 32;                     // in the plan's 64 coun
 constexpr int kMergeThreads = 256;
 constexpr int kMergePerThread = 8;
 constexpr int kMergeTile = kMergeThreads * kMergePerThread;
-// Problems with at most this many merged positions run in one launch, sorted and scanned inside one workgroup.
+// Problems with at most this many merged positions are ranked by counting and, unless their batch is very wide, scanned in one launch.
 constexpr int kSmallMax = 8192;
 
 // ----------------------------------------------------------------------------
@@ -436,8 +436,8 @@ hipError_t launch_tau_grad(const float* a, const float* ga, int64_t k, const flo
                            float* partial, float* gtau, hipStream_t st);
 hipError_t launch_scale(float* p, int64_t count, float f, hipStream_t st);
 
-// Small problems (small_kernels.hip): at most kSmallMax merged positions are sorted by one launch (ranks by counting)
-// and scanned by one workgroup per (slab of `cols` batch columns, operator) in a second.  A SmallProblem is a ScanProblem restricted to
+// Small problems (small_kernels.hip): at most kSmallMax merged positions are sorted by one launch (ranks by counting) and scanned by a
+// second, in which a workgroup takes a chunk of the rows and `cols` batch columns of an operator.  A SmallProblem is a ScanProblem restricted to
 // out_p / out_z; pointers move by the op_* strides (in elements; op_ws in bytes) from one operator to the next.
 struct SmallProblem {
     const float* inj; int64_t ld_inj; uint32_t inj_lo, inj_hi;

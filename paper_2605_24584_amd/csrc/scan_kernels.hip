@@ -2616,7 +2616,6 @@ k_seq_down(const ScanArgs A)
     float* const ef = reinterpret_cast<float*>(smem) + threadIdx.x;        // row i at ef[i * THREADS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t tile = blockIdx.x;
-    if (tile == 0 && tid == 0) A.counters[kNonFiniteWord] = 0u;      // the last kernel of the scan
     const uint32_t poison = plan_poison(A.counters);
     const int64_t tile_base = tile * (int64_t)(THREADS * ITEMS);
     const int64_t wave_row0 = tile_base + (int64_t)wave * 64 * ITEMS;
@@ -2743,6 +2742,8 @@ k_seq_down(const ScanArgs A)
         for (int i = 0; i < ITEMS; ++i) Ff[i] = second[i];
     }
     partition_place_split<THREADS, ITEMS, NV>(A.emit, 0, ok, Ff, STRICT ? second : Ff, S, sd, reinterpret_cast<float*>(smem), K);
+    // the scan's last kernel (at its end: the registers are full before)
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;
 }
 
 __global__ void __launch_bounds__(256)

@@ -2,8 +2,9 @@
 // whole path of one call (Sec. 3: sort, then the prefix recurrence and its mirror image) is one launch
 // that sorts (k_small_rank: ranks by counting, over the whole device) and one that runs the decayed scans in both directions
 // and scatters the results (k_small),
-// where the large path needs some thirty launches of a few microseconds each.  (App. "GPU runtime": below
-// n = 2^17 the paper's curves are flat at the cost of the launches.)  Several operators (the r anchor
+// where the large path needs about ten launches of a few microseconds each.  (App. "GPU runtime": below
+// n = 2^17 the paper's curves are flat at the cost of the launches.)  Where a wide batch makes the second launch read too much the scans
+// are the large path's (small_reads_too_much).  Several operators (the r anchor
 // pairs of a sum of operators) and several slabs of batch columns are separate workgroups of a launch.
 //
 // The numbers carried are those of the large path: F (inclusive decayed sum) and E (the sum over

@@ -112,7 +112,7 @@ def assert_all_non_finite(name, v, cols=slice(None)):
     (700, 300, 1), (4000, 4100, 2), (513, 1024, 64), (4000, 4000, 100), (300, 212, 1000),        # small problems, each form
     (30, 8000, 1100), (2000, 2000, 2100),
     (10000, 9000, 1), (9000, 8000, 8), (65000, 66072, 8), (1000, 40000, 33), (700, 30000, 256),  # larger ones, each form of the spine
-    (900000, 600000, 8), (30, 140000, 256),
+    (900000, 600000, 8), (30, 140000, 256), (2500000, 2200000, 1),
 ])
 def test_non_finite_rows_reach_every_row(k, n, batch, bad):
     """As in the dense product (0 * NaN and 0 * inf are NaN), one non-finite value of x or gy shows in every row of its column and in
