@@ -266,7 +266,7 @@ int laplex_phased_apply_backward(const float* a, const float* phi, int64_t k,
  * NULL if only gx is wanted.  r == 0 gives y = 0.
  * Streams: everything is ordered after the work already in `stream`, and work put
  * into `stream` afterwards is ordered after everything these calls do.  In between,
- * operators with more than 2^19 merged positions or 2^15 of either kind, and small
+ * operators with more than 2^19 merged positions or 2^15 of both kinds, and small
  * matrices, may run on up to four streams that the library creates once per device (default priority) and keeps;
  * while `stream` is being captured into a graph they stay on it.  The results do not
  * depend on which of the two happens.  Calls on different host threads take turns
