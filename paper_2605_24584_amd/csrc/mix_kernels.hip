@@ -1001,15 +1001,16 @@ void go_fold(const MixPath& A, const float* v, int64_t ldv, hipStream_t st)
     else LAPLEX_TIMED("mix_fold", st, hipLaunchKernelGGL((k_mix_fold<VEC, false>), grid, block, 0, st, A, v, ldv, lanes, spans));
 }
 
-// A few intervals and many threads for a workgroup where most intervals have several tasks, many and few where most have one.
+// Many threads for a few intervals where they have several tasks each (row-lanes to share a long sum among); else few threads, and as
+// many intervals as leave enough workgroups (11 x (422 x 7059), batch 256, half a task an interval: many threads 31 us, few 11).
 template <int VEC>
 void go_join(const MixPath& A, hipStream_t st)
 {
-    const bool several = A.l / kMixTaskRows * 2 > A.m;
-    const int per = several ? 16 : kJoinIntervals;
-    const dim3 grid((unsigned)((A.m + 1 + per - 1) / per * A.slabs), (unsigned)A.operators);
-    if (several) LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, 1024>), grid, dim3(1024), 0, st, A, per));
-    else LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, kJoinIntervals>), grid, dim3(kJoinIntervals), 0, st, A, per));
+    auto groups = [&](int per) { return (unsigned)((A.m + 1 + per - 1) / per * A.slabs); };
+    int per = kJoinIntervals;
+    while (per > 16 && (int64_t)groups(per) * A.operators < 1024) per /= 4;
+    if (A.l / 128 >= A.m) LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, 1024>), dim3(groups(16), (unsigned)A.operators), dim3(1024), 0, st, A, 16));
+    else LAPLEX_TIMED("mix_join", st, hipLaunchKernelGGL((k_mix_join<VEC, kJoinIntervals>), dim3(groups(per), (unsigned)A.operators), dim3(kJoinIntervals), 0, st, A, per));
 }
 
 }  // namespace
