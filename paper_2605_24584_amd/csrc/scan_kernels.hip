@@ -2864,9 +2864,10 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 //   single columns, one row-lane                    20000, batch 33 (3.5e6): 44 / 43; 12000, batch 130 (4.6e6): 51 / 51; 20000, batch 65
 //     (6.6e6): 50 / 60; 30000, batch 33 (7.9e6): 45 / 51
 // Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
-// 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243.
+// 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243; with two or four row-lanes up to 7e6 (a product: 90000 x 90000, batch
+// 64 (6.6e6): 52 / 50; 100000 x 100000, batch 64 (8.1e6): 53 / 54; 200000 x 3, batch 64 (8.1e6): 49 / 52).
 constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnsWork = 12e6, kSpineColumnWork = 5e6;
-constexpr double kSpineSuperWork = double(1 << 23);
+constexpr double kSpineSuperWork = double(1 << 23), kSpineSuperFewWork = 7e6;
 template <int VEC, bool STRICT>
 void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
 {
@@ -2880,7 +2881,8 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
     const bool groups_gain = VEC == 4 || g.rv >= 8;
     const double line = g.rv >= 8 ? kSpineWaveWork : VEC == 4 ? kSpineGroupWork : g.rv > 1 ? kSpineColumnsWork : kSpineColumnWork;
     const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= line;
-    const bool two = !one && groups_gain && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= kSpineSuperWork;
+    const double super_line = g.rv > 1 && g.rv < 8 ? kSpineSuperFewWork : kSpineSuperWork;
+    const bool two = !one && groups_gain && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= super_line;
     if (one || two) {
         const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
         auto groups = [&](int64_t n) { return (unsigned)(g.rv >= 8 ? (n + kScanWaves - 1) / kScanWaves : n); };
