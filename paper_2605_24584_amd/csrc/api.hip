@@ -470,7 +470,8 @@ struct MixCommon {
             return LAPLEX_OK;
         }
         const Plan P = plan_of(L, base);
-        if (mix_ranked(A.operators, A.N)) {
+        // (ranks alone make a plan that a plain call on one of the operators can take only if it is a small one for that, too)
+        if (mix_ranked(A.operators, A.N) && use_small(L)) {
             SmallArgs S = small_args(a, A.k, b, n, 1.0f, P, L, flags);      // no scan problem: the sort alone
             S.op_a = A.k; S.op_b = n; S.op_ws = (int64_t)M.inner;
             LAPLEX_HIP(launch_small(S, A.operators, st));

@@ -17,9 +17,9 @@
 // the operators together.
 //
 // Measured (MI355X, forward + backward): 16 operators of 32000 x 4096, batch 256: 2.97 ms one operator after the other on four
-// streams (320 launches, 4 GB of per-operator products and strict sums of the long side written and read) -> 0.55 ms in 15
-// launches; 16 of 1000 x 2048: 0.31 ms (k_small) -> 0.145.  Of the former 0.18 ms are k_mix_gather, which reads 2 x 16 rows per
-// output at 10 to 13 TB/s, most of it from the L2, 0.09 k_mix_fold (5.6 TB/s of the long rows), 0.11 the scans of what it
+// streams (320 launches, 4 GB of per-operator products and strict sums of the long side written and read) -> 0.55 ms in 17
+// launches; 16 of 1000 x 2048: 0.31 ms (k_small) -> 0.149.  Of the former 0.18 ms are k_mix_gather, which reads 2 x 16 rows per
+// output at 10 to 13 TB/s, most of it from the L2, 0.09 k_mix_fold (5.6 TB/s of the long rows), 0.12 the scans of what it
 // leaves, 0.09 the sort and the plan.
 #include "laplex_internal.h"
 

@@ -370,3 +370,32 @@ def test_mix_on_plans_that_other_calls_built(oracle, r, k, n, batch):
     B.laplex_apply(da[1], db[1], dx, y, ws[one:], 0)
     check(r)
     check(r - 1)
+
+
+@pytest.mark.parametrize("r,k,n,batch", [(2, 4000, 4000, 300), (2, 4000, 4000, 64), (2, 9000, 700, 8), (3, 700, 9000, 64), (2, 300, 400, 8), (1, 2000, 1500, 900)])
+def test_plain_calls_on_the_plans_of_a_sum(oracle, r, k, n, batch):
+    """The plans of a sum of operators, at their places in its workspace, serve calls on the single operators (whatever route those take), and
+    the sum afterwards."""
+    from test_gpu_parity import anchors, assert_close
+    q = np.random.default_rng(k + n + batch)
+    ab = [anchors("uniform", q, k, n) for _ in range(r)]
+    a, b = np.stack([u for u, _ in ab]), np.stack([v for _, v in ab])
+    w = q.normal(size=r).astype(np.float32)
+    x, g = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32)
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    ws = torch.zeros(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    one = (B.laplex_workspace_bytes(k, n, batch) + 255) // 256 * 256
+    y, y1, gx = torch.empty(k, batch, device="cuda"), torch.empty(k, batch, device="cuda"), torch.empty(n, batch, device="cuda")
+    B.laplex_mix_apply(da, db, dw, dx, y, ws, 0)
+    for p in range(r):
+        B.laplex_apply(da[p], db[p], dx, y1, ws[p * one:], B.LAPLEX_REUSE_PLAN)
+        B.laplex_apply_backward(da[p], db[p], dx, dg, gx, None, None, ws[p * one:], B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+        ref, tol = oracle.apply_scan(a[p], b[p], x)
+        (rgx, _, _), (tgx, _, _) = oracle.apply_backward_scan(a[p], b[p], x, g)
+        assert_close("y", y1.cpu().numpy(), ref, tol)
+        assert_close("gx", gx.cpu().numpy(), rgx, tgx)
+    B.laplex_mix_apply(da, db, dw, dx, y, ws, B.LAPLEX_REUSE_PLAN)
+    torch.cuda.synchronize()
+    ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+    assert_close("y", y.cpu().numpy(), ref, tol)
