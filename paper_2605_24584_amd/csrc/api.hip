@@ -207,9 +207,9 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
     } else if (both_sorted) {
         LAPLEX_HIP(launch_merge(a, k, b, n, tau, keys0, P.ids, st));
         LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
-    } else if (L.N <= kRunSortMax) {
-        LAPLEX_HIP(launch_run_sort(a, k, b, n, tau, reinterpret_cast<uint32_t*>(pair0), reinterpret_cast<uint32_t*>(pair1), P.ids, P.dh, P.pk, P.pk8, counters,
-                                   1, 0, 0, 0, st));
+    } else if (L.N <= kSplitSortMax) {
+        LAPLEX_HIP(launch_split_sort(a, k, b, n, tau, pair0, pair1, reinterpret_cast<uint32_t*>(ws + L.off_status),
+                                     P.ids, P.dh, P.pk, P.pk8, counters, 1, 0, 0, 0, st));
     } else {
         LAPLEX_HIP(launch_onesweep_sort(a, k, b, n, tau, pair0, pair1, P.ids, P.pk, small,
                                         reinterpret_cast<unsigned long long*>(ws + L.off_status), st));
@@ -355,18 +355,19 @@ struct MixLayout {
 constexpr int kMixLanes = 4;
 constexpr int64_t kMixLanesMaxElements = int64_t(1) << 24;      // (k + n) * batch up to which that pays
 
-// Common launches: what the two-launch sort takes (beyond it one operator fills the device), and a short side whose tiles (64 to
+// Common launches: up to 2^19 merged positions (beyond that one operator fills the device), and a short side whose tiles (64 to
 // 2048 rows) are few enough that each adds up the others itself: at 2^15 rows that is at most three times the tile's own bytes.
 // Small operators stay with k_small, two to four launches fewer, until the rows that its chunks read again, about r N^2 batch / 512,
 // are what a call waits for (us, k_small / common, forward; forward + backward): 2 x (2048 x 1000), batch 64 (1.2e9): 24 / 34; 58 / 72;
 // 16 x (1000 x 2048), batch 64 (9.5e9): 58 / 69; 149 / 128; 2 x (4000 x 4000), batch 64 (8.2e9): 61 / 49; 134 / 91; 16 x (4000 x 4000),
 // batch 64 (6.6e10): 198 / 77; 477 / 150.
+constexpr int64_t kMixMergedMax = int64_t(1) << 19;
 constexpr int64_t kMixShortMax = int64_t(1) << 15;
 constexpr double kMixCommonWork = 8e9;
 bool mix_common(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
     const int64_t N = k + n, m = k < n ? k : n, l = k < n ? n : k;
-    if (N > kRunSortMax || k < 1 || n < 1 || batch < 1 || m > kMixShortMax) return false;
+    if (N > kMixMergedMax || k < 1 || n < 1 || batch < 1 || m > kMixShortMax) return false;
     if (N <= kSmallMax) return (double)r * (double)(N * N) * (double)batch >= kMixCommonWork;
     // From long inputs to short outputs a single operator is as well off with its own launches unless the matrices are large and the
     // sides not too different (us, a product on a kept plan, own / common: 1 x (32000 x 100000), batch 8: 30 / 37, batch 64: 56 / 45; 1000 x
@@ -376,9 +377,10 @@ bool mix_common(int64_t r, int64_t k, int64_t n, int64_t batch)
     return true;
 }
 
-// Counting ranks costs r N^2 comparisons, two launches of the run sort about 23 us whatever the operators: 16 x 3048 positions 33
-// us / 23 us, 16 x 8000 100 / 25, 2 x 8000 18 / 24, one operator of 8192 12 / 22.
-bool mix_ranked(int64_t r, int64_t N) { return N <= kSmallMax && r * N * N <= 140000000; }
+// Counting ranks takes N / 32 workgroups per operator, sorting each operator in a workgroup of its own 12 to 19 us whatever their number
+// (us, ranks / sort, events around the launch: 16 x 1000 positions 13 / 14, 16 x 2000 21 / 15, 40 x 1000 26 / 14, 400 x 300 60 / 14,
+// 4 x 4000 15 / 17, 2 x 8000 19 / 22, 3 x 6000 22 / 20).
+bool mix_ranked(int64_t r, int64_t N) { return N <= kSmallMax && r * N <= 17000; }
 
 int mix_lanes(int64_t r, int64_t k, int64_t n, int64_t batch)
 {
@@ -475,9 +477,9 @@ struct MixCommon {
             SmallArgs S = small_args(a, A.k, b, n, 1.0f, P, L, flags);      // no scan problem: the sort alone
             S.op_a = A.k; S.op_b = n; S.op_ws = (int64_t)M.inner;
             LAPLEX_HIP(launch_small(S, A.operators, st));
-        } else LAPLEX_HIP(launch_run_sort(a, A.k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
-                                   P.ids, P.dh, P.pk, P.pk8, reinterpret_cast<uint32_t*>(base + L.off_counters),
-                                   A.operators, A.k, n, (int64_t)M.inner, st));
+        } else LAPLEX_HIP(launch_split_sort(a, A.k, b, n, 1.0f, reinterpret_cast<uint2*>(base + L.off_pair0), reinterpret_cast<uint2*>(base + L.off_pair1),
+                                     reinterpret_cast<uint32_t*>(base + L.off_status), P.ids, P.dh, P.pk, P.pk8,
+                                     reinterpret_cast<uint32_t*>(base + L.off_counters), A.operators, A.k, n, (int64_t)M.inner, st));
         LAPLEX_HIP(launch_mix_plan(A, st));
         return LAPLEX_OK;
     }
@@ -577,8 +579,9 @@ int mix_small_sorted(const MixLayout& M, const Layout& L, const Plan& P, char* b
                      uint32_t& flags, hipStream_t st)
 {
     if ((flags & LAPLEX_REUSE_PLAN) || mix_ranked(r, k + n)) return LAPLEX_OK;
-    LAPLEX_HIP(launch_run_sort(a, k, b, n, 1.0f, reinterpret_cast<uint32_t*>(base + L.off_pair0), reinterpret_cast<uint32_t*>(base + L.off_pair1),
-                               P.ids, P.dh, P.pk, P.pk8, reinterpret_cast<uint32_t*>(base + L.off_counters), r, k, n, (int64_t)M.inner, st));
+    LAPLEX_HIP(launch_split_sort(a, k, b, n, 1.0f, reinterpret_cast<uint2*>(base + L.off_pair0), reinterpret_cast<uint2*>(base + L.off_pair1),
+                                 reinterpret_cast<uint32_t*>(base + L.off_status), P.ids, P.dh, P.pk, P.pk8,
+                                 reinterpret_cast<uint32_t*>(base + L.off_counters), r, k, n, (int64_t)M.inner, st));
     flags |= LAPLEX_REUSE_PLAN;
     return LAPLEX_OK;
 }

@@ -24,10 +24,9 @@ inline int64_t sort_tiles_of(int64_t N)
     return (N + tile - 1) / tile;
 }
 constexpr int64_t kSortHistTile = 8192;                 // keys per workgroup of the histogram kernel, up to its grid limit
-// Up to this many merged positions the anchors are sorted in two launches by runs and buckets (run_sort_kernels.hip).
-constexpr int64_t kRunSortMax = int64_t(1) << 19;
-constexpr int kRunSampleBits = 6;                       // samples per run: 2^6
-constexpr int kRunSortMaxRuns = 128;                    // tiles of 1024, 2048 and 4096 positions
+// Up to this many merged positions the anchors are sorted by samples, tiles and stretches (split_sort_kernels.hip).
+constexpr int64_t kSplitSortMax = int64_t(1) << 22;
+size_t split_sort_words(int64_t N);                     // scratch words that takes besides the pair buffers
 // Small state of one sort, u32 words: [0, 1024) histogram of the four digits; then the per-pass tile
 // tickets, the error flag and the histogram's done counter in one cache line, and the mask of the passes that run in a line of its own.
 constexpr int kSortTicketWord = 1024;
@@ -211,6 +210,7 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     L.off_pair0 = s;  s = align_up(s + 2 * sizeof(uint32_t) * (size_t)N);
     L.off_pair1 = s;  s = align_up(s + 2 * sizeof(uint32_t) * (size_t)N);
     L.off_status = s;     s = align_up(s + sizeof(uint64_t) * 2 * (size_t)L.status_words);   // look-back words, two passes' worth
+    if (N <= kSplitSortMax && s < L.off_status + sizeof(uint32_t) * split_sort_words(N)) s = align_up(L.off_status + sizeof(uint32_t) * split_sort_words(N));
     L.off_sort_small = s; s = align_up(s + sizeof(uint32_t) * kSortSmallWords);            // global histogram, tickets, error, pass mask
 
     // scan view
@@ -290,12 +290,12 @@ hipError_t launch_onesweep_sort(const float* a, int64_t k, const float* b, int64
                                 uint2* pair0, uint2* pair1, uint32_t* ids, float* pk,
                                 uint32_t* small, unsigned long long* status, hipStream_t st);
 
-// Stable sort of up to kRunSortMax anchors (run_sort_kernels.hip): writes the whole plan, decays and cleared list counters
-// included.  runs: 2 N words and 64 beyond them that may be read, samples: 2^kRunSampleBits words per run, 16-byte aligned, scratch.  For
-// `operators` problems of the same sizes at once, their anchors op_a / op_b elements and everything else op_ws bytes apart.
-hipError_t launch_run_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, uint32_t* runs, uint32_t* samples,
-                           uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters,
-                           int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st);
+// Stable sort of up to kSplitSortMax anchors (split_sort_kernels.hip): writes the whole plan, decays and cleared list counters
+// included.  pair0, pair1: N pairs each, scratch: split_sort_words(N), 8-byte aligned.  For `operators` problems of the same sizes at
+// once, their anchors op_a / op_b elements and everything else op_ws bytes apart.
+hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, uint2* pair0, uint2* pair1, uint32_t* scratch,
+                             uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters,
+                             int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st);
 
 // Both inputs ascending: merged keys/ids in one pass (ties: a first).
 hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, float tau,

@@ -2,7 +2,7 @@
 // App. B "Combined complexity").  Hand-written for gfx950:
 // 64-wide wavefronts, ballot-based stable ranking, LDS-staged scatter.
 //
-//   (up to kRunSortMax merged positions: run_sort_kernels.hip)
+//   (up to kSplitSortMax merged positions: split_sort_kernels.hip)
 //   radix sort  one-sweep LSD sort, up to 4 passes of 8 bits (a pass whose digit is the same
 //               for every key is skipped): one histogram kernel (key
 //               build fused: a ++ b -> order-preserving u32 keys, ids = positions),

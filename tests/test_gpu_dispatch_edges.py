@@ -92,6 +92,51 @@ def test_run_sort_order_and_decays(oracle, N, kind):
     assert float((np.abs(y[pick, 0] - ref) / (1e-5 * ref + 1e-7)).max()) <= 1.0
 
 
+@pytest.mark.parametrize("kind", ["uniform", "grid", "clusters", "wide", "ordered_blocks"])
+@pytest.mark.parametrize("N", [(1 << 20) - 1, (1 << 20) + 1, 256 * 6144, 256 * 6144 + 1, 1 << 21, (1 << 21) + 1, 512 * 6144, 512 * 6144 + 1,
+                               1 << 22, (1 << 22) + 1])
+def test_sample_sort_order(N, kind):
+    """The sort by samples where its tiles and the number of its stretches change; `wide` spreads keys over all exponents of both signs,
+    `clusters` puts far more keys than bins allow into narrow windows, `ordered_blocks` makes a tile's share of a stretch very uneven."""
+    r = np.random.default_rng(N)
+    if kind == "uniform":
+        v = r.uniform(0, N / 64, N)
+    elif kind == "grid":
+        v = np.round(r.uniform(0, N / 512, N) * 4) * 0.25
+    elif kind == "clusters":
+        v = r.integers(0, 1 + N // 3000, N) * 1000.0 + r.normal(size=N) * 1e-3
+    elif kind == "wide":
+        v = np.exp(r.uniform(-80, 80, N)) * r.choice([-1.0, 1.0], N)
+    else:
+        v = np.sort(r.uniform(0, N / 64, N))
+        v = np.concatenate([v[i::3] for i in (1, 2, 0)])
+    v = v.astype(np.float32)
+    ids, _ = sorted_ids(v[:777], v[777:])
+    assert np.array_equal(ids, np.argsort(v, kind="stable"))
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("N,samples", [(9000, 9 * 16), (200000, 98 * 16), (600000, 256 * 16)])
+def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
+    """The positions that the sort takes its samples from hold the smallest keys: all others fall into the last stretch, which no
+    workgroup's LDS holds."""
+    r = np.random.default_rng(N + ties)
+    i = np.arange(samples, dtype=np.uint64)
+    h = (i * 2654435761 + 40503) & 0xFFFFFFFF
+    h ^= h >> 15; h = (h * 0x2C1B3C6D) & 0xFFFFFFFF; h ^= h >> 13
+    width = N // samples
+    at = (i * width + (h * width >> 32)).astype(np.int64)
+    assert np.unique(at).size == samples and at.max() < N
+    v = r.integers(50, 90, N) * 0.25 if ties else r.uniform(50, 50 + N / 64, N)
+    v[at] = r.uniform(0, 40, samples)
+    v = v.astype(np.float32)
+    k = N // 3
+    ids, y = sorted_ids(v[:k], v[k:])
+    assert np.array_equal(ids, np.argsort(v, kind="stable"))
+    ref, tol = oracle.apply_scan(v[:k], v[k:], np.ones((N - k, 1), np.float32))
+    assert float((np.abs(y - ref) / (1e-5 * tol + 1e-7)).max()) <= 1.0
+
+
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
 @pytest.mark.parametrize("k,n,batch", [
     (1, 510, 1), (1, 511, 1), (256, 257, 2), (700, 323, 1), (701, 324, 3), (3000, 5192, 1), (1, 8191, 2),      # chunks of 512 rows
