@@ -188,6 +188,13 @@ int scan_and_send_home(ScanProblem& p, const Layout& L, char* ws, bool want_firs
 // is too much, with wide batches, the tiled scans take over, on a plan that is ranked all the same.
 bool use_small(const Layout& L) { return L.N <= kSmallMax && !small_reads_too_much(L.N, L.batch); }
 
+// Narrow batches with inputs and outputs apart, outside the routes above: the strict scans Z at the outputs wait for the backward in the
+// sorted order, in the places that the saved inputs leave free there (xs), and ga is formed where gy is gathered.  A row of y and a row
+// of Z no longer go to random places each, and no pass over gy and Z follows (us, 2^20 x 2^20, batch 8: forward downsweep 92 -> 64, row
+// products 14 -> 0, backward reduce, with 2^20 random 4-byte stores of ga, 46 -> 72; the step 381 -> 356; 50000 x 50000, batch 3: 65 -> 60
+// for the five kernels).
+bool narrow_strict(const Layout& L) { return L.batch <= kStageMaxBatch && !use_permute(L); }
+
 SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float tau, const Plan& P, const Layout& L, uint32_t flags);
 
 // Sort (or merge) the anchors and compute the neighbour decays, unless the plan is reused.
@@ -713,11 +720,8 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
         p.out_p = nullptr; p.out_z = nullptr;
         return scan_and_send_home(p, L, w, true, save, y, ldy, save ? P.z : nullptr, 1, st);
     }
-    float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
-    const bool paired = batch == 1 && p.out_z != nullptr;      // y and the saved scan of a row as one 8-byte slot
-    if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_z = pairs + 1; p.ld_z = 2; }
+    if (p.out_z && narrow_strict(L)) { p.out_z = P.xs; p.z_sorted = true; }
     LAPLEX_HIP(launch_scan(p, L, w, st));
-    if (paired) LAPLEX_HIP(launch_unpair(pairs, k, y, ldy, P.z, st));
     return LAPLEX_OK;
 }
 
@@ -781,6 +785,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     const bool sorted = (flags & LAPLEX_A_SORTED) && (flags & LAPLEX_B_SORTED);
     LAPLEX_CHECK(build_plan(a, k, b, n, tau, L, w, flags, sorted, st));
     const bool routed = use_permute(L);        // batch 1, many rows: no random accesses (see rows_to_sorted)
+    const bool in_order = narrow_strict(L);    // ga comes from the scan that gathers gy
     if (ga) {
         if (!(flags & LAPLEX_SAVE_SCANS)) {   // strict scans of x at the outputs, not kept by the forward
             ScanProblem p = problem(P, L);
@@ -795,10 +800,11 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
                 p.out_z = nullptr;
                 LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, P.z, 1, nullptr, 1, st));
             } else {
+                if (in_order) { p.out_z = P.xs; p.z_sorted = true; }
                 LAPLEX_HIP(launch_scan(p, L, w, st));
             }
         }
-        LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
+        if (!in_order) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
     }
     // sorted-order x is in the saved region if the forward kept it or the re-scan above just wrote it
     const bool have_xs = (flags & LAPLEX_SAVE_SCANS) || ga;
@@ -813,6 +819,11 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         p.tag = "bwd";
         if (gx) LAPLEX_CHECK(scan_and_send_home(p, L, w, true, gb != nullptr, gx, ldgx, gb, 1, st));
         else LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, gb, 1, nullptr, 1, st));
+    } else if (in_order && ga && !gx && !gb) {
+        ScanProblem p = problem(P, L);
+        p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)k;
+        p.dot_z = P.xs; p.dot_out = ga;
+        LAPLEX_HIP(launch_sorted_rowdot(p, st));
     } else if (gx || gb) {
         ScanProblem p = problem(P, L);
         p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)k;
@@ -824,6 +835,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }
         p.stage = P.stage;
         p.wstage = (gb && have_xs) ? P.xs : nullptr;
+        if (in_order && ga) { p.dot_z = P.xs; p.dot_out = ga; }
         p.tag = "bwd";
         p.phase = fuse;           // phased backward: the streaming downsweep merges the two halves (see phase_fusable)
         p.phase_in = pin_bwd;     // ... and the other downsweeps' blocks get their doubled weight rows

@@ -83,6 +83,8 @@ struct ScanArgs {
     int inj_sorted;               // batch 1: `stage` already holds the injected rows in sorted order: nothing is gathered
     int out_sorted;               // batch 1: outputs are indexed by the sorted row, not by the id (a later pass takes them home)
     PartEmit emit;                // batch 1, sorted order: the results leave as records of a partition level (k_seq_down)
+    int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_sorted)
+    const float* dot_z; float* dot_out;
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
@@ -517,10 +519,44 @@ k_scan_meta(const ScanArgs A)
     }
 }
 
+constexpr uint32_t kNoRow = 0xFFFFFFFFu;
+
+// Sums over a row's columns (bv lanes), for all ITEMS rows of a row-lane at once, as a butterfly: a step adds up two lanes' partial sums and leaves half of the
+// rows with each, so ITEMS rows take ITEMS - 1 exchanges (and one more per doubling of bv beyond ITEMS) instead of
+// ITEMS * log2(bv): the exchanges share the LDS pipe with the scans (2999 x 100003, batch 33, forward + backward: 204 -> 185 us; Gram
+// form, n = 3 x 2^20, batch 64: 1745 -> 1685 us).  The sums are those of emit_row_sum bit for bit (the same pairs are added).  rows[i]: where row i's sum goes, or kNoRow.
+template <int ITEMS>
+__device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&rows)[ITEMS], int bv, int c, float* out, int64_t ld)
+{
+    int m = 1;
+#pragma unroll
+    for (int half = ITEMS / 2; half >= 1; half >>= 1) {
+        if (m < bv) {                                   // uniform
+            const bool upper = (c & m) != 0;
+#pragma unroll
+            for (int i = 0; i < half; ++i) {
+                const float mine = upper ? acc[i + half] : acc[i], other = upper ? acc[i] : acc[i + half];
+                acc[i] = mine + __shfl_xor(other, m);
+                rows[i] = upper ? rows[i + half] : rows[i];
+                rows[i + half] = kNoRow;
+            }
+            m <<= 1;
+        }
+    }
+    const int first = m;                                // lanes below it hold different rows
+    for (; m < bv; m <<= 1) acc[0] += __shfl_xor(acc[0], m);
+    if (c < first) {
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i)
+            if (rows[i] != kNoRow) out[(int64_t)rows[i] * ld] = acc[i];
+    }
+}
+
 // ---------------------------------------------------------------------------
 // reduce: forward and backward summary of every tile, and the tile's flags
 // ---------------------------------------------------------------------------
-template <int VEC, bool STRICT>
+// DOT: the rows' products with the strict scans of another problem are wanted (dot_out).
+template <int VEC, bool STRICT, bool DOT>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_reduce(const ScanArgs A)
 {
@@ -569,6 +605,28 @@ k_scan_reduce(const ScanArgs A)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
             if (T.id[i] != 0xFFFFFFFFu) store_vec<VEC>(A.stage + (row0 + i) * A.batch + col0, v[i]);
+    }
+
+    if constexpr (DOT) {        // (one slab: narrow batches)
+        float dot[ITEMS];
+        uint32_t rows[ITEMS];
+#pragma unroll
+        for (int i0 = 0; i0 < ITEMS; i0 += 4) {          // four rows at a time: a whole set of them takes two wavefronts off a SIMD
+            __builtin_amdgcn_sched_barrier(0);
+            float z[4][VEC];
+#pragma unroll
+            for (int i = i0; i < i0 + 4; ++i)
+                load_vec_or_zero<VEC>(z[i - i0], A.dot_z, (row0 + i) * A.batch + col0, col_ok && T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi);
+#pragma unroll
+            for (int i = i0; i < i0 + 4; ++i) {
+                dot[i] = 0.0f;
+                rows[i] = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi ? T.id[i] - A.inj_lo : kNoRow;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) dot[i] += v[i][e] * z[i - i0][e];
+            }
+        }
+        emit_row_sums<ITEMS>(dot, rows, bv, c, A.dot_out, 1);
+        __builtin_amdgcn_sched_barrier(0);
     }
 
     // The tile's summary as a weighted sum of the row-lanes' own (each from zero over its ITEMS rows): a row-lane's forward
@@ -1381,39 +1439,6 @@ __device__ __forceinline__ void emit_row_sum(const ScanArgs& A, float acc, int b
     }
 }
 
-// The same for all ITEMS rows of a row-lane at once, as a butterfly: a step adds up two lanes' partial sums and leaves half of the
-// rows with each, so ITEMS rows take ITEMS - 1 exchanges (and one more per doubling of bv beyond ITEMS) instead of
-// ITEMS * log2(bv): the exchanges share the LDS pipe with the scans (2999 x 100003, batch 33, forward + backward: 204 -> 185 us; Gram
-// form, n = 3 x 2^20, batch 64: 1745 -> 1685 us).  The sums are those of emit_row_sum bit for bit (the same pairs are added).  rows[i]: where row i's sum goes, or -1.
-template <int ITEMS>
-__device__ __forceinline__ void emit_row_sums(const ScanArgs& A, float (&acc)[ITEMS], int64_t (&rows)[ITEMS], int bv, int c, int64_t res_rows)
-{
-    int m = 1;
-#pragma unroll
-    for (int half = ITEMS / 2; half >= 1; half >>= 1) {
-        if (m < bv) {                                   // uniform
-            const bool upper = (c & m) != 0;
-#pragma unroll
-            for (int i = 0; i < half; ++i) {
-                const float mine = upper ? acc[i + half] : acc[i], other = upper ? acc[i] : acc[i + half];
-                acc[i] = mine + __shfl_xor(other, m);
-                rows[i] = upper ? rows[i + half] : rows[i];
-                rows[i + half] = -1;
-            }
-            m <<= 1;
-        }
-    }
-    const int first = m;                                // lanes below it hold different rows
-    for (; m < bv; m <<= 1) acc[0] += __shfl_xor(acc[0], m);
-    if (c >= first) return;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-        if (rows[i] < 0) continue;
-        if (A.slabs == 1) A.out_red[rows[i] * A.ld_red] = acc[i];
-        else A.red_partial[(int64_t)blockIdx.y * res_rows + rows[i]] = acc[i];
-    }
-}
-
 // Carries into a block, forward (Fc, Ec) and backward (Rc, Gc).  A block that is a tile of its own
 // reads them as the spine left them.  In the wide geometry the spine's carries belong to the tile of
 // 2^sub_shift blocks: the block's carry is the tile's, decayed to the block by one exponential of an
@@ -1525,7 +1550,7 @@ __device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
         }
         if (is_res && col_ok) {
             if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0, Z);
+            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
         }
         if (want_red) {
             float acc = 0.0f;
@@ -1713,7 +1738,7 @@ k_scan_down(const ScanArgs A)
     // backward walk with emission
     const int64_t res_rows = (int64_t)A.res_hi - (int64_t)A.res_lo;
     float racc[want_red ? ITEMS : 1];
-    int64_t rrow[want_red ? ITEMS : 1];
+    uint32_t rrow[want_red ? ITEMS : 1];
     float wnext[VEC];
     if (!w_ahead) fetch_row(ITEMS - 1, wnext);
 #pragma unroll
@@ -1746,10 +1771,10 @@ k_scan_down(const ScanArgs A)
         if (is_res && col_ok) {
             if (kStreamRows<VEC>) {
                 if (A.out_p) store_vec_stream<VEC>(A.out_p + rr * A.ld_p + col0, P);
-                if (STRICT && A.out_z) store_vec_stream<VEC>(A.out_z + rr * A.ld_z + col0, Z);
+                if (STRICT && A.out_z) store_vec_stream<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
             } else {
                 if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-                if (STRICT && A.out_z) store_vec<VEC>(A.out_z + rr * A.ld_z + col0, Z);
+                if (STRICT && A.out_z) store_vec<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
             }
         }
         if (want_red) {
@@ -1757,11 +1782,14 @@ k_scan_down(const ScanArgs A)
 #pragma unroll
             for (int e = 0; e < VEC; ++e) acc += wrow[e] * Z[e];     // wrow is 0 off the result rows
             racc[want_red ? i : 0] = acc;
-            rrow[want_red ? i : 0] = is_res ? rr : -1;
+            rrow[want_red ? i : 0] = is_res ? (uint32_t)rr : kNoRow;
         }
     }
     if constexpr (want_red) {
-        if (!(VEC == 1 && A.pair_out)) emit_row_sums<ITEMS>(A, racc, rrow, bv, c, res_rows);
+        if (!(VEC == 1 && A.pair_out)) {
+            if (A.slabs == 1) emit_row_sums<ITEMS>(racc, rrow, bv, c, A.out_red, A.ld_red);
+            else emit_row_sums<ITEMS>(racc, rrow, bv, c, A.red_partial + (int64_t)blockIdx.y * res_rows, 1);
+        }
     }
 }
 
@@ -2815,6 +2843,21 @@ k_rowdot_narrow(const float* __restrict__ u, int64_t ldu, int64_t op_u, const fl
     }
 }
 
+// out[id - lo] = sum_t u[id - lo, t] * z[j, t] for the sorted rows j whose id lies in [lo, hi): one thread per sorted row
+__global__ void __launch_bounds__(256)
+k_sorted_rowdot(const uint32_t* __restrict__ ids, int64_t N, uint32_t lo, uint32_t hi, const float* __restrict__ u, int64_t ldu,
+                const float* __restrict__ z, int64_t batch, float* __restrict__ out)
+{
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += stride) {
+        const uint32_t id = ids[j];
+        if (id < lo || id >= hi) continue;
+        float s = 0.0f;
+        for (int64_t t = 0; t < batch; ++t) s += u[(int64_t)(id - lo) * ldu + t] * z[j * batch + t];
+        out[id - lo] = s;
+    }
+}
+
 // out[r] += sum_t u[r, t] * v[r, t]: one thread per row (narrow batches)
 __global__ void __launch_bounds__(256)
 k_add_rowdot(const float* __restrict__ u, int64_t ldu, const float* __restrict__ v, int64_t ldv, int64_t rows, int64_t batch,
@@ -2943,7 +2986,8 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
         LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wave<VEC, STRICT>), lgrid, dim3(kLoneWaves * 64), 0, st, A));
     } else {
-        LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT>), rgrid, bblock, 0, st, A));
+        if (A.dot_out) LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, true>), rgrid, bblock, 0, st, A));
+        else LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, false>), rgrid, bblock, 0, st, A));
     }
     launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
@@ -3018,6 +3062,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.inj_sorted = p.inj_sorted ? 1 : 0; A.out_sorted = p.out_sorted ? 1 : 0;
     if (p.emit) A.emit = *p.emit;
     A.emit_first = p.emit_first ? 1 : 0;
+    A.z_sorted = p.z_sorted ? 1 : 0; A.dot_z = p.dot_z; A.dot_out = p.dot_out;
     A.ph = PhaseFuse{};
     if (p.phase) {
         // one wavefront must span a whole half-row: wide geometry, at most 256 columns per half, two slabs at most
@@ -3082,6 +3127,14 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         LAPLEX_TIMED("sum_slabs", st, hipLaunchKernelGGL(k_sum_slabs, dim3((unsigned)gsz), dim3(256), 0, st,
                                                          (const float*)A.red_partial, rows, g.slabs, p.out_red));
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_sorted_rowdot(const ScanProblem& p, hipStream_t st)
+{
+    int64_t g = (p.N + 255) / 256; if (g > 65536) g = 65536;
+    LAPLEX_TIMED("rowdot", st, hipLaunchKernelGGL(k_sorted_rowdot, dim3((unsigned)g), dim3(256), 0, st, p.ids, p.N, p.inj_lo, p.inj_hi,
+                                                  p.inj, p.ld_inj, p.dot_z, p.batch, p.dot_out));
     return hipGetLastError();
 }
 

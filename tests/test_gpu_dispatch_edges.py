@@ -137,6 +137,32 @@ def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
     assert float((np.abs(y - ref) / (1e-5 * tol + 1e-7)).max()) <= 1.0
 
 
+@pytest.mark.parametrize("saved", [True, False])
+@pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
+@pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0)])
+def test_narrow_batches_keep_strict_scans_in_order(oracle, k, n, batch, pad, wanted, saved):
+    """Batches of up to 8 columns outside the small path: ga from strict scans that wait in the sorted order, formed where gy is gathered
+    (or, when nothing else is wanted, on its own), beside every subset of the other gradients, with ties and padded rows."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + 3 * n + batch)
+    a, b = anchors("ties", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    padded = lambda v: dev(np.pad(v, ((0, 0), (0, pad))))[:, :batch]
+    da, db, dx, dg = dev(a), dev(b), padded(x), padded(g)
+    out = {"gx": torch.empty(n, batch + pad, device="cuda")[:, :batch], "ga": torch.empty(k, device="cuda"), "gb": torch.empty(n, device="cuda")}
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    flags = 0
+    if saved:
+        B.laplex_apply(da, db, dx, torch.empty(k, batch, device="cuda"), ws, B.LAPLEX_SAVE_SCANS)
+        flags = B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN
+    B.laplex_apply_backward(da, db, dx, dg, *(out[v] if v in wanted else None for v in ("gx", "ga", "gb")), ws, flags)
+    torch.cuda.synchronize()
+    for name, ref, tol in zip(("gx", "ga", "gb"), want, tols):
+        if name in wanted:
+            assert_close(name, out[name].cpu().numpy(), ref, tol)
+
+
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
 @pytest.mark.parametrize("k,n,batch", [
     (1, 510, 1), (1, 511, 1), (256, 257, 2), (700, 323, 1), (701, 324, 3), (3000, 5192, 1), (1, 8191, 2),      # chunks of 512 rows
