@@ -776,10 +776,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         if (ga) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
         if (gb) LAPLEX_HIP(launch_rowdot(x, ldx, zg, batch, n, batch, gb, st));
         if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, k, b, gb, n, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
-        if (tau != 1.0f) {
-            if (ga) LAPLEX_HIP(launch_scale(ga, k, tau, st));
-            if (gb) LAPLEX_HIP(launch_scale(gb, n, tau, st));
-        }
+        if (tau != 1.0f) LAPLEX_HIP(launch_scale(ga, k, gb, n, tau, st));
         return LAPLEX_OK;
     }
     const bool sorted = (flags & LAPLEX_A_SORTED) && (flags & LAPLEX_B_SORTED);
@@ -844,10 +841,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     }
     // the scans gave the gradients with respect to the scaled anchors
     if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, k, b, gb, n, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
-    if (tau != 1.0f) {
-        if (ga) LAPLEX_HIP(launch_scale(ga, k, tau, st));
-        if (gb) LAPLEX_HIP(launch_scale(gb, n, tau, st));
-    }
+    if (tau != 1.0f) LAPLEX_HIP(launch_scale(ga, k, gb, n, tau, st));
     return LAPLEX_OK;
 }
 
@@ -946,7 +940,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
         if (S.nprob > 0) LAPLEX_HIP(launch_small(S, 1, st));
         if (ga) LAPLEX_HIP(launch_rowdot2(gy, ldgy, P.z, batch, x, ldx, zg, batch, n, batch, ga, st));
         if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, n, nullptr, nullptr, 0, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
-        if (tau != 1.0f && ga) LAPLEX_HIP(launch_scale(ga, n, tau, st));
+        if (tau != 1.0f && ga) LAPLEX_HIP(launch_scale(ga, n, nullptr, 0, tau, st));
         return LAPLEX_OK;
     }
     LAPLEX_CHECK(build_plan(a, n, nullptr, 0, tau, L, w, flags, (flags & LAPLEX_A_SORTED) != 0, st));
@@ -995,7 +989,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
         if (paired) LAPLEX_HIP(launch_unpair(pairs, n, gx, ldgx, ga, st));
     }
     if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, n, nullptr, nullptr, 0, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
-    if (tau != 1.0f && ga) LAPLEX_HIP(launch_scale(ga, n, tau, st));
+    if (tau != 1.0f && ga) LAPLEX_HIP(launch_scale(ga, n, nullptr, 0, tau, st));
     return LAPLEX_OK;
 }
 
@@ -1574,7 +1568,7 @@ int laplex_scan_tile_rows(int64_t batch, int wide, int64_t* rows)
 {
     if (!rows) return LAPLEX_ERR_NULL;
     if (batch < 1 || (wide && batch % 4 != 0)) return LAPLEX_ERR_SIZE;
-    *rows = scan_geom(1, batch, wide ? 4 : 1).tile_rows;
+    *rows = scan_geom(LAPLEX_MAX_MERGED, batch, wide ? 4 : 1).tile_rows;
     return LAPLEX_OK;
 }
 

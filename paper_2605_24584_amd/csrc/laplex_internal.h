@@ -113,7 +113,8 @@ struct ScanGeom {
 
 inline int pow2_at_least(int64_t v) { int p = 1; while (p < v) p <<= 1; return p; }
 
-inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec)
+// whole: the routes through sorted order of batch 1, whose tiles are 8 wavefronts whatever the size
+inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec, bool whole = false)
 {
     ScanGeom g;
     g.vec = vec;
@@ -125,6 +126,11 @@ inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec)
     if (g.slabs < 1) g.slabs = 1;
     g.sub_shift = (vec == 4 && g.bv == 64) ? kWideSubShift : 0;
     g.waves = (vec == 4 && !g.sub_shift) ? kBlockWavesNarrow : kScanWaves;
+    // Staged batches with single columns: smaller blocks until there are 256 of them (batch 1: 8192 rows a block).  The random rows
+    // of a block are fetched by one compute unit
+    // (50000 x 50000, batch 1, us, blocks of 8 wavefronts / 1: reduce 23 / 11, downsweep 22 / 11; 300000 x 300000: 27 / 17, 24 / 17).
+    if (vec == 1 && batch <= kStageMaxBatch && !whole)
+        while (g.waves > 1 && N <= (int64_t)255 * g.waves * g.rv * g.items) g.waves /= 2;
     g.tile_rows = g.waves * g.rv * g.items;
     g.blocks = (N + g.tile_rows - 1) / g.tile_rows;
     g.tiles = (g.blocks + (int64_t(1) << g.sub_shift) - 1) >> g.sub_shift;
@@ -438,11 +444,11 @@ hipError_t launch_phase_merge(const float* src2, const float* phase, int64_t row
                               hipStream_t st);
 
 // Inverse temperature: gtau[0] = sum_i a_i ga_i + sum_j b_j gb_j (b, gb may be null with n = 0), in a fixed
-// order; `partial` is scratch for kTauPartials floats.  launch_scale: p[i] *= f.
+// order; `partial` is scratch for kTauPartials floats.  launch_scale: p[i] *= f, q[i] *= f (either may be null).
 constexpr int kTauPartials = 1024;
 hipError_t launch_tau_grad(const float* a, const float* ga, int64_t k, const float* b, const float* gb, int64_t n,
                            float* partial, float* gtau, hipStream_t st);
-hipError_t launch_scale(float* p, int64_t count, float f, hipStream_t st);
+hipError_t launch_scale(float* p, int64_t count, float* q, int64_t count_q, float f, hipStream_t st);
 
 // Small problems (small_kernels.hip): at most kSmallMax merged positions are sorted by one launch (ranks by counting) and scanned by a
 // second, in which a workgroup takes a chunk of the rows and `cols` batch columns of an operator.  A SmallProblem is a ScanProblem restricted to

@@ -112,11 +112,14 @@ k_tau_final(const float* __restrict__ partial, int count, float* __restrict__ gt
     if (threadIdx.x == 0) gtau[0] = red[0];
 }
 
+// two vectors (either may be empty) in one launch: it is all launch
 __global__ void __launch_bounds__(256)
-k_scale(float* __restrict__ p, int64_t count, float f)
+k_scale(float* __restrict__ p, int64_t count, float* __restrict__ q, int64_t count_q, float f)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride) p[i] *= f;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count + count_q; i += stride) {
+        if (i < count) p[i] *= f; else q[i - count] *= f;
+    }
 }
 
 
@@ -280,12 +283,14 @@ hipError_t launch_tau_grad(const float* a, const float* ga, int64_t k, const flo
     return hipGetLastError();
 }
 
-hipError_t launch_scale(float* p, int64_t count, float f, hipStream_t st)
+hipError_t launch_scale(float* p, int64_t count, float* q, int64_t count_q, float f, hipStream_t st)
 {
-    if (count <= 0) return hipSuccess;
-    int64_t g = (count + 255) / 256;
+    if (!p || count < 0) count = 0;
+    if (!q || count_q < 0) count_q = 0;
+    if (count + count_q <= 0) return hipSuccess;
+    int64_t g = (count + count_q + 255) / 256;
     if (g > 65536) g = 65536;
-    LAPLEX_TIMED("tau", st, hipLaunchKernelGGL(k_scale, dim3((unsigned)g), dim3(256), 0, st, p, count, f));
+    LAPLEX_TIMED("tau", st, hipLaunchKernelGGL(k_scale, dim3((unsigned)g), dim3(256), 0, st, p, count, q, count_q, f));
     return hipGetLastError();
 }
 

@@ -34,6 +34,8 @@
 #include "laplex_internal.h"
 #include "permute_tile.h"
 
+#include <type_traits>
+
 #include <string>
 
 
@@ -255,6 +257,50 @@ __device__ __forceinline__ void load_vec_or_zero(float* dst, const float* base, 
     for (int e = 0; e < VEC; ++e) dst[e] = ok ? t[e] : 0.0f;
 }
 
+// Rows that start on any 4-byte boundary, of a length that is no multiple of four (RAG): four columns a lane all the same.  A lane's
+// 16-byte access needs no alignment beyond that; the lane that holds a row's last columns loads the four columns that end with the
+// row and moves them down (the rest reads as zero), so nothing beyond a row is touched.  At least four columns.  With single columns a
+// row of 33 floats kept 33 of 64 lanes busy, one row at a time (2999 x 100003, batch 33, us, single columns / four: downsweeps 21 + 50 / 14 +
+// 26; 200000 x 200000, batch 63: 67 + 139 / 54 + 87).
+struct RowEnd { int shift; };                 // columns of the lane beyond the row's end: 0, or 1 to 3 in its last group
+typedef float v4r __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC, bool RAG>
+__device__ __forceinline__ RowEnd row_end(int64_t col0, int64_t batch)
+{
+    const int64_t over = col0 + VEC - batch;
+    return RowEnd{RAG && over > 0 && over < VEC ? (int)over : 0};
+}
+// dst <- ok ? the lane's columns of the row at base + off (off: of the lane's first column) : 0
+template <int VEC, bool STREAM, bool RAG>
+__device__ __forceinline__ void load_row_or_zero(float* dst, const float* base, int64_t off, bool ok, RowEnd end)
+{
+    if constexpr (!RAG) {
+        load_vec_or_zero<VEC, STREAM>(dst, base, off, ok);
+    } else {
+        static_assert(VEC == 4, "ragged rows are for lanes of four columns");
+        const v4r t = *reinterpret_cast<const v4r*>(base + (ok ? off - end.shift : 0));
+        const bool two = (end.shift & 2) != 0, one = (end.shift & 1) != 0;
+        const float a0 = two ? t[2] : t[0], a1 = two ? t[3] : t[1], a2 = two ? 0.0f : t[2], a3 = two ? 0.0f : t[3];
+        dst[0] = ok ? (one ? a1 : a0) : 0.0f;
+        dst[1] = ok ? (one ? a2 : a1) : 0.0f;
+        dst[2] = ok ? (one ? a3 : a2) : 0.0f;
+        dst[3] = ok ? (one ? 0.0f : a3) : 0.0f;
+    }
+}
+template <int VEC, bool RAG>
+__device__ __forceinline__ void store_row(float* dst, const float* src, RowEnd end)
+{
+    if constexpr (!RAG) {
+        if (kStreamRows<VEC>) store_vec_stream<VEC>(dst, src); else store_vec<VEC>(dst, src);
+    } else if (end.shift == 0) {
+        *reinterpret_cast<v4r*>(dst) = (v4r){src[0], src[1], src[2], src[3]};
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e + end.shift < VEC) dst[e] = src[e];
+    }
+}
+
 template <int VEC>
 struct TileRows {
     static constexpr int ITEMS = VEC == 4 ? kItemsVec4 : kItemsVec1;
@@ -344,20 +390,21 @@ __device__ __forceinline__ void enter_state(float* F, float* E, const float* Fc,
     }
 }
 
-template <int VEC, bool STREAM = false>
+template <int VEC, bool STREAM = false, bool RAG = false>
 __device__ __forceinline__ void load_injected(const ScanArgs& A, const TileRows<VEC>& T, int64_t col0, bool col_ok,
                                               float (*v)[VEC])
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
         const bool ok = col_ok && T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi;
-        load_vec_or_zero<VEC, STREAM>(v[i], A.inj, (int64_t)(T.id[i] - A.inj_lo) * A.ld_inj + col0, ok);
+        load_row_or_zero<VEC, STREAM, RAG>(v[i], A.inj, (int64_t)(T.id[i] - A.inj_lo) * A.ld_inj + col0, ok, end);
     }
 }
 
 // weights of the row reduction at the result rows (zero elsewhere, or when no reduction is wanted)
-template <int VEC>
+template <int VEC, bool RAG = false>
 __device__ __forceinline__ void load_weights(const ScanArgs& A, const TileRows<VEC>& T, int64_t row0, int64_t col0,
                                              bool col_ok, bool want, float (*wv)[VEC])
 {
@@ -372,7 +419,7 @@ __device__ __forceinline__ void load_weights(const ScanArgs& A, const TileRows<V
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const bool ok = col_ok && T.id[i] >= A.res_lo && T.id[i] < A.res_hi;
-            load_vec_or_zero<VEC>(wv[i], A.w, (int64_t)(T.id[i] - A.res_lo) * A.ld_w + col0, ok);
+            load_row_or_zero<VEC, false, RAG>(wv[i], A.w, (int64_t)(T.id[i] - A.res_lo) * A.ld_w + col0, ok, row_end<VEC, RAG>(col0, A.batch));
         }
     } else {
 #pragma unroll
@@ -556,7 +603,7 @@ __device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&ro
 // reduce: forward and backward summary of every tile, and the tile's flags
 // ---------------------------------------------------------------------------
 // DOT: the rows' products with the strict scans of another problem are wanted (dot_out).
-template <int VEC, bool STRICT, bool DOT>
+template <int VEC, bool STRICT, bool DOT, bool RAG>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_reduce(const ScanArgs A)
 {
@@ -595,7 +642,7 @@ k_scan_reduce(const ScanArgs A)
         for (int i = 0; i < ITEMS; ++i)
             load_vec_or_zero<VEC>(v[i], A.stage, (row0 + i) * A.batch + col0, col_ok && T.id[i] != 0xFFFFFFFFu);
     } else {
-        load_injected<VEC, kStreamRows<VEC>>(A, T, col0, col_ok, v);
+        load_injected<VEC, kStreamRows<VEC>, RAG>(A, T, col0, col_ok, v);
     }
     __syncthreads();
     if (c == 0 && mine) atomicOr(&tile_flags, mine);
@@ -976,8 +1023,11 @@ k_phase_split_blocks(const ScanArgs A, int from_list)
 // LDS and no barrier, and a workgroup is four independent wavefronts.  Same outputs as k_scan_reduce.
 // ---------------------------------------------------------------------------
 constexpr int kLoneWaves = 4;
+// tiles up to which a workgroup per tile is taken instead: four times the wavefronts, each with a quarter of the chain (us, reduce,
+// wavefront / workgroup: 805 tiles of 36 columns 26 / 9, 626 of 64 columns 14 / 11)
+constexpr int64_t kLoneTilesMin = 2048;
 
-template <int VEC, bool STRICT>
+template <int VEC, bool STRICT, bool RAG>
 __global__ void __launch_bounds__(kLoneWaves * 64)
 k_scan_reduce_wave(const ScanArgs A)
 {
@@ -1011,7 +1061,7 @@ k_scan_reduce_wave(const ScanArgs A)
         mine |= here;
         float v[ITEMS][VEC];
         if (__ballot(here & kFlagInj)) {                     // uniform: rows are read only where something is injected
-            load_injected<VEC, kStreamRows<VEC>>(A, T, col0, col_ok, v);
+            load_injected<VEC, kStreamRows<VEC>, RAG>(A, T, col0, col_ok, v);
         } else {
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i)
@@ -1186,6 +1236,12 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
                                             int rl, int step, int64_t col0, bool col_ok, float* F, float* E)
 {
     constexpr int kAhead = 4;
+    constexpr int kSums = VEC == 1 ? kAhead : 1;             // one sum per entry in flight (short chains of roundings) where that costs nothing
+    float f[kSums][VEC], q[kSums][VEC];
+#pragma unroll
+    for (int i = 0; i < kSums; ++i)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { f[i][e] = i == 0 ? F[e] : 0.0f; q[i][e] = STRICT && i == 0 ? E[e] : 0.0f; }
     const bool read_all = A.counters[kNonFiniteWord] != 0u;
     // the entry's end towards the edge, and the row behind it (sentinels beyond the ends of the sequence)
     auto end_of = [&](int64_t v) { const int64_t e = (v + 1) * SR; return e < A.N ? e : A.N; };
@@ -1221,10 +1277,15 @@ __device__ __forceinline__ void add_entries(const ScanArgs& A, const Level& L, i
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
                 const float x = w[i] * S[i][e];
-                F[e] += x;
-                if (STRICT) E[e] += edge ? (starts ? Q[i][e] : 0.0f) : x;
+                f[i % kSums][e] += x;
+                if (STRICT) q[i % kSums][e] += edge ? (starts ? Q[i][e] : 0.0f) : x;
             }
         }
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        F[e] = kSums == 1 ? f[0][e] : (f[0][e] + f[1 % kSums][e]) + (f[2 % kSums][e] + f[3 % kSums][e]);
+        if (STRICT) E[e] = kSums == 1 ? q[0][e] : (q[0][e] + q[1 % kSums][e]) + (q[2 % kSums][e] + q[3 % kSums][e]);
     }
 }
 
@@ -1488,7 +1549,7 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 // and symmetrically from the right.  The decays come from the anchors directly, so
 // the kernel has no scan, no LDS and no barrier; the batch columns are streamed.
 // ---------------------------------------------------------------------------
-template <int VEC, bool STRICT>
+template <int VEC, bool STRICT, bool RAG>
 __device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
@@ -1511,7 +1572,8 @@ __device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
     load_meta<VEC>(A, row0, T);
     const bool want_red = STRICT && A.out_red != nullptr;
     float wv[ITEMS][VEC];
-    load_weights<VEC>(A, T, row0, col0, col_ok, want_red, wv);
+    load_weights<VEC, RAG>(A, T, row0, col0, col_ok, want_red, wv);
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
     float Fin[VEC], Ein[VEC], Rin[VEC], Gin[VEC];
     load_block_carries<VEC, STRICT>(A, tile, col0, col_ok, Fin, Ein, Rin, Gin);
 
@@ -1549,8 +1611,13 @@ __device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
             Z[e] = taint((seen_b ? Rj : Gin[e]) - (seen_f ? Fj : Ein[e]), poison);
         }
         if (is_res && col_ok) {
-            if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-            if (STRICT && A.out_z) store_vec<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
+            if (RAG) {
+                if (A.out_p) store_row<VEC, RAG>(A.out_p + rr * A.ld_p + col0, P, end);
+                if (STRICT && A.out_z) store_row<VEC, RAG>(A.out_z + rr * A.ld_z + col0, Z, end);
+            } else {
+                if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
+                if (STRICT && A.out_z) store_vec<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
+            }
         }
         if (want_red) {
             float acc = 0.0f;
@@ -1561,7 +1628,7 @@ __device__ __forceinline__ void sparse_block(const ScanArgs& A, int64_t tile)
     }
 }
 
-template <int VEC, bool STRICT>
+template <int VEC, bool STRICT, bool RAG>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_down_sparse(const ScanArgs A)
 {
@@ -1570,7 +1637,7 @@ k_scan_down_sparse(const ScanArgs A)
     const int flags = (int)A.blk_flags[blockIdx.x];
     // result rows and nothing injected (blocks with a few injected rows exist in the wide geometry only, which has a kernel of its own)
     if (!(flags & kFlagRes) || (flags & kFlagInj)) return;
-    sparse_block<VEC, STRICT>(A, blockIdx.x);
+    sparse_block<VEC, STRICT, RAG>(A, blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1579,7 +1646,7 @@ k_scan_down_sparse(const ScanArgs A)
 // WAVES: wavefronts of the workgroup (sizes the LDS buffer); RED: the row reduction is wanted (out_red);
 // ZS: the reduction takes in the saved strict scans (A.zs) -- without them the kernel fits in 128 registers
 // at scalar lanes, and a compute unit holds two workgroups of eight wavefronts instead of one.
-template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS = RED>
+template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS, bool RAG>
 __global__ void __launch_bounds__(WAVES * 64)
 k_scan_down(const ScanArgs A)
 {
@@ -1597,7 +1664,7 @@ k_scan_down(const ScanArgs A)
     const int64_t tile = A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
     const int flags = (int)A.blk_flags[tile];
     if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) {
-        if (A.every_block && (flags & kFlagRes)) sparse_block<VEC, STRICT>(A, tile);      // nothing injected
+        if (A.every_block && (flags & kFlagRes)) sparse_block<VEC, STRICT, RAG>(A, tile);      // nothing injected
         return;
     }
     const uint32_t poison = plan_poison(A.counters);
@@ -1629,8 +1696,9 @@ k_scan_down(const ScanArgs A)
         for (int i = 0; i < ITEMS; ++i)
             load_vec_or_zero<VEC>(v[i], A.stage, (row0 + i) * A.batch + col0, col_ok && T.id[i] != 0xFFFFFFFFu);
     } else {
-        load_injected<VEC, kStreamRows<VEC>>(A, T, col0, col_ok, v);
+        load_injected<VEC, kStreamRows<VEC>, RAG>(A, T, col0, col_ok, v);
     }
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
 
     constexpr bool want_red = STRICT && RED;
     // The saved strict scans enter the row reduction only through sum_t v * zs, which needs nothing from
@@ -1645,7 +1713,7 @@ k_scan_down(const ScanArgs A)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             const bool ok = col_ok && T.id[i] >= A.res_lo && T.id[i] < A.res_hi;
-            load_vec_or_zero<VEC, kStreamRows<VEC>>(zrow[i], A.zs, ((int64_t)T.id[i] - (int64_t)A.res_lo) * A.batch + col0, ok);
+            load_row_or_zero<VEC, kStreamRows<VEC>, RAG>(zrow[i], A.zs, ((int64_t)T.id[i] - (int64_t)A.res_lo) * A.batch + col0, ok, end);
         }
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
@@ -1659,7 +1727,7 @@ k_scan_down(const ScanArgs A)
         for (int e = 0; e < VEC; ++e) wrow[e] = 0.0f;
         if (want_red) {                                  // uniform branches
             if (A.wstage) load_vec_or_zero<VEC, kStreamRows<VEC>>(wrow, A.wstage, (row0 + i) * A.batch + col0, ok);
-            else load_vec_or_zero<VEC, kStreamRows<VEC>>(wrow, A.w, rr * A.ld_w + col0, ok);
+            else load_row_or_zero<VEC, kStreamRows<VEC>, RAG>(wrow, A.w, rr * A.ld_w + col0, ok, end);
         }
     };
 
@@ -1769,13 +1837,8 @@ k_scan_down(const ScanArgs A)
             continue;
         }
         if (is_res && col_ok) {
-            if (kStreamRows<VEC>) {
-                if (A.out_p) store_vec_stream<VEC>(A.out_p + rr * A.ld_p + col0, P);
-                if (STRICT && A.out_z) store_vec_stream<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
-            } else {
-                if (A.out_p) store_vec<VEC>(A.out_p + rr * A.ld_p + col0, P);
-                if (STRICT && A.out_z) store_vec<VEC>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z);
-            }
+            if (A.out_p) store_row<VEC, RAG>(A.out_p + rr * A.ld_p + col0, P, end);
+            if (STRICT && A.out_z) store_row<VEC, RAG>(A.out_z + (A.z_sorted ? row0 + i : rr) * A.ld_z + col0, Z, end);
         }
         if (want_red) {
             float acc = ZS ? vz[ZS ? i : 0] : 0.0f;
@@ -2909,6 +2972,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
 // 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243; with two or four row-lanes up to 7e6 (a product: 90000 x 90000, batch
 // 64 (6.6e6): 52 / 50; 100000 x 100000, batch 64 (8.1e6): 53 / 54; 200000 x 3, batch 64 (8.1e6): 49 / 52).
+constexpr int kFewSpineWaves = 4;
 constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnsWork = 12e6, kSpineColumnWork = 5e6;
 constexpr double kSpineSuperWork = double(1 << 23), kSpineSuperFewWork = 7e6;
 template <int VEC, bool STRICT>
@@ -2929,12 +2993,16 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
     if (one || two) {
         const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
         auto groups = [&](int64_t n) { return (unsigned)(g.rv >= 8 ? (n + kScanWaves - 1) / kScanWaves : n); };
+        // With two levels a tile reads at most 32 entries of its group and the other groups: fewer wavefronts share it where they
+        // have two or four row-lanes each (kFewSpineWaves: four entries in flight per row-lane, 16 row-lanes)
+        const bool few = two && VEC == 4 && g.rv >= 4 && lists == 0;      // (the workgroups that list blocks are whole ones)
+        const dim3 sblock(few ? kFewSpineWaves * 64 : kScanThreads);
         const dim3 sgrid(groups(super.count), (unsigned)g.slabs, 2), dgrid((unsigned)lists + groups(g.tiles), (unsigned)g.slabs, 2);
-        auto go = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, dgrid, block, 0, st, A, super, lists)); };
-        auto sums = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, sgrid, block, 0, st, A, super)); };
-        if (two) { if (g.rv >= 8) sums(k_spine_super<VEC, STRICT, 1>); else sums(k_spine_super<VEC, STRICT, kScanWaves>); }
+        auto go = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, dgrid, g.rv >= 8 ? block : sblock, 0, st, A, super, lists)); };
+        auto sums = [&](auto kernel) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, sgrid, g.rv >= 8 ? block : sblock, 0, st, A, super)); };
+        if (two) { if (g.rv >= 8) sums(k_spine_super<VEC, STRICT, 1>); else if (few) sums(k_spine_super<VEC, STRICT, kFewSpineWaves>); else sums(k_spine_super<VEC, STRICT, kScanWaves>); }
         if (g.rv >= 8) { if (two) go(k_spine_direct<VEC, STRICT, 1, true>); else go(k_spine_direct<VEC, STRICT, 1, false>); }
-        else           { if (two) go(k_spine_direct<VEC, STRICT, kScanWaves, true>); else go(k_spine_direct<VEC, STRICT, kScanWaves, false>); }
+        else           { if (few) go(k_spine_direct<VEC, STRICT, kFewSpineWaves, true>); else if (two) go(k_spine_direct<VEC, STRICT, kScanWaves, true>); else go(k_spine_direct<VEC, STRICT, kScanWaves, false>); }
         return;
     }
     if (g.chunks > 1) {     // one chunk: nothing to carry between chunks, the tiles' carries come from k_spine_down alone
@@ -2944,7 +3012,7 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
     LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
 }
 
-template <int VEC, bool STRICT>
+template <int VEC, bool STRICT, bool RAG>
 void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bool two, hipStream_t st)
 {
     const dim3 block(kScanThreads);                 // spine kernels
@@ -2982,12 +3050,12 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
             LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wide<STRICT, 2>), dim3(rgrid.x), dim3(kWideWaves * 64), 0, st, A));
         else
             LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wide<STRICT, 1>), rgrid, dim3(kWideWaves * 64), 0, st, A));
-    } else if (!A.stage) {            // one wavefront per tile
+    } else if (!A.stage && (int64_t)rgrid.x * rgrid.y > kLoneTilesMin) {      // one wavefront per tile
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
-        LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wave<VEC, STRICT>), lgrid, dim3(kLoneWaves * 64), 0, st, A));
+        LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wave<VEC, STRICT, RAG>), lgrid, dim3(kLoneWaves * 64), 0, st, A));
     } else {
-        if (A.dot_out) LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, true>), rgrid, bblock, 0, st, A));
-        else LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, false>), rgrid, bblock, 0, st, A));
+        if (A.dot_out) LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, !RAG, RAG>), rgrid, bblock, 0, st, A));      // (narrow batches only)
+        else LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, false, RAG>), rgrid, bblock, 0, st, A));
     }
     launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
@@ -3010,15 +3078,16 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         const bool red = STRICT && A.out_red != nullptr;
         auto go = [&](auto kernel) { LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL(kernel, dgrid, bblock, 0, st, A)); };
         const bool zs = red && A.zs != nullptr;
-        if (g.waves == kScanWaves) {
-            if (zs) go(k_scan_down<VEC, STRICT, kScanWaves, STRICT, STRICT>);
-            else if (red) go(k_scan_down<VEC, STRICT, kScanWaves, STRICT, false>);
-            else go(k_scan_down<VEC, STRICT, kScanWaves, false, false>);
-        } else {
-            if (zs) go(k_scan_down<VEC, STRICT, kBlockWavesNarrow, STRICT, STRICT>);
-            else if (red) go(k_scan_down<VEC, STRICT, kBlockWavesNarrow, STRICT, false>);
-            else go(k_scan_down<VEC, STRICT, kBlockWavesNarrow, false, false>);
-        }
+        auto with = [&](auto waves) {
+            constexpr int W = decltype(waves)::value;
+            if (zs) go(k_scan_down<VEC, STRICT, W, STRICT, STRICT, RAG>);
+            else if (red) go(k_scan_down<VEC, STRICT, W, STRICT, false, RAG>);
+            else go(k_scan_down<VEC, STRICT, W, false, false, RAG>);
+        };
+        if (g.waves == kBlockWavesNarrow) with(std::integral_constant<int, kBlockWavesNarrow>{});
+        else if (VEC == 1 && g.waves == 2) with(std::integral_constant<int, VEC == 1 ? 2 : kScanWaves>{});
+        else if (VEC == 1 && g.waves == 1) with(std::integral_constant<int, VEC == 1 ? 1 : kScanWaves>{});
+        else with(std::integral_constant<int, RAG ? kBlockWavesNarrow : kScanWaves>{});       // (ragged rows: never the wide geometry)
     }
     if (A.every_block) return;
     if (VEC == 4 && g.sub_shift) {
@@ -3035,7 +3104,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
             LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse_wide<STRICT>), sgrid, dim3(kStreamWaves * 64), 0, st, A));
         }
     } else {
-        LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse<VEC, STRICT>), grid, bblock, 0, st, A));
+        LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL((k_scan_down_sparse<VEC, STRICT, RAG>), grid, bblock, 0, st, A));
     }
 }
 
@@ -3050,7 +3119,10 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     if (p.out_p) v4 = v4 && aligned16(p.out_p) && p.ld_p % 4 == 0;
     if (p.out_z) v4 = v4 && aligned16(p.out_z) && (p.ld_z == 0 || p.ld_z % 4 == 0);
     if (p.out_red) v4 = v4 && aligned16(p.w) && p.ld_w % 4 == 0 && (!p.zs || aligned16(p.zs));
-    const ScanGeom g = scan_geom(p.N, p.batch, v4 ? 4 : 1);
+    // Rows that allow no 16-byte accesses take lanes of four columns as well (RowEnd), where that is not the wide geometry, whose kernels
+    // want whole groups, and the batch is not staged.
+    const bool rag = !v4 && p.batch > kStageMaxBatch && p.batch <= 128 && !p.phase && !p.phase_in;
+    const ScanGeom g = scan_geom(p.N, p.batch, v4 || rag ? 4 : 1, p.inj_sorted && p.out_sorted);
 
     ScanArgs A;
     A.ids = p.ids; A.dh = p.dh; A.pk = p.pk; A.pk8 = p.pk8; A.N = p.N;
@@ -3119,8 +3191,9 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
 
     const std::string tag = p.tag ? p.tag : "scan";
     const bool two = p.emit_values == 2;
-    if (v4) { if (strict) launch_all<4, true>(A, g, tag, two, st); else launch_all<4, false>(A, g, tag, two, st); }
-    else    { if (strict) launch_all<1, true>(A, g, tag, two, st); else launch_all<1, false>(A, g, tag, two, st); }
+    if (v4)       { if (strict) launch_all<4, true, false>(A, g, tag, two, st); else launch_all<4, false, false>(A, g, tag, two, st); }
+    else if (rag) { if (strict) launch_all<4, true, true>(A, g, tag, two, st); else launch_all<4, false, true>(A, g, tag, two, st); }
+    else          { if (strict) launch_all<1, true, false>(A, g, tag, two, st); else launch_all<1, false, false>(A, g, tag, two, st); }
     if (p.out_red && g.slabs > 1) {
         const int64_t rows = (int64_t)p.res_hi - (int64_t)p.res_lo;
         int64_t gsz = (rows + 255) / 256; if (gsz > 65536) gsz = 65536; if (gsz < 1) gsz = 1;

@@ -137,6 +137,67 @@ def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
     assert float((np.abs(y - ref) / (1e-5 * tol + 1e-7)).max()) <= 1.0
 
 
+@pytest.mark.parametrize("k,n,batch,pad,shift", [
+    (5000, 4000, 9, 0, 0), (5000, 4000, 10, 3, 0), (4100, 4100, 15, 0, 1), (9000, 33, 17, 0, 0), (33, 9000, 31, 1, 2), (6001, 3002, 33, 0, 0),
+    (4000, 6000, 63, 0, 3), (4000, 6000, 65, 0, 0), (5000, 5000, 64, 1, 0), (5000, 5000, 12, 0, 1), (4500, 4500, 127, 0, 0), (4500, 4500, 128, 0, 2),
+    (4500, 4500, 129, 0, 0), (70000, 62000, 65, 0, 0),                          # single columns again; a wavefront per tile
+])
+def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
+    """Rows that start anywhere, of lengths that are no multiple of four: lanes of four columns whose last group ends with the row.  Forward,
+    backward (scans saved and recomputed) and the square form; nothing beyond a row may be written or take part."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + 3 * n + batch + pad)
+    a, b = anchors("ties", r, k, n)
+
+    def matrix(values):           # columns beyond the batch hold NaN, rows start `shift` floats behind an allocation's start
+        rows, ld = values.shape[0], batch + pad
+        flat = torch.full((shift + rows * ld,), float("nan"), device="cuda")
+        m = flat[shift:].view(rows, ld)
+        m[:, :batch] = dev(values)
+        return flat, m[:, :batch]
+
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    (_, dx), (_, dg), (yf, y), (gxf, gx) = matrix(x), matrix(g), matrix(np.zeros_like(g)), matrix(np.zeros_like(x))
+    da, db = dev(a), dev(b)
+    ga, gb = torch.empty(k, device="cuda"), torch.empty(n, device="cuda")
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    for flags in (B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, 0):
+        B.laplex_apply(da, db, dx, y, ws, flags & ~B.LAPLEX_REUSE_PLAN)
+        B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, flags)
+        torch.cuda.synchronize()
+        assert_close("y", y.cpu().numpy(), ref, tol)
+        for name, got, rv, tv in zip(("gx", "ga", "gb"), (gx, ga, gb), want, tols):
+            assert_close(name, got.cpu().numpy(), rv, tv)
+    if pad:
+        assert torch.isnan(yf[shift:].view(k, batch + pad)[:, batch:]).all() and torch.isnan(gxf[shift:].view(n, batch + pad)[:, batch:]).all()
+    wsg = torch.empty(B.laplex_workspace_bytes(0, n, batch), dtype=torch.uint8, device="cuda")
+    _, yg = matrix(np.zeros_like(x))
+    B.laplex_gram(db, dx, yg, wsg, 0)
+    torch.cuda.synchronize()
+    ref, tol = oracle.apply_scan(b, b, x)
+    assert_close("gram", yg.cpu().numpy(), ref, tol)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties"])
+@pytest.mark.parametrize("N,batch", [(65 * 1024, 1), (255 * 1024, 1), (255 * 1024 + 1, 1), (255 * 2048 + 1, 1), (255 * 4096 + 1, 1), (255 * 512, 2), (255 * 512 + 1, 2), (255 * 256 + 1, 3),
+                                     (255 * 128, 7), (255 * 128 + 1, 5)])
+def test_narrow_batches_where_their_blocks_grow(oracle, N, batch, kind):
+    """Single columns, up to 8 of them: blocks of one, two, four and eight wavefronts, at the sizes where they change."""
+    from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward
+    r = np.random.default_rng(N + batch)
+    k = N // 3
+    a, b = anchors(kind, r, k, N - k)
+    x, g = r.normal(size=(N - k, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    y, ws = gpu_apply(a, b, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    for name, got, rv, tv in zip(("gx", "ga", "gb"), gpu_backward(a, b, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws), want, tols):
+        assert_close(name, got, rv, tv)
+
+
 @pytest.mark.parametrize("saved", [True, False])
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
 @pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0)])
