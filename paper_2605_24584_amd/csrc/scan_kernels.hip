@@ -3006,8 +3006,9 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
         return;
     }
     if (g.chunks > 1) {     // one chunk: nothing to carry between chunks, the tiles' carries come from k_spine_down alone
+        // (whole groups of columns: what the last group of ragged rows holds beyond the batch is zero all the way, not left unwritten)
         LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_reduce<VEC, STRICT>), cgrid, block, 0, st, A));
-        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_top<STRICT>), dim3((unsigned)A.batch, 2), dim3(kSpineThreads), 0, st, A.l2, A.bpad));
+        LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_top<STRICT>), dim3((unsigned)(VEC == 4 ? A.bpad : A.batch), 2), dim3(kSpineThreads), 0, st, A.l2, A.bpad));
     }
     LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_spine_down<VEC, STRICT>), cgrid, block, 0, st, A));
 }

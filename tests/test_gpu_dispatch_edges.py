@@ -140,7 +140,8 @@ def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
 @pytest.mark.parametrize("k,n,batch,pad,shift", [
     (5000, 4000, 9, 0, 0), (5000, 4000, 10, 3, 0), (4100, 4100, 15, 0, 1), (9000, 33, 17, 0, 0), (33, 9000, 31, 1, 2), (6001, 3002, 33, 0, 0),
     (4000, 6000, 63, 0, 3), (4000, 6000, 65, 0, 0), (5000, 5000, 64, 1, 0), (5000, 5000, 12, 0, 1), (4500, 4500, 127, 0, 0), (4500, 4500, 128, 0, 2),
-    (4500, 4500, 129, 0, 0), (70000, 62000, 65, 0, 0),                          # single columns again; a wavefront per tile
+    (4500, 4500, 129, 0, 0), (70000, 62000, 65, 0, 0),                          # single columns again; a wavefront per tile, three spine launches
+    (30000, 34000, 33, 0, 0),                                                   # two spine launches
 ])
 def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
     """Rows that start anywhere, of lengths that are no multiple of four: lanes of four columns whose last group ends with the row.  Forward,
@@ -162,7 +163,7 @@ def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
     (_, dx), (_, dg), (yf, y), (gxf, gx) = matrix(x), matrix(g), matrix(np.zeros_like(g)), matrix(np.zeros_like(x))
     da, db = dev(a), dev(b)
     ga, gb = torch.empty(k, device="cuda"), torch.empty(n, device="cuda")
-    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    ws = torch.full((B.laplex_workspace_bytes(k, n, batch),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing is written
     for flags in (B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, 0):
         B.laplex_apply(da, db, dx, y, ws, flags & ~B.LAPLEX_REUSE_PLAN)
         B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, flags)
@@ -172,7 +173,7 @@ def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
             assert_close(name, got.cpu().numpy(), rv, tv)
     if pad:
         assert torch.isnan(yf[shift:].view(k, batch + pad)[:, batch:]).all() and torch.isnan(gxf[shift:].view(n, batch + pad)[:, batch:]).all()
-    wsg = torch.empty(B.laplex_workspace_bytes(0, n, batch), dtype=torch.uint8, device="cuda")
+    wsg = torch.full((B.laplex_workspace_bytes(0, n, batch),), 255, dtype=torch.uint8, device="cuda")
     _, yg = matrix(np.zeros_like(x))
     B.laplex_gram(db, dx, yg, wsg, 0)
     torch.cuda.synchronize()
@@ -212,7 +213,7 @@ def test_narrow_batches_keep_strict_scans_in_order(oracle, k, n, batch, pad, wan
     padded = lambda v: dev(np.pad(v, ((0, 0), (0, pad))))[:, :batch]
     da, db, dx, dg = dev(a), dev(b), padded(x), padded(g)
     out = {"gx": torch.empty(n, batch + pad, device="cuda")[:, :batch], "ga": torch.empty(k, device="cuda"), "gb": torch.empty(n, device="cuda")}
-    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    ws = torch.full((B.laplex_workspace_bytes(k, n, batch),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing is written
     flags = 0
     if saved:
         B.laplex_apply(da, db, dx, torch.empty(k, batch, device="cuda"), ws, B.LAPLEX_SAVE_SCANS)
