@@ -801,7 +801,8 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
                 LAPLEX_HIP(launch_scan(p, L, w, st));
             }
         }
-        if (!in_order) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
+        // (where gy is scanned below, its rows meet the strict scans' there)
+        if (routed || (!in_order && !gx && !gb)) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
     }
     // sorted-order x is in the saved region if the forward kept it or the re-scan above just wrote it
     const bool have_xs = (flags & LAPLEX_SAVE_SCANS) || ga;
@@ -832,7 +833,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }
         p.stage = P.stage;
         p.wstage = (gb && have_xs) ? P.xs : nullptr;
-        if (in_order && ga) { p.dot_z = P.xs; p.dot_out = ga; }
+        if (ga) { p.dot_z = in_order ? P.xs : P.z; p.dot_out = ga; p.dot_sorted = in_order; }
         p.tag = "bwd";
         p.phase = fuse;           // phased backward: the streaming downsweep merges the two halves (see phase_fusable)
         p.phase_in = pin_bwd;     // ... and the other downsweeps' blocks get their doubled weight rows

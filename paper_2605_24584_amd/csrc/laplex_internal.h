@@ -414,7 +414,8 @@ struct ScanProblem {
     // out_z[sorted row * batch + t], which may be `stage` itself (an injected row and a result row never share one) ...
     bool z_sorted = false;
     // ... and the reduce of the problem that injects those rows forms dot_out[id - inj_lo] = sum_t inj_row[t] * dot_z[sorted row * batch + t]
-    const float* dot_z = nullptr; float* dot_out = nullptr;
+    // (dot_sorted; else the rows of dot_z are in the caller's order, dot_z[(id - inj_lo) * batch + t], any batch)
+    const float* dot_z = nullptr; float* dot_out = nullptr; bool dot_sorted = false;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
     // batch 1, routes without random accesses: `stage` already holds the injected rows in sorted order (zero elsewhere), and
     // the outputs of result row j of the sorted sequence go to out_p[j * ld_p], out_z[j * ld_z], out_red[j * ld_red]

@@ -86,7 +86,7 @@ struct ScanArgs {
     int out_sorted;               // batch 1: outputs are indexed by the sorted row, not by the id (a later pass takes them home)
     PartEmit emit;                // batch 1, sorted order: the results leave as records of a partition level (k_seq_down)
     int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_sorted)
-    const float* dot_z; float* dot_out;
+    const float* dot_z; float* dot_out; int dot_sorted;      // row products of the reduce (ScanProblem)
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
@@ -599,6 +599,37 @@ __device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&ro
     }
 }
 
+// dot_out of a row-lane's injected rows (one slab).
+template <int VEC, bool RAG>
+__device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<VEC>& T, int64_t row0, int64_t col0, bool col_ok, int bv, int c,
+                                             float (*v)[VEC])
+{
+    constexpr int ITEMS = TileRows<VEC>::ITEMS;
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+    float dot[ITEMS];
+    uint32_t rows[ITEMS];
+#pragma unroll
+    for (int i0 = 0; i0 < ITEMS; i0 += 4) {          // four rows at a time: a whole set of them takes two wavefronts off a SIMD
+        __builtin_amdgcn_sched_barrier(0);
+        float z[4][VEC];
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) {
+            const bool in = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi;
+            const int64_t at = A.dot_sorted ? row0 + i : (int64_t)(T.id[i] - A.inj_lo);
+            load_row_or_zero<VEC, false, RAG>(z[i - i0], A.dot_z, at * A.batch + col0, col_ok && in, end);
+        }
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) {
+            dot[i] = 0.0f;
+            rows[i] = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi ? T.id[i] - A.inj_lo : kNoRow;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) dot[i] += v[i][e] * z[i - i0][e];
+        }
+    }
+    emit_row_sums<ITEMS>(dot, rows, bv, c, A.dot_out, 1);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---------------------------------------------------------------------------
 // reduce: forward and backward summary of every tile, and the tile's flags
 // ---------------------------------------------------------------------------
@@ -654,27 +685,7 @@ k_scan_reduce(const ScanArgs A)
             if (T.id[i] != 0xFFFFFFFFu) store_vec<VEC>(A.stage + (row0 + i) * A.batch + col0, v[i]);
     }
 
-    if constexpr (DOT) {        // (one slab: narrow batches)
-        float dot[ITEMS];
-        uint32_t rows[ITEMS];
-#pragma unroll
-        for (int i0 = 0; i0 < ITEMS; i0 += 4) {          // four rows at a time: a whole set of them takes two wavefronts off a SIMD
-            __builtin_amdgcn_sched_barrier(0);
-            float z[4][VEC];
-#pragma unroll
-            for (int i = i0; i < i0 + 4; ++i)
-                load_vec_or_zero<VEC>(z[i - i0], A.dot_z, (row0 + i) * A.batch + col0, col_ok && T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi);
-#pragma unroll
-            for (int i = i0; i < i0 + 4; ++i) {
-                dot[i] = 0.0f;
-                rows[i] = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi ? T.id[i] - A.inj_lo : kNoRow;
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) dot[i] += v[i][e] * z[i - i0][e];
-            }
-        }
-        emit_row_sums<ITEMS>(dot, rows, bv, c, A.dot_out, 1);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v);
 
     // The tile's summary as a weighted sum of the row-lanes' own (each from zero over its ITEMS rows): a row-lane's forward
     // state reaches the tile's last row through ONE exponential of an anchor difference, its backward state the tile's first
@@ -1023,11 +1034,13 @@ k_phase_split_blocks(const ScanArgs A, int from_list)
 // LDS and no barrier, and a workgroup is four independent wavefronts.  Same outputs as k_scan_reduce.
 // ---------------------------------------------------------------------------
 constexpr int kLoneWaves = 4;
-// tiles up to which a workgroup per tile is taken instead: four times the wavefronts, each with a quarter of the chain (us, reduce,
-// wavefront / workgroup: 805 tiles of 36 columns 26 / 9, 626 of 64 columns 14 / 11)
-constexpr int64_t kLoneTilesMin = 2048;
+// Tiles up to which a workgroup per tile is taken instead: four times the wavefronts, each with a quarter of the chain (us, reduce,
+// wavefront / workgroup: 469 tiles of 32 columns 15.0 / 11.6, 805 of 36 26 / 9 (four columns a lane, one before), 781 of 64 14.6 / 13.5, 781 of
+// 128 15.4 / 14.5, 1406 of 128 17.2 / 19.1, 1562 of 64 17.0 / 20.3); with row products, whose loads lengthen the chain, twice as many (781 of 64
+// 26 / 17, 1406 of 128 28.6 / 24.4, 1562 of 32 30.7 / 28.3).
+constexpr int64_t kLoneTilesMin = 1024;
 
-template <int VEC, bool STRICT, bool RAG>
+template <int VEC, bool STRICT, bool DOT, bool RAG>
 __global__ void __launch_bounds__(kLoneWaves * 64)
 k_scan_reduce_wave(const ScanArgs A)
 {
@@ -1062,6 +1075,7 @@ k_scan_reduce_wave(const ScanArgs A)
         float v[ITEMS][VEC];
         if (__ballot(here & kFlagInj)) {                     // uniform: rows are read only where something is injected
             load_injected<VEC, kStreamRows<VEC>, RAG>(A, T, col0, col_ok, v);
+            if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v);
         } else {
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i)
@@ -3051,12 +3065,13 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
             LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wide<STRICT, 2>), dim3(rgrid.x), dim3(kWideWaves * 64), 0, st, A));
         else
             LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wide<STRICT, 1>), rgrid, dim3(kWideWaves * 64), 0, st, A));
-    } else if (!A.stage && (int64_t)rgrid.x * rgrid.y > kLoneTilesMin) {      // one wavefront per tile
+    } else if (!A.stage && (int64_t)rgrid.x * rgrid.y > (A.dot_out ? 2 : 1) * kLoneTilesMin) {      // one wavefront per tile
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
-        LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wave<VEC, STRICT, RAG>), lgrid, dim3(kLoneWaves * 64), 0, st, A));
+        auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, lgrid, dim3(kLoneWaves * 64), 0, st, A)); };
+        if (A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, true, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
     } else {
-        if (A.dot_out) LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, !RAG, RAG>), rgrid, bblock, 0, st, A));      // (narrow batches only)
-        else LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce<VEC, STRICT, false, RAG>), rgrid, bblock, 0, st, A));
+        auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, rgrid, bblock, 0, st, A)); };
+        if (A.dot_out) go(k_scan_reduce<VEC, STRICT, true, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);
     }
     launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
@@ -3120,6 +3135,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     if (p.out_p) v4 = v4 && aligned16(p.out_p) && p.ld_p % 4 == 0;
     if (p.out_z) v4 = v4 && aligned16(p.out_z) && (p.ld_z == 0 || p.ld_z % 4 == 0);
     if (p.out_red) v4 = v4 && aligned16(p.w) && p.ld_w % 4 == 0 && (!p.zs || aligned16(p.zs));
+    if (p.dot_out) v4 = v4 && aligned16(p.dot_z);
     // Rows that allow no 16-byte accesses take lanes of four columns as well (RowEnd), where that is not the wide geometry, whose kernels
     // want whole groups, and the batch is not staged.
     const bool rag = !v4 && p.batch > kStageMaxBatch && p.batch <= 128 && !p.phase && !p.phase_in;
@@ -3135,7 +3151,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.inj_sorted = p.inj_sorted ? 1 : 0; A.out_sorted = p.out_sorted ? 1 : 0;
     if (p.emit) A.emit = *p.emit;
     A.emit_first = p.emit_first ? 1 : 0;
-    A.z_sorted = p.z_sorted ? 1 : 0; A.dot_z = p.dot_z; A.dot_out = p.dot_out;
+    A.z_sorted = p.z_sorted ? 1 : 0; A.dot_z = p.dot_z; A.dot_out = p.dot_out; A.dot_sorted = p.dot_sorted ? 1 : 0;
     A.ph = PhaseFuse{};
     if (p.phase) {
         // one wavefront must span a whole half-row: wide geometry, at most 256 columns per half, two slabs at most
@@ -3188,6 +3204,17 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         A.few_res_ok = g.sub_shift && disjoint && res_rows * 4 <= g.blocks;
         // (the metadata pass runs before the reduce; with a dense injection the reduce then visits every
         //  tile and overwrites the provisional summaries, with a sparse one only the listed tiles)
+    }
+
+    // The products of rows that several slabs share, or that the wide geometry's reduce reads, are a pass of their own, and so are those of
+    // few rows among many: every tile of the reduce would wait for one or two of them (us, backward reduce and row products apart /
+    // together: 50000 x 50000, batch 16: 11 + 12 / 14, 20000, batch 64: 11 + 8 / 13, 200000, batch 63: 23 + 35 / 49, 500000, batch 64: 38 + 77 /
+    // 83; 2999 x 100003, batch 33: 12 + 3 / 17).
+    if (p.dot_out && ((!p.dot_sorted && (g.sub_shift || g.slabs > 1)) || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
+        const hipError_t e = p.dot_sorted ? launch_sorted_rowdot(p, st)
+                                          : launch_rowdot(p.inj, p.ld_inj, p.dot_z, p.batch, (int64_t)p.inj_hi - p.inj_lo, p.batch, p.dot_out, st);
+        if (e != hipSuccess) return e;
+        A.dot_out = nullptr;
     }
 
     const std::string tag = p.tag ? p.tag : "scan";

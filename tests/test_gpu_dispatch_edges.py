@@ -201,10 +201,12 @@ def test_narrow_batches_where_their_blocks_grow(oracle, N, batch, kind):
 
 @pytest.mark.parametrize("saved", [True, False])
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
-@pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0)])
-def test_narrow_batches_keep_strict_scans_in_order(oracle, k, n, batch, pad, wanted, saved):
-    """Batches of up to 8 columns outside the small path: ga from strict scans that wait in the sorted order, formed where gy is gathered
-    (or, when nothing else is wanted, on its own), beside every subset of the other gradients, with ties and padded rows."""
+@pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0),
+                                           (7000, 6000, 12, 0), (100, 9000, 33, 0), (6000, 5000, 33, 1), (5000, 4000, 64, 0), (140000, 130000, 16, 0)])
+def test_where_the_anchor_gradient_of_the_outputs_is_formed(oracle, k, n, batch, pad, wanted, saved):
+    """Outside the small path: up to 8 columns ga comes from strict scans that wait in the sorted order, formed where gy is gathered (or,
+    when nothing else is wanted or the outputs are few, on its own); beyond, from the caller's order, in a workgroup's or a wavefront's
+    reduce.  Beside every subset of the other gradients, with ties and padded rows."""
     from test_gpu_parity import anchors, assert_close
     r = np.random.default_rng(k + 3 * n + batch)
     a, b = anchors("ties", r, k, n)
