@@ -15,15 +15,9 @@ constexpr int kRadixBits = 8;
 constexpr int kRadix = 1 << kRadixBits;
 constexpr int kSortPasses = 4;
 constexpr int kSortThreads = 512;                       // 8 wavefronts
-// Keys per thread of a sort pass, hence per tile (512 x 8 or 16).  A short sort is bound by the latency of one tile (its
-// ranking, the hop from tile to tile), not by throughput: it gets smaller tiles, so more of them run side by side.
-inline int sort_keys_per_thread(int64_t N) { return N <= (int64_t(5) << 18) ? 8 : 16; }
-inline int64_t sort_tiles_of(int64_t N)
-{
-    const int64_t tile = (int64_t)kSortThreads * sort_keys_per_thread(N);
-    return (N + tile - 1) / tile;
-}
-constexpr int64_t kSortHistTile = 8192;                 // keys per workgroup of the histogram kernel, up to its grid limit
+constexpr int kSortKeysPerThread = 16;
+constexpr int kSortTile = kSortThreads * kSortKeysPerThread;
+inline int64_t sort_tiles_of(int64_t N) { return (N + kSortTile - 1) / kSortTile; }
 // Up to this many merged positions the anchors are sorted by samples, tiles and stretches (split_sort_kernels.hip).
 constexpr int64_t kSplitSortMax = int64_t(1) << 22;
 size_t split_sort_words(int64_t N);                     // scratch words that takes besides the pair buffers
