@@ -562,7 +562,7 @@ def test_hip_graph_replays_mix_on_the_large_path():
 
 # ------------------------------------------------------------------ non-finite anchors
 
-# the run sort, and the radix sort with each of its tiles and histograms
+# the sort by samples at sizes where its tiles change, and the radix sort
 @pytest.mark.parametrize("k,n", [(700, 9000), (300000, 400000), (700000, 900000), (2200000, 2100000)])
 @pytest.mark.parametrize("sorted_flags", [0, B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED])
 def test_non_finite_anchors_do_not_fault(oracle, sorted_flags, k, n):
