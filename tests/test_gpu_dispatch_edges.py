@@ -199,6 +199,38 @@ def test_narrow_batches_where_their_blocks_grow(oracle, N, batch, kind):
         assert_close(name, got, rv, tv)
 
 
+def families(call):
+    """The kernel families that the call launches, and how often."""
+    B.laplex_profile_begin("*")
+    call()
+    B.laplex_profile_end()
+    return {name: launches for name, (_, launches) in B.laplex_profile_families().items()}
+
+
+@pytest.mark.parametrize("k,n,batch", [(64, 255 * 4096 - 64, 1), (1, 9000, 1), (50, 120000, 2), (64, 250000, 3), (10000, 4, 3), (100000, 40, 7), (16, 30000, 5)])
+def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
+    """Single columns in blocks of one, two and four wavefronts, a handful of inputs or outputs: no block is listed by a launch of its own."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + n + batch)
+    a, b = anchors("uniform", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    da, db, dx, dg = dev(a), dev(b), dev(x), dev(g)
+    y, gx, ga, gb = torch.empty_like(dg), torch.empty_like(dx), torch.empty_like(da), torch.empty_like(db)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+
+    def step():
+        B.laplex_apply(da, db, dx, y, ws, B.LAPLEX_SAVE_SCANS)
+        B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    seen = families(step)
+    assert seen["scan_reduce.fwd"] == seen["scan_reduce.bwd"] == 1
+    assert not any(name.startswith(("scan_meta", "scan_down_sparse")) for name in seen), seen
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    for name, got, rv, tv in zip(("gx", "ga", "gb"), (gx, ga, gb), want, tols):
+        assert_close(name, got.cpu().numpy(), rv, tv)
+
+
 @pytest.mark.parametrize("saved", [True, False])
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
 @pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0),
