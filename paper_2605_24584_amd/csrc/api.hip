@@ -188,12 +188,16 @@ int scan_and_send_home(ScanProblem& p, const Layout& L, char* ws, bool want_firs
 // is too much, with wide batches, the tiled scans take over, on a plan that is ranked all the same.
 bool use_small(const Layout& L) { return L.N <= kSmallMax && !small_reads_too_much(L.N, L.batch); }
 
-// Narrow batches with inputs and outputs apart, outside the routes above: the strict scans Z at the outputs wait for the backward in the
-// sorted order, in the places that the saved inputs leave free there (xs), and ga is formed where gy is gathered.  A row of y and a row
-// of Z no longer go to random places each, and no pass over gy and Z follows (us, 2^20 x 2^20, batch 8: forward downsweep 92 -> 64, row
-// products 14 -> 0, backward reduce, with 2^20 random 4-byte stores of ga, 46 -> 72; the step 381 -> 356; 50000 x 50000, batch 3: 65 -> 60
-// for the five kernels).
-bool narrow_strict(const Layout& L) { return L.batch <= kStageMaxBatch && !use_permute(L); }
+// Do the strict scans Z at the outputs wait for the backward in the sorted order, in the places that the saved inputs leave free there
+// (xs), and is ga formed where gy is gathered?  Then a row of y and a row of Z no longer go to random places each, but rows of Z are read
+// back one by one and ga goes to random places.  4 and 8 columns, where a row is read and written with 128-bit accesses, and outputs that
+// are a quarter of the merged rows or more (us, forward + backward on a kept plan, Z in the caller's order / here: 2^20 x 2^20, batch 8: 304 /
+// 288, batch 4: 275 / 263; 130000 x 130000, batch 8: 70 / 66; few outputs: 2^18 x 2^20, batch 8: 205 / 219, batch 4: 177 / 183; single
+// columns: 2^20 x 2^20, batch 1: 148 / 156, 3: 207 / 230, 5: 288 / 343, 7: 329 / 370; 20000 x 20000, batch 3: 45 / 49).
+bool strict_in_order(const Layout& L)
+{
+    return (L.batch == 4 || L.batch == 8) && L.N > kSmallMax && L.zrows < L.N && 4 * L.zrows >= L.N;
+}
 
 SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float tau, const Plan& P, const Layout& L, uint32_t flags);
 
@@ -720,8 +724,12 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
         p.out_p = nullptr; p.out_z = nullptr;
         return scan_and_send_home(p, L, w, true, save, y, ldy, save ? P.z : nullptr, 1, st);
     }
-    if (p.out_z && narrow_strict(L)) { p.out_z = P.xs; p.z_sorted = true; }
+    if (p.out_z && strict_in_order(L)) { p.out_z = P.xs; p.z_sorted = true; }
+    float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
+    const bool paired = batch == 1 && p.out_z != nullptr;      // y and the saved scan of a row as one 8-byte slot
+    if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_z = pairs + 1; p.ld_z = 2; }
     LAPLEX_HIP(launch_scan(p, L, w, st));
+    if (paired) LAPLEX_HIP(launch_unpair(pairs, k, y, ldy, P.z, st));
     return LAPLEX_OK;
 }
 
@@ -782,7 +790,8 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     const bool sorted = (flags & LAPLEX_A_SORTED) && (flags & LAPLEX_B_SORTED);
     LAPLEX_CHECK(build_plan(a, k, b, n, tau, L, w, flags, sorted, st));
     const bool routed = use_permute(L);        // batch 1, many rows: no random accesses (see rows_to_sorted)
-    const bool in_order = narrow_strict(L);    // ga comes from the scan that gathers gy
+    const bool in_order = strict_in_order(L);  // ga comes from the scan that gathers gy
+    const bool apart = !in_order && L.batch <= kStageMaxBatch;      // ... or from a launch of its own, in the caller's order
     if (ga) {
         if (!(flags & LAPLEX_SAVE_SCANS)) {   // strict scans of x at the outputs, not kept by the forward
             ScanProblem p = problem(P, L);
@@ -802,7 +811,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
             }
         }
         // (where gy is scanned below, its rows meet the strict scans' there)
-        if (routed || (!in_order && !gx && !gb)) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
+        if (apart || (!in_order && !gx && !gb)) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
     }
     // sorted-order x is in the saved region if the forward kept it or the re-scan above just wrote it
     const bool have_xs = (flags & LAPLEX_SAVE_SCANS) || ga;
@@ -833,7 +842,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }
         p.stage = P.stage;
         p.wstage = (gb && have_xs) ? P.xs : nullptr;
-        if (ga) { p.dot_z = in_order ? P.xs : P.z; p.dot_out = ga; p.dot_sorted = in_order; }
+        if (ga && !apart) { p.dot_z = in_order ? P.xs : P.z; p.dot_out = ga; p.dot_sorted = in_order; }
         p.tag = "bwd";
         p.phase = fuse;           // phased backward: the streaming downsweep merges the two halves (see phase_fusable)
         p.phase_in = pin_bwd;     // ... and the other downsweeps' blocks get their doubled weight rows

@@ -404,11 +404,11 @@ struct ScanProblem {
     int64_t batch;
     float* stage;          // narrow batches: the reduce writes the injected rows here in sorted order, the downsweep reads them back
     const float* wstage;   // narrow batches: the weights w in sorted order (an earlier problem's stage), or null
-    // narrow batches, injected and result rows apart: the strict scans Z of the result rows go to their places in the sorted order,
+    // 4 or 8 columns, injected and result rows apart: the strict scans Z of the result rows go to their places in the sorted order,
     // out_z[sorted row * batch + t], which may be `stage` itself (an injected row and a result row never share one) ...
     bool z_sorted = false;
     // ... and the reduce of the problem that injects those rows forms dot_out[id - inj_lo] = sum_t inj_row[t] * dot_z[sorted row * batch + t]
-    // (dot_sorted; else the rows of dot_z are in the caller's order, dot_z[(id - inj_lo) * batch + t], any batch)
+    // (dot_sorted; else the rows of dot_z are in the caller's order, dot_z[(id - inj_lo) * batch + t], from 9 columns on)
     const float* dot_z = nullptr; float* dot_out = nullptr; bool dot_sorted = false;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
     // batch 1, routes without random accesses: `stage` already holds the injected rows in sorted order (zero elsewhere), and
@@ -423,7 +423,7 @@ struct ScanProblem {
 };
 hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
 
-// dot_out of a problem on its own (same fields), for a caller that wants nothing else of it.
+// dot_out of a problem with dot_sorted on its own (same fields; 4 or 8 columns), for a caller that wants nothing else of it.
 hipError_t launch_sorted_rowdot(const ScanProblem& p, hipStream_t st);
 
 // Phase modulation of the phased kernel (phase_kernels.hip): split a (rows, batch) matrix into its

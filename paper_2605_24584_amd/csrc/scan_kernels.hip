@@ -633,7 +633,7 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 // ---------------------------------------------------------------------------
 // reduce: forward and backward summary of every tile, and the tile's flags
 // ---------------------------------------------------------------------------
-// DOT: the rows' products with the strict scans of another problem are wanted (dot_out).
+// DOT: the rows' products with the strict scans of another problem are wanted (dot_out); lanes of four columns only.
 template <int VEC, bool STRICT, bool DOT, bool RAG>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_reduce(const ScanArgs A)
@@ -2920,17 +2920,27 @@ k_rowdot_narrow(const float* __restrict__ u, int64_t ldu, int64_t op_u, const fl
     }
 }
 
-// out[id - lo] = sum_t u[id - lo, t] * z[j, t] for the sorted rows j whose id lies in [lo, hi): one thread per sorted row
+// out[id - lo] = sum_t u[id - lo, t] * z[j, t] for the sorted rows j whose id lies in [lo, hi), 4 GROUPS columns: one thread per sorted row.
+// Rows of u start anywhere.
+template <int GROUPS>
 __global__ void __launch_bounds__(256)
 k_sorted_rowdot(const uint32_t* __restrict__ ids, int64_t N, uint32_t lo, uint32_t hi, const float* __restrict__ u, int64_t ldu,
-                const float* __restrict__ z, int64_t batch, float* __restrict__ out)
+                const float* __restrict__ z, float* __restrict__ out)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += stride) {
         const uint32_t id = ids[j];
         if (id < lo || id >= hi) continue;
+        v4r x[GROUPS];
+        float4 y[GROUPS];
+#pragma unroll
+        for (int q = 0; q < GROUPS; ++q) {
+            x[q] = *reinterpret_cast<const v4r*>(u + (int64_t)(id - lo) * ldu + 4 * q);
+            y[q] = *reinterpret_cast<const float4*>(z + (j * GROUPS + q) * 4);
+        }
         float s = 0.0f;
-        for (int64_t t = 0; t < batch; ++t) s += u[(int64_t)(id - lo) * ldu + t] * z[j * batch + t];
+#pragma unroll
+        for (int q = 0; q < GROUPS; ++q) { s += x[q][0] * y[q].x; s += x[q][1] * y[q].y; s += x[q][2] * y[q].z; s += x[q][3] * y[q].w; }
         out[id - lo] = s;
     }
 }
@@ -3068,10 +3078,10 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     } else if (!A.stage && (int64_t)rgrid.x * rgrid.y > (A.dot_out ? 2 : 1) * kLoneTilesMin) {      // one wavefront per tile
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, lgrid, dim3(kLoneWaves * 64), 0, st, A)); };
-        if (A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, true, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
+        if (VEC == 4 && A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
     } else {
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, rgrid, bblock, 0, st, A)); };
-        if (A.dot_out) go(k_scan_reduce<VEC, STRICT, true, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);
+        if (VEC == 4 && A.dot_out) go(k_scan_reduce<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);
     }
     launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
@@ -3214,8 +3224,8 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     // The products of rows that several slabs share, or that the wide geometry's reduce reads, are a pass of their own, and so are those of
     // few rows among many: every tile of the reduce would wait for one or two of them (us, backward reduce and row products apart /
     // together: 50000 x 50000, batch 16: 11 + 12 / 14, 20000, batch 64: 11 + 8 / 13, 200000, batch 63: 23 + 35 / 49, 500000, batch 64: 38 + 77 /
-    // 83; 2999 x 100003, batch 33: 12 + 3 / 17).
-    if (p.dot_out && ((!p.dot_sorted && (g.sub_shift || g.slabs > 1)) || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
+    // 83; 2999 x 100003, batch 33: 12 + 3 / 17).  Strict scans in the sorted order: where gy does not allow 16-byte accesses.
+    if (p.dot_out && (p.dot_sorted ? !v4 : g.sub_shift || g.slabs > 1 || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
         const hipError_t e = p.dot_sorted ? launch_sorted_rowdot(p, st)
                                           : launch_rowdot(p.inj, p.ld_inj, p.dot_z, p.batch, (int64_t)p.inj_hi - p.inj_lo, p.batch, p.dot_out, st);
         if (e != hipSuccess) return e;
@@ -3239,8 +3249,13 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
 hipError_t launch_sorted_rowdot(const ScanProblem& p, hipStream_t st)
 {
     int64_t g = (p.N + 255) / 256; if (g > 65536) g = 65536;
-    LAPLEX_TIMED("rowdot", st, hipLaunchKernelGGL(k_sorted_rowdot, dim3((unsigned)g), dim3(256), 0, st, p.ids, p.N, p.inj_lo, p.inj_hi,
-                                                  p.inj, p.ld_inj, p.dot_z, p.batch, p.dot_out));
+    auto go = [&](auto kernel) {
+        LAPLEX_TIMED("rowdot", st, hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(256), 0, st, p.ids, p.N, p.inj_lo, p.inj_hi,
+                                                      p.inj, p.ld_inj, p.dot_z, p.dot_out));
+    };
+    if (p.batch == 4) go(k_sorted_rowdot<1>);
+    else if (p.batch == 8) go(k_sorted_rowdot<2>);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -231,14 +231,30 @@ def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
         assert_close(name, got.cpu().numpy(), rv, tv)
 
 
+@pytest.mark.parametrize("k,n,batch,in_order", [(9000, 9000, 8, True), (3000, 9000, 4, True), (2999, 9001, 4, False), (1000, 100000, 8, False),
+                                                (9000, 9000, 1, False), (9000, 9000, 3, False), (7000, 6000, 7, False)])
+def test_which_strict_scans_wait_in_the_sorted_order(k, n, batch, in_order):
+    """Where they do, the backward's reduce forms ga and no launch for the row products follows."""
+    r = np.random.default_rng(k + n + batch)
+    normal = lambda *shape: dev(r.normal(size=shape).astype(np.float32))
+    a, b, x, g = normal(k), normal(n), normal(n, batch), normal(k, batch)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    B.laplex_apply(a, b, x, torch.empty_like(g), ws, B.LAPLEX_SAVE_SCANS)
+    gx, ga, gb = torch.empty_like(x), torch.empty_like(a), torch.empty_like(b)
+    seen = families(lambda: B.laplex_apply_backward(a, b, x, g, gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN))
+    assert ("rowdot" not in seen) == in_order, seen
+
+
 @pytest.mark.parametrize("saved", [True, False])
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
 @pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0),
-                                           (7000, 6000, 12, 0), (100, 9000, 33, 0), (6000, 5000, 33, 1), (5000, 4000, 64, 0), (140000, 130000, 16, 0)])
+                                           (7000, 6000, 12, 0), (100, 9000, 33, 0), (6000, 5000, 33, 1), (5000, 4000, 64, 0), (140000, 130000, 16, 0),
+                                           (3000, 9000, 8, 0), (2999, 9001, 8, 0), (3000, 9000, 4, 0), (2999, 9001, 4, 1), (6000, 6000, 8, 1), (6000, 6000, 4, 3)])
 def test_where_the_anchor_gradient_of_the_outputs_is_formed(oracle, k, n, batch, pad, wanted, saved):
-    """Outside the small path: up to 8 columns ga comes from strict scans that wait in the sorted order, formed where gy is gathered (or,
-    when nothing else is wanted or the outputs are few, on its own); beyond, from the caller's order, in a workgroup's or a wavefront's
-    reduce.  Beside every subset of the other gradients, with ties and padded rows."""
+    """Outside the small path: with 4 or 8 columns and a quarter of the rows or more outputs, ga comes from strict scans that wait in the
+    sorted order, formed where gy is gathered (or, when nothing else is wanted or gy allows no 16-byte accesses, on its own); otherwise from
+    the caller's order, beyond 8 columns in a workgroup's or a wavefront's reduce.  Beside every subset of the other gradients, with ties and
+    padded rows."""
     from test_gpu_parity import anchors, assert_close
     r = np.random.default_rng(k + 3 * n + batch)
     a, b = anchors("ties", r, k, n)
