@@ -191,7 +191,7 @@ bool use_small(const Layout& L) { return L.N <= kSmallMax && !small_reads_too_mu
 // Do the strict scans Z at the outputs wait for the backward in the sorted order, in the places that the saved inputs leave free there
 // (xs), and is ga formed where gy is gathered?  Then a row of y and a row of Z no longer go to random places each, but rows of Z are read
 // back one by one and ga goes to random places.  4 and 8 columns, where a row is read and written with 128-bit accesses, and outputs that
-// are a quarter of the merged rows or more (us, forward + backward on a kept plan, Z in the caller's order / here: 2^20 x 2^20, batch 8: 304 /
+// are a quarter of the merged rows or more.  Whether the matrices allow that is decided where they are scanned, and noted in the plan (us, forward + backward on a kept plan, Z in the caller's order / here: 2^20 x 2^20, batch 8: 304 /
 // 288, batch 4: 275 / 263; 130000 x 130000, batch 8: 70 / 66; few outputs: 2^18 x 2^20, batch 8: 205 / 219, batch 4: 177 / 183; single
 // columns: 2^20 x 2^20, batch 1: 148 / 156, 3: 207 / 230, 5: 288 / 343, 7: 329 / 370; 20000 x 20000, batch 3: 45 / 49).
 bool strict_in_order(const Layout& L)
@@ -724,7 +724,7 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
         p.out_p = nullptr; p.out_z = nullptr;
         return scan_and_send_home(p, L, w, true, save, y, ldy, save ? P.z : nullptr, 1, st);
     }
-    if (p.out_z && strict_in_order(L)) { p.out_z = P.xs; p.z_sorted = true; }
+    if (p.out_z && strict_in_order(L)) p.z_in_order = P.xs;
     float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
     const bool paired = batch == 1 && p.out_z != nullptr;      // y and the saved scan of a row as one 8-byte slot
     if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_z = pairs + 1; p.ld_z = 2; }
@@ -806,7 +806,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
                 p.out_z = nullptr;
                 LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, P.z, 1, nullptr, 1, st));
             } else {
-                if (in_order) { p.out_z = P.xs; p.z_sorted = true; }
+                if (in_order) p.z_in_order = P.xs;
                 LAPLEX_HIP(launch_scan(p, L, w, st));
             }
         }
@@ -829,8 +829,8 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     } else if (in_order && ga && !gx && !gb) {
         ScanProblem p = problem(P, L);
         p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)k;
-        p.dot_z = P.xs; p.dot_out = ga;
-        LAPLEX_HIP(launch_sorted_rowdot(p, st));
+        p.dot_z = P.z; p.dot_in_order = P.xs; p.dot_out = ga;
+        LAPLEX_HIP(launch_sorted_rowdot(p, L, w, st));
     } else if (gx || gb) {
         ScanProblem p = problem(P, L);
         p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)k;
@@ -842,7 +842,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }
         p.stage = P.stage;
         p.wstage = (gb && have_xs) ? P.xs : nullptr;
-        if (ga && !apart) { p.dot_z = in_order ? P.xs : P.z; p.dot_out = ga; p.dot_sorted = in_order; }
+        if (ga && !apart) { p.dot_z = P.z; p.dot_out = ga; p.dot_in_order = in_order ? P.xs : nullptr; }
         p.tag = "bwd";
         p.phase = fuse;           // phased backward: the streaming downsweep merges the two halves (see phase_fusable)
         p.phase_in = pin_bwd;     // ... and the other downsweeps' blocks get their doubled weight rows

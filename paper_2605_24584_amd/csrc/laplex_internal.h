@@ -32,6 +32,7 @@ constexpr int kSortSmallWords = 1088;
 constexpr int kScanCounters = 3;
 constexpr int kNonFiniteWord = 2;
 constexpr int kPlanIndexWord = 33;                      // nonzero: what the common launches of a sum of operators add to the plan is there (kMixIndexed + operators)
+constexpr int kStrictOrderWord = 34;                    // nonzero: the saved strict scans lie in the sorted order (ScanProblem::z_in_order)
 constexpr int kPlanStatusWord = 32;                     // in the plan's 64 counter words: the sort's error flag, kept with the plan
 constexpr int kMergeThreads = 256;
 constexpr int kMergePerThread = 8;
@@ -404,12 +405,14 @@ struct ScanProblem {
     int64_t batch;
     float* stage;          // narrow batches: the reduce writes the injected rows here in sorted order, the downsweep reads them back
     const float* wstage;   // narrow batches: the weights w in sorted order (an earlier problem's stage), or null
-    // 4 or 8 columns, injected and result rows apart: the strict scans Z of the result rows go to their places in the sorted order,
-    // out_z[sorted row * batch + t], which may be `stage` itself (an injected row and a result row never share one) ...
-    bool z_sorted = false;
-    // ... and the reduce of the problem that injects those rows forms dot_out[id - inj_lo] = sum_t inj_row[t] * dot_z[sorted row * batch + t]
-    // (dot_sorted; else the rows of dot_z are in the caller's order, dot_z[(id - inj_lo) * batch + t], from 9 columns on)
-    const float* dot_z = nullptr; float* dot_out = nullptr; bool dot_sorted = false;
+    // 4 or 8 columns, injected and result rows apart: where the matrices allow 16-byte accesses, the strict scans Z of the result rows go to
+    // their places in the sorted order instead of out_z, z_in_order[sorted row * batch + t], which may be `stage` itself (an injected row
+    // and a result row never share one); the plan's word kStrictOrderWord says where they are ...
+    float* z_in_order = nullptr;
+    // ... and the reduce of the problem that injects those rows forms dot_out[id - inj_lo] = sum_t inj_row[t] * Z row[t], the row being
+    // dot_z[(id - inj_lo) * batch + t], or if dot_in_order is not null and that word is set dot_in_order[sorted row * batch + t]
+    // (without dot_in_order from 9 columns on)
+    const float* dot_z = nullptr; float* dot_out = nullptr; const float* dot_in_order = nullptr;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
     // batch 1, routes without random accesses: `stage` already holds the injected rows in sorted order (zero elsewhere), and
     // the outputs of result row j of the sorted sequence go to out_p[j * ld_p], out_z[j * ld_z], out_red[j * ld_red]
@@ -423,8 +426,8 @@ struct ScanProblem {
 };
 hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
 
-// dot_out of a problem with dot_sorted on its own (same fields; 4 or 8 columns), for a caller that wants nothing else of it.
-hipError_t launch_sorted_rowdot(const ScanProblem& p, hipStream_t st);
+// dot_out of a problem with dot_in_order on its own (same fields; 4 or 8 columns), for a caller that wants nothing else of it.
+hipError_t launch_sorted_rowdot(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
 
 // Phase modulation of the phased kernel (phase_kernels.hip): split a (rows, batch) matrix into its
 // cosine and sine halves, dst (rows, 2*batch) contiguous; merge two halves back and, if wanted, form

@@ -85,8 +85,9 @@ struct ScanArgs {
     int inj_sorted;               // batch 1: `stage` already holds the injected rows in sorted order: nothing is gathered
     int out_sorted;               // batch 1: outputs are indexed by the sorted row, not by the id (a later pass takes them home)
     PartEmit emit;                // batch 1, sorted order: the results leave as records of a partition level (k_seq_down)
-    int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_sorted)
-    const float* dot_z; float* dot_out; int dot_sorted;      // row products of the reduce (ScanProblem)
+    int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_in_order)
+    int z_word;                   // 1 + the plan's word that says so, or 0: left alone
+    const float* dot_z; float* dot_out; const float* dot_in_order;      // row products of the reduce (ScanProblem)
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
@@ -606,6 +607,8 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+    const bool in_order = A.dot_in_order && A.counters[kStrictOrderWord];      // uniform
+    const float* const zrows = in_order ? A.dot_in_order : A.dot_z;
     float dot[ITEMS];
     uint32_t rows[ITEMS];
 #pragma unroll
@@ -615,8 +618,8 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 #pragma unroll
         for (int i = i0; i < i0 + 4; ++i) {
             const bool in = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi;
-            const int64_t at = A.dot_sorted ? row0 + i : (int64_t)(T.id[i] - A.inj_lo);
-            load_row_or_zero<VEC, false, RAG>(z[i - i0], A.dot_z, at * A.batch + col0, col_ok && in, end);
+            const int64_t at = in_order ? row0 + i : (int64_t)(T.id[i] - A.inj_lo);
+            load_row_or_zero<VEC, false, RAG>(z[i - i0], zrows, at * A.batch + col0, col_ok && in, end);
         }
 #pragma unroll
         for (int i = i0; i < i0 + 4; ++i) {
@@ -651,6 +654,7 @@ k_scan_reduce(const ScanArgs A)
     const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
     const bool col_ok = col0 < A.batch;
     if (tid == 0) tile_flags = 0;
+    if (A.z_word && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) A.counters[kStrictOrderWord] = (uint32_t)A.z_word - 1u;
 
     // decays over this row-lane's rows, this wavefront's rows and the whole tile, from the anchors
     // (not products of the rows' decays: see k_decay); asked for first so the loads go out early
@@ -2920,16 +2924,18 @@ k_rowdot_narrow(const float* __restrict__ u, int64_t ldu, int64_t op_u, const fl
     }
 }
 
-// out[id - lo] = sum_t u[id - lo, t] * z[j, t] for the sorted rows j whose id lies in [lo, hi), 4 GROUPS columns: one thread per sorted row.
-// Rows of u start anywhere.
+// out[r] = sum_t u[r, t] * z[r, t], 4 GROUPS columns, one thread per row; or, if the strict scans lie in the sorted order (the plan's word),
+// out[id - lo] = sum_t u[id - lo, t] * zs[j, t] for the sorted rows j whose id lies in [lo, hi).  Rows of u start anywhere.
 template <int GROUPS>
 __global__ void __launch_bounds__(256)
 k_sorted_rowdot(const uint32_t* __restrict__ ids, int64_t N, uint32_t lo, uint32_t hi, const float* __restrict__ u, int64_t ldu,
-                const float* __restrict__ z, float* __restrict__ out)
+                const float* __restrict__ z, const float* __restrict__ zs, const uint32_t* __restrict__ counters, float* __restrict__ out)
 {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < N; j += stride) {
-        const uint32_t id = ids[j];
+    const bool in_order = counters[kStrictOrderWord] != 0u;      // uniform
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, rows = in_order ? N : (int64_t)(hi - lo);
+    if (in_order) z = zs;
+    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < rows; j += stride) {
+        const uint32_t id = in_order ? ids[j] : lo + (uint32_t)j;
         if (id < lo || id >= hi) continue;
         v4r x[GROUPS];
         float4 y[GROUPS];
@@ -3150,6 +3156,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     // want whole groups, and the batch is not staged.
     const bool rag = !v4 && p.batch > kStageMaxBatch && p.batch <= 128 && !p.phase && !p.phase_in;
     const ScanGeom g = scan_geom(p.N, p.batch, v4 || rag ? 4 : 1, p.inj_sorted && p.out_sorted);
+    const bool z_sorted = p.z_in_order && v4;
 
     ScanArgs A;
     A.ids = p.ids; A.dh = p.dh; A.pk = p.pk; A.pk8 = p.pk8; A.N = p.N;
@@ -3161,7 +3168,9 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.inj_sorted = p.inj_sorted ? 1 : 0; A.out_sorted = p.out_sorted ? 1 : 0;
     if (p.emit) A.emit = *p.emit;
     A.emit_first = p.emit_first ? 1 : 0;
-    A.z_sorted = p.z_sorted ? 1 : 0; A.dot_z = p.dot_z; A.dot_out = p.dot_out; A.dot_sorted = p.dot_sorted ? 1 : 0;
+    A.z_sorted = z_sorted ? 1 : 0; A.z_word = p.z_in_order ? 1 + A.z_sorted : 0;
+    if (z_sorted) A.out_z = p.z_in_order;
+    A.dot_z = p.dot_z; A.dot_out = p.dot_out; A.dot_in_order = p.dot_in_order;
     A.ph = PhaseFuse{};
     if (p.phase) {
         // one wavefront must span a whole half-row: wide geometry, at most 256 columns per half, two slabs at most
@@ -3224,9 +3233,10 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     // The products of rows that several slabs share, or that the wide geometry's reduce reads, are a pass of their own, and so are those of
     // few rows among many: every tile of the reduce would wait for one or two of them (us, backward reduce and row products apart /
     // together: 50000 x 50000, batch 16: 11 + 12 / 14, 20000, batch 64: 11 + 8 / 13, 200000, batch 63: 23 + 35 / 49, 500000, batch 64: 38 + 77 /
-    // 83; 2999 x 100003, batch 33: 12 + 3 / 17).  Strict scans in the sorted order: where gy does not allow 16-byte accesses.
-    if (p.dot_out && (p.dot_sorted ? !v4 : g.sub_shift || g.slabs > 1 || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
-        const hipError_t e = p.dot_sorted ? launch_sorted_rowdot(p, st)
+    // 83; 2999 x 100003, batch 33: 12 + 3 / 17).  Strict scans that may lie in the sorted order: where gy does not
+    // allow 16-byte accesses.
+    if (p.dot_out && (p.dot_in_order ? !v4 : g.sub_shift || g.slabs > 1 || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
+        const hipError_t e = p.dot_in_order ? launch_sorted_rowdot(p, L, ws, st)
                                           : launch_rowdot(p.inj, p.ld_inj, p.dot_z, p.batch, (int64_t)p.inj_hi - p.inj_lo, p.batch, p.dot_out, st);
         if (e != hipSuccess) return e;
         A.dot_out = nullptr;
@@ -3246,12 +3256,13 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_sorted_rowdot(const ScanProblem& p, hipStream_t st)
+hipError_t launch_sorted_rowdot(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st)
 {
+    const uint32_t* const counters = reinterpret_cast<const uint32_t*>(ws + L.off_counters);
     int64_t g = (p.N + 255) / 256; if (g > 65536) g = 65536;
     auto go = [&](auto kernel) {
         LAPLEX_TIMED("rowdot", st, hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(256), 0, st, p.ids, p.N, p.inj_lo, p.inj_hi,
-                                                      p.inj, p.ld_inj, p.dot_z, p.dot_out));
+                                                      p.inj, p.ld_inj, p.dot_z, p.dot_in_order, counters, p.dot_out));
     };
     if (p.batch == 4) go(k_sorted_rowdot<1>);
     else if (p.batch == 8) go(k_sorted_rowdot<2>);

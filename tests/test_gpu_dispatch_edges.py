@@ -245,6 +245,39 @@ def test_which_strict_scans_wait_in_the_sorted_order(k, n, batch, in_order):
     assert ("rowdot" not in seen) == in_order, seen
 
 
+@pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga", "gb")])
+@pytest.mark.parametrize("pads", [(0, 0, 1), (1, 1, 0), (0, 1, 1), (1, 0, 0), (1, 1, 1)])
+@pytest.mark.parametrize("k,n,batch", [(9000, 9000, 8), (5000, 15000, 4), (9000, 20, 8)])
+def test_strict_scans_of_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pads, wanted):
+    """x, y and gy each with rows on 16-byte boundaries or not: the order that the forward kept its strict scans in is the one the backward reads."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + n + batch)
+    a, b = anchors("ties", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    padded = lambda v, pad: dev(np.pad(v, ((0, 0), (0, pad))))[:, :batch]
+    da, db, dx, dy, dg = dev(a), dev(b), padded(x, pads[0]), padded(np.zeros_like(g), pads[1]), padded(g, pads[2])
+    out = {"gx": torch.empty(n, batch, device="cuda"), "ga": torch.empty(k, device="cuda"), "gb": torch.empty(n, device="cuda")}
+    pick = lambda: (out[v] if v in wanted else None for v in ("gx", "ga", "gb"))
+    ws = torch.full((B.laplex_workspace_bytes(k, n, batch),), 255, dtype=torch.uint8, device="cuda")      # NaN wherever nothing is written
+
+    def check():
+        torch.cuda.synchronize()
+        for name, ref, tol in zip(("gx", "ga", "gb"), want, tols):
+            if name in wanted:
+                assert_close(name, out[name].cpu().numpy(), ref, tol)
+                out[name].fill_(float("nan"))
+
+    B.laplex_apply(da, db, dx, dy, ws, B.LAPLEX_SAVE_SCANS)
+    B.laplex_apply_backward(da, db, dx, dg, *pick(), ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    check()
+    B.laplex_apply_backward(da, db, dev(x), dg, *pick(), ws, B.LAPLEX_REUSE_PLAN)      # the strict scans once more, of rows that allow it
+    check()
+    B.laplex_apply(da, db, dx, dy, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    B.laplex_apply_backward(da, db, dx, dg, *pick(), ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    check()
+
+
 @pytest.mark.parametrize("saved", [True, False])
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga"), ("ga", "gb"), ("gx", "ga", "gb")])
 @pytest.mark.parametrize("k,n,batch,pad", [(9000, 3, 8, 0), (5, 9000, 1, 0), (7000, 6000, 3, 2), (6001, 5002, 7, 0), (4097, 8000, 4, 1), (9000, 9000, 2, 0),
