@@ -194,8 +194,11 @@ bool use_small(const Layout& L) { return L.N <= kSmallMax && !small_reads_too_mu
 // are a quarter of the merged rows or more.  Whether the matrices allow that is decided where they are scanned, and noted in the plan (us, forward + backward on a kept plan, Z in the caller's order / here: 2^20 x 2^20, batch 8: 304 /
 // 288, batch 4: 275 / 263; 130000 x 130000, batch 8: 70 / 66; few outputs: 2^18 x 2^20, batch 8: 205 / 219, batch 4: 177 / 183; single
 // columns: 2^20 x 2^20, batch 1: 148 / 156, 3: 207 / 230, 5: 288 / 343, 7: 329 / 370; 20000 x 20000, batch 3: 45 / 49).
+// A single column up to 2^19 rows, whose places fit the caches: two launches fewer (20000 x 20000: 53.6 / 51.9, 200000 x 200000: 66.3 / 64.0).
+constexpr int64_t kColumnInOrderMax = int64_t(1) << 19;
 bool strict_in_order(const Layout& L)
 {
+    if (L.batch == 1) return L.N > kSmallMax && L.N <= kColumnInOrderMax && L.zrows < L.N && !use_permute(L);
     return (L.batch == 4 || L.batch == 8) && L.N > kSmallMax && L.zrows < L.N && 4 * L.zrows >= L.N;
 }
 
@@ -726,7 +729,7 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
     }
     if (p.out_z && strict_in_order(L)) p.z_in_order = P.xs;
     float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
-    const bool paired = batch == 1 && p.out_z != nullptr;      // y and the saved scan of a row as one 8-byte slot
+    const bool paired = batch == 1 && p.out_z && !p.z_in_order;      // y and the saved scan of a row as one 8-byte slot
     if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_z = pairs + 1; p.ld_z = 2; }
     LAPLEX_HIP(launch_scan(p, L, w, st));
     if (paired) LAPLEX_HIP(launch_unpair(pairs, k, y, ldy, P.z, st));

@@ -405,12 +405,12 @@ struct ScanProblem {
     int64_t batch;
     float* stage;          // narrow batches: the reduce writes the injected rows here in sorted order, the downsweep reads them back
     const float* wstage;   // narrow batches: the weights w in sorted order (an earlier problem's stage), or null
-    // 4 or 8 columns, injected and result rows apart: where the matrices allow 16-byte accesses, the strict scans Z of the result rows go to
+    // 1, 4 or 8 columns, injected and result rows apart: where the matrices allow 16-byte accesses, the strict scans Z of the result rows go to
     // their places in the sorted order instead of out_z, z_in_order[sorted row * batch + t], which may be `stage` itself (an injected row
-    // and a result row never share one); the plan's word kStrictOrderWord says where they are ...
+    // and a result row never share one); the plan's word kStrictOrderWord says where they are (a single column: always there) ...
     float* z_in_order = nullptr;
     // ... and the reduce of the problem that injects those rows forms dot_out[id - inj_lo] = sum_t inj_row[t] * Z row[t], the row being
-    // dot_z[(id - inj_lo) * batch + t], or if dot_in_order is not null and that word is set dot_in_order[sorted row * batch + t]
+    // dot_z[(id - inj_lo) * batch + t], or if dot_in_order is not null and they are there dot_in_order[sorted row * batch + t]
     // (without dot_in_order from 9 columns on)
     const float* dot_z = nullptr; float* dot_out = nullptr; const float* dot_in_order = nullptr;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
@@ -426,7 +426,7 @@ struct ScanProblem {
 };
 hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
 
-// dot_out of a problem with dot_in_order on its own (same fields; 4 or 8 columns), for a caller that wants nothing else of it.
+// dot_out of a problem with dot_in_order on its own (same fields; 1, 4 or 8 columns), for a caller that wants nothing else of it.
 hipError_t launch_sorted_rowdot(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st);
 
 // Phase modulation of the phased kernel (phase_kernels.hip): split a (rows, batch) matrix into its

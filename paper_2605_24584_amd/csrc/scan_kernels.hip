@@ -603,11 +603,10 @@ __device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&ro
 // dot_out of a row-lane's injected rows (one slab).
 template <int VEC, bool RAG>
 __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<VEC>& T, int64_t row0, int64_t col0, bool col_ok, int bv, int c,
-                                             float (*v)[VEC])
+                                             float (*v)[VEC], bool in_order)
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
-    const bool in_order = A.dot_in_order && A.counters[kStrictOrderWord];      // uniform
     const float* const zrows = in_order ? A.dot_in_order : A.dot_z;
     float dot[ITEMS];
     uint32_t rows[ITEMS];
@@ -636,7 +635,7 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 // ---------------------------------------------------------------------------
 // reduce: forward and backward summary of every tile, and the tile's flags
 // ---------------------------------------------------------------------------
-// DOT: the rows' products with the strict scans of another problem are wanted (dot_out); lanes of four columns only.
+// DOT: the rows' products with the strict scans of another problem are wanted (dot_out).
 template <int VEC, bool STRICT, bool DOT, bool RAG>
 __global__ void __launch_bounds__(kScanThreads)
 k_scan_reduce(const ScanArgs A)
@@ -660,6 +659,7 @@ k_scan_reduce(const ScanArgs A)
     // (not products of the rows' decays: see k_decay); asked for first so the loads go out early
     const float tile_df = span_decay_f(A, tile * A.tile_rows, A.tile_rows);
     const float tile_db = span_decay_b(A, tile * A.tile_rows, A.tile_rows);
+    const uint32_t z_in_order = !DOT || !A.dot_in_order ? 0u : A.batch == 1 ? 1u : A.counters[kStrictOrderWord];
 
     TileRows<VEC> T;
     load_meta<VEC>(A, row0, T);
@@ -689,7 +689,7 @@ k_scan_reduce(const ScanArgs A)
             if (T.id[i] != 0xFFFFFFFFu) store_vec<VEC>(A.stage + (row0 + i) * A.batch + col0, v[i]);
     }
 
-    if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v);
+    if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v, z_in_order != 0u);
 
     // The tile's summary as a weighted sum of the row-lanes' own (each from zero over its ITEMS rows): a row-lane's forward
     // state reaches the tile's last row through ONE exponential of an anchor difference, its backward state the tile's first
@@ -1079,7 +1079,7 @@ k_scan_reduce_wave(const ScanArgs A)
         float v[ITEMS][VEC];
         if (__ballot(here & kFlagInj)) {                     // uniform: rows are read only where something is injected
             load_injected<VEC, kStreamRows<VEC>, RAG>(A, T, col0, col_ok, v);
-            if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v);
+            if constexpr (DOT) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v, false);
         } else {
 #pragma unroll
             for (int i = 0; i < ITEMS; ++i)
@@ -2924,21 +2924,26 @@ k_rowdot_narrow(const float* __restrict__ u, int64_t ldu, int64_t op_u, const fl
     }
 }
 
-// out[r] = sum_t u[r, t] * z[r, t], 4 GROUPS columns, one thread per row; or, if the strict scans lie in the sorted order (the plan's word),
-// out[id - lo] = sum_t u[id - lo, t] * zs[j, t] for the sorted rows j whose id lies in [lo, hi).  Rows of u start anywhere.
+// out[r] = sum_t u[r, t] * z[r, t], 4 GROUPS columns, one thread per row; or, if the strict scans lie in the sorted order (the plan's word;
+// GROUPS = 0, a single column: always), out[id - lo] = sum_t u[id - lo, t] * zs[j, t] for the sorted rows j whose id lies in [lo, hi).  Rows
+// of u start anywhere.
 template <int GROUPS>
 __global__ void __launch_bounds__(256)
 k_sorted_rowdot(const uint32_t* __restrict__ ids, int64_t N, uint32_t lo, uint32_t hi, const float* __restrict__ u, int64_t ldu,
                 const float* __restrict__ z, const float* __restrict__ zs, const uint32_t* __restrict__ counters, float* __restrict__ out)
 {
-    const bool in_order = counters[kStrictOrderWord] != 0u;      // uniform
+    const bool in_order = GROUPS == 0 || counters[kStrictOrderWord] != 0u;      // uniform
     const int64_t stride = (int64_t)gridDim.x * blockDim.x, rows = in_order ? N : (int64_t)(hi - lo);
     if (in_order) z = zs;
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < rows; j += stride) {
         const uint32_t id = in_order ? ids[j] : lo + (uint32_t)j;
         if (id < lo || id >= hi) continue;
-        v4r x[GROUPS];
-        float4 y[GROUPS];
+        if constexpr (GROUPS == 0) {
+            out[id - lo] = u[(int64_t)(id - lo) * ldu] * z[j];
+            continue;
+        }
+        v4r x[GROUPS ? GROUPS : 1];
+        float4 y[GROUPS ? GROUPS : 1];
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) {
             x[q] = *reinterpret_cast<const v4r*>(u + (int64_t)(id - lo) * ldu + 4 * q);
@@ -3087,7 +3092,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         if (VEC == 4 && A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
     } else {
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, rgrid, bblock, 0, st, A)); };
-        if (VEC == 4 && A.dot_out) go(k_scan_reduce<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);
+        if (A.dot_out) go(k_scan_reduce<VEC, STRICT, true, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);
     }
     launch_spine<VEC, STRICT>(A, g, fs.c_str(), st);
     if (VEC == 4 && g.sub_shift && A.pin.half && A.pin.split_blocks) {     // phased: the doubled rows the downsweeps will read
@@ -3156,7 +3161,8 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     // want whole groups, and the batch is not staged.
     const bool rag = !v4 && p.batch > kStageMaxBatch && p.batch <= 128 && !p.phase && !p.phase_in;
     const ScanGeom g = scan_geom(p.N, p.batch, v4 || rag ? 4 : 1, p.inj_sorted && p.out_sorted);
-    const bool z_sorted = p.z_in_order && v4;
+    const bool whole_rows = v4 || p.batch == 1;         // a row is one access, or a few of 16 bytes
+    const bool z_sorted = p.z_in_order && whole_rows;
 
     ScanArgs A;
     A.ids = p.ids; A.dh = p.dh; A.pk = p.pk; A.pk8 = p.pk8; A.N = p.N;
@@ -3168,7 +3174,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.inj_sorted = p.inj_sorted ? 1 : 0; A.out_sorted = p.out_sorted ? 1 : 0;
     if (p.emit) A.emit = *p.emit;
     A.emit_first = p.emit_first ? 1 : 0;
-    A.z_sorted = z_sorted ? 1 : 0; A.z_word = p.z_in_order ? 1 + A.z_sorted : 0;
+    A.z_sorted = z_sorted ? 1 : 0; A.z_word = p.z_in_order && p.batch > 1 ? 1 + A.z_sorted : 0;      // (a single column: always in order)
     if (z_sorted) A.out_z = p.z_in_order;
     A.dot_z = p.dot_z; A.dot_out = p.dot_out; A.dot_in_order = p.dot_in_order;
     A.ph = PhaseFuse{};
@@ -3234,8 +3240,8 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     // few rows among many: every tile of the reduce would wait for one or two of them (us, backward reduce and row products apart /
     // together: 50000 x 50000, batch 16: 11 + 12 / 14, 20000, batch 64: 11 + 8 / 13, 200000, batch 63: 23 + 35 / 49, 500000, batch 64: 38 + 77 /
     // 83; 2999 x 100003, batch 33: 12 + 3 / 17).  Strict scans that may lie in the sorted order: where gy does not
-    // allow 16-byte accesses.
-    if (p.dot_out && (p.dot_in_order ? !v4 : g.sub_shift || g.slabs > 1 || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
+    // allow 16-byte accesses, too.
+    if (p.dot_out && ((p.dot_in_order ? !whole_rows : g.sub_shift || g.slabs > 1) || ((int64_t)p.inj_hi - p.inj_lo) * 4 < p.N)) {
         const hipError_t e = p.dot_in_order ? launch_sorted_rowdot(p, L, ws, st)
                                           : launch_rowdot(p.inj, p.ld_inj, p.dot_z, p.batch, (int64_t)p.inj_hi - p.inj_lo, p.batch, p.dot_out, st);
         if (e != hipSuccess) return e;
@@ -3264,7 +3270,8 @@ hipError_t launch_sorted_rowdot(const ScanProblem& p, const Layout& L, char* ws,
         LAPLEX_TIMED("rowdot", st, hipLaunchKernelGGL(kernel, dim3((unsigned)g), dim3(256), 0, st, p.ids, p.N, p.inj_lo, p.inj_hi,
                                                       p.inj, p.ld_inj, p.dot_z, p.dot_in_order, counters, p.dot_out));
     };
-    if (p.batch == 4) go(k_sorted_rowdot<1>);
+    if (p.batch == 1) go(k_sorted_rowdot<0>);
+    else if (p.batch == 4) go(k_sorted_rowdot<1>);
     else if (p.batch == 8) go(k_sorted_rowdot<2>);
     else return hipErrorInvalidValue;
     return hipGetLastError();

@@ -232,7 +232,7 @@ def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
 
 
 @pytest.mark.parametrize("k,n,batch,in_order", [(9000, 9000, 8, True), (3000, 9000, 4, True), (2999, 9001, 4, False), (1000, 100000, 8, False),
-                                                (9000, 9000, 1, False), (9000, 9000, 3, False), (7000, 6000, 7, False)])
+                                                (9000, 9000, 1, True), (1 << 18, 1 << 18, 1, True), (1 << 18, (1 << 18) + 1, 1, False), (9000, 9000, 3, False), (7000, 6000, 7, False)])
 def test_which_strict_scans_wait_in_the_sorted_order(k, n, batch, in_order):
     """Where they do, the backward's reduce forms ga and no launch for the row products follows."""
     r = np.random.default_rng(k + n + batch)
@@ -247,7 +247,7 @@ def test_which_strict_scans_wait_in_the_sorted_order(k, n, batch, in_order):
 
 @pytest.mark.parametrize("wanted", [("ga",), ("gx", "ga", "gb")])
 @pytest.mark.parametrize("pads", [(0, 0, 1), (1, 1, 0), (0, 1, 1), (1, 0, 0), (1, 1, 1)])
-@pytest.mark.parametrize("k,n,batch", [(9000, 9000, 8), (5000, 15000, 4), (9000, 20, 8)])
+@pytest.mark.parametrize("k,n,batch", [(9000, 9000, 8), (5000, 15000, 4), (9000, 20, 8), (9000, 9000, 1), (100, 9000, 1)])
 def test_strict_scans_of_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pads, wanted):
     """x, y and gy each with rows on 16-byte boundaries or not: the order that the forward kept its strict scans in is the one the backward reads."""
     from test_gpu_parity import anchors, assert_close
