@@ -607,7 +607,6 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
-    const float* const zrows = in_order ? A.dot_in_order : A.dot_z;
     float dot[ITEMS];
     uint32_t rows[ITEMS];
 #pragma unroll
@@ -617,8 +616,10 @@ __device__ __forceinline__ void row_products(const ScanArgs& A, const TileRows<V
 #pragma unroll
         for (int i = i0; i < i0 + 4; ++i) {
             const bool in = T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi;
-            const int64_t at = in_order ? row0 + i : (int64_t)(T.id[i] - A.inj_lo);
-            load_row_or_zero<VEC, false, RAG>(z[i - i0], zrows, at * A.batch + col0, col_ok && in, end);
+            if (in_order)      // uniform
+                load_row_or_zero<VEC, false, RAG>(z[i - i0], A.dot_in_order, (row0 + i) * A.batch + col0, col_ok && in, end);
+            else
+                load_row_or_zero<VEC, false, RAG>(z[i - i0], A.dot_z, (int64_t)(T.id[i] - A.inj_lo) * A.batch + col0, col_ok && in, end);
         }
 #pragma unroll
         for (int i = i0; i < i0 + 4; ++i) {
@@ -653,7 +654,6 @@ k_scan_reduce(const ScanArgs A)
     const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
     const bool col_ok = col0 < A.batch;
     if (tid == 0) tile_flags = 0;
-    if (A.z_word && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) A.counters[kStrictOrderWord] = (uint32_t)A.z_word - 1u;
 
     // decays over this row-lane's rows, this wavefront's rows and the whole tile, from the anchors
     // (not products of the rows' decays: see k_decay); asked for first so the loads go out early
@@ -763,6 +763,7 @@ k_scan_reduce(const ScanArgs A)
         const bool vec_ok = col_ok && (tile_flags & kFlagInj);
         store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, tf, (float)tile_flags, A.counters);
         store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, tb, (float)tile_flags, A.counters);
+        if (A.z_word && blockIdx.x == 0 && sw) A.counters[kStrictOrderWord] = (uint32_t)A.z_word - 1u;
     }
 }
 
