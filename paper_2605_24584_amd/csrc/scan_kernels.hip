@@ -86,7 +86,6 @@ struct ScanArgs {
     int out_sorted;               // batch 1: outputs are indexed by the sorted row, not by the id (a later pass takes them home)
     PartEmit emit;                // batch 1, sorted order: the results leave as records of a partition level (k_seq_down)
     int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_in_order)
-    int z_word;                   // 1 + the plan's word that says so, or 0: left alone
     const float* dot_z; float* dot_out; const float* dot_in_order;      // row products of the reduce (ScanProblem)
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
@@ -763,7 +762,8 @@ k_scan_reduce(const ScanArgs A)
         const bool vec_ok = col_ok && (tile_flags & kFlagInj);
         store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, tf, (float)tile_flags, A.counters);
         store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, tb, (float)tile_flags, A.counters);
-        if (A.z_word && blockIdx.x == 0 && sw) A.counters[kStrictOrderWord] = (uint32_t)A.z_word - 1u;
+        if constexpr (VEC == 4)      // (single columns: half a microsecond, their scalar registers are all taken; launch_scan clears the word)
+            if (blockIdx.x == 0 && sw && A.z_sorted) A.counters[kStrictOrderWord] = 1u;
     }
 }
 
@@ -3175,7 +3175,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.inj_sorted = p.inj_sorted ? 1 : 0; A.out_sorted = p.out_sorted ? 1 : 0;
     if (p.emit) A.emit = *p.emit;
     A.emit_first = p.emit_first ? 1 : 0;
-    A.z_sorted = z_sorted ? 1 : 0; A.z_word = p.z_in_order && p.batch > 1 ? 1 + A.z_sorted : 0;      // (a single column: always in order)
+    A.z_sorted = z_sorted ? 1 : 0;
     if (z_sorted) A.out_z = p.z_in_order;
     A.dot_z = p.dot_z; A.dot_out = p.dot_out; A.dot_in_order = p.dot_in_order;
     A.ph = PhaseFuse{};
@@ -3247,6 +3247,11 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
                                           : launch_rowdot(p.inj, p.ld_inj, p.dot_z, p.batch, (int64_t)p.inj_hi - p.inj_lo, p.batch, p.dot_out, st);
         if (e != hipSuccess) return e;
         A.dot_out = nullptr;
+    }
+
+    if (p.z_in_order && !z_sorted) {      // the plan says where the strict scans lie (the reduce sets the word)
+        const hipError_t e = launch_fill(reinterpret_cast<float*>(A.counters + kStrictOrderWord), 1, 1, 1, 0.0f, st);
+        if (e != hipSuccess) return e;
     }
 
     const std::string tag = p.tag ? p.tag : "scan";
