@@ -115,6 +115,28 @@ def test_sample_sort_order(N, kind):
     assert np.array_equal(ids, np.argsort(v, kind="stable"))
 
 
+@pytest.mark.parametrize("kind", ["few", "half", "equal", "nan"])
+@pytest.mark.parametrize("N", [100003, 1 << 20, (1 << 21) + 5, 1 << 22])
+def test_sample_sort_bounds_of_one_key(N, kind):
+    """More anchors of a value than a stretch holds: many bounds share their key, at the first bound, in the middle and at the last one
+    (`nan`: the largest key of all)."""
+    r = np.random.default_rng(N)
+    if kind == "few":
+        v = r.integers(0, 31, N) * 0.25
+    elif kind == "half":
+        v = np.where(r.random(N) < 0.5, 3.0, r.uniform(0, N / 64, N))
+    elif kind == "equal":
+        v = np.full(N, -1.5)
+    else:
+        v = r.uniform(0, N / 64, N)
+        v[r.random(N) < 0.25] = np.nan
+    v = v.astype(np.float32)
+    if kind == "nan":
+        v.view(np.uint32)[np.isnan(v)] = 0x7FFFFFFF      # one payload: the key orders payloads, numpy does not
+    ids, _ = sorted_ids(v[:777], v[777:])
+    assert np.array_equal(ids, np.argsort(v, kind="stable"))
+
+
 @pytest.mark.parametrize("ties", [False, True])
 @pytest.mark.parametrize("N,samples", [(9000, 9 * 16), (200000, 98 * 16), (600000, 256 * 16)])
 def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
