@@ -283,9 +283,90 @@ k_split_tiles(const SplitArgs A)
         if (i * THREADS + tid < len) out[i * THREADS + tid] = laid[i * THREADS + tid];
 }
 
-// A stretch beyond the capacity (the samples bound its length only with overwhelming probability): the workgroup sorts it in memory,
-// by the 8-bit digits of (key, id) from the lowest up, stably; digits that do not vary are passed over.  from: cnt pairs; to_id, to_pk:
-// the stretch's place in the plan.  Leaves the pairs in from.
+// Where (key, id) lies in the range of a stretch, as 64 bits from the top: (key - smallest key, id - smallest id) without the low bits that
+// no key differs in.
+struct StretchRange {
+    uint32_t kmin, imin;
+    int low_zeros, id_bits, up;
+    __device__ __forceinline__ StretchRange(uint32_t kmin_, uint32_t kmax, uint32_t imin_, uint32_t imax, uint32_t vary)
+        : kmin(kmin_), imin(imin_), low_zeros(vary ? __ffs((int)vary) - 1 : 0)
+    {
+        const uint32_t span = (kmax - kmin_) >> low_zeros, ispan = imax - imin_;
+        id_bits = ispan ? 32 - __clz((int)ispan) : 0;
+        const int bits = (span ? 32 - __clz((int)span) : 0) + id_bits;
+        up = bits > 0 ? 64 - bits : 0;
+    }
+    // The fraction times bins: the bin in the upper word, the fraction inside the bin below.
+    __device__ __forceinline__ unsigned long long place(uint32_t key, uint32_t id, uint32_t bins) const
+    {
+        const unsigned long long f = ((((unsigned long long)((key - kmin) >> low_zeros)) << id_bits) | (id - imin)) << up;
+        return (f >> 32) * bins + ((f & 0xFFFFFFFFull) * bins >> 32);
+    }
+};
+
+// A stretch beyond the capacity (the samples bound its length with a chance of up to 1e-3 per sort, see split_geom): the workgroup sorts it
+// in memory.  from: cnt pairs; to_id, to_pk: the stretch's place in the plan.  Leaves the pairs in from.
+//
+// First by the count that sorts a stretch in LDS: bins of the pairs' places in the range, the pairs laid out bin by bin, and every pair
+// ranked among its bin's; false, and the pairs as they were, where a bin holds too many for that.  lds: 2 * CAP words, part: THREADS / 64.
+constexpr uint32_t kMemoryBin = 32;
+template <int THREADS, int CAP>
+__device__ bool count_in_memory(uint2* from, uint32_t* to_id, float* to_pk, int cnt, const StretchRange& R, uint32_t* lds, uint32_t* part)
+{
+    constexpr int BINS = 2 * CAP, ROWS = BINS / THREADS, SIDE = 4;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    for (int i = tid; i < BINS; i += THREADS) lds[i] = 0u;
+    __syncthreads();
+    auto each = [&](auto load, auto use) {          // pairs of a thread side by side
+        for (int e0 = tid; e0 < cnt; e0 += SIDE * THREADS) {
+            uint2 v[SIDE];
+#pragma unroll
+            for (int u = 0; u < SIDE; ++u) v[u] = load(e0 + u * THREADS < cnt ? e0 + u * THREADS : cnt - 1);
+#pragma unroll
+            for (int u = 0; u < SIDE; ++u)
+                if (e0 + u * THREADS < cnt) use(v[u]);
+        }
+    };
+    auto unordered = [&](int e) { return from[e]; };
+    auto binned = [&](int e) { return make_uint2(__float_as_uint(to_pk[e]), to_id[e]); };
+    auto bin_of = [&](uint2 v) { return (uint32_t)(R.place(v.x, v.y, BINS) >> 32); };
+    each(unordered, [&](uint2 v) { atomicAdd(&lds[bin_of(v)], 1u); });
+    __syncthreads();
+    uint32_t* const row = lds + wave * (ROWS * 64) + lane;
+    uint32_t run = 0u, big = 0u;
+    for (int i = 0; i < ROWS; ++i) { const uint32_t c = row[i * 64]; run += c; big = c > big ? c : big; }
+    run = wave_scan(run);
+    if (lane == 63) part[wave] = run;
+    if (__syncthreads_or(big > kMemoryBin)) return false;
+    run = 0u;
+    for (int w = 0; w < wave; ++w) run += part[w];
+    for (int i = 0; i < ROWS; ++i) {
+        const uint32_t c = row[i * 64], inc = wave_scan(c);
+        row[i * 64] = run + inc - c;
+        run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    }
+    __syncthreads();
+    each(unordered, [&](uint2 v) {
+        const uint32_t at = atomicAdd(&lds[bin_of(v)], 1u);
+        to_pk[at] = __uint_as_float(v.x); to_id[at] = v.y;
+    });
+    __threadfence_block();
+    __syncthreads();
+    each(binned, [&](uint2 v) {                     // a bin's counter stands at its end now, the one before at its start
+        const uint32_t b = bin_of(v), first = b ? lds[b - 1] : 0u, end = lds[b];
+        uint32_t at = first;
+        for (uint32_t q = first; q < end; ++q) {
+            const uint2 o = binned((int)q);
+            at += o.x < v.x || (o.x == v.x && o.y < v.y) ? 1u : 0u;
+        }
+        from[at] = v;
+    });
+    __threadfence_block();
+    __syncthreads();
+    return true;
+}
+
+// Otherwise by the 8-bit digits of (key, id) from the lowest up, stably; digits that do not vary are passed over.
 template <int THREADS>
 __device__ void sort_in_memory(uint2* from, uint32_t* to_id, float* to_pk, int cnt, uint32_t vary_key, uint32_t vary_id, uint32_t* lds)
 {
@@ -511,24 +592,16 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
         int bins = 2 * cnt < CAP ? 2 * cnt : CAP;
         clear(bins);
         __syncthreads();
-        // A pair as a fraction of the range of the stretch, (key - smallest key, id - smallest id) moved to the top of 64 bits without the
-        // low bits that no key differs in: bin = fraction * bins, and what is left of the product is the fraction inside the bin.
-        const uint32_t vary = s_key_or & ~s_key_and;
-        const uint32_t kmin = s_key_min, imin = s_id_min;
-        if (tid == 0) publish(kmin, s_key_max);
-        const int low_zeros = vary ? __ffs((int)vary) - 1 : 0;
-        const uint32_t span = (s_key_max - kmin) >> low_zeros, ispan = s_id_max - imin;
-        const int id_bits = ispan ? 32 - __clz((int)ispan) : 0, bits = (span ? 32 - __clz((int)span) : 0) + id_bits;
-        const int up = bits > 0 ? 64 - bits : 0;
+        const StretchRange R(s_key_min, s_key_max, s_id_min, s_id_max, s_key_or & ~s_key_and);
+        if (tid == 0) publish(s_key_min, s_key_max);
         uint32_t left[ITEMS];                       // the fraction inside the bin, its first 32 bits
         uint32_t seg[ITEMS], rank[ITEMS];           // first slot and size (upper half) of the group the pair belongs to; its place there
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {
             if (i * THREADS < cnt) {                // uniform
-                const unsigned long long f = ((((unsigned long long)((key[i] - kmin) >> low_zeros)) << id_bits) | (id[i] - imin)) << up;
-                const unsigned long long lo = (f & 0xFFFFFFFFull) * (uint32_t)bins, hi = (f >> 32) * (uint32_t)bins + (lo >> 32);
-                seg[i] = (uint32_t)(hi >> 32);
-                left[i] = (uint32_t)hi;
+                const unsigned long long place = R.place(key[i], id[i], (uint32_t)bins);
+                seg[i] = (uint32_t)(place >> 32);
+                left[i] = (uint32_t)place;
                 if (i * THREADS + tid < cnt) rank[i] = atomicAdd(&buf[seg[i]], 1u);
             }
         }
@@ -630,19 +703,24 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
         }
     } else {
         uint2* const spare = op_shift(A.spare, op * A.op_ws) + base;
-        uint32_t k_and = 0xFFFFFFFFu, k_or = 0u, i_and = 0xFFFFFFFFu, i_or = 0u;
+        uint32_t k_and = 0xFFFFFFFFu, k_or = 0u, k_min = 0xFFFFFFFFu, k_max = 0u, i_min = 0xFFFFFFFFu, i_max = 0u;
         for (int e = tid; e < cnt; e += THREADS) {
             const int t = tile_of(e);
             const uint2 v = pairs[place[t] + (uint32_t)e];
             spare[e] = v;
-            k_and &= v.x; k_or |= v.x; i_and &= v.y; i_or |= v.y;
+            k_and &= v.x; k_or |= v.x;
+            k_min = v.x < k_min ? v.x : k_min; k_max = v.x > k_max ? v.x : k_max;
+            i_min = v.y < i_min ? v.y : i_min; i_max = v.y > i_max ? v.y : i_max;
         }
-        if (tid == 0) { s_id_min = 0xFFFFFFFFu; s_id_max = 0u; }
-        __syncthreads();
-        atomicAnd(&s_key_and, k_and); atomicOr(&s_key_or, k_or); atomicAnd(&s_id_min, i_and); atomicOr(&s_id_max, i_or);
+        atomicAnd(&s_key_and, k_and); atomicOr(&s_key_or, k_or); atomicMin(&s_key_min, k_min); atomicMax(&s_key_max, k_max);
+        atomicMin(&s_id_min, i_min); atomicMax(&s_id_max, i_max);
         __threadfence_block();
         __syncthreads();
-        sort_in_memory<THREADS>(spare, ids + base, pk + base + 1, cnt, s_key_or & ~s_key_and, s_id_max & ~s_id_min, buf);
+        const uint32_t vary = s_key_or & ~s_key_and;
+        if (!count_in_memory<THREADS, CAP>(spare, ids + base, pk + base + 1, cnt, StretchRange(s_key_min, s_key_max, s_id_min, s_id_max, vary), buf, part)) {
+            const uint32_t id_span = s_id_max - s_id_min;      // the low digits of the ids up to where the smallest and the largest differ
+            sort_in_memory<THREADS>(spare, ids + base, pk + base + 1, cnt, vary, id_span ? 0xFFFFFFFFu >> __clz((int)(s_id_min ^ s_id_max)) : 0u, buf);
+        }
         for (int e = tid; e < cnt; e += THREADS) {
             const uint2 v = spare[e];
             write(base + e, v.x, e > 0 ? spare[e - 1].x : 0u, v.y, e > 0);

@@ -137,18 +137,52 @@ def test_sample_sort_bounds_of_one_key(N, kind):
     assert np.array_equal(ids, np.argsort(v, kind="stable"))
 
 
-@pytest.mark.parametrize("ties", [False, True])
-@pytest.mark.parametrize("N,samples", [(9000, 9 * 16), (200000, 98 * 16), (600000, 256 * 16)])
-def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
-    """The positions that the sort takes its samples from hold the smallest keys: all others fall into the last stretch, which no
-    workgroup's LDS holds."""
-    r = np.random.default_rng(N + ties)
+def sample_positions(N, samples):
+    """Where the sort takes its samples from (sample_position in split_sort_kernels.hip)."""
     i = np.arange(samples, dtype=np.uint64)
     h = (i * 2654435761 + 40503) & 0xFFFFFFFF
     h ^= h >> 15; h = (h * 0x2C1B3C6D) & 0xFFFFFFFF; h ^= h >> 13
     width = N // samples
     at = (i * width + (h * width >> 32)).astype(np.int64)
     assert np.unique(at).size == samples and at.max() < N
+    return at
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties", "window"])
+@pytest.mark.parametrize("over", [1, 500, 3000])
+def test_sample_sort_a_little_beyond_the_capacity(kind, over):
+    """An unlucky place of the samples leaves one stretch `over` pairs more than LDS holds (16384): sorted in memory, by one count or, where
+    too many pairs share a bin (`window`), by digits."""
+    N, buckets, per, cap = 600000, 256, 16, 16384
+    r = np.random.default_rng(over)
+    at = sample_positions(N, buckets * per)
+    lo, hi = 100.0, 200.0                   # the stretch: keys in [lo, hi), its bounds among the samples
+    inside = cap + over - per
+    v = np.empty(N)
+    s = np.empty(buckets * per)
+    s[: 100 * per] = r.uniform(0, lo, 100 * per)
+    s[100 * per: 101 * per] = np.linspace(lo, hi, per, endpoint=False)
+    s[101 * per:] = np.r_[hi, r.uniform(hi, 900, buckets * per - 101 * per - 1)]
+    rest = np.setdiff1d(np.arange(N), at)
+    keys = np.empty(rest.size)
+    keys[:inside] = r.uniform(lo, hi - 1e-3, inside) if kind != "window" else np.where(r.random(inside) < 0.6, 150.0, r.uniform(lo, hi - 1e-3, inside))
+    keys[inside:] = np.where(r.random(rest.size - inside) < 0.1, r.uniform(0, lo - 1e-3, rest.size - inside), r.uniform(hi, 900, rest.size - inside))
+    if kind == "ties":
+        keys = np.floor(keys * 4) / 4
+    v[rest], v[at] = r.permutation(keys), r.permutation(s)
+    v = v.astype(np.float32)
+    assert np.sum((v >= np.float32(lo)) & (v < np.float32(hi))) == cap + over
+    ids, _ = sorted_ids(v[:777], v[777:])
+    assert np.array_equal(ids, np.argsort(v, kind="stable"))
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("N,samples", [(9000, 9 * 16), (200000, 98 * 16), (600000, 256 * 16)])
+def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
+    """The positions that the sort takes its samples from hold the smallest keys: all others fall into the last stretch, which no
+    workgroup's LDS holds."""
+    r = np.random.default_rng(N + ties)
+    at = sample_positions(N, samples)
     v = r.integers(50, 90, N) * 0.25 if ties else r.uniform(50, 50 + N / 64, N)
     v[at] = r.uniform(0, 40, samples)
     v = v.astype(np.float32)
