@@ -464,7 +464,7 @@ def measure(spec, steps, warmup, torch, np, B):
     out = {
         "ms_per_step": round(ms_per_step, 4), "value": elements / (ms_per_step * 1e-3),
         "config": {"workload": spec["name"], "k": k, "n": n, "batch": batch, "anchors": spec["anchors"],
-                   "pass": spec["passname"], "sort": "radix sort inside every step",
+                   "pass": spec["passname"], "sort": ("radix sort" if N > 1 << 22 else "sort by samples") + " inside every step",
                    "workspace_bytes": spec["ws"].numel(), "device_bytes_peak": torch.cuda.max_memory_allocated()},
         "roofline": roofline,
         "families_ms_one_step": {f: round(v[0], 4) for f, v in sorted(families.items(), key=lambda kv: -kv[1][0])[:16]},

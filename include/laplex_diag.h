@@ -14,8 +14,8 @@ extern "C" {
 
 /*
  * Kernel-family timing.  Between begin and end,
- * every launch of the named kernel family ("sort_hist", "radix_scatter", "merge",
- * "decay", "rowdot", "sum_slabs", "fill", and "scan_meta.T", "scan_reduce.T",
+ * every launch of the named kernel family ("split_sample", "split_pick", "split_tiles",
+ * "split_sort", "sort_hist", "radix_scatter", "merge", "decay", "rowdot", "sum_slabs", "fill", and "scan_meta.T", "scan_reduce.T",
  * "scan_spine.T", "scan_down.T", "scan_down_sparse.T" with T = "fwd" for the
  * forward scans of x, "bwd" for the backward scans of gy, "rescan" for the
  * backward's repeat of the forward scans when they were not saved) is bracketed by a pair of HIP
@@ -38,10 +38,13 @@ int laplex_profile_family(int64_t index, char* name /* host */, size_t name_byte
 /*
  * Diagnostics: rows of the merged sequence that one workgroup (for batches of
  * 253 columns and more with 128-bit lanes: one wavefront) of the downsweep
- * kernels owns, a "block", for a given batch, with 128-bit lanes (wide != 0:
- * batch and leading dimensions multiples of 4, 16-byte aligned pointers) or
- * scalar lanes.  Lets a benchmark count which blocks a launch visits.  `rows`
- * is a host pointer.
+ * kernels owns, a "block", for a given batch, with lanes of four columns (wide
+ * != 0: batch and leading dimensions multiples of 4, 16-byte aligned pointers;
+ * batches of 9 to 128 columns take such lanes without these conditions too, and
+ * then have the rows of the next multiple of 4) or lanes of one.  With up to 8
+ * single columns the rows also depend on the merged length, an eighth, a
+ * quarter or half of the value given here while that makes 256 blocks or fewer.
+ * Lets a benchmark count which blocks a launch visits.  `rows` is a host pointer.
  */
 int laplex_scan_tile_rows(int64_t batch, int wide, int64_t* rows);
 

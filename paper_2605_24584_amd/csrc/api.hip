@@ -329,7 +329,7 @@ Wgram64Layout wgram64_layout(int64_t k, int64_t n)
 }
 
 // The plan (ids, sorted anchors) of the doubled anchors: few merged positions are ranked by counting in one
-// launch, more go through the radix sort (or the merge path).
+// launch, more take the sort of every other call (build_plan).
 int build_wgram_plan(const float* a, int64_t k, const float* b, int64_t n, const Layout& L, const Plan& P, char* w,
                      uint32_t flags, hipStream_t st)
 {

@@ -3001,15 +3001,13 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 //     50000, batch 20 (3.1e6): 32 / 35 / 29 (24 / 29); 400000, batch 8 (4.9e6): 56 / 55 / 53 (48 / 52); 70000, batch 32 (9.6e6):
 //     41 / 40 / 29 (25 / 29); 200000, batch 16 (9.8e6): 39 / 43 / 36 (32 / 36); 700000, batch 8 (1.5e7): 81 / 84 / 76 (73 / 76)
 //   fewer, a workgroup per tile, 4 columns a lane   30000, batch 256 (3.5e6): 52 / 43 / 45 (41 / 45); 60000, batch 256 (1.4e7): 70 / 67 / 65
-//   single columns, several row-lanes (two levels read 256 bytes per entry there and gain nothing)
-//     60000, batch 17 (4.4e6): 51 / 46; 80000, batch 17 (7.8e6): 59 / 58; 70000, batch 31 (1.1e7): 60 / 55
-//   single columns, one row-lane                    20000, batch 33 (3.5e6): 44 / 43; 12000, batch 130 (4.6e6): 51 / 51; 20000, batch 65
-//     (6.6e6): 50 / 60; 30000, batch 33 (7.9e6): 45 / 51
+//   single columns, one row-lane (beyond 128 columns that allow no 16-byte accesses; two levels read 256 bytes per entry there and gain
+//     nothing)                                      12000, batch 130 (4.6e6): 51 / 51; 65 such columns, 20000 (6.6e6): 50 / 60
 // Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
 // 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243; with two or four row-lanes up to 7e6 (a product: 90000 x 90000, batch
 // 64 (6.6e6): 52 / 50; 100000 x 100000, batch 64 (8.1e6): 53 / 54; 200000 x 3, batch 64 (8.1e6): 49 / 52).
 constexpr int kFewSpineWaves = 4;
-constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnsWork = 12e6, kSpineColumnWork = 5e6;
+constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnWork = 5e6;
 constexpr double kSpineSuperWork = double(1 << 23), kSpineSuperFewWork = 7e6;
 template <int VEC, bool STRICT>
 void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipStream_t st)
@@ -3022,7 +3020,7 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
     super.count = (g.tiles + kSuperTiles - 1) / kSuperTiles;
     if (!g.sub_shift) { super.s = A.blk_f; super.q = A.blk_e; }
     const bool groups_gain = VEC == 4 || g.rv >= 8;
-    const double line = g.rv >= 8 ? kSpineWaveWork : VEC == 4 ? kSpineGroupWork : g.rv > 1 ? kSpineColumnsWork : kSpineColumnWork;
+    const double line = g.rv >= 8 ? kSpineWaveWork : VEC == 4 ? kSpineGroupWork : kSpineColumnWork;
     const bool one = (double)g.tiles * (double)g.tiles * (double)A.bpad <= line;
     const double super_line = g.rv > 1 && g.rv < 8 ? kSpineSuperFewWork : kSpineSuperWork;
     const bool two = !one && groups_gain && (double)g.tiles * (double)(kSuperTiles + super.count) * (double)A.bpad <= super_line;
@@ -3030,7 +3028,7 @@ void launch_spine(const ScanArgs& A, const ScanGeom& g, const char* family, hipS
         const int lists = A.down_from_list && !A.reduce_from_list ? (int)g.chunks : 0;
         auto groups = [&](int64_t n) { return (unsigned)(g.rv >= 8 ? (n + kScanWaves - 1) / kScanWaves : n); };
         // With two levels a tile reads at most 32 entries of its group and the other groups: fewer wavefronts share it where they
-        // have two or four row-lanes each (kFewSpineWaves: four entries in flight per row-lane, 16 row-lanes)
+        // have four row-lanes each (kFewSpineWaves: four entries in flight per row-lane, 16 row-lanes)
         const bool few = two && VEC == 4 && g.rv >= 4 && lists == 0;      // (the workgroups that list blocks are whole ones)
         const dim3 sblock(few ? kFewSpineWaves * 64 : kScanThreads);
         const dim3 sgrid(groups(super.count), (unsigned)g.slabs, 2), dgrid((unsigned)lists + groups(g.tiles), (unsigned)g.slabs, 2);
@@ -3090,6 +3088,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     } else if (!A.stage && (int64_t)rgrid.x * rgrid.y > (A.dot_out ? 2 : 1) * kLoneTilesMin) {      // one wavefront per tile
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, lgrid, dim3(kLoneWaves * 64), 0, st, A)); };
+        // (single columns come here with several slabs only, whose row products are a pass of their own)
         if (VEC == 4 && A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
     } else {
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, rgrid, bblock, 0, st, A)); };

@@ -14,8 +14,8 @@
 // where the tiles' counts add up to.  What bounds it is the chain of dependent steps of each launch, and in the tiles the counts: an LDS
 // atomic that returns a value serves about one lane a clock.
 //
-// The sort in LDS is one count, not a merge or a radix pass: a pair's place in the range of its stretch gives its bin (twice as many
-// bins as pairs), the bins' counts its group, and the few pairs of a group are compared with each other.  Only groups beyond 16 pairs
+// The sort in LDS is one count, not a merge or a radix pass: a pair's place in the range of its stretch gives its bin (up to
+// twice as many bins as pairs), the bins' counts its group, and the few pairs of a group are compared with each other.  Only groups beyond 16 pairs
 // (keys far from evenly spread inside the stretch, equal keys) are counted again, in as many bins as they have pairs.
 //
 // Measured (MI355X, us, this sort / runs merged in LDS up to 2^19 and radix passes with a decay pass beyond, which it replaced; uniform
@@ -106,6 +106,7 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* part, uint3
 }
 
 // One sample per stretch of N / samples positions, at a place inside it that a hash picks: no period of the input coincides with them.
+// (Its multipliers are Knuth's, The Art of Computer Programming 6.4, and one of the 32-bit mixers that C. Wellons' hash prospector lists.)
 __device__ __forceinline__ int sample_position(int i, int N, int samples)
 {
     const int width = N / samples;
@@ -757,8 +758,10 @@ namespace {
 // length, so from 2^19 positions on there are as few of them as the capacity (1024 x 16 pairs) allows, in whole rounds of the 256
 // compute units (us for the whole sort; 2^20 + 1024 positions: 256 stretches 41, 512 of half the length, two to a compute unit, 49;
 // 2^21: 256 of 8192 pairs 59, 512 of 4096 67).  The samples keep a stretch inside the capacity: with s samples per stretch, of which it
-// would have to hold fewer than s where its length calls for s * capacity / average, the chance is below 1e-3 for a whole sort at the
-// worst sizes and below 1e-6 at most.  Tiles: the fewest keys that still make at most 512 of them.
+// would have to hold fewer than s where its length calls for s * capacity / average, the chance of one beyond it is, for a whole sort, 2e-4
+// at 256 * 6144 positions, 9e-4 at 2^21, 5e-4 at 512 * 6144, 8e-4 at 2^22, and falls to below 1e-5 at five sixths of these sizes (18 or 19
+// pairs a thread, a longer LDS buffer, would bring it to 1e-5, and cost 5 to 10 % in spilled registers).  Such a set of anchors is sorted
+// in memory there (count_in_memory: 58 us more at 2^21).  Tiles: the fewest keys that still make at most 512 of them.
 struct SplitGeom { int per, threads, group_bits; int64_t tile, tiles, buckets, samples; };
 constexpr int kTileThreads = 1024;
 SplitGeom split_geom(int64_t N)
