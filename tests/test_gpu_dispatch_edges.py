@@ -37,7 +37,7 @@ def test_weighted_gram_tile_edges(oracle, k, n, gap):
     assert float((np.abs(got - ref) / (1e-12 * tol + 1e-300)).max()) <= 1.0
 
 
-RUN_SORT_SIZES = [8193, 9217, (1 << 17) - 1, 1 << 17, (1 << 17) + 1, 1 << 18, (1 << 18) + 1, 1 << 19, (1 << 19) + 1]
+SAMPLE_SORT_SIZES = [8193, 9217, (1 << 17) - 1, 1 << 17, (1 << 17) + 1, 1 << 18, (1 << 18) + 1, 1 << 19, (1 << 19) + 1]
 
 
 def sorted_ids(keys_a, keys_b):
@@ -52,11 +52,12 @@ def sorted_ids(keys_a, keys_b):
     return perm.cpu().numpy(), y.cpu().numpy()
 
 
-@pytest.mark.parametrize("kind", ["uniform", "few_values", "equal", "ascending", "repeating", "between_samples"])
-@pytest.mark.parametrize("N", RUN_SORT_SIZES)
-def test_run_sort_order_and_decays(oracle, N, kind):
-    """The two-launch sort at the ends of its configurations (tiles of 1024, 2048, 4096 keys).  `between_samples` puts, in
-    every run, all keys between two of the run's samples into one narrow window: a stretch beyond the capacity of a workgroup."""
+@pytest.mark.parametrize("kind", ["uniform", "few_values", "equal", "ascending", "repeating", "narrow_windows"])
+@pytest.mark.parametrize("N", SAMPLE_SORT_SIZES)
+def test_sample_sort_order_and_decays(oracle, N, kind):
+    """The sort by samples at the ends of its first configurations.  `narrow_windows` takes, from every 1024 to 4096 consecutive positions, a
+    few dozen neighbouring ones into one narrow window of the keys: dense bins in a stretch (stretches beyond the capacity:
+    test_sample_sort_a_little_beyond_the_capacity and the one after it)."""
     r = np.random.default_rng(N)
     tile = 1024 if N <= 1 << 17 else 2048 if N <= 1 << 18 else 4096
     step = tile // 64
@@ -197,7 +198,9 @@ def test_sample_sort_beyond_the_capacity(oracle, N, samples, ties):
     (5000, 4000, 9, 0, 0), (5000, 4000, 10, 3, 0), (4100, 4100, 15, 0, 1), (9000, 33, 17, 0, 0), (33, 9000, 31, 1, 2), (6001, 3002, 33, 0, 0),
     (4000, 6000, 63, 0, 3), (4000, 6000, 65, 0, 0), (5000, 5000, 64, 1, 0), (5000, 5000, 12, 0, 1), (4500, 4500, 127, 0, 0), (4500, 4500, 128, 0, 2),
     (4500, 4500, 129, 0, 0), (70000, 62000, 65, 0, 0),                          # single columns again; a wavefront per tile, three spine launches
-    (30000, 34000, 33, 0, 0),                                                   # two spine launches
+    (30000, 34000, 33, 0, 0),                                                   # 500 tiles that each read all others
+    (2999, 100003, 33, 0, 0), (45000, 50000, 33, 2, 1), (100000, 110000, 13, 0, 0),    # more of them, in groups: two spine launches
+    (40000, 31000, 64, 0, 0),                                                   # ... and rows that do allow it
 ])
 def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
     """Rows that start anywhere, of lengths that are no multiple of four: lanes of four columns whose last group ends with the row.  Forward,
@@ -285,6 +288,16 @@ def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
     assert_close("y", y.cpu().numpy(), ref, tol)
     for name, got, rv, tv in zip(("gx", "ga", "gb"), (gx, ga, gb), want, tols):
         assert_close(name, got.cpu().numpy(), rv, tv)
+
+
+@pytest.mark.parametrize("k,n,batch,launches", [(30000, 34000, 33, 1), (2999, 100003, 33, 2), (45000, 50000, 33, 2), (100000, 110000, 13, 2), (70000, 62000, 65, 3),
+                                                (1000, 40000, 33, 1), (40000, 31000, 64, 2), (1500, 82000, 40, 2), (900000, 600000, 8, 2)])
+def test_spine_launches(k, n, batch, launches):
+    """The cases of test_direct_spine and test_rows_that_allow_no_16_byte_access that are there for a form of the spine reach it."""
+    a, b, x = (torch.rand(*shape, device="cuda") for shape in ((k,), (n,), (n, batch)))
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    seen = families(lambda: B.laplex_apply(a, b, x, torch.empty(k, batch, device="cuda"), ws))
+    assert seen["scan_spine.fwd"] == launches, seen
 
 
 @pytest.mark.parametrize("k,n,batch,in_order", [(9000, 9000, 8, True), (3000, 9000, 4, True), (2999, 9001, 4, False), (1000, 100000, 8, False),
@@ -456,7 +469,8 @@ def test_mix_common_launches_non_finite_anchors(oracle):
     (3, 4097, 4096, 3, 2), (2, 4096, 4097, 33, 1), (2, 6000, 3000, 100, 0), (1, 30000, 600, 8, 0), (2, 700, 20000, 64, 0),
     (2, 9000, 31, 16, 0), (1, 33, 9001, 2, 0),                    # hundreds of long rows between two short ones: several tasks each
     (2, 7000, 906, 64, 0), (2, 7000, 905, 64, 0), (16, 500, 898, 256, 0),       # from 8e9 / (r batch) = N^2 on: common launches
-    (3, 6831, 1, 1, 0), (3, 1, 6832, 1, 0), (16, 1500, 1500, 1, 0),             # the last operators ranked by counting, the first sorted
+    (3, 6831, 1, 1, 0), (3, 1, 6832, 1, 0), (16, 1500, 1500, 1, 0),             # operators sorted in a workgroup each
+    (5, 3000, 400, 1, 0), (5, 400, 3001, 1, 0), (17, 999, 1, 3, 0), (17, 1, 1000, 3, 0),      # r N = 17000, the last ones ranked by counting; the first sorted
 ])
 def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
     """Sums of operators in common launches: either side the shorter one, one and several tiles of the short side (256
@@ -500,8 +514,9 @@ def test_mix_common_launches(oracle, kind, r, k, n, batch, pad):
     (4000, 4200, 1), (9000, 7385, 1),                             # one and two tiles of 8192 rows, and a row more
     (65000, 66072, 8), (65000, 66073, 8),                         # 128 tiles of 1024 rows, and one more
     (32768, 32769, 32), (20, 60000, 8),                           # few outputs: the list of heavy blocks beside the sums
-    (1000, 40000, 33), (700, 30000, 256),                         # a summary is a wavefront wide: a workgroup per tile
+    (1000, 40000, 33), (700, 30000, 256),                         # a workgroup per tile: four row-lanes, one
     (900000, 600000, 8), (30, 140000, 256),                       # two levels: groups of 32 tiles, the last one shorter
+    (40000, 31000, 64), (1500, 82000, 40),                        # ... four row-lanes, 555 and 653 tiles
 ])
 def test_direct_spine(oracle, kind, k, n, batch):
     """The spine that adds the other tiles' summaries directly, at one tile, at the ends of its groups, with runs of equal keys that

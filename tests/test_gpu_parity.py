@@ -127,8 +127,8 @@ SHAPES = [(1, 1, 1), (5, 1, 2), (1, 6, 1), (37, 53, 3), (100, 9000, 1), (9000, 1
 # ------------------------------------------------------------------ the sort
 
 @pytest.mark.parametrize("kind", KINDS)
-# up to 8192 merged positions ranks by counting, up to 2^19 runs and buckets (their edges: test_gpu_dispatch_edges), then radix passes:
-# tiles of 4096 pairs up to 5 * 2^18 positions, of 8192 beyond, and beyond 2^22 - 1 a histogram that keeps its counters once per LDS bank
+# up to 8192 merged positions ranks by counting, up to 2^22 the sort by samples (their edges: test_gpu_dispatch_edges), beyond that radix
+# passes
 @pytest.mark.parametrize("k,n", [(1, 1), (3, 0), (0, 5), (100, 157), (9000, 8000), (20000, 70001),
                                  (130000, 132001), (300001, 400122), (1500000, 1000003), (2300001, 2100003),
                                  (655360, 655360), (655361, 655360), (2097152, 2097151), (2097152, 2097152)])
@@ -146,8 +146,8 @@ def test_permutation_bit_exact(oracle, kind, k, n):
 @pytest.mark.parametrize("off_a,off_b", [(1, 0), (2, 3), (3, 1), (0, 2)])
 @pytest.mark.parametrize("k,n", [(1, 2), (2, 1), (3, 7), (4100, 4100), (9001, 20003), (2100001, 2100002), (300001, 400122), (700003, 900002)])
 def test_anchor_arrays_off_a_16_byte_boundary(oracle, off_a, off_b, k, n):
-    """The radix sort's two histograms (the last two sizes, and the one before them) read the anchors 16 bytes at a time between a
-    scalar head and a scalar tail; the other sorts read them one by one."""
+    """The radix sort's histogram (4200003 positions) reads the anchors 16 bytes at a time between a scalar head and a scalar tail; the
+    other sorts read them one by one."""
     r = np.random.default_rng(k * 5 + n + off_a * 16 + off_b)
     a, b = anchors("ties", r, k, n)
     x = r.normal(size=(n, 1)).astype(np.float32)
