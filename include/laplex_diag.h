@@ -44,7 +44,8 @@ int laplex_profile_family(int64_t index, char* name /* host */, size_t name_byte
  * then have the rows of the next multiple of 4) or lanes of one.  With up to 8
  * single columns the rows also depend on the merged length, an eighth, a
  * quarter or half of the value given here while that makes few blocks (255 at
- * most with one or two columns, 127 with more).
+ * most with one or two columns, 127 with three or four, 79 with more, before
+ * the last halving).
  * Lets a benchmark count which blocks a launch visits.  `rows` is a host pointer.
  */
 int laplex_scan_tile_rows(int64_t batch, int wide, int64_t* rows);

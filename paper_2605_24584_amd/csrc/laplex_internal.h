@@ -121,15 +121,16 @@ inline ScanGeom scan_geom(int64_t N, int64_t batch, int vec, bool whole = false)
     if (g.slabs < 1) g.slabs = 1;
     g.sub_shift = (vec == 4 && g.bv == 64) ? kWideSubShift : 0;
     g.waves = (vec == 4 && !g.sub_shift) ? kBlockWavesNarrow : kScanWaves;
-    // Staged batches with single columns: smaller blocks until there are 256 of them (batch 1: 8192 rows a block), 128 from three columns
-    // on.  The random rows of a block are fetched by one compute unit
+    // Staged batches with single columns: smaller blocks until there are 256 of them (batch 1: 8192 rows a block), 128 with three and four
+    // columns, 80 with more.  The random rows of a block are fetched by one compute unit
     // (50000 x 50000, batch 1, us, blocks of 8 wavefronts / 1: reduce 23 / 11, downsweep 22 / 11; 300000 x 300000: 27 / 17, 24 / 17);
     // but a block's state is the sum of what every other block within reach leaves, and with 16 or 8 row-lanes a wavefront reads fewer of
-    // them side by side (a product on a kept plan, 8 wavefronts / 128 / 256 blocks: 20000 x 20000, batch 5, all within reach 21.2 / 21.0 / 26.2,
-    // spread 20.9 / 17.8 / 18.9; 80000 x 80000, batch 7, 26.2 / 26.1 / 30.3, spread 22.9 / 22.7 / 22.0; 250000 x 250000, batch 3, 30.1 / 30.1 /
-    // 33.0, spread 27.7 / 27.7 / 26.9; batch 1, 524800 x 524800, 50.6 / 51.0 / 39.0; batch 2, 40000 x 40000, 39.2 / 19.7 / 19.9).
+    // them side by side (a product on a kept plan, 8 wavefronts / until there are 80 / 128 / 256 blocks: 30000 x 30000, batch 5, all within
+    // reach 21.8 / 21.6 / 24.4 / 32.0, spread 21.3 / 19.2 / 18.4 / 19.3; 65000 x 65000, 24.7 / 24.8 / 26.4 / 35.0, spread 22.2 / 22.1 / 20.0 /
+    // 20.7; 250000 x 250000, batch 3, 8 wavefronts / 128 / 256: 30.1 / 30.1 / 33.0, spread 27.7 / 27.7 / 26.9; batch 1, 524800 x 524800, 50.6 /
+    // 51.0 / 39.0; batch 2, 40000 x 40000, 39.2 / 19.7 / 19.9).
     if (vec == 1 && batch <= kStageMaxBatch && !whole) {
-        const int64_t blocks = g.rv >= 32 ? 255 : 127;       // at most so many: smaller ones
+        const int64_t blocks = g.rv >= 32 ? 255 : g.rv >= 16 ? 127 : 79;       // at most so many: smaller ones
         while (g.waves > 1 && N <= blocks * g.waves * g.rv * g.items) g.waves /= 2;
     }
     g.tile_rows = g.waves * g.rv * g.items;

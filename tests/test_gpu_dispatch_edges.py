@@ -243,7 +243,8 @@ def test_rows_that_allow_no_16_byte_access(oracle, k, n, batch, pad, shift):
 @pytest.mark.parametrize("kind", ["uniform", "ties"])
 @pytest.mark.parametrize("N,batch", [(65 * 1024, 1), (255 * 1024, 1), (255 * 1024 + 1, 1), (255 * 2048 + 1, 1), (255 * 4096 + 1, 1), (255 * 512, 2), (255 * 512 + 1, 2), (255 * 256 + 1, 3),
                                      (255 * 128, 7), (255 * 128 + 1, 5),
-                                     (127 * 256, 3), (127 * 256 + 1, 3), (127 * 512 + 1, 4), (127 * 128, 7), (127 * 128 + 1, 5), (127 * 512 + 1, 6), (127 * 1024 + 1, 8)])
+                                     (127 * 256, 3), (127 * 256 + 1, 3), (127 * 512 + 1, 3), (79 * 128, 7), (79 * 128 + 1, 5), (79 * 256 + 1, 6), (79 * 512, 5),
+                                     (79 * 512 + 1, 7)])
 def test_narrow_batches_where_their_blocks_grow(oracle, N, batch, kind):
     """Single columns, up to 8 of them: blocks of one, two, four and eight wavefronts, at the sizes where they change."""
     from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward
