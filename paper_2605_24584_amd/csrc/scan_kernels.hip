@@ -3217,11 +3217,11 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         A.reduce_from_list = inj_rows * 4 <= g.tiles;
         A.down_from_list = both * 4 <= g.blocks;
         if (p.inj_sorted && p.out_sorted) A.reduce_from_list = A.down_from_list = 0;   // every block is visited
-        // ... and so it is where single columns have blocks of fewer than eight wavefronts (scan_geom): they are many beside the rows, and
-        // listing them, a launch more before the reduce and one more after the downsweep, costs more than it saves (us, a product, 64 inputs,
-        // lists / every block / blocks of eight wavefronts, too few for lists: 2^20 outputs, batch 1: 79 / 36 / 48; 500000, batch 2: 45 / 30 / 42;
-        // 250000, batch 3: 33 / 22 / 25; 100000, batch 7: 30 / 21 / 22)
-        if (g.vec == 1 && g.waves < kScanWaves) A.reduce_from_list = A.down_from_list = 0;
+        // ... and so it is with narrow batches of single columns up to 512 blocks: listing them, a launch more before the reduce (a wavefront
+        // per block) and one more after the downsweep, costs more than it saves (us, a product, 64 inputs, lists / every block: 2^20 outputs,
+        // batch 1: 79 / 36; 500000, batch 2: 45 / 30; 250000, batch 3: 33 / 22; 100000, batch 7: 30 / 21; at 512 blocks 2^21, batch 2: 108 /
+        // 71, 2^20, batch 3: 60 / 37; at 2048 2^21, batch 7: 79 / 82, backward 128 / 157)
+        if (g.vec == 1 && p.batch <= kStageMaxBatch && g.blocks <= 512) A.reduce_from_list = A.down_from_list = 0;
         // One downsweep for all blocks when every block is visited: each of its workgroups looks at its block and takes the scan or
         // the closed form, in place of a launch for either, which cost 4 to 15 us where it found few blocks (us, forward + backward,
         // two launches / one: n = k = 2^16, batch 8: 92 / 88; 2999 x 100003, batch 33: 210 / 195; inputs and outputs apart, 2^20 each,

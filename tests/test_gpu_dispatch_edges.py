@@ -268,9 +268,10 @@ def families(call):
     return {name: launches for name, (_, launches) in B.laplex_profile_families().items()}
 
 
-@pytest.mark.parametrize("k,n,batch", [(64, 255 * 4096 - 64, 1), (1, 9000, 1), (50, 120000, 2), (64, 250000, 3), (10000, 4, 3), (100000, 40, 7), (16, 30000, 5)])
+@pytest.mark.parametrize("k,n,batch", [(64, 255 * 4096 - 64, 1), (1, 9000, 1), (50, 120000, 2), (64, 250000, 3), (10000, 4, 3), (100000, 40, 7), (16, 30000, 5), (20, 500000, 7),
+                                       ((1 << 21) - 1, 1, 2)])
 def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
-    """Single columns in blocks of one, two and four wavefronts, a handful of inputs or outputs: no block is listed by a launch of its own."""
+    """Narrow batches of single columns, a handful of inputs or outputs, up to 512 blocks: none is listed by a launch of its own."""
     from test_gpu_parity import anchors, assert_close
     r = np.random.default_rng(k + n + batch)
     a, b = anchors("uniform", r, k, n)
