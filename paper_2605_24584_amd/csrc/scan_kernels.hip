@@ -3220,7 +3220,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         // ... and so it is with narrow batches of single columns up to 512 blocks: listing them, a launch more before the reduce (a wavefront
         // per block) and one more after the downsweep, costs more than it saves (us, a product, 64 inputs, lists / every block: 2^20 outputs,
         // batch 1: 79 / 36; 500000, batch 2: 45 / 30; 250000, batch 3: 33 / 22; 100000, batch 7: 30 / 21; at 512 blocks 2^21, batch 2: 108 /
-        // 71, 2^20, batch 3: 60 / 37; at 2048 2^21, batch 7: 79 / 82, backward 128 / 157)
+        // 71, 2^20, batch 3: 60 / 37; forward and backward, gx alone, 118868 x 20, batch 7: 97 / 74; at 2048 2^21, batch 7: 79 / 82, backward 128 / 157)
         if (g.vec == 1 && p.batch <= kStageMaxBatch && g.blocks <= 512) A.reduce_from_list = A.down_from_list = 0;
         // One downsweep for all blocks when every block is visited: each of its workgroups looks at its block and takes the scan or
         // the closed form, in place of a launch for either, which cost 4 to 15 us where it found few blocks (us, forward + backward,
