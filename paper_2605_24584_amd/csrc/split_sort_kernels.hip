@@ -14,29 +14,20 @@
 // where the tiles' counts add up to.  What bounds it is the chain of dependent steps of each launch, and in the tiles the counts: an LDS
 // atomic that returns a value serves about one lane a clock.
 //
-// The sort in LDS is one count, not a merge or a radix pass: a pair's place in the range of its stretch gives its bin (up to
-// twice as many bins as pairs), the bins' counts its group, and the few pairs of a group are compared with each other.  Only groups beyond 16 pairs
-// (keys far from evenly spread inside the stretch, equal keys) are counted again, in as many bins as they have pairs.
+// The sort in LDS is one count, not a merge or a radix pass (split_sort.h): a pair's place in the range of its stretch gives its bin (four times as many
+// bins as pairs, their counts one byte each), the bins' counts its group, and the few pairs of a group are compared with each other.  Only where a group
+// is beyond 16 pairs (keys far from evenly spread inside the stretch, many equal ones) is everything counted again.
 //
 // Measured (MI355X, us, this sort / runs merged in LDS up to 2^19 and radix passes with a decay pass beyond, which it replaced; uniform
-// keys): 9000 positions 20 / 22, 2^17: 25 / 27, 4 10^5: 32 / 50, 2^19 + 1: 33 / 65, 2^20 + 1024: 40 / 81, 2^21: 60 / 105, 3 2^20: 85 / 131,
-// 4 10^6: 112 / 145.  Of the last kernel's 14 us per workgroup at 2^20 + 1024 positions gathering is 4, the counts 3, comparing 1.5,
-// writing 2.5, finding the place 2.
-#include "laplex_internal.h"
+// keys): 9000 positions 20 / 22, 2^17: 25 / 27, 4 10^5: 32 / 50, 2^19 + 1: 33 / 65, 2^20 + 1024: 40 / 81, 2^21: 56 / 105, 3 2^20: 79 / 131,
+// 4 10^6: 105 / 145.  Bins four to a word, the anchor itself as the place where the range is wide, no bank conflicts in the search among the bounds (before: two bins to a
+// pair, a 64-bit place of key and id): the last kernel 38 -> 32 us at 2^21 positions, the tiles 16 -> 13; 2^19 x 2^19 with normal anchors, batch 8, forward +
+// backward 215 -> 209, the weighted Gram matrix of 1024 over 2^20 69.1 -> 67.6; 2^17 x 2^17 on a grid 98 -> 100, where the stretch around zero is counted once more.
+#include "split_sort.h"
 
 namespace laplex {
 
 namespace {
-
-__device__ __forceinline__ uint32_t split_key(float f)
-{
-    const uint32_t u = __float_as_uint(f + 0.0f);       // -0.0 sorts as +0.0
-    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-}
-__device__ __forceinline__ float split_key_to_float(uint32_t key)
-{
-    return __uint_as_float(key ^ ((key >> 31) ? 0x80000000u : 0xFFFFFFFFu));
-}
 
 struct SplitArgs {
     const float* a; const float* b; int64_t k; float tau; int N;
@@ -47,7 +38,7 @@ struct SplitArgs {
     uint16_t* starts;               // [tiles][buckets + 1]
     uint32_t* sampled;              // [samples] keys
     uint32_t* ids; float* dh; float* pk; float2* pk8; uint32_t* counters;     // the plan
-    int tiles, buckets, samples, per_bound;
+    int tiles, buckets, samples, per_bound, id_bits;
     int64_t op_a, op_b, op_ws;      // strides from one operator to the next (elements; bytes of workspace)
 };
 
@@ -57,52 +48,6 @@ __device__ __forceinline__ T* op_shift(T* p, int64_t bytes) { return reinterpret
 __device__ __forceinline__ uint32_t split_anchor(const SplitArgs& A, int64_t op, int64_t pos)
 {
     return split_key(A.tau * (pos < A.k ? A.a[op * A.op_a + pos] : A.b[op * A.op_b + pos - A.k]));
-}
-
-// Inclusive scan of one word per lane.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);      // row_shr:1, 2, 4, 8
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);      // the row before's last lane into rows 1 and 3
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);      // lane 31 into rows 2 and 3
-    return v;
-}
-
-// Reduction over the wavefront, the result in lane 63 only.
-template <typename OP>
-__device__ __forceinline__ uint32_t wave_fold(uint32_t v, uint32_t none, OP op)
-{
-    auto step = [&](uint32_t o) { v = op(v, o); };
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x111, 0xF, 0xF, false));
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x112, 0xF, 0xF, false));
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x114, 0xF, 0xF, false));
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x118, 0xF, 0xF, false));
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x142, 0xA, 0xF, false));
-    step((uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x143, 0xC, 0xF, false));
-    return v;
-}
-
-// Exclusive scan of one word per thread; *total gets the sum.  part: THREADS / 64 words of LDS, free again when this returns.
-template <int THREADS>
-__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* part, uint32_t* total)
-{
-    const int wave = threadIdx.x >> 6;
-    const uint32_t inc = wave_scan(v);
-    if ((threadIdx.x & 63) == 63) part[wave] = inc;
-    __syncthreads();
-    uint32_t before = 0u, all = 0u;
-#pragma unroll
-    for (int w = 0; w < THREADS / 64; ++w) {
-        const uint32_t t = part[w];
-        if (w < wave) before += t;
-        all += t;
-    }
-    *total = all;
-    __syncthreads();
-    return before + inc - v;
 }
 
 // One sample per stretch of N / samples positions, at a place inside it that a hash picks: no period of the input coincides with them.
@@ -189,7 +134,6 @@ k_split_pick(const SplitArgs A)
     }
 }
 
-constexpr int kSplitMaxBuckets = 1024;
 constexpr int64_t kSplitWholeMax = kSmallMax;      // positions that one workgroup sorts in one launch
 
 
@@ -198,7 +142,7 @@ __global__ void __launch_bounds__(THREADS)
 k_split_tiles(const SplitArgs A)
 {
     constexpr int TILE = THREADS * PER, BUCKETS_PER = kSplitMaxBuckets / THREADS > 0 ? kSplitMaxBuckets / THREADS : 1;
-    __shared__ uint32_t bound_key[kSplitMaxBuckets], bound_id[kSplitMaxBuckets];
+    __shared__ uint32_t bound_key[kBoundWords], bound_id[kSplitMaxBuckets];
     __shared__ uint32_t hist[kSplitMaxBuckets];
     __shared__ uint16_t same[kSplitMaxBuckets];             // bounds with this one's key, from it on
     __shared__ uint2 laid[TILE];
@@ -206,56 +150,16 @@ k_split_tiles(const SplitArgs A)
     const int tid = threadIdx.x, buckets = A.buckets;
     const int64_t op = blockIdx.y, base = (int64_t)blockIdx.x * TILE;
     const int len = A.N - base < TILE ? (int)(A.N - base) : TILE;
-    const unsigned long long* const bounds = op_shift(A.bounds, op * A.op_ws);
     uint32_t key[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
         const int q = i * THREADS + tid;
         key[i] = split_anchor(A, op, base + (q < len ? q : len - 1));
     }
-    int top = 1;                    // half the power of two that holds all stretches
-    while (2 * top < buckets) top *= 2;
-    int tied = 0;
-    for (int i = tid; i < kSplitMaxBuckets; i += THREADS) {
-        hist[i] = 0u;
-        if (i >= 2 * top) continue;
-        const unsigned long long v = i > 0 && i < buckets ? bounds[i] : ~0ull;      // (never reached: ids are below 2^32 - 1)
-        bound_key[i] = (uint32_t)(v >> 32); bound_id[i] = (uint32_t)v;
-        tied |= i > 0 && i + 1 < buckets && bounds[i + 1] >> 32 == v >> 32;
-    }
-    tied = __syncthreads_or(tied);
-    if (tied) {                     // uniform: many equal anchors.  How many bounds share a key
-        for (int i = tid; i < 2 * top; i += THREADS) {
-            const uint32_t v = bound_key[i];
-            int last = i;
-            for (int step = top; step > 0; step >>= 1) last += (last + step < buckets && bound_key[last + step] <= v) ? step : 0;
-            same[i] = (uint16_t)(i > 0 ? last - i + 1 : 1);
-        }
-        __syncthreads();
-    }
+    for (int i = tid; i < kSplitMaxBuckets; i += THREADS) hist[i] = 0u;
+    const StretchBounds<THREADS> bound(op_shift(A.bounds, op * A.op_ws), buckets, 1, bound_key, bound_id, same);
     uint32_t at[PER];               // stretch in the upper half, place among the tile's pairs of the stretch in the lower half
-#pragma unroll
-    for (int i = 0; i < PER; ++i) at[i] = 0u;
-    for (int step = top; step > 0; step >>= 1) {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) at[i] += bound_key[at[i] + step] < key[i] ? step : 0;
-    }
-    // the bounds of an equal key, if there are any, by their ids: a search among those that share it (in place of a second search among all of
-    // them, keys and ids; 2^22 anchors, us: 31 values 59 / 40, narrow clusters 53 / 36, 32 of a value 39 / 33, none equal 33 / 32)
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const uint32_t me = (uint32_t)(base + i * THREADS + tid), next = at[i] + 1 < (uint32_t)(2 * top) ? at[i] + 1 : at[i];
-        if (next != at[i] && bound_key[next] == key[i] && bound_id[next] <= me) {
-            uint32_t g = next;
-            if (tied) {
-                const uint32_t end = next + same[next];
-                uint32_t step = 1u;
-                while (next + step < end) step *= 2u;
-                for (; step > 0u; step >>= 1) g += (g + step < end && bound_id[g + step] <= me) ? step : 0u;
-            }
-            at[i] = g;
-        }
-    }
+    bound.find(key, at, [&](int i) { return (uint32_t)(base + i * THREADS + tid); });
 #pragma unroll
     for (int i = 0; i < PER; ++i)
         if (i * THREADS + tid < len) at[i] = (at[i] << 16) | atomicAdd(&hist[at[i]], 1u);
@@ -284,155 +188,6 @@ k_split_tiles(const SplitArgs A)
         if (i * THREADS + tid < len) out[i * THREADS + tid] = laid[i * THREADS + tid];
 }
 
-// Where (key, id) lies in the range of a stretch, as 64 bits from the top: (key - smallest key, id - smallest id) without the low bits that
-// no key differs in.
-struct StretchRange {
-    uint32_t kmin, imin;
-    int low_zeros, id_bits, up;
-    __device__ __forceinline__ StretchRange(uint32_t kmin_, uint32_t kmax, uint32_t imin_, uint32_t imax, uint32_t vary)
-        : kmin(kmin_), imin(imin_), low_zeros(vary ? __ffs((int)vary) - 1 : 0)
-    {
-        const uint32_t span = (kmax - kmin_) >> low_zeros, ispan = imax - imin_;
-        id_bits = ispan ? 32 - __clz((int)ispan) : 0;
-        const int bits = (span ? 32 - __clz((int)span) : 0) + id_bits;
-        up = bits > 0 ? 64 - bits : 0;
-    }
-    // The fraction times bins: the bin in the upper word, the fraction inside the bin below.
-    __device__ __forceinline__ unsigned long long place(uint32_t key, uint32_t id, uint32_t bins) const
-    {
-        const unsigned long long f = ((((unsigned long long)((key - kmin) >> low_zeros)) << id_bits) | (id - imin)) << up;
-        return (f >> 32) * bins + ((f & 0xFFFFFFFFull) * bins >> 32);
-    }
-};
-
-// A stretch beyond the capacity (the samples bound its length with a chance of up to 1e-3 per sort, see split_geom): the workgroup sorts it
-// in memory.  from: cnt pairs; to_id, to_pk: the stretch's place in the plan.  Leaves the pairs in from.
-//
-// First by the count that sorts a stretch in LDS: bins of the pairs' places in the range, the pairs laid out bin by bin, and every pair
-// ranked among its bin's; false, and the pairs as they were, where a bin holds too many for that.  lds: 2 * CAP words, part: THREADS / 64.
-constexpr uint32_t kMemoryBin = 32;
-template <int THREADS, int CAP>
-__device__ bool count_in_memory(uint2* from, uint32_t* to_id, float* to_pk, int cnt, const StretchRange& R, uint32_t* lds, uint32_t* part)
-{
-    constexpr int BINS = 2 * CAP, ROWS = BINS / THREADS, SIDE = 4;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    for (int i = tid; i < BINS; i += THREADS) lds[i] = 0u;
-    __syncthreads();
-    auto each = [&](auto load, auto use) {          // pairs of a thread side by side
-        for (int e0 = tid; e0 < cnt; e0 += SIDE * THREADS) {
-            uint2 v[SIDE];
-#pragma unroll
-            for (int u = 0; u < SIDE; ++u) v[u] = load(e0 + u * THREADS < cnt ? e0 + u * THREADS : cnt - 1);
-#pragma unroll
-            for (int u = 0; u < SIDE; ++u)
-                if (e0 + u * THREADS < cnt) use(v[u]);
-        }
-    };
-    auto unordered = [&](int e) { return from[e]; };
-    auto binned = [&](int e) { return make_uint2(__float_as_uint(to_pk[e]), to_id[e]); };
-    auto bin_of = [&](uint2 v) { return (uint32_t)(R.place(v.x, v.y, BINS) >> 32); };
-    each(unordered, [&](uint2 v) { atomicAdd(&lds[bin_of(v)], 1u); });
-    __syncthreads();
-    uint32_t* const row = lds + wave * (ROWS * 64) + lane;
-    uint32_t run = 0u, big = 0u;
-    for (int i = 0; i < ROWS; ++i) { const uint32_t c = row[i * 64]; run += c; big = c > big ? c : big; }
-    run = wave_scan(run);
-    if (lane == 63) part[wave] = run;
-    if (__syncthreads_or(big > kMemoryBin)) return false;
-    run = 0u;
-    for (int w = 0; w < wave; ++w) run += part[w];
-    for (int i = 0; i < ROWS; ++i) {
-        const uint32_t c = row[i * 64], inc = wave_scan(c);
-        row[i * 64] = run + inc - c;
-        run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-    }
-    __syncthreads();
-    each(unordered, [&](uint2 v) {
-        const uint32_t at = atomicAdd(&lds[bin_of(v)], 1u);
-        to_pk[at] = __uint_as_float(v.x); to_id[at] = v.y;
-    });
-    __threadfence_block();
-    __syncthreads();
-    each(binned, [&](uint2 v) {                     // a bin's counter stands at its end now, the one before at its start
-        const uint32_t b = bin_of(v), first = b ? lds[b - 1] : 0u, end = lds[b];
-        uint32_t at = first;
-        for (uint32_t q = first; q < end; ++q) {
-            const uint2 o = binned((int)q);
-            at += o.x < v.x || (o.x == v.x && o.y < v.y) ? 1u : 0u;
-        }
-        from[at] = v;
-    });
-    __threadfence_block();
-    __syncthreads();
-    return true;
-}
-
-// Otherwise by the 8-bit digits of (key, id) from the lowest up, stably; digits that do not vary are passed over.
-template <int THREADS>
-__device__ void sort_in_memory(uint2* from, uint32_t* to_id, float* to_pk, int cnt, uint32_t vary_key, uint32_t vary_id, uint32_t* lds)
-{
-    constexpr int WAVES = THREADS / 64;
-    uint32_t (*wcount)[256] = reinterpret_cast<uint32_t (*)[256]>(lds);     // [WAVES][256]
-    uint32_t* const next = lds + WAVES * 256;                                // [256]
-    uint32_t* const part = next + 256;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    bool in_plan = false;
-    for (int pass = 0; pass < 8; ++pass) {
-        const bool of_key = pass >= 4;
-        const int shift = (pass & 3) * 8;
-        if ((((of_key ? vary_key : vary_id) >> shift) & 255u) == 0u) continue;      // uniform
-        auto load = [&](int i) { return in_plan ? make_uint2(__float_as_uint(to_pk[i]), to_id[i]) : from[i]; };
-        auto digit = [&](uint2 v) { return ((of_key ? v.x : v.y) >> shift) & 255u; };
-        __syncthreads();
-        if (tid < 256) next[tid] = 0u;
-        __syncthreads();
-        for (int i = tid; i < cnt; i += THREADS) atomicAdd(&next[digit(load(i))], 1u);
-        __syncthreads();
-        uint32_t total;
-        const uint32_t c = tid < 256 ? next[tid] : 0u;
-        const uint32_t ex = block_scan<THREADS>(c, part, &total);
-        if (tid < 256) next[tid] = ex;
-        for (int i0 = 0; i0 < cnt; i0 += THREADS) {
-            for (int i = tid; i < WAVES * 256; i += THREADS) wcount[0][i] = 0u;
-            __syncthreads();
-            const bool ok = i0 + tid < cnt;
-            const uint2 v = load(ok ? i0 + tid : cnt - 1);
-            const uint32_t d = digit(v);
-            uint64_t peers = __ballot(ok);
-#pragma unroll
-            for (int bit = 0; bit < 8; ++bit) {
-                const bool set = (d >> bit) & 1u;
-                const uint64_t m = __ballot(set);
-                peers &= set ? m : ~m;
-            }
-            const uint32_t below = (uint32_t)__popcll(peers & ((1ull << lane) - 1ull));
-            if (ok && below == 0u) wcount[wave][d] = (uint32_t)__popcll(peers);
-            __syncthreads();
-            if (tid < 256) {
-                uint32_t run = next[tid];
-                for (int w = 0; w < WAVES; ++w) { const uint32_t t = wcount[w][tid]; wcount[w][tid] = run; run += t; }
-                next[tid] = run;
-            }
-            __syncthreads();
-            if (ok) {
-                const uint32_t dst = wcount[wave][d] + below;
-                if (in_plan) from[dst] = v; else { to_pk[dst] = __uint_as_float(v.x); to_id[dst] = v.y; }
-            }
-            __syncthreads();
-        }
-        __threadfence_block();
-        __syncthreads();
-        in_plan = !in_plan;
-    }
-    if (in_plan)
-        for (int i = tid; i < cnt; i += THREADS) from[i] = make_uint2(__float_as_uint(to_pk[i]), to_id[i]);
-    __threadfence_block();
-    __syncthreads();
-}
-
-constexpr int kSplitRounds = 6;
-constexpr uint32_t kSplitSmallGroup = 16;     // pairs that a bin may hold and still be put in order by comparing them
-
 // WHOLE: the anchors are one stretch, and are read where they are (buckets = 1, no tiles).
 template <int THREADS, int ITEMS, bool WHOLE>
 __global__ void __launch_bounds__(THREADS, 4)
@@ -442,8 +197,8 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
     __shared__ __align__(16) uint32_t buf[2 * CAP];        // counts of bins, then the pairs
     __shared__ uint32_t offset[MAX_TILES + 2];             // pairs of the stretch in the tiles before
     __shared__ uint32_t place[MAX_TILES + 1];                  // pair e of the stretch lies at place[tile] + e
-    __shared__ uint32_t part[WAVES], sums[WAVES];
-    __shared__ uint32_t s_key_and, s_key_or, s_key_min, s_key_max, s_id_min, s_id_max, s_big, s_long;
+    __shared__ uint32_t part[WAVES], s_long;
+    __shared__ StretchShared<THREADS> S;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int64_t op = blockIdx.y;
     const uint2* const pairs = op_shift(A.pairs, op * A.op_ws);
@@ -455,7 +210,7 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
     const int g = blockIdx.x, tiles = A.tiles, N = A.N;
 
     if (g == 0 && tid < 64) op_shift(A.counters, op * A.op_ws)[tid] = 0u;        // list lengths of the scans; the plan is valid
-    if (tid == 0) { s_key_and = 0xFFFFFFFFu; s_key_or = 0u; s_key_min = 0xFFFFFFFFu; s_key_max = 0u; s_id_min = 0xFFFFFFFFu; s_id_max = 0u; s_big = 0u; s_long = 0u; }
+    if (tid == 0) { S.init(); s_long = 0u; }
     // where the stretch lies in every tile, and where in the sorted sequence
     constexpr int LOADS = 4;
     int cnt = A.N, base = 0;
@@ -467,11 +222,11 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
             n = row[1] - lo;
         }
         const uint32_t inc_n = wave_scan(n), inc_lo = wave_scan(lo);
-        if (lane == 63) { part[wave] = inc_n; sums[wave] = inc_lo; }
+        if (lane == 63) { part[wave] = inc_n; S.sums[wave] = inc_lo; }
         __syncthreads();
         uint32_t before = 0u, all_n = 0u, all_lo = 0u;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) { before += w < wave ? part[w] : 0u; all_n += part[w]; all_lo += sums[w]; }
+        for (int w = 0; w < WAVES; ++w) { before += w < wave ? part[w] : 0u; all_n += part[w]; all_lo += S.sums[w]; }
         const uint32_t ex = before + inc_n - n;
         if (tid < tiles) { offset[tid] = ex; place[tid] = (uint32_t)(tid * tile_size) + lo - ex; }
         if (tid == 0) { offset[tiles] = offset[tiles + 1] = all_n; place[tiles] = 0u; }
@@ -558,136 +313,15 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
         }
         __syncthreads();
         uint32_t key[ITEMS], id[ITEMS];
-        uint32_t k_and = 0xFFFFFFFFu, k_or = 0u, k_min = 0xFFFFFFFFu, k_max = 0u, i_min = 0xFFFFFFFFu, i_max = 0u;
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            key[i] = id[i] = 0u;
-            if (i * THREADS < cnt) {                // uniform
-                const int e = i * THREADS + tid < cnt ? i * THREADS + tid : cnt - 1;      // (the last pair once more: it changes none of the sums)
-                if (WHOLE) {
-                    key[i] = split_anchor(A, op, e); id[i] = (uint32_t)e;
-                } else {
-                    const unsigned long long v = slot[e];
-                    key[i] = (uint32_t)(v >> 32); id[i] = (uint32_t)v;
-                }
-                k_and &= key[i]; k_or |= key[i];
-                k_min = key[i] < k_min ? key[i] : k_min; k_max = key[i] > k_max ? key[i] : k_max;
-                i_min = id[i] < i_min ? id[i] : i_min; i_max = id[i] > i_max ? id[i] : i_max;
+        uint32_t rank[ITEMS];
+        stretch_ranks<THREADS, ITEMS>(key, id, cnt, WHOLE ? split_anchor(A, op, 0) : (uint32_t)(slot[0] >> 32), A.id_bits, buf, S, rank, [&](int e, uint32_t& key_e, uint32_t& id_e) {
+            if (WHOLE) {
+                key_e = split_anchor(A, op, e); id_e = (uint32_t)e;
+            } else {
+                const unsigned long long v = slot[e];
+                key_e = (uint32_t)(v >> 32); id_e = (uint32_t)v;
             }
-        }
-        if (!WHOLE) __syncthreads();
-        const auto lesser = [](uint32_t p, uint32_t q) { return p < q ? p : q; };
-        const auto greater = [](uint32_t p, uint32_t q) { return p > q ? p : q; };
-        k_and = wave_fold(k_and, 0xFFFFFFFFu, [](uint32_t p, uint32_t q) { return p & q; });
-        k_or = wave_fold(k_or, 0u, [](uint32_t p, uint32_t q) { return p | q; });
-        k_min = wave_fold(k_min, 0xFFFFFFFFu, lesser); k_max = wave_fold(k_max, 0u, greater);
-        i_min = wave_fold(i_min, 0xFFFFFFFFu, lesser); i_max = wave_fold(i_max, 0u, greater);
-        if (lane == 63) {
-            atomicAnd(&s_key_and, k_and); atomicOr(&s_key_or, k_or); atomicMin(&s_key_min, k_min); atomicMax(&s_key_max, k_max);
-            atomicMin(&s_id_min, i_min); atomicMax(&s_id_max, i_max);
-        }
-        auto clear = [&](int count) {               // whole rows of quads of the scan below
-            const int quads = (count + 4 * THREADS - 1) / (4 * THREADS) * THREADS;
-            for (int i = tid; i < quads; i += THREADS) reinterpret_cast<uint4*>(buf)[i] = make_uint4(0u, 0u, 0u, 0u);
-        };
-        int bins = 2 * cnt < CAP ? 2 * cnt : CAP;
-        clear(bins);
-        __syncthreads();
-        const StretchRange R(s_key_min, s_key_max, s_id_min, s_id_max, s_key_or & ~s_key_and);
-        if (tid == 0) publish(s_key_min, s_key_max);
-        uint32_t left[ITEMS];                       // the fraction inside the bin, its first 32 bits
-        uint32_t seg[ITEMS], rank[ITEMS];           // first slot and size (upper half) of the group the pair belongs to; its place there
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            if (i * THREADS < cnt) {                // uniform
-                const unsigned long long place = R.place(key[i], id[i], (uint32_t)bins);
-                seg[i] = (uint32_t)(place >> 32);
-                left[i] = (uint32_t)place;
-                if (i * THREADS + tid < cnt) rank[i] = atomicAdd(&buf[seg[i]], 1u);
-            }
-        }
-        for (int round = 0; ; ++round) {
-            __syncthreads();
-            // exclusive scan of the counts, in quads; a wavefront owns a stretch of whole rows of 64 quads.  Start in the lower half of a
-            // word, count in the upper.
-            uint4* const quad = reinterpret_cast<uint4*>(buf) + lane;
-            const int rows = (bins + 4 * THREADS - 1) / (4 * THREADS);
-            uint32_t big = 0u, run = 0u;
-            for (int i = 0; i < rows; ++i) {
-                const uint4 c = quad[(wave * rows + i) * 64];
-                const uint32_t b01 = c.x > c.y ? c.x : c.y, b23 = c.z > c.w ? c.z : c.w;
-                big = b01 > big ? b01 : big; big = b23 > big ? b23 : big;
-                run += c.x + c.y + c.z + c.w;
-            }
-            run = wave_scan(run);
-            if (lane == 63) sums[wave] = run;
-            if (__any(big > kSplitSmallGroup) && lane == 0) s_big = (uint32_t)round + 1u;
-            __syncthreads();
-            run = 0u;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) run += w < wave ? sums[w] : 0u;
-            for (int i = 0; i < rows; ++i) {
-                const uint4 c = quad[(wave * rows + i) * 64];
-                const uint32_t sum = c.x + c.y + c.z + c.w, inc = wave_scan(sum), ex = run + inc - sum;
-                quad[(wave * rows + i) * 64] = make_uint4(ex | (c.x << 16), (ex + c.x) | (c.y << 16), (ex + c.x + c.y) | (c.z << 16), (ex + c.x + c.y + c.z) | (c.w << 16));
-                run += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-            }
-            const bool again = s_big == (uint32_t)round + 1u;      // uniform
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) {
-                if (i * THREADS + tid < cnt) {
-                    seg[i] = buf[seg[i]];
-                }
-            }
-            __syncthreads();
-            if (!again || round == kSplitRounds) break;
-            // groups that are still large are split into as many bins as they have pairs: from here on a bin is a slot
-            bins = cnt;
-            clear(bins);
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < ITEMS; ++i) {
-                if (i * THREADS + tid < cnt) {
-                    const uint32_t n = seg[i] >> 16;
-                    uint32_t bin = seg[i] & 0xFFFFu;
-                    if (n > kSplitSmallGroup) {
-                        const unsigned long long v = (unsigned long long)left[i] * n;
-                        bin += (uint32_t)(v >> 32);
-                        left[i] = (uint32_t)v;
-                    }
-                    rank[i] = atomicAdd(&buf[bin], 1u);
-                    seg[i] = bin;
-                }
-            }
-        }
-        // group by group into LDS; then a pair's place in its group by comparing, four pairs of a thread side by side
-#pragma unroll
-        for (int i = 0; i < ITEMS; ++i) {
-            if (i * THREADS + tid < cnt) slot[(seg[i] & 0xFFFFu) + rank[i]] = ((unsigned long long)key[i] << 32) | id[i];
-            else seg[i] = 0u;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i0 = 0; i0 < ITEMS; i0 += 4) {
-            if (i0 * THREADS < cnt) {               // uniform
-                uint32_t most = 0u;
-#pragma unroll
-                for (int i = i0; i < i0 + 4; ++i) { rank[i] = seg[i] & 0xFFFFu; most = seg[i] > most ? seg[i] : most; }
-                most >>= 16;
-                if (most < 2u) most = 0u;
-                for (uint32_t q = 0; q < most; ++q) {
-                    unsigned long long o[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) o[u] = slot[q < seg[i0 + u] >> 16 ? (seg[i0 + u] & 0xFFFFu) + q : (uint32_t)lane];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const unsigned long long me = ((unsigned long long)key[i0 + u] << 32) | id[i0 + u];
-                        rank[i0 + u] += (q < seg[i0 + u] >> 16 && o[u] < me) ? 1u : 0u;
-                    }
-                }
-            }
-        }
+        }, publish);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
@@ -713,14 +347,14 @@ k_split_sort(const SplitArgs A, int tile_size, int group_bits)
             k_min = v.x < k_min ? v.x : k_min; k_max = v.x > k_max ? v.x : k_max;
             i_min = v.y < i_min ? v.y : i_min; i_max = v.y > i_max ? v.y : i_max;
         }
-        atomicAnd(&s_key_and, k_and); atomicOr(&s_key_or, k_or); atomicMin(&s_key_min, k_min); atomicMax(&s_key_max, k_max);
-        atomicMin(&s_id_min, i_min); atomicMax(&s_id_max, i_max);
+        atomicAnd(&S.key_and, k_and); atomicOr(&S.key_or, k_or); atomicMin(&S.key_min, k_min); atomicMax(&S.key_max, k_max);
+        atomicMin(&S.id_min, i_min); atomicMax(&S.id_max, i_max);
         __threadfence_block();
         __syncthreads();
-        const uint32_t vary = s_key_or & ~s_key_and;
-        if (!count_in_memory<THREADS, CAP>(spare, ids + base, pk + base + 1, cnt, StretchRange(s_key_min, s_key_max, s_id_min, s_id_max, vary), buf, part)) {
-            const uint32_t id_span = s_id_max - s_id_min;      // the low digits of the ids up to where the smallest and the largest differ
-            sort_in_memory<THREADS>(spare, ids + base, pk + base + 1, cnt, vary, id_span ? 0xFFFFFFFFu >> __clz((int)(s_id_min ^ s_id_max)) : 0u, buf);
+        const uint32_t vary = S.key_or & ~S.key_and;
+        if (!count_in_memory<THREADS, CAP>(spare, ids + base, pk + base + 1, cnt, StretchRange(S.key_min, S.key_max, S.id_min, S.id_max, vary), buf, part)) {
+            const uint32_t id_span = S.id_max - S.id_min;      // the low digits of the ids up to where the smallest and the largest differ
+            sort_in_memory<THREADS>(spare, ids + base, pk + base + 1, cnt, vary, id_span ? 0xFFFFFFFFu >> __clz((int)(S.id_min ^ S.id_max)) : 0u, buf);
         }
         for (int e = tid; e < cnt; e += THREADS) {
             const uint2 v = spare[e];
@@ -807,6 +441,7 @@ hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t 
     A.starts = reinterpret_cast<uint16_t*>(A.sampled + G.samples);
     A.ids = ids; A.dh = dh; A.pk = pk; A.pk8 = pk8; A.counters = counters;
     A.tiles = (int)G.tiles; A.buckets = (int)G.buckets; A.samples = (int)G.samples; A.per_bound = (int)(G.samples / G.buckets);
+    A.id_bits = 1; while ((int64_t(1) << A.id_bits) < k + n) ++A.id_bits;
     A.op_a = op_a; A.op_b = op_b; A.op_ws = op_ws;
     const unsigned ops = (unsigned)operators;
     if (k + n <= kSplitWholeMax) {
