@@ -294,9 +294,10 @@ KERNEL_OF = {
     "scan_down.fwd": "k_scan_down, forward problem (reads x, writes y and the saved scans)",
     "scan_down.bwd": "k_scan_down, backward problem (reads gy, x and the saved scans, writes gx and the anchor gradient)",
     "radix_scatter": "k_onesweep_pass (one radix pass: reads the pairs once, writes them once)",
-    "permute_part.fwd": "k_part (partition levels: x into sorted order, y and the saved scans home)",
-    "permute_part.bwd": "k_part (partition levels: gy into sorted order, gx and gb home)",
-    "permute_part.rank": "k_part (partition levels of the inverse permutation)",
+    "deep_sort": "k_deep_sort (a unit of the sorted sequence gathered, sorted in LDS and written to the plan)",
+    "deep_pieces": "k_deep_distribute<true> (pairs of a bucket to its stretches)",
+    "permute_part.fwd": "k_part (second partition level: y and the saved scans home)",
+    "permute_part.bwd": "k_part (second partition level: gx and gb home)",
 }
 
 
@@ -313,24 +314,25 @@ def family_bytes(fam, spec, np, B):
     if fam == "sort_hist":
         return 4 * N, "the anchors read once"
     if fam == "decay":
-        if batch == 1 and N >= (1 << 22):
-            return 9 * N, "sorted anchors read (the sort's last pass wrote them), decays written, every eighth anchor pair once more"
         return 8 * N, "sorted anchors read (the sort's last pass wrote them), decays written"
+    if fam == "deep_tiles":
+        return 10 * N, "the anchors read, keys and 2-byte places written"
+    if fam == "deep_pieces":
+        return 16 * N, "keys and 2-byte places read, (key, id) pairs and 2-byte places written"
+    if fam == "deep_sort":
+        return 23 * N, "(key, id) pairs read; ids, anchors, decays, 2-byte places and every eighth anchor pair once more written"
     base, _, tag = fam.partition(".")
-    # batch 1 from 2^22 merged positions on: values travel between the caller's order and the sorted order as records
+    # batch 1 from 2^22 merged positions on: x and gy follow the sort's own passes into the sorted order, results travel home as records
     # (destination, value[, value]) through partition levels, and the scans work on plain arrays in sorted order
     routed = batch == 1 and N >= (1 << 22)
+    if routed and base in ("move_tiles", "move_pieces"):
+        return 10 * inj.get(tag, 0), "a value and its 2-byte place read, the value written"
+    if routed and base == "move_units":
+        return 4 * inj.get(tag, 0) + 6 * N, "the values and every position's 2-byte place read, the sorted-order array written whole"
     if routed and base == "permute_part":
-        if tag == "rank":
-            return 12 * N + 16 * N, "level 1: ids read, (id, position) pairs written; level 2: pairs read and written"
-        m_in, m_out = inj.get(tag, 0), res.get(tag, 0)
-        return 32 * m_in + 24 * m_out, ("the injected values: rank and value read, pairs written, pairs read and written (two levels); "
-                                        "the results: level 2 only (12 B records read and written; level 1 is the downsweep's)")
+        return 24 * res.get(tag, 0), "12-byte records read and written (the first level is the downsweep's)"
     if routed and base == "permute_final":
-        if tag == "rank":
-            return 8 * N + 4 * N, "pairs read, rank written"
-        m_in, m_out = inj.get(tag, 0), res.get(tag, 0)
-        return 8 * m_in + 4 * N + 12 * m_out + 8 * m_out, "pairs read, the sorted-order array written whole; result records read, both outputs written"
+        return 20 * res.get(tag, 0), "12-byte records read, both outputs written"
     if tag not in inj:
         return None, None
     if routed and base == "scan_reduce":
@@ -464,7 +466,7 @@ def measure(spec, steps, warmup, torch, np, B):
     out = {
         "ms_per_step": round(ms_per_step, 4), "value": elements / (ms_per_step * 1e-3),
         "config": {"workload": spec["name"], "k": k, "n": n, "batch": batch, "anchors": spec["anchors"],
-                   "pass": spec["passname"], "sort": ("radix sort" if N > 1 << 22 else "sort by samples") + " inside every step",
+                   "pass": spec["passname"], "sort": ("radix sort" if N > 1 << 22 and batch > 1 else "sort by samples") + " inside every step",
                    "workspace_bytes": spec["ws"].numel(), "device_bytes_peak": torch.cuda.max_memory_allocated()},
         "roofline": roofline,
         "families_ms_one_step": {f: round(v[0], 4) for f, v in sorted(families.items(), key=lambda kv: -kv[1][0])[:16]},

@@ -129,9 +129,10 @@ Plan plan_of(const Layout& L, char* ws)
 }
 
 // ----------------------------------------------------------------------------
-// Batch 1 with many rows: x and gy reach the sorted order, and the results the caller's order, as records through
-// partition passes (permute_kernels.hip) instead of by one random access per value.  Below g_permute_min merged
-// positions the tables fit the device's caches and the random accesses are as fast.
+// Batch 1 with many rows: x and gy reach the sorted order along the passes of the sort (deep_sort_kernels.hip), and the results the
+// caller's order as records through partition passes (permute_kernels.hip), instead of by one random access per value.  Below
+// g_permute_min merged positions the tables fit the device's caches and the random accesses are as fast (us, routed / gathered, n = k,
+// forward + backward: 2^20 260 / 208, 2^20.5 301 / 303, 2^21 329 / 379, 2^22 516 / 732; forward alone: 2^20.5 208 / 170, 2^21 225 / 222, 2^21.3 255 / 331).
 // ----------------------------------------------------------------------------
 std::atomic<int64_t> g_permute_min{int64_t(1) << 22};
 
@@ -150,17 +151,27 @@ PermuteJob permute_job(const Layout& L, char* ws, const char* tag)
     return J;
 }
 
-// dst[rank[first_id + i]] = src[i * ld] for i < count, zero at every other sorted position: rows of the caller's matrix
+DeepPlan deep_plan(const Layout& L, char* ws)
+{
+    DeepPlan D{};
+    auto u16 = [&](size_t o) { return reinterpret_cast<uint16_t*>(ws + o); };
+    D.from1 = u16(L.off_from1); D.slot2 = u16(L.off_slot2); D.slot3 = u16(L.off_slot3); D.slot3_high = u16(L.off_slot3_high);
+    D.before = reinterpret_cast<uint32_t*>(ws + L.off_before); D.start1 = u16(L.off_start1); D.starts2 = u16(L.off_starts2);
+    D.bucket_base = reinterpret_cast<uint32_t*>(ws + L.off_deep_bases);
+    D.piece_base = D.bucket_base + L.deep.buckets + 1;
+    D.piece_tile = D.piece_base + L.deep.buckets + 1;
+    D.unit_count = reinterpret_cast<uint32_t*>(ws + L.off_units);
+    D.units = reinterpret_cast<uint4*>(D.unit_count) + 1;
+    return D;
+}
+
+// dst[sorted position of first_id + i] = src[i * ld] for i < count, zero at every other sorted position: rows of the caller's matrix
 // (the inputs: first_id = k; the outputs: first_id = 0) into sorted order.
 int rows_to_sorted(const Layout& L, char* ws, const float* src, int64_t ld, int64_t first_id, int64_t count, float* dst,
                    const char* tag, hipStream_t st)
 {
-    PermuteJob J = permute_job(L, ws, tag);
-    J.source = PermuteJob::kValues;
-    J.rank = reinterpret_cast<const uint32_t*>(ws + L.off_rank) + first_id;
-    J.val0 = src; J.ld_val = ld; J.source_count = count; J.dest_count = L.N;
-    J.values = 1; J.out0 = dst; J.ld0 = 1;
-    LAPLEX_HIP(launch_permute(J, st));
+    LAPLEX_HIP(launch_deep_move(L.deep, deep_plan(L, ws), src, ld, first_id, first_id + count, reinterpret_cast<float*>(ws + L.off_by_tile),
+                                reinterpret_cast<float*>(ws + L.off_by_piece), dst, tag, st));
     return LAPLEX_OK;
 }
 
@@ -171,8 +182,7 @@ int scan_and_send_home(ScanProblem& p, const Layout& L, char* ws, bool want_firs
                        float* out0, int64_t ld0, float* out1, int64_t ld1, hipStream_t st)
 {
     PermuteJob J = permute_job(L, ws, p.tag);
-    J.source = PermuteJob::kRows;
-    J.source_count = L.N; J.dest_count = (int64_t)p.res_hi - (int64_t)p.res_lo;
+    J.dest_count = (int64_t)p.res_hi - (int64_t)p.res_lo;
     J.values = (want_first && want_second) ? 2 : 1;
     J.out0 = out0; J.ld0 = ld0; J.out1 = out1; J.ld1 = ld1;
     PartEmit E;
@@ -218,6 +228,8 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
     if (L.N <= kSmallMax) {      // (the promises of sorted anchors are not needed here)
         LAPLEX_HIP(launch_small(small_args(a, k, b, n, tau, P, L, flags), 1, st));      // no scan problem: the sort alone
         LAPLEX_HIP(launch_decay(nullptr, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
+    } else if (use_permute(L)) {      // (anchors that arrive sorted as well: values move along the way of this sort)
+        LAPLEX_HIP(launch_deep_sort(a, k, b, n, tau, L.deep, deep_plan(L, ws), ws + L.off_deep, P.ids, P.dh, P.pk, P.pk8, counters, st));
     } else if (both_sorted) {
         LAPLEX_HIP(launch_merge(a, k, b, n, tau, keys0, P.ids, st));
         LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
@@ -228,14 +240,6 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
         LAPLEX_HIP(launch_onesweep_sort(a, k, b, n, tau, pair0, pair1, P.ids, P.pk, small,
                                         reinterpret_cast<unsigned long long*>(ws + L.off_status), st));
         LAPLEX_HIP(launch_decay(nullptr, small, P.dh, P.pk, P.pk8, counters, L.N, st));
-    }
-    if (use_permute(L)) {        // the inverse permutation, part of the plan: rank[ids[j]] = j
-        PermuteJob J = permute_job(L, ws, "rank");
-        J.source = PermuteJob::kRowIndex;
-        J.ids = P.ids; J.source_count = L.N; J.dest_count = L.N;
-        J.values = 1; J.out0 = reinterpret_cast<float*>(ws + L.off_rank); J.ld0 = 1;
-        J.poison = nullptr;          // positions, not values: an invalid plan shows in the results
-        LAPLEX_HIP(launch_permute(J, st));
     }
     return LAPLEX_OK;
 }

@@ -21,6 +21,31 @@ inline int64_t sort_tiles_of(int64_t N) { return (N + kSortTile - 1) / kSortTile
 // Up to this many merged positions the anchors are sorted by samples, tiles and stretches (split_sort_kernels.hip).
 constexpr int64_t kSplitSortMax = int64_t(1) << 22;
 size_t split_sort_words(int64_t N);                     // scratch words that takes besides the pair buffers
+// Batch 1, many anchors: sorted by samples in two distributions, and values moved into the sorted order along the same way
+// (deep_sort_kernels.hip).  Tiles and pieces of kDeepTile positions; buckets (at most 1024) of per_bucket stretches each.
+constexpr int kDeepTile = 16384;
+struct DeepGeom {
+    int64_t N;
+    int buckets, per_bucket, samples_per, capacity;      // capacity: pairs of a unit (consecutive stretches sorted together), but for a longer stretch
+    int64_t tiles, max_pieces, max_units, stretches, samples;
+};
+DeepGeom deep_geom(int64_t N);
+size_t deep_scratch_bytes(const DeepGeom& G);           // the sort's scratch
+// What the plan holds of it besides the sorted order itself.
+struct DeepPlan {
+    uint16_t* from1;             // [N] by place in the tile layout: index inside the tile
+    uint16_t* slot2;             // [N] by place in the bucket: place inside the piece's layout
+    uint16_t* slot3;             // [N] by place in the unit as gathered: place in it as sorted; slot3_high: upper halves, only for units that a
+    uint16_t* slot3_high;        //     workgroup's LDS does not hold
+    uint32_t* before;            // [buckets][tiles] pairs of the bucket in earlier tiles
+    uint16_t* start1;            // [buckets][tiles] place of the bucket's run in the tile's layout
+    uint16_t* starts2;           // [max_pieces][per_bucket + 1] places of the stretches' runs in a piece's layout
+    uint32_t* bucket_base;       // [buckets + 1] first sorted position
+    uint32_t* piece_base;        // [buckets + 1] first piece
+    uint32_t* piece_tile;        // [max_pieces] the tile that holds the piece's first pair
+    uint32_t* unit_count;        // [1]
+    uint4* units;                // [max_units] (bucket << 20 | first stretch << 10 | last stretch, first sorted position, pairs, -)
+};
 // Small state of one sort, u32 words: [0, 1024) histogram of the four digits; then the per-pass tile
 // tickets, the error flag and the histogram's done counter in one cache line, and the mask of the passes that run in a line of its own.
 constexpr int kSortTicketWord = 1024;
@@ -69,7 +94,7 @@ constexpr int kSpineSuperTiles = 32;   // tiles summed up together by the spine 
 // ----------------------------------------------------------------------------
 constexpr int kPermuteWindowBits = 14;
 constexpr int kPermuteMaxBucketBits = 9;
-bool permute_supported(int64_t source_count, int64_t dest_count);      // destinations fit two partition levels
+bool permute_supported(int64_t dest_count);      // destinations fit two partition levels
 size_t permute_cursor_words(int64_t dest_count);                        // the buckets' cursors of both levels
 // records that a level's output array must hold for `dest_count` destinations: whole windows when one level fills
 // the windows directly (at most 2^9 of them), else whole regions of 2^9 windows; and whether there are two levels
@@ -184,7 +209,10 @@ struct Layout {
     size_t off_pair = 0;         // f32[max(result rows)][2], batch 1 only
     // batch 1 beyond the small path: the routes through sorted order without random accesses
     bool permute = false;        // the regions below exist
-    size_t off_rank = 0;         // u32[N]     plan: rank[id] = sorted position of anchor id
+    DeepGeom deep{};             // the sort of these problems, and of its plan (DeepPlan):
+    size_t off_from1 = 0, off_slot2 = 0, off_slot3 = 0, off_slot3_high = 0, off_before = 0, off_start1 = 0, off_starts2 = 0, off_units = 0, off_deep_bases = 0;
+    size_t off_deep = 0;         // scratch, sort view: the sort's own
+    size_t off_by_tile = 0, off_by_piece = 0;      // f32[N] each, scratch: values on their way into the sorted order
     size_t off_pk8 = 0;          // float2[(N+2)/8 + 1]  plan: (pk[8m], pk[8m + 1]), the anchors the sorted-order kernels need
     size_t off_rec_dv[2] = {0, 0}, off_rec_v1[2] = {0, 0};   // records of the two partition levels: (destination, value) pairs, second values
     size_t off_pt_cursors = 0;   // u32[permute_cursor_words]  records placed per bucket, both levels
@@ -204,9 +232,17 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     L.off_z = o;    o = align_up(o + sizeof(float) * (size_t)zrows * (size_t)batch);
     const size_t stage_bytes = batch <= kStageMaxBatch ? sizeof(float) * (size_t)N * (size_t)batch : 0;
     L.off_xs = o;   o = align_up(o + stage_bytes);
-    L.permute = permute_regions && batch == 1 && N > kSmallMax && permute_supported(N, N);
-    L.off_rank = o;
-    if (L.permute) o = align_up(o + sizeof(uint32_t) * (size_t)N);
+    L.permute = permute_regions && batch == 1 && N > kSmallMax && permute_supported(N);
+    if (L.permute) {
+        L.deep = deep_geom(N);
+        const DeepGeom& G = L.deep;
+        auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
+        L.off_from1 = take(2 * (size_t)N); L.off_slot2 = take(2 * (size_t)N); L.off_slot3 = take(2 * (size_t)N); L.off_slot3_high = take(2 * (size_t)N);
+        L.off_before = take(4 * (size_t)G.buckets * (size_t)G.tiles); L.off_start1 = take(2 * (size_t)G.buckets * (size_t)G.tiles);
+        L.off_starts2 = take(2 * (size_t)G.max_pieces * (size_t)(G.per_bucket + 1));
+        L.off_units = take(16 * ((size_t)G.max_units + 1));
+        L.off_deep_bases = take(4 * (2 * (size_t)(G.buckets + 1) + (size_t)G.max_pieces));
+    }
     L.off_pk8 = o;
     if (L.permute) o = align_up(o + 2 * sizeof(float) * ((size_t)(N + 2) / 8 + 1));
     L.off_scratch = o;
@@ -220,6 +256,8 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     L.off_status = s;     s = align_up(s + sizeof(uint64_t) * 2 * (size_t)L.status_words);   // look-back words, two passes' worth
     if (N <= kSplitSortMax && s < L.off_status + sizeof(uint32_t) * split_sort_words(N)) s = align_up(L.off_status + sizeof(uint32_t) * split_sort_words(N));
     L.off_sort_small = s; s = align_up(s + sizeof(uint32_t) * kSortSmallWords);            // global histogram, tickets, error, pass mask
+    L.off_deep = L.off_pair0;
+    if (L.permute) { const size_t d = align_up(L.off_deep + deep_scratch_bytes(L.deep)); s = s > d ? s : d; }
 
     // scan view
     size_t c = o;
@@ -256,16 +294,21 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
     const int64_t pair_rows = zrows > N - zrows ? zrows : N - zrows;
     if (batch == 1) c = align_up(L.off_pair + sizeof(float) * 2 * (size_t)pair_rows);
     L.total = s > c ? s : c;
-    if (L.permute) {
-        size_t q = align_up(L.total);
+    if (L.permute) {      // beside the scan view, where the pairs above would lie: values on their way in, then records on their way out
+        size_t q = L.off_pair;
+        L.off_by_tile = q; q = align_up(q + sizeof(float) * (size_t)N);
+        L.off_by_piece = q; q = align_up(q + sizeof(float) * (size_t)N);
+        L.total = L.total > q ? L.total : q;
+        q = L.off_pair;
         const int64_t side = zrows > N - zrows ? zrows : N - zrows;      // result rows of a problem: at most this many
-        const size_t cap1 = (size_t)permute_capacity(N), cap2 = (size_t)permute_capacity(side);
-        for (int lv = 0; lv < 2; ++lv) {     // (the second level's buffers only where some move has two levels)
-            L.off_rec_dv[lv] = q; if (lv == 0 || permute_two_levels(N)) q = align_up(q + 2 * sizeof(uint32_t) * cap1);
-            L.off_rec_v1[lv] = q; if (lv == 0 || permute_two_levels(side)) q = align_up(q + sizeof(float) * cap2);
+        const size_t cap = (size_t)permute_capacity(side);
+        for (int lv = 0; lv < 2; ++lv) {     // (the second level's buffers only where a move has two levels)
+            const bool there = lv == 0 || permute_two_levels(side);
+            L.off_rec_dv[lv] = q; if (there) q = align_up(q + 2 * sizeof(uint32_t) * cap);
+            L.off_rec_v1[lv] = q; if (there) q = align_up(q + sizeof(float) * cap);
         }
-        L.off_pt_cursors = q; q = align_up(q + sizeof(uint32_t) * permute_cursor_words(N));
-        L.total = q;
+        L.off_pt_cursors = q; q = align_up(q + sizeof(uint32_t) * permute_cursor_words(side));
+        L.total = L.total > q ? L.total : q;
     }
     L.off_small = align_up(L.total);
     if (N <= kSmallMax) L.total = align_up(L.off_small + sizeof(float) * (size_t)N * (size_t)batch);
@@ -305,6 +348,13 @@ hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t 
                              uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters,
                              int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st);
 
+// The same order for batch 1 beyond the small path, in two distributions; writes the whole plan, DeepPlan included.
+hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, const DeepGeom& G, const DeepPlan& P, char* scratch,
+                            uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters, hipStream_t st);
+// dst[sorted position of id] = src[(id - lo) * ld] for lo <= id < hi, zero at every other position; by_tile, by_piece: N floats of scratch each.
+hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const float* src, int64_t ld, int64_t lo, int64_t hi,
+                            float* by_tile, float* by_piece, float* dst, const char* tag, hipStream_t st);
+
 // Both inputs ascending: merged keys/ids in one pass (ties: a first).
 hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, float tau,
                         uint32_t* keys, uint32_t* ids, hipStream_t st);
@@ -342,29 +392,19 @@ struct PartEmit {
     int64_t dest_count = 0;           // destinations are below this
 };
 
-// One move of values between the caller's order and the sorted order (launch_permute).
-//   kRows:     source row j of the sorted sequence goes to destination ids[j] - lo if lo <= ids[j] < hi (results back to
-//              the caller's order); its values are val0[j * ld_val] (and val1[j * ld_val])
-//   kRowIndex: destination ids[j], value j itself (as a 32-bit word): the inverse permutation
-//   kValues:   source element i goes to destination rank[i] with value val0[i * ld_val] (the caller's rows into sorted order)
-// The last pass writes out0[d * ld0] (and out1[d * ld1]) for EVERY destination d < dest_count: zero where no record arrived.
+// Results home: row j of the sorted sequence goes to destination ids[j] - lo of the caller's order, as a record (destination, value[, value])
+// through partition levels.  The producer (the batch-1 downsweep) places the records of the first level itself: permute_begin clears the
+// cursors and says where they go; permute_finish runs what follows.  The last pass writes out0[d * ld0] (and out1[d * ld1]) for every
+// destination d < dest_count: zero where no record arrived.
 struct PermuteJob {
-    enum Source { kRows = 0, kRowIndex = 1, kValues = 2 };
-    int source = kRows;
-    const uint32_t* ids = nullptr; uint32_t lo = 0, hi = 0;
-    const uint32_t* rank = nullptr;
-    const float* val0 = nullptr; const float* val1 = nullptr; int64_t ld_val = 1;
-    int64_t source_count = 0, dest_count = 0;
+    int64_t dest_count = 0;
     int values = 1;                                    // values per record: 1 or 2
     float* out0 = nullptr; int64_t ld0 = 1; float* out1 = nullptr; int64_t ld1 = 1;
     uint2* rec_dv[2] = {nullptr, nullptr}; float* rec_v1[2] = {nullptr, nullptr};   // records of the two levels
     uint32_t* cursors = nullptr;                       // permute_cursor_words(dest_count) words of scratch
-    const uint32_t* poison = nullptr;                  // nonzero: every value written becomes a NaN (null: never)
+    const uint32_t* poison = nullptr;                  // nonzero: every value written becomes a NaN
     const char* tag = "move";                          // names the timing families permute_part.<tag>, permute_final.<tag>
 };
-hipError_t launch_permute(const PermuteJob& J, hipStream_t st);
-// The same in two halves, for a producer that places the records of the first level itself (the batch-1 downsweep):
-// permute_begin clears the cursors and says where the first level's records go; permute_finish runs what follows it.
 hipError_t permute_begin(const PermuteJob& J, PartEmit* first_level, hipStream_t st);
 hipError_t permute_finish(const PermuteJob& J, hipStream_t st);
 

@@ -1,16 +1,13 @@
-// Moving values between the caller's order and the sorted order of the plan without random accesses
-// (the gather of S4 and the scatter of S7 at batch 1; Sec. 3 "Complexity": the permutation is the price
-// of sorting arbitrary anchors).
+// Results of batch 1 back to the caller's order without random accesses (the scatter of S7; Sec. 3 "Complexity": the permutation is the
+// price of sorting arbitrary anchors).
 //
-// At batch 1 a row is one float.  Fetching x[id] for a billion sorted positions costs a 128-byte line
-// per float, and storing a result at y[id] a partial line; both are bound by the number of memory
-// transactions, not by bytes.  Here every value travels as a record (destination, value[, value]) through
-// at most two partition passes, each of which reads its records once and writes them once in runs, and a
-// last pass that places the records of one window of 16384 consecutive destinations inside LDS and writes
-// the window out whole:
+// At batch 1 a row is one float.  Storing a result at y[id] costs a partial line and is bound by the number of memory
+// transactions, not by bytes.  Here every result travels as a record (destination, value[, value]) through at most two partition
+// levels, each of which reads its records once and writes them once in runs, and a last pass that places the records of one window of
+// 16384 consecutive destinations inside LDS and writes the window out whole:
 //
-//   level 1   records -> up to 512 buckets by the top bits of the destination (only when there are more
-//             than 512 windows)
+//   level 1   the batch-1 downsweep places its results itself, into up to 512 buckets by the top bits of the destination (or, with
+//             at most 512 windows, into the windows)
 //   level 2   the records of one bucket -> its (up to 512) windows
 //   final     one workgroup per window: scatter inside LDS, coalesced store (destinations that no record
 //             names read as zero)
@@ -22,6 +19,7 @@
 // bucket's cursor (device scope).  Measured on this device: 512 such atomics per tile of 64 KB, all tiles on
 // the same 512 words, cost 15 % on top of a plain copy of the tile.  The order of the records inside a bucket
 // depends on the order in which the atomics land; the result does not (every destination is written once).
+// (The way in, x and gy into the sorted order, follows the sort's own passes: deep_sort_kernels.hip.)
 #include "permute_tile.h"
 
 #include <string>
@@ -34,23 +32,16 @@ constexpr int kPtThreads = 1024;
 constexpr int kPtPer = 16;                               // records per thread
 constexpr int kPtTile = kPtThreads * kPtPer;             // 16384 records per tile: a run is 32 records on average with 512 buckets
 static_assert(kPtTile == (1 << kPermuteWindowBits), "a tile of level 2 is one window's worth of records");
-constexpr int kFromRecords = 3;                          // source of level 2 (beside PermuteJob::Source)
 
 struct PartArgs {
-    int mode;                      // PermuteJob::Source, or kFromRecords
-    // sources
-    const uint32_t* ids; uint32_t lo, hi;               // rows: destination = ids[j] - lo for lo <= ids[j] < hi
-    const uint32_t* rank;                               // values: destination = rank[i]
-    const float* val0; const float* val1; int64_t ld_val;
-    int64_t count;                                      // source rows / values
     const uint2* in_dv; const float* in_v1;             // records of the level before: (destination, first value), second value ...
     const uint32_t* in_len;                             // ... and how many each of its buckets holds (its cursors)
-    int chain_bits;                // level 2: a bucket of the level before is read by 2^chain_bits consecutive tiles; -1: tiles over the source
+    int chain_bits;                // a bucket of the level before is read by 2^chain_bits consecutive tiles
     PartEmit emit;                 // this level
 };
 
-// One partition level.  NV: values per record (1 or 2).
-template <int MODE, int NV>
+// The second partition level.  NV: values per record (1 or 2).
+template <int NV>
 __global__ void __launch_bounds__(kPtThreads)
 k_part(const PartArgs A)
 {
@@ -58,22 +49,15 @@ k_part(const PartArgs A)
     __shared__ uint2 sdv[kPtTile];                  // the tile's records, bucket by bucket: (destination, first value); then the second values
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    const int64_t chain = A.chain_bits < 0 ? 0 : tile >> A.chain_bits;
-    const int64_t chunk = A.chain_bits < 0 ? tile : tile & (((int64_t)1 << A.chain_bits) - 1);
+    const int64_t chain = tile >> A.chain_bits;
+    const int64_t chunk = tile & (((int64_t)1 << A.chain_bits) - 1);
 
     // the tile's source records
-    int64_t src0, src1;
-    if (MODE == kFromRecords) {
-        uint32_t len = A.in_len[chain];                         // records of this bucket of the level before
-        const uint32_t cap = 1u << (A.chain_bits + kPermuteWindowBits);
-        len = len < cap ? len : cap;                            // (a valid plan never fills a region beyond its size)
-        const int64_t base = chain << A.chain_bits << kPermuteWindowBits;     // 2^chain_bits tiles cover the bucket's region
-        src0 = base + chunk * kPtTile;
-        src1 = base + len < src0 + kPtTile ? base + len : src0 + kPtTile;
-    } else {
-        src0 = tile * kPtTile;
-        src1 = A.count < src0 + kPtTile ? A.count : src0 + kPtTile;
-    }
+    uint32_t bucket_len = A.in_len[chain];                  // records of this bucket of the level before
+    const uint32_t cap = 1u << (A.chain_bits + kPermuteWindowBits);
+    bucket_len = bucket_len < cap ? bucket_len : cap;       // (a valid plan never fills a region beyond its size)
+    const int64_t base = chain << A.chain_bits << kPermuteWindowBits;     // 2^chain_bits tiles cover the bucket's region
+    const int64_t src0 = base + chunk * kPtTile, src1 = base + bucket_len < src0 + kPtTile ? base + bucket_len : src0 + kPtTile;
     if (src0 >= src1) return;
 
     uint32_t dest[kPtPer];
@@ -84,30 +68,10 @@ k_part(const PartArgs A)
         const int64_t j = src0 + i * kPtThreads + tid;
         const bool in = j < src1;
         const int64_t jc = in ? j : src0;
-        bool ok;
-        if (MODE == kFromRecords) {
-            const uint2 dv = A.in_dv[jc];
-            dest[i] = dv.x; v0[i] = __uint_as_float(dv.y);
-            if (NV == 2) v1[i] = A.in_v1[jc];
-            ok = in;
-        } else if (MODE == PermuteJob::kRows) {
-            const uint32_t id = A.ids[jc];
-            ok = in && id >= A.lo && id < A.hi;
-            dest[i] = id - A.lo;
-            v0[i] = A.val0[jc * A.ld_val];
-            if (NV == 2) v1[i] = A.val1[jc * A.ld_val];
-        } else if (MODE == PermuteJob::kRowIndex) {
-            dest[i] = A.ids[jc];
-            v0[i] = __uint_as_float((uint32_t)jc);
-            ok = in;
-        } else {
-            dest[i] = A.rank[jc];
-            v0[i] = A.val0[jc * A.ld_val];
-            if (NV == 2) v1[i] = A.val1[jc * A.ld_val];
-            ok = in;
-        }
-        ok = ok && (int64_t)dest[i] < A.emit.dest_count;      // always true for a valid plan; keeps every store inside the arrays
-        okmask |= ok ? 1u << i : 0u;
+        const uint2 dv = A.in_dv[jc];
+        dest[i] = dv.x; v0[i] = __uint_as_float(dv.y);
+        if (NV == 2) v1[i] = A.in_v1[jc];
+        okmask |= in && (int64_t)dest[i] < A.emit.dest_count ? 1u << i : 0u;      // (the latter always, for a valid plan)
     }
     PartTicket<kPtPer> K;
     partition_reserve<kPtThreads, kPtPer>(A.emit, chain, dest, okmask, S, K);
@@ -123,10 +87,8 @@ struct FinalArgs {
 };
 
 // The last pass: one workgroup per window of 16384 consecutive destinations.  The windows are taken from the last one down: the level
-// before it fills them in ascending order, so the records it wrote last are still in the 256 MB memory-side cache, and the scan's reduce,
-// which reads what this pass writes in ascending order, finds the low windows there (us, ascending / descending, 2^25 positions: this pass
-// 74 -> 66 with one value, 82 -> 73 with two, k_seq_reduce 95 -> 77; forward + backward at 2^24 x 2^24 2510 -> 2446, 30e6 x 25e6 3918 -> 3822,
-// 2^27 x 2^27, where an eighth of a pass fits, 17159 -> 17125).
+// before it fills them in ascending order, so the records it wrote last are still in the 256 MB memory-side cache (us, ascending /
+// descending, 2^25 positions, two values: 82 -> 73).
 template <int NV>
 __global__ void __launch_bounds__(kPtThreads)
 k_part_final(const FinalArgs A)
@@ -170,23 +132,11 @@ k_zero_words(uint32_t* __restrict__ p, int64_t count)
 
 int ceil_log2(int64_t v) { int l = 0; while (((int64_t)1 << l) < v) ++l; return l; }
 
-template <int NV>
-void launch_level(const PartArgs& A, int64_t tiles, const char* family, hipStream_t st)
-{
-    const dim3 grid((unsigned)tiles), block(kPtThreads);
-    switch (A.mode) {
-        case PermuteJob::kRows:     LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_part<PermuteJob::kRows, NV>), grid, block, 0, st, A)); break;
-        case PermuteJob::kRowIndex: LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_part<PermuteJob::kRowIndex, NV>), grid, block, 0, st, A)); break;
-        case PermuteJob::kValues:   LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_part<PermuteJob::kValues, NV>), grid, block, 0, st, A)); break;
-        default:                    LAPLEX_TIMED(family, st, hipLaunchKernelGGL((k_part<kFromRecords, NV>), grid, block, 0, st, A)); break;
-    }
-}
-
 }  // namespace
 
-bool permute_supported(int64_t source_count, int64_t dest_count)
+bool permute_supported(int64_t dest_count)
 {
-    if (source_count <= 0 || dest_count <= 0) return false;
+    if (dest_count <= 0) return false;
     const int64_t windows = (dest_count + (1 << kPermuteWindowBits) - 1) >> kPermuteWindowBits;
     return ceil_log2(windows) <= 2 * kPermuteMaxBucketBits;
 }
@@ -243,33 +193,17 @@ hipError_t permute_finish(const PermuteJob& J, hipStream_t st)
     F.in_dv = J.rec_dv[0]; F.in_v1 = J.rec_v1[0];
     if (g.p1 > 0) {      // level 2: each bucket of level 1 -> its windows, records into the second buffer
         PartArgs A{};
-        A.mode = kFromRecords;
         A.in_dv = J.rec_dv[0]; A.in_v1 = J.rec_v1[0]; A.in_len = cursor1;
         A.chain_bits = g.p2;
         A.emit.bucket_bits = g.p2; A.emit.shift = kPermuteWindowBits; A.emit.region_shift = kPermuteWindowBits;
         A.emit.out_dv = J.rec_dv[1]; A.emit.out_v1 = J.rec_v1[1]; A.emit.cursor = cursor2; A.emit.dest_count = J.dest_count;
-        if (J.values == 2) launch_level<2>(A, g.tiles2, f1.c_str(), st); else launch_level<1>(A, g.tiles2, f1.c_str(), st);
+        if (J.values == 2) LAPLEX_TIMED(f1.c_str(), st, hipLaunchKernelGGL((k_part<2>), dim3((unsigned)g.tiles2), dim3(kPtThreads), 0, st, A));
+        else LAPLEX_TIMED(f1.c_str(), st, hipLaunchKernelGGL((k_part<1>), dim3((unsigned)g.tiles2), dim3(kPtThreads), 0, st, A));
         F.in_dv = J.rec_dv[1]; F.in_v1 = J.rec_v1[1];
     }
     if (J.values == 2) LAPLEX_TIMED(f2.c_str(), st, hipLaunchKernelGGL((k_part_final<2>), dim3((unsigned)g.windows), dim3(kPtThreads), 0, st, F));
     else LAPLEX_TIMED(f2.c_str(), st, hipLaunchKernelGGL((k_part_final<1>), dim3((unsigned)g.windows), dim3(kPtThreads), 0, st, F));
     return hipGetLastError();
-}
-
-hipError_t launch_permute(const PermuteJob& J, hipStream_t st)
-{
-    if (J.source_count <= 0 || J.dest_count <= 0) return hipSuccess;
-    PartArgs A{};
-    hipError_t e = permute_begin(J, &A.emit, st);
-    if (e != hipSuccess) return e;
-    A.mode = J.source;
-    A.ids = J.ids; A.lo = J.lo; A.hi = J.hi; A.rank = J.rank;
-    A.val0 = J.val0; A.val1 = J.val1; A.ld_val = J.ld_val; A.count = J.source_count;
-    A.chain_bits = -1;
-    const std::string f1 = std::string("permute_part.") + J.tag;
-    const int64_t tiles1 = (J.source_count + kPtTile - 1) / kPtTile;
-    if (J.values == 2) launch_level<2>(A, tiles1, f1.c_str(), st); else launch_level<1>(A, tiles1, f1.c_str(), st);
-    return permute_finish(J, st);
 }
 
 }  // namespace laplex

@@ -689,3 +689,88 @@ def test_plain_calls_on_the_plans_of_a_sum(oracle, r, k, n, batch):
     torch.cuda.synchronize()
     ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
     assert_close("y", y.cpu().numpy(), ref, tol)
+
+
+def _deep_sample_positions(N):
+    """Where the sort of many anchors at batch 1 takes its samples (deep_geom, deep_sample_position)."""
+    stretches = min((N + 767) // 768, 1 << 20)
+    buckets = 1
+    while buckets * buckets < N // 3600: buckets += 1
+    while buckets * 1024 < stretches: buckets += 1
+    per = min((stretches + buckets - 1) // buckets, 1024)
+    samples = buckets * per * min(6, (1 << 22) // (buckets * per))
+    step = (N << 20) // samples
+    at = []
+    for i in range(samples):
+        lo, hi = (i * step) >> 20, ((i + 1) * step) >> 20
+        h = (i * 2654435761 + 40503) & 0xFFFFFFFF
+        h ^= h >> 15; h = (h * 0x2C1B3C6D) & 0xFFFFFFFF; h ^= h >> 13
+        at.append(lo + (h * (hi - lo) >> 32))
+    return np.array(at)
+
+
+@pytest.mark.parametrize("k,n,kind", [
+    (1, 8192, "uniform"), (8192, 1, "ties"), (16384, 16384, "uniform"), (16383, 1, "all_equal"), (16385, 16384, "ascending"), (40000, 9152, "uniform"),
+    (3, 65533, "clustered"), (131072, 8191, "ties"), (20000, 300001, "descending"), (150000, 150000, "two_values"),
+    (30000, 41000, "unsampled"), (9000, 200000, "unsampled"),
+])
+@pytest.mark.parametrize("flags", [0, B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED])
+def test_sort_in_two_distributions(oracle, k, n, kind, flags):
+    """Batch 1 on the routes through sorted order at the edges of the sort's tiles and pieces, with the outputs ending inside a tile or with it; anchors of one and
+    two values and in order; and anchors whose samples all miss the middle of the range, so that one stretch holds nearly everything (beyond a
+    workgroup's LDS and, with more than 65536 pairs, beyond 16-bit places).  The permutation bit for bit, the values by the bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close, gpu_apply, gpu_backward, gpu_perm, gpu_plan_status
+    N = k + n
+    r = np.random.default_rng(N + len(kind))
+    span = N / 64.0
+    if kind in ("uniform", "ties", "all_equal", "clustered"):
+        a, b = anchors(kind, r, k, n)
+    else:
+        v = r.uniform(0, span, N)
+        if kind == "ascending": v = np.concatenate([np.sort(v[:k]), np.sort(v[k:])])
+        if kind == "descending": v = -np.sort(-v)
+        if kind == "two_values": v = np.where(v < span / 3, 1.0, 2.0)
+        if kind == "unsampled":
+            at = _deep_sample_positions(N)
+            v = span * (0.25 + 0.5 * r.permutation(N) / N)
+            v[at[::2]] = r.uniform(0, 0.2 * span, at[::2].size); v[at[1::2]] = r.uniform(0.8 * span, span, at[1::2].size)
+        v = v.astype(np.float32)
+        a, b = v[:k], v[k:]
+    if flags and kind != "ascending":
+        a, b = np.sort(a), np.sort(b)
+    x, g = r.normal(size=(n, 1)).astype(np.float32), r.normal(size=(k, 1)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    B.laplex_diag_set_route_min(0)
+    try:
+        y, ws = gpu_apply(a, b, x, flags=flags | B.LAPLEX_SAVE_SCANS)
+        assert np.array_equal(gpu_perm(ws, N), oracle.merged_permutation(a, b)) and gpu_plan_status(ws, N) == 0
+        assert_close("y", y, ref, tol)
+        for got in (gpu_backward(a, b, x, g, flags=flags | B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws), gpu_backward(a, b, x, g, flags=flags)):
+            for name, u, rv, tv in zip(("gx", "ga", "gb"), got, want, tols):
+                assert_close(name, u, rv, tv)
+    finally:
+        B.laplex_diag_set_route_min(1 << 22)
+
+
+def test_sort_in_two_distributions_non_finite_anchors(oracle):
+    """Values are unspecified, but the calls end, and the workspace serves a clean problem afterwards."""
+    from test_gpu_parity import anchors, assert_close, gpu_perm
+    q = np.random.default_rng(5)
+    k, n = 30000, 50000
+    x = q.normal(size=(n, 1)).astype(np.float32)
+    B.laplex_diag_set_route_min(0)
+    try:
+        ws = torch.empty(B.laplex_workspace_bytes(k, n, 1), dtype=torch.uint8, device="cuda")
+        y = torch.zeros(k, 1, device="cuda")
+        for bad in (3, 2, 1, 0):
+            a, b = anchors("ties", q, k, n)
+            if bad: a[::50 if bad > 1 else 1] = np.nan; b[::33] = -np.nan; a[3] = np.inf; b[5] = -np.inf
+            if bad > 2: b[:] = np.inf
+            B.laplex_apply(dev(a), dev(b), dev(x), y, ws, 0)
+            torch.cuda.synchronize()
+        assert np.array_equal(gpu_perm(ws, k + n), oracle.merged_permutation(a, b))
+        ref, tol = oracle.apply_scan(a, b, x)
+        assert_close("y", y.cpu().numpy(), ref, tol)
+    finally:
+        B.laplex_diag_set_route_min(1 << 22)
