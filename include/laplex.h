@@ -47,7 +47,10 @@
  * built on them) sort by counting ranks over the whole device, and, unless the
  * batch is so wide that the large path's scans are faster, run both scans in one
  * launch whose workgroups take chunks of the merged sequence and form the state
- * at a chunk's edges themselves.  Arguments, flags, workspace and results are the
+ * at a chunk's edges themselves.  With few pairs of an output and an input (up
+ * to 4096 x 4096 of them in one column) the products are formed pair by pair from
+ * the anchors a and b instead, in the launch that sorts; a kept plan is then not
+ * looked at, and the anchors have to be those it was built from.  Arguments, flags, workspace and results are the
  * same (the sorted-input promises are then not needed and not used); values differ
  * from the large path's in rounding only.
  *

@@ -774,22 +774,28 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     if (use_small(L)) {            // a sort, one launch for both scan problems, then the two row reductions
         SmallArgs S = small_args(a, k, b, n, tau, P, L, flags);
         float* zg = reinterpret_cast<float*>(w + L.off_small);
+        const bool fused = small_pairwise(k, n, batch, 1) == 1;      // the row reductions where the products are formed
+        SmallDots D{};
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {     // strict scans of x at the outputs, not kept by the forward
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = x; q.ld_inj = ldx; q.inj_lo = (uint32_t)k; q.inj_hi = (uint32_t)(k + n);
             q.res_lo = 0; q.res_hi = (uint32_t)k;
-            q.out_z = P.z;
+            if (fused) D.prob[0] = {ga, gy, ldgy, nullptr, 0, nullptr}; else q.out_z = P.z;
         }
         if (gx || gb) {
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = gy; q.ld_inj = ldgy; q.inj_lo = 0; q.inj_hi = (uint32_t)k;
             q.res_lo = (uint32_t)k; q.res_hi = (uint32_t)(k + n);
             q.out_p = gx; q.ld_p = ldgx;
-            q.out_z = gb ? zg : nullptr;
+            if (gb && fused) D.prob[S.nprob - 1] = {gb, x, ldx, nullptr, 0, nullptr}; else q.out_z = gb ? zg : nullptr;
         }
-        if (S.nprob > 0) LAPLEX_HIP(launch_small(S, 1, st));
-        if (ga) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
-        if (gb) LAPLEX_HIP(launch_rowdot(x, ldx, zg, batch, n, batch, gb, st));
+        if (ga && fused && (flags & LAPLEX_SAVE_SCANS)) {
+            D.row_out = ga; D.row_u = gy; D.ld_row = ldgy; D.row_v = P.z; D.rows = k;
+            if (S.nprob == 0) S.reuse_plan = 1;      // the saved scans alone: no plan is looked at
+        }
+        if (S.nprob > 0 || D.row_out) LAPLEX_HIP(launch_small(S, 1, st, &D));
+        if (ga && !fused) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
+        if (gb && !fused) LAPLEX_HIP(launch_rowdot(x, ldx, zg, batch, n, batch, gb, st));
         if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, k, b, gb, n, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
         if (tau != 1.0f) LAPLEX_HIP(launch_scale(ga, k, gb, n, tau, st));
         return LAPLEX_OK;
@@ -940,22 +946,29 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
     const Plan P = plan_of(L, w);
     if (use_small(L)) {            // the two-launch path for small problems, then one row reduction
         SmallArgs S = small_args(a, n, nullptr, 0, tau, P, L, flags);
+        // the row reduction where the products are formed, once the strict scans of x are there
+        const bool fused = ga && small_pairwise(n, n, batch, 1) == 1;
+        SmallDots D{};
         float* zg = reinterpret_cast<float*>(w + L.off_small);
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = x; q.ld_inj = ldx; q.inj_lo = 0; q.inj_hi = (uint32_t)n;
             q.res_lo = 0; q.res_hi = (uint32_t)n;
             q.out_z = P.z;
+            if (fused) {             // (a launch of their own: the next one reads them)
+                LAPLEX_HIP(launch_small(S, 1, st));
+                S.nprob = 0; S.prob[0] = SmallProblem{}; S.reuse_plan = 1;
+            }
         }
         if (gx || ga) {
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = gy; q.ld_inj = ldgy; q.inj_lo = 0; q.inj_hi = (uint32_t)n;
             q.res_lo = 0; q.res_hi = (uint32_t)n;
             q.out_p = gx; q.ld_p = ldgx;
-            q.out_z = ga ? zg : nullptr;
+            if (fused) D.prob[0] = {ga, x, ldx, gy, ldgy, P.z}; else q.out_z = ga ? zg : nullptr;
         }
-        if (S.nprob > 0) LAPLEX_HIP(launch_small(S, 1, st));
-        if (ga) LAPLEX_HIP(launch_rowdot2(gy, ldgy, P.z, batch, x, ldx, zg, batch, n, batch, ga, st));
+        if (S.nprob > 0) LAPLEX_HIP(launch_small(S, 1, st, &D));
+        if (ga && !fused) LAPLEX_HIP(launch_rowdot2(gy, ldgy, P.z, batch, x, ldx, zg, batch, n, batch, ga, st));
         if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, n, nullptr, nullptr, 0, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
         if (tau != 1.0f && ga) LAPLEX_HIP(launch_scale(ga, n, nullptr, 0, tau, st));
         return LAPLEX_OK;

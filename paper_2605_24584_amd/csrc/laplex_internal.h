@@ -513,7 +513,18 @@ struct SmallArgs {
     int64_t batch; int cols;                   // cols: set by the launcher, power of two <= 16
     int nprob; SmallProblem prob[2];
 };
-hipError_t launch_small(const SmallArgs& A, int64_t operators, hipStream_t st);
+// Whether launch_small forms the products pair by pair from the anchors, beside the sort instead of after it (0: no), and in how many slabs
+// of columns; k, n: outputs and inputs (Gram form: n twice).
+int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators);
+// Row reductions in the launch that forms the products pair by pair, where it does and in one slab of columns (small_pairwise = 1):
+//   out[r] = sum_t w[r * ld_w + t] Z[r][t] (+ u[r * ld_u + t] v[r * batch + t]), Z the problem's strict sums (out null: none);
+//   row_out[r] = sum_t row_u[r * ld_row + t] row_v[r * batch + t], r < rows, beside the problems.
+struct SmallDot { float* out; const float* w; int64_t ld_w; const float* u; int64_t ld_u; const float* v; };
+struct SmallDots {
+    SmallDot prob[2];
+    float* row_out; const float* row_u; int64_t ld_row; const float* row_v; int64_t rows;
+};
+hipError_t launch_small(const SmallArgs& A, int64_t operators, hipStream_t st, const SmallDots* dots = nullptr);
 // Whether the chunks of launch_small's scans read so much of each other's rows that the tiled scans are faster (see its definition).
 bool small_reads_too_much(int64_t N, int64_t batch);
 

@@ -1,4 +1,5 @@
-// Small problems in two launches.  When the merged sequence a ++ b has at most kSmallMax positions the
+// Small problems in one launch or two.  With few pairs of an output and an input the products are formed from the definition, beside the sort
+// (k_small_pairs).  Else, when the merged sequence a ++ b has at most kSmallMax positions, the
 // whole path of one call (Sec. 3: sort, then the prefix recurrence and its mirror image) is one launch
 // that sorts (k_small_rank: ranks by counting, over the whole device) and one that runs the decayed scans in both directions
 // and scatters the results (k_small),
@@ -11,6 +12,8 @@
 // strictly smaller keys), summarised per segment as (D, S, H, Q):
 //     F_out = D F_in + S,    E_out = H ? D F_in + Q : E_in.
 #include "laplex_internal.h"
+
+#include <type_traits>
 
 namespace laplex {
 
@@ -41,11 +44,14 @@ __device__ __forceinline__ float small_key_to_float(uint32_t key)
 // Output: the plan's ids and sorted anchors (pk, between its two sentinels).
 constexpr int kRankQueriesMax = 256;      // queries per workgroup: 32 .. 256, chosen by the launcher
 
-__global__ void __launch_bounds__(kSmallThreads)
-k_small_rank(SmallArgs A, int queries)
+struct RankShared {
+    unsigned long long query[kRankQueriesMax];
+    uint32_t partial[kRankQueriesMax][kSmallWaves];
+};
+__device__ __forceinline__ void small_rank(const SmallArgs& A, int queries, int block, RankShared& L)
 {
-    __shared__ unsigned long long query[kRankQueriesMax];
-    __shared__ uint32_t partial[kRankQueriesMax][kSmallWaves];
+    auto& query = L.query;
+    auto& partial = L.partial;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t op = blockIdx.y;
     const int N = (int)(A.k + A.n);
@@ -66,7 +72,7 @@ k_small_rank(SmallArgs A, int queries)
         const int e = wave * 64 * kSmallItems + r * 64 + lane;
         cand[r] = e < N ? composite(e) : ~0ull;
     }
-    const int q0 = blockIdx.x * queries;
+    const int q0 = block * queries;
     if (tid < queries) query[tid] = q0 + tid < N ? composite(q0 + tid) : 0ull;
     __syncthreads();
     const bool any = wave * 64 * kSmallItems < N;                   // uniform: does this wavefront hold candidates at all
@@ -88,11 +94,237 @@ k_small_rank(SmallArgs A, int queries)
         g_ids[rank] = (uint32_t)me;
         g_pk[rank + 1] = small_key_to_float((uint32_t)(me >> 32));
     }
-    if (blockIdx.x == 0 && tid == 0) {
+    if (block == 0 && tid == 0) {
         g_pk[0] = __uint_as_float(0xFF800000u);
         g_pk[N + 1] = __uint_as_float(0x7F800000u);
         reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(A.counters) + op * A.op_ws)[kPlanIndexWord] = 0u;      // a new plan
     }
+}
+
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_rank(SmallArgs A, int queries)
+{
+    __shared__ RankShared L;
+    small_rank(A, queries, (int)blockIdx.x, L);
+}
+
+// ---------------------------------------------------------------------------
+// Few pairs: the products by the definition (Sec. 1), y_i = sum_j exp(-|a_i - b_j|) x_j and, for the anchor gradients, the same sum with the sign
+// of b_j - a_i and without the pairs that are tied, straight from the anchors.  They need no sorted order, so the plan is ranked by other workgroups of the same launch, and a
+// call is one launch where ranks and scans are two in a row (measured: see small_pairwise).  Bound by the launch and one chain of loads,
+// then by the vector units: an exponential of six instructions and one or two multiply-adds a column for every pair.
+// A wavefront takes ROWS result rows and every fourth 64 of the injected rows, a lane one injected row at a time; lanes and the four quarters are added up
+// as a butterfly and in order, so the sums are trees over chains of m / 256 terms.
+// ---------------------------------------------------------------------------
+constexpr int kPairSplits = 4;                                             // wavefronts that share result rows
+constexpr int kPairGroups = kSmallWaves / kPairSplits;
+template <int C> constexpr int kPairKeptGroups = C == 1 ? 1 : kPairGroups;      // (rows of several columns are staged once for as many result rows as there are)
+template <int C> constexpr int kPairRows = C <= 2 ? 4 : 2;                 // result rows of a wavefront
+
+// exp(-x) for x >= 0 to about one unit in the last place: the hardware's 2^t, with what rounding the product x log2(e) lost put back.
+// (200: the result is zero from 104 on.)
+__device__ __forceinline__ float exp_minus(float x)
+{
+    constexpr float log2e = 1.44269504088896340736f, log2e_low = 1.92596299112661746887e-8f, ln2 = 0.69314718055994530942f;
+    x = fminf(x, 200.0f);
+    const float t = x * -log2e;
+    float low = __builtin_fmaf(x, -log2e, -t);
+    low = __builtin_fmaf(x, -log2e_low, low);
+    const float e = __builtin_amdgcn_exp2f(t);
+    return __builtin_fmaf(e, low * ln2, e);
+}
+
+// The sum over the wavefront, in lane 63 only.  The last LATE of its six steps are in fp64, like the sum of the quarters after them: a tree's error is that
+// of its upper levels.  Relative l2 errors against fp64 (y, gx, ga, gb; mean over 32 combinations of sizes, anchors and columns) are 0.73, 0.70, 0.79 and 0.76 of those of the
+// scans in place of which these sums are taken (fp32 throughout: 1.03, 0.99, 1.04, 0.99; n = k = 4096, uniform anchors: y 9.6e-8 -> 6.9e-8).
+template <int LATE>
+__device__ __forceinline__ double wave_sum(float v)
+{
+    double d = 0.0;
+    auto step = [&](auto index, auto ctrl, auto rows) {
+        constexpr int I = decltype(index)::value, CTRL = decltype(ctrl)::value, ROWS = decltype(rows)::value;
+        if constexpr (I < 6 - LATE) {
+            v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xF, false));
+        } else {
+            if constexpr (I == 6 - LATE) d = (double)v;
+            const int low = __builtin_amdgcn_update_dpp(0, __double2loint(d), CTRL, ROWS, 0xF, false);
+            const int high = __builtin_amdgcn_update_dpp(0, __double2hiint(d), CTRL, ROWS, 0xF, false);
+            d += __hiloint2double(high, low);
+        }
+    };
+    using std::integral_constant;
+    using All = integral_constant<int, 0xF>;
+    step(integral_constant<int, 0>{}, integral_constant<int, 0x111>{}, All{});                          // row_shr:1, 2, 4, 8
+    step(integral_constant<int, 1>{}, integral_constant<int, 0x112>{}, All{});
+    step(integral_constant<int, 2>{}, integral_constant<int, 0x114>{}, All{});
+    step(integral_constant<int, 3>{}, integral_constant<int, 0x118>{}, All{});
+    step(integral_constant<int, 4>{}, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});  // the row before's last lane into rows 1 and 3
+    step(integral_constant<int, 5>{}, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});  // lane 31 into rows 2 and 3
+    return d;
+}
+
+// LDS: injected rows of more than one column, kPairStage at a time (their anchors, and the columns in planes of up to four, so that a lane's read is as wide
+// and conflict-free as it can be; a lane that read its row's columns one by one from memory touched every line of them once per column: 4096 x 4096, batch 8, 126 us), and at the
+// end the sums of the wavefronts.
+constexpr int kPairStage = 1024;
+template <int C, int GROUPS>
+struct PairShared {
+    static constexpr int W = C < 4 ? C : 4;
+    union {
+        struct { __align__(16) float v[C > 1 ? C / W : 1][C > 1 ? kPairStage : 1][W]; float at[C > 1 ? kPairStage : 1]; } stage;
+        double part[kPairSplits][GROUPS * kPairRows<C>][C][2];
+    };
+};
+
+template <int C, bool STRICT, int GROUPS>
+__device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProblem& P, const SmallDot& D, int64_t op, int block, int slabs, PairShared<C, GROUPS>& L)
+{
+    constexpr int ROWS = kPairRows<C>, BLOCK = GROUPS * ROWS, THREADS = GROUPS * kPairSplits * 64, LATE = C <= 2 ? 6 : 3;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int split = wave % kPairSplits, group = wave / kPairSplits;
+    const int slab = block % slabs, block0 = (block / slabs) * BLOCK, row0 = block0 + group * ROWS;
+    const int64_t col0 = (int64_t)slab * C;
+    const float* const a = A.a + op * A.op_a;
+    const float* const b = A.b + op * A.op_b;
+    auto anchor = [&](uint32_t id) {
+        float v = A.tau * (id < A.k ? a[id] : b[id - A.k]);
+        asm("" : "+v"(v));          // (the product rounded, as the plan has it: fused into the difference below a tie would not be zero)
+        return v;
+    };
+    const int m = (int)(P.inj_hi - P.inj_lo), res = (int)(P.res_hi - P.res_lo);
+    const float* const inj = P.inj + op * P.op_inj + col0;
+    float at[ROWS], p[ROWS][C], z[ROWS][C];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        at[r] = anchor(P.res_lo + (uint32_t)(row0 + r < res ? row0 + r : res - 1));
+#pragma unroll
+        for (int c = 0; c < C; ++c) p[r][c] = z[r][c] = 0.0f;
+    }
+    auto pair = [&](float from, const float (&v)[C]) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const float d = from - at[r];
+            const float e = exp_minus(fabsf(d)), s = __builtin_copysignf(e, d);
+            const bool tie = d == 0.0f;
+#pragma unroll
+            for (int c = 0; c < C; ++c) p[r][c] = __builtin_fmaf(e, v[c], p[r][c]);
+            if (STRICT) {
+                if (__any(tie)) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) z[r][c] = tie ? z[r][c] : __builtin_fmaf(s, v[c], z[r][c]);
+                } else {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) z[r][c] = __builtin_fmaf(s, v[c], z[r][c]);
+                }
+            }
+        }
+    };
+    if constexpr (C == 1) {
+        constexpr int U = 4;
+        for (int j0 = split * 64 + lane; j0 < m; j0 += U * kPairSplits * 64) {
+            float from[U], v[U][1];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = j0 + u * kPairSplits * 64, jc = j < m ? j : j0;
+                from[u] = anchor(P.inj_lo + (uint32_t)jc);
+                v[u][0] = j < m ? inj[(int64_t)jc * P.ld_inj] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) pair(from[u], v[u]);
+        }
+    } else {
+        constexpr int W = PairShared<C, GROUPS>::W, LOADS = C * kPairStage / THREADS, ANCHORS = kPairStage / THREADS;
+        float next[LOADS], next_at[ANCHORS];
+        auto fetch = [&](int base) {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int q = i * THREADS + tid, j = base + q / C, c = q % C;
+                next[i] = j < m && col0 + c < A.batch ? inj[(int64_t)j * P.ld_inj + c] : 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < ANCHORS; ++i) {
+                const int j = base + i * THREADS + tid;
+                next_at[i] = anchor(P.inj_lo + (uint32_t)(j < m ? j : m - 1));
+            }
+        };
+        fetch(0);
+        for (int base = 0; base < m; base += kPairStage) {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int q = i * THREADS + tid, j = q / C, c = q % C;
+                L.stage.v[c / W][j][c % W] = next[i];
+            }
+#pragma unroll
+            for (int i = 0; i < ANCHORS; ++i) L.stage.at[i * THREADS + tid] = next_at[i];
+            __syncthreads();
+            if (base + kPairStage < m) fetch(base + kPairStage);
+            const int end = m - base < kPairStage ? m - base : kPairStage;
+#pragma unroll 1
+            for (int j = split * 64 + lane; j < end; j += kPairSplits * 64) {
+                float v[C];
+#pragma unroll
+                for (int c = 0; c < C; ++c) v[c] = L.stage.v[c / W][j][c % W];
+                pair(L.stage.at[j], v);
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const double ps = wave_sum<LATE>(p[r][c]), zs = STRICT ? wave_sum<LATE>(z[r][c]) : 0.0;
+            if (lane == 63) { L.part[split][group * ROWS + r][c][0] = ps; L.part[split][group * ROWS + r][c][1] = zs; }
+        }
+    }
+    __syncthreads();
+    static_assert(BLOCK * C <= 64, "the results of a workgroup are one wavefront's");
+    if (tid >= BLOCK * C) return;
+    const int row = tid / C, c = tid % C, rr = block0 + row;
+    const int64_t col = col0 + c;
+    const bool ok = rr < res && col < A.batch;
+    double ps = 0.0, zs = 0.0;
+#pragma unroll
+    for (int q = 0; q < kPairSplits; ++q) { ps += L.part[q][row][c][0]; zs += L.part[q][row][c][1]; }
+    const float pv = (float)ps, zv = (float)zs;
+    if (ok && P.out_p) (P.out_p + op * P.op_p)[(int64_t)rr * P.ld_p + col] = pv;
+    if (STRICT && ok && P.out_z) (P.out_z + op * P.op_z)[(int64_t)rr * A.batch + col] = zv;
+    if (STRICT && D.out) {              // one slab: all columns of a row are here
+        float dot = ok ? D.w[(int64_t)rr * D.ld_w + col] * zv : 0.0f;
+        if (ok && D.u) dot += D.u[(int64_t)rr * D.ld_u + col] * D.v[(int64_t)rr * A.batch + col];
+#pragma unroll
+        for (int d = 1; d < C; d <<= 1) dot += __shfl_xor(dot, d);
+        if (ok && c == 0) D.out[rr] = dot;
+    }
+}
+
+// Workgroups [0, pairs0): the first problem's, [pairs0, pairs0 + pairs1): the second's, then those of the ranks (GROUPS = kPairGroups only),
+// then the row products'.  On a kept plan the workgroups are smaller: nothing ranks beside them, and a row's sums are the same.
+template <int C, bool STRICT, int GROUPS>
+__global__ void __launch_bounds__(GROUPS * kPairSplits * 64)
+k_small_pairs(const SmallArgs A, const SmallDots D, int slabs, int pairs0, int pairs1, int rank_blocks, int queries)
+{
+    constexpr bool RANKS = GROUPS == kPairGroups;
+    struct Nothing {};
+    __shared__ union { PairShared<C, GROUPS> pairs; std::conditional_t<RANKS, RankShared, Nothing> rank; } L;
+    const int64_t op = blockIdx.y;
+    int block = (int)blockIdx.x;
+    if (block < pairs0) { small_pairs<C, STRICT, GROUPS>(A, A.prob[0], D.prob[0], op, block, slabs, L.pairs); return; }
+    block -= pairs0;
+    if (block < pairs1) { small_pairs<C, STRICT, GROUPS>(A, A.prob[1], D.prob[1], op, block, slabs, L.pairs); return; }
+    block -= pairs1;
+    if constexpr (RANKS) {
+        if (block < rank_blocks) { small_rank(A, queries, block, L.rank); return; }
+        block -= rank_blocks;
+    }
+    // (a row's columns side by side and added up as above: the same bits whoever forms the strict sums)
+    const int64_t row = (int64_t)block * (GROUPS * kPairSplits * 64 / C) + threadIdx.x / C;
+    const int64_t col = threadIdx.x % C;
+    const bool ok = row < D.rows && col < A.batch;
+    float dot = ok ? D.row_u[row * D.ld_row + col] * D.row_v[row * A.batch + col] : 0.0f;
+#pragma unroll
+    for (int d = 1; d < C; d <<= 1) dot += __shfl_xor(dot, d);
+    if (ok && col == 0) D.row_out[row] = dot;
 }
 
 // ---------------------------------------------------------------------------
@@ -325,13 +557,61 @@ bool small_reads_too_much(int64_t N, int64_t batch)
     return chunks > 1 && (double)chunks * (double)N * (double)batch > kSmallReads;
 }
 
-hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st)
+static int pair_columns(int64_t batch) { return batch >= 5 ? 8 : batch >= 3 ? 4 : (int)batch; }
+
+// Where forming every pair's exponential is faster than ranking first and scanning then.  The line is the same whatever a call wants and whether its
+// plan is kept, since the form shows in the last bits; it lies where a product on a kept plan, which saves no launch, is no slower.
+// Measured (us, pair by pair / ranks, then scans; forward, forward on a kept plan, forward + backward): n = k = 4096, batch 1 15.4 / 24.2, 10.0 / 11.2, 30.2 /
+// 41.9; 1024 9.7 / 16.8, 9.6 / 9.6, 19.9 / 31.6; 2048, batch 4 11.0 / 18.7, 9.9 / 9.6, 23.3 / 34.8; 1500, batch 8 11.4 / 17.7, 9.8 / 9.7, 25.7 / 33.5;
+// 64 x 64, batch 8 9.6 / 13.2, 10.0 / 9.7, 20.4 / 29.7; 8 operators of 300 x 1000 14.3 / 22.1, 13.5 / 13.4, 43.4 / 48.6 (9.6: what a launch alone takes from here).
+// Beyond the lines: Gram form of 6000, batch 1 21.1 / 21.7, 16.4 / 10.4, 49.4 / 38.0; 4096 x 4096, batch 2 15.4 / 24.0, 11.7 / 11.1, 37.5 / 42.3; 700 x 4096,
+// batch 8 11.8 / 20.1, 11.7 / 10.1, 28.7 / 37.0; 300 x 300, batch 256 16.6 / 15.5, 13.6 / 9.9, 60.7 / 32.2.
+constexpr double kPairCost = 2.4e8, kPairCostWide = 9e7, kPairCostSlabs = 4e7;      // cycles of a lane, about
+constexpr int64_t kPairRowsWide = 3072;
+int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators)
+{
+    const int cols = pair_columns(batch);
+    const int64_t slabs = (batch + cols - 1) / cols;
+    if (cols > 1 && (k > kPairRowsWide || n > kPairRowsWide)) return 0;
+    const double cost = (double)k * (double)n * (double)(slabs * operators) * (12.0 + 2.0 * cols);
+    return cost <= (slabs > 1 ? kPairCostSlabs : cols > 1 ? kPairCostWide : kPairCost) ? (int)slabs : 0;
+}
+
+hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st, const SmallDots* dots)
 {
     SmallArgs A = A0;
     const int64_t N = A.k + A.n;
+    int queries = 32;          // of the ranks, per workgroup (more per workgroup measured slower until the grid gets very large)
+    while (queries < kRankQueriesMax && ((N + queries - 1) / queries) * operators > 8192) queries <<= 1;
+    const bool rows_only = A.nprob == 0 && dots && dots->row_out;
+    const int pair_slabs = A.nprob > 0 || rows_only ? small_pairwise(A.k, A.n ? A.n : A.k, A.batch, operators) : 0;
+    if (pair_slabs) {
+        const SmallDots D = dots ? *dots : SmallDots{};
+        const int cols = pair_columns(A.batch);
+        bool strict = A.nprob == 0;       // (row products alone: either form)
+        const int groups = A.reuse_plan && cols == 1 ? kPairKeptGroups<1> : kPairGroups, threads = groups * kPairSplits * 64;
+        int blocks[2] = {0, 0};
+        for (int i = 0; i < A.nprob; ++i) {
+            strict = strict || A.prob[i].out_z != nullptr || D.prob[i].out != nullptr;
+            const int rows = groups * (cols <= 2 ? kPairRows<1> : kPairRows<8>);
+            blocks[i] = (int)((A.prob[i].res_hi - A.prob[i].res_lo + rows - 1) / rows) * pair_slabs;
+        }
+        const int rank_blocks = A.reuse_plan ? 0 : (int)((N + queries - 1) / queries);
+        const int row_blocks = D.row_out ? (int)((D.rows * cols + threads - 1) / threads) : 0;
+        const dim3 grid((unsigned)(blocks[0] + blocks[1] + rank_blocks + row_blocks), (unsigned)operators);
+        auto go = [&](auto kernel) { LAPLEX_TIMED("small_pairs", st, hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, A, D, pair_slabs, blocks[0], blocks[1], rank_blocks, queries)); };
+        auto with = [&](auto columns) {
+            constexpr int C = decltype(columns)::value;
+            if (A.reuse_plan) { if (strict) go(k_small_pairs<C, true, kPairKeptGroups<C>>); else go(k_small_pairs<C, false, kPairKeptGroups<C>>); }
+            else { if (strict) go(k_small_pairs<C, true, kPairGroups>); else go(k_small_pairs<C, false, kPairGroups>); }
+        };
+        if (cols == 1) with(std::integral_constant<int, 1>{});
+        else if (cols == 2) with(std::integral_constant<int, 2>{});
+        else if (cols == 4) with(std::integral_constant<int, 4>{});
+        else with(std::integral_constant<int, 8>{});
+        return hipGetLastError();
+    }
     if (!A.reuse_plan) {
-        int queries = 32;          // per workgroup (more per workgroup measured slower until the grid gets very large)
-        while (queries < kRankQueriesMax && ((N + queries - 1) / queries) * operators > 8192) queries <<= 1;
         LAPLEX_TIMED("small_sort", st, hipLaunchKernelGGL(k_small_rank, dim3((unsigned)((N + queries - 1) / queries), (unsigned)operators),
                                                           dim3(kSmallThreads), 0, st, A, queries));
     }

@@ -774,3 +774,65 @@ def test_sort_in_two_distributions_non_finite_anchors(oracle):
         assert_close("y", y.cpu().numpy(), ref, tol)
     finally:
         B.laplex_diag_set_route_min(1 << 22)
+
+
+@pytest.mark.parametrize("k,n,batch", [
+    (1, 1, 1), (16, 255, 1), (17, 257, 1), (4096, 4096, 1), (4100, 4092, 1), (5, 8187, 1), (8187, 5, 1),      # one column: the last two sizes of the line
+    (16, 1023, 2), (15, 1024, 2), (2366, 2366, 2), (7, 1025, 4), (9, 3072, 3), (3073, 9, 3), (8, 2049, 8), (1793, 1792, 8), (1793, 1793, 8),
+    (33, 70, 9), (600, 601, 16), (1024, 1024, 16), (100, 130, 70),                                            # several slabs
+])
+@pytest.mark.parametrize("tau", [1.0, 0.37])
+def test_products_pair_by_pair(oracle, k, n, batch, tau):
+    """Small problems either side of the lines up to which the products come straight from the anchors: tiles of result rows, stages of injected rows and
+    slabs of columns that end anywhere, ties (also after the multiplication by tau), padded rows, gradients wanted one by one, saved or not; the
+    same bits whether the plan is kept or not.  Bars of test_gpu_parity."""
+    from test_gpu_parity import anchors, assert_close, gpu_perm
+    r = np.random.default_rng(k + 3 * n + batch)
+    a, b = anchors("ties", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.tau_apply(a, b, tau, x, brute=True)
+    (rgx, rga, rgb, _), (tgx, tga, tgb, _) = oracle.tau_backward(a, b, tau, x, g, brute=True)
+    da, db, dg = dev(a), dev(b), dev(g)
+    dx = torch.zeros(n, batch + 3, device="cuda")[:, :batch]; dx.copy_(dev(x))
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    y = torch.full((k, batch + 1), float("nan"), device="cuda")
+    B.laplex_apply_tau(da, db, tau, dx, y[:, :batch], ws, B.LAPLEX_SAVE_SCANS)
+    torch.cuda.synchronize()
+    assert_close("y", y[:, :batch].cpu().numpy(), ref, tol)
+    assert bool(torch.isnan(y[:, batch]).all())
+    scaled = np.float32(tau) * a, np.float32(tau) * b
+    assert np.array_equal(gpu_perm(ws, k + n), oracle.merged_permutation(*scaled))
+    y2 = torch.zeros(k, batch, device="cuda")
+    B.laplex_apply_tau(da, db, tau, dx, y2, ws, B.LAPLEX_REUSE_PLAN)
+    assert_close("y on a kept plan", y2.cpu().numpy(), ref, tol)
+    first = None
+    for flags in (B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, 0):
+        for want in ((1, 1, 1), (0, 1, 0), (1, 0, 0), (0, 0, 1), (1, 1, 0)):
+            fresh = ws if flags else torch.empty_like(ws)
+            gx = torch.full((n, batch + 2), float("nan"), device="cuda")[:, :batch] if want[0] else None
+            ga = torch.full((k,), float("nan"), device="cuda") if want[1] else None
+            gb = torch.full((n,), float("nan"), device="cuda") if want[2] else None
+            B.laplex_apply_backward_tau(da, db, tau, dx, dg, gx, ga, gb, None, fresh, flags)
+            torch.cuda.synchronize()
+            got = [None if v is None else v.cpu().numpy() for v in (gx, ga, gb)]
+            if first is None: first = got
+            for name, v, rv, tv, f in zip(("gx", "ga", "gb"), got, (rgx, rga, rgb), (tgx, tga, tgb), first):
+                if v is not None:
+                    assert_close(name, v, rv, tv)
+                    assert not all(want) or np.array_equal(v, f), name
+
+
+@pytest.mark.parametrize("n,batch", [(1, 1), (4100, 1), (4096, 1), (2121, 4), (1792, 8), (300, 20)])
+def test_gram_pair_by_pair(oracle, n, batch):
+    from test_gpu_parity import anchors, assert_close, gpu_gram, gpu_gram_backward
+    r = np.random.default_rng(n + batch)
+    a, _ = anchors("ties", r, n, 1)
+    x, g = (r.normal(size=(n, batch)).astype(np.float32) for _ in range(2))
+    ref, tol = oracle.gram_brute(a, x)
+    y, ws = gpu_gram(a, x, flags=B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y, ref, tol)
+    want, tols = oracle.gram_backward_brute(a, x, g)
+    saved, alone = gpu_gram_backward(a, x, g, flags=B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, ws=ws), gpu_gram_backward(a, x, g)
+    for name, u, v, rv, tv in zip(("gx", "ga"), saved, alone, want, tols):
+        assert_close(name, u, rv, tv)
+        assert np.array_equal(u, v), name
