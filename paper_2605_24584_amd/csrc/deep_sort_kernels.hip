@@ -476,8 +476,9 @@ __device__ __forceinline__ void each_of_unit(const DeepPlan& P, int per_bucket, 
     }
 }
 
+// (The larger units as 16 pairs a thread: as 8 of 1024 threads, whose registers spill, 2^31 positions take 112.4 ms a step in place of 110.0.)
 template <int THREADS, int ITEMS>
-__global__ void __launch_bounds__(THREADS, THREADS == 512 ? 6 : 8)
+__global__ void __launch_bounds__(THREADS, ITEMS == 16 ? 4 : 6)
 k_deep_sort(const DeepArgs A)
 {
     constexpr int CAP = THREADS * ITEMS;
@@ -833,7 +834,7 @@ hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n
     LAPLEX_TIMED("deep_pieces", st, hipLaunchKernelGGL((k_deep_distribute<true>), dim3((unsigned)G.max_pieces), dim3(kDeepThreads), 0, st, A));
     LAPLEX_TIMED("deep_units", st, hipLaunchKernelGGL(k_deep_units, dim3((unsigned)A.buckets), dim3(kSplitMaxBuckets), 0, st, A, (uint32_t)G.capacity));
     const dim3 units((unsigned)((G.max_units + 7) / 8 * 8));
-    if (G.capacity == 8192) LAPLEX_TIMED("deep_sort", st, hipLaunchKernelGGL((k_deep_sort<1024, 8>), units, dim3(1024), 0, st, A));
+    if (G.capacity == 8192) LAPLEX_TIMED("deep_sort", st, hipLaunchKernelGGL((k_deep_sort<512, 16>), units, dim3(512), 0, st, A));
     else LAPLEX_TIMED("deep_sort", st, hipLaunchKernelGGL((k_deep_sort<512, 8>), units, dim3(512), 0, st, A));
     LAPLEX_TIMED("deep_edges", st, hipLaunchKernelGGL(k_deep_edges, of(G.max_units, 256), dim3(256), 0, st, A));
     return hipGetLastError();
