@@ -396,14 +396,22 @@ namespace {
 // at 256 * 6144 positions, 9e-4 at 2^21, 5e-4 at 512 * 6144, 8e-4 at 2^22, and falls to below 1e-5 at five sixths of these sizes (18 or 19
 // pairs a thread, a longer LDS buffer, would bring it to 1e-5, and cost 5 to 10 % in spilled registers).  Such a set of anchors is sorted
 // in memory there (count_in_memory: 58 us more at 2^21).  Tiles: the fewest keys that still make at most 512 of them.
+// Up to 2^17 positions, where stretches are far fewer than the device has room for, they are short and taken by more threads than they need, and
+// half the samples do, since the capacity is four and more times the average (us for the whole sort, 1024 pairs by 256 threads, 16 samples
+// each / now; uniform and grid anchors: 20000 21.0 / 19.7, 26.0 / 23.3; 65536 22.2 / 20.8, 28.0 / 23.7; 131072 24.3 / 22.7, 29.6 / 26.3).  Beyond, half the samples leave
+// longer longest stretches, which is what the sort waits for (2^19: 33 / 39; 2^20: 39 / 44).
 struct SplitGeom { int per, threads, group_bits; int64_t tile, tiles, buckets, samples; };
 constexpr int kTileThreads = 1024;
-SplitGeom split_geom(int64_t N)
+SplitGeom split_geom(int64_t N, bool many = false)      // many: several operators in one launch, which fill the device between them
 {
     SplitGeom G;
     int64_t per_bound = 16;
-    if (N <= int64_t(1) << 17) {
+    if (many && N <= int64_t(1) << 17) {
         G.per = 1; G.threads = 256; G.buckets = (N + 1023) / 1024;
+    } else if (N <= int64_t(1) << 16) {
+        G.per = 1; G.threads = 256; G.buckets = (N + 511) / 512; per_bound = 8;
+    } else if (N <= int64_t(1) << 17) {
+        G.per = 1; G.threads = 512; G.buckets = (N + 1023) / 1024; per_bound = 8;
     } else if (N <= int64_t(1) << 19) {
         G.per = 2; G.threads = 512; G.buckets = (N + 2047) / 2048;
     } else {
@@ -421,7 +429,7 @@ SplitGeom split_geom(int64_t N)
 }
 }  // namespace
 
-size_t split_sort_words(int64_t N)
+size_t split_sort_words(int64_t N)          // (for one operator or many: those take fewer stretches and as many samples)
 {
     const SplitGeom G = split_geom(N);
     return (size_t)(2 * G.buckets + 4 * (G.buckets + 1) + G.samples + (G.tiles * (G.buckets + 1) + 1) / 2);
@@ -431,7 +439,7 @@ hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t 
                              uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters,
                              int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st)
 {
-    const SplitGeom G = split_geom(k + n);
+    const SplitGeom G = split_geom(k + n, operators > 1);
     SplitArgs A{};
     A.a = a; A.b = b; A.k = k; A.tau = tau; A.N = (int)(k + n);
     A.pairs = pair0; A.spare = pair1;

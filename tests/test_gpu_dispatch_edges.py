@@ -836,3 +836,10 @@ def test_gram_pair_by_pair(oracle, n, batch):
     for name, u, v, rv, tv in zip(("gx", "ga"), saved, alone, want, tols):
         assert_close(name, u, rv, tv)
         assert np.array_equal(u, v), name
+
+
+@pytest.mark.parametrize("kind", ["uniform", "few_values", "equal", "ascending", "repeating", "narrow_windows"])
+@pytest.mark.parametrize("N", [(1 << 16) - 1, 1 << 16, (1 << 16) + 1])
+def test_sample_sort_short_stretches(oracle, N, kind):
+    """The same where the sort's stretches go from 512 to 1024 pairs on average."""
+    test_sample_sort_order_and_decays(oracle, N, kind)
