@@ -212,6 +212,10 @@ bool strict_in_order(const Layout& L)
     return (L.batch == 4 || L.batch == 8) && L.N > kSmallMax && L.zrows < L.N && 4 * L.zrows >= L.N;
 }
 
+// Gram form, 9 to 128 columns: the backward scans x again beside gy (k_scan_down_pair), and what the forward saves, where the strict
+// scans would lie, are the states that enter its blocks.  (Fewer columns are staged in sorted order, more have blocks of another shape.)
+bool gram_scans_together(const Layout& L) { return L.batch > kStageMaxBatch && L.batch <= 128; }
+
 SmallArgs small_args(const float* a, int64_t k, const float* b, int64_t n, float tau, const Plan& P, const Layout& L, uint32_t flags);
 
 // Sort (or merge) the anchors and compute the neighbour decays, unless the plan is reused.
@@ -905,6 +909,7 @@ static int gram_impl(const float* a, int64_t n, const float* x, int64_t ldx, int
     if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_z = pairs + 1; p.ld_z = 2; }
     p.stage = (flags & LAPLEX_SAVE_SCANS) ? P.xs : P.stage;
     p.tag = "fwd";
+    if (p.out_z && gram_scans_together(L)) { p.out_z = nullptr; p.carries = P.z; }
     if (use_permute(L)) {          // batch 1, many rows: x into sorted order, the scans there, y (and the saved scans) home
         const bool save = (flags & LAPLEX_SAVE_SCANS) != 0;
         LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, 0, n, p.stage, "fwd", st));
@@ -987,6 +992,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
             p.out_z = nullptr;
             LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, P.z, 1, nullptr, 1, st));
         } else {
+            if (gram_scans_together(L)) { p.out_z = nullptr; p.carries = P.z; }
             LAPLEX_HIP(launch_scan(p, L, w, st));
         }
     }
@@ -1009,6 +1015,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
         p.res_lo = 0; p.res_hi = (uint32_t)n;
         p.out_p = gx; p.ld_p = ldgx;
         p.out_red = ga; p.w = x; p.ld_w = ldx; p.zs = ga ? P.z : nullptr;
+        if (ga && gram_scans_together(L)) { p.zs = nullptr; p.pair_carries = P.z; }
         float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
         const bool paired = batch == 1 && gx && ga;
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }

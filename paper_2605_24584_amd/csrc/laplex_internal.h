@@ -460,6 +460,10 @@ struct ScanProblem {
     // dot_z[(id - inj_lo) * batch + t], or if dot_in_order is not null and they are there dot_in_order[sorted row * batch + t]
     // (without dot_in_order from 9 columns on)
     const float* dot_z = nullptr; float* dot_out = nullptr; const float* dot_in_order = nullptr;
+    // 9 to 128 columns, every row injected and read (the Gram form): `carries` keeps the states that enter the blocks, [2][2][tiles][bpad] floats (inclusive,
+    // strict), of a problem whose strict sums a later one needs (without out_p nothing else of it is wanted); pair_carries: those of the weights w, so
+    // that out_red[m] = sum_t (inj Z^w + w Z^inj)[m, t] in one walk
+    float* carries = nullptr; const float* pair_carries = nullptr;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
     // batch 1, routes without random accesses: `stage` already holds the injected rows in sorted order (zero elsewhere), and
     // the outputs of result row j of the sorted sequence go to out_p[j * ld_p], out_z[j * ld_z], out_red[j * ld_red]

@@ -87,6 +87,8 @@ struct ScanArgs {
     PartEmit emit;                // batch 1, sorted order: the results leave as records of a partition level (k_seq_down)
     int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_in_order)
     const float* dot_z; float* dot_out; const float* dot_in_order;      // row products of the reduce (ScanProblem)
+    const float* pair_car_f; const float* pair_car_e;      // carries of a second matrix, x, scanned beside the injected one (k_scan_down_pair), or null
+    int keep_carries;             // 1: the carries stay where l1 has them and no strict value is written; 2: and there is no downsweep
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
@@ -1876,6 +1878,191 @@ k_scan_down(const ScanArgs A)
 }
 
 // ---------------------------------------------------------------------------
+// downsweep of the Gram form's backward: gy and x scanned together
+// ---------------------------------------------------------------------------
+// ga_m = sum_t (gy Z^x + x Z^g)[m, t] needs the strict scans of both matrices.  Those of x are not kept by the forward (a matrix written there,
+// scattered, and gathered again here): only the states that enter its blocks are, and the rows of x, which are read here in any case, are walked before
+// those of gy, their strict scans held in LDS.  Bound by the gathered rows and by its own latency: 2.4 GB at n = 3 x 2^20, batch 64 (gy and x read,
+// gx written) in 663 us, where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
+// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1450 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 461 us;
+// n = 300001, batch 128: 388 -> 348 us; n = 10^5, batch 64: 127 -> 126 us.
+// A block has the rows of k_scan_down's, as eight wavefronts with four rows a row-lane instead of four with eight: 128 registers, two
+// workgroups to a compute unit.  Registers are what decides it: both matrices in one walk 1315 us (50 registers in scratch, which is memory
+// traffic for every lane), one after the other 843 us (12), the carries loaded only once the summaries are stored 817 us, and no product of the
+// decays kept from one walk for the next 663 us.
+constexpr int kPairWaves = 8, kPairItems = 4;
+constexpr int kPairColumns = 128;         // columns of a block, at most (one slab)
+struct PairSegs {
+    float D[2][kPairWaves];
+    int H[2][kPairWaves];
+    float S[2][kPairWaves][kPairColumns], Q[2][kPairWaves][kPairColumns];
+};
+
+template <bool RAG>
+__global__ void __launch_bounds__(kPairWaves * 64, 4)
+k_scan_down_pair(const ScanArgs A)
+{
+    constexpr int ITEMS = kPairItems, WAVES = kPairWaves, THREADS = WAVES * 64, VEC = 4;
+    __shared__ float4 zx_all[ITEMS * THREADS], ef_all[ITEMS * THREADS];
+    static_assert(sizeof(PairSegs) <= sizeof(ef_all), "the exchange of wavefront summaries lies where gy's strict forward values are written later");
+    PairSegs& W = *reinterpret_cast<PairSegs*>(ef_all);
+    float4* const zx = zx_all + threadIdx.x;          // the strict scans of x, row i at zx[i * THREADS]
+    float4* const ef = ef_all + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
+    const uint32_t poison = plan_poison(A.counters);
+    const int64_t tile = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bv = A.bv, rv = A.rv;
+    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
+    const int64_t wave_row0 = tile * A.tile_rows + (int64_t)(wave * rv) * ITEMS;
+    const int64_t row0 = wave_row0 + (int64_t)r * ITEMS;
+    const int64_t col0 = (int64_t)c * VEC;
+    const bool col_ok = col0 < A.batch;
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+
+    float dh[ITEMS + 1];
+    uint32_t id[ITEMS];
+#pragma unroll
+    for (int i = 0; i <= ITEMS; ++i) {
+        const int64_t j = row0 + i;
+        const float d = A.dh[j <= A.N ? j : A.N];
+        dh[i] = j <= A.N ? d : -1.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const int64_t j = row0 + i;
+        const uint32_t v = A.ids[j < A.N ? j : A.N - 1];
+        id[i] = j < A.N ? v : 0xFFFFFFFFu;
+    }
+    auto head_fwd = [&](int i) { return id[i] != 0xFFFFFFFFu && dh[i] >= 0.0f; };
+    auto head_bwd = [&](int i) { return id[i] != 0xFFFFFFFFu && dh[i + 1] >= 0.0f; };
+    float x[ITEMS][VEC], v[ITEMS][VEC];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) load_row_or_zero<VEC, true, RAG>(x[i], A.w, (int64_t)id[i] * A.ld_w + col0, col_ok && id[i] != 0xFFFFFFFFu, end);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) load_row_or_zero<VEC, true, RAG>(v[i], A.inj, (int64_t)id[i] * A.ld_inj + col0, col_ok && id[i] != 0xFFFFFFFFu, end);
+    const int64_t tile_base = tile * A.tile_rows, rows_after = row0 + ITEMS;
+    const float lane_df = span_decay_f(A, row0, ITEMS), lane_db = span_decay_b(A, row0, ITEMS);
+    const float wave_df = span_decay_f(A, wave_row0, rv * ITEMS), wave_db = span_decay_b(A, wave_row0, rv * ITEMS);
+    const float Df = span_decay_f(A, tile_base, row0 - tile_base), Db = span_decay_b(A, rows_after, tile_base + A.tile_rows - rows_after);
+    const bool Hf = span_head_f(A, tile_base, row0 - tile_base), Hb = span_head_b(A, rows_after, tile_base + A.tile_rows - rows_after);
+
+    __builtin_amdgcn_sched_barrier(0);
+    auto put = [&](int dir, const Seg<VEC, true>& s, float D) {
+        if (c == 0) { W.D[dir][wave] = D; W.H[dir][wave] = s.H; }
+        *reinterpret_cast<float4*>(&W.S[dir][wave][c * VEC]) = make_float4(s.S[0], s.S[1], s.S[2], s.S[3]);
+        *reinterpret_cast<float4*>(&W.Q[dir][wave][c * VEC]) = make_float4(s.Q[0], s.Q[1], s.Q[2], s.Q[3]);
+    };
+    // the states a row-lane starts from: the earlier rows of the block, and the block's carries decayed over them
+    auto states = [&](float (&u)[ITEMS][VEC], const float* car_f, const float* car_e, float (&F)[VEC], float (&E)[VEC], float (&R)[VEC], float (&G)[VEC]) {
+        Seg<VEC, true> f = seg_identity<VEC, true>(), b = f;
+#pragma unroll
+        for (int i = 0; i <= ITEMS; ++i) asm volatile("" : "+v"(dh[i]));          // nothing of the other problem's walk is kept for this one
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) seg_push<VEC, true>(f, head_fwd(i), dh[i], u[i]);
+        f.D = lane_df;
+        f = wave_scan<true, VEC, true>(f, lane, bv, rv);
+        if (r == rv - 1) put(0, f, wave_df);
+        f = seg_shfl<VEC, true>(f, (lane - bv) & 63);
+        if (r == 0) f = seg_identity<VEC, true>();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = ITEMS - 1; i >= 0; --i) seg_push<VEC, true>(b, head_bwd(i), dh[i + 1], u[i]);
+        b.D = lane_db;
+        b = wave_scan<false, VEC, true>(b, lane, bv, rv);
+        if (r == 0) put(1, b, wave_db);
+        b = seg_shfl<VEC, true>(b, (lane + bv) & 63);
+        if (r == rv - 1) b = seg_identity<VEC, true>();
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t at = tile * A.bpad + (col_ok ? col0 : 0), back = A.l1.count * A.bpad;
+        float Fc[VEC], Ec[VEC], Rc[VEC], Gc[VEC];
+        load_vec<VEC>(Fc, car_f + at); load_vec<VEC>(Ec, car_e + at);
+        load_vec<VEC>(Rc, car_f + back + at); load_vec<VEC>(Gc, car_e + back + at);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { F[e] = E[e] = R[e] = G[e] = 0.0f; }
+#pragma unroll 1
+        for (int q = 0; q < WAVES - 1; ++q) {          // (uniform: wave of them before this one, the others after it)
+            const int dir = q < wave ? 0 : 1, w = q < wave ? q : WAVES - 1 - (q - wave);
+            Seg<VEC, true> o;
+            o.D = W.D[dir][w]; o.H = W.H[dir][w]; o.C = o.D;
+            const float4 S = *reinterpret_cast<const float4*>(&W.S[dir][w][c * VEC]), Q = *reinterpret_cast<const float4*>(&W.Q[dir][w][c * VEC]);
+            o.S[0] = S.x; o.S[1] = S.y; o.S[2] = S.z; o.S[3] = S.w;
+            o.Q[0] = Q.x; o.Q[1] = Q.y; o.Q[2] = Q.z; o.Q[3] = Q.w;
+            if (dir == 0) seg_apply<VEC, true>(o, F, E); else seg_apply<VEC, true>(o, R, G);
+        }
+        seg_apply<VEC, true>(f, F, E);
+        seg_apply<VEC, true>(b, R, G);
+        enter_state<VEC, true>(F, E, Fc, Ec, Df, Hf);
+        enter_state<VEC, true>(R, G, Rc, Gc, Db, Hb);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    float F[VEC], E[VEC], R[VEC], G[VEC];
+    states(x, A.pair_car_f, A.pair_car_e, F, E, R, G);
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool h = head_fwd(i);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            E[e] = h ? dh[i] * F[e] : E[e];
+            F[e] = (h ? E[e] : F[e]) + x[i][e];
+        }
+        zx[i * THREADS] = make_float4(E[0], E[1], E[2], E[3]);
+    }
+#pragma unroll
+    for (int i = ITEMS - 1; i >= 0; --i) {
+        const bool h = head_bwd(i);
+        const float4 ef = zx[i * THREADS];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            G[e] = h ? dh[i + 1] * R[e] : G[e];
+            R[e] = (h ? G[e] : R[e]) + x[i][e];
+        }
+        zx[i * THREADS] = make_float4(G[0] - ef.x, G[1] - ef.y, G[2] - ef.z, G[3] - ef.w);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();          // every wavefront is done with the summaries
+    states(v, A.l1.car_f, A.l1.car_e, F, E, R, G);
+    __syncthreads();
+    float Ff[ITEMS][VEC];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+        const bool h = head_fwd(i);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            E[e] = h ? dh[i] * F[e] : E[e];
+            F[e] = (h ? E[e] : F[e]) + v[i][e];
+            Ff[i][e] = F[e];
+        }
+        ef[i * THREADS] = make_float4(E[0], E[1], E[2], E[3]);
+    }
+    float racc[ITEMS];
+    uint32_t rrow[ITEMS];
+#pragma unroll
+    for (int i = ITEMS - 1; i >= 0; --i) {
+        __builtin_amdgcn_sched_barrier(0);
+        const bool h = head_bwd(i);
+        const float4 zi = zx[i * THREADS], ei = ef[i * THREADS];
+        const float Zx[VEC] = {zi.x, zi.y, zi.z, zi.w}, Ef[VEC] = {ei.x, ei.y, ei.z, ei.w};
+        float P[VEC], acc = 0.0f;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            G[e] = h ? dh[i + 1] * R[e] : G[e];
+            R[e] = (h ? G[e] : R[e]) + v[i][e];
+            P[e] = taint(Ff[i][e] + R[e] - v[i][e], poison);
+            acc += v[i][e] * Zx[e];
+        }
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc += x[i][e] * (G[e] - Ef[e]);
+        const bool is_res = id[i] != 0xFFFFFFFFu;
+        if (is_res && col_ok && A.out_p) store_row<VEC, RAG>(A.out_p + (int64_t)id[i] * A.ld_p + col0, P, end);
+        racc[i] = taint(acc, poison);
+        rrow[i] = is_res ? id[i] : kNoRow;
+    }
+    emit_row_sums<ITEMS>(racc, rrow, bv, c, A.out_red, A.ld_red);
+}
+
+// ---------------------------------------------------------------------------
 // downsweep, wide geometry, blocks with injected rows and at most kFewRows result rows (an apply
 // with few outputs): one WAVEFRONT per block.  Result row r is
 //   P_r = D_f Fc + D_b Rc + sum_l exp(-|p_r - p_l|) v_l          (Sec. 1: the definition, inside the block)
@@ -3111,6 +3298,17 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         else
             LAPLEX_TIMED(ff.c_str(), st, hipLaunchKernelGGL((k_scan_down_fewres<STRICT, 1>), fgrid, dim3(kFewWaves * 64), 0, st, A));
     }
+    if (A.keep_carries == 2) return;
+    if constexpr (VEC == 4 && STRICT) {
+        if (A.pair_car_f) {
+            LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down_pair<RAG>), dim3((unsigned)g.blocks), dim3(kPairWaves * 64), 0, st, A));
+            return;
+        }
+        if (A.keep_carries) {          // (9 to 128 columns, every block with injected and result rows)
+            LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down<VEC, false, kBlockWavesNarrow, false, false, RAG>), dgrid, bblock, 0, st, A));
+            return;
+        }
+    }
     {
         const bool red = STRICT && A.out_red != nullptr;
         auto go = [&](auto kernel) { LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL(kernel, dgrid, bblock, 0, st, A)); };
@@ -3149,7 +3347,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
 
 hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStream_t st)
 {
-    const bool strict = p.out_z != nullptr || p.out_red != nullptr || p.emit_strict;
+    const bool strict = p.out_z != nullptr || p.out_red != nullptr || p.emit_strict || p.carries != nullptr;
     // 128-bit lanes need every row start of every matrix touched to be 16-byte aligned
     bool v4 = p.batch % 4 == 0 && p.batch >= 4;
     v4 = v4 && aligned16(p.inj) && p.ld_inj % 4 == 0;
@@ -3204,6 +3402,11 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.l1 = Level{reinterpret_cast<float4*>(ws + L.off_agg_scalar), reinterpret_cast<float*>(ws + L.off_agg_s),
                  reinterpret_cast<float*>(ws + L.off_agg_q), reinterpret_cast<float*>(ws + L.off_car_f),
                  reinterpret_cast<float*>(ws + L.off_car_e), g.tiles};
+    A.keep_carries = p.carries ? (p.out_p ? 1 : 2) : 0;
+    if (p.carries) { A.l1.car_f = p.carries; A.l1.car_e = p.carries + 2 * g.tiles * L.bpad; }
+    A.pair_car_f = p.pair_carries;
+    A.pair_car_e = p.pair_carries ? p.pair_carries + 2 * g.tiles * L.bpad : nullptr;
+    if ((p.carries || p.pair_carries) && (g.vec != 4 || g.sub_shift || g.slabs != 1 || p.stage)) return hipErrorInvalidValue;
     A.l2 = Level{reinterpret_cast<float4*>(ws + L.off_agg2_scalar), reinterpret_cast<float*>(ws + L.off_agg2_s),
                  reinterpret_cast<float*>(ws + L.off_agg2_q), reinterpret_cast<float*>(ws + L.off_car2_f),
                  reinterpret_cast<float*>(ws + L.off_car2_e), g.chunks};

@@ -843,3 +843,37 @@ def test_gram_pair_by_pair(oracle, n, batch):
 def test_sample_sort_short_stretches(oracle, N, kind):
     """The same where the sort's stretches go from 512 to 1024 pairs on average."""
     test_sample_sort_order_and_decays(oracle, N, kind)
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties"])
+@pytest.mark.parametrize("n,batch,pad", [(8193, 9, 0), (8704, 12, 4), (8705, 16, 1), (8703, 33, 0), (8449, 64, 0), (8256, 65, 3), (8255, 128, 0), (12289, 127, 0)])
+def test_gram_both_matrices_in_one_walk(oracle, n, batch, pad, kind):
+    """Square form, 9 to 128 columns: the backward scans x beside gy from the carries that the forward kept; whole and partial blocks (512 to 64
+    rows), whole and ragged rows, equal anchors."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(n + batch)
+    a, _ = anchors(kind, r, n, 1)
+    x, g = (r.normal(size=(n, batch)).astype(np.float32) for _ in range(2))
+    ref, tol = oracle.gram_scan(a, x)
+    want, tols = oracle.gram_backward_scan(a, x, g)
+    da = torch.from_numpy(a).cuda()
+    wide = torch.zeros(3, n, batch + pad, device="cuda")
+    dx, dg, gx = (w[:, :batch] for w in wide)
+    dx.copy_(torch.from_numpy(x)); dg.copy_(torch.from_numpy(g))
+    y = torch.empty(n, batch, device="cuda"); ga = torch.empty(n, device="cuda")
+    ws = torch.full((B.laplex_workspace_bytes(0, n, batch),), 0xFF, dtype=torch.uint8, device="cuda")
+    B.laplex_gram(da, dx, y, ws, B.LAPLEX_SAVE_SCANS)
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    first = None
+    for flags, want_gx in ((B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, True), (B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, False), (0, True), (0, False)):
+        ga.fill_(np.nan); wide[2].fill_(np.nan)
+        B.laplex_gram_backward(da, dx, dg, gx if want_gx else None, ga, ws, flags)
+        torch.cuda.synchronize()
+        got = gx.cpu().numpy(), ga.cpu().numpy()
+        if first is None: first = got
+        assert_close("ga", got[1], want[1], tols[1])
+        assert np.array_equal(got[1], first[1])
+        if want_gx:
+            assert_close("gx", got[0], want[0], tols[0])
+            assert np.array_equal(got[0], first[0])
+        assert pad == 0 or bool(torch.isnan(wide[2, :, batch:]).all())
