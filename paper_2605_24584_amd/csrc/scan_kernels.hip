@@ -1883,13 +1883,13 @@ k_scan_down(const ScanArgs A)
 // ga_m = sum_t (gy Z^x + x Z^g)[m, t] needs the strict scans of both matrices.  Those of x are not kept by the forward (a matrix written there,
 // scattered, and gathered again here): only the states that enter its blocks are, and the rows of x, which are read here in any case, are walked before
 // those of gy, their strict scans held in LDS.  Bound by the gathered rows and by its own latency: 2.4 GB at n = 3 x 2^20, batch 64 (gy and x read,
-// gx written) in 663 us, where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
-// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1450 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 461 us;
+// gx written) in 649 us, where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
+// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1430 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 461 us;
 // n = 300001, batch 128: 388 -> 348 us; n = 10^5, batch 64: 127 -> 126 us.
 // A block has the rows of k_scan_down's, as eight wavefronts with four rows a row-lane instead of four with eight: 128 registers, two
 // workgroups to a compute unit.  Registers are what decides it: both matrices in one walk 1315 us (50 registers in scratch, which is memory
 // traffic for every lane), one after the other 843 us (12), the carries loaded only once the summaries are stored 817 us, and no product of the
-// decays kept from one walk for the next 663 us.
+// decays kept from one walk for the next 663 us, and the plan's status word read after the walks 649 us (none left).
 constexpr int kPairWaves = 8, kPairItems = 4;
 constexpr int kPairColumns = 128;         // columns of a block, at most (one slab)
 struct PairSegs {
@@ -1909,7 +1909,6 @@ k_scan_down_pair(const ScanArgs A)
     float4* const zx = zx_all + threadIdx.x;          // the strict scans of x, row i at zx[i * THREADS]
     float4* const ef = ef_all + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
-    const uint32_t poison = plan_poison(A.counters);
     const int64_t tile = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bv = A.bv, rv = A.rv;
@@ -2036,6 +2035,7 @@ k_scan_down_pair(const ScanArgs A)
         }
         ef[i * THREADS] = make_float4(E[0], E[1], E[2], E[3]);
     }
+    const uint32_t poison = plan_poison(A.counters);          // (here: a register less through the walks)
     float racc[ITEMS];
     uint32_t rrow[ITEMS];
 #pragma unroll
