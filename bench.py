@@ -291,8 +291,8 @@ KERNEL_OF = {
     "scan_down_sparse.bwd": "k_scan_down_sparse_wide<true> (backward downsweep: reads x, writes gx and gb)",
     "scan_reduce.fwd": "forward reduce (reads the injected rows of x once for both directions)",
     "scan_reduce.bwd": "backward reduce (reads the injected rows of gy once for both directions)",
-    "scan_down.fwd": "k_scan_down, forward problem (reads x, writes y and the saved scans)",
-    "scan_down.bwd": "k_scan_down, backward problem (reads gy, x and the saved scans, writes gx and the anchor gradient)",
+    "scan_down.fwd": "k_scan_down, forward problem (reads x, writes y and, but for the square form, the saved scans)",
+    "scan_down.bwd": "backward downsweep (k_scan_down: reads gy, x and, for the square form at batch 1 to 8, the saved scans; k_scan_down_pair: gy and x; writes gx and the anchor gradient)",
     "radix_scatter": "k_onesweep_pass (one radix pass: reads the pairs once, writes them once)",
     "deep_sort": "k_deep_sort (a unit of the sorted sequence gathered, sorted in LDS and written to the plan)",
     "deep_pieces": "k_deep_distribute<true> (pairs of a bucket to its stretches)",
@@ -350,12 +350,13 @@ def family_bytes(fam, spec, np, B):
     if base == "scan_down":
         total = 8 * N + 4 * batch * (N if narrow else inj[tag]) + 4 * batch * res[tag]
         note = "id and decay per row, the injected rows" + (" (from the sorted-order stage)" if narrow else "") + ", the result rows written"
+        together = gram and 9 <= batch <= 128        # the backward scans x beside gy: no strict scan is kept
         if tag == "fwd":
-            total += 4 * batch * res[tag]; note += ", the saved strict scans written"
+            if not together: total += 4 * batch * res[tag]; note += ", the saved strict scans written"
         else:
             total += 4 * batch * (N if narrow else res[tag]) + 4 * res[tag]
             note += ", the weights of the row reduction read, the anchor gradient written"
-            if gram:
+            if gram and not together:
                 total += 4 * batch * res[tag]; note += ", the saved strict scans read"
         return total, note
     if fam == "scan_down_sparse.bwd" and not gram and batch >= 253 and batch % 4 == 0:

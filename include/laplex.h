@@ -84,7 +84,8 @@ enum {
 
 enum {
     /* The caller promises a / b ascending.  With both set (or A_SORTED for the
-     * Gram form) the radix sort is replaced by one merge-path pass.  A wrong
+     * Gram form) the sort is replaced by one merge-path pass (not with one column
+     * from 2^22 merged positions on, where x follows the sort's passes).  A wrong
      * promise gives wrong values, never a fault. */
     LAPLEX_A_SORTED = 1u,
     LAPLEX_B_SORTED = 2u,
@@ -92,7 +93,8 @@ enum {
      * earlier call with the same k, n, batch): skip sort, merge and decay. */
     LAPLEX_REUSE_PLAN = 4u,
     /* Forward calls: also store, per output row and batch column, the signed
-     * difference of the strict right and left scans in the workspace.
+     * difference of the strict right and left scans in the workspace (the Gram
+     * form with 9 to 128 columns: what its backward needs to form them again).
      * Backward calls: that region was stored by the forward call on the same
      * (anchors, x); use it for the anchor gradient instead of re-scanning x. */
     LAPLEX_SAVE_SCANS = 8u

@@ -15,8 +15,10 @@ extern "C" {
 /*
  * Kernel-family timing.  Between begin and end,
  * every launch of the named kernel family ("split_sample", "split_pick", "split_tiles",
- * "split_sort", "sort_hist", "radix_scatter", "merge", "decay", "rowdot", "sum_slabs", "fill", and "scan_meta.T", "scan_reduce.T",
- * "scan_spine.T", "scan_down.T", "scan_down_sparse.T" with T = "fwd" for the
+ * "split_sort", "deep_sample", "deep_bounds", "deep_tiles", "deep_columns", "deep_pieces", "deep_units", "deep_sort", "deep_edges",
+ * "sort_hist", "radix_scatter", "merge", "decay", "small_sort", "small", "small_pairs", "rowdot", "sum_slabs", "fill", and "scan_meta.T",
+ * "scan_reduce.T", "scan_spine.T", "scan_down.T", "scan_down_sparse.T", "move_tiles.T", "move_pieces.T", "move_units.T" (one column: values into
+ * sorted order), "permute_part.T", "permute_final.T" (results home) with T = "fwd" for the
  * forward scans of x, "bwd" for the backward scans of gy, "rescan" for the
  * backward's repeat of the forward scans when they were not saved) is bracketed by a pair of HIP
  * events on the stream it is launched on.  laplex_profile_end waits for those
@@ -77,8 +79,8 @@ int laplex_diag_set_plan_status(void* ws, size_t ws_bytes, int64_t count, uint32
 
 /*
  * Test hook (host, process-wide): batch-1 problems with at least this many merged positions k + n (and more
- * than 8192) move x, gy and the results between the caller's order and the sorted order through partition
- * passes instead of random accesses (default 2^22: below, the tables fit the device's caches and the random accesses are as fast).  Lets tests
+ * than 8192) sort by samples in two distributions, move x and gy into sorted order through that sort's passes and the results
+ * home through partition passes, instead of by random accesses (default 2^22: below, the tables fit the device's caches and the random accesses are as fast).  Lets tests
  * run that route on small problems.  A plan must be reused under the setting it was built with.
  */
 int laplex_diag_set_route_min(int64_t merged_positions);
