@@ -24,11 +24,11 @@
 // would have to leave most of it free.
 //
 // What bounds it: memory traffic in the tiles (10 bytes a pair, 3.8 TB/s), latency elsewhere: a workgroup passes eight to twelve barriers with
-// loads and LDS atomics in between, two or three workgroups a compute unit (16 bytes a pair in the pieces, 3.1 TB/s, 23 in the sort, 3.2).
+// loads and LDS atomics in between, two or three workgroups a compute unit (16 bytes a pair in the pieces, 3.5 TB/s, 23 in the sort, 3.2).
 //
 // Measured (MI355X, us, before / now; before: four radix passes with chained look-back, histogram, a decay pass, the inverse permutation by
-// partition passes of (id, position), and values in as (rank, value) records): the plan of 2^28 positions 7720 / 4220, a move of 2^27 values into their
-// order 1350 / 1050; forward + backward at 2^27 x 2^27 17097 / 12973, 2^24 x 2^24 with 32 equal anchors a value 2441 / 1851, 2^22 x 2^22 574 /
+// partition passes of (id, position), and values in as (rank, value) records): the plan of 2^28 positions 7720 / 4080, a move of 2^27 values into their
+// order 1350 / 1050; forward + backward at 2^27 x 2^27 17115 / 12850, 2^24 x 2^24 with 32 equal anchors a value 2451 / 1841, 2^22 x 2^22 574 /
 // 515, 2^24 x 2^24 in order (merge path before) 2325 / 2045.  The workspace is 26 % smaller.  What was tried and did not pay: units of stretches with three times the
 // pairs (LDS for the longest, a third filled): 5090 us for the sort of 2^28 pairs in place of 1893; 1024 threads of 4 pairs 2254, 256 of 16 2092.
 #include "split_sort.h"
@@ -239,8 +239,17 @@ k_deep_distribute(const DeepArgs A)
         at[i] = S.hist[at[i] >> 16] + (at[i] & 0xFFFFu);
         S.lay[at[i]] = key[i];
         if (PIECES && q < (uint32_t)len) slot2[q] = (uint16_t)at[i];
+        if (PIECES && i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+    // (a piece's ids are there as well: two places to a register while the keys come back, and places formed again; with one each six registers went
+    // to scratch, 24 bytes of memory traffic a lane: 2^28 pairs 1370 -> 1227 us, 2^25 183 -> 172)
+#pragma unroll
+    for (int i = 0; PIECES && i < kDeepPer; i += 2) {
+        at[i] |= at[i + 1] << 16;
+        asm volatile("" : "+v"(at[i]));
     }
     __syncthreads();
+    if (PIECES) asm volatile("" : "+v"(me));
 #pragma unroll
     for (int i = 0; i < kDeepPer; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads) + me;
@@ -249,8 +258,9 @@ k_deep_distribute(const DeepArgs A)
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) S.lay[at[i]] = other[i];
+    for (int i = 0; i < kDeepPer; ++i) S.lay[!PIECES ? at[i] : i % 2 ? at[i - 1] >> 16 : at[i] & 0xFFFFu] = other[i];
     __syncthreads();
+    if (PIECES) asm volatile("" : "+v"(me));
 #pragma unroll
     for (int i = 0; i < kDeepPer; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads) + me;
