@@ -584,9 +584,13 @@ __device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&ro
             const bool upper = (c & m) != 0;
 #pragma unroll
             for (int i = 0; i < half; ++i) {
-                const float mine = upper ? acc[i + half] : acc[i], other = upper ? acc[i] : acc[i + half];
+                // (values, not elements, are chosen: an array of which an element is chosen by address lies in scratch or LDS; 2999 x 100003, batch 33,
+                // forward + backward: 122.5 -> 119.6 us, 2^20 x 2^20, batch 8: 347 -> 344.5)
+                const float a0 = acc[i], a1 = acc[i + half];
+                const uint32_t r0 = rows[i], r1 = rows[i + half];
+                const float mine = upper ? a1 : a0, other = upper ? a0 : a1;
                 acc[i] = mine + __shfl_xor(other, m);
-                rows[i] = upper ? rows[i + half] : rows[i];
+                rows[i] = upper ? r1 : r0;
                 rows[i + half] = kNoRow;
             }
             m <<= 1;
@@ -1884,7 +1888,7 @@ k_scan_down(const ScanArgs A)
 // scattered, and gathered again here): only the states that enter its blocks are, and the rows of x, which are read here in any case, are walked before
 // those of gy, their strict scans held in LDS.  Bound by the gathered rows and by its own latency: 2.4 GB at n = 3 x 2^20, batch 64 (gy and x read,
 // gx written) in 649 us, where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
-// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1430 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 461 us;
+// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1430 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 449 us;
 // n = 300001, batch 128: 388 -> 348 us; n = 10^5, batch 64: 127 -> 126 us.
 // A block has the rows of k_scan_down's, as eight wavefronts with four rows a row-lane instead of four with eight: 128 registers, two
 // workgroups to a compute unit.  Registers are what decides it: both matrices in one walk 1315 us (50 registers in scratch, which is memory
@@ -2036,8 +2040,6 @@ k_scan_down_pair(const ScanArgs A)
         ef[i * THREADS] = make_float4(E[0], E[1], E[2], E[3]);
     }
     const uint32_t poison = plan_poison(A.counters);          // (here: a register less through the walks)
-    float racc[ITEMS];
-    uint32_t rrow[ITEMS];
 #pragma unroll
     for (int i = ITEMS - 1; i >= 0; --i) {
         __builtin_amdgcn_sched_barrier(0);
@@ -2056,9 +2058,13 @@ k_scan_down_pair(const ScanArgs A)
         for (int e = 0; e < VEC; ++e) acc += x[i][e] * (G[e] - Ef[e]);
         const bool is_res = id[i] != 0xFFFFFFFFu;
         if (is_res && col_ok && A.out_p) store_row<VEC, RAG>(A.out_p + (int64_t)id[i] * A.ld_p + col0, P, end);
-        racc[i] = taint(acc, poison);
-        rrow[i] = is_res ? id[i] : kNoRow;
+        zx[i * THREADS].x = taint(acc, poison);          // (waits there: four registers less through the walk)
     }
+    __builtin_amdgcn_sched_barrier(0);
+    float racc[ITEMS];
+    uint32_t rrow[ITEMS];
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) { racc[i] = zx[i * THREADS].x; rrow[i] = id[i] != 0xFFFFFFFFu ? id[i] : kNoRow; }
     emit_row_sums<ITEMS>(racc, rrow, bv, c, A.out_red, A.ld_red);
 }
 
