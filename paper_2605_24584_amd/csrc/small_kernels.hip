@@ -112,7 +112,7 @@ k_small_rank(SmallArgs A, int queries)
 // Few pairs: the products by the definition (Sec. 1), y_i = sum_j exp(-|a_i - b_j|) x_j and, for the anchor gradients, the same sum with the sign
 // of b_j - a_i and without the pairs that are tied, straight from the anchors.  They need no sorted order, so the plan is ranked by other workgroups of the same launch, and a
 // call is one launch where ranks and scans are two in a row (measured: see small_pairwise).  Bound by the launch and one chain of loads,
-// then by the vector units: an exponential of six instructions and one or two multiply-adds a column for every pair.
+// then by the vector units: an exponential of eight instructions and one or two multiply-adds a column for every pair.
 // A wavefront takes ROWS result rows and every fourth 64 of the injected rows, a lane one injected row at a time; lanes and the four quarters are added up
 // as a butterfly and in order, so the sums are trees over chains of m / 256 terms.
 // ---------------------------------------------------------------------------
@@ -121,17 +121,19 @@ constexpr int kPairGroups = kSmallWaves / kPairSplits;
 template <int C> constexpr int kPairKeptGroups = C == 1 ? 1 : kPairGroups;      // (rows of several columns are staged once for as many result rows as there are)
 template <int C> constexpr int kPairRows = C <= 2 ? 4 : 2;                 // result rows of a wavefront
 
-// exp(-x) for x >= 0 to about one unit in the last place: the hardware's 2^t, with what rounding the product x log2(e) lost put back.
-// (200: the result is zero from 104 on.)
+// exp(-x) for x >= 0 within 0.82 units in the last place (measured over [0, 104]), subnormal results included: x log2(e) is split into a whole
+// number, which goes straight into the exponent, and a fraction for the hardware's 2^f, which returns no subnormal numbers itself (2^t of the whole
+// product lost every weight below 2^-126, and with it outputs whose nearest input is 88 to 104 away).  The exponent is kept 64 too high
+// until the last multiplication, the one place where a subnormal result is rounded; from 130 on the result is zero, as it is from 104 on.
+// (n = k = 4096, batch 1: 14.6 us; v_ldexp in place of the last two steps 14.8, with v_rndne and v_cvt before it 15.2; 2^t at once 14.7.)
 __device__ __forceinline__ float exp_minus(float x)
 {
-    constexpr float log2e = 1.44269504088896340736f, log2e_low = 1.92596299112661746887e-8f, ln2 = 0.69314718055994530942f;
-    x = fminf(x, 200.0f);
-    const float t = x * -log2e;
-    float low = __builtin_fmaf(x, -log2e, -t);
-    low = __builtin_fmaf(x, -log2e_low, low);
-    const float e = __builtin_amdgcn_exp2f(t);
-    return __builtin_fmaf(e, low * ln2, e);
+    constexpr float log2e = 1.44269504088896340736f, log2e_low = 1.92596299112661746887e-8f, down = 5.42101086242752217004e-20f;      // down: 2^-64
+    constexpr float round = 12582912.0f + 64.0f;          // 3 * 2^22: adding it rounds to a whole number, which is then in the lower bits
+    x = fminf(x, 130.0f);
+    const float sum = __builtin_fmaf(x, -log2e, round);
+    const float f = __builtin_fmaf(x, -log2e_low, __builtin_fmaf(x, -log2e, round - sum));
+    return __uint_as_float(__float_as_uint(__builtin_amdgcn_exp2f(f)) + (__float_as_uint(sum) << 23)) * down;
 }
 
 // The sum over the wavefront, in lane 63 only.  The last LATE of its six steps are in fp64, like the sum of the quarters after them: a tree's error is that

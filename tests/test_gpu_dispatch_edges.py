@@ -877,3 +877,45 @@ def test_gram_both_matrices_in_one_walk(oracle, n, batch, pad, kind):
             assert_close("gx", got[0], want[0], tols[0])
             assert np.array_equal(got[0], first[0])
         assert pad == 0 or bool(torch.isnan(wide[2, :, batch:]).all())
+
+
+@pytest.mark.parametrize("batch", [1, 2, 4, 8])
+def test_products_pair_by_pair_weights(batch):
+    """One input of value one: the products are the weights exp(-d) themselves, d from 0 to beyond where they end.  Three units in the last place where they are
+    normal numbers; below, where a unit is 2^-149, one and a half: half of one for the rounding, one for what the exponential is off before it."""
+    d = np.concatenate([np.linspace(0, 110, 600), np.linspace(86, 104.5, 400)]).astype(np.float32)
+    a, b = (d * np.where(np.arange(d.size) % 2, 1, -1)).astype(np.float32), np.zeros(1, dtype=np.float32)
+    ws = torch.empty(B.laplex_workspace_bytes(a.size, 1, batch), dtype=torch.uint8, device="cuda")
+    y = torch.empty(a.size, batch, device="cuda")
+    B.laplex_apply(dev(a), dev(b), torch.ones(1, batch, device="cuda"), y, ws, 0)
+    torch.cuda.synchronize()
+    ref = np.exp(-d.astype(np.float64))[:, None]
+    unit = np.spacing(ref.astype(np.float32)).astype(np.float64)
+    units = np.abs(y.cpu().numpy().astype(np.float64) - ref) / unit
+    low = np.broadcast_to(ref < 2.0 ** -126, units.shape)
+    assert units[~low].max() <= 3.0 and units[low].max() <= 1.5, (units[~low].max(), units[low].max())
+
+
+@pytest.mark.parametrize("k,n,batch", [(700, 900, 1), (4000, 4000, 1), (8000, 100, 1), (500, 400, 2), (300, 1100, 4), (900, 300, 8), (4200, 3900, 1), (2500, 2400, 8),
+                                       (40, 60, 20)])
+def test_small_problems_of_two_clusters_far_apart(oracle, k, n, batch):
+    """Outputs 88 to 103 away from every input, rows of size 1e30: weights that are no normal numbers, sums that are.  |err| against fp64 is at most
+    2^-149 (a unit of such a weight) and 1e-6 of the weight (anchors of size 100 differ by exact numbers; products of two normal decays in the scans) for
+    every term; either side of the lines up to which the products are formed pair by pair."""
+    r = np.random.default_rng(k + batch)
+    a, b = r.uniform(0, 7, k).astype(np.float32), r.uniform(95, 103, n).astype(np.float32)
+    x, g = (r.choice([-1e30, 1e30], (s, batch)) * r.uniform(1, 2, (s, batch)) for s in (n, k))
+    x, g = x.astype(np.float32), g.astype(np.float32)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    y, gx, ga, gb = (torch.full(s, float("nan"), device="cuda") for s in ((k, batch), (n, batch), (k,), (n,)))
+    B.laplex_apply(dev(a), dev(b), dev(x), y, ws, B.LAPLEX_SAVE_SCANS)
+    B.laplex_apply_backward(dev(a), dev(b), dev(x), dev(g), gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+    torch.cuda.synchronize()
+    w = np.exp(-np.abs(a.astype(np.float64)[:, None] - b.astype(np.float64)[None, :]))
+    off = 2.0 ** -149 + 1e-6 * w
+    x, g = x.astype(np.float64), g.astype(np.float64)
+    ref = w @ x, w.T @ g, np.sum(g * (w @ x), 1), -np.sum(x * (w.T @ g), 1)
+    bar = off @ np.abs(x), off.T @ np.abs(g), np.sum(np.abs(g) * (off @ np.abs(x)), 1), np.sum(np.abs(x) * (off.T @ np.abs(g)), 1)
+    for name, got, rv, tv in zip(("y", "gx", "ga", "gb"), (y, gx, ga, gb), ref, bar):
+        worst = float((np.abs(got.cpu().numpy().astype(np.float64) - rv) / tv).max())
+        assert worst <= 1.0, f"{name}: {worst:.3g} times the bar"
