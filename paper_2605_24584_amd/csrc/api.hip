@@ -596,7 +596,8 @@ int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* 
     return LAPLEX_OK;
 }
 
-// The plans of many small operators where sorting them beats ranking them: the flags then say that they are there.
+// The plans of many small operators where sorting them beats ranking them (so many that none of their products are formed pair by pair, beside the
+// ranks: small_pairwise): the flags then say that they are there.
 int mix_small_sorted(const MixLayout& M, const Layout& L, const Plan& P, char* base, const float* a, const float* b, int64_t r, int64_t k, int64_t n,
                      uint32_t& flags, hipStream_t st)
 {
@@ -778,28 +779,29 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     if (use_small(L)) {            // a sort, one launch for both scan problems, then the two row reductions
         SmallArgs S = small_args(a, k, b, n, tau, P, L, flags);
         float* zg = reinterpret_cast<float*>(w + L.off_small);
-        const bool fused = small_pairwise(k, n, batch, 1) == 1;      // the row reductions where the products are formed
+        // the row reductions where the products are formed
+        const bool fused_a = small_pairwise(k, n, batch, 1, false) == 1, fused_b = small_pairwise(k, n, batch, 1, true) == 1;
         SmallDots D{};
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {     // strict scans of x at the outputs, not kept by the forward
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = x; q.ld_inj = ldx; q.inj_lo = (uint32_t)k; q.inj_hi = (uint32_t)(k + n);
             q.res_lo = 0; q.res_hi = (uint32_t)k;
-            if (fused) D.prob[0] = {ga, gy, ldgy, nullptr, 0, nullptr}; else q.out_z = P.z;
+            if (fused_a) D.prob[0] = {ga, gy, ldgy, nullptr, 0, nullptr}; else q.out_z = P.z;
         }
         if (gx || gb) {
             SmallProblem& q = S.prob[S.nprob++];
             q.inj = gy; q.ld_inj = ldgy; q.inj_lo = 0; q.inj_hi = (uint32_t)k;
             q.res_lo = (uint32_t)k; q.res_hi = (uint32_t)(k + n);
             q.out_p = gx; q.ld_p = ldgx;
-            if (gb && fused) D.prob[S.nprob - 1] = {gb, x, ldx, nullptr, 0, nullptr}; else q.out_z = gb ? zg : nullptr;
+            if (gb && fused_b) D.prob[S.nprob - 1] = {gb, x, ldx, nullptr, 0, nullptr}; else q.out_z = gb ? zg : nullptr;
         }
-        if (ga && fused && (flags & LAPLEX_SAVE_SCANS)) {
+        if (ga && fused_a && (flags & LAPLEX_SAVE_SCANS)) {
             D.row_out = ga; D.row_u = gy; D.ld_row = ldgy; D.row_v = P.z; D.rows = k;
             if (S.nprob == 0) S.reuse_plan = 1;      // the saved scans alone: no plan is looked at
         }
         if (S.nprob > 0 || D.row_out) LAPLEX_HIP(launch_small(S, 1, st, &D));
-        if (ga && !fused) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
-        if (gb && !fused) LAPLEX_HIP(launch_rowdot(x, ldx, zg, batch, n, batch, gb, st));
+        if (ga && !fused_a) LAPLEX_HIP(launch_rowdot(gy, ldgy, P.z, batch, k, batch, ga, st));
+        if (gb && !fused_b) LAPLEX_HIP(launch_rowdot(x, ldx, zg, batch, n, batch, gb, st));
         if (gtau) LAPLEX_HIP(launch_tau_grad(a, ga, k, b, gb, n, reinterpret_cast<float*>(w + L.off_scratch), gtau, st));
         if (tau != 1.0f) LAPLEX_HIP(launch_scale(ga, k, gb, n, tau, st));
         return LAPLEX_OK;
@@ -952,7 +954,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
     if (use_small(L)) {            // the two-launch path for small problems, then one row reduction
         SmallArgs S = small_args(a, n, nullptr, 0, tau, P, L, flags);
         // the row reduction where the products are formed, once the strict scans of x are there
-        const bool fused = ga && small_pairwise(n, n, batch, 1) == 1;
+        const bool fused = ga && small_pairwise(n, n, batch, 1, true) == 1;
         SmallDots D{};
         float* zg = reinterpret_cast<float*>(w + L.off_small);
         if (ga && !(flags & LAPLEX_SAVE_SCANS)) {

@@ -517,10 +517,10 @@ struct SmallArgs {
     int64_t batch; int cols;                   // cols: set by the launcher, power of two <= 16
     int nprob; SmallProblem prob[2];
 };
-// Whether launch_small forms the products pair by pair from the anchors, beside the sort instead of after it (0: no), and in how many slabs
-// of columns; k, n: outputs and inputs (Gram form: n twice).
-int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators);
-// Row reductions in the launch that forms the products pair by pair, where it does and in one slab of columns (small_pairwise = 1):
+// Whether launch_small forms products pair by pair from the anchors, beside the sort instead of after it (0: no), and in how many slabs of columns;
+// k, n: outputs and inputs (Gram form: n twice); transposed: the product with the transposed matrix (results at the inputs), and the Gram form's.
+int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators, bool transposed);
+// Row reductions in the launch that forms the products pair by pair, for problems where it does and in one slab of columns (small_pairwise = 1):
 //   out[r] = sum_t w[r * ld_w + t] Z[r][t] (+ u[r * ld_u + t] v[r * batch + t]), Z the problem's strict sums (out null: none);
 //   row_out[r] = sum_t row_u[r * ld_row + t] row_v[r * batch + t], r < rows, beside the problems.
 struct SmallDot { float* out; const float* w; int64_t ld_w; const float* u; int64_t ld_u; const float* v; };

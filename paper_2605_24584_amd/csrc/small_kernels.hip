@@ -240,6 +240,7 @@ __device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProbl
         auto fetch = [&](int base) {
 #pragma unroll
             for (int i = 0; i < LOADS; ++i) {
+                if (base + i * THREADS / C >= m) break;          // uniform
                 const int q = i * THREADS + tid, j = base + q / C, c = q % C;
                 next[i] = j < m && col0 + c < A.batch ? inj[(int64_t)j * P.ld_inj + c] : 0.0f;
             }
@@ -253,6 +254,7 @@ __device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProbl
         for (int base = 0; base < m; base += kPairStage) {
 #pragma unroll
             for (int i = 0; i < LOADS; ++i) {
+                if (base + i * THREADS / C >= m) break;
                 const int q = i * THREADS + tid, j = q / C, c = q % C;
                 L.stage.v[c / W][j][c % W] = next[i];
             }
@@ -271,8 +273,10 @@ __device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProbl
             __syncthreads();
         }
     }
+    // (a wavefront that held no injected row has nothing to add up)
+    const int splits = m >= kPairSplits * 64 ? kPairSplits : (m + 63) / 64;
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
+    for (int r = 0; r < ROWS && split < splits; ++r) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
             const double ps = wave_sum<LATE>(p[r][c]), zs = STRICT ? wave_sum<LATE>(z[r][c]) : 0.0;
@@ -286,8 +290,7 @@ __device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProbl
     const int64_t col = col0 + c;
     const bool ok = rr < res && col < A.batch;
     double ps = 0.0, zs = 0.0;
-#pragma unroll
-    for (int q = 0; q < kPairSplits; ++q) { ps += L.part[q][row][c][0]; zs += L.part[q][row][c][1]; }
+    for (int q = 0; q < splits; ++q) { ps += L.part[q][row][c][0]; zs += L.part[q][row][c][1]; }
     const float pv = (float)ps, zv = (float)zs;
     if (ok && P.out_p) (P.out_p + op * P.op_p)[(int64_t)rr * P.ld_p + col] = pv;
     if (STRICT && ok && P.out_z) (P.out_z + op * P.op_z)[(int64_t)rr * A.batch + col] = zv;
@@ -561,57 +564,108 @@ bool small_reads_too_much(int64_t N, int64_t batch)
 
 static int pair_columns(int64_t batch) { return batch >= 5 ? 8 : batch >= 3 ? 4 : (int)batch; }
 
-// Where forming every pair's exponential is faster than ranking first and scanning then.  The line is the same whatever a call wants and whether its
-// plan is kept, since the form shows in the last bits; it lies where a product on a kept plan, which saves no launch, is no slower.
-// Measured (us, pair by pair / ranks, then scans; forward, forward on a kept plan, forward + backward): n = k = 4096, batch 1 15.4 / 24.2, 10.0 / 11.2, 30.2 /
-// 41.9; 1024 9.7 / 16.8, 9.6 / 9.6, 19.9 / 31.6; 2048, batch 4 11.0 / 18.7, 9.9 / 9.6, 23.3 / 34.8; 1500, batch 8 11.4 / 17.7, 9.8 / 9.7, 25.7 / 33.5;
-// 64 x 64, batch 8 9.6 / 13.2, 10.0 / 9.7, 20.4 / 29.7; 8 operators of 300 x 1000 14.3 / 22.1, 13.5 / 13.4, 43.4 / 48.6 (9.6: what a launch alone takes from here).
-// Beyond the lines: Gram form of 6000, batch 1 21.1 / 21.7, 16.4 / 10.4, 49.4 / 38.0; 4096 x 4096, batch 2 15.4 / 24.0, 11.7 / 11.1, 37.5 / 42.3; 700 x 4096,
-// batch 8 11.8 / 20.1, 11.7 / 10.1, 28.7 / 37.0; 300 x 300, batch 256 16.6 / 15.5, 13.6 / 9.9, 60.7 / 32.2.
-constexpr double kPairCost = 2.4e8, kPairCostWide = 9e7, kPairCostSlabs = 4e7;      // cycles of a lane, about
-constexpr int64_t kPairRowsWide = 3072;
-int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators)
+// Where forming every pair's exponential is faster than ranking first and scanning then, in a forward product.  The line is the same whatever a call wants of
+// it and whether its plan is kept, since the form shows in the last bits; it lies where a product on a kept plan, which saves no launch, takes no
+// longer.  What is counted:
+//   pairs       about the cycles of a lane (PairLimits::cost)
+//   workgroups  One of up to 8 (16) result rows takes its 3 to 5 us of launch, loads, barriers and sums over lanes however few injected rows there are.
+//               A compute unit holds one of 1024 threads at a time (8 columns with strict sums, 85 registers) or two: more than 256 in one launch queue up.
+//   stages      of injected rows of several columns: each waits for its loads
+//   ranks       of many operators, which share the compute units with the pairs
+// A backward pass has its plan: its transposed product is formed pair by pair only where the forward product, of the opposite shape, is as well and
+// has saved the time; the Gram form's, which goes with its forward, like the transposed one (beside scans in the forward, 1089 x 9, batch 9, forward + backward 31.2 / 33.6 us; 794 x 2405, batch 8 33.6 / 40.3).
+// Measured (us, ranks, then scans / pair by pair; forward, forward on a kept plan, forward + backward): n = k = 4096, batch 1 24.2 / 14.6, 11.2 / 9.9, 41.9 / 29.8; 1986 x 121, batch 1
+// 17.5 / 10.4, 10.1 / 10.1, 32.0 / 21.2; 2981 x 1035, batch 3 18.9 / 11.6, 10.2 / 10.2, 34.5 / 27.2; Gram form of 1348, batch 4 17.0 / 10.2, 9.6 / 9.7, 29.8 / 21.0, of 1645, batch 8
+// 17.4 / 11.8, 9.8 / 10.1, 30.5 / 29.0; 640 x 1979, batch 8 17.4 / 10.2, 10.0 / 10.1, 32.9 / 24.0; 575 x 648, batch 9 16.1 / 10.2, 10.2 / 10.2, 31.0 / 27.7; 118 x 118, batch 128 (240
+// workgroups), Gram form 13.5 / 9.8, 9.6 / 9.7, 26.9 / 24.0; sixteen operators of 100 x 39, batch 1 19.7 / 14.1, 13.5 / 13.8, 45.6 / 43.8; six of 143 x 87, batch 9 18.1 / 14.3, 13.7 / 13.9,
+// 46.4 / 44.6; forward alone: 10 x 3000, batch 64 (8 workgroups, 3000 x 10 would have 3000) 18.5 / 11.6, 2248 x 190, batch 5 17.9 / 11.0.
+// Beyond: Gram form of 2115, batch 4 17.5 / 12.2, 9.8 / 11.1, 31.3 / 36.6; 490 x 3539, batch 5 18.6 / 12.5, 10.0 / 12.3; 3765 x 36, batch 8 (471 workgroups) 17.8 / 13.9, 9.3 / 9.3, keeping its scans
+// 19.6 / 21.4; 243 x 243, batch 100 (403), Gram form 14.2 / 10.0, 9.8 / 9.9, 26.4 / 34.3; 3000 x 10, batch 256 (12000) 22.3 / 138, 13.3 / 134, 49.7 / 336; two operators of 2453 x 1295,
+// batch 1 21.4 / 18.4, 13.5 / 13.8, keeping scans 23.2 / 24.9; twelve of 15 x 1640, batch 9 21.6 / 22.0, 14.0 / 14.4, 21.7 / 24.6; sixteen of 100 x 900, batch 8 23.3 / 24.0, 14.3 / 15.9, 53.8 / 101.
+struct PairLimits { double cost, cost_operators; int64_t injected, workgroups; };
+constexpr PairLimits kPairLimits[4] = {      // one slab of 1, 2, 4, 8 columns
+    {2.4e8, 1.2e8, kSmallMax, kSmallMax}, {9e7, 5e7, 3 * kPairStage, 416}, {6.5e7, 5e7, 3 * kPairStage, 416}, {8e7, 3e7, 2 * kPairStage, 352}};
+constexpr PairLimits kPairLimitsSlabs = {7e7, 2.5e7, 2 * kPairStage, 352};
+constexpr int64_t kPairAtOnce = 256;                    // workgroups of 8 columns
+constexpr double kPairCostQueued = 1.5e7;               // ... and what more of them may cost
+constexpr double kPairCostSlabsBackward = 2.5e7;
+constexpr int64_t kPairWorkgroupsOperators = 300, kPairRankedOperators = 12000;
+static double pair_cost(int64_t k, int64_t n, int cols, int64_t slabs, int64_t operators)
+{
+    return (double)k * (double)n * (double)(slabs * operators) * (12.0 + 2.0 * cols);
+}
+static int64_t pair_workgroups(int64_t results, int cols, int64_t slabs, int64_t operators)
+{
+    const int rows = kPairGroups * (cols <= 2 ? kPairRows<1> : kPairRows<8>);
+    return (results + rows - 1) / rows * slabs * operators;
+}
+static bool pairs_pay(int64_t results, int64_t injected, int cols, int64_t slabs, int64_t operators)
+{
+    const PairLimits& M = slabs > 1 ? kPairLimitsSlabs : kPairLimits[cols == 1 ? 0 : cols == 2 ? 1 : cols == 4 ? 2 : 3];
+    const double cost = pair_cost(results, injected, cols, slabs, operators);
+    const int64_t workgroups = pair_workgroups(results, cols, slabs, operators);
+    if (injected > M.injected || workgroups > M.workgroups || cost > M.cost) return false;
+    if (cols == 8 && workgroups > kPairAtOnce && cost > kPairCostQueued) return false;
+    return operators == 1 || ((cols == 8 || workgroups <= kPairWorkgroupsOperators) && operators * (results + injected) <= kPairRankedOperators && cost <= M.cost_operators);
+}
+int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators, bool transposed)
 {
     const int cols = pair_columns(batch);
     const int64_t slabs = (batch + cols - 1) / cols;
-    if (cols > 1 && (k > kPairRowsWide || n > kPairRowsWide)) return 0;
-    const double cost = (double)k * (double)n * (double)(slabs * operators) * (12.0 + 2.0 * cols);
-    return cost <= (slabs > 1 ? kPairCostSlabs : cols > 1 ? kPairCostWide : kPairCost) ? (int)slabs : 0;
+    if (!pairs_pay(k, n, cols, slabs, operators)) return 0;
+    if (transposed) {
+        if (!pairs_pay(n, k, cols, slabs, operators)) return 0;
+        if (cols == 8 && pair_workgroups(k > n ? k : n, cols, slabs, operators) > kPairAtOnce) return 0;
+        if (slabs > 1 && pair_cost(k, n, cols, slabs, operators) > kPairCostSlabsBackward) return 0;
+    }
+    return (int)slabs;
 }
 
-hipError_t launch_small(const SmallArgs& A0, int64_t operators, hipStream_t st, const SmallDots* dots)
+hipError_t launch_small(const SmallArgs& all, int64_t operators, hipStream_t st, const SmallDots* dots)
 {
-    SmallArgs A = A0;
+    SmallArgs pairs = all, A = all;           // the problems formed pair by pair; those that are scanned
+    SmallDots D = dots ? *dots : SmallDots{};
+    pairs.nprob = A.nprob = 0;
+    int pair_slabs = 1;
+    for (int i = 0; i < all.nprob; ++i) {
+        const SmallProblem& p = all.prob[i];
+        const int slabs = small_pairwise(all.k, all.n ? all.n : all.k, all.batch, operators, p.res_lo > 0 || all.n == 0);
+        if (slabs) {
+            pair_slabs = slabs;
+            D.prob[pairs.nprob] = dots ? dots->prob[i] : SmallDot{};
+            pairs.prob[pairs.nprob++] = p;
+        } else {
+            A.prob[A.nprob++] = p;
+        }
+    }
     const int64_t N = A.k + A.n;
     int queries = 32;          // of the ranks, per workgroup (more per workgroup measured slower until the grid gets very large)
     while (queries < kRankQueriesMax && ((N + queries - 1) / queries) * operators > 8192) queries <<= 1;
-    const bool rows_only = A.nprob == 0 && dots && dots->row_out;
-    const int pair_slabs = A.nprob > 0 || rows_only ? small_pairwise(A.k, A.n ? A.n : A.k, A.batch, operators) : 0;
-    if (pair_slabs) {
-        const SmallDots D = dots ? *dots : SmallDots{};
-        const int cols = pair_columns(A.batch);
-        bool strict = A.nprob == 0;       // (row products alone: either form)
-        const int groups = A.reuse_plan && cols == 1 ? kPairKeptGroups<1> : kPairGroups, threads = groups * kPairSplits * 64;
+    if (pairs.nprob > 0 || D.row_out) {
+        const int cols = pair_columns(pairs.batch);
+        bool strict = pairs.nprob == 0;       // (row products alone: either form)
+        const int groups = pairs.reuse_plan && cols == 1 ? kPairKeptGroups<1> : kPairGroups, threads = groups * kPairSplits * 64;
         int blocks[2] = {0, 0};
-        for (int i = 0; i < A.nprob; ++i) {
-            strict = strict || A.prob[i].out_z != nullptr || D.prob[i].out != nullptr;
+        for (int i = 0; i < pairs.nprob; ++i) {
+            strict = strict || pairs.prob[i].out_z != nullptr || D.prob[i].out != nullptr;
             const int rows = groups * (cols <= 2 ? kPairRows<1> : kPairRows<8>);
-            blocks[i] = (int)((A.prob[i].res_hi - A.prob[i].res_lo + rows - 1) / rows) * pair_slabs;
+            blocks[i] = (int)((pairs.prob[i].res_hi - pairs.prob[i].res_lo + rows - 1) / rows) * pair_slabs;
         }
-        const int rank_blocks = A.reuse_plan ? 0 : (int)((N + queries - 1) / queries);
+        const int rank_blocks = pairs.reuse_plan ? 0 : (int)((N + queries - 1) / queries);
         const int row_blocks = D.row_out ? (int)((D.rows * cols + threads - 1) / threads) : 0;
         const dim3 grid((unsigned)(blocks[0] + blocks[1] + rank_blocks + row_blocks), (unsigned)operators);
-        auto go = [&](auto kernel) { LAPLEX_TIMED("small_pairs", st, hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, A, D, pair_slabs, blocks[0], blocks[1], rank_blocks, queries)); };
+        auto go = [&](auto kernel) { LAPLEX_TIMED("small_pairs", st, hipLaunchKernelGGL(kernel, grid, dim3((unsigned)threads), 0, st, pairs, D, pair_slabs, blocks[0], blocks[1], rank_blocks, queries)); };
         auto with = [&](auto columns) {
             constexpr int C = decltype(columns)::value;
-            if (A.reuse_plan) { if (strict) go(k_small_pairs<C, true, kPairKeptGroups<C>>); else go(k_small_pairs<C, false, kPairKeptGroups<C>>); }
+            if (pairs.reuse_plan) { if (strict) go(k_small_pairs<C, true, kPairKeptGroups<C>>); else go(k_small_pairs<C, false, kPairKeptGroups<C>>); }
             else { if (strict) go(k_small_pairs<C, true, kPairGroups>); else go(k_small_pairs<C, false, kPairGroups>); }
         };
         if (cols == 1) with(std::integral_constant<int, 1>{});
         else if (cols == 2) with(std::integral_constant<int, 2>{});
         else if (cols == 4) with(std::integral_constant<int, 4>{});
         else with(std::integral_constant<int, 8>{});
-        return hipGetLastError();
+        if (A.nprob == 0) return hipGetLastError();
+        A.reuse_plan = 1;                     // (ranked there, or kept)
     }
     if (!A.reuse_plan) {
         LAPLEX_TIMED("small_sort", st, hipLaunchKernelGGL(k_small_rank, dim3((unsigned)((N + queries - 1) / queries), (unsigned)operators),

@@ -919,3 +919,63 @@ def test_small_problems_of_two_clusters_far_apart(oracle, k, n, batch):
     for name, got, rv, tv in zip(("y", "gx", "ga", "gb"), (y, gx, ga, gb), ref, bar):
         worst = float((np.abs(got.cpu().numpy().astype(np.float64) - rv) / tv).max())
         assert worst <= 1.0, f"{name}: {worst:.3g} times the bar"
+
+
+@pytest.mark.parametrize("k,n,batch,forward,backward", [
+    (4096, 4096, 1, True, True), (3000, 10, 1, True, True), (10, 3000, 1, True, True),
+    (3072, 900, 4, True, True), (900, 3073, 4, False, False), (16, 3000, 2, True, True), (1700, 1500, 8, True, True),
+    (2048, 100, 8, True, True), (100, 2048, 8, True, True), (2049, 100, 8, True, False), (100, 2049, 8, False, False),     # 256 workgroups; two stages
+    (3000, 10, 8, False, False), (500, 13, 32, True, True), (700, 13, 32, True, False), (900, 13, 32, False, False),       # several slabs: 252, 352, 452 workgroups
+    (10, 2000, 32, True, False), (3000, 10, 256, False, False), (10, 3000, 256, False, False), (575, 648, 9, True, True), (640, 1979, 9, False, False),
+])
+def test_which_small_problems_go_pair_by_pair(oracle, k, n, batch, forward, backward):
+    """Problems of many result rows and hardly any injected ones, whose workgroups queue up however few the pairs are, stay with the scans (3000 x 10, batch 256, forward and
+    backward: 49.7 us, 336 pair by pair); what either product is formed by shows in the launches.  The sums where the two go different ways."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + 5 * n + batch)
+    a, b = anchors("ties", r, k, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    want, tols = oracle.apply_backward_scan(a, b, x, g)
+    da, db, dx, dg = dev(a), dev(b), dev(x), dev(g)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    y, gx, ga, gb = torch.empty_like(dg), torch.empty_like(dx), torch.empty_like(da), torch.empty_like(db)
+    seen = families(lambda: B.laplex_apply(da, db, dx, y, ws, B.LAPLEX_SAVE_SCANS))
+    assert seen == ({"small_pairs": 1} if forward else {"small_sort": 1, "small": 1})
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    seen = families(lambda: B.laplex_apply_backward(da, db, dx, dg, gx, None, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN))
+    assert ("small_pairs" in seen, "small" in seen) == (backward, not backward)
+    first = None
+    for flags in (B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN, B.LAPLEX_REUSE_PLAN, 0):
+        for v in (gx, ga, gb): v.fill_(float("nan"))
+        B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, flags)
+        torch.cuda.synchronize()
+        got = [v.cpu().numpy() for v in (gx, ga, gb)]
+        if first is None: first = got
+        for name, v, rv, tv, f in zip(("gx", "ga", "gb"), got, want, tols, first):
+            assert_close(name, v, rv, tv)
+            assert np.array_equal(v, f), name
+
+
+@pytest.mark.parametrize("r,k,n,batch,forward,backward", [
+    (16, 100, 39, 1, True, True), (2, 2300, 582, 1, True, True), (8, 632, 944, 1, False, False), (12, 15, 1640, 9, False, False), (6, 143, 87, 9, True, True),
+    (16, 100, 900, 8, False, False), (16, 10, 600, 32, True, False), (4, 7, 300, 9, True, False), (16, 10, 1100, 8, False, False),
+])
+def test_which_small_sums_go_pair_by_pair(oracle, r, k, n, batch, forward, backward):
+    """The same for sums of operators; those sorted by samples in a launch of their own (more than 17000 anchors) are never among them."""
+    from test_gpu_parity import assert_close
+    q = np.random.default_rng(r + k + n)
+    a, b = (np.round(q.uniform(0, (k + n) / 64, (r, s)) * 8).astype(np.float32) / 8 for s in (k, n))
+    x, g, w = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=(k, batch)).astype(np.float32), q.normal(size=r).astype(np.float32)
+    da, db, dw, dx, dg = dev(a), dev(b), dev(w), dev(x), dev(g)
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    y, gx, ga, gb, gw = torch.empty_like(dg), torch.empty_like(dx), torch.empty_like(da), torch.empty_like(db), torch.empty_like(dw)
+    seen = families(lambda: B.laplex_mix_apply(da, db, dw, dx, y, ws, B.LAPLEX_SAVE_SCANS))
+    assert ("small_pairs" in seen, "small" in seen) == (forward, not forward), seen
+    seen = families(lambda: B.laplex_mix_apply_backward(da, db, dw, dx, dg, gx, ga, gb, gw, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN))
+    assert ("small_pairs" in seen, "small" in seen) == (backward, not backward), seen
+    ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
+    for name, v, rv, tv in zip(("gx", "ga", "gb", "gw"), (gx, ga, gb, gw), want, tols):
+        assert_close(name, v.cpu().numpy(), rv, tv)
