@@ -578,7 +578,7 @@ static int pair_columns(int64_t batch) { return batch >= 5 ? 8 : batch >= 3 ? 4 
 // 17.5 / 10.4, 10.1 / 10.1, 32.0 / 21.2; 2981 x 1035, batch 3 18.9 / 11.6, 10.2 / 10.2, 34.5 / 27.2; Gram form of 1348, batch 4 17.0 / 10.2, 9.6 / 9.7, 29.8 / 21.0, of 1645, batch 8
 // 17.4 / 11.8, 9.8 / 10.1, 30.5 / 29.0; 640 x 1979, batch 8 17.4 / 10.2, 10.0 / 10.1, 32.9 / 24.0; 575 x 648, batch 9 16.1 / 10.2, 10.2 / 10.2, 31.0 / 27.7; 118 x 118, batch 128 (240
 // workgroups), Gram form 13.5 / 9.8, 9.6 / 9.7, 26.9 / 24.0; sixteen operators of 100 x 39, batch 1 19.7 / 14.1, 13.5 / 13.8, 45.6 / 43.8; six of 143 x 87, batch 9 18.1 / 14.3, 13.7 / 13.9,
-// 46.4 / 44.6; forward alone: 10 x 3000, batch 64 (8 workgroups, 3000 x 10 would have 3000) 18.5 / 11.6, 2248 x 190, batch 5 17.9 / 11.0.
+// 46.4 / 44.6; forward alone: 2 x 1969, batch 31 (4 workgroups; its transpose has 988) 17.0 / 9.4, 2248 x 190, batch 5 17.9 / 11.0.
 // Beyond: Gram form of 2115, batch 4 17.5 / 12.2, 9.8 / 11.1, 31.3 / 36.6; 490 x 3539, batch 5 18.6 / 12.5, 10.0 / 12.3; 3765 x 36, batch 8 (471 workgroups) 17.8 / 13.9, 9.3 / 9.3, keeping its scans
 // 19.6 / 21.4; 243 x 243, batch 100 (403), Gram form 14.2 / 10.0, 9.8 / 9.9, 26.4 / 34.3; 3000 x 10, batch 256 (12000) 22.3 / 138, 13.3 / 134, 49.7 / 336; two operators of 2453 x 1295,
 // batch 1 21.4 / 18.4, 13.5 / 13.8, keeping scans 23.2 / 24.9; twelve of 15 x 1640, batch 9 21.6 / 22.0, 14.0 / 14.4, 21.7 / 24.6; sixteen of 100 x 900, batch 8 23.3 / 24.0, 14.3 / 15.9, 53.8 / 101.
