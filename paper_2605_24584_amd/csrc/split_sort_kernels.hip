@@ -427,12 +427,13 @@ SplitGeom split_geom(int64_t N, bool many = false)      // many: several operato
     while (G.group_bits < 6 && (G.tile >> G.group_bits) > 2 * G.buckets) ++G.group_bits;      // (four times as many pairs as lanes: twice the average run)
     return G;
 }
+size_t split_words(const SplitGeom& G) { return (size_t)(2 * G.buckets + 4 * (G.buckets + 1) + G.samples + (G.tiles * (G.buckets + 1) + 1) / 2); }
 }  // namespace
 
-size_t split_sort_words(int64_t N)          // (for one operator or many: those take fewer stretches and as many samples)
+size_t split_sort_words(int64_t N)          // (for one operator or for each of many, whichever takes more: from 2^16 to 2^17 positions many take twice the samples)
 {
-    const SplitGeom G = split_geom(N);
-    return (size_t)(2 * G.buckets + 4 * (G.buckets + 1) + G.samples + (G.tiles * (G.buckets + 1) + 1) / 2);
+    const size_t one = split_words(split_geom(N)), many = split_words(split_geom(N, true));
+    return one > many ? one : many;
 }
 
 hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, uint2* pair0, uint2* pair1, uint32_t* scratch,
@@ -440,6 +441,7 @@ hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t 
                              int64_t operators, int64_t op_a, int64_t op_b, int64_t op_ws, hipStream_t st)
 {
     const SplitGeom G = split_geom(k + n, operators > 1);
+    if (split_words(G) > split_sort_words(k + n)) return hipErrorInvalidValue;      // (what `scratch` holds)
     SplitArgs A{};
     A.a = a; A.b = b; A.k = k; A.tau = tau; A.N = (int)(k + n);
     A.pairs = pair0; A.spare = pair1;

@@ -979,3 +979,21 @@ def test_which_small_sums_go_pair_by_pair(oracle, r, k, n, batch, forward, backw
     want, tols = oracle.mix_backward(a, b, w, x, g, brute=False)
     for name, v, rv, tv in zip(("gx", "ga", "gb", "gw"), (gx, ga, gb, gw), want, tols):
         assert_close(name, v.cpu().numpy(), rv, tv)
+
+
+@pytest.mark.parametrize("r,k,n,batch", [(2, 40000, 25536, 2), (2, 40000, 25537, 2), (3, 31072, 100000, 1)])
+def test_mix_sorted_by_samples_up_to_2_to_17(oracle, r, k, n, batch):
+    """Sums whose operators have 2^16 to 2^17 anchors: each is sorted with twice as many samples as such a problem by itself, in scratch that has to be sized for them."""
+    from test_gpu_parity import assert_close, gpu_perm
+    q = np.random.default_rng(k + n)
+    a, b = (np.round(q.uniform(0, (k + n) / 64, (r, s)) * 8).astype(np.float32) / 8 for s in (k, n))
+    x, w = q.normal(size=(n, batch)).astype(np.float32), q.normal(size=r).astype(np.float32)
+    ws = torch.empty(B.laplex_mix_workspace_bytes(r, k, n, batch), dtype=torch.uint8, device="cuda")
+    y = torch.empty(k, batch, device="cuda")
+    B.laplex_mix_apply(dev(a), dev(b), dev(w), dev(x), y, ws, 0)
+    torch.cuda.synchronize()
+    ref, tol = oracle.mix_apply(a, b, w, x, brute=False)
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    one = (B.laplex_workspace_bytes(k, n, batch) + 255) // 256 * 256
+    for p in range(r):
+        assert np.array_equal(gpu_perm(ws[p * one:], k + n), oracle.merged_permutation(a[p], b[p])), p
