@@ -84,8 +84,7 @@ enum {
 
 enum {
     /* The caller promises a / b ascending.  With both set (or A_SORTED for the
-     * Gram form) the sort is replaced by one merge-path pass (not with one column
-     * from 2^22 merged positions on, where x follows the sort's passes).  A wrong
+     * Gram form) the sort is replaced by one merge-path pass.  A wrong
      * promise gives wrong values, never a fault. */
     LAPLEX_A_SORTED = 1u,
     LAPLEX_B_SORTED = 2u,

@@ -17,7 +17,7 @@ extern "C" {
  * every launch of the named kernel family ("split_sample", "split_pick", "split_tiles",
  * "split_sort", "deep_sample", "deep_bounds", "deep_tiles", "deep_columns", "deep_pieces", "deep_units", "deep_sort", "deep_edges",
  * "sort_hist", "radix_scatter", "merge", "decay", "small_sort", "small", "small_pairs", "rowdot", "sum_slabs", "fill", and "scan_meta.T",
- * "scan_reduce.T", "scan_spine.T", "scan_down.T", "scan_down_sparse.T", "move_tiles.T", "move_pieces.T", "move_units.T" (one column: values into
+ * "scan_reduce.T", "scan_spine.T", "scan_down.T", "scan_down_sparse.T", "move_tiles.T", "move_pieces.T", "move_units.T", "move_in_order.T" (one column: values into
  * sorted order), "permute_part.T", "permute_final.T" (results home) with T = "fwd" for the
  * forward scans of x, "bwd" for the backward scans of gy, "rescan" for the
  * backward's repeat of the forward scans when they were not saved) is bracketed by a pair of HIP

@@ -166,12 +166,15 @@ DeepPlan deep_plan(const Layout& L, char* ws)
 }
 
 // dst[sorted position of first_id + i] = src[i * ld] for i < count, zero at every other sorted position: rows of the caller's matrix
-// (the inputs: first_id = k; the outputs: first_id = 0) into sorted order.
-int rows_to_sorted(const Layout& L, char* ws, const float* src, int64_t ld, int64_t first_id, int64_t count, float* dst,
+// (the inputs: first_id = k; the outputs: first_id = 0) into sorted order.  ascending: the caller promises anchors that arrive in order, so that the ids
+// of either side ascend and rows are fetched one after the other, where the plan's tables of moves are neither needed nor there.
+int rows_to_sorted(const Layout& L, char* ws, const float* src, int64_t ld, int64_t first_id, int64_t count, bool ascending, float* dst,
                    const char* tag, hipStream_t st)
 {
-    LAPLEX_HIP(launch_deep_move(L.deep, deep_plan(L, ws), src, ld, first_id, first_id + count, reinterpret_cast<float*>(ws + L.off_by_tile),
-                                reinterpret_cast<float*>(ws + L.off_by_piece), dst, tag, st));
+    const uint32_t* ids = plan_of(L, ws).ids;
+    if (ascending) LAPLEX_HIP(launch_move_in_order(L.N, ids, src, ld, first_id, first_id + count, dst, tag, st));
+    else LAPLEX_HIP(launch_deep_move(L.deep, deep_plan(L, ws), ids, src, ld, first_id, first_id + count, reinterpret_cast<float*>(ws + L.off_by_tile),
+                                     reinterpret_cast<float*>(ws + L.off_by_piece), dst, tag, st));
     return LAPLEX_OK;
 }
 
@@ -232,11 +235,11 @@ int build_plan(const float* a, int64_t k, const float* b, int64_t n, float tau, 
     if (L.N <= kSmallMax) {      // (the promises of sorted anchors are not needed here)
         LAPLEX_HIP(launch_small(small_args(a, k, b, n, tau, P, L, flags), 1, st));      // no scan problem: the sort alone
         LAPLEX_HIP(launch_decay(nullptr, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
-    } else if (use_permute(L)) {      // (anchors that arrive sorted as well: values move along the way of this sort)
-        LAPLEX_HIP(launch_deep_sort(a, k, b, n, tau, L.deep, deep_plan(L, ws), ws + L.off_deep, P.ids, P.dh, P.pk, P.pk8, counters, st));
     } else if (both_sorted) {
         LAPLEX_HIP(launch_merge(a, k, b, n, tau, keys0, P.ids, st));
-        LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st));
+        LAPLEX_HIP(launch_decay(keys0, nullptr, P.dh, P.pk, P.pk8, counters, L.N, st, use_permute(L) ? deep_plan(L, ws).unit_count : nullptr));
+    } else if (use_permute(L)) {
+        LAPLEX_HIP(launch_deep_sort(a, k, b, n, tau, L.deep, deep_plan(L, ws), ws + L.off_deep, P.ids, P.dh, P.pk, P.pk8, counters, st));
     } else if (L.N <= kSplitSortMax) {
         LAPLEX_HIP(launch_split_sort(a, k, b, n, tau, pair0, pair1, reinterpret_cast<uint32_t*>(ws + L.off_status),
                                      P.ids, P.dh, P.pk, P.pk8, counters, 1, 0, 0, 0, st));
@@ -731,7 +734,7 @@ static int apply_impl(const float* a, int64_t k, const float* b, int64_t n,
     p.tag = "fwd";
     p.phase_in = pin;             // phased: x is modulated on the way into the reduce (see phase_fusable)
     if (use_permute(L)) {          // x into sorted order, the scans there, y (and the saved scans) home
-        LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, p.stage, "fwd", st));
+        LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, sorted, p.stage, "fwd", st));
         const bool save = p.out_z != nullptr;
         p.out_p = nullptr; p.out_z = nullptr;
         return scan_and_send_home(p, L, w, true, save, y, ldy, save ? P.z : nullptr, 1, st);
@@ -821,7 +824,7 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
             p.tag = "rescan";
             p.phase_in = pin_fwd;
             if (routed) {
-                LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, P.xs, "rescan", st));
+                LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, sorted, P.xs, "rescan", st));
                 p.out_z = nullptr;
                 LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, P.z, 1, nullptr, 1, st));
             } else {
@@ -835,8 +838,8 @@ static int apply_backward_impl(const float* a, int64_t k, const float* b, int64_
     // sorted-order x is in the saved region if the forward kept it or the re-scan above just wrote it
     const bool have_xs = (flags & LAPLEX_SAVE_SCANS) || ga;
     if (routed && (gx || gb)) {
-        if (gb && !have_xs) LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, P.xs, "bwd_x", st));    // the weights of gb
-        LAPLEX_CHECK(rows_to_sorted(L, w, gy, ldgy, 0, k, P.stage, "bwd", st));
+        if (gb && !have_xs) LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, k, n, sorted, P.xs, "bwd_x", st));    // the weights of gb
+        LAPLEX_CHECK(rows_to_sorted(L, w, gy, ldgy, 0, k, sorted, P.stage, "bwd", st));
         ScanProblem p = problem(P, L);
         p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)k;
         p.res_lo = (uint32_t)k; p.res_hi = (uint32_t)(k + n);
@@ -914,7 +917,7 @@ static int gram_impl(const float* a, int64_t n, const float* x, int64_t ldx, int
     if (p.out_z && gram_scans_together(L)) { p.out_z = nullptr; p.carries = P.z; }
     if (use_permute(L)) {          // batch 1, many rows: x into sorted order, the scans there, y (and the saved scans) home
         const bool save = (flags & LAPLEX_SAVE_SCANS) != 0;
-        LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, 0, n, p.stage, "fwd", st));
+        LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, 0, n, (flags & LAPLEX_A_SORTED) != 0, p.stage, "fwd", st));
         p.out_p = nullptr; p.out_z = nullptr; p.ld_p = 0; p.ld_z = 0;
         return scan_and_send_home(p, L, w, true, save, y, ldy, save ? P.z : nullptr, 1, st);
     }
@@ -990,7 +993,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
         p.stage = P.xs;
         p.tag = "rescan";
         if (routed) {
-            LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, 0, n, P.xs, "rescan", st));
+            LAPLEX_CHECK(rows_to_sorted(L, w, x, ldx, 0, n, (flags & LAPLEX_A_SORTED) != 0, P.xs, "rescan", st));
             p.out_z = nullptr;
             LAPLEX_CHECK(scan_and_send_home(p, L, w, false, true, P.z, 1, nullptr, 1, st));
         } else {
@@ -1001,7 +1004,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
     if (routed && (gx || ga)) {
         // gx and x * Z^g leave the downsweep together (the second as the row's second output, into ga); the saved scans of x
         // are in the caller's order already, so  ga = x Z^g + gy Z^x  is completed by one pointwise pass
-        LAPLEX_CHECK(rows_to_sorted(L, w, gy, ldgy, 0, n, P.stage, "bwd", st));
+        LAPLEX_CHECK(rows_to_sorted(L, w, gy, ldgy, 0, n, (flags & LAPLEX_A_SORTED) != 0, P.stage, "bwd", st));
         ScanProblem p = problem(P, L);
         p.inj = gy; p.ld_inj = ldgy; p.inj_lo = 0; p.inj_hi = (uint32_t)n;
         p.res_lo = 0; p.res_hi = (uint32_t)n;

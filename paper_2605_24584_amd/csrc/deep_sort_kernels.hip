@@ -29,7 +29,7 @@
 // Measured (MI355X, us, before / now; before: four radix passes with chained look-back, histogram, a decay pass, the inverse permutation by
 // partition passes of (id, position), and values in as (rank, value) records): the plan of 2^28 positions 7720 / 4080, a move of 2^27 values into their
 // order 1350 / 1050; forward + backward at 2^27 x 2^27 17115 / 12850, 2^24 x 2^24 with 32 equal anchors a value 2451 / 1841, 2^22 x 2^22 574 /
-// 515, 2^24 x 2^24 in order (merge path before) 2325 / 2045.  The workspace is 26 % smaller.  What was tried and did not pay: units of stretches with three times the
+// 515.  Anchors that are promised to arrive in order are merged, not sorted (move_in_order, below).  The workspace is 26 % smaller.  What was tried and did not pay: units of stretches with three times the
 // pairs (LDS for the longest, a third filled): 5090 us for the sort of 2^28 pairs in place of 1893; 1024 threads of 4 pairs 2254, 256 of 16 2092.
 #include "split_sort.h"
 
@@ -109,8 +109,9 @@ __device__ __forceinline__ bool find_piece(const DeepPlan& P, int buckets, uint3
 {
     if (threadIdx.x == 0) word[0] = 0xFFFFFFFFu;
     __syncthreads();
+    const bool tables = *P.unit_count != kDeepMerged;
     for (int i = threadIdx.x; i < buckets; i += kDeepThreads)
-        if (P.piece_base[i] <= piece && piece < P.piece_base[i + 1]) word[0] = (uint32_t)i;
+        if (tables && P.piece_base[i] <= piece && piece < P.piece_base[i + 1]) word[0] = (uint32_t)i;
     __syncthreads();
     const uint32_t b = word[0];
     __syncthreads();
@@ -420,9 +421,9 @@ struct DeepUnit {
     int b, g0, g1, pieces;
     int64_t base, cnt;
     uint32_t piece0, first;           // first: sorted position of the bucket's first pair
-    __device__ __forceinline__ bool find(const DeepPlan& P)
+    __device__ __forceinline__ bool find(const DeepPlan& P, uint32_t total)
     {
-        const uint32_t total = *P.unit_count, per = (total + 7u) / 8u, u = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+        const uint32_t per = (total + 7u) / 8u, u = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
         if ((blockIdx.x >> 3) >= per || u >= total) return false;
         const uint4 v = P.units[u];
         b = (int)(v.x >> 20); g0 = (int)(v.x >> 10 & 1023u); g1 = (int)(v.x & 1023u) + 1;
@@ -497,7 +498,7 @@ k_deep_sort(const DeepArgs A)
     __shared__ StretchShared<THREADS> S;
     const int tid = threadIdx.x;
     DeepUnit U;
-    if (!U.find(A.P)) return;
+    if (!U.find(A.P, *A.P.unit_count)) return;
     if (tid == 0) S.init();
     const int64_t cnt = U.cnt, base = U.base;
     if (cnt == 0) return;               // uniform
@@ -613,11 +614,32 @@ k_deep_edges(const DeepArgs A)
 // ---------------------------------------------------------------------------------------------------------------------
 struct MoveArgs {
     DeepPlan P;
+    const uint32_t* ids;
     int buckets, per_bucket; int64_t N, tiles;
     const float* src; int64_t ld; int64_t lo, hi;
     int64_t tile0, tile1;            // tiles that hold ids of the range
     float* by_tile; float* by_piece; float* dst;
 };
+
+// Anchors that came in order: the ids of either side ascend along the sorted sequence, and rows are fetched one after the other.  Bound by memory: 4 bytes
+// of id, 4 of result and a value for every row of the side (us, sort and moves along its passes / merge and this: forward 1380000 x 3220000 276 / 116, 2^23 x 2^23
+// 660 / 362, Gram form of 2^23 412 / 172; forward + backward 2516583 x 5872025 557 / 338; radix sort and records of (rank, value): 194, 685, 289; 475).
+__device__ __forceinline__ void move_in_order(int64_t N, const uint32_t* ids, const float* src, int64_t ld, int64_t lo, int64_t hi, float* dst, int64_t quad)
+{
+    auto value = [&](uint32_t id) { return (int64_t)id >= lo && (int64_t)id < hi ? src[((int64_t)id - lo) * ld] : 0.0f; };
+    const int64_t j = 4 * quad;
+    if (j + 4 <= N) {
+        const uint4 v = reinterpret_cast<const uint4*>(ids)[quad];
+        reinterpret_cast<float4*>(dst)[quad] = make_float4(value(v.x), value(v.y), value(v.z), value(v.w));
+    } else {
+        for (int64_t i = j; i < N; ++i) dst[i] = value(ids[i]);
+    }
+}
+__global__ void __launch_bounds__(256)
+k_move_in_order(int64_t N, const uint32_t* __restrict__ ids, const float* __restrict__ src, int64_t ld, int64_t lo, int64_t hi, float* __restrict__ dst)
+{
+    move_in_order(N, ids, src, ld, lo, hi, dst, (int64_t)blockIdx.x * 256 + threadIdx.x);
+}
 
 // A tile's values in its layout.
 __global__ void __launch_bounds__(kDeepThreads, 8)
@@ -629,6 +651,7 @@ k_move_tiles(const MoveArgs A)
     const int len = A.N - base < kDeepTile ? (int)(A.N - base) : kDeepTile;
     float* const by_tile = A.by_tile + base;
     const uint16_t* const from1 = A.P.from1 + base;
+    const bool tables = *A.P.unit_count != kDeepMerged;
     float x[kDeepPer];
     uint16_t from[kDeepPer];
 #pragma unroll
@@ -641,6 +664,7 @@ k_move_tiles(const MoveArgs A)
         const int q = i * kDeepThreads + tid;
         from[i] = from1[(uint32_t)(q < len ? q : 0)];
     }
+    if (!tables) return;                // uniform (asked for above: nothing waits for it)
 #pragma unroll
     for (int i = 0; i < kDeepPer; ++i) v[i * kDeepThreads + tid] = x[i];
     __syncthreads();
@@ -705,8 +729,13 @@ k_move_units(const MoveArgs A)
     __shared__ float v[CAP];
     __shared__ UnitRuns<THREADS, ITEMS> R;
     const int tid = threadIdx.x;
+    const uint32_t units = *A.P.unit_count;
+    if (units == kDeepMerged) {         // uniform
+        for (int64_t q = (int64_t)blockIdx.x * THREADS + tid; 4 * q < A.N; q += (int64_t)gridDim.x * THREADS) move_in_order(A.N, A.ids, A.src, A.ld, A.lo, A.hi, A.dst, q);
+        return;
+    }
     DeepUnit U;
-    if (!U.find(A.P)) return;
+    if (!U.find(A.P, units)) return;
     const int64_t cnt = U.cnt, base = U.base;
     uint32_t from, to;
     seq_range(A, U.b, from, to);
@@ -850,11 +879,18 @@ hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n
     return hipGetLastError();
 }
 
-hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const float* src, int64_t ld, int64_t lo, int64_t hi,
+hipError_t launch_move_in_order(int64_t N, const uint32_t* ids, const float* src, int64_t ld, int64_t lo, int64_t hi, float* dst, const char* tag, hipStream_t st)
+{
+    const std::string f = std::string("move_in_order.") + tag;
+    LAPLEX_TIMED(f.c_str(), st, hipLaunchKernelGGL(k_move_in_order, dim3((unsigned)((N + 1023) / 1024)), dim3(256), 0, st, N, ids, src, ld, lo, hi, dst));
+    return hipGetLastError();
+}
+
+hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const uint32_t* ids, const float* src, int64_t ld, int64_t lo, int64_t hi,
                             float* by_tile, float* by_piece, float* dst, const char* tag, hipStream_t st)
 {
     MoveArgs A{};
-    A.P = P; A.buckets = G.buckets; A.per_bucket = G.per_bucket; A.N = G.N; A.tiles = G.tiles;
+    A.P = P; A.ids = ids; A.buckets = G.buckets; A.per_bucket = G.per_bucket; A.N = G.N; A.tiles = G.tiles;
     A.src = src; A.ld = ld; A.lo = lo; A.hi = hi;
     A.tile0 = lo / kDeepTile; A.tile1 = (hi + kDeepTile - 1) / kDeepTile;
     A.by_tile = by_tile; A.by_piece = by_piece; A.dst = dst;

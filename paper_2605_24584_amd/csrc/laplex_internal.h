@@ -31,6 +31,7 @@ struct DeepGeom {
 };
 DeepGeom deep_geom(int64_t N);
 size_t deep_scratch_bytes(const DeepGeom& G);           // the sort's scratch
+constexpr uint32_t kDeepMerged = 0xFFFFFFFFu;
 // What the plan holds of it besides the sorted order itself.
 struct DeepPlan {
     uint16_t* from1;             // [N] by place in the tile layout: index inside the tile
@@ -43,7 +44,7 @@ struct DeepPlan {
     uint32_t* bucket_base;       // [buckets + 1] first sorted position
     uint32_t* piece_base;        // [buckets + 1] first piece
     uint32_t* piece_tile;        // [max_pieces] the tile that holds the piece's first pair
-    uint32_t* unit_count;        // [1]
+    uint32_t* unit_count;        // [1] or kDeepMerged: the order comes from a merge, and none of these tables is there
     uint4* units;                // [max_units] (bucket << 20 | first stretch << 10 | last stretch, first sorted position, pairs, -)
 };
 // Small state of one sort, u32 words: [0, 1024) histogram of the four digits; then the per-pass tile
@@ -351,9 +352,11 @@ hipError_t launch_split_sort(const float* a, int64_t k, const float* b, int64_t 
 // The same order for batch 1 beyond the small path, in two distributions; writes the whole plan, DeepPlan included.
 hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n, float tau, const DeepGeom& G, const DeepPlan& P, char* scratch,
                             uint32_t* ids, float* dh, float* pk, float2* pk8, uint32_t* counters, hipStream_t st);
-// dst[sorted position of id] = src[(id - lo) * ld] for lo <= id < hi, zero at every other position; by_tile, by_piece: N floats of scratch each.
-hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const float* src, int64_t ld, int64_t lo, int64_t hi,
+// dst[sorted position of id] = src[(id - lo) * ld] for lo <= id < hi, zero at every other position; by_tile, by_piece: N floats of scratch each.  On a plan
+// that was merged from anchors in order, which has no tables of moves (kDeepMerged), and by launch_move_in_order on any: by the ids.
+hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const uint32_t* ids, const float* src, int64_t ld, int64_t lo, int64_t hi,
                             float* by_tile, float* by_piece, float* dst, const char* tag, hipStream_t st);
+hipError_t launch_move_in_order(int64_t N, const uint32_t* ids, const float* src, int64_t ld, int64_t lo, int64_t hi, float* dst, const char* tag, hipStream_t st);
 
 // Both inputs ascending: merged keys/ids in one pass (ties: a first).
 hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, float tau,
@@ -364,9 +367,9 @@ hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, fl
 // keys == nullptr: the anchors are in pk[1 .. N] already (after the radix sort, ghist = its small words, or a sort that never waits,
 // ghist = nullptr) and the kernel adds the sentinels; otherwise the merge path, which leaves sorted keys in `keys`.  The last kernel
 // of these plan builds: it also
-// clears the scans' list counters (64 words).
+// clears the scans' list counters (64 words) and, where there is a `merged`, says there that the plan has no tables of moves.
 hipError_t launch_decay(const uint32_t* keys, const uint32_t* ghist, float* dh, float* pk, float2* pk8, uint32_t* counters,
-                        int64_t N, hipStream_t st);
+                        int64_t N, hipStream_t st, uint32_t* merged = nullptr);
 
 hipError_t launch_fill(float* p, int64_t rows, int64_t cols, int64_t ld, float v, hipStream_t st);
 hipError_t launch_copy_u32(const uint32_t* src, uint32_t* dst, int64_t count, hipStream_t st);

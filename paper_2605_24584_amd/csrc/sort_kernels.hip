@@ -534,8 +534,9 @@ k_merge(const float* __restrict__ a, int64_t k, const float* __restrict__ b, int
 template <bool FROM_PK>
 __global__ void __launch_bounds__(256)
 k_decay(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ ghist, float* __restrict__ dh, float* __restrict__ pk,
-        float2* __restrict__ pk8, uint32_t* __restrict__ counters, int64_t N)
+        float2* __restrict__ pk8, uint32_t* __restrict__ counters, int64_t N, uint32_t* __restrict__ merged)
 {
+    if (merged != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *merged = kDeepMerged;
     // list lengths of the scans that follow; and the sort's error flag moves to the plan (the sort's own words are scratch)
     if (blockIdx.x == 0 && threadIdx.x < 64)
         counters[threadIdx.x] = (threadIdx.x == kPlanStatusWord && ghist != nullptr) ? ghist[kSortErrorWord] : 0u;
@@ -674,11 +675,11 @@ hipError_t launch_merge(const float* a, int64_t k, const float* b, int64_t n, fl
 }
 
 hipError_t launch_decay(const uint32_t* keys, const uint32_t* ghist, float* dh, float* pk, float2* pk8, uint32_t* counters,
-                        int64_t N, hipStream_t st)
+                        int64_t N, hipStream_t st, uint32_t* merged)
 {
     const dim3 grid(grid_for((N + 5) / 4, 256)), block(256);
-    if (keys == nullptr) LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<true>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N));
-    else LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<false>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N));
+    if (keys == nullptr) LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<true>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N, merged));
+    else LAPLEX_TIMED("decay", st, hipLaunchKernelGGL(k_decay<false>, grid, block, 0, st, keys, ghist, dh, pk, pk8, counters, N, merged));
     return hipGetLastError();
 }
 

@@ -997,3 +997,86 @@ def test_mix_sorted_by_samples_up_to_2_to_17(oracle, r, k, n, batch):
     one = (B.laplex_workspace_bytes(k, n, batch) + 255) // 256 * 256
     for p in range(r):
         assert np.array_equal(gpu_perm(ws[p * one:], k + n), oracle.merged_permutation(a[p], b[p])), p
+
+
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal"])
+@pytest.mark.parametrize("k,n,ld", [(9000, 200000, 1), (65536, 65537, 2), (1, 8192, 1), (40003, 9, 3), (0, 70001, 1), (0, 98304, 2)])
+def test_one_column_in_order(oracle, k, n, ld, kind):
+    """Batch 1 on the routes through sorted order, anchors that arrive in order and are promised to (k = 0: Gram form): merged, not sorted, and rows fetched by the ids. The plan
+    serves calls without the promise, which find no tables of moves in it, and a plan that was sorted serves calls with it; the same bits either way."""
+    from test_gpu_parity import anchors, assert_close, gpu_perm, gpu_plan_status
+    r = np.random.default_rng(k + n + ld)
+    gram = k == 0
+    a, b = anchors(kind, r, k or 1, n)
+    a, b = np.sort(a), np.sort(b)
+    rows = n if gram else k
+    x, g = r.normal(size=(n, 1)).astype(np.float32), r.normal(size=(rows, 1)).astype(np.float32)
+    if gram:
+        (ref, tol), (want, tols) = oracle.gram_scan(b, x), oracle.gram_backward_scan(b, x, g)
+        promise = B.LAPLEX_A_SORTED
+    else:
+        (ref, tol), (want, tols) = oracle.apply_scan(a, b, x), oracle.apply_backward_scan(a, b, x, g)
+        promise = B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED
+    wide = [torch.zeros(s, ld, device="cuda") for s in (n, rows)]
+    dx, dg = (w[:, :1] for w in wide)
+    dx.copy_(dev(x)); dg.copy_(dev(g))
+    da, db = dev(a), dev(b)
+    y, gx, ga, gb = torch.empty(rows, 1, device="cuda"), torch.empty(n, 1, device="cuda"), torch.empty(rows, device="cuda"), torch.empty(n, device="cuda")
+    ws = torch.full((B.laplex_workspace_bytes(k, n, 1),), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def forward(flags):
+        B.laplex_gram(db, dx, y, ws, flags) if gram else B.laplex_apply(da, db, dx, y, ws, flags)
+
+    def backward(flags):
+        B.laplex_gram_backward(db, dx, dg, gx, ga, ws, flags) if gram else B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, flags)
+
+    perm = np.argsort(b, kind="stable") if gram else oracle.merged_permutation(a, b)
+    B.laplex_diag_set_route_min(0)
+    try:
+        first = None
+        for built, later in ((promise, promise), (promise, 0), (0, promise), (0, 0)):
+            seen = families(lambda: forward(built | B.LAPLEX_SAVE_SCANS))
+            assert ("merge" in seen) == ("move_in_order.fwd" in seen) == (built != 0) and ("deep_sort" in seen) == (built == 0), seen
+            assert np.array_equal(gpu_perm(ws, k + n), perm) and gpu_plan_status(ws, k + n) == 0
+            for again in (False, True):
+                if again: y.fill_(np.nan); forward(later | B.LAPLEX_REUSE_PLAN)
+                torch.cuda.synchronize()
+                assert_close("y", y.cpu().numpy(), ref, tol)
+            for flags in (B.LAPLEX_REUSE_PLAN, 0):
+                for v in (gx, ga, gb): v.fill_(np.nan)
+                backward(later | flags)
+                torch.cuda.synchronize()
+                got = [y.cpu().numpy(), gx.cpu().numpy(), ga.cpu().numpy()] + ([] if gram else [gb.cpu().numpy()])
+                if first is None: first = got
+                for name, v, rv, tv, f in zip(("gx", "ga", "gb"), got[1:], want, tols, first[1:]):
+                    assert_close(name, v, rv, tv)
+                    assert np.array_equal(v, f), name
+                assert np.array_equal(got[0], first[0])
+    finally:
+        B.laplex_diag_set_route_min(1 << 22)
+
+
+def test_one_column_in_order_with_a_wrong_promise():
+    """Anchors that are not in order, and not finite: any values, but the calls end and the workspace serves a clean problem afterwards."""
+    from test_gpu_parity import gpu_perm
+    q = np.random.default_rng(7)
+    k, n = 30000, 50001
+    x = torch.ones(n, 1, device="cuda")
+    y = torch.empty(k, 1, device="cuda")
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, 1), dtype=torch.uint8, device="cuda")
+    promise = B.LAPLEX_A_SORTED | B.LAPLEX_B_SORTED
+    B.laplex_diag_set_route_min(0)
+    try:
+        for bad in (True, False):
+            a, b = q.uniform(0, 1000, k).astype(np.float32), q.uniform(0, 1000, n).astype(np.float32)
+            if bad: a[::50] = np.nan; b[3] = np.inf
+            for flags in (promise, B.LAPLEX_REUSE_PLAN, promise | B.LAPLEX_REUSE_PLAN):
+                B.laplex_apply(dev(a), dev(b), x, y, ws, flags)
+                torch.cuda.synchronize()
+        a, b = np.sort(a), np.sort(b)
+        B.laplex_apply(dev(a), dev(b), x, y, ws, promise)
+        pos = np.empty(k + n, np.int64); pos[gpu_perm(ws, k + n)] = np.arange(k + n)
+        v = np.concatenate([a, b])
+        assert np.all(np.diff(v[np.argsort(pos)]) >= 0)
+    finally:
+        B.laplex_diag_set_route_min(1 << 22)
