@@ -154,12 +154,13 @@ PermuteJob permute_job(const Layout& L, char* ws, const char* tag)
 DeepPlan deep_plan(const Layout& L, char* ws)
 {
     DeepPlan D{};
+    D.tile_bits = L.deep.tile_bits;
     auto u16 = [&](size_t o) { return reinterpret_cast<uint16_t*>(ws + o); };
     D.from1 = u16(L.off_from1); D.slot2 = u16(L.off_slot2); D.slot3 = u16(L.off_slot3); D.slot3_high = u16(L.off_slot3_high);
     D.before = reinterpret_cast<uint32_t*>(ws + L.off_before); D.start1 = u16(L.off_start1); D.starts2 = u16(L.off_starts2);
     D.bucket_base = reinterpret_cast<uint32_t*>(ws + L.off_deep_bases);
     D.piece_base = D.bucket_base + L.deep.buckets + 1;
-    D.piece_tile = D.piece_base + L.deep.buckets + 1;
+    D.pieces = reinterpret_cast<uint4*>(ws + L.off_pieces);
     D.unit_count = reinterpret_cast<uint32_t*>(ws + L.off_units);
     D.units = reinterpret_cast<uint4*>(D.unit_count) + 1;
     return D;
@@ -189,7 +190,7 @@ int scan_and_send_home(ScanProblem& p, const Layout& L, char* ws, bool want_firs
     J.values = (want_first && want_second) ? 2 : 1;
     J.out0 = out0; J.ld0 = ld0; J.out1 = out1; J.ld1 = ld1;
     PartEmit E;
-    LAPLEX_HIP(permute_begin(J, &E, st));
+    permute_begin(J, &E);
     p.inj_sorted = p.out_sorted = true;
     p.emit = &E; p.emit_values = J.values; p.emit_first = want_first; p.emit_strict = want_second;
     LAPLEX_HIP(launch_scan(p, L, ws, st));

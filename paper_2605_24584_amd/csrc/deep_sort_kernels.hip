@@ -3,9 +3,9 @@
 //
 //   samples         one anchor per 128 (fewer beyond 2^29 positions), sorted by launch_split_sort; every samples_per-th is the first pair of a
 //                   stretch of the sorted sequence, and the first of per_bucket stretches the first of a bucket
-//   k_deep_tiles    (k_deep_distribute<false>) a tile of 16384 consecutive positions is laid out bucket by bucket, in the tile's own place
+//   k_deep_tiles    (k_deep_distribute<false>) a tile of 16384 (8192, see deep_geom) consecutive positions is laid out bucket by bucket, in the tile's own place
 //   k_deep_col_*, k_deep_bases    where every tile's run of a bucket lies in that bucket (prefix sums over the tiles)
-//   k_deep_pieces   (k_deep_distribute<true>) a piece of 16384 consecutive pairs of a bucket is gathered from the tiles' runs and laid out
+//   k_deep_pieces   (k_deep_distribute<true>) a piece of as many consecutive pairs of a bucket is gathered from the tiles' runs and laid out
 //                   stretch by stretch, in the piece's own place
 //   k_deep_units    consecutive stretches that fit a workgroup's LDS together
 //   k_deep_sort     a unit is gathered from its bucket's pieces, sorted in LDS and written to the plan: ids, anchors, decays
@@ -39,8 +39,9 @@ namespace laplex {
 
 namespace {
 
-constexpr int kDeepThreads = 1024, kDeepPer = kDeepTile / kDeepThreads;
+constexpr int kDeepThreads = 1024;        // of a tile or piece: 8 or 16 positions each (PER)
 constexpr int kDeepChunk = 64;            // tiles whose runs are added up together
+constexpr int kDeepManyPieces = 8191;     // (what a unit's record has room for)
 
 struct DeepArgs {
     const float* a; const float* b; int64_t k; float tau; int64_t N;
@@ -93,47 +94,40 @@ __device__ __forceinline__ uint32_t run_of(const uint32_t* mask, const uint32_t*
 }
 
 // LDS of a distribution.  lay: the layout buffer; before the pairs are laid out it holds the runs of a gathered piece.
+template <int PER>
 struct DeepShared {
-    __align__(16) uint32_t lay[kDeepTile];
+    __align__(16) uint32_t lay[kDeepThreads * PER];
     uint32_t bound_key[kBoundWords], bound_id[kSplitMaxBuckets];
     uint32_t hist[kSplitMaxBuckets + 1];       // (before the counts: mask and words of the runs)
     uint16_t same[kSplitMaxBuckets];
     uint32_t part[kDeepThreads / 64];
 };
-static_assert(sizeof(DeepShared) <= 80 * 1024, "two workgroups to a compute unit");
-static_assert(2 * (kDeepTile / 32) <= kSplitMaxBuckets, "mask and words fit where the counts go later");
+static_assert(sizeof(DeepShared<16>) <= 80 * 1024, "two workgroups to a compute unit");
+static_assert(2 * (kDeepThreads * 16 / 32) <= kSplitMaxBuckets, "mask and words fit where the counts go later");
 
 // The piece a workgroup of k_deep_pieces or k_move_pieces takes, and its runs: place e of the piece lies at delta[run] + e of the tile layout.
-struct DeepPiece { int bucket; uint32_t seq0; int len; };
-__device__ __forceinline__ bool find_piece(const DeepPlan& P, int buckets, uint32_t piece, uint32_t* word, DeepPiece& out)
+struct DeepPiece { int bucket; uint32_t seq0; int len; uint32_t tile; };
+__device__ __forceinline__ bool find_piece(const DeepPlan& P, int buckets, uint32_t piece, DeepPiece& out)
 {
-    if (threadIdx.x == 0) word[0] = 0xFFFFFFFFu;
-    __syncthreads();
-    const bool tables = *P.unit_count != kDeepMerged;
-    for (int i = threadIdx.x; i < buckets; i += kDeepThreads)
-        if (tables && P.piece_base[i] <= piece && piece < P.piece_base[i + 1]) word[0] = (uint32_t)i;
-    __syncthreads();
-    const uint32_t b = word[0];
-    __syncthreads();
-    if (b == 0xFFFFFFFFu) return false;
-    out.bucket = (int)b;
-    out.seq0 = (piece - P.piece_base[b]) * (uint32_t)kDeepTile;
-    const uint32_t left = P.bucket_base[b + 1] - P.bucket_base[b] - out.seq0;
-    out.len = left < (uint32_t)kDeepTile ? (int)left : kDeepTile;
+    const uint4 v = P.pieces[piece];            // (uniform, all three; beyond the last piece, or without tables, whatever lies there)
+    const uint32_t all = P.piece_base[buckets];
+    if (*P.unit_count == kDeepMerged || piece >= all) return false;
+    out.tile = v.x; out.bucket = (int)v.y; out.seq0 = v.z; out.len = (int)v.w;
     return true;
 }
-// delta: kDeepTile words, mask and before: kDeepTile / 32 words each, part: kDeepThreads / 64.  Ends with a barrier.
-__device__ __forceinline__ void piece_runs(const DeepPlan& P, int64_t tiles, uint32_t piece, const DeepPiece& p, uint32_t* delta,
-                                           uint32_t* mask, uint32_t* before, uint32_t* part)
+// delta: a word for every pair of a piece, mask and before: a word for every 32, part: kDeepThreads / 64.  Ends with a barrier.
+template <int PER>
+__device__ __forceinline__ void piece_runs(const DeepPlan& P, int64_t tiles, const DeepPiece& p, uint32_t* delta, uint32_t* mask, uint32_t* before, uint32_t* part)
 {
+    constexpr int TILE = kDeepThreads * PER;
     const int tid = threadIdx.x;
     const uint32_t* const col = P.before + (int64_t)p.bucket * tiles;
     const uint16_t* const start = P.start1 + (int64_t)p.bucket * tiles;
     const uint32_t cnt = P.bucket_base[p.bucket + 1] - P.bucket_base[p.bucket], end = p.seq0 + (uint32_t)p.len;
-    if (tid < kDeepTile / 32) mask[tid] = 0u;
+    if (tid < TILE / 32) mask[tid] = 0u;
     __syncthreads();
     uint32_t runs = 0u;
-    for (int64_t t0 = P.piece_tile[piece]; t0 < tiles; t0 += kDeepThreads) {
+    for (int64_t t0 = p.tile; t0 < tiles; t0 += kDeepThreads) {
         const int64_t t = t0 + tid;
         uint32_t ex = 0u, nx = 0u, st = 0u;
         if (t < tiles) { ex = col[t]; nx = t + 1 < tiles ? col[t + 1] : cnt; st = start[t]; }
@@ -142,63 +136,64 @@ __device__ __forceinline__ void piece_runs(const DeepPlan& P, int64_t tiles, uin
         uint32_t total;
         const uint32_t at = runs + block_scan<kDeepThreads>(some ? 1u : 0u, part, &total);
         if (some) {
-            delta[at] = (uint32_t)t * (uint32_t)kDeepTile + st + p.seq0 - ex;
+            delta[at] = (uint32_t)t * (uint32_t)TILE + st + p.seq0 - ex;
             atomicOr(&mask[(lo - p.seq0) >> 5], 1u << ((lo - p.seq0) & 31u));
         }
         runs += total;
         if (__syncthreads_or(t < tiles && nx >= end)) break;
     }
-    const uint32_t bits = tid < kDeepTile / 32 ? (uint32_t)__popc(mask[tid]) : 0u;
+    const uint32_t bits = tid < TILE / 32 ? (uint32_t)__popc(mask[tid]) : 0u;
     uint32_t total;
     const uint32_t ex = block_scan<kDeepThreads>(bits, part, &total);
-    if (tid < kDeepTile / 32) before[tid] = ex;
+    if (tid < TILE / 32) before[tid] = ex;
     __syncthreads();
 }
 
 // A distribution: of the anchors of a tile to the buckets (PIECES = false), or of a piece of a bucket to the bucket's stretches.
-template <bool PIECES>
+template <bool PIECES, int PER>
 __global__ void __launch_bounds__(kDeepThreads, 8)
 k_deep_distribute(const DeepArgs A)
 {
-    __shared__ DeepShared S;
+    constexpr int TILE = kDeepThreads * PER;
+    __shared__ DeepShared<PER> S;
     const int tid = threadIdx.x;
     const int targets = PIECES ? A.per_bucket : A.buckets;
-    DeepPiece p{0, 0u, kDeepTile};
-    int64_t out = (int64_t)blockIdx.x * kDeepTile;           // first place of the layout
-    uint32_t key[kDeepPer];
+    DeepPiece p{0, 0u, TILE, 0u};
+    int64_t out = (int64_t)blockIdx.x * TILE;           // first place of the layout
+    uint32_t key[PER];
     if (PIECES) {
-        if (!find_piece(A.P, A.buckets, blockIdx.x, S.part, p)) return;
+        if (!find_piece(A.P, A.buckets, blockIdx.x, p)) return;
         out = (int64_t)A.P.bucket_base[p.bucket] + p.seq0;
-        piece_runs(A.P, A.tiles, blockIdx.x, p, S.lay, S.hist, S.hist + kDeepTile / 32, S.part);
+        piece_runs<PER>(A.P, A.tiles, p, S.lay, S.hist, S.hist + TILE / 32, S.part);
         // the ids wait in the layout buffer, each in a word that its own thread alone reads
-        uint32_t id[kDeepPer];
+        uint32_t id[PER];
 #pragma unroll
-        for (int i = 0; i < kDeepPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const uint32_t e = (uint32_t)(i * kDeepThreads + tid) < (uint32_t)p.len ? (uint32_t)(i * kDeepThreads + tid) : (uint32_t)p.len - 1u;
-            const uint32_t src = S.lay[run_of(S.hist, S.hist + kDeepTile / 32, e)] + e;
+            const uint32_t src = S.lay[run_of(S.hist, S.hist + TILE / 32, e)] + e;
             key[i] = A.keys1[src];
-            id[i] = (src & ~(uint32_t)(kDeepTile - 1)) + A.P.from1[src];
+            id[i] = (src & ~(uint32_t)(TILE - 1)) + A.P.from1[src];
             if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);        // (no more than four addresses at once: two workgroups to a compute unit leave 64 registers)
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kDeepPer; ++i) S.lay[i * kDeepThreads + tid] = id[i];
+        for (int i = 0; i < PER; ++i) S.lay[i * kDeepThreads + tid] = id[i];
     } else {
         const int64_t left = A.N - out;
-        p.len = left < kDeepTile ? (int)left : kDeepTile;
+        p.len = left < TILE ? (int)left : TILE;
         const int last = p.len - 1;
         const int64_t of_a = A.k > out ? A.k - out : 0;         // the tile's first anchors are outputs'
         const float* const a = A.a + (of_a ? out : 0);
         const float* const b = A.b + (out - A.k);
 #pragma unroll
-        for (int i = 0; i < kDeepPer; ++i) {
+        for (int i = 0; i < PER; ++i) {
             const int q = i * kDeepThreads + tid, c = q < last ? q : last;
             key[i] = split_key(A.tau * (c < of_a ? a : b)[c]);
         }
     }
     const int len = p.len;
     for (int i = tid; i < kSplitMaxBuckets + 1; i += kDeepThreads) S.hist[i] = 0u;
-    uint32_t at[kDeepPer];          // target in the upper half, place among the tile's pairs of the target in the lower half; then the place in the layout
+    uint32_t at[PER];          // target in the upper half, place among the tile's pairs of the target in the lower half; then the place in the layout
     {
         // (the bounds of the buckets lie per_bucket apart: the first of every bucket's stretches)
         const StretchBounds<kDeepThreads> bound(PIECES ? A.bounds + (int64_t)p.bucket * A.per_bucket : A.bounds, targets, PIECES ? 1 : A.per_bucket,
@@ -208,7 +203,7 @@ k_deep_distribute(const DeepArgs A)
     }
     // (places beyond the last pair go behind all targets)
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         at[i] = i * kDeepThreads + tid < len ? at[i] : (uint32_t)kSplitMaxBuckets;
         at[i] = (at[i] << 16) | atomicAdd(&S.hist[at[i]], 1u);
         asm volatile("" : "+v"(at[i]));         // (one register, not two)
@@ -230,12 +225,12 @@ k_deep_distribute(const DeepArgs A)
     uint2* const pairs2 = A.pairs2 + out;
     uint32_t* const keys1 = A.keys1 + out;
     uint16_t* const from1 = A.P.from1 + out;
-    uint32_t other[kDeepPer];       // the other half of a pair: its id, or for a tile the index it came from
+    uint32_t other[PER];       // the other half of a pair: its id, or for a tile the index it came from
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) other[i] = PIECES ? S.lay[(uint32_t)(i * kDeepThreads) + me] : (uint32_t)(i * kDeepThreads) + me;
+    for (int i = 0; i < PER; ++i) other[i] = PIECES ? S.lay[(uint32_t)(i * kDeepThreads) + me] : (uint32_t)(i * kDeepThreads) + me;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads) + me;
         at[i] = S.hist[at[i] >> 16] + (at[i] & 0xFFFFu);
         S.lay[at[i]] = key[i];
@@ -245,25 +240,25 @@ k_deep_distribute(const DeepArgs A)
     // (a piece's ids are there as well: two places to a register while the keys come back, and places formed again; with one each six registers went
     // to scratch, 24 bytes of memory traffic a lane: 2^28 pairs 1370 -> 1227 us, 2^25 183 -> 172)
 #pragma unroll
-    for (int i = 0; PIECES && i < kDeepPer; i += 2) {
+    for (int i = 0; PIECES && i < PER; i += 2) {
         at[i] |= at[i + 1] << 16;
         asm volatile("" : "+v"(at[i]));
     }
     __syncthreads();
     if (PIECES) asm volatile("" : "+v"(me));
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads) + me;
         key[i] = S.lay[q];
         if (!PIECES && q < (uint32_t)len) keys1[q] = key[i];
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) S.lay[!PIECES ? at[i] : i % 2 ? at[i - 1] >> 16 : at[i] & 0xFFFFu] = other[i];
+    for (int i = 0; i < PER; ++i) S.lay[!PIECES ? at[i] : i % 2 ? at[i - 1] >> 16 : at[i] & 0xFFFFu] = other[i];
     __syncthreads();
     if (PIECES) asm volatile("" : "+v"(me));
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads) + me;
         if (q < (uint32_t)len) {
             if (PIECES) pairs2[q] = make_uint2(key[i], S.lay[q]);
@@ -330,7 +325,7 @@ k_deep_bases(const DeepArgs A)
     }
     uint32_t total, pieces;
     const uint32_t ex = block_scan<kSplitMaxBuckets>(cnt, part, &total);
-    const uint32_t pex = block_scan<kSplitMaxBuckets>((cnt + (uint32_t)(kDeepTile - 1)) / (uint32_t)kDeepTile, part, &pieces);
+    const uint32_t pex = block_scan<kSplitMaxBuckets>((uint32_t)(((uint64_t)cnt + (1u << A.P.tile_bits) - 1u) >> A.P.tile_bits), part, &pieces);
     __syncthreads();
     if (b < A.buckets) { A.P.bucket_base[b] = ex; A.P.piece_base[b] = pex; }
     if (b == A.buckets - 1) { A.P.bucket_base[b + 1] = total; A.P.piece_base[b + 1] = pieces; }
@@ -363,8 +358,11 @@ k_deep_col_runs(const DeepArgs A)
         if (t < A.tiles) {
             A.P.before[(int64_t)b * A.tiles + t] = ex;
             A.P.start1[(int64_t)b * A.tiles + t] = (uint16_t)from;
-            const uint32_t piece = (uint32_t)(((uint64_t)ex + (kDeepTile - 1)) / kDeepTile);
-            if ((uint64_t)piece * kDeepTile < (uint64_t)ex + n) A.P.piece_tile[A.P.piece_base[b] + piece] = (uint32_t)t;
+            const uint32_t tile = 1u << A.P.tile_bits, piece = (uint32_t)(((uint64_t)ex + tile - 1u) >> A.P.tile_bits);
+            if (((uint64_t)piece << A.P.tile_bits) < (uint64_t)ex + n) {
+                const uint32_t seq0 = piece << A.P.tile_bits, left = A.P.bucket_base[b + 1] - A.P.bucket_base[b] - seq0;
+                A.P.pieces[A.P.piece_base[b] + piece] = make_uint4((uint32_t)t, (uint32_t)b, seq0, left < tile ? left : tile);
+            }
         }
     }
 }
@@ -410,7 +408,7 @@ k_deep_units(const DeepArgs A, uint32_t capacity)
     __syncthreads();
     if (g < units) {
         const uint32_t g0 = cut[g], g1 = cut[g + 1];
-        A.P.units[at + g] = make_uint4((uint32_t)b << 20 | g0 << 10 | (g1 - 1u), A.P.bucket_base[b] + from[g0], from[g1] - from[g0], 0u);
+        A.P.units[at + g] = make_uint4((uint32_t)b << 20 | g0 << 10 | (g1 - 1u), A.P.bucket_base[b] + from[g0], from[g1] - from[g0], piece0 | (uint32_t)(pieces < kDeepManyPieces ? pieces : kDeepManyPieces) << 19);
     }
 }
 
@@ -428,7 +426,8 @@ struct DeepUnit {
         const uint4 v = P.units[u];
         b = (int)(v.x >> 20); g0 = (int)(v.x >> 10 & 1023u); g1 = (int)(v.x & 1023u) + 1;
         base = v.y; cnt = v.z;
-        piece0 = P.piece_base[b]; pieces = (int)(P.piece_base[b + 1] - piece0);
+        piece0 = v.w & 0x7FFFFu; pieces = (int)(v.w >> 19);
+        if (pieces == kDeepManyPieces) pieces = (int)(P.piece_base[b + 1] - P.piece_base[b]);      // uniform
         first = P.bucket_base[b];
         return true;
     }
@@ -463,7 +462,7 @@ __device__ __forceinline__ void unit_runs(const DeepPlan& P, int per_bucket, con
         at += w < wave ? R.some[w] : 0u;
     }
     if (n) {
-        R.delta[at] = (uint32_t)tid * (uint32_t)kDeepTile + lo - ex;
+        R.delta[at] = ((uint32_t)tid << P.tile_bits) + lo - ex;
         if (ex < (uint32_t)(THREADS * ITEMS)) atomicOr(&R.mask[ex >> 5], 1u << (ex & 31u));
     }
     __syncthreads();
@@ -481,7 +480,7 @@ __device__ __forceinline__ void each_of_unit(const DeepPlan& P, int per_bucket, 
     for (int p = 0; p < U.pieces; ++p) {
         const uint16_t* const row = P.starts2 + (int64_t)(U.piece0 + p) * (per_bucket + 1);
         const int lo = row[U.g0], n = row[U.g1] - lo;
-        const int64_t from = (int64_t)U.first + (int64_t)p * kDeepTile + lo;
+        const int64_t from = (int64_t)U.first + ((int64_t)p << P.tile_bits) + lo;
         for (int i = threadIdx.x; i < n; i += THREADS) use(e0 + i, from + i, p);
         e0 += n;
     }
@@ -642,34 +641,36 @@ k_move_in_order(int64_t N, const uint32_t* __restrict__ ids, const float* __rest
 }
 
 // A tile's values in its layout.
+template <int PER>
 __global__ void __launch_bounds__(kDeepThreads, 8)
 k_move_tiles(const MoveArgs A)
 {
-    __shared__ __align__(16) float v[kDeepTile];
+    constexpr int TILE = kDeepThreads * PER;
+    __shared__ __align__(16) float v[TILE];
     const int tid = threadIdx.x;
-    const int64_t base = (A.tile0 + blockIdx.x) * kDeepTile;
-    const int len = A.N - base < kDeepTile ? (int)(A.N - base) : kDeepTile;
+    const int64_t base = (A.tile0 + blockIdx.x) * TILE;
+    const int len = A.N - base < TILE ? (int)(A.N - base) : TILE;
     float* const by_tile = A.by_tile + base;
     const uint16_t* const from1 = A.P.from1 + base;
     const bool tables = *A.P.unit_count != kDeepMerged;
-    float x[kDeepPer];
-    uint16_t from[kDeepPer];
+    float x[PER];
+    uint16_t from[PER];
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const int64_t id = base + i * kDeepThreads + tid;
         x[i] = id >= A.lo && id < A.hi ? A.src[(id - A.lo) * A.ld] : 0.0f;
     }
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const int q = i * kDeepThreads + tid;
         from[i] = from1[(uint32_t)(q < len ? q : 0)];
     }
     if (!tables) return;                // uniform (asked for above: nothing waits for it)
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) v[i * kDeepThreads + tid] = x[i];
+    for (int i = 0; i < PER; ++i) v[i * kDeepThreads + tid] = x[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const int q = i * kDeepThreads + tid;
         if (q < len) by_tile[(uint32_t)q] = v[from[i]];
     }
@@ -684,25 +685,27 @@ __device__ __forceinline__ void seq_range(const MoveArgs& A, int b, uint32_t& fr
 }
 
 // A piece's values in its layout.
+template <int PER>
 __global__ void __launch_bounds__(kDeepThreads, 8)
 k_move_pieces(const MoveArgs A)
 {
-    __shared__ __align__(16) float v[kDeepTile];
-    __shared__ uint32_t mask[kDeepTile / 32], before[kDeepTile / 32], part[kDeepThreads / 64];
+    constexpr int TILE = kDeepThreads * PER;
+    __shared__ __align__(16) float v[TILE];
+    __shared__ uint32_t mask[TILE / 32], before[TILE / 32], part[kDeepThreads / 64];
     const int tid = threadIdx.x;
     DeepPiece p;
-    if (!find_piece(A.P, A.buckets, blockIdx.x, part, p)) return;
+    if (!find_piece(A.P, A.buckets, blockIdx.x, p)) return;
     uint32_t from, to;
     seq_range(A, p.bucket, from, to);
     if (p.seq0 >= to || p.seq0 + (uint32_t)p.len <= from) return;       // uniform: nothing of the range
     const int64_t out = (int64_t)A.P.bucket_base[p.bucket] + p.seq0;
-    piece_runs(A.P, A.tiles, blockIdx.x, p, reinterpret_cast<uint32_t*>(v), mask, before, part);
+    piece_runs<PER>(A.P, A.tiles, p, reinterpret_cast<uint32_t*>(v), mask, before, part);
     float* const by_piece = A.by_piece + out;
     const uint16_t* const slot2 = A.P.slot2 + out;
-    float x[kDeepPer];
-    uint16_t slot[kDeepPer];
+    float x[PER];
+    uint16_t slot[PER];
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const uint32_t q = (uint32_t)(i * kDeepThreads + tid), e = q < (uint32_t)p.len ? q : (uint32_t)p.len - 1u;
         const uint32_t src = reinterpret_cast<const uint32_t*>(v)[run_of(mask, before, e)] + e;
         x[i] = p.seq0 + e >= from && p.seq0 + e < to ? A.by_tile[src] : 0.0f;
@@ -710,17 +713,19 @@ k_move_pieces(const MoveArgs A)
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i)
+    for (int i = 0; i < PER; ++i)
         if (i * kDeepThreads + tid < p.len) v[slot[i]] = x[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kDeepPer; ++i) {
+    for (int i = 0; i < PER; ++i) {
         const int q = i * kDeepThreads + tid;
         if (q < p.len) by_piece[(uint32_t)q] = v[q];
     }
 }
 
-// A unit's values in sorted order.
+// A unit's values in sorted order.  (256 threads of 16 pairs: the units of 2^22 to 2^23 positions are a few more than as many workgroups of 512 threads as fit; us, forward on
+// a kept plan, 512 of 8 / this: 2^22 x 2^22 115.4 / 113.1, 2^23 x 2^23 211 / 206.)  What slot3 says does not depend on how the sort went about the unit, in LDS or in
+// memory: places among the pairs as gathered count piece by piece either way, so that this may go the other way.
 template <int THREADS, int ITEMS>
 __global__ void __launch_bounds__(THREADS, 8)
 k_move_units(const MoveArgs A)
@@ -740,7 +745,7 @@ k_move_units(const MoveArgs A)
     uint32_t from, to;
     seq_range(A, U.b, from, to);
     // pieces that were written: those with a place of the range
-    const uint32_t first = from / (uint32_t)kDeepTile, last = to > from ? (to - 1u) / (uint32_t)kDeepTile : 0u;
+    const uint32_t first = from >> A.P.tile_bits, last = to > from ? (to - 1u) >> A.P.tile_bits : 0u;
     const bool any = to > from;
     if (cnt <= CAP && U.pieces <= THREADS) {      // uniform
         unit_runs<THREADS, ITEMS>(A.P, A.per_bucket, U, R);
@@ -748,7 +753,7 @@ k_move_units(const MoveArgs A)
         const float* const by_piece = A.by_piece + U.first;
         const uint16_t* const slot3 = A.P.slot3 + base;
         float* const dst = A.dst + base;
-        const uint32_t lo = first * (uint32_t)kDeepTile, span = any ? (last - first + 1u) * (uint32_t)kDeepTile : 0u;
+        const uint32_t lo = first << A.P.tile_bits, span = any ? (last - first + 1u) << A.P.tile_bits : 0u;
         float x[ITEMS];
         uint16_t slot[ITEMS];
 #pragma unroll
@@ -813,6 +818,10 @@ struct DeepScratch {
 
 }  // namespace
 
+// Tiles and pieces of 8192 positions where those of 16384 would leave most of the compute units one workgroup, or none (us, 16384 / 8192, forward on a kept plan, forward,
+// forward + backward: 1258292 x 2936012 77.9 / 72.5, 220 / 206, 323 / 306; 2^22 x 2^22 116 / 114, 351 / 328, 536 / 514; Gram form of 10^7 252 / 246, 497 / 474, 907 / 886;
+// 2^23 x 2^23 211 / 211, 573 / 563, 914 / 910), but not where runs get short (2^24 x 2^24 forward + backward 1842 / 1857; 2^25 x 2^25 forward 2001 / 2057).
+constexpr int64_t kDeepSmallTilesMax = int64_t(1) << 24;
 DeepGeom deep_geom(int64_t N)
 {
     DeepGeom G;
@@ -832,7 +841,8 @@ DeepGeom deep_geom(int64_t N)
     G.samples_per = per < 6 ? (int)per : 6;
     G.samples = G.stretches * G.samples_per;
     G.max_units = 2 * (N / G.capacity) + 2 * G.buckets;
-    G.tiles = (N + kDeepTile - 1) / kDeepTile;
+    G.tile_bits = N <= kDeepSmallTilesMax ? 13 : 14;
+    G.tiles = (N + ((int64_t)1 << G.tile_bits) - 1) >> G.tile_bits;
     G.max_pieces = G.tiles + G.buckets;
     return G;
 }
@@ -861,7 +871,8 @@ hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n
                                            reinterpret_cast<uint32_t*>(scratch + D.sample_counters), 1, 0, 0, 0, st);
     if (e != hipSuccess) return e;
     LAPLEX_TIMED("deep_bounds", st, hipLaunchKernelGGL(k_deep_bounds, of(A.stretches, 256), dim3(256), 0, st, A));
-    LAPLEX_TIMED("deep_tiles", st, hipLaunchKernelGGL((k_deep_distribute<false>), dim3((unsigned)A.tiles), dim3(kDeepThreads), 0, st, A));
+    auto distribute = [&](const char* family, auto kernel, int64_t groups) { LAPLEX_TIMED(family, st, hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kDeepThreads), 0, st, A)); };
+    if (G.tile_bits == 13) distribute("deep_tiles", k_deep_distribute<false, 8>, A.tiles); else distribute("deep_tiles", k_deep_distribute<false, 16>, A.tiles);
     LAPLEX_TIMED("deep_columns", st, hipLaunchKernelGGL(k_deep_col_sums, dim3((unsigned)A.chunks), dim3(kSplitMaxBuckets), 0, st, A));
     if (A.chunks <= kDeepFewChunks) {
         LAPLEX_TIMED("deep_columns", st, hipLaunchKernelGGL((k_deep_bases<true>), dim3(1), dim3(kSplitMaxBuckets), 0, st, A));
@@ -870,7 +881,7 @@ hipError_t launch_deep_sort(const float* a, int64_t k, const float* b, int64_t n
         LAPLEX_TIMED("deep_columns", st, hipLaunchKernelGGL((k_deep_bases<false>), dim3(1), dim3(kSplitMaxBuckets), 0, st, A));
     }
     LAPLEX_TIMED("deep_columns", st, hipLaunchKernelGGL(k_deep_col_runs, dim3((unsigned)A.chunks, (unsigned)((A.buckets + 63) / 64)), dim3(1024), 0, st, A));
-    LAPLEX_TIMED("deep_pieces", st, hipLaunchKernelGGL((k_deep_distribute<true>), dim3((unsigned)G.max_pieces), dim3(kDeepThreads), 0, st, A));
+    if (G.tile_bits == 13) distribute("deep_pieces", k_deep_distribute<true, 8>, G.max_pieces); else distribute("deep_pieces", k_deep_distribute<true, 16>, G.max_pieces);
     LAPLEX_TIMED("deep_units", st, hipLaunchKernelGGL(k_deep_units, dim3((unsigned)A.buckets), dim3(kSplitMaxBuckets), 0, st, A, (uint32_t)G.capacity));
     const dim3 units((unsigned)((G.max_units + 7) / 8 * 8));
     if (G.capacity == 8192) LAPLEX_TIMED("deep_sort", st, hipLaunchKernelGGL((k_deep_sort<512, 16>), units, dim3(512), 0, st, A));
@@ -892,14 +903,15 @@ hipError_t launch_deep_move(const DeepGeom& G, const DeepPlan& P, const uint32_t
     MoveArgs A{};
     A.P = P; A.ids = ids; A.buckets = G.buckets; A.per_bucket = G.per_bucket; A.N = G.N; A.tiles = G.tiles;
     A.src = src; A.ld = ld; A.lo = lo; A.hi = hi;
-    A.tile0 = lo / kDeepTile; A.tile1 = (hi + kDeepTile - 1) / kDeepTile;
+    A.tile0 = lo >> G.tile_bits; A.tile1 = (hi + ((int64_t)1 << G.tile_bits) - 1) >> G.tile_bits;
     A.by_tile = by_tile; A.by_piece = by_piece; A.dst = dst;
     const std::string ft = std::string("move_tiles.") + tag, fp = std::string("move_pieces.") + tag, fs = std::string("move_units.") + tag;
-    LAPLEX_TIMED(ft.c_str(), st, hipLaunchKernelGGL(k_move_tiles, dim3((unsigned)(A.tile1 - A.tile0)), dim3(kDeepThreads), 0, st, A));
-    LAPLEX_TIMED(fp.c_str(), st, hipLaunchKernelGGL(k_move_pieces, dim3((unsigned)G.max_pieces), dim3(kDeepThreads), 0, st, A));
+    auto move = [&](const std::string& family, auto kernel, int64_t groups) { LAPLEX_TIMED(family.c_str(), st, hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kDeepThreads), 0, st, A)); };
+    if (G.tile_bits == 13) { move(ft, k_move_tiles<8>, A.tile1 - A.tile0); move(fp, k_move_pieces<8>, G.max_pieces); }
+    else { move(ft, k_move_tiles<16>, A.tile1 - A.tile0); move(fp, k_move_pieces<16>, G.max_pieces); }
     const dim3 units((unsigned)((G.max_units + 7) / 8 * 8));
     if (G.capacity == 8192) LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_move_units<1024, 8>), units, dim3(1024), 0, st, A));
-    else LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_move_units<512, 8>), units, dim3(512), 0, st, A));
+    else LAPLEX_TIMED(fs.c_str(), st, hipLaunchKernelGGL((k_move_units<256, 16>), units, dim3(256), 0, st, A));
     return hipGetLastError();
 }
 

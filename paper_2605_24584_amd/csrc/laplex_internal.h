@@ -22,10 +22,10 @@ inline int64_t sort_tiles_of(int64_t N) { return (N + kSortTile - 1) / kSortTile
 constexpr int64_t kSplitSortMax = int64_t(1) << 22;
 size_t split_sort_words(int64_t N);                     // scratch words that takes besides the pair buffers
 // Batch 1, many anchors: sorted by samples in two distributions, and values moved into the sorted order along the same way
-// (deep_sort_kernels.hip).  Tiles and pieces of kDeepTile positions; buckets (at most 1024) of per_bucket stretches each.
-constexpr int kDeepTile = 16384;
+// (deep_sort_kernels.hip).  Tiles and pieces of 2^tile_bits positions; buckets (at most 1024) of per_bucket stretches each.
 struct DeepGeom {
     int64_t N;
+    int tile_bits;                                       // 13 or 14
     int buckets, per_bucket, samples_per, capacity;      // capacity: pairs of a unit (consecutive stretches sorted together), but for a longer stretch
     int64_t tiles, max_pieces, max_units, stretches, samples;
 };
@@ -34,6 +34,7 @@ size_t deep_scratch_bytes(const DeepGeom& G);           // the sort's scratch
 constexpr uint32_t kDeepMerged = 0xFFFFFFFFu;
 // What the plan holds of it besides the sorted order itself.
 struct DeepPlan {
+    int tile_bits;
     uint16_t* from1;             // [N] by place in the tile layout: index inside the tile
     uint16_t* slot2;             // [N] by place in the bucket: place inside the piece's layout
     uint16_t* slot3;             // [N] by place in the unit as gathered: place in it as sorted; slot3_high: upper halves, only for units that a
@@ -43,9 +44,10 @@ struct DeepPlan {
     uint16_t* starts2;           // [max_pieces][per_bucket + 1] places of the stretches' runs in a piece's layout
     uint32_t* bucket_base;       // [buckets + 1] first sorted position
     uint32_t* piece_base;        // [buckets + 1] first piece
-    uint32_t* piece_tile;        // [max_pieces] the tile that holds the piece's first pair
+    uint4* pieces;               // [max_pieces] (tile that holds the piece's first pair, bucket, that pair's place in the bucket, pairs)
     uint32_t* unit_count;        // [1] or kDeepMerged: the order comes from a merge, and none of these tables is there
-    uint4* units;                // [max_units] (bucket << 20 | first stretch << 10 | last stretch, first sorted position, pairs, -)
+    uint4* units;                // [max_units] (bucket << 20 | first stretch << 10 | last stretch, first sorted position, pairs, first piece of the bucket | its pieces << 19,
+                                 //     but at most 8191: what a workgroup needs to go on is one access away)
 };
 // Small state of one sort, u32 words: [0, 1024) histogram of the four digits; then the per-pass tile
 // tickets, the error flag and the histogram's done counter in one cache line, and the mask of the passes that run in a line of its own.
@@ -91,21 +93,28 @@ constexpr int kSpineSuperTiles = 32;   // tiles summed up together by the spine 
 // ----------------------------------------------------------------------------
 // Batch 1, many rows: values move between the caller's order and the sorted order as records through
 // partition passes instead of by random accesses (permute_kernels.hip).  A window is the stretch of
-// destinations that the last pass places inside LDS; a partition level has at most 2^9 buckets.
+// destinations that the last pass places inside LDS; a partition level has at most 2^9 buckets.  Up to 2^22 destinations, of which 512 windows
+// of half the size hold all, have such windows: whole ones leave half the compute units without one (us, forward on a kept plan: 1258292 x 2936012
+// 72.5 -> 69.3, 2200000 x 2200000 86.7 -> 84.8).
 // ----------------------------------------------------------------------------
 constexpr int kPermuteWindowBits = 14;
 constexpr int kPermuteMaxBucketBits = 9;
+inline int permute_window_bits(int64_t dest_count)
+{
+    return dest_count <= (int64_t)1 << (kPermuteWindowBits - 1 + kPermuteMaxBucketBits) ? kPermuteWindowBits - 1 : kPermuteWindowBits;
+}
 bool permute_supported(int64_t dest_count);      // destinations fit two partition levels
 size_t permute_cursor_words(int64_t dest_count);                        // the buckets' cursors of both levels
 // records that a level's output array must hold for `dest_count` destinations: whole windows when one level fills
 // the windows directly (at most 2^9 of them), else whole regions of 2^9 windows; and whether there are two levels
 inline bool permute_two_levels(int64_t dest_count)
 {
-    return ((dest_count + ((int64_t)1 << kPermuteWindowBits) - 1) >> kPermuteWindowBits) > ((int64_t)1 << kPermuteMaxBucketBits);
+    const int bits = permute_window_bits(dest_count);
+    return ((dest_count + ((int64_t)1 << bits) - 1) >> bits) > ((int64_t)1 << kPermuteMaxBucketBits);
 }
 inline int64_t permute_capacity(int64_t dest_count)
 {
-    const int64_t region = (int64_t)1 << (kPermuteWindowBits + (permute_two_levels(dest_count) ? kPermuteMaxBucketBits : 0));
+    const int64_t region = (int64_t)1 << (permute_window_bits(dest_count) + (permute_two_levels(dest_count) ? kPermuteMaxBucketBits : 0));
     return (dest_count + region - 1) / region * region;
 }
 
@@ -211,7 +220,7 @@ struct Layout {
     // batch 1 beyond the small path: the routes through sorted order without random accesses
     bool permute = false;        // the regions below exist
     DeepGeom deep{};             // the sort of these problems, and of its plan (DeepPlan):
-    size_t off_from1 = 0, off_slot2 = 0, off_slot3 = 0, off_slot3_high = 0, off_before = 0, off_start1 = 0, off_starts2 = 0, off_units = 0, off_deep_bases = 0;
+    size_t off_from1 = 0, off_slot2 = 0, off_slot3 = 0, off_slot3_high = 0, off_before = 0, off_start1 = 0, off_starts2 = 0, off_units = 0, off_pieces = 0, off_deep_bases = 0;
     size_t off_deep = 0;         // scratch, sort view: the sort's own
     size_t off_by_tile = 0, off_by_piece = 0;      // f32[N] each, scratch: values on their way into the sorted order
     size_t off_pk8 = 0;          // float2[(N+2)/8 + 1]  plan: (pk[8m], pk[8m + 1]), the anchors the sorted-order kernels need
@@ -242,7 +251,8 @@ inline Layout make_layout(int64_t N, int64_t zrows, int64_t batch, bool permute_
         L.off_before = take(4 * (size_t)G.buckets * (size_t)G.tiles); L.off_start1 = take(2 * (size_t)G.buckets * (size_t)G.tiles);
         L.off_starts2 = take(2 * (size_t)G.max_pieces * (size_t)(G.per_bucket + 1));
         L.off_units = take(16 * ((size_t)G.max_units + 1));
-        L.off_deep_bases = take(4 * (2 * (size_t)(G.buckets + 1) + (size_t)G.max_pieces));
+        L.off_pieces = take(16 * (size_t)G.max_pieces);
+        L.off_deep_bases = take(4 * 2 * (size_t)(G.buckets + 1));
     }
     L.off_pk8 = o;
     if (L.permute) o = align_up(o + 2 * sizeof(float) * ((size_t)(N + 2) / 8 + 1));
@@ -393,11 +403,13 @@ struct PartEmit {
     float* out_v1 = nullptr;          // second values
     uint32_t* cursor = nullptr;       // records placed so far, per bucket (zero when the level starts)
     int64_t dest_count = 0;           // destinations are below this
+    uint32_t* clear = nullptr;        // cursors that the producer clears before any record is placed ...
+    int64_t clear_words = 0;          // ... as many words
 };
 
 // Results home: row j of the sorted sequence goes to destination ids[j] - lo of the caller's order, as a record (destination, value[, value])
-// through partition levels.  The producer (the batch-1 downsweep) places the records of the first level itself: permute_begin clears the
-// cursors and says where they go; permute_finish runs what follows.  The last pass writes out0[d * ld0] (and out1[d * ld1]) for every
+// through partition levels.  The producer (the batch-1 scan) clears the cursors in its reduce and places the records of the first level in its downsweep: permute_begin says
+// where they go; permute_finish runs what follows.  The last pass writes out0[d * ld0] (and out1[d * ld1]) for every
 // destination d < dest_count: zero where no record arrived.
 struct PermuteJob {
     int64_t dest_count = 0;
@@ -408,7 +420,7 @@ struct PermuteJob {
     const uint32_t* poison = nullptr;                  // nonzero: every value written becomes a NaN
     const char* tag = "move";                          // names the timing families permute_part.<tag>, permute_final.<tag>
 };
-hipError_t permute_begin(const PermuteJob& J, PartEmit* first_level, hipStream_t st);
+void permute_begin(const PermuteJob& J, PartEmit* first_level);
 hipError_t permute_finish(const PermuteJob& J, hipStream_t st);
 
 // Phased backward, fused (Sec. 3 "Phased Laplace kernels"): the scan problem runs on the doubled batch

@@ -4,7 +4,7 @@
 // At batch 1 a row is one float.  Storing a result at y[id] costs a partial line and is bound by the number of memory
 // transactions, not by bytes.  Here every result travels as a record (destination, value[, value]) through at most two partition
 // levels, each of which reads its records once and writes them once in runs, and a last pass that places the records of one window of
-// 16384 consecutive destinations inside LDS and writes the window out whole:
+// 16384 (8192, see permute_window_bits) consecutive destinations inside LDS and writes the window out whole:
 //
 //   level 1   the batch-1 downsweep places its results itself, into up to 512 buckets by the top bits of the destination (or, with
 //             at most 512 windows, into the windows)
@@ -86,14 +86,14 @@ struct FinalArgs {
     const uint32_t* poison;                        // the plan's status word, or null (never for the plan's own arrays)
 };
 
-// The last pass: one workgroup per window of 16384 consecutive destinations.  The windows are taken from the last one down: the level
+// The last pass: one workgroup per window of 2^BITS consecutive destinations.  The windows are taken from the last one down: the level
 // before it fills them in ascending order, so the records it wrote last are still in the 256 MB memory-side cache (us, ascending /
 // descending, 2^25 positions, two values: 82 -> 73).
-template <int NV>
+template <int NV, int BITS>
 __global__ void __launch_bounds__(kPtThreads)
 k_part_final(const FinalArgs A)
 {
-    constexpr int W = 1 << kPermuteWindowBits;
+    constexpr int W = 1 << BITS;
     __shared__ float s0[W];
     __shared__ float s1[NV == 2 ? W : 1];
     const int tid = threadIdx.x;
@@ -102,7 +102,7 @@ k_part_final(const FinalArgs A)
     if (count > (uint32_t)W) count = (uint32_t)W;
     for (int i = tid; i < W; i += kPtThreads) { s0[i] = 0.0f; if (NV == 2) s1[i] = 0.0f; }
     __syncthreads();
-    const int64_t base = w << kPermuteWindowBits;
+    const int64_t base = w << BITS;
     for (uint32_t i = tid; i < count; i += kPtThreads) {
         const uint2 dv = A.in_dv[base + i];
         const uint32_t d = dv.x & (uint32_t)(W - 1);
@@ -120,16 +120,6 @@ k_part_final(const FinalArgs A)
     }
 }
 
-__global__ void __launch_bounds__(256)
-k_zero_words(uint32_t* __restrict__ p, int64_t count)
-{
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-        if (i + 4 <= count) *reinterpret_cast<uint4*>(p + i) = make_uint4(0u, 0u, 0u, 0u);
-        else for (int64_t j = i; j < count; ++j) p[j] = 0u;
-    }
-}
-
 int ceil_log2(int64_t v) { int l = 0; while (((int64_t)1 << l) < v) ++l; return l; }
 
 }  // namespace
@@ -137,23 +127,26 @@ int ceil_log2(int64_t v) { int l = 0; while (((int64_t)1 << l) < v) ++l; return 
 bool permute_supported(int64_t dest_count)
 {
     if (dest_count <= 0) return false;
-    const int64_t windows = (dest_count + (1 << kPermuteWindowBits) - 1) >> kPermuteWindowBits;
+    const int bits = permute_window_bits(dest_count);
+    const int64_t windows = (dest_count + (1 << bits) - 1) >> bits;
     return ceil_log2(windows) <= 2 * kPermuteMaxBucketBits;
 }
 
 size_t permute_cursor_words(int64_t dest_count)
 {
     // level 1: at most 2^9 buckets; level 2 (or the only level): one cursor per window, padded to a power of two
-    const int64_t windows = (dest_count + (1 << kPermuteWindowBits) - 1) >> kPermuteWindowBits;
+    const int bits = permute_window_bits(dest_count);
+    const int64_t windows = (dest_count + (1 << bits) - 1) >> bits;
     return (size_t)(((int64_t)1 << kPermuteMaxBucketBits) + ((int64_t)1 << ceil_log2(windows)));
 }
 
 namespace {
-struct Geom { int lw, p1, p2; int64_t windows, tiles2; };
+struct Geom { int bits, lw, p1, p2; int64_t windows, tiles2; };
 Geom geom_of(int64_t dest_count)
 {
     Geom g;
-    g.windows = (dest_count + (1 << kPermuteWindowBits) - 1) >> kPermuteWindowBits;
+    g.bits = permute_window_bits(dest_count);
+    g.windows = (dest_count + (1 << g.bits) - 1) >> g.bits;
     g.lw = ceil_log2(g.windows);
     g.p2 = g.lw < kPermuteMaxBucketBits ? g.lw : kPermuteMaxBucketBits;
     g.p1 = g.lw - g.p2;
@@ -162,23 +155,20 @@ Geom geom_of(int64_t dest_count)
 }
 }  // namespace
 
-hipError_t permute_begin(const PermuteJob& J, PartEmit* first_level, hipStream_t st)
+void permute_begin(const PermuteJob& J, PartEmit* first_level)
 {
     const Geom g = geom_of(J.dest_count);
     uint32_t* const cursor1 = J.cursors;                                          // level 1's buckets
     uint32_t* const cursor2 = J.cursors + ((int64_t)1 << kPermuteMaxBucketBits);  // the windows
-    const int64_t words = ((int64_t)1 << kPermuteMaxBucketBits) + ((int64_t)1 << g.lw);
-    int64_t grid = (words / 4 + 255) / 256; if (grid < 1) grid = 1;
-    LAPLEX_TIMED("permute_zero", st, hipLaunchKernelGGL(k_zero_words, dim3((unsigned)grid), dim3(256), 0, st, J.cursors, words));
     PartEmit E;
+    E.clear = J.cursors; E.clear_words = ((int64_t)1 << kPermuteMaxBucketBits) + ((int64_t)1 << g.lw);
     E.out_dv = J.rec_dv[0]; E.out_v1 = J.rec_v1[0]; E.dest_count = J.dest_count;
     if (g.p1 > 0) {      // two levels: the first one fills 2^p1 buckets of 2^p2 windows each
         E.bucket_bits = g.p1; E.shift = kPermuteWindowBits + g.p2; E.region_shift = kPermuteWindowBits + g.p2; E.cursor = cursor1;
     } else {             // one level: straight into the windows
-        E.bucket_bits = g.p2; E.shift = kPermuteWindowBits; E.region_shift = kPermuteWindowBits; E.cursor = cursor2;
+        E.bucket_bits = g.p2; E.shift = g.bits; E.region_shift = g.bits; E.cursor = cursor2;
     }
     *first_level = E;
-    return hipGetLastError();
 }
 
 hipError_t permute_finish(const PermuteJob& J, hipStream_t st)
@@ -201,8 +191,10 @@ hipError_t permute_finish(const PermuteJob& J, hipStream_t st)
         else LAPLEX_TIMED(f1.c_str(), st, hipLaunchKernelGGL((k_part<1>), dim3((unsigned)g.tiles2), dim3(kPtThreads), 0, st, A));
         F.in_dv = J.rec_dv[1]; F.in_v1 = J.rec_v1[1];
     }
-    if (J.values == 2) LAPLEX_TIMED(f2.c_str(), st, hipLaunchKernelGGL((k_part_final<2>), dim3((unsigned)g.windows), dim3(kPtThreads), 0, st, F));
-    else LAPLEX_TIMED(f2.c_str(), st, hipLaunchKernelGGL((k_part_final<1>), dim3((unsigned)g.windows), dim3(kPtThreads), 0, st, F));
+    auto last = [&](auto kernel) { LAPLEX_TIMED(f2.c_str(), st, hipLaunchKernelGGL(kernel, dim3((unsigned)g.windows), dim3(kPtThreads), 0, st, F)); };
+    constexpr int B = kPermuteWindowBits;
+    if (g.bits == B) { if (J.values == 2) last(k_part_final<2, B>); else last(k_part_final<1, B>); }
+    else { if (J.values == 2) last(k_part_final<2, B - 1>); else last(k_part_final<1, B - 1>); }
     return hipGetLastError();
 }
 

@@ -2839,6 +2839,8 @@ k_seq_reduce(const ScanArgs A)
     const int64_t tile_base = tile * (kScanWaves * 64 * ITEMS);
     const int64_t wave_row0 = tile_base + (int64_t)wave * 64 * ITEMS;
     const int64_t row0 = wave_row0 + (int64_t)lane * ITEMS;
+    // (the records' cursors, which the downsweep needs at zero: a launch of its own took 5 us)
+    for (int64_t i = tile * (kScanWaves * 64) + tid; i < A.emit.clear_words; i += (int64_t)gridDim.x * (kScanWaves * 64)) A.emit.clear[i] = 0u;
     // from this row-lane's last row to the tile's last, and from its first row back to the tile's first: one exponential of
     // an anchor difference each (the tile's summary is the weighted sum of the row-lanes' own: see k_scan_reduce)
     const int64_t tile_end = tile_base + (int64_t)kScanWaves * 64 * ITEMS;

@@ -1080,3 +1080,36 @@ def test_one_column_in_order_with_a_wrong_promise():
         assert np.all(np.diff(v[np.argsort(pos)]) >= 0)
     finally:
         B.laplex_diag_set_route_min(1 << 22)
+
+
+@pytest.mark.parametrize("k,n", [((1 << 23) + 5, (1 << 23) + 9), ((1 << 25) + 3, (1 << 25) + 12345), ((1 << 28) + 11, (1 << 28) + 7777), (3 << 21, 1 << 20), ((1 << 22) + 1, 5)])
+def test_one_column_every_output_at_large_sizes(k, n):
+    """Batch 1 beyond what an oracle on the host can check output by output: tiles of 16384 (beyond 2^24 positions), more than 64 chunks of them (2^26), units of 8192 pairs (2^29), windows of
+    8192 and 16384.  Anchors are distinct floats from 2^30 on, 128 and more apart, so that a weight is one or nothing, and an output is its tied input, or zero."""
+    import gc
+    gc.collect(); torch.cuda.empty_cache()
+    gen = torch.Generator(device="cuda"); gen.manual_seed(k)
+    m = max(k, n)
+    first = 0x4E800000                                       # 2^30
+    at_a, at_b = (torch.randperm(m, generator=gen, device="cuda", dtype=torch.int32)[:s] for s in (k, n))
+    a, b = ((v + first).view(torch.float32) for v in (at_a, at_b))
+    x, g = (torch.randn(s, 1, generator=gen, device="cuda") for s in (n, k))
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, 1), dtype=torch.uint8, device="cuda")
+    y, gx, ga, gb = torch.empty_like(g), torch.empty_like(x), torch.empty_like(a), torch.empty_like(b)
+    for flags in (B.LAPLEX_SAVE_SCANS, 0):
+        B.laplex_apply(a, b, x, y, ws, flags)
+        B.laplex_apply_backward(a, b, x, g, gx, ga, gb, ws, flags | B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+        of = torch.zeros(m, device="cuda")
+        of[at_b] = x[:, 0]
+        assert torch.equal(y[:, 0], of[at_a])
+        of.zero_(); of[at_a] = g[:, 0]
+        assert torch.equal(gx[:, 0], of[at_b])
+        assert not bool(ga.any()) and not bool(gb.any())
+        y.fill_(float("nan")); gx.fill_(float("nan")); ga.fill_(float("nan")); gb.fill_(float("nan"))
+        del of
+
+
+def test_one_column_bucket_of_many_pieces(oracle):
+    """A bucket of more pieces than a workgroup has threads (512 in the sort, 256 where values move): its stretches that would fit LDS are handled in memory, too."""
+    test_sort_in_two_distributions(oracle, 2500000, 2300000, "unsampled", 0)
