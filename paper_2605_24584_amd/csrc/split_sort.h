@@ -284,24 +284,25 @@ constexpr uint32_t kSplitSmallGroup = 16;     // pairs that a bin may hold and s
 template <int THREADS>
 struct StretchShared {
     uint32_t sums[THREADS / 64];
-    uint32_t key_and, key_or, key_min, key_max, id_min, id_max, big;
-    __device__ __forceinline__ void init() { key_and = 0xFFFFFFFFu; key_or = 0u; key_min = 0xFFFFFFFFu; key_max = 0u; id_min = 0xFFFFFFFFu; id_max = 0u; big = 0u; }
+    uint32_t key_and, key_or, key_min, key_max, id_min, id_max, big, quantum;
+    __device__ __forceinline__ void init() { key_and = 0xFFFFFFFFu; key_or = 0u; key_min = 0xFFFFFFFFu; key_max = 0u; id_min = 0xFFFFFFFFu; id_max = 0u; big = 0u; quantum = 0xFFFFFFFFu; }
 };
 
 // A pair's bin.  Where the range has far more keys than pairs, by the anchor itself, as evenly spread inside a stretch as any function of the key
-// (near zero the key is not); else by 32 bits of its place in the range: those of (key - smallest key) without the low bits that no key differs in, and
+// (near zero the key is not), and by the id behind it where the anchors are on a grid and near zero; else by 32 bits of its place in the range: those of (key - smallest key) without the low bits that no key differs in, and
 // behind them the upper bits of the id, as far as there is room, scaled so that the range fills the bins.  Never decreasing in (key, id), also
 // where the range ends in an anchor that is not finite: no number goes into the last bin.
 struct StretchBins {
     uint32_t kmin, mult, last, id_mask;
-    float pmin, scale;
+    float pmin, scale, per_quantum, per_id;
     int low_zeros, key_up, id_down, id_up;
-    bool by_value;
+    bool by_value, by_quantum;
     __device__ __forceinline__ StretchBins(uint32_t kmin_, uint32_t kmax, uint32_t vary, int id_bits, int cnt, int bins)
         : kmin(kmin_), last((uint32_t)bins - 1u), low_zeros(vary ? __ffs((int)vary) - 1 : 0)
     {
         const uint32_t span = (kmax - kmin_) >> low_zeros;
         by_value = span >> 4 >= (uint32_t)cnt;
+        by_quantum = false; per_quantum = per_id = 0.0f;
         pmin = split_key_to_float(kmin_);
         scale = (float)bins / (split_key_to_float(kmax) - pmin);
         const int room = span ? __clz((int)span) : 32;
@@ -312,10 +313,31 @@ struct StretchBins {
         const float top = (float)(span << key_up | (room ? 0xFFFFFFFFu >> (32 - room) : 0u)) + 1.0f;        // at most 2^32, at least 2^31
         mult = (uint32_t)((float)bins * (4294967296.0f / top) * 0.999999f);
     }
+    // Equal anchors of a grid near zero, where one step of it is many times as many keys as elsewhere in the range: by the anchor, and by the id up to the next multiple
+    // of 2^(quantum - 150).
+    __device__ __forceinline__ bool may_have_quantum(uint32_t kmax) const
+    {
+        const int from = (int)(__float_as_uint(pmin) >> 23), to = (int)(__float_as_uint(split_key_to_float(kmax)) >> 23);      // (signs: 256 apart)
+        return low_zeros >= 8 && (from - to > 1 || to - from > 1);
+    }
+    __device__ __forceinline__ static uint32_t quantum_of(uint32_t key)
+    {
+        const uint32_t u = __float_as_uint(split_key_to_float(key)), e = (u >> 23) & 255u, m = (u & 0x7FFFFFu) | (e ? 0x800000u : 0u);
+        return m ? (e ? e : 1u) + (uint32_t)__ffs((int)m) - 1u : 0xFFFFFFFFu;
+    }
+    __device__ __forceinline__ void set_quantum(uint32_t quantum, uint32_t kmax, int id_bits, int bins)
+    {
+        per_quantum = ldexpf(1.0f, quantum < 277u ? 150 - (int)quantum : -127);
+        const float quanta = (split_key_to_float(kmax) - pmin) * per_quantum;
+        by_quantum = quanta < 4194304.0f;               // (else, or not a number: the ids would be lost behind so many)
+        per_id = ldexpf(1.0f, -id_bits);
+        if (by_quantum) scale = (float)bins / (quanta + 1.0f);
+    }
     __device__ __forceinline__ uint32_t of(uint32_t key, uint32_t id) const
     {
         uint32_t b;
-        if (by_value) b = (uint32_t)fminf((split_key_to_float(key) - pmin) * scale, 65535.0f);      // uniform
+        if (by_quantum) b = (uint32_t)fminf(__builtin_fmaf(split_key_to_float(key) - pmin, per_quantum, (float)id * per_id) * scale, 65535.0f);      // uniform
+        else if (by_value) b = (uint32_t)fminf((split_key_to_float(key) - pmin) * scale, 65535.0f);      // uniform
         else b = __umulhi((((key - kmin) >> low_zeros) << key_up) | (((id >> id_down) << id_up) & id_mask), mult);
         return b < last ? b : last;
     }
@@ -364,7 +386,17 @@ __device__ __forceinline__ void stretch_ranks(uint32_t (&key)[ITEMS], uint32_t (
     if (tid == 0) known(S.key_min, S.key_max);
     uint32_t seg[ITEMS];                        // first slot and size (upper half) of the group the pair belongs to (rank: its place there)
     {
-        const StretchBins B(S.key_min, S.key_max, S.key_or, id_bits, cnt, 4 * words);
+        StretchBins B(S.key_min, S.key_max, S.key_or, id_bits, cnt, 4 * words);
+        if (B.may_have_quantum(S.key_max)) {             // uniform
+            uint32_t q = 0xFFFFFFFFu;
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+                if (i * THREADS < cnt) q = lesser(q, StretchBins::quantum_of(key[i]));
+            q = wave_fold(q, 0xFFFFFFFFu, lesser);
+            if (lane == 63) atomicMin(&S.quantum, q);
+            __syncthreads();
+            B.set_quantum(S.quantum, S.key_max, id_bits, 4 * words);
+        }
         bool over = false;
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) {

@@ -22,7 +22,8 @@
 // keys): 9000 positions 20 / 22, 2^17: 25 / 27, 4 10^5: 32 / 50, 2^19 + 1: 33 / 65, 2^20 + 1024: 40 / 81, 2^21: 56 / 105, 3 2^20: 79 / 131,
 // 4 10^6: 105 / 145.  Bins four to a word, the anchor itself as the place where the range is wide, no bank conflicts in the search among the bounds (before: two bins to a
 // pair, a 64-bit place of key and id): the last kernel 38 -> 32 us at 2^21 positions, the tiles 16 -> 13; 2^19 x 2^19 with normal anchors, batch 8, forward +
-// backward 215 -> 209, the weighted Gram matrix of 1024 over 2^20 69.1 -> 67.6; 2^17 x 2^17 on a grid 98 -> 100, where the stretch around zero is counted once more.
+// backward 215 -> 209, the weighted Gram matrix of 1024 over 2^20 69.1 -> 67.6.  Near zero the stretches of a grid are counted by the multiple and the id instead of once
+// more (a product with batch 1, 32 equal anchors to a value: 20000 positions 42.0 -> 40.0, 65537: 45.0 -> 40.2, 200000: 53.5 -> 46.4, 2^21: 124 -> 116).
 #include "split_sort.h"
 
 namespace laplex {
@@ -398,7 +399,7 @@ namespace {
 // in memory there (count_in_memory: 58 us more at 2^21).  Tiles: the fewest keys that still make at most 512 of them.
 // Up to 2^17 positions, where stretches are far fewer than the device has room for, they are short and taken by more threads than they need, and
 // half the samples do, since the capacity is four and more times the average (us for the whole sort, 1024 pairs by 256 threads, 16 samples
-// each / now; uniform and grid anchors: 20000 21.0 / 19.7, 26.0 / 23.3; 65536 22.2 / 20.8, 28.0 / 23.7; 131072 24.3 / 22.7, 29.6 / 26.3).  Beyond, half the samples leave
+// each / now: 20000 21.0 / 19.7; 65536 22.2 / 20.8; 131072 24.3 / 22.7).  Beyond, half the samples leave
 // longer longest stretches, which is what the sort waits for (2^19: 33 / 39; 2^20: 39 / 44).
 struct SplitGeom { int per, threads, group_bits; int64_t tile, tiles, buckets, samples; };
 constexpr int kTileThreads = 1024;

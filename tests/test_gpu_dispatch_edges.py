@@ -1113,3 +1113,19 @@ def test_one_column_every_output_at_large_sizes(k, n):
 def test_one_column_bucket_of_many_pieces(oracle):
     """A bucket of more pieces than a workgroup has threads (512 in the sort, 256 where values move): its stretches that would fit LDS are handled in memory, too."""
     test_sort_in_two_distributions(oracle, 2500000, 2300000, "unsampled", 0)
+
+
+@pytest.mark.parametrize("kind", ["from_zero", "both_sides", "subnormal", "wide", "not_finite"])
+@pytest.mark.parametrize("N", [9000, 65536, 100000, 600000, 5000000])
+def test_sample_sort_grid_near_zero(N, kind):
+    """Some 32 equal anchors to a multiple of 1/4 (of 2^-140; beside 2^60; beside anchors that are not finite), zero among them: the stretches where a step of the grid is many
+    times as many keys as elsewhere are counted by the multiple and the id.  The order is numpy's stable one."""
+    r = np.random.default_rng(N + len(kind))
+    v = np.round(r.uniform(0 if kind in ("from_zero", "subnormal") else -N / 256, N / 128, N) * 4)
+    v = (v * (2.0 ** -140 if kind == "subnormal" else 0.25)).astype(np.float32)
+    if kind == "wide": v[::7] = 2.0 ** 60; v[1::11] = -2.0 ** -60
+    if kind == "not_finite": v[::500] = np.inf; v[1::700] = -np.inf
+    v += 0.0          # (-0.0 sorts as 0.0)
+    k = N // 3
+    ids, _ = sorted_ids(v[:k], v[k:])
+    assert np.array_equal(ids.view(np.uint32), np.argsort(v, kind="stable").astype(np.uint32))
