@@ -532,6 +532,10 @@ struct SmallArgs {
     int64_t batch; int cols;                   // cols: set by the launcher, power of two <= 16
     int nprob; SmallProblem prob[2];
 };
+// Counting ranks takes N / 32 workgroups per operator, sorting each operator in a workgroup of its own 12 to 19 us whatever their number
+// (us, ranks / sort, events around the launch: 16 x 1000 positions 13 / 14, 16 x 2000 21 / 15, 40 x 1000 26 / 14, 400 x 300 60 / 14,
+// 4 x 4000 15 / 17, 2 x 8000 19 / 22, 3 x 6000 22 / 20).
+inline bool mix_ranked(int64_t r, int64_t N) { return N <= kSmallMax && r * N <= 17000; }
 // Whether launch_small forms products pair by pair from the anchors, beside the sort instead of after it (0: no), and in how many slabs of columns;
 // k, n: outputs and inputs (Gram form: n twice); transposed: the product with the transposed matrix (results at the inputs), and the Gram form's.
 int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators, bool transposed);

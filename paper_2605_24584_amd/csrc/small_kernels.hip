@@ -290,7 +290,11 @@ __device__ __forceinline__ void small_pairs(const SmallArgs& A, const SmallProbl
     const int64_t col = col0 + c;
     const bool ok = rr < res && col < A.batch;
     double ps = 0.0, zs = 0.0;
-    for (int q = 0; q < splits; ++q) { ps += L.part[q][row][c][0]; zs += L.part[q][row][c][1]; }
+#pragma unroll
+    for (int q = 0; q < kPairSplits; ++q) {          // (all are read at once, also what no wavefront wrote)
+        const double pq = L.part[q][row][c][0], zq = L.part[q][row][c][1];
+        ps += q < splits ? pq : 0.0; zs += q < splits ? zq : 0.0;
+    }
     const float pv = (float)ps, zv = (float)zs;
     if (ok && P.out_p) (P.out_p + op * P.op_p)[(int64_t)rr * P.ld_p + col] = pv;
     if (STRICT && ok && P.out_z) (P.out_z + op * P.op_z)[(int64_t)rr * A.batch + col] = zv;
@@ -571,7 +575,8 @@ static int pair_columns(int64_t batch) { return batch >= 5 ? 8 : batch >= 3 ? 4 
 //   workgroups  One of up to 8 (16) result rows takes its 3 to 5 us of launch, loads, barriers and sums over lanes however few injected rows there are.
 //               A compute unit holds one of 1024 threads at a time (8 columns with strict sums, 85 registers) or two: more than 256 in one launch queue up.
 //   stages      of injected rows of several columns: each waits for its loads
-//   ranks       of many operators, which share the compute units with the pairs
+//   ranks       of many operators, which share the compute units with the pairs (so many that they are sorted in a launch before: one column is no worse off then, seven of
+//               15 x 4361 25.1 / 21.5)
 // A backward pass has its plan: its transposed product is formed pair by pair only where the forward product, of the opposite shape, is as well and
 // has saved the time; the Gram form's, which goes with its forward, like the transposed one (beside scans in the forward, 1089 x 9, batch 9, forward + backward 31.2 / 33.6 us; 794 x 2405, batch 8 33.6 / 40.3).
 // Measured (us, ranks, then scans / pair by pair; forward, forward on a kept plan, forward + backward): n = k = 4096, batch 1 24.2 / 14.6, 11.2 / 9.9, 41.9 / 29.8; 1986 x 121, batch 1
@@ -588,8 +593,9 @@ constexpr PairLimits kPairLimits[4] = {      // one slab of 1, 2, 4, 8 columns
 constexpr PairLimits kPairLimitsSlabs = {7e7, 2.5e7, 2 * kPairStage, 352};
 constexpr int64_t kPairAtOnce = 256;                    // workgroups of 8 columns
 constexpr double kPairCostQueued = 1.5e7;               // ... and what more of them may cost
-constexpr double kPairCostSlabsBackward = 2.5e7;
+constexpr double kPairCostSlabsBackward = 2.5e7, kPairCostOperatorsBackward = 4e7;
 constexpr int64_t kPairWorkgroupsOperators = 300, kPairRankedOperators = 12000;
+constexpr double kPairCostBeside = 3e8, kPairCostRanked = 1.5e7;      // one column, ranks beside it: shared by the operators; beside more ranks than that
 static double pair_cost(int64_t k, int64_t n, int cols, int64_t slabs, int64_t operators)
 {
     return (double)k * (double)n * (double)(slabs * operators) * (12.0 + 2.0 * cols);
@@ -606,7 +612,11 @@ static bool pairs_pay(int64_t results, int64_t injected, int cols, int64_t slabs
     const int64_t workgroups = pair_workgroups(results, cols, slabs, operators);
     if (injected > M.injected || workgroups > M.workgroups || cost > M.cost) return false;
     if (cols == 8 && workgroups > kPairAtOnce && cost > kPairCostQueued) return false;
-    return operators == 1 || ((cols == 8 || workgroups <= kPairWorkgroupsOperators) && operators * (results + injected) <= kPairRankedOperators && cost <= M.cost_operators);
+    if (operators == 1) return true;
+    if (cols < 8 && workgroups > kPairWorkgroupsOperators) return false;
+    const bool beside = mix_ranked(operators, results + injected), many = operators * (results + injected) > kPairRankedOperators;
+    if (cols > 1) return !many && cost <= M.cost_operators;
+    return cost <= (!beside ? M.cost_operators : many ? kPairCostRanked : kPairCostBeside / (double)operators);
 }
 int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators, bool transposed)
 {
@@ -616,7 +626,8 @@ int small_pairwise(int64_t k, int64_t n, int64_t batch, int64_t operators, bool 
     if (transposed) {
         if (!pairs_pay(n, k, cols, slabs, operators)) return 0;
         if (cols == 8 && pair_workgroups(k > n ? k : n, cols, slabs, operators) > kPairAtOnce) return 0;
-        if (slabs > 1 && pair_cost(k, n, cols, slabs, operators) > kPairCostSlabsBackward) return 0;
+        const double cost = pair_cost(k, n, cols, slabs, operators);
+        if ((slabs > 1 && cost > kPairCostSlabsBackward) || (operators > 1 && cost > kPairCostOperatorsBackward)) return 0;
     }
     return (int)slabs;
 }

@@ -959,10 +959,11 @@ def test_which_small_problems_go_pair_by_pair(oracle, k, n, batch, forward, back
 
 @pytest.mark.parametrize("r,k,n,batch,forward,backward", [
     (16, 100, 39, 1, True, True), (2, 2300, 582, 1, True, True), (8, 632, 944, 1, False, False), (12, 15, 1640, 9, False, False), (6, 143, 87, 9, True, True),
-    (16, 100, 900, 8, False, False), (16, 10, 600, 32, True, False), (4, 7, 300, 9, True, False), (16, 10, 1100, 8, False, False),
+    (16, 100, 900, 8, False, False), (16, 10, 600, 32, True, False), (4, 7, 300, 9, True, False), (16, 10, 1100, 8, False, False), (16, 10, 1100, 1, True, False),
+    (12, 328, 878, 1, False, False), (10, 6, 1554, 1, True, False),      # one column, beside 14000 and 15000 ranks: many and few pairs
 ])
 def test_which_small_sums_go_pair_by_pair(oracle, r, k, n, batch, forward, backward):
-    """The same for sums of operators; those sorted by samples in a launch of their own (more than 17000 anchors) are never among them."""
+    """The same for sums of operators; those sorted by samples in a launch of their own (more than 17000 anchors) only with one column."""
     from test_gpu_parity import assert_close
     q = np.random.default_rng(r + k + n)
     a, b = (np.round(q.uniform(0, (k + n) / 64, (r, s)) * 8).astype(np.float32) / 8 for s in (k, n))
