@@ -822,6 +822,10 @@ struct DeepScratch {
 // forward + backward: 1258292 x 2936012 77.9 / 72.5, 220 / 206, 323 / 306; 2^22 x 2^22 116 / 114, 351 / 328, 536 / 514; Gram form of 10^7 252 / 246, 497 / 474, 907 / 886;
 // 2^23 x 2^23 211 / 211, 573 / 563, 914 / 910), but not where runs get short (2^24 x 2^24 forward + backward 1842 / 1857; 2^25 x 2^25 forward 2001 / 2057).
 constexpr int64_t kDeepSmallTilesMax = int64_t(1) << 24;
+// Stretches longer than a workgroup sorts in LDS, expected per sort of anchors without ties (a stretch's length is a sum of samples_per gaps between samples, so a Gamma variable): 1e-3
+// at 2^28 positions, 0.05 at 2^29 (five samples a stretch), 1e-4 at 2^30, 98 at 2^31 (four samples, 2048 pairs on average), 3700 at 3e9 and 44000, 4.2 %, at 2^32.  A workgroup sorts such a
+// stretch in memory.  At 2^31 they hide among the other units; the largest problems wait for them: forward + backward 106 ms for 2^30 x 2^30 (the sort of the units 19), 162 for
+// 1.5e9 x 1.5e9 (39) and 417 for 2147483647 x 2147483647 (199, and 27 instead of 7 a move).
 DeepGeom deep_geom(int64_t N)
 {
     DeepGeom G;

@@ -585,7 +585,7 @@ __device__ __forceinline__ void emit_row_sums(float (&acc)[ITEMS], uint32_t (&ro
 #pragma unroll
             for (int i = 0; i < half; ++i) {
                 // (values, not elements, are chosen: an array of which an element is chosen by address lies in scratch or LDS; 2999 x 100003, batch 33,
-                // forward + backward: 122.5 -> 119.6 us, 2^20 x 2^20, batch 8: 347 -> 344.5)
+                // forward + backward: 122.5 -> 119.6 us, 2^20 x 2^20, batch 8: 350.9 -> 349.9)
                 const float a0 = acc[i], a1 = acc[i + half];
                 const uint32_t r0 = rows[i], r1 = rows[i + half];
                 const float mine = upper ? a1 : a0, other = upper ? a0 : a1;

@@ -153,8 +153,8 @@ struct StretchRange {
     }
 };
 
-// A stretch beyond the capacity (the samples bound its length with a chance of up to 1e-3 per sort, see split_geom): the workgroup sorts it
-// in memory.  from: cnt pairs; to_id, to_pk: the stretch's place in the plan.  Leaves the pairs in from.
+// A stretch beyond the capacity (split_geom's samples leave a chance of up to 1e-3 per sort that there is one; for the many more stretches of
+// a sort in two distributions see deep_geom): the workgroup sorts it in memory.  from: cnt pairs; to_id, to_pk: the stretch's place in the plan.  Leaves the pairs in from.
 //
 // First by the count that sorts a stretch in LDS: bins of the pairs' places in the range, the pairs laid out bin by bin, and every pair
 // ranked among its bin's; false, and the pairs as they were, where a bin holds too many for that.  lds: 2 * CAP words, part: THREADS / 64.

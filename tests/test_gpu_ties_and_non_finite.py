@@ -140,6 +140,29 @@ def test_non_finite_rows_reach_every_row(k, n, batch, bad):
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n,batch", [(9000, 1), (9000, 8), (8193, 9), (9001, 33), (20000, 64), (30011, 128), (9000, 130), (300, 16)])
+def test_gram_non_finite_rows_reach_every_row(n, batch, bad):
+    """The same for the Gram form: one row of x or gy shows in its column of y or gx, and through either scan in every anchor's gradient (9 to 128 columns of more than 8192 rows: x
+    is scanned again beside gy, from the states that the forward kept)."""
+    q = np.random.default_rng(n + batch)
+    b = dev(q.uniform(0, 3000, n).astype(np.float32))
+    x, g = (q.normal(size=(n, batch)).astype(np.float32) for _ in "xg")
+    col = batch // 2
+    ws = torch.empty(B.laplex_workspace_bytes(0, n, batch), dtype=torch.uint8, device="cuda")
+    for side in ("x", "gy"):
+        for save in (B.LAPLEX_SAVE_SCANS, 0):
+            dx, dg = dev(x), dev(g)
+            (dx if side == "x" else dg)[q.integers(0, n), col] = bad
+            y, gx, ga = torch.zeros(n, batch, device="cuda"), torch.zeros(n, batch, device="cuda"), torch.zeros(n, device="cuda")
+            B.laplex_gram(b, dx, y, ws, save)
+            B.laplex_gram_backward(b, dx, dg, gx, ga, ws, save | B.LAPLEX_REUSE_PLAN)
+            torch.cuda.synchronize()
+            assert_all_non_finite("ga", ga)
+            assert_all_non_finite("y" if side == "x" else "gx", y if side == "x" else gx, col)
+            assert bool(torch.isfinite(gx if side == "x" else y).all())
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("r,k,n,batch", [(2, 3000, 7000, 1), (2, 7000, 3000, 33), (3, 5000, 5000, 64), (2, 300, 400, 8), (4, 33000, 33000, 2)])
 def test_mix_non_finite_rows_reach_every_row(r, k, n, batch, bad):
     """The same for sums of operators, on each of their routes."""
