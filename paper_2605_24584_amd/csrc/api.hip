@@ -131,8 +131,10 @@ Plan plan_of(const Layout& L, char* ws)
 // ----------------------------------------------------------------------------
 // Batch 1 with many rows: x and gy reach the sorted order along the passes of the sort (deep_sort_kernels.hip), and the results the
 // caller's order as records through partition passes (permute_kernels.hip), instead of by one random access per value.  Below
-// g_permute_min merged positions the tables fit the device's caches and the random accesses are as fast (us, routed / gathered, n = k,
-// forward + backward: 2^20 260 / 208, 2^20.5 301 / 303, 2^21 329 / 379, 2^22 516 / 732; forward alone: 2^20.5 208 / 170, 2^21 225 / 222, 2^21.3 255 / 331).
+// g_permute_min merged positions the tables fit the device's caches and the random accesses are as fast (us, routed / gathered, n = k: forward
+// on a kept plan, forward, forward + backward: 2^20 53 / 62, 157 / 118, 233 / 207; 2^20.5 64 / 95, 185 / 172, 270 / 305; 2^21 70 / 115, 202 / 223,
+// 300 / 381; 2^22 112 / 209, 316 / 451, 505 / 736).  The line is that of n = k, where a new plan alone decides: the Gram form would gain from fewer rows on,
+// between 2^21 (58 / 89, 164 / 145, 245 / 278) and 2^21.25 (69 / 124, 179 / 198, 274 / 387), and has no line of its own yet.
 // ----------------------------------------------------------------------------
 std::atomic<int64_t> g_permute_min{int64_t(1) << 22};
 

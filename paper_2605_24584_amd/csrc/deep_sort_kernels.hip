@@ -24,11 +24,11 @@
 // would have to leave most of it free.
 //
 // What bounds it: memory traffic in the tiles (10 bytes a pair, 3.8 TB/s), latency elsewhere: a workgroup passes eight to twelve barriers with
-// loads and LDS atomics in between, two or three workgroups a compute unit (16 bytes a pair in the pieces, 3.5 TB/s, 23 in the sort, 3.2).
+// loads and LDS atomics in between, two or three workgroups a compute unit (16 bytes a pair in the pieces, 3.6 TB/s, 23 in the sort, 3.2).
 //
 // Measured (MI355X, us, before / now; before: four radix passes with chained look-back, histogram, a decay pass, the inverse permutation by
 // partition passes of (id, position), and values in as (rank, value) records): the plan of 2^28 positions 7720 / 4080, a move of 2^27 values into their
-// order 1350 / 1050; forward + backward at 2^27 x 2^27 17115 / 12850, 2^24 x 2^24 with 32 equal anchors a value 2451 / 1841, 2^22 x 2^22 574 /
+// order 1350 / 1050; forward + backward at 2^27 x 2^27 17115 / 12776, 2^24 x 2^24 with 32 equal anchors a value 2451 / 1829, 2^22 x 2^22 574 /
 // 515.  Anchors that are promised to arrive in order are merged, not sorted (move_in_order, below).  The workspace is 26 % smaller.  What was tried and did not pay: units of stretches with three times the
 // pairs (LDS for the longest, a third filled): 5090 us for the sort of 2^28 pairs in place of 1893; 1024 threads of 4 pairs 2254, 256 of 16 2092.
 #include "split_sort.h"

@@ -1886,9 +1886,9 @@ k_scan_down(const ScanArgs A)
 // ---------------------------------------------------------------------------
 // ga_m = sum_t (gy Z^x + x Z^g)[m, t] needs the strict scans of both matrices.  Those of x are not kept by the forward (a matrix written there,
 // scattered, and gathered again here): only the states that enter its blocks are, and the rows of x, which are read here in any case, are walked before
-// those of gy, their strict scans held in LDS.  Bound by the gathered rows and by its own latency: 2.4 GB at n = 3 x 2^20, batch 64 (gy and x read,
-// gx written) in 649 us, where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
-// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1430 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 449 us;
+// those of gy, their strict scans held in LDS.  Bound by the gathered rows and by its own latency: 2.62 GB by the counters at n = 3 x 2^20, batch 64 (gy
+// and x read, gx written: 2.45) in 650 us (637 to 900 over the launches of a run: the first twenty are the slow ones), where the downsweep that gathers the kept scans too takes 671 us for 3.2 GB; what is won is the forward's half of
+// them: its downsweep 500 -> 328 us, forward and backward 1635 -> 1440 us.  n = 10^6, batch 12 and 31: 422 -> 337, 592 -> 449 us;
 // n = 300001, batch 128: 388 -> 348 us; n = 10^5, batch 64: 127 -> 126 us.
 // A block has the rows of k_scan_down's, as eight wavefronts with four rows a row-lane instead of four with eight: 128 registers, two
 // workgroups to a compute unit.  Registers are what decides it: both matrices in one walk 1315 us (50 registers in scratch, which is memory
