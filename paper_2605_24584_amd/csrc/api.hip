@@ -1579,6 +1579,20 @@ int laplex_diag_set_plan_status(void* ws, size_t ws_bytes, int64_t count, uint32
     return LAPLEX_OK;
 }
 
+int laplex_diag_set_wait_limit(void* ws, size_t ws_bytes, int64_t count, uint32_t polls, laplex_stream_t stream)
+{
+    if (count <= kSmallMax || count > LAPLEX_MAX_MERGED) return LAPLEX_ERR_SIZE;
+    if (!ws) return LAPLEX_ERR_NULL;
+    if (misaligned(ws, 256)) return LAPLEX_ERR_ALIGN;
+    const Layout L = make_layout(count, 0, 1);          // the plan's offsets depend on the merged length only
+    if (ws_bytes < L.off_counters + sizeof(uint32_t) * 64) return LAPLEX_ERR_WORKSPACE;
+    const uint32_t value = polls + 1u;
+    float bits;
+    __builtin_memcpy(&bits, &value, sizeof(bits));
+    LAPLEX_HIP(launch_fill(reinterpret_cast<float*>(static_cast<char*>(ws) + L.off_counters) + kWaitWord, 1, 1, 1, bits, stream));
+    return LAPLEX_OK;
+}
+
 int laplex_diag_set_route_min(int64_t merged_positions)
 {
     if (merged_positions < 0) return LAPLEX_ERR_SIZE;

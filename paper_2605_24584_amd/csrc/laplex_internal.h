@@ -61,6 +61,8 @@ constexpr int kScanCounters = 3;
 constexpr int kNonFiniteWord = 2;
 constexpr int kPlanIndexWord = 33;                      // nonzero: what the common launches of a sum of operators add to the plan is there (kMixIndexed + operators)
 constexpr int kStrictOrderWord = 34;                    // nonzero: the saved strict scans lie in the sorted order (ScanProblem::z_in_order)
+constexpr int kWaitWord = 35;                           // nonzero: blocks that wait for each other's summaries poll this often, less one (tests)
+constexpr int kGateWord = 36;                           // and the next: the gate of the scans in one launch (OneLaunch)
 constexpr int kPlanStatusWord = 32;                     // in the plan's 64 counter words: the sort's error flag, kept with the plan
 constexpr int kMergeThreads = 256;
 constexpr int kMergePerThread = 8;

@@ -52,6 +52,12 @@ struct Level {            // summaries of one level (tiles, or chunks of tiles) 
     int64_t count;
 };
 
+// A scan whose blocks publish their summaries and add up each other's, in one launch (see "one launch" below).
+struct OneLaunch {
+    uint32_t* gate = nullptr;     // null: not so; [0] arrivals, zero between scans; [1] another number after each scan, odd if a summary was not finite
+    int stage_kept = 0;           // the injected rows in sorted order are wanted after the scan
+};
+
 struct ScanArgs {
     const uint32_t* ids; const float* dh; const float* pk; int64_t N;
     const float2* pk8;                   // (pk[8m], pk[8m + 1]), or null
@@ -90,6 +96,7 @@ struct ScanArgs {
     const float* pair_car_f; const float* pair_car_e;      // carries of a second matrix, x, scanned beside the injected one (k_scan_down_pair), or null
     int keep_carries;             // 1: the carries stay where l1 has them and no strict value is written; 2: and there is no downsweep
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
+    OneLaunch one;                // one.gate: the downsweep forms the blocks' summaries and carries itself (k_scan_down<..., ONE>)
     PhaseFuse ph;                 // ph.half != 0: the phased backward's streaming downsweep merges the two halves itself
     PhaseIn pin;                  // pin.half != 0: the injected matrix (or the weights) is x modulated by its rows' phases
 };
@@ -432,16 +439,16 @@ __device__ __forceinline__ void load_weights(const ScanArgs& A, const TileRows<V
 }
 
 // LDS exchange of per-wavefront summaries: [dir][wave] scalars and [dir][wave][column] vectors.
-template <int VEC>
+template <int VEC, int WAVES = kScanWaves>
 struct WaveSegs {
-    float D[2][kScanWaves], C[2][kScanWaves];
-    int H[2][kScanWaves];
-    float S[2][kScanWaves][64 * VEC];
-    float Q[2][kScanWaves][64 * VEC];
+    float D[2][WAVES], C[2][WAVES];
+    int H[2][WAVES];
+    float S[2][WAVES][64 * VEC];
+    float Q[2][WAVES][64 * VEC];
 };
 
-template <int VEC, bool STRICT>
-__device__ __forceinline__ void put_wave_seg(WaveSegs<VEC>& W, int dir, int wave, int c, const Seg<VEC, STRICT>& s)
+template <int VEC, bool STRICT, int WAVES>
+__device__ __forceinline__ void put_wave_seg(WaveSegs<VEC, WAVES>& W, int dir, int wave, int c, const Seg<VEC, STRICT>& s)
 {
     if (c == 0) { W.D[dir][wave] = s.D; if (STRICT) { W.C[dir][wave] = s.C; W.H[dir][wave] = s.H; } }
 #pragma unroll
@@ -451,8 +458,8 @@ __device__ __forceinline__ void put_wave_seg(WaveSegs<VEC>& W, int dir, int wave
     }
 }
 
-template <int VEC, bool STRICT>
-__device__ __forceinline__ Seg<VEC, STRICT> get_wave_seg(const WaveSegs<VEC>& W, int dir, int wave, int c)
+template <int VEC, bool STRICT, int WAVES>
+__device__ __forceinline__ Seg<VEC, STRICT> get_wave_seg(const WaveSegs<VEC, WAVES>& W, int dir, int wave, int c)
 {
     Seg<VEC, STRICT> s;
     s.D = W.D[dir][wave];
@@ -1567,6 +1574,148 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 }
 
 // ---------------------------------------------------------------------------
+// one launch: the blocks of a downsweep publish their own summaries (what a reduce would leave) and add up each other's (what the
+// direct spine would leave), so that the injected rows are read once and nothing is launched in between.
+//
+// Bound by latency: a step of 2^16 x 2^16 at batch 8 takes 66 us so, 82 with three launches a scan, each of which waited for the ids, the rows
+// and the anchors anew (11 + 6 + 11 and 14 + 6 + 13 us beside some 3 between them; now 18 and 21: rows there after 4 us, summaries
+// after 8, published after 11, the others' added up after 15).  12000 to 160000 positions at batch 1, 3, 8, 16: 9 to 15 us less a step.
+//
+// What one workgroup writes for another to read in the same launch goes through relaxed agent-scope atomics, which pass by the chiplets'
+// own L2s; a summary is complete before the gate counts it (s_waitcnt).  The gate is one word that every block adds one to and one that
+// the last block changes.  No wait is without end: after a number of polls a block takes the other blocks' share from their
+// rows themselves (add_rows_of), so no order of dispatch and no number of resident workgroups is needed for a result, only for speed.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t load_now(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void store_now(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <int VEC>
+__device__ __forceinline__ void load_vec_now(float* dst, const float* src)
+{
+    if constexpr (VEC == 4) {
+        const unsigned long long* p = reinterpret_cast<const unsigned long long*>(src);
+        const unsigned long long a = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long b = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        dst[0] = __uint_as_float((uint32_t)a); dst[1] = __uint_as_float((uint32_t)(a >> 32));
+        dst[2] = __uint_as_float((uint32_t)b); dst[3] = __uint_as_float((uint32_t)(b >> 32));
+    } else {
+        dst[0] = __uint_as_float(load_now(reinterpret_cast<const uint32_t*>(src)));
+    }
+}
+template <int VEC>
+__device__ __forceinline__ void store_vec_now(float* dst, const float* src)
+{
+    if constexpr (VEC == 4) {
+        unsigned long long* p = reinterpret_cast<unsigned long long*>(dst);
+        auto two = [&](int e) { return (unsigned long long)__float_as_uint(src[e]) | (unsigned long long)__float_as_uint(src[e + 1]) << 32; };
+        __hip_atomic_store(p, two(0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 1, two(2), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        store_now(reinterpret_cast<uint32_t*>(dst), __float_as_uint(src[0]));
+    }
+}
+// Polls after which a block stops waiting (milliseconds; a wait lasts microseconds where the blocks are resident together).  The plan's
+// word kWaitWord, zero but in tests, gives another limit, less one.
+constexpr uint32_t kMaxPolls = 1u << 12;
+__device__ __forceinline__ uint32_t poll_limit(const uint32_t* counters) { return counters[kWaitWord] ? counters[kWaitWord] - 1u : kMaxPolls; }
+
+// F, E += the rows of block v themselves, decayed to the edge `at`.
+template <int VEC, bool SQ, bool RAG>
+__device__ __forceinline__ void add_rows_of(const ScanArgs& A, int64_t v, float at, int64_t col0, bool col_ok, float* F, float* E)
+{
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+    const int64_t j1 = (v + 1) * A.tile_rows < A.N ? (v + 1) * A.tile_rows : A.N;
+#pragma unroll 1
+    for (int64_t j = v * A.tile_rows; j < j1; ++j) {
+        const uint32_t id = A.ids[j];
+        const float p = A.pk[j + 1], w = expf(-fabsf(at - p));
+        const bool in = col_ok && id >= A.inj_lo && id < A.inj_hi;
+        float x[VEC];
+        load_row_or_zero<VEC, false, RAG>(x, A.inj, (int64_t)(id - A.inj_lo) * A.ld_inj + col0, in, end);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { const float y = in ? w * x[e] : 0.0f; F[e] += y; if (SQ) E[e] += p == at ? 0.0f : y; }
+    }
+}
+
+// F, E (R, G) += the published summaries of the `left` blocks before block t (of the `right` ones after it); this row-lane takes every
+// `step`-th from `rl` on, on either side at once (add_entries, but that a block's strict sum is only fetched where it ends at the edge's
+// key).  ready: every block has published.
+template <int VEC, bool SQ, bool RAG>
+__device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left, int right, int rl, int step, bool ready, bool read_all,
+                                              int64_t col0, bool col_ok, float* F, float* E, float* R, float* G)
+{
+    constexpr int kAhead = VEC == 4 ? 1 : 2;
+    const int SR = A.tile_rows, N = (int)A.N, count = (int)A.l1.count;
+    auto end_of = [&](int v) { const int64_t e = (int64_t)(v + 1) * SR; return e < A.N ? (int)e : N; };
+    const float at[2] = {A.pk[(int64_t)t * SR], A.pk[end_of(t) + 1]};
+    const int others[2] = {left, right};
+    auto block = [&](int dir, int o) { return dir == 0 ? t - 1 - o : t + 1 + o; };
+    bool more = true;
+#pragma unroll 1
+    for (int o0 = rl; more && (o0 < left || o0 < right); o0 += kAhead * step) {
+        float near_[2][kAhead], w[2][kAhead], S[2][kAhead][VEC];
+        uint32_t in = 0u;
+        float any = 0.0f;
+#pragma unroll
+        for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const int o = o0 + i * step, v = o < others[dir] ? block(dir, o) : t;
+                near_[dir][i] = A.pk[dir == 0 ? end_of(v) : v * (int64_t)SR + 1];
+            }
+#pragma unroll
+        for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const bool live = o0 + i * step < others[dir];
+                w[dir][i] = live ? expf(-fabsf(at[dir] - near_[dir][i])) : 0.0f;
+                in |= w[dir][i] != 0.0f || (read_all && live) ? 1u << (2 * i + dir) : 0u;
+                any += w[dir][i];
+            }
+        more = any != 0.0f || read_all;                      // (farther blocks are out of reach as well)
+        const uint32_t missing = ready ? 0u : in;            // blocks that may not have published
+        const uint32_t there = in & ~missing;
+#pragma unroll
+        for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const bool ok = col_ok && (there >> (2 * i + dir) & 1u);
+                load_vec_now<VEC>(S[dir][i], A.l1.s + (ok ? ((int64_t)dir * count + block(dir, o0 + i * step)) * A.bpad + col0 : 0));
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) S[dir][i][e] = ok ? S[dir][i][e] : 0.0f;
+            }
+#pragma unroll
+        for (int dir = 0; dir < 2; ++dir)
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const bool edge = near_[dir][i] == at[dir];
+                float Q[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) Q[e] = 0.0f;
+                if (SQ && edge && col_ok && (there >> (2 * i + dir) & 1u)) {      // (rare: a run of equal keys across blocks)
+                    const int v = block(dir, o0 + i * step);
+                    const float far = A.pk[dir == 0 ? (int64_t)v * SR : (int64_t)end_of(v) + 1];
+                    if (w[dir][i] != 0.0f && far != at[dir]) load_vec_now<VEC>(Q, A.l1.q + ((int64_t)dir * count + v) * A.bpad + col0);
+                }
+                float* const f = dir == 0 ? F : R;
+                float* const q = dir == 0 ? E : G;
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const float x = w[dir][i] * S[dir][i][e];
+                    f[e] += x;
+                    if (SQ) q[e] += edge ? Q[e] : x;
+                }
+            }
+        if (missing) {
+#pragma unroll 1
+            for (int i = 0; i < kAhead; ++i) {
+                if (missing >> (2 * i) & 1u) add_rows_of<VEC, SQ, RAG>(A, block(0, o0 + i * step), at[0], col0, col_ok, F, E);
+                if (missing >> (2 * i + 1) & 1u) add_rows_of<VEC, SQ, RAG>(A, block(1, o0 + i * step), at[1], col0, col_ok, R, G);
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // downsweep_sparse: tiles with result rows and nothing injected.  With no
 // injection inside the tile every row is a closed form of the two carries:
 //   F_j = cf_j F_in,           cf_j = product of the decays from the tile start to j
@@ -1671,26 +1820,32 @@ k_scan_down_sparse(const ScanArgs A)
 // WAVES: wavefronts of the workgroup (sizes the LDS buffer); RED: the row reduction is wanted (out_red);
 // ZS: the reduction takes in the saved strict scans (A.zs) -- without them the kernel fits in 128 registers
 // at scalar lanes, and a compute unit holds two workgroups of eight wavefronts instead of one.
-template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS, bool RAG>
-__global__ void __launch_bounds__(WAVES * 64)
+// ONE: no reduce and no spine have run (see "one launch" above).  1: the summaries have what STRICT asks for; 2: the strict sums too, and the carries
+// are kept (the Gram form's forward).  Up to 32 lanes across the batch, one slab.
+template <int VEC, bool STRICT, int WAVES, bool RED, bool ZS, bool RAG, int ONE>
+__global__ void __launch_bounds__(WAVES * 64, ONE ? 3 : 1)
 k_scan_down(const ScanArgs A)
 {
     constexpr int ITEMS = TileRows<VEC>::ITEMS;
     // One LDS buffer, used twice: first for the exchange of wavefront summaries, then (strict scans only)
     // for the per-row strict forward values, which would otherwise cost ITEMS * VEC registers per lane.
     constexpr size_t kEfBytes = STRICT ? sizeof(float) * ITEMS * WAVES * 64 * VEC : 0;
-    constexpr size_t kSmem = sizeof(WaveSegs<VEC>) > kEfBytes ? sizeof(WaveSegs<VEC>) : kEfBytes;
+    typedef WaveSegs<VEC, WAVES> Exchange;
+    constexpr size_t kSmem = sizeof(Exchange) > kEfBytes ? sizeof(Exchange) : kEfBytes;
     __shared__ __align__(16) unsigned char smem[kSmem];
-    WaveSegs<VEC>& W = *reinterpret_cast<WaveSegs<VEC>*>(smem);
+    Exchange& W = *reinterpret_cast<Exchange*>(smem);
     float* const ef = reinterpret_cast<float*>(smem) + (size_t)threadIdx.x * VEC;   // row i at ef[i * ef_stride]
     constexpr size_t ef_stride = (size_t)WAVES * 64 * VEC;
     if (A.every_block && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
-    if (A.down_from_list && blockIdx.x >= A.counters[1]) return;
-    const int64_t tile = A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
-    const int flags = (int)A.blk_flags[tile];
-    if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) {
-        if (A.every_block && (flags & kFlagRes)) sparse_block<VEC, STRICT, RAG>(A, tile);      // nothing injected
-        return;
+    constexpr bool SQ = STRICT || ONE == 2;           // strict sums are part of the summaries
+    if (!ONE && A.down_from_list && blockIdx.x >= A.counters[1]) return;
+    const int64_t tile = !ONE && A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
+    if constexpr (!ONE) {
+        const int flags = (int)A.blk_flags[tile];
+        if ((flags & (kFlagInj | kFlagRes | kFlagFewInj | kFlagFewRes)) != (kFlagInj | kFlagRes)) {
+            if (A.every_block && (flags & kFlagRes)) sparse_block<VEC, STRICT, RAG>(A, tile);      // nothing injected
+            return;
+        }
     }
     const uint32_t poison = plan_poison(A.counters);
 
@@ -1712,11 +1867,15 @@ k_scan_down(const ScanArgs A)
     const float enter_db = span_decay_b(A, rows_after, tile_base + A.tile_rows - rows_after);
     const bool enter_hf = span_head_f(A, tile_base, row0 - tile_base);
     const bool enter_hb = span_head_b(A, rows_after, tile_base + A.tile_rows - rows_after);
+    const int64_t tile_end = tile_base + A.tile_rows;
+    const float publish_wf = ONE ? span_decay_f(A, rows_after, tile_end - rows_after) : 0.0f, publish_wb = ONE ? span_decay_b(A, tile_base, row0 - tile_base) : 0.0f;
 
     TileRows<VEC> T;
     load_meta<VEC>(A, row0, T);
     float v[ITEMS][VEC];
-    if (A.stage) {      // uniform: the reduce left this tile's injected rows in sorted order (zeros elsewhere)
+    uint32_t gate_old = 0u;
+    if constexpr (ONE != 0) gate_old = load_now(A.one.gate + 1);
+    if (!ONE && A.stage) {      // uniform: the reduce left this tile's injected rows in sorted order (zeros elsewhere)
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i)
             load_vec_or_zero<VEC>(v[i], A.stage, (row0 + i) * A.batch + col0, col_ok && T.id[i] != 0xFFFFFFFFu);
@@ -1760,19 +1919,65 @@ k_scan_down(const ScanArgs A)
     // others, instead of one row ahead of their use, where each would be waited for in turn
     constexpr bool w_ahead = want_red && VEC == 1;
     float wall[w_ahead ? ITEMS : 1][VEC];
-    if (w_ahead) {
+    if (w_ahead && !ONE) {
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) fetch_row(i, wall[i]);
     }
 
     // carries into the block
     float Fc[VEC], Ec[VEC], Rc[VEC], Gc[VEC];
-    load_block_carries<VEC, STRICT>(A, tile, col0, col_ok, Fc, Ec, Rc, Gc);
+    if constexpr (!ONE) load_block_carries<VEC, STRICT>(A, tile, col0, col_ok, Fc, Ec, Rc, Gc);
     Seg<VEC, STRICT> fe, be;
-    {
-        Seg<VEC, STRICT> f = seg_identity<VEC, STRICT>();
+    constexpr int kHalf = 32 * VEC;                   // ONE: columns of a row, at most; the second half of the exchange holds the weighted sums
+    __shared__ int wave_flags[ONE ? WAVES : 1];
+    __shared__ float red[ONE ? (SQ ? 4 : 2) : 1][ONE ? WAVES : 1][ONE ? kHalf : 1];
+    __shared__ int gate_word;
+    if constexpr (ONE != 0) {
+        int mine = 0;
 #pragma unroll
-        for (int i = 0; i < ITEMS; ++i) seg_push<VEC, STRICT>(f, head_f<VEC>(T, i), T.dh[i], v[i]);
+        for (int i = 0; i < ITEMS; ++i) {
+            mine |= (T.id[i] >= A.inj_lo && T.id[i] < A.inj_hi) ? kFlagInj : 0;
+            mine |= (T.id[i] >= A.res_lo && T.id[i] < A.res_hi) ? kFlagRes : 0;
+        }
+        const int here = (__ballot(mine & kFlagInj) ? kFlagInj : 0) | (__ballot(mine & kFlagRes) ? kFlagRes : 0);
+        if (lane == 0) wave_flags[wave] = here;
+    }
+    // one direction's share of the block's summary, as in k_scan_reduce: row-lanes' own sums, brought to the block's end by one exponential
+    auto publish_wave = [&](int dir, const Seg<VEC, SQ>& s, float weight) {
+        const uint64_t heads = SQ ? __ballot(s.H != 0) : 0ull;
+        const int cut = dir == 0 ? (heads ? (63 - __clzll((long long)heads)) >> A.bv_log2 : -1)         // last row-lane with a head, seen from the left
+                                 : (heads ? (__ffsll((long long)heads) - 1) >> A.bv_log2 : rv);         // first one, i.e. the last seen from the right
+        float S[VEC], Q[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            S[e] = weight * s.S[e];
+            Q[e] = (dir == 0 ? r < cut : r > cut) ? S[e] : (r == cut ? s.Q[e] : 0.0f);
+        }
+        for (int m = bv; m < 64; m <<= 1) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { S[e] += __shfl_xor(S[e], m); if (SQ) Q[e] += __shfl_xor(Q[e], m); }
+        }
+        if (r == 0) {
+            if (c == 0 && SQ) W.H[dir][wave] = heads != 0;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) { W.S[dir][wave][kHalf + c * VEC + e] = S[e]; if (SQ) W.Q[dir][wave][kHalf + c * VEC + e] = Q[e]; }
+        }
+    };
+    auto walked = [&](const Seg<VEC, SQ>& s) {        // what the walks need of a summary
+        if constexpr (SQ == STRICT) return s;
+        else {
+            Seg<VEC, STRICT> o = seg_identity<VEC, STRICT>();
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) o.S[e] = s.S[e];
+            return o;
+        }
+    };
+    {
+        Seg<VEC, SQ> own = seg_identity<VEC, SQ>();
+#pragma unroll
+        for (int i = 0; i < ITEMS; ++i) seg_push<VEC, SQ>(own, head_f<VEC>(T, i), T.dh[i], v[i]);
+        if constexpr (ONE != 0) publish_wave(0, own, publish_wf);
+        Seg<VEC, STRICT> f = walked(own);
         f.D = lane_df;
         f = wave_scan<true, VEC, STRICT>(f, lane, bv, rv);
         if (r == rv - 1) {
@@ -1784,9 +1989,11 @@ k_scan_down(const ScanArgs A)
         if (r == 0) fe = seg_identity<VEC, STRICT>();
     }
     {
-        Seg<VEC, STRICT> b = seg_identity<VEC, STRICT>();
+        Seg<VEC, SQ> own = seg_identity<VEC, SQ>();
 #pragma unroll
-        for (int i = ITEMS - 1; i >= 0; --i) seg_push<VEC, STRICT>(b, head_b<VEC>(T, i), T.dh[i + 1], v[i]);
+        for (int i = ITEMS - 1; i >= 0; --i) seg_push<VEC, SQ>(own, head_b<VEC>(T, i), T.dh[i + 1], v[i]);
+        if constexpr (ONE != 0) publish_wave(1, own, publish_wb);
+        Seg<VEC, STRICT> b = walked(own);
         b.D = lane_db;
         b = wave_scan<false, VEC, STRICT>(b, lane, bv, rv);
         if (r == 0) {
@@ -1797,7 +2004,56 @@ k_scan_down(const ScanArgs A)
         be = seg_shfl<VEC, STRICT>(b, (lane + bv) & 63);
         if (r == rv - 1) be = seg_identity<VEC, STRICT>();
     }
+    if constexpr (ONE != 0) asm volatile("" : "+v"(gate_old));          // (read before this block arrives: the barrier is not passed without it)
     __syncthreads();
+    int tile_flags = 0;
+    if constexpr (ONE != 0) {
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) tile_flags |= wave_flags[w];
+        if (wave == 0) {
+            bool finite = true;
+            const int dir = lane >> A.bv_log2;          // a lane per direction and column group
+            if (dir < 2 && col_ok) {
+                float S[VEC], Q[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) S[e] = Q[e] = 0.0f;
+#pragma unroll
+                for (int u = 0; u < WAVES; ++u) {
+                    const int w = dir == 0 ? u : WAVES - 1 - u;
+                    const bool h = SQ && W.H[dir][w] != 0;
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        if (SQ) Q[e] = h ? S[e] + W.Q[dir][w][kHalf + c * VEC + e] : Q[e];      // everything before this wavefront, and its own share
+                        S[e] += W.S[dir][w][kHalf + c * VEC + e];
+                    }
+                }
+                const int64_t at = ((int64_t)dir * A.l1.count + tile) * A.bpad + col0;
+                store_vec_now<VEC>(A.l1.s + at, S);
+                if (SQ) store_vec_now<VEC>(A.l1.q + at, Q);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) finite = finite && fabsf(S[e]) < __uint_as_float(0x7F800000u);
+            }
+            const bool odd = __ballot(!finite) != 0ull;      // a sum that is not finite reaches every block: 0 * NaN
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) {
+                const uint32_t before = __hip_atomic_fetch_add(A.one.gate, 1u + (odd ? 0x10000u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if ((before & 0xFFFFu) == (uint32_t)A.l1.count - 1u) {      // the last one: the gate is as it was, and says that all are there
+                    store_now(A.one.gate, 0u);
+                    store_now(A.one.gate + 1, ((gate_old & ~1u) + 2u) | ((before >> 16) != 0u || odd ? 1u : 0u));
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // beside the wait: the rows' products with another problem's strict scans, the rows in sorted order
+        if (A.dot_out) row_products<VEC, RAG>(A, T, row0, col0, col_ok, bv, c, v, A.dot_in_order && (A.batch == 1 || A.counters[kStrictOrderWord] != 0u));
+        if ((tile_flags & kFlagInj) && A.stage && A.one.stage_kept && col_ok) {
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i)
+                if (T.id[i] != 0xFFFFFFFFu) store_vec<VEC>(A.stage + (row0 + i) * A.batch + col0, v[i]);
+        }
+        if constexpr (VEC == 4) { if (blockIdx.x == 0 && tid == 0 && A.z_sorted) A.counters[kStrictOrderWord] = 1u; }
+        if (!(tile_flags & kFlagRes)) return;          // uniform
+    }
     // entering states: what the earlier rows of the tile contribute (their summaries applied to zero) ...
     float F[VEC], E[VEC], R[VEC], G[VEC];
 #pragma unroll
@@ -1808,11 +2064,68 @@ k_scan_down(const ScanArgs A)
     for (int w = WAVES - 1; w > wave; --w) seg_apply<VEC, STRICT>(get_wave_seg<VEC, STRICT>(W, 1, w, c), R, G);
     seg_apply<VEC, STRICT>(fe, F, E);
     seg_apply<VEC, STRICT>(be, R, G);
+    if constexpr (ONE != 0) {
+        if (w_ahead) {
+#pragma unroll
+            for (int i = 0; i < ITEMS; ++i) fetch_row(i, wall[i]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        const int64_t count = A.l1.count;
+        if (wave == 0) {
+            const uint32_t polls = poll_limit(A.counters);
+            uint32_t now = 0u;
+            for (uint32_t tries = 0u;; ++tries) {
+                now = load_now(A.one.gate + 1);
+                if (now != gate_old || tries >= polls) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+            if (lane == 0) gate_word = (now != gate_old ? 1 : 0) | (now != gate_old && (now & 1u) ? 2 : 0);
+        }
+        __syncthreads();
+        const bool ready = (gate_word & 1) != 0, read_all = (gate_word & 2) != 0;
+        float Fs[VEC], Es[VEC], Rs[VEC], Gs[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) Fs[e] = Es[e] = Rs[e] = Gs[e] = 0.0f;
+        add_published<VEC, SQ, RAG>(A, (int)tile, (int)tile, (int)(count - 1 - tile), wave * rv + r, WAVES * rv, ready, read_all, col0, col_ok, Fs, Es, Rs, Gs);
+        for (int m = bv; m < 64; m <<= 1) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                Fs[e] += __shfl_xor(Fs[e], m); Rs[e] += __shfl_xor(Rs[e], m);
+                if (SQ) { Es[e] += __shfl_xor(Es[e], m); Gs[e] += __shfl_xor(Gs[e], m); }
+            }
+        }
+        if (r == 0) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                red[0][wave][c * VEC + e] = Fs[e]; red[1][wave][c * VEC + e] = Rs[e];
+                if constexpr (SQ) { red[2][wave][c * VEC + e] = Es[e]; red[3][wave][c * VEC + e] = Gs[e]; }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            Fc[e] = Ec[e] = Rc[e] = Gc[e] = 0.0f;
+#pragma unroll
+            for (int u = 0; u < WAVES; ++u) {
+                Fc[e] += red[0][u][c * VEC + e]; Rc[e] += red[1][u][c * VEC + e];
+                if constexpr (SQ) { Ec[e] += red[2][u][c * VEC + e]; Gc[e] += red[3][u][c * VEC + e]; }
+            }
+        }
+        if constexpr (ONE == 2) {
+            if (wave == 0 && r == 0 && col_ok) {
+                const int64_t o0 = tile * A.bpad + col0, o1 = (count + tile) * A.bpad + col0;
+                store_vec<VEC>(A.l1.car_f + o0, Fc); store_vec<VEC>(A.l1.car_e + o0, Ec);
+                store_vec<VEC>(A.l1.car_f + o1, Rc); store_vec<VEC>(A.l1.car_e + o1, Gc);
+            }
+            if (A.keep_carries == 2) return;
+        }
+    }
+    if (ONE) __builtin_amdgcn_sched_barrier(0);
     // ... plus the tile's carries, decayed over those rows by one exponential of an anchor difference
     enter_state<VEC, STRICT>(F, E, Fc, Ec, enter_df, enter_hf);
     enter_state<VEC, STRICT>(R, G, Rc, Gc, enter_db, enter_hb);
 
-    if (STRICT) __syncthreads();      // every wavefront is done with the summaries: the buffer now holds E per row
+    if (STRICT && !ONE) __syncthreads();      // every wavefront is done with the summaries: the buffer now holds E per row
 
     // forward walk: keep F of every row in registers, E of every row in LDS
     float Ff[ITEMS][VEC];
@@ -1829,6 +2142,7 @@ k_scan_down(const ScanArgs A)
     }
 
     // backward walk with emission
+    if (ONE) __builtin_amdgcn_sched_barrier(0);
     const int64_t res_rows = (int64_t)A.res_hi - (int64_t)A.res_lo;
     float racc[want_red ? ITEMS : 1];
     uint32_t rrow[want_red ? ITEMS : 1];
@@ -3201,6 +3515,12 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
 // 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243; with two or four row-lanes up to 7e6 (a product: 90000 x 90000, batch
 // 64 (6.6e6): 52 / 50; 100000 x 100000, batch 64 (8.1e6): 53 / 54; 200000 x 3, batch 64 (8.1e6): 49 / 52).
+// Scans in one launch: up to so many wavefronts (blocks of eight: the second number).  Their blocks wait for each other, so all of them should
+// be resident, beside those of the other hardware queues, of which a process has four: a compute unit holds 12 such wavefronts (one
+// workgroup of eight).  A few sizes beyond would gain as well, with the device to themselves (us, forward + backward, three launches a scan / one: 1016 wavefronts
+// of 8 columns 94 / 82, 1018 of 3 86 / 77; but 1250 of 64 and of 128 columns 94 / 95 and 99 / 100), and where they don't fit at once a step takes
+// milliseconds (390000 positions of 5 columns in 763 blocks of eight: 117 us / 5.7 ms).  At the line: 160000 positions of 8 columns 84 / 69, 390000 of 1 92 / 80, 20000 of 64 65 / 57.
+constexpr int64_t kOneWaves = 768, kOneWavesFull = 512;
 constexpr int kFewSpineWaves = 4;
 constexpr double kSpineWaveWork = 2.5e6, kSpineGroupWork = double(1 << 24), kSpineColumnWork = 5e6;
 constexpr double kSpineSuperWork = double(1 << 23), kSpineSuperFewWork = 7e6;
@@ -3275,6 +3595,23 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         else LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_seq_down<STRICT, false, 1>), tiles, dblock, 0, st, A));
         return;
     }
+    if (A.one.gate) {      // (timed with the reduces: nothing but this launch reads the injected rows)
+        auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, grid, bblock, 0, st, A)); };
+        const bool red = STRICT && A.out_red != nullptr, zs = red && A.zs != nullptr;
+        auto with = [&](auto waves) {
+            constexpr int W = decltype(waves)::value;
+            if constexpr (VEC == 4 && STRICT) { if (A.keep_carries) { go(k_scan_down<VEC, false, W, false, false, RAG, 2>); return; } }
+            if (zs) go(k_scan_down<VEC, STRICT, W, STRICT, STRICT, RAG, 1>);
+            else if (red) go(k_scan_down<VEC, STRICT, W, STRICT, false, RAG, 1>);
+            else go(k_scan_down<VEC, STRICT, W, false, false, RAG, 1>);
+        };
+        if constexpr (VEC == 4) with(std::integral_constant<int, kBlockWavesNarrow>{});
+        else if (g.waves == 1) with(std::integral_constant<int, 1>{});
+        else if (g.waves == 2) with(std::integral_constant<int, 2>{});
+        else if (g.waves == 4) with(std::integral_constant<int, 4>{});
+        else with(std::integral_constant<int, kScanWaves>{});
+        return;
+    }
     if (VEC == 4 && g.sub_shift) {    // wide geometry: a workgroup per tile, a wavefront per block
         if (A.pin.half && A.pin.virtual_inj)      // phased: x read once for both halves
             LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL((k_scan_reduce_wide<STRICT, 2>), dim3(rgrid.x), dim3(kWideWaves * 64), 0, st, A));
@@ -3313,7 +3650,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
             return;
         }
         if (A.keep_carries) {          // (9 to 128 columns, every block with injected and result rows)
-            LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down<VEC, false, kBlockWavesNarrow, false, false, RAG>), dgrid, bblock, 0, st, A));
+            LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down<VEC, false, kBlockWavesNarrow, false, false, RAG, 0>), dgrid, bblock, 0, st, A));
             return;
         }
     }
@@ -3323,9 +3660,9 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         const bool zs = red && A.zs != nullptr;
         auto with = [&](auto waves) {
             constexpr int W = decltype(waves)::value;
-            if (zs) go(k_scan_down<VEC, STRICT, W, STRICT, STRICT, RAG>);
-            else if (red) go(k_scan_down<VEC, STRICT, W, STRICT, false, RAG>);
-            else go(k_scan_down<VEC, STRICT, W, false, false, RAG>);
+            if (zs) go(k_scan_down<VEC, STRICT, W, STRICT, STRICT, RAG, 0>);
+            else if (red) go(k_scan_down<VEC, STRICT, W, STRICT, false, RAG, 0>);
+            else go(k_scan_down<VEC, STRICT, W, false, false, RAG, 0>);
         };
         if (g.waves == kBlockWavesNarrow) with(std::integral_constant<int, kBlockWavesNarrow>{});
         else if (VEC == 1 && g.waves == 2) with(std::integral_constant<int, VEC == 1 ? 2 : kScanWaves>{});
@@ -3445,6 +3782,12 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
         A.few_res_ok = g.sub_shift && disjoint && res_rows * 4 <= g.blocks;
         // (the metadata pass runs before the reduce; with a dense injection the reduce then visits every
         //  tile and overwrites the provisional summaries, with a sparse one only the listed tiles)
+    }
+
+    A.one = OneLaunch{};      // (every block visited; no more than 32 lanes across the batch, whose other half of the exchange is taken)
+    if (A.every_block && g.slabs == 1 && g.bv <= 32 && !p.inj_sorted && !p.pair_carries) {
+        if (g.blocks * g.waves <= (g.waves == kScanWaves ? kOneWavesFull : kOneWaves)) A.one.gate = A.counters + kGateWord;
+        A.one.stage_kept = p.stage != nullptr && p.stage == reinterpret_cast<float*>(ws + L.off_xs) ? 1 : 0;
     }
 
     // The products of rows that several slabs share, or that the wide geometry's reduce reads, are a pass of their own, and so are those of

@@ -293,6 +293,47 @@ def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
         assert_close(name, got.cpu().numpy(), rv, tv)
 
 
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
+@pytest.mark.parametrize("k,n,batch", [(4096, 4097, 8), (98304, 98304, 8), (98304, 98305, 8), (4096, 4097, 64), (12285, 12291, 64), (9001, 3000, 33), (5000, 3200, 13),
+                                       (393216, 393216, 1), (4096, 4097, 1), (150000, 5000, 3), (20000, 21000, 5), (0, 98303, 8), (0, 20001, 1), (0, 9001, 64), (0, 12001, 33)])
+def test_scans_in_one_launch(oracle, k, n, batch, kind):
+    """Few blocks: they publish their summaries and add up each other's in the launch that scans, at both ends of that range (768 wavefronts); and
+    again with no wait for the others, whose share is then taken from their rows (k = 0: the Gram form)."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + n + batch)
+    a, b = anchors(kind, r, k or n, n)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(k or n, batch)).astype(np.float32)
+    if k:
+        ref, tol = oracle.apply_scan(a, b, x)
+        want, tols = oracle.apply_backward_scan(a, b, x, g)
+    else:
+        ref, tol = oracle.gram_scan(a, x)
+        want, tols = oracle.gram_backward_scan(a, x, g)
+    da, db, dx, dg = dev(a), dev(b), dev(x), dev(g)
+    y, gx, ga, gb = torch.empty_like(dg), torch.empty_like(dx), torch.empty_like(da), torch.empty_like(db)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+
+    def step(flags):
+        if k:
+            B.laplex_apply(da, db, dx, y, ws, flags | B.LAPLEX_SAVE_SCANS)
+            B.laplex_apply_backward(da, db, dx, dg, gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        else:
+            B.laplex_gram(da, dx, y, ws, flags | B.LAPLEX_SAVE_SCANS)
+            B.laplex_gram_backward(da, dx, dg, gx, ga, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+        torch.cuda.synchronize()
+
+    def check():
+        assert_close("y", y.cpu().numpy(), ref, tol)
+        for name, got, rv, tv in zip(("gx", "ga", "gb"), (gx, ga, gb), want, tols):
+            assert_close(name, got.cpu().numpy(), rv, tv)
+    step(0)
+    check()
+    if (k + n) * batch <= 400000:      # (every block reads every row within reach)
+        B.laplex_diag_set_wait_limit(ws, k + n, 0)
+        step(B.LAPLEX_REUSE_PLAN)
+        check()
+
+
 @pytest.mark.parametrize("k,n,batch,launches", [(30000, 34000, 33, 1), (2999, 100003, 33, 2), (45000, 50000, 33, 2), (100000, 110000, 13, 2), (70000, 62000, 65, 3),
                                                 (1000, 40000, 33, 1), (40000, 31000, 64, 2), (1500, 82000, 40, 2), (900000, 600000, 8, 2)])
 def test_spine_launches(k, n, batch, launches):
