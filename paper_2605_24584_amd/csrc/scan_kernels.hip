@@ -1048,7 +1048,7 @@ k_phase_split_blocks(const ScanArgs A, int from_list)
 
 // ---------------------------------------------------------------------------
 // reduce, one WAVEFRONT per tile (batches that are not staged in sorted order, outside the wide
-// geometry): row-lane r walks its share of the tile's rows chunk by chunk, so the summary needs no
+// geometry; single columns, and where row products are wanted): row-lane r walks its share of the tile's rows chunk by chunk, so the summary needs no
 // LDS and no barrier, and a workgroup is four independent wavefronts.  Same outputs as k_scan_reduce.
 // ---------------------------------------------------------------------------
 constexpr int kLoneWaves = 4;
@@ -1125,6 +1125,100 @@ k_scan_reduce_wave(const ScanArgs A)
         b.D = b.C = tile_db;
         store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, b, (float)tile_flags, A.counters);
     }
+}
+
+// ---------------------------------------------------------------------------
+// reduce, one WAVEFRONT per tile, lanes of four columns: the tile's summaries as weighted sums, as in the wide geometry,
+//   S_f = sum_j exp(-(p_last - p_j)) v_j,   S_b = sum_j exp(-(p_j - p_first)) v_j,
+// the strict ones over the rows whose key is not the last (first) one.  Lane l looks at row l of 64: its id, its anchor, one
+// exponential each way; the injected rows' entries are packed side by side in LDS (a wavefront's own), and every row-lane takes every rv-th of them.
+// No row depends on another and rows that are not injected are not looked at twice; four rows in flight per row-lane at 63 registers (eight at 102: the same).
+// Bound by the rows' reads: n = 3 x 2^20, batch 64 (0.8 GB) 150 us where walks row by row took 161 (125 registers, half the wavefronts).  A product on a kept plan, us: 5 10^5 x
+// 5 10^5, batch 64 128 -> 117, batch 16 56 -> 53; 2 10^5 x 2 10^5, batch 33 68 -> 63; 1024 x 2^20, batch 64 91 -> 85; 10^5 x 10^5, batch 128 68 -> 64.
+// ---------------------------------------------------------------------------
+template <bool STRICT, bool RAG>
+__global__ void __launch_bounds__(kLoneWaves * 64)
+k_scan_reduce_rows(const ScanArgs A)
+{
+    constexpr int VEC = 4, AHEAD = 4;
+    __shared__ uint4 entries[kLoneWaves][64];              // row, weights forward and backward, 1: before the last key, 2: after the first
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int bv = A.bv, rv = A.rv;
+    const int c = lane & (bv - 1), r = lane >> A.bv_log2;
+    const int64_t slot = (int64_t)blockIdx.x * kLoneWaves + wave;
+    if (A.reduce_from_list ? slot >= (int64_t)A.counters[0] : slot >= A.l1.count) return;
+    const int64_t tile = A.reduce_from_list ? (int64_t)lane_u(A.list_inj[slot], 0) : slot;
+    const int64_t base = tile * A.tile_rows, end = base + A.tile_rows < A.N ? base + A.tile_rows : A.N;
+    const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
+    const bool col_ok = col0 < A.batch;
+    const RowEnd tail = row_end<VEC, RAG>(col0, A.batch);
+    const float p_before = A.pk[base], p_first = A.pk[base + 1], p_last = A.pk[end], p_after = A.pk[end + 1];
+    uint4* const mine = entries[wave];
+
+    float Sf[VEC], Sb[VEC], Qf[VEC], Qb[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) Sf[e] = Sb[e] = Qf[e] = Qb[e] = 0.0f;
+    int flags = 0;
+    auto fetch = [&](int64_t o, uint32_t& id, float& p) {
+        const int64_t j = base + o + lane, jc = j < end ? j : end - 1;
+        id = j < end ? A.ids[jc] : 0xFFFFFFFFu;
+        p = A.pk[jc + 1];
+    };
+    uint32_t id;
+    float p;
+    fetch(0, id, p);
+    for (int64_t o = 0; base + o < end; o += 64) {
+        const bool in = id >= A.inj_lo && id < A.inj_hi;
+        const uint64_t mask = __ballot(in);
+        if (mask) flags |= kFlagInj;
+        if (__ballot(id >= A.res_lo && id < A.res_hi)) flags |= kFlagRes;
+        const int count = __popcll(mask);
+        __builtin_amdgcn_wave_barrier();
+        if (in) {
+            const int at = __popcll(mask & ((1ull << lane) - 1ull));
+            mine[at] = make_uint4(id - A.inj_lo, __float_as_uint(expf(-(p_last - p))), __float_as_uint(expf(-(p - p_first))), (p != p_last ? 1u : 0u) | (p != p_first ? 2u : 0u));
+        }
+        __builtin_amdgcn_wave_barrier();
+        fetch(o + 64 < A.tile_rows ? o + 64 : o, id, p);
+        for (int t = 0; t < count; t += AHEAD * rv) {
+            uint4 w[AHEAD];
+            float v[AHEAD][VEC];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                const int at = t + i * rv + r;
+                w[i] = mine[at < count ? at : 0];
+                if (at >= count) w[i].y = w[i].z = w[i].w = 0u;
+                load_row_or_zero<VEC, true, RAG>(v[i], A.inj, (int64_t)w[i].x * A.ld_inj + col0, at < count && col_ok, tail);
+            }
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) {
+                const float wf = __uint_as_float(w[i].y), wb = __uint_as_float(w[i].z);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    Sf[e] += wf * v[i][e]; Sb[e] += wb * v[i][e];
+                    if (STRICT) { Qf[e] += w[i].w & 1u ? wf * v[i][e] : 0.0f; Qb[e] += w[i].w & 2u ? wb * v[i][e] : 0.0f; }
+                }
+            }
+        }
+    }
+    for (int m = bv; m < 64; m <<= 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            Sf[e] += __shfl_xor(Sf[e], m); Sb[e] += __shfl_xor(Sb[e], m);
+            if (STRICT) { Qf[e] += __shfl_xor(Qf[e], m); Qb[e] += __shfl_xor(Qb[e], m); }
+        }
+    }
+    if (r > 0) return;
+    if (c == 0 && blockIdx.y == 0) A.blk_flags[tile] = (uint32_t)flags;     // in this geometry a tile is one block
+    const bool sw = c == 0 && blockIdx.y == 0, vec_ok = col_ok && (flags & kFlagInj);   // zero vectors are never fetched: not written either
+    Seg<VEC, STRICT> f = seg_identity<VEC, STRICT>(), b = f;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) { f.S[e] = Sf[e]; b.S[e] = Sb[e]; if (STRICT) { f.Q[e] = Qf[e]; b.Q[e] = Qb[e]; } }
+    f.D = f.C = expf(-(p_last - p_before)); b.D = b.C = expf(-(p_after - p_first));
+    if (STRICT) { f.H = p_last != p_before ? 1 : 0; b.H = p_after != p_first ? 1 : 0; }
+    store_level_seg<VEC, STRICT>(A.l1, 0, tile, A.bpad, col0, vec_ok, sw, f, (float)flags, A.counters);
+    store_level_seg<VEC, STRICT>(A.l1, 1, tile, A.bpad, col0, vec_ok, sw, b, (float)flags, A.counters);
 }
 
 // ---------------------------------------------------------------------------
@@ -3621,7 +3715,8 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         const dim3 lgrid((rgrid.x + kLoneWaves - 1) / kLoneWaves, rgrid.y);
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, lgrid, dim3(kLoneWaves * 64), 0, st, A)); };
         // (single columns come here with several slabs only, whose row products are a pass of their own)
-        if (VEC == 4 && A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, VEC == 4, RAG>); else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
+        if constexpr (VEC == 4) { if (A.dot_out) go(k_scan_reduce_wave<VEC, STRICT, true, RAG>); else go(k_scan_reduce_rows<STRICT, RAG>); }
+        else go(k_scan_reduce_wave<VEC, STRICT, false, RAG>);
     } else {
         auto go = [&](auto kernel) { LAPLEX_TIMED(fr.c_str(), st, hipLaunchKernelGGL(kernel, rgrid, bblock, 0, st, A)); };
         if (A.dot_out) go(k_scan_reduce<VEC, STRICT, true, RAG>); else go(k_scan_reduce<VEC, STRICT, false, RAG>);

@@ -334,6 +334,30 @@ def test_scans_in_one_launch(oracle, k, n, batch, kind):
         check()
 
 
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal"])
+@pytest.mark.parametrize("k,n,batch", [(70000, 70001, 33), (66000, 66000, 64), (40000, 30001, 100), (33000, 33001, 127), (300000, 240001, 13), (64, 140000, 64), (140000, 33, 48), (0, 132001, 48)])
+def test_reduce_with_a_wavefront_per_tile(oracle, k, n, batch, kind):
+    """More than 1024 tiles of up to 128 columns: their summaries are weighted sums of the injected rows, which are packed first (k = 0: the Gram form)."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + n + batch)
+    a, b = anchors(kind, r, k or n, n)
+    x = r.normal(size=(n, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x) if k else oracle.gram_scan(a, x)
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    y = torch.empty(k or n, batch, device="cuda")
+    step = (lambda v: B.laplex_apply(dev(a), dev(b), dev(v), y, ws, B.LAPLEX_SAVE_SCANS)) if k else (lambda v: B.laplex_gram(dev(a), dev(v), y, ws, B.LAPLEX_SAVE_SCANS))
+    step(x)
+    torch.cuda.synchronize()
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    bad = x.copy()                                   # one column of them: no other column changes, and that one has no finite element left
+    bad[n // 3, batch - 1] = np.inf
+    first = y.cpu().numpy()
+    step(bad)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    assert np.array_equal(got[:, : batch - 1], first[:, : batch - 1]) and not np.isfinite(got[:, batch - 1]).any()
+
+
 @pytest.mark.parametrize("k,n,batch,launches", [(30000, 34000, 33, 1), (2999, 100003, 33, 2), (45000, 50000, 33, 2), (100000, 110000, 13, 2), (70000, 62000, 65, 3),
                                                 (1000, 40000, 33, 1), (40000, 31000, 64, 2), (1500, 82000, 40, 2), (900000, 600000, 8, 2)])
 def test_spine_launches(k, n, batch, launches):
