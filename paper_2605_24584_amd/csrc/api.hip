@@ -464,6 +464,7 @@ struct MixCommon {
     const float* a; const float* b; int64_t n; hipStream_t st;
     MixGather sum;      // w and the regions; a call fills in what it wants
     float* dot_long; float* dot_short; float* dot_total; float* p; float* z;
+    MixEnds ends;
 
     MixCommon(const MixLayout& M_, const float* a_, const float* b_, const float* w, int64_t r, int64_t k, int64_t n_, int64_t batch,
               char* base_, hipStream_t st_)
@@ -518,7 +519,7 @@ struct MixCommon {
         MixGather S = sum;
         S.u = grad ? u : nullptr; S.ldu = ldu; S.out = out; S.ldo = ldo; S.dot1 = dots(grad, dot_long);
         LAPLEX_HIP(launch_mix_gather(A, S, false, st));
-        if (grad && A.slabs > 1) LAPLEX_HIP(launch_mix_finish(A, dot_long, sum.w, A.l, grad, st));
+        if (grad && A.slabs > 1) { ends.dot[0] = dot_long; ends.out[0] = grad; ends.count[0] = A.l; }
         return LAPLEX_OK;
     }
     // ... and at the short rows (from p and z)
@@ -529,13 +530,20 @@ struct MixCommon {
         S.p = out || gw ? p : nullptr; S.z = grad ? z : nullptr;
         S.dot1 = dots(grad, dot_short); S.dot2 = gw ? dot_total : nullptr;
         LAPLEX_HIP(launch_mix_gather(A, S, true, st));
-        return short_dots(grad, gw);
+        short_dots(grad, gw);
+        return LAPLEX_OK;
     }
     // the short rows' dots: with the strict sums the anchor gradients, with the products, added up, the weights' gradients
-    int short_dots(float* grad, float* gw)
+    void short_dots(float* grad, float* gw)
     {
-        if (grad && A.slabs > 1) LAPLEX_HIP(launch_mix_finish(A, dot_short, sum.w, A.m, grad, st));
-        if (gw) LAPLEX_HIP(launch_mix_total(A, dot_total, gw, st));
+        if (grad && A.slabs > 1) { ends.dot[1] = dot_short; ends.out[1] = grad; ends.count[1] = A.m; }
+        if (gw) { ends.dot_total = dot_total; ends.total = gw; ends.total_rows = A.m; }
+    }
+    // the dots of the call, which nothing before its end reads
+    int finish()
+    {
+        ends.w = sum.w;
+        LAPLEX_HIP(launch_mix_ends(A, ends, st));
         return LAPLEX_OK;
     }
 };
@@ -580,9 +588,9 @@ int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* 
             S.dot_z = C.dots(gb, C.dot_short); S.dot_p = gw ? C.dot_total : nullptr;
             LAPLEX_CHECK(C.scan_long(gy, ldgy, S));
             if (gx) LAPLEX_CHECK(C.at_short(nullptr, 0, gx, ldgx, nullptr, nullptr));
-            LAPLEX_CHECK(C.short_dots(gb, gw));
+            C.short_dots(gb, gw);
         }
-        return LAPLEX_OK;
+        return C.finish();
     }
     if (ga || gw) {
         MixFolded S{};
@@ -594,7 +602,7 @@ int mix_common_backward(MixCommon& C, const float* x, int64_t ldx, const float* 
         LAPLEX_CHECK(C.scan_short(gy, ldgy));
         LAPLEX_CHECK(C.at_long(x, ldx, gx, ldgx, gb));
     }
-    return LAPLEX_OK;
+    return C.finish();
 }
 
 // The plans of many small operators where sorting them beats ranking them: the flags then say that they are there.  (So many that of their products only those of one

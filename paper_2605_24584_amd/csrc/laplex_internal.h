@@ -625,8 +625,14 @@ hipError_t launch_mix_replan(const MixPath& A, hipStream_t st);
 hipError_t launch_mix_scan(const MixPath& A, const float* v, int64_t ldv, hipStream_t st);
 hipError_t launch_mix_fold(const MixPath& A, const float* v, int64_t ldv, const MixFolded& S, hipStream_t st);
 hipError_t launch_mix_gather(const MixPath& A, const MixGather& S, bool rows, hipStream_t st);
-hipError_t launch_mix_finish(const MixPath& A, const float* dot, const float* w, int64_t count, float* out, hipStream_t st);
-hipError_t launch_mix_total(const MixPath& A, const float* dot, float* out, hipStream_t st);
+// A call's dots brought together: out[i][q][row] = w[q] sum over slabs of dot[i][slab][q][row] (row < count[i]), total[q] = the sum over slabs and rows of
+// dot_total[slab][q][row] (row < total_rows); null outputs are left out.
+struct MixEnds {
+    const float* w = nullptr;
+    const float* dot[2] = {nullptr, nullptr}; float* out[2] = {nullptr, nullptr}; int count[2] = {0, 0};
+    const float* dot_total = nullptr; float* total = nullptr; int total_rows = 0;
+};
+hipError_t launch_mix_ends(const MixPath& A, const MixEnds& E, hipStream_t st);
 
 // Weighted Gram matrix (gram_kernels.hip): U, V, W (fp64, k each) by a scan of its own over the plan (ids, pk) of the
 // doubled anchors, then the fill  M[i*ldm + j] = exp(-|a_i - a_j|) (U[lo] + (W[hi] - W[lo]) + V[hi]),  lo / hi the pair
