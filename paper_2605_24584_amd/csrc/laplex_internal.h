@@ -63,6 +63,7 @@ constexpr int kPlanIndexWord = 33;                      // nonzero: what the com
 constexpr int kStrictOrderWord = 34;                    // nonzero: the saved strict scans lie in the sorted order (ScanProblem::z_in_order)
 constexpr int kWaitWord = 35;                           // nonzero: blocks that wait for each other's summaries poll this often, less one (tests)
 constexpr int kGateWord = 36;                           // and the next: the gate of the scans in one launch (OneLaunch)
+constexpr int kPairRedoWord = 38;                       // set by k_scan_down_matrix: some value is not finite (the scan's reduce clears it)
 constexpr int kPlanStatusWord = 32;                     // in the plan's 64 counter words: the sort's error flag, kept with the plan
 constexpr int kMergeThreads = 256;
 constexpr int kMergePerThread = 8;

@@ -94,6 +94,7 @@ struct ScanArgs {
     int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_in_order)
     const float* dot_z; float* dot_out; const float* dot_in_order;      // row products of the reduce (ScanProblem)
     const float* pair_car_f; const float* pair_car_e;      // carries of a second matrix, x, scanned beside the injected one (k_scan_down_pair), or null
+    int pair_redo;                // the launch of k_scan_down_pair is behind one of k_scan_down_matrix: it has work only where that found a value that is not finite
     int keep_carries;             // 1: the carries stay where l1 has them and no strict value is written; 2: and there is no downsweep
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
     OneLaunch one;                // one.gate: the downsweep forms the blocks' summaries and carries itself (k_scan_down<..., ONE>)
@@ -666,6 +667,7 @@ k_scan_reduce(const ScanArgs A)
     const int64_t col0 = ((int64_t)blockIdx.y * bv + c) * VEC;
     const bool col_ok = col0 < A.batch;
     if (tid == 0) tile_flags = 0;
+    if (VEC == 4 && A.pair_redo && blockIdx.x == 0 && tid == 0) A.counters[kPairRedoWord] = 0u;
 
     // decays over this row-lane's rows, this wavefront's rows and the whole tile, from the anchors
     // (not products of the rows' decays: see k_decay); asked for first so the loads go out early
@@ -1155,6 +1157,7 @@ k_scan_reduce_rows(const ScanArgs A)
     const RowEnd tail = row_end<VEC, RAG>(col0, A.batch);
     const float p_before = A.pk[base], p_first = A.pk[base + 1], p_last = A.pk[end], p_after = A.pk[end + 1];
     uint4* const mine = entries[wave];
+    if (A.pair_redo && blockIdx.x == 0 && threadIdx.x == 0) A.counters[kPairRedoWord] = 0u;
 
     float Sf[VEC], Sb[VEC], Qf[VEC], Qb[VEC];
 #pragma unroll
@@ -2310,7 +2313,8 @@ struct PairSegs {
     float S[2][kPairWaves][kPairColumns], Q[2][kPairWaves][kPairColumns];
 };
 
-template <bool RAG>
+// REDO: the launch behind k_scan_down_matrix, of a few workgroups that take block after block.
+template <bool RAG, bool REDO>
 __global__ void __launch_bounds__(kPairWaves * 64, 4)
 k_scan_down_pair(const ScanArgs A)
 {
@@ -2321,7 +2325,8 @@ k_scan_down_pair(const ScanArgs A)
     float4* const zx = zx_all + threadIdx.x;          // the strict scans of x, row i at zx[i * THREADS]
     float4* const ef = ef_all + threadIdx.x;
     if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
-    const int64_t tile = blockIdx.x;
+    if (REDO && A.counters[kPairRedoWord] == 0u) return;                           // uniform: k_scan_down_matrix has done it all
+    for (int64_t tile = blockIdx.x;;) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int bv = A.bv, rv = A.rv;
     const int c = lane & (bv - 1), r = lane >> A.bv_log2;
@@ -2474,6 +2479,177 @@ k_scan_down_pair(const ScanArgs A)
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) { racc[i] = zx[i * THREADS].x; rrow[i] = id[i] != 0xFFFFFFFFu ? id[i] : kNoRow; }
     emit_row_sums<ITEMS>(racc, rrow, bv, c, A.out_red, A.ld_red);
+    if (!REDO || (tile += gridDim.x) >= A.l1.count) return;          // uniform
+    __syncthreads();                    // every wavefront is done with the block
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the same on the matrix cores, 33 to 64 columns
+// ---------------------------------------------------------------------------
+// Sixteen sorted rows are a wavefront's, and inside them everything is a product with a 16 x 16 matrix of the anchors alone (the definition of
+// Sec. 1 where the scans of Sec. 3 were):
+//   F + R - v = L v,  L_ij = exp(-|p_i - p_j|);    Z = K v,  K_ij = sgn(p_j - p_i) L_ij;
+// the rows' sums are the last and the first row of these; and what enters the sixteen rows, (F, E, R, G), adds a product with four columns: the decays from either end for F and R where a row's key is not that end's, and
+// for the strict sums one for E and G where it is.  L and K are the same for gy and x.  v_mfma_f32_16x16x4_f32 multiplies and adds in fp32 and keeps
+// subnormal numbers; lane (c, r) holds rows 4 r .. 4 r + 3 and columns 4 c .. 4 c + 3 both as the operand (row 4 r + q in step q) and as the result.
+// k_scan_down_pair is bound by its vector instructions (1670 a wavefront: 537 of 650 us at n = 3 x 2^20, batch 64, by the counters); here they are fewer than 970 beside 76
+// matrix ones, and it takes 556 us, 4.4 TB/s (forward and backward 1419 -> 1332). Held at 80 registers for three workgroups a compute unit it spills 31: 1127 us. Relative 2-norm errors of gx and ga
+// against fp64, walks / here: normal anchors 9.9 / 9.0 and 12.1 / 11.5 10^-8, uniform 11.5 / 9.9 and 13.4 / 12.2, all within reach 15.2 / 13.5 and 18.0 / 16.7, a grid 10.2 / 10.0 and 12.3 / 12.4.
+// 0 * inf and 0 * NaN are no part of a strict sum: where a value or a state is not finite a word is set, and k_scan_down_pair, launched behind this
+// kernel, does everything again (else it returns at once).
+constexpr int kMatrixRows = 16;
+constexpr int64_t kRedoGroups = 512;      // (returning at once from 24576 of them took 12 us)
+template <bool RAG>
+__global__ void __launch_bounds__(kPairWaves * 64, 4)
+k_scan_down_matrix(const ScanArgs A)
+{
+    constexpr int VEC = 4, WAVES = kPairWaves;
+    __shared__ float4 sums[2][4][WAVES][16];               // of x and of gy: forward, backward, strict, per wavefront and column group
+    __shared__ float decay[WAVES][2][WAVES];               // to the wavefront from before and after: kSame for rows that end at its edge's key, 0 for none
+    constexpr float kSame = 2.0f;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, r = lane >> 4;
+    const int64_t tile = blockIdx.x, tile_base = tile * A.tile_rows, N = A.N;
+    const int64_t tile_end = tile_base + A.tile_rows < N ? tile_base + A.tile_rows : N;
+    auto first_of = [&](int w) { const int64_t j = tile_base + w * kMatrixRows; return j < N ? j : N; };
+    const int64_t lo = first_of(wave), hi = lo + kMatrixRows < N ? lo + kMatrixRows : N;
+    const int64_t col0 = (int64_t)c * VEC;
+    const bool col_ok = col0 < A.batch;
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+
+    uint32_t id[4];
+    float p[4], x[4][VEC], v[4][VEC];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t j = lo + 4 * r + i, jc = j < N ? j : N - 1;
+        const uint32_t at = A.ids[jc];
+        p[i] = A.pk[jc + 1];
+        id[i] = j < N ? at : 0xFFFFFFFFu;
+    }
+    if (!RAG && A.batch == 16 * VEC && hi - lo == kMatrixRows) {      // uniform: every lane has its rows and columns
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_vec_stream<VEC>(x[i], A.w + (int64_t)id[i] * A.ld_w + col0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_vec_stream<VEC>(v[i], A.inj + (int64_t)id[i] * A.ld_inj + col0);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_row_or_zero<VEC, true, RAG>(x[i], A.w, (int64_t)id[i] * A.ld_w + col0, col_ok && id[i] != 0xFFFFFFFFu, end);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_row_or_zero<VEC, true, RAG>(v[i], A.inj, (int64_t)id[i] * A.ld_inj + col0, col_ok && id[i] != 0xFFFFFFFFu, end);
+    }
+    const float p_row = A.pk[(lo + c < N ? lo + c : N - 1) + 1];                   // anchor of the row that this lane's matrix elements belong to
+    const float p_before = A.pk[lo], p_after = A.pk[hi + 1];
+    // what the lane adds to the states: r = 0: F, 1: E (forward, from before the rows), 2: R, 3: G (backward, from after them)
+    const bool back = r >= 2, strict = (r & 1) != 0;
+    const float p_edge = back ? p_after : p_before, p_block = back ? A.pk[tile_end + 1] : A.pk[tile_base];
+    const bool same_block = p_block == p_edge;
+    const float block_decay = same_block ? 1.0f : expf(-fabsf(p_edge - p_block));
+    const int64_t car_at = ((back ? A.l1.count : 0) + tile) * A.bpad + (col_ok ? col0 : 0);
+    float carry[2][VEC], state[2][VEC];
+    load_vec<VEC>(carry[0], (strict && same_block ? A.pair_car_e : A.pair_car_f) + car_at);
+    load_vec<VEC>(carry[1], (strict && same_block ? A.l1.car_e : A.l1.car_f) + car_at);
+    if (lane < 2 * WAVES) {
+        const int u = lane & (WAVES - 1), dir = lane / WAVES;
+        const int64_t u_lo = first_of(u), u_hi = u_lo + kMatrixRows < N ? u_lo + kMatrixRows : N;
+        const float near_ = dir == 0 ? A.pk[u_hi] : A.pk[u_lo + 1], mine = dir == 0 ? p_before : p_after;
+        const bool in = (dir == 0 ? u < wave : u > wave) && u_hi > u_lo;
+        decay[wave][dir][u] = !in ? 0.0f : near_ == mine ? kSame : expf(-fabsf(mine - near_));
+    }
+    float near_[4], signed_[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float d = p[q] - p_row, e = expf(-fabsf(d));
+        near_[q] = e;
+        signed_[q] = d == 0.0f ? 0.0f : __builtin_copysignf(e, d);
+    }
+    float odd = 0.0f;                                      // becomes a NaN with the first value that is not finite
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { odd = __builtin_fmaf(x[i][e], 0.0f, odd); odd = __builtin_fmaf(v[i][e], 0.0f, odd); }
+    auto multiply = [&](const float (&m)[4], const float (&rows)[4][VEC], v4f (&out)[VEC]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) out[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(m[q], rows[q][e], out[e], 0, 0, 0);
+    };
+    auto zero = [](v4f (&out)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) out[e] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    // The rows' sums are rows of the products: the forward ones the last row of L v and, with the sign turned, of K v, the backward ones the first
+    // row of either (rows past the end have the last one's anchor and add nothing).
+    auto keep_sums = [&](int which, const v4f (&l)[VEC], const v4f (&k)[VEC]) {
+        if (r == 3) {
+            sums[which][0][wave][c] = make_float4(l[0][3], l[1][3], l[2][3], l[3][3]);
+            sums[which][2][wave][c] = make_float4(-k[0][3], -k[1][3], -k[2][3], -k[3][3]);
+        } else if (r == 0) {
+            sums[which][1][wave][c] = make_float4(l[0][0], l[1][0], l[2][0], l[3][0]);
+            sums[which][3][wave][c] = make_float4(k[0][0], k[1][0], k[2][0], k[3][0]);
+        }
+    };
+    v4f zx[VEC], zg[VEC], out[VEC];
+    zero(out); zero(zx); zero(zg);
+    multiply(near_, x, out);
+    multiply(signed_, x, zx);
+    keep_sums(0, out, zx);
+    zero(out);
+    multiply(near_, v, out);
+    multiply(signed_, v, zg);
+    keep_sums(1, out, zg);
+    __syncthreads();
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) state[which][e] = 0.0f;
+    }
+#pragma unroll 2
+    for (int n = 0; n < WAVES; ++n) {
+        const int u = back ? WAVES - 1 - n : n;          // the nearest ones, whose share is largest, last
+        const float g = decay[wave][back ? 1 : 0][u];
+        const int kind = (back ? 1 : 0) + (strict && g == kSame ? 2 : 0);
+        const float w = g == kSame ? 1.0f : g;          // (0 for the other side: a sum that is not finite makes the state a NaN, and all is done again)
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+            const float4 t = sums[which][kind][u][c];
+            state[which][0] += w * t.x; state[which][1] += w * t.y; state[which][2] += w * t.z; state[which][3] += w * t.w;
+        }
+    }
+    // (the block's carries last: they are the largest part where anchors are close, and every sum after them would be rounded at their size)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        if (col_ok) { state[0][e] = __builtin_fmaf(block_decay, carry[0][e], state[0][e]); state[1][e] = __builtin_fmaf(block_decay, carry[1][e], state[1][e]); }
+        odd = __builtin_fmaf(state[0][e], 0.0f, odd); odd = __builtin_fmaf(state[1][e], 0.0f, odd);
+    }
+    const bool same = p_row == p_edge;
+    const float d_edge = same ? 1.0f : expf(-fabsf(p_edge - p_row));
+    // (an invalid plan: every product gets a NaN with what enters the rows)
+    const float poison = __uint_as_float(plan_poison(A.counters));
+    const float into_p = (strict ? 0.0f : d_edge) + poison, into_z = (strict == same ? (back ? d_edge : -d_edge) : 0.0f) + poison;
+    auto with_states = [&](float coefficient, const float (&st)[VEC], v4f (&to)[VEC]) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) to[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(coefficient, st[e], to[e], 0, 0, 0);
+    };
+    with_states(into_p, state[1], out);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float P[VEC] = {out[0][i], out[1][i], out[2][i], out[3][i]};
+        if (id[i] != 0xFFFFFFFFu && col_ok && A.out_p) store_row<VEC, RAG>(A.out_p + (int64_t)id[i] * A.ld_p + col0, P, end);
+    }
+    with_states(into_z, state[0], zx);
+    with_states(into_z, state[1], zg);
+    float racc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        racc[i] = v[i][0] * zx[0][i] + v[i][1] * zx[1][i] + v[i][2] * zx[2][i] + v[i][3] * zx[3][i];
+        racc[i] += x[i][0] * zg[0][i] + x[i][1] * zg[1][i] + x[i][2] * zg[2][i] + x[i][3] * zg[3][i];
+    }
+    uint32_t rrow[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rrow[i] = id[i] != 0xFFFFFFFFu ? id[i] : kNoRow;
+    emit_row_sums<4>(racc, rrow, 16, c, A.out_red, A.ld_red);
+    if (__ballot(odd != 0.0f) && lane == 0) A.counters[kPairRedoWord] = 1u;      // (odd is zero or a NaN)
 }
 
 // ---------------------------------------------------------------------------
@@ -3741,7 +3917,13 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
     if (A.keep_carries == 2) return;
     if constexpr (VEC == 4 && STRICT) {
         if (A.pair_car_f) {
-            LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down_pair<RAG>), dim3((unsigned)g.blocks), dim3(kPairWaves * 64), 0, st, A));
+            const dim3 blocks((unsigned)g.blocks), few((unsigned)(g.blocks < kRedoGroups ? g.blocks : kRedoGroups)), threads(kPairWaves * 64);
+            if (A.pair_redo) {
+                LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down_matrix<RAG>), blocks, threads, 0, st, A));
+                LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down_pair<RAG, true>), few, threads, 0, st, A));
+            } else {
+                LAPLEX_TIMED(fd.c_str(), st, hipLaunchKernelGGL((k_scan_down_pair<RAG, false>), blocks, threads, 0, st, A));
+            }
             return;
         }
         if (A.keep_carries) {          // (9 to 128 columns, every block with injected and result rows)
@@ -3845,6 +4027,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.keep_carries = p.carries ? (p.out_p ? 1 : 2) : 0;
     if (p.carries) { A.l1.car_f = p.carries; A.l1.car_e = p.carries + 2 * g.tiles * L.bpad; }
     A.pair_car_f = p.pair_carries;
+    A.pair_redo = p.pair_carries && g.vec == 4 && g.bv == 16 && g.tile_rows == kPairWaves * kMatrixRows ? 1 : 0;
     A.pair_car_e = p.pair_carries ? p.pair_carries + 2 * g.tiles * L.bpad : nullptr;
     if ((p.carries || p.pair_carries) && (g.vec != 4 || g.sub_shift || g.slabs != 1 || p.stage)) return hipErrorInvalidValue;
     A.l2 = Level{reinterpret_cast<float4*>(ws + L.off_agg2_scalar), reinterpret_cast<float*>(ws + L.off_agg2_s),

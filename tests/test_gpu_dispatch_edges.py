@@ -358,6 +358,55 @@ def test_reduce_with_a_wavefront_per_tile(oracle, k, n, batch, kind):
     assert np.array_equal(got[:, : batch - 1], first[:, : batch - 1]) and not np.isfinite(got[:, batch - 1]).any()
 
 
+@pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "huge_gaps", "clustered"])
+@pytest.mark.parametrize("n,batch", [(8193, 64), (8305, 33), (9000, 36), (9100, 63), (12301, 48), (140000, 64)])
+def test_gram_backward_on_the_matrix_cores(oracle, n, batch, kind):
+    """33 to 64 columns: sixteen rows a wavefront, whole and partly filled blocks, rows that end on any boundary."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(n + batch)
+    a, _ = anchors(kind, r, n, 1)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(n, batch)).astype(np.float32)
+    (rgx, rga), (tgx, tga) = oracle.gram_backward_scan(a, x, g)
+    ws = torch.empty(B.laplex_workspace_bytes(0, n, batch), dtype=torch.uint8, device="cuda")
+    gx, ga = torch.full((n, batch), float("nan"), device="cuda"), torch.full((n,), float("nan"), device="cuda")
+    seen = families(lambda: B.laplex_gram_backward(dev(a), dev(x), dev(g), gx, ga, ws, 0))
+    torch.cuda.synchronize()
+    assert seen["scan_down.bwd"] == 2, seen              # (the second launch is there for values that are not finite)
+    assert_close("gx", gx.cpu().numpy(), rgx, tgx)
+    assert_close("ga", ga.cpu().numpy(), rga, tga)
+
+
+@pytest.mark.parametrize("where", ["x", "g", "both"])
+@pytest.mark.parametrize("kind", ["ties", "uniform"])
+def test_gram_backward_on_the_matrix_cores_leaves_what_is_not_finite_to_the_walks(kind, where):
+    """64 columns against the same in two halves, which are walked: infinities and NaN reach the same elements, and rows tied with them stay finite."""
+    from test_gpu_parity import anchors
+    n, batch = 9001, 64
+    r = np.random.default_rng(7)
+    a, _ = anchors(kind, r, n, 1)
+    x, g = r.normal(size=(n, batch)).astype(np.float32), r.normal(size=(n, batch)).astype(np.float32)
+    for m in ([x] if where == "x" else [g] if where == "g" else [x, g]):
+        m[n // 2, 3] = np.inf
+        m[n // 5, 40] = -np.inf
+        m[n // 7, 50] = np.nan
+
+    def backward(cols):
+        ws = torch.empty(B.laplex_workspace_bytes(0, n, cols.stop - cols.start), dtype=torch.uint8, device="cuda")
+        xs, gs = dev(np.ascontiguousarray(x[:, cols])), dev(np.ascontiguousarray(g[:, cols]))
+        gx, ga = torch.empty_like(xs), torch.empty(n, device="cuda")
+        for _ in range(2):                               # (the word that asks for the walks is cleared in between)
+            B.laplex_gram_backward(dev(a), xs, gs, gx, ga, ws, 0)
+        torch.cuda.synchronize()
+        return gx.cpu().numpy(), ga.cpu().numpy()
+    gx, ga = backward(slice(0, 64))
+    halves = [backward(slice(0, 32)), backward(slice(32, 64))]
+    both = np.concatenate([h[0] for h in halves], axis=1)
+    assert np.array_equal(np.isnan(gx), np.isnan(both)) and np.array_equal(np.isinf(gx), np.isinf(both))
+    assert np.array_equal(np.isfinite(ga), np.isfinite(halves[0][1]) & np.isfinite(halves[1][1]))
+    fine = np.isfinite(gx)
+    assert np.allclose(gx[fine], both[fine], rtol=1e-4, atol=1e-4)
+
+
 @pytest.mark.parametrize("k,n,batch,launches", [(30000, 34000, 33, 1), (2999, 100003, 33, 2), (45000, 50000, 33, 2), (100000, 110000, 13, 2), (70000, 62000, 65, 3),
                                                 (1000, 40000, 33, 1), (40000, 31000, 64, 2), (1500, 82000, 40, 2), (900000, 600000, 8, 2)])
 def test_spine_launches(k, n, batch, launches):
