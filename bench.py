@@ -292,7 +292,7 @@ KERNEL_OF = {
     "scan_reduce.fwd": "forward reduce (reads the injected rows of x once for both directions)",
     "scan_reduce.bwd": "backward reduce (reads the injected rows of gy once for both directions)",
     "scan_down.fwd": "k_scan_down, forward problem (reads x, writes y and, but for the square form, the saved scans)",
-    "scan_down.bwd": "backward downsweep (k_scan_down: reads gy, x and, for the square form at batch 1 to 8, the saved scans; k_scan_down_pair: gy and x; writes gx and the anchor gradient)",
+    "scan_down.bwd": "backward downsweep (k_scan_down: reads gy, x and, for the square form at batch 1 to 8, the saved scans; k_scan_down_matrix and k_scan_down_pair: gy and x; writes gx and the anchor gradient)",
     "radix_scatter": "k_onesweep_pass (one radix pass: reads the pairs once, writes them once)",
     "deep_sort": "k_deep_sort (a unit of the sorted sequence gathered, sorted in LDS and written to the plan)",
     "deep_pieces": "k_deep_distribute<true> (pairs of a bucket to its stretches)",
