@@ -80,7 +80,7 @@ int laplex_diag_set_plan_status(void* ws, size_t ws_bytes, int64_t count, uint32
 /*
  * Test hook: how often the blocks of a scan in one launch look whether the others are there before they take the others' share from the
  * rows themselves, for the plan in `ws` (count as for laplex_get_plan_status; plans of more than 8192 positions only) until it is built
- * anew.  0: once; results then differ in rounding only.  polls < 2^32 - 1; 2^32 - 1 gives the default back.
+ * anew.  0: never; results then differ in rounding only.  polls < 2^32 - 1; 2^32 - 1 gives the default back.
  */
 int laplex_diag_set_wait_limit(void* ws, size_t ws_bytes, int64_t count, uint32_t polls, laplex_stream_t stream);
 

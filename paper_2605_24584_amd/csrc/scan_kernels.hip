@@ -1681,7 +1681,8 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 // What one workgroup writes for another to read in the same launch goes through relaxed agent-scope atomics, which pass by the chiplets'
 // own L2s; a summary is complete before the gate counts it (s_waitcnt).  The gate is one word that every block adds one to and one that
 // the last block changes.  No wait is without end: after a number of polls a block takes the other blocks' share from their
-// rows themselves (add_rows_of), so no order of dispatch and no number of resident workgroups is needed for a result, only for speed.
+// rows themselves (add_rows_of; of all blocks, also those out of reach, since a value that is not finite reaches every block), so no order of dispatch
+// and no number of resident workgroups is needed for a result, only for speed.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t load_now(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_now(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -2170,16 +2171,17 @@ k_scan_down(const ScanArgs A)
         const int64_t count = A.l1.count;
         if (wave == 0) {
             const uint32_t polls = poll_limit(A.counters);
-            uint32_t now = 0u;
-            for (uint32_t tries = 0u;; ++tries) {
+            uint32_t now = gate_old;
+            for (uint32_t tries = 0u; tries < polls; ++tries) {
                 now = load_now(A.one.gate + 1);
-                if (now != gate_old || tries >= polls) break;
+                if (now != gate_old) break;
                 __builtin_amdgcn_s_sleep(1);
             }
             if (lane == 0) gate_word = (now != gate_old ? 1 : 0) | (now != gate_old && (now & 1u) ? 2 : 0);
         }
         __syncthreads();
-        const bool ready = (gate_word & 1) != 0, read_all = (gate_word & 2) != 0;
+        const bool ready = (gate_word & 1) != 0;
+        const bool read_all = !ready || (gate_word & 2) != 0;          // (without the others' word for it that all sums are finite: 0 * NaN)
         float Fs[VEC], Es[VEC], Rs[VEC], Gs[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) Fs[e] = Es[e] = Rs[e] = Gs[e] = 0.0f;

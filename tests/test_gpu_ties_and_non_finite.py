@@ -163,6 +163,43 @@ def test_gram_non_finite_rows_reach_every_row(n, batch, bad):
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("k,n,batch", [(10000, 9000, 1), (9000, 8000, 8), (65000, 66072, 8), (7000, 2000, 3), (5000, 4000, 5), (6000, 3001, 33), (4097, 4097, 64), (5000, 4000, 128),
+                                       (0, 9000, 1), (0, 9000, 8), (0, 8193, 9), (0, 9001, 33), (0, 20000, 64), (0, 9003, 127)])
+def test_non_finite_rows_reach_blocks_that_do_not_wait(k, n, batch, bad):
+    """The two tests above where a scan is one launch, with no block waiting for the others (k = 0: the Gram form)."""
+    q = np.random.default_rng(k + n + batch)
+    a, b = (dev(q.uniform(0, 3000, s).astype(np.float32)) for s in (k or n, n))
+    x, g = (q.normal(size=(s, batch)).astype(np.float32) for s in (n, k or n))
+    col = batch // 2
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    built = 0
+    for side in ("x", "gy"):
+        dx, dg = dev(x), dev(g)
+        (dx if side == "x" else dg)[q.integers(0, n if side == "x" else k or n), col] = bad
+        y, gx, ga, gb = torch.zeros_like(dg), torch.zeros_like(dx), torch.zeros_like(a), torch.zeros_like(b)
+        for again in range(2):                       # the first pass builds the plan, the second scans on it without waiting
+            flags = B.LAPLEX_SAVE_SCANS | built
+            if k:
+                B.laplex_apply(a, b, dx, y, ws, flags)
+                B.laplex_apply_backward(a, b, dx, dg, gx, ga, gb, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+            else:
+                B.laplex_gram(b, dx, y, ws, flags)
+                B.laplex_gram_backward(b, dx, dg, gx, ga, ws, B.LAPLEX_SAVE_SCANS | B.LAPLEX_REUSE_PLAN)
+            if not built:
+                B.laplex_diag_set_wait_limit(ws, k + n, 0)
+                built = B.LAPLEX_REUSE_PLAN
+                for v in (y, gx, ga, gb):
+                    v.zero_()
+        torch.cuda.synchronize()
+        if side == "x" or not k:
+            assert_all_non_finite("ga", ga)
+        if side == "gy" and k:
+            assert_all_non_finite("gb", gb)
+        assert_all_non_finite("y" if side == "x" else "gx", y if side == "x" else gx, col)
+        assert bool(torch.isfinite(gx if side == "x" else y).all())
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
 @pytest.mark.parametrize("r,k,n,batch", [(2, 3000, 7000, 1), (2, 7000, 3000, 33), (3, 5000, 5000, 64), (2, 300, 400, 8), (4, 33000, 33000, 2)])
 def test_mix_non_finite_rows_reach_every_row(r, k, n, batch, bad):
     """The same for sums of operators, on each of their routes."""
