@@ -78,9 +78,9 @@ int laplex_diag_move_rows(const float* src, float* dst, const uint32_t* row_ids,
 int laplex_diag_set_plan_status(void* ws, size_t ws_bytes, int64_t count, uint32_t value, laplex_stream_t stream);
 
 /*
- * Test hook: how often the blocks of a scan in one launch look whether the others are there before they take the others' share from the
- * rows themselves, for the plan in `ws` (count as for laplex_get_plan_status; plans of more than 8192 positions only) until it is built
- * anew.  0: never; results then differ in rounding only.  polls < 2^32 - 1; 2^32 - 1 gives the default back.
+ * Test hook: how often the blocks of a scan in one launch look whether the others are there before each of them forms the summaries of
+ * all blocks itself, for the plan in `ws` (count as for laplex_get_plan_status; plans of more than 8192 positions only) until it is built
+ * anew.  0: never.  Results are the same, bit for bit.  polls < 2^32 - 1; 2^32 - 1 gives the default back.
  */
 int laplex_diag_set_wait_limit(void* ws, size_t ws_bytes, int64_t count, uint32_t polls, laplex_stream_t stream);
 

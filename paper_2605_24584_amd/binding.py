@@ -198,7 +198,7 @@ def laplex_diag_set_plan_status(ws, count: int, value: int, stream=None) -> None
 
 
 def laplex_diag_set_wait_limit(ws, count: int, polls: int, stream=None) -> None:
-    """Test hook: how often a scan's blocks look for each other before they read the other blocks' rows themselves."""
+    """Test hook: how often a scan's blocks look for each other before each forms the summaries of all blocks itself."""
     _check(lib().laplex_diag_set_wait_limit(_ptr(ws), ws.numel(), count, polls, _stream(stream)))
 
 

@@ -1680,9 +1680,9 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 //
 // What one workgroup writes for another to read in the same launch goes through relaxed agent-scope atomics, which pass by the chiplets'
 // own L2s; a summary is complete before the gate counts it (s_waitcnt).  The gate is one word that every block adds one to and one that
-// the last block changes.  No wait is without end: after a number of polls a block takes the other blocks' share from their
-// rows themselves (add_rows_of; of all blocks, also those out of reach, since a value that is not finite reaches every block), so no order of dispatch
-// and no number of resident workgroups is needed for a result, only for speed.
+// the last block changes.  No wait is without end: after a number of polls a block forms and publishes all blocks' summaries itself, one after the
+// other (form_summary).  They are the same bits as everyone else's, so neither an order of dispatch nor a number of resident workgroups is needed for a
+// result or changes one: they decide its time only.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t load_now(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void store_now(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -1716,29 +1716,94 @@ __device__ __forceinline__ void store_vec_now(float* dst, const float* src)
 constexpr uint32_t kMaxPolls = 1u << 12;
 __device__ __forceinline__ uint32_t poll_limit(const uint32_t* counters) { return counters[kWaitWord] ? counters[kWaitWord] - 1u : kMaxPolls; }
 
-// F, E += the rows of block v themselves, decayed to the edge `at`.
-template <int VEC, bool SQ, bool RAG>
-__device__ __forceinline__ void add_rows_of(const ScanArgs& A, int64_t v, float at, int64_t col0, bool col_ok, float* F, float* E)
+// One direction's share of a block's summary, as in k_scan_reduce: row-lanes' own sums, brought to the block's end by one exponential, a
+// wavefront's into the exchange (from column `half` on)
+template <int VEC, bool SQ, int WAVES>
+__device__ __forceinline__ void publish_wave(const ScanArgs& A, WaveSegs<VEC, WAVES>& W, int half, int dir, int wave, int lane, const Seg<VEC, SQ>& s, float weight)
 {
-    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
-    const int64_t j1 = (v + 1) * A.tile_rows < A.N ? (v + 1) * A.tile_rows : A.N;
-#pragma unroll 1
-    for (int64_t j = v * A.tile_rows; j < j1; ++j) {
-        const uint32_t id = A.ids[j];
-        const float p = A.pk[j + 1], w = expf(-fabsf(at - p));
-        const bool in = col_ok && id >= A.inj_lo && id < A.inj_hi;
-        float x[VEC];
-        load_row_or_zero<VEC, false, RAG>(x, A.inj, (int64_t)(id - A.inj_lo) * A.ld_inj + col0, in, end);
+    const int bv = A.bv, rv = A.rv, c = lane & (bv - 1), r = lane >> A.bv_log2;
+    const uint64_t heads = SQ ? __ballot(s.H != 0) : 0ull;
+    const int cut = dir == 0 ? (heads ? (63 - __clzll((long long)heads)) >> A.bv_log2 : -1)         // last row-lane with a head, seen from the left
+                             : (heads ? (__ffsll((long long)heads) - 1) >> A.bv_log2 : rv);         // first one, i.e. the last seen from the right
+    float S[VEC], Q[VEC];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) { const float y = in ? w * x[e] : 0.0f; F[e] += y; if (SQ) E[e] += p == at ? 0.0f : y; }
+    for (int e = 0; e < VEC; ++e) {
+        S[e] = weight * s.S[e];
+        Q[e] = (dir == 0 ? r < cut : r > cut) ? S[e] : (r == cut ? s.Q[e] : 0.0f);
+    }
+    for (int m = bv; m < 64; m <<= 1) {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { S[e] += __shfl_xor(S[e], m); if (SQ) Q[e] += __shfl_xor(Q[e], m); }
+    }
+    if (r == 0) {
+        if (c == 0 && SQ) W.H[dir][wave] = heads != 0;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) { W.S[dir][wave][half + c * VEC + e] = S[e]; if (SQ) W.Q[dir][wave][half + c * VEC + e] = Q[e]; }
+    }
+}
+
+// The wavefronts' shares added up and published by one wavefront, a lane per direction and column group; complete when it returns.  Are the
+// sums finite?
+template <int VEC, bool SQ, int WAVES>
+__device__ __forceinline__ bool publish_block(const ScanArgs& A, const WaveSegs<VEC, WAVES>& W, int half, int64_t tile, int lane, int64_t col0, bool col_ok)
+{
+    bool finite = true;
+    const int c = lane & (A.bv - 1), dir = lane >> A.bv_log2;
+    if (dir < 2 && col_ok) {
+        float S[VEC], Q[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) S[e] = Q[e] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < WAVES; ++u) {
+            const int w = dir == 0 ? u : WAVES - 1 - u;
+            const bool h = SQ && W.H[dir][w] != 0;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+                if (SQ) Q[e] = h ? S[e] + W.Q[dir][w][half + c * VEC + e] : Q[e];      // everything before this wavefront, and its own share
+                S[e] += W.S[dir][w][half + c * VEC + e];
+            }
+        }
+        const int64_t at = ((int64_t)dir * A.l1.count + tile) * A.bpad + col0;
+        store_vec_now<VEC>(A.l1.s + at, S);
+        if (SQ) store_vec_now<VEC>(A.l1.q + at, Q);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) finite = finite && fabsf(S[e]) < __uint_as_float(0x7F800000u);
+    }
+    finite = __ballot(!finite) == 0ull;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return finite;
+}
+
+// The share of this wavefront in the summary of any block: the additions of the block's own workgroup in their order, but row by row, so that little code
+// and few registers lie beside the path that is taken (with that path's own code here a step of 2^16 x 2^16 at batch 8 took 4 us more, on no account but its size).
+template <int VEC, bool SQ, int WAVES, bool RAG>
+__device__ __forceinline__ void form_summary(const ScanArgs& A, WaveSegs<VEC, WAVES>& W, int half, int64_t tile, int wave, int lane, int64_t col0, bool col_ok)
+{
+    constexpr int ITEMS = TileRows<VEC>::ITEMS;
+    const RowEnd end = row_end<VEC, RAG>(col0, A.batch);
+    const int64_t base = tile * A.tile_rows, row0 = base + (int64_t)(wave * A.rv + (lane >> A.bv_log2)) * ITEMS;
+#pragma unroll 1
+    for (int dir = 0; dir < 2; ++dir) {
+        Seg<VEC, SQ> own = seg_identity<VEC, SQ>();
+#pragma unroll 1
+        for (int n = 0; n < ITEMS; ++n) {
+            const int64_t j = row0 + (dir == 0 ? n : ITEMS - 1 - n);
+            const uint32_t id = j < A.N ? A.ids[j] : 0xFFFFFFFFu;
+            const float d = j < A.N ? A.dh[j + dir] : -1.0f;
+            float x[VEC];
+            load_row_or_zero<VEC, false, RAG>(x, A.inj, (int64_t)(id - A.inj_lo) * A.ld_inj + col0, col_ok && id >= A.inj_lo && id < A.inj_hi, end);
+            seg_push<VEC, SQ>(own, d >= 0.0f, d, x);
+        }
+        const int64_t after = row0 + ITEMS;
+        publish_wave<VEC, SQ, WAVES>(A, W, half, dir, wave, lane, own, dir == 0 ? span_decay_f(A, after, base + A.tile_rows - after) : span_decay_b(A, base, row0 - base));
     }
 }
 
 // F, E (R, G) += the published summaries of the `left` blocks before block t (of the `right` ones after it); this row-lane takes every
 // `step`-th from `rl` on, on either side at once (add_entries, but that a block's strict sum is only fetched where it ends at the edge's
-// key).  ready: every block has published.
-template <int VEC, bool SQ, bool RAG>
-__device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left, int right, int rl, int step, bool ready, bool read_all,
+// key).  Every block has published; read_all: some sum is not finite and reaches every block, 0 * NaN.
+template <int VEC, bool SQ>
+__device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left, int right, int rl, int step, bool read_all,
                                               int64_t col0, bool col_ok, float* F, float* E, float* R, float* G)
 {
     constexpr int kAhead = VEC == 4 ? 1 : 2;
@@ -1770,13 +1835,11 @@ __device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left
                 any += w[dir][i];
             }
         more = any != 0.0f || read_all;                      // (farther blocks are out of reach as well)
-        const uint32_t missing = ready ? 0u : in;            // blocks that may not have published
-        const uint32_t there = in & ~missing;
 #pragma unroll
         for (int dir = 0; dir < 2; ++dir)
 #pragma unroll
             for (int i = 0; i < kAhead; ++i) {
-                const bool ok = col_ok && (there >> (2 * i + dir) & 1u);
+                const bool ok = col_ok && (in >> (2 * i + dir) & 1u);
                 load_vec_now<VEC>(S[dir][i], A.l1.s + (ok ? ((int64_t)dir * count + block(dir, o0 + i * step)) * A.bpad + col0 : 0));
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) S[dir][i][e] = ok ? S[dir][i][e] : 0.0f;
@@ -1789,7 +1852,7 @@ __device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left
                 float Q[VEC];
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) Q[e] = 0.0f;
-                if (SQ && edge && col_ok && (there >> (2 * i + dir) & 1u)) {      // (rare: a run of equal keys across blocks)
+                if (SQ && edge && col_ok && (in >> (2 * i + dir) & 1u)) {      // (rare: a run of equal keys across blocks)
                     const int v = block(dir, o0 + i * step);
                     const float far = A.pk[dir == 0 ? (int64_t)v * SR : (int64_t)end_of(v) + 1];
                     if (w[dir][i] != 0.0f && far != at[dir]) load_vec_now<VEC>(Q, A.l1.q + ((int64_t)dir * count + v) * A.bpad + col0);
@@ -1803,13 +1866,6 @@ __device__ __forceinline__ void add_published(const ScanArgs& A, int t, int left
                     if (SQ) q[e] += edge ? Q[e] : x;
                 }
             }
-        if (missing) {
-#pragma unroll 1
-            for (int i = 0; i < kAhead; ++i) {
-                if (missing >> (2 * i) & 1u) add_rows_of<VEC, SQ, RAG>(A, block(0, o0 + i * step), at[0], col0, col_ok, F, E);
-                if (missing >> (2 * i + 1) & 1u) add_rows_of<VEC, SQ, RAG>(A, block(1, o0 + i * step), at[1], col0, col_ok, R, G);
-            }
-        }
     }
 }
 
@@ -2040,27 +2096,6 @@ k_scan_down(const ScanArgs A)
         const int here = (__ballot(mine & kFlagInj) ? kFlagInj : 0) | (__ballot(mine & kFlagRes) ? kFlagRes : 0);
         if (lane == 0) wave_flags[wave] = here;
     }
-    // one direction's share of the block's summary, as in k_scan_reduce: row-lanes' own sums, brought to the block's end by one exponential
-    auto publish_wave = [&](int dir, const Seg<VEC, SQ>& s, float weight) {
-        const uint64_t heads = SQ ? __ballot(s.H != 0) : 0ull;
-        const int cut = dir == 0 ? (heads ? (63 - __clzll((long long)heads)) >> A.bv_log2 : -1)         // last row-lane with a head, seen from the left
-                                 : (heads ? (__ffsll((long long)heads) - 1) >> A.bv_log2 : rv);         // first one, i.e. the last seen from the right
-        float S[VEC], Q[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            S[e] = weight * s.S[e];
-            Q[e] = (dir == 0 ? r < cut : r > cut) ? S[e] : (r == cut ? s.Q[e] : 0.0f);
-        }
-        for (int m = bv; m < 64; m <<= 1) {
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) { S[e] += __shfl_xor(S[e], m); if (SQ) Q[e] += __shfl_xor(Q[e], m); }
-        }
-        if (r == 0) {
-            if (c == 0 && SQ) W.H[dir][wave] = heads != 0;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) { W.S[dir][wave][kHalf + c * VEC + e] = S[e]; if (SQ) W.Q[dir][wave][kHalf + c * VEC + e] = Q[e]; }
-        }
-    };
     auto walked = [&](const Seg<VEC, SQ>& s) {        // what the walks need of a summary
         if constexpr (SQ == STRICT) return s;
         else {
@@ -2074,7 +2109,7 @@ k_scan_down(const ScanArgs A)
         Seg<VEC, SQ> own = seg_identity<VEC, SQ>();
 #pragma unroll
         for (int i = 0; i < ITEMS; ++i) seg_push<VEC, SQ>(own, head_f<VEC>(T, i), T.dh[i], v[i]);
-        if constexpr (ONE != 0) publish_wave(0, own, publish_wf);
+        if constexpr (ONE != 0) publish_wave<VEC, SQ, WAVES>(A, W, kHalf, 0, wave, lane, own, publish_wf);
         Seg<VEC, STRICT> f = walked(own);
         f.D = lane_df;
         f = wave_scan<true, VEC, STRICT>(f, lane, bv, rv);
@@ -2090,7 +2125,7 @@ k_scan_down(const ScanArgs A)
         Seg<VEC, SQ> own = seg_identity<VEC, SQ>();
 #pragma unroll
         for (int i = ITEMS - 1; i >= 0; --i) seg_push<VEC, SQ>(own, head_b<VEC>(T, i), T.dh[i + 1], v[i]);
-        if constexpr (ONE != 0) publish_wave(1, own, publish_wb);
+        if constexpr (ONE != 0) publish_wave<VEC, SQ, WAVES>(A, W, kHalf, 1, wave, lane, own, publish_wb);
         Seg<VEC, STRICT> b = walked(own);
         b.D = lane_db;
         b = wave_scan<false, VEC, STRICT>(b, lane, bv, rv);
@@ -2109,30 +2144,7 @@ k_scan_down(const ScanArgs A)
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) tile_flags |= wave_flags[w];
         if (wave == 0) {
-            bool finite = true;
-            const int dir = lane >> A.bv_log2;          // a lane per direction and column group
-            if (dir < 2 && col_ok) {
-                float S[VEC], Q[VEC];
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) S[e] = Q[e] = 0.0f;
-#pragma unroll
-                for (int u = 0; u < WAVES; ++u) {
-                    const int w = dir == 0 ? u : WAVES - 1 - u;
-                    const bool h = SQ && W.H[dir][w] != 0;
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        if (SQ) Q[e] = h ? S[e] + W.Q[dir][w][kHalf + c * VEC + e] : Q[e];      // everything before this wavefront, and its own share
-                        S[e] += W.S[dir][w][kHalf + c * VEC + e];
-                    }
-                }
-                const int64_t at = ((int64_t)dir * A.l1.count + tile) * A.bpad + col0;
-                store_vec_now<VEC>(A.l1.s + at, S);
-                if (SQ) store_vec_now<VEC>(A.l1.q + at, Q);
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) finite = finite && fabsf(S[e]) < __uint_as_float(0x7F800000u);
-            }
-            const bool odd = __ballot(!finite) != 0ull;      // a sum that is not finite reaches every block: 0 * NaN
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const bool odd = !publish_block<VEC, SQ, WAVES>(A, W, kHalf, tile, lane, col0, col_ok);      // a sum that is not finite reaches every block: 0 * NaN
             if (lane == 0) {
                 const uint32_t before = __hip_atomic_fetch_add(A.one.gate, 1u + (odd ? 0x10000u : 0u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 if ((before & 0xFFFFu) == (uint32_t)A.l1.count - 1u) {      // the last one: the gate is as it was, and says that all are there
@@ -2180,12 +2192,23 @@ k_scan_down(const ScanArgs A)
             if (lane == 0) gate_word = (now != gate_old ? 1 : 0) | (now != gate_old && (now & 1u) ? 2 : 0);
         }
         __syncthreads();
-        const bool ready = (gate_word & 1) != 0;
-        const bool read_all = !ready || (gate_word & 2) != 0;          // (without the others' word for it that all sums are finite: 0 * NaN)
+        if (__builtin_expect((gate_word & 1) == 0, 0)) {          // uniform: no waiting any longer (the walks are done with the exchange)
+            bool odd = false;
+#pragma unroll 1
+            for (int64_t t = 0; t < count; ++t) {
+                form_summary<VEC, SQ, WAVES, RAG>(A, W, kHalf, t, wave, lane, col0, col_ok);
+                __syncthreads();
+                if (wave == 0) odd = !publish_block<VEC, SQ, WAVES>(A, W, kHalf, t, lane, col0, col_ok) || odd;
+                __syncthreads();
+            }
+            if (tid == 0) gate_word = odd ? 2 : 0;
+            __syncthreads();
+        }
+        const bool read_all = (gate_word & 2) != 0;
         float Fs[VEC], Es[VEC], Rs[VEC], Gs[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) Fs[e] = Es[e] = Rs[e] = Gs[e] = 0.0f;
-        add_published<VEC, SQ, RAG>(A, (int)tile, (int)tile, (int)(count - 1 - tile), wave * rv + r, WAVES * rv, ready, read_all, col0, col_ok, Fs, Es, Rs, Gs);
+        add_published<VEC, SQ>(A, (int)tile, (int)tile, (int)(count - 1 - tile), wave * rv + r, WAVES * rv, read_all, col0, col_ok, Fs, Es, Rs, Gs);
         for (int m = bv; m < 64; m <<= 1) {
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {

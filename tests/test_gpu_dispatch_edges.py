@@ -294,11 +294,13 @@ def test_few_rows_on_one_side_visit_every_short_block(oracle, k, n, batch):
 
 
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal", "clustered"])
-@pytest.mark.parametrize("k,n,batch", [(4096, 4097, 8), (98304, 98304, 8), (98304, 98305, 8), (4096, 4097, 64), (12285, 12291, 64), (9001, 3000, 33), (5000, 3200, 13),
-                                       (393216, 393216, 1), (4096, 4097, 1), (150000, 5000, 3), (20000, 21000, 5), (0, 98303, 8), (0, 20001, 1), (0, 9001, 64), (0, 12001, 33)])
-def test_scans_in_one_launch(oracle, k, n, batch, kind):
+@pytest.mark.parametrize("k,n,batch,one", [(4096, 4097, 8, True), (98304, 98304, 8, True), (98304, 98305, 8, False), (4096, 4097, 64, True), (12285, 12291, 64, True), (9001, 3000, 33, True),
+                                           (5000, 3200, 13, True), (393216, 393216, 1, True), (393216, 393217, 1, False), (4096, 4097, 1, True), (150000, 5000, 3, True), (20000, 21000, 5, True),
+                                           (4097, 4096, 65, True), (4500, 4501, 97, True), (6144, 6144, 128, True), (6144, 6145, 128, False),
+                                           (0, 98303, 8, True), (0, 20001, 1, True), (0, 9001, 64, True), (0, 12001, 33, True), (0, 9002, 128, True)])
+def test_scans_in_one_launch(oracle, k, n, batch, one, kind):
     """Few blocks: they publish their summaries and add up each other's in the launch that scans, at both ends of that range (768 wavefronts); and
-    again with no wait for the others, whose share is then taken from their rows (k = 0: the Gram form)."""
+    again with no wait for the others, whose summaries every block then forms itself: the same bits (k = 0: the Gram form, whose backward is not one launch beyond 8 columns)."""
     from test_gpu_parity import anchors, assert_close
     r = np.random.default_rng(k + n + batch)
     a, b = anchors(kind, r, k or n, n)
@@ -328,10 +330,15 @@ def test_scans_in_one_launch(oracle, k, n, batch, kind):
             assert_close(name, got.cpu().numpy(), rv, tv)
     step(0)
     check()
-    if (k + n) * batch <= 400000:      # (every block reads every row within reach)
-        B.laplex_diag_set_wait_limit(ws, k + n, 0)
-        step(B.LAPLEX_REUSE_PLAN)
-        check()
+    seen = families(lambda: step(B.LAPLEX_REUSE_PLAN))
+    launches = {name for name in seen if name.startswith(("scan_spine", "scan_down"))}
+    assert any(name.endswith(".fwd") for name in launches) == (not one), seen
+    assert any(name.endswith(".bwd") for name in launches) == (not one or (k == 0 and batch > 8)), seen
+    waited = [v.clone() for v in (y, gx, ga, gb)]
+    B.laplex_diag_set_wait_limit(ws, k + n, 0)
+    step(B.LAPLEX_REUSE_PLAN)
+    check()
+    assert all(torch.equal(v, w) for v, w in zip((y, gx, ga, gb) if k else (y, gx, ga), waited))
 
 
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal"])
