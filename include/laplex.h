@@ -18,6 +18,10 @@
  *  - Calls only enqueue work on `stream`; they never synchronise, allocate or
  *    free.  Two calls that share a workspace must be ordered by the caller
  *    (same stream, or events).
+ *  - The same call gives the same bits whatever else the device is doing.  On a stream with
+ *    fewer compute units (a mask of units, a partition of the device) values may differ
+ *    from those of the whole device in rounding: how many there are decides how
+ *    some scans are launched.
  *  - Return value: LAPLEX_OK or a negative LAPLEX_ERR_*.  Arguments are
  *    checked on the host before the first HIP call, so an argument error
  *    leaves every buffer untouched.  No exception crosses the boundary.

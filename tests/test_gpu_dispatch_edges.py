@@ -341,6 +341,40 @@ def test_scans_in_one_launch(oracle, k, n, batch, one, kind):
     assert all(torch.equal(v, w) for v, w in zip((y, gx, ga, gb) if k else (y, gx, ga), waited))
 
 
+def masked_stream(units):
+    """A stream whose workgroups run on the device's first `units` compute units, and what destroys it."""
+    import ctypes
+    with open("/proc/self/maps") as maps:
+        path = next(line.split()[-1] for line in maps if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    words = (ctypes.c_uint32 * 8)(*[0xFFFFFFFF if 32 * (i + 1) <= units else (1 << max(units - 32 * i, 0)) - 1 for i in range(8)])
+    stream = ctypes.c_void_p()
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(stream), 8, words) == 0
+    return stream.value, lambda: hip.hipStreamDestroy(stream)
+
+
+@pytest.mark.parametrize("units,k,n,batch,one", [(256, 98304, 98304, 8, True), (64, 24576, 24576, 8, True), (64, 24576, 24577, 8, False), (40, 49152, 12288, 1, True), (40, 393216, 393216, 1, False),
+                                                 (32, 4096, 4097, 64, False)])
+def test_scans_in_one_launch_fit_the_stream(oracle, units, k, n, batch, one):
+    """Blocks that wait for each other are no more than the compute units of the stream hold: three wavefronts for each."""
+    from test_gpu_parity import anchors, assert_close
+    r = np.random.default_rng(k + n + units)
+    a, b = anchors("uniform", r, k, n)
+    x = r.normal(size=(n, batch)).astype(np.float32)
+    ref, tol = oracle.apply_scan(a, b, x)
+    da, db, dx, y = dev(a), dev(b), dev(x), torch.empty(k, batch, device="cuda")
+    ws = torch.empty(B.laplex_workspace_bytes(k, n, batch), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    stream, destroy = masked_stream(units)
+    try:
+        seen = families(lambda: B.laplex_apply(da, db, dx, y, ws, 0, stream=stream))
+        torch.cuda.synchronize()
+    finally:
+        destroy()
+    assert_close("y", y.cpu().numpy(), ref, tol)
+    assert any(name.startswith(("scan_spine", "scan_down")) for name in seen) == (not one), seen
+
+
 @pytest.mark.parametrize("kind", ["uniform", "ties", "all_equal"])
 @pytest.mark.parametrize("k,n,batch", [(70000, 70001, 33), (66000, 66000, 64), (40000, 30001, 100), (33000, 33001, 127), (300000, 240001, 13), (64, 140000, 64), (140000, 33, 48), (0, 132001, 48)])
 def test_reduce_with_a_wavefront_per_tile(oracle, k, n, batch, kind):
