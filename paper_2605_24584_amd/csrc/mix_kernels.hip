@@ -805,7 +805,7 @@ k_mix_scan_down(const MixPath A, const float* __restrict__ v, int64_t ldv, const
 //                  out_i = sum_q w_q (el F_lo + er R_lo'),   dot1[q][i] = sum_t u_it (strict R - strict F)
 //   ROWS = true    targets: the short side, whose products P_q and strict sums Z_q (either may be null) lie in memory:
 //                  out_j = sum_q w_q P_q[j],   dot1[q][j] = sum_t u_jt Z_q[j][t],   dot2[q][j] = sum_t u_jt P_q[j][t]
-// Dots are left per slab (dot[slab][q][row]) for k_mix_finish to add; a single slab writes w_q dot1, the gradient, itself.
+// Dots are left per slab (dot[slab][q][row]) for k_mix_ends to add; a single slab writes w_q dot1, the gradient, itself.
 // ---------------------------------------------------------------------------
 template <int VEC, int T, bool ROWS>
 __global__ void __launch_bounds__(kMixThreads)

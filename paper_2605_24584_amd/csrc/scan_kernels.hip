@@ -3811,13 +3811,15 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) ==
 // Two levels up to 2^23 values (forward + backward, three launches / two): n = k = 2^20, batch 8 (1.6e6): 424 / 406; 1024 x 2^18, batch
 // 256 (6.3e6): 312 / 291; n = k = 2^17, batch 64 (1.3e7): 231 / 243; with two or four row-lanes up to 7e6 (a product: 90000 x 90000, batch
 // 64 (6.6e6): 52 / 50; 100000 x 100000, batch 64 (8.1e6): 53 / 54; 200000 x 3, batch 64 (8.1e6): 49 / 52).
-// Scans in one launch: up to so many wavefronts (blocks of eight: the second number) on a stream that has 256 compute units, fewer in proportion where it has
-// fewer (stream_units).  Their blocks wait for each other, so all of them should
-// be resident, beside those of the other hardware queues, of which a process has four: a compute unit holds 12 such wavefronts (one
-// workgroup of eight).  A few sizes beyond would gain as well, with the device to themselves (us, forward + backward, three launches a scan / one: 1016 wavefronts
+// Scans in one launch: up to so many wavefronts on a stream that has 256 compute units, fewer in proportion where it has fewer (stream_units).  Their
+// blocks wait for each other, so all of them should be resident, beside those of the other hardware queues, of which a process has four: a
+// compute unit holds 12 such wavefronts, as blocks of one, two or four.  (Of eight it holds one block, so the line would be 512; single columns have such blocks from 640 on.)
+// A few sizes beyond would gain as well, with the device to themselves (us, forward + backward, three launches a scan / one: 1016 wavefronts
 // of 8 columns 94 / 82, 1018 of 3 86 / 77; but 1250 of 64 and of 128 columns 94 / 95 and 99 / 100), and where they don't fit at once a step takes
-// milliseconds (390000 positions of 5 columns in 763 blocks of eight: 117 us / 5.7 ms).  At the line: 160000 positions of 8 columns 84 / 69, 390000 of 1 92 / 80, 20000 of 64 65 / 57.
-constexpr int64_t kOneWaves = 768, kOneWavesFull = 512, kOneUnits = 256;
+// milliseconds (390000 positions of 5 columns in 763 blocks of eight: 117 us / 5.7 ms).  At the line: 160000 positions of 8 columns 84 / 69, 390000 of 1 92 / 80, 20000 of 64
+// 65 / 57.  The Gram form's backward with kept strict sums and one to eight columns holds 13 to 26 registers in scratch so and none with three launches, and gains all the same: its step with
+// 65536 rows, batch 8 80.5 / 66.7, batch 4 95.4 / 76.7; 30000, batch 8 76.3 / 62.7; 10^5, batch 1 75.3 / 64.7, batch 2 73.7 / 67.9; 150000, batch 3 83.2 / 73.7.
+constexpr int64_t kOneWaves = 768, kOneUnits = 256;
 
 // Compute units that a stream's workgroups may run on: the device's (a partition may have 32), less those that a mask of units takes away.
 // Where nobody says, as many as the lines were measured with.  (0.25 us; allowed while the stream is being captured.)
@@ -3925,8 +3927,7 @@ void launch_all(const ScanArgs& A, const ScanGeom& g, const std::string& tag, bo
         if constexpr (VEC == 4) with(std::integral_constant<int, kBlockWavesNarrow>{});
         else if (g.waves == 1) with(std::integral_constant<int, 1>{});
         else if (g.waves == 2) with(std::integral_constant<int, 2>{});
-        else if (g.waves == 4) with(std::integral_constant<int, 4>{});
-        else with(std::integral_constant<int, kScanWaves>{});
+        else with(std::integral_constant<int, 4>{});
         return;
     }
     if (VEC == 4 && g.sub_shift) {    // wide geometry: a workgroup per tile, a wavefront per block
@@ -4111,8 +4112,8 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
 
     A.one = OneLaunch{};      // (every block visited; no more than 32 lanes across the batch, whose other half of the exchange is taken)
     if (A.every_block && g.slabs == 1 && g.bv <= 32 && !p.inj_sorted && !p.pair_carries) {
-        const int64_t waves = g.blocks * g.waves, line = g.waves == kScanWaves ? kOneWavesFull : kOneWaves;
-        if (waves <= line && waves * kOneUnits <= line * stream_units(st)) A.one.gate = A.counters + kGateWord;
+        const int64_t waves = g.blocks * g.waves;
+        if (g.waves <= kBlockWavesNarrow && waves <= kOneWaves && waves * kOneUnits <= kOneWaves * stream_units(st)) A.one.gate = A.counters + kGateWord;
         A.one.stage_kept = p.stage != nullptr && p.stage == reinterpret_cast<float*>(ws + L.off_xs) ? 1 : 0;
     }
 
