@@ -1026,7 +1026,7 @@ static int gram_backward_impl(const float* a, int64_t n, const float* x, int64_t
         p.res_lo = 0; p.res_hi = (uint32_t)n;
         p.out_p = gx; p.ld_p = ldgx;
         p.out_red = ga; p.w = x; p.ld_w = ldx; p.zs = ga ? P.z : nullptr;
-        if (ga && gram_scans_together(L)) { p.zs = nullptr; p.pair_carries = P.z; }
+        if (ga && gram_scans_together(L)) { p.zs = nullptr; p.pair_carries = P.z; p.pair_kept = (flags & LAPLEX_SAVE_SCANS) != 0; }
         float* const pairs = reinterpret_cast<float*>(w + L.off_pair);
         const bool paired = batch == 1 && gx && ga;
         if (paired) { p.out_p = pairs; p.ld_p = 2; p.out_red = pairs + 1; p.ld_red = 2; }

@@ -59,6 +59,7 @@ constexpr int kSortSmallWords = 1088;
 // In the plan's 64 counter words: the lengths of the scans' two lists and whether a tile's sum of the scan at hand is not finite.
 constexpr int kScanCounters = 3;
 constexpr int kNonFiniteWord = 2;
+constexpr int kCarriesOddWord = 3;                      // nonzero: so it was when the kept carries of the Gram form's forward were made (scans in one launch don't say; k_scan_down_matrix looks itself too)
 constexpr int kPlanIndexWord = 33;                      // nonzero: what the common launches of a sum of operators add to the plan is there (kMixIndexed + operators)
 constexpr int kStrictOrderWord = 34;                    // nonzero: the saved strict scans lie in the sorted order (ScanProblem::z_in_order)
 constexpr int kWaitWord = 35;                           // nonzero: blocks that wait for each other's summaries poll this often, less one (tests)
@@ -480,8 +481,8 @@ struct ScanProblem {
     const float* dot_z = nullptr; float* dot_out = nullptr; const float* dot_in_order = nullptr;
     // 9 to 128 columns, every row injected and read (the Gram form): `carries` keeps the states that enter the blocks, [2][2][tiles][bpad] floats (inclusive,
     // strict), of a problem whose strict sums a later one needs (without out_p nothing else of it is wanted); pair_carries: those of the weights w, so
-    // that out_red[m] = sum_t (inj Z^w + w Z^inj)[m, t] in one walk
-    float* carries = nullptr; const float* pair_carries = nullptr;
+    // that out_red[m] = sum_t (inj Z^w + w Z^inj)[m, t] in one walk (pair_kept: an earlier call left them)
+    float* carries = nullptr; const float* pair_carries = nullptr; bool pair_kept = false;
     const char* tag;   // names the timing families: scan_reduce.<tag>, scan_spine.<tag>, scan_down.<tag>
     // batch 1, routes without random accesses: `stage` already holds the injected rows in sorted order (zero elsewhere), and
     // the outputs of result row j of the sorted sequence go to out_p[j * ld_p], out_z[j * ld_z], out_red[j * ld_red]

@@ -95,6 +95,7 @@ struct ScanArgs {
     int z_sorted;                 // out_z is indexed by the sorted row (ScanProblem::z_in_order)
     const float* dot_z; float* dot_out; const float* dot_in_order;      // row products of the reduce (ScanProblem)
     const float* pair_car_f; const float* pair_car_e;      // carries of a second matrix, x, scanned beside the injected one (k_scan_down_pair), or null
+    uint32_t carries_kept;        // all ones: they are from an earlier call, and kCarriesOddWord is about them
     int pair_redo;                // the launch of k_scan_down_pair is behind one of k_scan_down_matrix: it has work only where that found a value that is not finite
     int keep_carries;             // 1: the carries stay where l1 has them and no strict value is written; 2: and there is no downsweep
     int emit_first;               // one value per record: the first output of a row (F + R - v), else its second
@@ -1991,7 +1992,10 @@ k_scan_down(const ScanArgs A)
     Exchange& W = *reinterpret_cast<Exchange*>(smem);
     float* const ef = reinterpret_cast<float*>(smem) + (size_t)threadIdx.x * VEC;   // row i at ef[i * ef_stride]
     constexpr size_t ef_stride = (size_t)WAVES * 64 * VEC;
-    if (A.every_block && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
+    if (A.every_block && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {      // (the last kernel of the scan)
+        if (VEC == 4 && !STRICT && A.keep_carries == 1) A.counters[kCarriesOddWord] = A.counters[kNonFiniteWord];
+        A.counters[kNonFiniteWord] = 0u;
+    }
     constexpr bool SQ = STRICT || ONE == 2;           // strict sums are part of the summaries
     if (!ONE && A.down_from_list && blockIdx.x >= A.counters[1]) return;
     const int64_t tile = !ONE && A.down_from_list ? A.list_both[blockIdx.x] : blockIdx.x;     // the block this workgroup owns
@@ -2342,18 +2346,24 @@ struct PairSegs {
 // REDO: the launch behind k_scan_down_matrix, of a few workgroups that take block after block.
 template <bool RAG, bool REDO>
 __global__ void __launch_bounds__(kPairWaves * 64, 4)
-k_scan_down_pair(const ScanArgs A)
+k_scan_down_pair(const ScanArgs args)
 {
+    typedef const ScanArgs __attribute__((address_space(4))) ConstantArgs;
+    ConstantArgs* here = (ConstantArgs*)__builtin_amdgcn_kernarg_segment_ptr();          // (where `args` lies)
     constexpr int ITEMS = kPairItems, WAVES = kPairWaves, THREADS = WAVES * 64, VEC = 4;
     __shared__ float4 zx_all[ITEMS * THREADS], ef_all[ITEMS * THREADS];
     static_assert(sizeof(PairSegs) <= sizeof(ef_all), "the exchange of wavefront summaries lies where gy's strict forward values are written later");
     PairSegs& W = *reinterpret_cast<PairSegs*>(ef_all);
-    float4* const zx = zx_all + threadIdx.x;          // the strict scans of x, row i at zx[i * THREADS]
-    float4* const ef = ef_all + threadIdx.x;
-    if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
-    if (REDO && A.counters[kPairRedoWord] == 0u) return;                           // uniform: k_scan_down_matrix has done it all
+    float4* zx = zx_all + threadIdx.x;          // the strict scans of x, row i at zx[i * THREADS]
+    float4* ef = ef_all + threadIdx.x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) args.counters[kNonFiniteWord] = 0u;      // (the last kernel of the scan)
+    if (REDO && args.counters[kPairRedoWord] == 0u) return;                           // uniform: k_scan_down_matrix has done it all
     for (int64_t tile = blockIdx.x;;) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tid = threadIdx.x;
+    if (REDO) { asm volatile("" : "+v"(tid)); asm volatile("" : "+s"(here)); }      // (nothing made of them is kept from one block for the next: 20 registers went to scratch, now 2)
+    const ScanArgs& A = REDO ? *(const ScanArgs*)here : args;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (REDO) { zx = zx_all + tid; ef = ef_all + tid; }
     const int bv = A.bv, rv = A.rv;
     const int c = lane & (bv - 1), r = lane >> A.bv_log2;
     const int64_t wave_row0 = tile * A.tile_rows + (int64_t)(wave * rv) * ITEMS;
@@ -2534,6 +2544,13 @@ k_scan_down_matrix(const ScanArgs A)
     __shared__ float4 sums[2][4][WAVES][16];               // of x and of gy: forward, backward, strict, per wavefront and column group
     __shared__ float decay[WAVES][2][WAVES];               // to the wavefront from before and after: kSame for rows that end at its edge's key, 0 for none
     constexpr float kSame = 2.0f;
+    // A value known not to be finite, from gy's reduce or x's: all is left to the launch behind this one.  (3 x 2^20 rows, batch 64, forward and backward with such
+    // a value: 1586 us, and 2127 where this kernel first runs to its end; 300001 rows 240 and 299.  Looking costs calls without one 0.3 % and 0.9 %; a return between the loads, or no row
+    // read or written in place of a return, cost no less.)
+    if ((A.counters[kNonFiniteWord] | (A.counters[kCarriesOddWord] & A.carries_kept)) != 0u) {          // uniform over the launch
+        if (blockIdx.x == 0 && threadIdx.x == 0) A.counters[kPairRedoWord] = 1u;
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, r = lane >> 4;
     const int64_t tile = blockIdx.x, tile_base = tile * A.tile_rows, N = A.N;
@@ -4075,6 +4092,7 @@ hipError_t launch_scan(const ScanProblem& p, const Layout& L, char* ws, hipStrea
     A.keep_carries = p.carries ? (p.out_p ? 1 : 2) : 0;
     if (p.carries) { A.l1.car_f = p.carries; A.l1.car_e = p.carries + 2 * g.tiles * L.bpad; }
     A.pair_car_f = p.pair_carries;
+    A.carries_kept = p.pair_kept ? 0xFFFFFFFFu : 0u;
     A.pair_redo = p.pair_carries && g.vec == 4 && g.bv == 16 && g.tile_rows == kPairWaves * kMatrixRows ? 1 : 0;
     A.pair_car_e = p.pair_carries ? p.pair_carries + 2 * g.tiles * L.bpad : nullptr;
     if ((p.carries || p.pair_carries) && (g.vec != 4 || g.sub_shift || g.slabs != 1 || p.stage)) return hipErrorInvalidValue;

@@ -221,3 +221,33 @@ def test_mix_non_finite_rows_reach_every_row(r, k, n, batch, bad):
             assert_all_non_finite("gx", gx, col)
             for v in gb:
                 assert_all_non_finite("gb", v)
+
+
+@pytest.mark.parametrize("n,batch", [(9001, 64), (60000, 33), (150001, 64)])
+def test_gram_steps_with_and_without_non_finite_rows_on_one_plan(n, batch):
+    """What a step with a value that is not finite leaves in the plan changes no later step; forward and backward, and the backward alone."""
+    q = np.random.default_rng(n + batch)
+    a, x, g = (dev(v.astype(np.float32)) for v in (q.uniform(0, 3000, n), q.normal(size=(n, batch)), q.normal(size=(n, batch))))
+    ws = torch.empty(B.laplex_workspace_bytes(0, n, batch), dtype=torch.uint8, device="cuda")
+
+    def step(flags, x, g, forward):
+        y, gx, ga = torch.zeros_like(g), torch.zeros_like(x), torch.zeros_like(a)
+        if forward:
+            B.laplex_gram(a, x, y, ws, flags | B.LAPLEX_SAVE_SCANS)
+        B.laplex_gram_backward(a, x, g, gx, ga, ws, B.LAPLEX_REUSE_PLAN | (B.LAPLEX_SAVE_SCANS if forward else 0))
+        torch.cuda.synchronize()
+        return y, gx, ga
+    xn, gn = x.clone(), g.clone()
+    xn[n // 3, batch // 2] = float("nan")
+    gn[n // 5, batch // 3] = float("inf")
+    want = step(0, x, g, True)
+    alone = step(B.LAPLEX_REUSE_PLAN, x, g, False)
+    for xs, gs in ((xn, g), (x, gn), (xn, gn)):
+        for forward in (True, False):
+            y, gx, ga = step(B.LAPLEX_REUSE_PLAN, xs, gs, forward)
+            assert_all_non_finite("ga", ga)
+            if gs is gn:
+                assert_all_non_finite("gx", gx, batch // 3)
+            assert bool(torch.isfinite(gx[:, 0]).all())
+            for again, first in ((True, want), (False, alone), (True, want)):
+                assert all(torch.equal(v, w) for v, w in zip(step(B.LAPLEX_REUSE_PLAN, x, g, again)[0 if again else 1:], first[0 if again else 1:]))
