@@ -289,8 +289,8 @@ def paper_sweep(args, torch, np, B, synth):
 
 KERNEL_OF = {
     "scan_down_sparse.bwd": "k_scan_down_sparse_wide<true> (backward downsweep: reads x, writes gx and gb)",
-    "scan_reduce.fwd": "forward reduce (reads the injected rows of x once for both directions)",
-    "scan_reduce.bwd": "backward reduce (reads the injected rows of gy once for both directions)",
+    "scan_reduce.fwd": "forward reduce (reads the injected rows of x once for both directions); up to 768 wavefronts the whole scan, k_scan_down in one launch",
+    "scan_reduce.bwd": "backward reduce (reads the injected rows of gy once for both directions); up to 768 wavefronts the whole scan, k_scan_down in one launch",
     "scan_down.fwd": "k_scan_down, forward problem (reads x, writes y and, but for the square form, the saved scans)",
     "scan_down.bwd": "backward downsweep (k_scan_down: reads gy, x and, for the square form at batch 1 to 8, the saved scans; k_scan_down_matrix and k_scan_down_pair: gy and x; writes gx and the anchor gradient)",
     "radix_scatter": "k_onesweep_pass (one radix pass: reads the pairs once, writes them once)",
@@ -440,8 +440,16 @@ def measure(spec, steps, warmup, torch, np, B):
 
     ms_per_step = (t1 - t0) * 1e3 / steps
     elements = N * batch
+    # the Gram form's backward with 33 to 64 columns: behind the downsweep a launch of the same family that returns at once where all
+    # values are finite (4 to 5 us); it is part of the family's time, not a launch to average over
+    idle = steps if dominant == "scan_down.bwd" and spec["gram"] and 33 <= batch <= 64 else 0
+    dom_launches -= idle
     per_step_launches = dom_launches / steps
     fam_bytes, note = family_bytes(dominant, spec, np, B)
+    if dominant.startswith("scan_reduce.") and dominant.replace("reduce", "spine") not in families:
+        fam_bytes, note = None, "a scan in one launch: not counted"
+    elif idle:
+        note += "; a launch behind it that returns at once is in the time"
     dom_ms_per_step = dom_ms / steps
     roofline = {"bound": "hbm", "kernel": KERNEL_OF.get(dominant, dominant), "family": dominant,
                 "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None, "traffic": None,
