@@ -1677,7 +1677,7 @@ __device__ __forceinline__ void load_block_carries(const ScanArgs& A, int64_t bl
 // direct spine would leave), so that the injected rows are read once and nothing is launched in between.
 //
 // Bound by latency: a step of 2^16 x 2^16 at batch 8 takes 66 us so, 82 with three launches a scan, each of which waited for the ids, the rows
-// and the anchors anew (11 + 6 + 11 and 14 + 6 + 13 us beside some 3 between them; now 18 and 21: rows there after 4 us, summaries
+// and the anchors anew (11 + 6 + 11 and 14 + 6 + 13 us beside some 3 between them; now 20 and 24: rows there after 4 us, summaries
 // after 8, published after 11, the others' added up after 15).  12000 to 160000 positions at batch 1, 3, 8, 16: 9 to 15 us less a step.
 //
 // What one workgroup writes for another to read in the same launch goes through relaxed agent-scope atomics, which pass by the chiplets'
