@@ -18,7 +18,8 @@
  *  - Calls only enqueue work on `stream`; they never synchronise, allocate or
  *    free.  Two calls that share a workspace must be ordered by the caller
  *    (same stream, or events).
- *  - The same call gives the same bits whatever else the device is doing.  On a stream with
+ *  - The same call gives the same bits whatever else the device is doing (unless its
+ *    plan comes out invalid, see laplex_get_plan_status).  On a stream with
  *    fewer compute units (a mask of units, a partition of the device) values may differ
  *    from those of the whole device in rounding: how many there are decides how
  *    some scans are launched.
